@@ -15,7 +15,7 @@
  *    tables themselves (arrays of condensa_tensor, arrays of pointers, arrays of densities) are
  *    HOST memory; they are consumed before the call returns and may be freed right after.
  *  - The caller owns all memory, including the workspace.  The library allocates no device
- *    memory and frees none.  (It keeps a small pinned host staging ring for the tables.)
+ *    memory and frees none.  (It keeps a small pool of pinned host memory for the tables.)
  *  - All device work is enqueued on `stream` (a hipStream_t, NULL = the default stream) and the
  *    call returns without waiting.  Results, including condensa_select records, are in device
  *    memory once the stream has reached that point.

@@ -1,6 +1,8 @@
 // C-ABI entry points of the compression-step library (see include/condensa.h): argument checks,
 // table building, workspace carving and the kernel launch sequences.
+#include <chrono>
 #include <memory>
+#include <thread>
 
 #include "host.h"
 #include "k_apply.h"
@@ -60,44 +62,83 @@ condensa_status resolve_config(const condensa_config* c, Config* out) {
     return CONDENSA_OK;
 }
 
-// ---- pinned staging ring -------------------------------------------------------------------------
+// ---- pinned staging slots --------------------------------------------------------------------------
 
 namespace {
+// The slots' words and their first kStageBytes each are one pinned block, allocated on the first call; a larger image
+// gets a buffer of its own, which stays with the slot.  A slot is free when it is not being filled and the device
+// has stored the ticket of its last use.
+constexpr int kStageSlots = 32;
+constexpr size_t kStageBytes = 64u << 10;
+constexpr unsigned kStageFlags = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
 struct Stage {
-    void* host = nullptr;
-    size_t cap = 0;
-    hipEvent_t ev = nullptr;
-    bool pending = false;
+    char* big = nullptr;
+    size_t big_cap = 0;
+    u64 ticket = 0;
+    bool filling = false;
 };
-constexpr int kRing = 8;
-Stage g_ring[kRing];
-int g_ring_next = 0;
-std::mutex g_ring_mu;
+Stage g_stage[kStageSlots];
+char* g_stage_block = nullptr;                // [kStageSlots] words of 64 bytes, then [kStageSlots] images
+int g_stage_next = 0;
+std::mutex g_stage_mu;
+
+u64* stage_done(int i) { return reinterpret_cast<u64*>(g_stage_block + static_cast<size_t>(i) * 64); }
 }  // namespace
 
-condensa_status stage_upload(void* dst_dev, const void* src_host, size_t bytes, hipStream_t stream) {
-    if (bytes == 0) return CONDENSA_OK;
-    std::lock_guard<std::mutex> lock(g_ring_mu);
-    Stage& s = g_ring[g_ring_next];
-    g_ring_next = (g_ring_next + 1) % kRing;
-    if (s.pending) {
-        CONDENSA_HIP(hipEventSynchronize(s.ev));
-        s.pending = false;
+condensa_status StageImage::acquire(size_t bytes, hipStream_t stream) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
+    std::unique_lock<std::mutex> lock(g_stage_mu);
+    if (g_stage_block == nullptr) {
+        void* p = nullptr;
+        CONDENSA_HIP(hipHostMalloc(&p, kStageSlots * (64 + kStageBytes), kStageFlags));
+        std::memset(p, 0, kStageSlots * 64);
+        g_stage_block = static_cast<char*>(p);
     }
-    if (s.cap < bytes) {
-        if (s.host) CONDENSA_HIP(hipHostFree(s.host));
-        s.host = nullptr;
-        s.cap = 0;
-        const size_t cap = align_up(bytes < (64u << 10) ? (64u << 10) : bytes, 4096);
-        CONDENSA_HIP(hipHostMalloc(&s.host, cap, hipHostMallocDefault));
-        s.cap = cap;
+    int found = -1;
+    for (int tries = 0; found < 0; ++tries) {
+        for (int k = 0; k < kStageSlots && found < 0; ++k) {
+            const int i = (g_stage_next + k) % kStageSlots;
+            if (!g_stage[i].filling && __atomic_load_n(stage_done(i), __ATOMIC_ACQUIRE) == g_stage[i].ticket) found = i;
+        }
+        if (found < 0) {                      // every slot is in flight: the call waits for the device to catch up
+            lock.unlock();
+            if (tries < 2000) std::this_thread::yield();
+            else std::this_thread::sleep_for(std::chrono::microseconds(20));
+            lock.lock();
+        }
     }
-    if (!s.ev) CONDENSA_HIP(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
-    std::memcpy(s.host, src_host, bytes);
-    CONDENSA_HIP(hipMemcpyAsync(dst_dev, s.host, bytes, hipMemcpyHostToDevice, stream));
-    CONDENSA_HIP(hipEventRecord(s.ev, stream));
-    s.pending = true;
+    Stage& s = g_stage[found];
+    if (bytes > kStageBytes && s.big_cap < bytes) {
+        if (s.big) CONDENSA_HIP(hipHostFree(s.big));
+        s.big = nullptr;
+        s.big_cap = 0;
+        void* p = nullptr;
+        CONDENSA_HIP(hipHostMalloc(&p, align_up(bytes, 4096), kStageFlags));
+        s.big = static_cast<char*>(p);
+        s.big_cap = align_up(bytes, 4096);
+    }
+    g_stage_next = (found + 1) % kStageSlots;
+    s.filling = true;
+    slot_ = found;
+    data_ = bytes > kStageBytes ? s.big : g_stage_block + kStageSlots * 64 + static_cast<size_t>(found) * kStageBytes;
+    done_ = capture == hipStreamCaptureStatusNone ? stage_done(found) : nullptr;
+    ticket_ = s.ticket + 1;
     return CONDENSA_OK;
+}
+
+void StageImage::commit() {
+    if (slot_ < 0) return;
+    std::lock_guard<std::mutex> lock(g_stage_mu);
+    g_stage[slot_].filling = false;
+    if (done_) g_stage[slot_].ticket = ticket_;
+    slot_ = -1;
+}
+
+StageImage::~StageImage() {                   // not committed: nothing on the device refers to the slot
+    if (slot_ < 0) return;
+    std::lock_guard<std::mutex> lock(g_stage_mu);
+    g_stage[slot_].filling = false;
 }
 
 // ---- phase timing ----------------------------------------------------------------------------------
@@ -379,6 +420,76 @@ static unsigned fill_grid(u64 words) {
     return static_cast<unsigned>(b);
 }
 
+static condensa_status poke_upload(void* dst_dev, const char* src_host, size_t bytes, hipStream_t st);
+
+// What every call starts with: the tables [tensors | outputs | rankings] reach the front of the workspace, the
+// counter and histogram region is cleared and the chunk -> tensor map is written.  One launch while the tables are
+// small (kBeginTensors tensors, one staging slot), two beyond that.  `fixed`: for callers that cannot allocate, the
+// memory to build the tables' image in; they then travel as kernel arguments.
+static condensa_status begin_call(const Layout& L, const Tables& tb, int n_tensors, const OutDesc* out, size_t n_out,
+                                  const Slot* slots, size_t n_slots, void* ws, hipStream_t st, char* fixed = nullptr) {
+    const size_t td_bytes = static_cast<size_t>(tb.n_td) * sizeof(TensorDesc), out_bytes = n_out * sizeof(OutDesc),
+                 slot_bytes = n_slots * sizeof(Slot);
+    const u64 n_words = L.zero_bytes / 8;
+    auto fill = [&](char* td_at, char* out_at, char* slots_at) {
+        std::memcpy(td_at, tb.td, td_bytes);
+        if (out_bytes) std::memcpy(out_at, out, out_bytes);
+        if (slot_bytes) std::memcpy(slots_at, slots, slot_bytes);
+    };
+    if (fixed) {
+        fill(fixed + L.td, fixed + L.out, fixed + L.slots);
+        const condensa_status rc = poke_upload(ws, fixed, L.upload_bytes, st);
+        if (rc != CONDENSA_OK) return rc;
+        hipLaunchKernelGGL(k_prepare, dim3(fill_grid(n_words)), dim3(kBlock), 0, st, at<u64>(ws, L.zero_begin), n_words,
+                           at<TensorDesc>(ws, L.td), n_tensors, at<u32>(ws, L.chunk_map), tb.n_chunks,
+                           static_cast<u64*>(nullptr), static_cast<u64>(0));
+        CONDENSA_LAUNCH_CHECK();
+        return CONDENSA_OK;
+    }
+    StageImage img;
+    const condensa_status rc = img.acquire(td_bytes + out_bytes + slot_bytes, st);      // each a multiple of 32 bytes
+    if (rc != CONDENSA_OK) return rc;
+    fill(img.data(), img.data() + td_bytes, img.data() + td_bytes + out_bytes);
+    UploadArgs up{};
+    up.src = reinterpret_cast<const uint4*>(img.data());
+    up.dst[0] = at<uint4>(ws, L.td); up.dst[1] = at<uint4>(ws, L.out); up.dst[2] = at<uint4>(ws, L.slots);
+    up.end[0] = static_cast<u32>(td_bytes / 16);
+    up.end[1] = up.end[0] + static_cast<u32>(out_bytes / 16);
+    up.end[2] = up.end[1] + static_cast<u32>(slot_bytes / 16);
+    up.done = img.done();
+    up.ticket = img.ticket();
+    if (n_tensors <= kBeginTensors && td_bytes + out_bytes + slot_bytes <= kStageBytes) {
+        BeginArgs b{};
+        b.up = up;
+        b.zero = at<uint4>(ws, L.zero_begin);
+        b.n_zero = L.zero_bytes / 16;
+        b.chunk_map = at<u32>(ws, L.chunk_map);
+        b.n_chunks = static_cast<u32>(tb.n_chunks);
+        b.n_tensors = n_tensors;
+        for (int t = 0; t <= n_tensors; ++t) b.chunk_start[t] = static_cast<u32>(tb.td[t].chunk_start);
+        u64 blocks = (b.n_zero + 2 * kBeginThreads - 1) / (2 * kBeginThreads);
+        const u64 map_blocks = (tb.n_chunks + 2 * kBeginThreads - 1) / (2 * kBeginThreads);
+        if (blocks < map_blocks) blocks = map_blocks;
+        blocks = (blocks > 512 ? 512 : blocks) + 1;
+        hipLaunchKernelGGL(k_begin, dim3(static_cast<unsigned>(blocks)), dim3(kBeginThreads), 0, st, b);
+        CONDENSA_LAUNCH_CHECK();
+        img.commit();
+        return CONDENSA_OK;
+    }
+    const u32 up_blocks = (up.end[2] + 4 * kBlock - 1) / (4 * kBlock);
+    hipLaunchKernelGGL(k_upload, dim3(up_blocks ? up_blocks : 1), dim3(kBlock), 0, st, up);
+    CONDENSA_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_prepare, dim3(fill_grid(n_words)), dim3(kBlock), 0, st, at<u64>(ws, L.zero_begin), n_words,
+                       at<TensorDesc>(ws, L.td), n_tensors, at<u32>(ws, L.chunk_map), tb.n_chunks, img.done(), img.ticket());
+    // the upload is in the stream: were this launch to fail, its slot could not be handed out before the upload has run
+    const hipError_t launched = hipGetLastError();
+    if (launched != hipSuccess) (void)hipStreamSynchronize(st);
+    else img.commit();
+    g_launches.fetch_add(1, std::memory_order_relaxed);
+    CONDENSA_HIP(launched);
+    return CONDENSA_OK;
+}
+
 // Radix levels over the weights: 3 x (histogram sweep + bin search).
 template <bool LC, bool VEC>
 static condensa_status launch_radix_levels(const DataArgs& a, int n_slots, hipStream_t st, const Config& cfg,
@@ -585,8 +696,8 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
 
     const bool window = !no_alloc && want_window(tb.N, per_tensor, J, false, cfg);
     Slot* slots = arena.array<Slot>(static_cast<size_t>(L.n_slots) + 3);
-    char* up = arena.array<char>(L.upload_bytes);
-    if (!slots || !up) return CONDENSA_ERR_SIZE;
+    char* fixed = no_alloc ? arena.array<char>(L.upload_bytes) : nullptr;
+    if (!slots || (no_alloc && !fixed)) return CONDENSA_ERR_SIZE;
     for (int g = 0; g < L.n_groups; ++g)
         for (int j = 0; j < J; ++j) {
             const u64 n = per_tensor ? tb.td[g].n : tb.N;
@@ -595,17 +706,9 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
     const size_t n_up_slots = static_cast<size_t>(L.n_slots) + ((window && J == 1) ? 3 : 0);
     if (window && J == 1) init_sample_slots(slots + L.n_slots, slots[0], cfg[CONDENSA_OPT_WINDOW_MARGIN]);
 
-    // one upload: [tensor table | output table | rankings]
-    std::memcpy(up + L.td, tb.td, static_cast<size_t>(tb.n_td) * sizeof(TensorDesc));
-    std::memcpy(up + L.out, out, n_out * sizeof(OutDesc));
-    std::memcpy(up + L.slots, slots, n_up_slots * sizeof(Slot));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = no_alloc ? poke_upload(workspace_dev, up, L.upload_bytes, st) : stage_upload(workspace_dev, up, L.upload_bytes, st);
+    rc = begin_call(L, tb, n_tensors, out, n_out, slots, n_up_slots, workspace_dev, st, fixed);
     if (rc != CONDENSA_OK) return rc;
-    hipLaunchKernelGGL(k_prepare, dim3(fill_grid(L.zero_bytes / 8)), dim3(kBlock), 0, st,
-                       at<u64>(workspace_dev, L.zero_begin), static_cast<u64>(L.zero_bytes / 8),
-                       at<TensorDesc>(workspace_dev, L.td), n_tensors, at<u32>(workspace_dev, L.chunk_map), tb.n_chunks);
-    CONDENSA_LAUNCH_CHECK();
 
     DataArgs a{};
     a.td = at<TensorDesc>(workspace_dev, L.td);
@@ -811,17 +914,9 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
     init_slot(&slot, tb.N, kept_count(density, tb.N), window ? 2u : 1u);
     if (window) init_sample_slots(slot4 + 1, slot, cfg[CONDENSA_OPT_WINDOW_MARGIN]);
 
-    std::vector<char> up(L.upload_bytes, 0);
-    std::memcpy(up.data() + L.td, tb.td, static_cast<size_t>(tb.n_td) * sizeof(TensorDesc));
-    std::memcpy(up.data() + L.out, out.data(), out.size() * sizeof(OutDesc));
-    std::memcpy(up.data() + L.slots, slot4, (window ? 4 : 1) * sizeof(Slot));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = stage_upload(workspace_dev, up.data(), L.upload_bytes, st);
+    rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slot4, window ? 4 : 1, workspace_dev, st);
     if (rc != CONDENSA_OK) return rc;
-    hipLaunchKernelGGL(k_prepare, dim3(fill_grid(L.zero_bytes / 8)), dim3(kBlock), 0, st,
-                       at<u64>(workspace_dev, L.zero_begin), static_cast<u64>(L.zero_bytes / 8),
-                       at<TensorDesc>(workspace_dev, L.td), n_tensors, at<u32>(workspace_dev, L.chunk_map), tb.n_chunks);
-    CONDENSA_LAUNCH_CHECK();
 
     DataArgs a{};
     a.td = at<TensorDesc>(workspace_dev, L.td);
@@ -949,15 +1044,10 @@ condensa_status condensa_count_nonzero(const condensa_tensor* tensors, int n_ten
     ranges.push_back(byte_range(workspace_dev, workspace_bytes < L.total ? workspace_bytes : L.total, true));
     ranges.push_back(byte_range(count_dev, sizeof(uint64_t), true));
     if (ranges_conflict(ranges.data(), ranges.size())) return CONDENSA_ERR_ARG;
-    std::vector<char> up(L.upload_bytes, 0);
-    std::memcpy(up.data() + L.td, tb.td, static_cast<size_t>(tb.n_td) * sizeof(TensorDesc));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = stage_upload(workspace_dev, up.data(), L.upload_bytes, st);
+    rc = begin_call(L, tb, n_tensors, nullptr, 0, nullptr, 0, workspace_dev, st);
     if (rc != CONDENSA_OK) return rc;
-    hipLaunchKernelGGL(k_prepare, dim3(fill_grid(L.zero_bytes / 8)), dim3(kBlock), 0, st,
-                       at<u64>(workspace_dev, L.zero_begin), static_cast<u64>(L.zero_bytes / 8),
-                       at<TensorDesc>(workspace_dev, L.td), n_tensors, at<u32>(workspace_dev, L.chunk_map), tb.n_chunks);
-    CONDENSA_LAUNCH_CHECK();
+
     DataArgs a{};
     a.td = at<TensorDesc>(workspace_dev, L.td);
     a.chunk_map = at<u32>(workspace_dev, L.chunk_map);
@@ -1047,17 +1137,9 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
         init_sample_slots(&slots[L.n_slots], slots[0], cfg[CONDENSA_OPT_WINDOW_MARGIN]);
         slots[0].path = 2;
     }
-    std::vector<char> up(L.upload_bytes, 0);
-    std::memcpy(up.data() + L.td, tb.td, static_cast<size_t>(tb.n_td) * sizeof(TensorDesc));
-    std::memcpy(up.data() + L.out, out.data(), out.size() * sizeof(OutDesc));
-    std::memcpy(up.data() + L.slots, slots.data(), (static_cast<size_t>(L.n_slots) + (fused ? 3 : 0)) * sizeof(Slot));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = stage_upload(workspace_dev, up.data(), L.upload_bytes, st);
+    rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slots.data(), static_cast<size_t>(L.n_slots) + (fused ? 3 : 0), workspace_dev, st);
     if (rc != CONDENSA_OK) return rc;
-    hipLaunchKernelGGL(k_prepare, dim3(fill_grid(L.zero_bytes / 8)), dim3(kBlock), 0, st,
-                       at<u64>(workspace_dev, L.zero_begin), static_cast<u64>(L.zero_bytes / 8),
-                       at<TensorDesc>(workspace_dev, L.td), n_tensors, at<u32>(workspace_dev, L.chunk_map), tb.n_chunks);
-    CONDENSA_LAUNCH_CHECK();
 
     StructArgs a{};
     a.td = at<TensorDesc>(workspace_dev, L.td);
@@ -1557,16 +1639,10 @@ condensa_status condensa_lc_sgd_step(const condensa_tensor* tensors, int n_tenso
     if (ranges_conflict(ranges.data(), ranges.size())) return CONDENSA_ERR_ARG;
     rc = check_workspace(workspace_dev, workspace_bytes, L);
     if (rc != CONDENSA_OK) return rc;
-    std::vector<char> up(L.upload_bytes, 0);
-    std::memcpy(up.data() + L.td, tb.td, static_cast<size_t>(tb.n_td) * sizeof(TensorDesc));
-    std::memcpy(up.data() + L.out, out.data(), out.size() * sizeof(OutDesc));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = stage_upload(workspace_dev, up.data(), L.upload_bytes, st);
+    rc = begin_call(L, tb, n_tensors, out.data(), out.size(), nullptr, 0, workspace_dev, st);
     if (rc != CONDENSA_OK) return rc;
-    hipLaunchKernelGGL(k_prepare, dim3(fill_grid(L.zero_bytes / 8)), dim3(kBlock), 0, st,
-                       at<u64>(workspace_dev, L.zero_begin), static_cast<u64>(L.zero_bytes / 8),
-                       at<TensorDesc>(workspace_dev, L.td), n_tensors, at<u32>(workspace_dev, L.chunk_map), tb.n_chunks);
-    CONDENSA_LAUNCH_CHECK();
+
     if (tb.n_chunks == 0) return CONDENSA_OK;
     DataArgs a{};
     a.td = at<TensorDesc>(workspace_dev, L.td);

@@ -204,13 +204,89 @@ __device__ inline SlotStep wave_enter_level(const Slot& s, int L, int key_bits, 
     return cur;
 }
 
-// First kernel of every call: clears the flag / counter / histogram region and writes the
-// chunk -> tensor map (a kernel rather than a memset: memset nodes do not belong in work that a caller may
-// capture in a graph, as the caller of the allocation-free entry point may).
+// ---- what every call starts with -----------------------------------------------------------------
+//
+// The tables of a call lie in pinned host memory (StageImage) and are fetched over the host link by the kernel that
+// begins the call; the last thing that kernel does with the image is to store its ticket, which frees the slot.
+struct UploadArgs {
+    const uint4* src;      // pinned image: tensor table, output table, rankings, one after the other
+    uint4* dst[3];         // where each goes
+    u32 end[3];            // 16-byte words up to the end of each
+    u64* done;             // pinned: receives ticket (NULL: nothing)
+    u64 ticket;
+};
+__device__ inline void upload_words(const UploadArgs& u, u32 first, u32 stride) {
+    for (u32 i0 = first; i0 < u.end[2]; i0 += 4 * stride) {          // four loads in flight: a round trip is about a microsecond
+        uint4 v[4];
+#pragma unroll
+        for (u32 k = 0; k < 4; ++k) if (i0 + k * stride < u.end[2]) v[k] = u.src[i0 + k * stride];
+#pragma unroll
+        for (u32 k = 0; k < 4; ++k) {
+            const u32 i = i0 + k * stride;
+            if (i >= u.end[2]) break;
+            const int part = i < u.end[0] ? 0 : (i < u.end[1] ? 1 : 2);
+            u.dst[part][i - (part ? u.end[part - 1] : 0)] = v[k];
+        }
+    }
+}
+__device__ inline void store_ticket(u64* done, u64 ticket) {
+    if (done) __hip_atomic_store(done, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The one launch that begins a call with few tensors: workgroup 0 fetches the tables, the others clear the flag /
+// counter / histogram region and write the chunk -> tensor map (a kernel rather than a memset: memset nodes do not
+// belong in work that a caller may capture in a graph).  The map needs the tensors' first chunks only; they come as
+// kernel arguments, so no workgroup but the first touches the host link.
+// Bound by latency: a launch, a round trip or two over the link, a few MB of stores.  Upload and preparation of the
+// 17-tensor L-C step: a blit of 4.0 us and a kernel of 5.0 before, 5.2 now; of 96 tensors: a DMA copy (30 us and more)
+// and 5.8 us before, 5.4 now (10.9 with 256 threads: the link wants every load of the image in flight at once).
+constexpr int kBeginThreads = 1024;
+constexpr int kBeginTensors = 256;
+struct BeginArgs {
+    UploadArgs up;
+    uint4* zero;
+    u64 n_zero;            // 16-byte words
+    u32* chunk_map;
+    u32 n_chunks;
+    int n_tensors;
+    u32 chunk_start[kBeginTensors + 1];
+};
+static_assert(sizeof(BeginArgs) <= 3584, "kernel arguments");
+__global__ __launch_bounds__(kBeginThreads) void k_begin(BeginArgs b) {
+    __shared__ u32 s_start[kBeginTensors + 1];
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0) {
+        upload_words(b.up, tid, kBeginThreads);
+        __syncthreads();                   // every load has returned: its value went into a store
+        if (tid == 0) store_ticket(b.up.done, b.up.ticket);
+        return;
+    }
+    for (int t = tid; t <= b.n_tensors; t += kBeginThreads) s_start[t] = b.chunk_start[t];
+    __syncthreads();
+    const u64 stride = static_cast<u64>(gridDim.x - 1) * kBeginThreads;
+    const u64 i0 = static_cast<u64>(blockIdx.x - 1) * kBeginThreads + tid;
+    const uint4 z = make_uint4(0, 0, 0, 0);
+    for (u64 i = i0; i < b.n_zero; i += stride) b.zero[i] = z;
+    for (u64 c = i0; c < b.n_chunks; c += stride) {
+        int lo = 0, hi = b.n_tensors - 1;
+        while (lo < hi) {                  // largest t with chunk_start[t] <= c
+            const int mid = (lo + hi + 1) >> 1;
+            if (s_start[mid] <= c) lo = mid; else hi = mid - 1;
+        }
+        b.chunk_map[c] = static_cast<u32>(lo);
+    }
+}
+
+// Many tensors (or tables beyond one staging slot): the upload, then the clearing and the map as a second launch,
+// which also frees the slot -- it starts when the upload has ended.  The entry point for callers that cannot
+// allocate brings its tables as kernel arguments (k_poke) and uses the second part only.
+__global__ __launch_bounds__(kBlock) void k_upload(UploadArgs u) { upload_words(u, blockIdx.x * kBlock + threadIdx.x, gridDim.x * kBlock); }
+
 __global__ __launch_bounds__(kBlock) void k_prepare(u64* zero, u64 n_words, const TensorDesc* td, int n_tensors,
-                                                    u32* chunk_map, u64 n_chunks) {
+                                                    u32* chunk_map, u64 n_chunks, u64* done, u64 ticket) {
     const u64 stride = static_cast<u64>(gridDim.x) * kBlock;
     const u64 i0 = static_cast<u64>(blockIdx.x) * kBlock + threadIdx.x;
+    if (i0 == 0) store_ticket(done, ticket);
     for (u64 i = i0; i < n_words; i += stride) zero[i] = 0;
     for (u64 c = i0; c < n_chunks; c += stride) chunk_map[c] = static_cast<u32>(tensor_of_chunk(td, n_tensors, c));
 }
