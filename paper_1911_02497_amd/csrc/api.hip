@@ -9,7 +9,7 @@
 #include "k_quantize.h"
 #include "k_fused.h"
 #include "k_select.h"
-#include "k_small.h"
+#include "k_listed.h"
 #include "k_structure.h"
 #include "k_window.h"
 #include "k_struct_fused.h"
@@ -221,6 +221,61 @@ static u64 window_cand_capacity(u64 N, int J, const Config& cfg) {
     return c;
 }
 
+// Which selection a call takes.  GLOBAL scope: sampled window or radix levels?  Measured (one MI355X, 2^24..2^30
+// weights, 1/4/10 densities): the radix levels cost three sweeps whatever the number of densities and ~50 us of
+// fixed work; the window path costs one sweep, ~0.2 ms of small kernels, and candidate lists and a sweep that grow
+// with the number of densities.  One density breaks even near 2^26 element reads, four near 2^27.5, ten near 2^30.
+static bool want_window(u64 N, bool per_tensor, int J, bool lc, const Config& cfg) {
+    if (per_tensor) return false;
+    if ((N >> kCandTensorShift) != 0) return false;        // candidates carry their tensor above a 44-bit flat index
+    const int64_t mode = cfg[CONDENSA_OPT_SELECT_PATH];
+    if (mode == 1) return false;
+    if (mode == 2) return N >= 1;
+    u64 need = static_cast<u64>(J) << 26;
+    if (J > 4) need = need * static_cast<u64>(J) / 4;
+    return N * (lc ? 2u : 1u) >= need;
+}
+
+// On the automatic path the calls below the window path's sizes, and those of PER_TENSOR scope, take the listed
+// windows (k_listed.h), whose lists hold 32-bit indices.
+static bool want_list(u64 N, int n_tensors, int n_slots, bool per_tensor, int J, bool lc, const Config& cfg) {
+    if (cfg[CONDENSA_OPT_SELECT_PATH] != 0 || N == 0) return false;
+    if (N + static_cast<u64>(n_tensors) * kChunk >= (static_cast<u64>(1) << 32)) return false;
+    if (n_slots > kListMaxRankings) return false;
+    return per_tensor || !want_window(N, per_tensor, J, lc, cfg);
+}
+
+// Segments of the rankings' lists: what their sweep's wavefronts call for (elements per wavefront).
+static u64 list_wave_elems(int J, bool lc) { return 256u * static_cast<u64>(J > 1 ? kListMultiQuads : (lc ? kFusedQuadsLC : kFusedQuadsPrune)); }
+static u32 list_max_segs(u64 n, int n_slots, int J, bool lc) {
+    u32 most = J > 1 ? 256u : static_cast<u32>(kListSegs);
+    while (most > 16 && static_cast<u64>(most) * n_slots > (1u << 16)) most /= 2;        // many rankings share the atomics' rate
+    return list_segments(n, list_wave_elems(J, lc), most);
+}
+// List entries of one ranking, a multiple of kListRow n_segs; and the most that the rankings of one density can add up
+// to when the tensors' sizes are not known yet.
+static u64 list_entries(u64 n, u32 n_segs, const Config& cfg) {
+    const u64 unit = static_cast<u64>(kListRow) * n_segs;
+    return (list_capacity(n, static_cast<int>(cfg[CONDENSA_OPT_CAND_SHIFT])) + unit - 1) / unit * unit;
+}
+static u64 list_entries_bound(u64 N, int n_tensors, bool per_tensor, u32 max_segs, const Config& cfg) {
+    if (!per_tensor) return list_entries(N, max_segs, cfg);
+    const u64 nt = static_cast<u64>(n_tensors);
+    const int64_t shift = cfg[CONDENSA_OPT_CAND_SHIFT];
+    u64 most = shift > 0 ? (N >> shift) + 4096 * nt : N / 4 + 4096 * nt;
+    if (shift <= 0 && N / 16 + (nt << 19) < most) most = N / 16 + (nt << 19);
+    if (shift <= 0 && N < most) most = N;
+    return most + static_cast<u64>(kListRow) * max_segs * nt;
+}
+static u32 list_groups(u64 n, const Config& cfg) {         // sampling workgroups of a population
+    const int64_t opt = cfg[CONDENSA_OPT_SAMPLE_LOG2];
+    if (opt <= 0) return list_sample_groups(n);
+    if ((static_cast<u64>(1) << opt) <= static_cast<u64>(kListThreads) * kListUnits * kSampleUnit) return 1;
+    u32 w = 32;                                            // fewer draws would leave order statistics no room
+    while (w < static_cast<u32>(kListMaxW) && static_cast<u64>(w) * kListThreads * kSampleUnit < (static_cast<u64>(1) << opt)) w *= 2;
+    return w;
+}
+
 Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const Config& cfg, bool no_window) {
     Layout L;
     const bool per_tensor = (scope == CONDENSA_SCOPE_PER_TENSOR);
@@ -235,6 +290,41 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
     L.out = off;    off += align_up(static_cast<size_t>(J) * (n_tensors > 0 ? n_tensors : 1) * sizeof(OutDesc));
     L.slots = off;  off += align_up(static_cast<size_t>(L.n_slots) * sizeof(Slot) + (structure ? 3 : 2 * kMaxJ) * sizeof(Slot));
     L.upload_bytes = off;
+    const bool element = op == CONDENSA_OP_PRUNE || op == CONDENSA_OP_LC_STEP;
+    if (element && !no_window && want_list(N, n_tensors, L.n_slots, per_tensor, J, op == CONDENSA_OP_LC_STEP, cfg)) {
+        const u64 nt = static_cast<u64>(n_tensors);
+        const u64 groups = per_tensor ? (cfg[CONDENSA_OPT_SAMPLE_LOG2] > 0 ? nt * kListMaxW : nt + (N >> 14) + kListMaxW) : list_groups(N, cfg);
+        L.l_max_segs = list_max_segs(N, L.n_slots, J, op == CONDENSA_OP_LC_STEP);
+        const u64 entries = static_cast<u64>(J) * list_entries_bound(N, n_tensors, per_tensor, L.l_max_segs, cfg);
+        L.listed = true;
+        L.l_rank = off;    off += align_up(static_cast<size_t>(L.n_slots) * sizeof(ListRank) + (per_tensor ? groups * sizeof(u32) : 0));
+        L.zero_begin = off;
+        L.ctl = off;       off += align_up(sizeof(Control));
+        L.l_cnt = off;     off += align_up(static_cast<size_t>(L.n_slots) * L.l_max_segs * sizeof(u64));
+        L.l_nnz = off;     off += align_up(kListSegs * sizeof(u32));
+        L.seg = off;       off += op == CONDENSA_OP_LC_STEP ? align_up(kNnzSegs * sizeof(u64)) : 0;
+        L.l_hist = off;    off += align_up(static_cast<size_t>(L.n_slots) * kListBins * sizeof(u32));
+        L.l_gathered = off; off += align_up(static_cast<size_t>(L.n_slots) * sizeof(u32));
+        L.l_fb = off;      off += align_up(sizeof(FallbackCtl));
+        L.l_fb_hist = off; off += align_up(static_cast<size_t>(2 * 3) * kBins * sizeof(u32));
+        L.zero_bytes = off - L.zero_begin;
+        L.chunk_map = off; off += align_up(static_cast<size_t>(L.max_chunks + 1) * sizeof(u32));
+        L.tiecnt = off;    off += align_up(static_cast<size_t>(L.max_chunks) * sizeof(u32));
+        L.l_fail = off;    off += align_up(static_cast<size_t>(L.n_slots) * sizeof(u32));
+        L.l_want = off;    off += align_up(static_cast<size_t>(L.n_slots) * sizeof(u32));
+        L.l_gather_cap = (1u << 22) / L.n_slots > kListGather ? kListGather : ((1u << 22) / L.n_slots < kListRanked ? kListRanked : (1u << 22) / L.n_slots);
+        L.l_gkey = off;    off += align_up(static_cast<size_t>(L.n_slots) * L.l_gather_cap * sizeof(u32));
+        L.l_gidx = off;    off += align_up(static_cast<size_t>(L.n_slots) * L.l_gather_cap * sizeof(u32));
+        L.l_win = off;     off += align_up(static_cast<size_t>(L.n_slots) * sizeof(ListWin));
+        L.l_sorted = off;  off += J > 1 ? align_up(static_cast<size_t>(L.n_groups) * sizeof(ListSorted)) : 0;
+        L.l_local = off;   off += align_up(static_cast<size_t>(groups) * J * sizeof(ListWin));
+        L.l_key = off;     off += align_up(static_cast<size_t>(entries) * sizeof(u32));
+        L.l_idx = off;     off += align_up(static_cast<size_t>(entries) * sizeof(u32));
+        L.cand_cap = entries;
+        L.sample_cap = groups;
+        L.total = off;
+        return L;
+    }
     L.zero_begin = off;
     L.ctl = off;    off += align_up(sizeof(Control));
     L.hist0 = off;  off += align_up(static_cast<size_t>(L.n_groups) * kBins * sizeof(u64));
@@ -261,10 +351,7 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
     L.zero_bytes = off - L.zero_begin;
     L.chunk_map = off; off += align_up(static_cast<size_t>(L.max_chunks + 1) * sizeof(u32));
     if (tie_lists) {
-        // small calls on the automatic path finish on one list that can hold every element (k_small.h)
-        if (!no_window && N > 0 && N <= kSmallCallElems && cfg[CONDENSA_OPT_SELECT_PATH] == 0) L.small_cap = N;
-        u64 entries = static_cast<u64>(J) * kTieListCap;
-        if (entries < L.small_cap) entries = L.small_cap;
+        const u64 entries = static_cast<u64>(J) * kTieListCap;
         L.tl_key = off; off += align_up(static_cast<size_t>(entries) * sizeof(u32));
         L.tl_idx = off; off += align_up(static_cast<size_t>(entries) * sizeof(u64));
     }
@@ -422,22 +509,47 @@ static unsigned fill_grid(u64 words) {
 
 static condensa_status poke_upload(void* dst_dev, const char* src_host, size_t bytes, hipStream_t st);
 
+// The image of a call's tables in its staging slot.
+static UploadArgs fill_image(const StageImage& img, const Layout& L, void* ws, const Tables& tb, const OutDesc* out, size_t out_bytes,
+                             const Slot* slots, size_t slot_bytes, const void* lists, size_t list_bytes) {
+    const void* src[4] = {tb.td, out, slots, lists};
+    const size_t bytes[4] = {static_cast<size_t>(tb.n_td) * sizeof(TensorDesc), out_bytes, slot_bytes, list_bytes};
+    const size_t dst[4] = {L.td, L.out, L.slots, L.l_rank};
+    UploadArgs up{};
+    up.src = reinterpret_cast<const uint4*>(img.data());
+    size_t at0 = 0;
+    for (int i = 0; i < 4; ++i) {
+        if (bytes[i]) std::memcpy(img.data() + at0, src[i], bytes[i]);
+        at0 += bytes[i];
+        up.dst[i] = at<uint4>(ws, dst[i]);
+        up.end[i] = static_cast<u32>(at0 / 16);
+    }
+    up.done = img.done();
+    up.ticket = img.ticket();
+    return up;
+}
+
+// Workgroups of the launch that begins a call, beside the one that fetches the tables.
+static u64 begin_blocks(u64 n_zero, u64 n_chunks) {
+    const u64 words = n_zero > n_chunks ? n_zero : n_chunks;
+    const u64 blocks = (words + 2 * kBeginThreads - 1) / (2 * kBeginThreads);
+    return blocks > 512 ? 512 : (blocks ? blocks : 1);
+}
+
 // What every call starts with: the tables [tensors | outputs | rankings] reach the front of the workspace, the
 // counter and histogram region is cleared and the chunk -> tensor map is written.  One launch while the tables are
 // small (kBeginTensors tensors, one staging slot), two beyond that.  `fixed`: for callers that cannot allocate, the
 // memory to build the tables' image in; they then travel as kernel arguments.
 static condensa_status begin_call(const Layout& L, const Tables& tb, int n_tensors, const OutDesc* out, size_t n_out,
-                                  const Slot* slots, size_t n_slots, void* ws, hipStream_t st, char* fixed = nullptr) {
+                                  const Slot* slots, size_t n_slots, void* ws, hipStream_t st, char* fixed = nullptr,
+                                  const void* lists = nullptr, size_t list_bytes = 0) {
     const size_t td_bytes = static_cast<size_t>(tb.n_td) * sizeof(TensorDesc), out_bytes = n_out * sizeof(OutDesc),
                  slot_bytes = n_slots * sizeof(Slot);
     const u64 n_words = L.zero_bytes / 8;
-    auto fill = [&](char* td_at, char* out_at, char* slots_at) {
-        std::memcpy(td_at, tb.td, td_bytes);
-        if (out_bytes) std::memcpy(out_at, out, out_bytes);
-        if (slot_bytes) std::memcpy(slots_at, slots, slot_bytes);
-    };
     if (fixed) {
-        fill(fixed + L.td, fixed + L.out, fixed + L.slots);
+        std::memcpy(fixed + L.td, tb.td, td_bytes);
+        if (out_bytes) std::memcpy(fixed + L.out, out, out_bytes);
+        if (slot_bytes) std::memcpy(fixed + L.slots, slots, slot_bytes);
         const condensa_status rc = poke_upload(ws, fixed, L.upload_bytes, st);
         if (rc != CONDENSA_OK) return rc;
         hipLaunchKernelGGL(k_prepare, dim3(fill_grid(n_words)), dim3(kBlock), 0, st, at<u64>(ws, L.zero_begin), n_words,
@@ -447,18 +559,10 @@ static condensa_status begin_call(const Layout& L, const Tables& tb, int n_tenso
         return CONDENSA_OK;
     }
     StageImage img;
-    const condensa_status rc = img.acquire(td_bytes + out_bytes + slot_bytes, st);      // each a multiple of 32 bytes
+    const condensa_status rc = img.acquire(td_bytes + out_bytes + slot_bytes + list_bytes, st);    // each a multiple of 16 bytes
     if (rc != CONDENSA_OK) return rc;
-    fill(img.data(), img.data() + td_bytes, img.data() + td_bytes + out_bytes);
-    UploadArgs up{};
-    up.src = reinterpret_cast<const uint4*>(img.data());
-    up.dst[0] = at<uint4>(ws, L.td); up.dst[1] = at<uint4>(ws, L.out); up.dst[2] = at<uint4>(ws, L.slots);
-    up.end[0] = static_cast<u32>(td_bytes / 16);
-    up.end[1] = up.end[0] + static_cast<u32>(out_bytes / 16);
-    up.end[2] = up.end[1] + static_cast<u32>(slot_bytes / 16);
-    up.done = img.done();
-    up.ticket = img.ticket();
-    if (n_tensors <= kBeginTensors && td_bytes + out_bytes + slot_bytes <= kStageBytes) {
+    const UploadArgs up = fill_image(img, L, ws, tb, out, out_bytes, slots, slot_bytes, lists, list_bytes);
+    if (n_tensors <= kBeginTensors && td_bytes + out_bytes + slot_bytes + list_bytes <= kStageBytes) {
         BeginArgs b{};
         b.up = up;
         b.zero = at<uint4>(ws, L.zero_begin);
@@ -467,16 +571,13 @@ static condensa_status begin_call(const Layout& L, const Tables& tb, int n_tenso
         b.n_chunks = static_cast<u32>(tb.n_chunks);
         b.n_tensors = n_tensors;
         for (int t = 0; t <= n_tensors; ++t) b.chunk_start[t] = static_cast<u32>(tb.td[t].chunk_start);
-        u64 blocks = (b.n_zero + 2 * kBeginThreads - 1) / (2 * kBeginThreads);
-        const u64 map_blocks = (tb.n_chunks + 2 * kBeginThreads - 1) / (2 * kBeginThreads);
-        if (blocks < map_blocks) blocks = map_blocks;
-        blocks = (blocks > 512 ? 512 : blocks) + 1;
+        const u64 blocks = begin_blocks(b.n_zero, tb.n_chunks) + 1;
         hipLaunchKernelGGL(k_begin, dim3(static_cast<unsigned>(blocks)), dim3(kBeginThreads), 0, st, b);
         CONDENSA_LAUNCH_CHECK();
         img.commit();
         return CONDENSA_OK;
     }
-    const u32 up_blocks = (up.end[2] + 4 * kBlock - 1) / (4 * kBlock);
+    const u32 up_blocks = (up.end[3] + 4 * kBlock - 1) / (4 * kBlock);
     hipLaunchKernelGGL(k_upload, dim3(up_blocks ? up_blocks : 1), dim3(kBlock), 0, st, up);
     CONDENSA_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_prepare, dim3(fill_grid(n_words)), dim3(kBlock), 0, st, at<u64>(ws, L.zero_begin), n_words,
@@ -492,12 +593,11 @@ static condensa_status begin_call(const Layout& L, const Tables& tb, int n_tenso
 
 // Radix levels over the weights: 3 x (histogram sweep + bin search).
 template <bool LC, bool VEC>
-static condensa_status launch_radix_levels(const DataArgs& a, int n_slots, hipStream_t st, const Config& cfg,
-                                           int levels = n_levels(31)) {
+static condensa_status launch_radix_levels(const DataArgs& a, int n_slots, hipStream_t st, const Config& cfg) {
     if (a.n_chunks > 0) {
         // as the gated fallback of the window path these launches are (normally empty) resolve work
         PhaseTimer timer(a.only_failed ? CONDENSA_PHASE_RESOLVE : CONDENSA_PHASE_SWEEP, st, cfg);
-        for (int level = 0; level < levels; ++level) {
+        for (int level = 0; level < n_levels(31); ++level) {
             // Every workgroup flushes the non-zero bins of its LDS histograms (J of them past level 0) with
             // global atomics: few wide workgroups keep that flush small (level 0 of 20 M weights: 36 -> 19 us).
             const bool wide = !a.per_tensor;
@@ -551,35 +651,187 @@ static condensa_status run_selection(DataArgs a, const Layout& L, void* ws, bool
         if (rc != CONDENSA_OK) return rc;
         a.only_failed = 1;
     }
-    if (!use_window && a.small_cap >= a.N && a.n_chunks > 0 && a.merged) {
-        // a small call: level 0, then the keys of the thresholds' bins as a list, then one workgroup per ranking
-        rc = launch_radix_levels<LC, VEC>(a, n_slots, st, cfg, 1);
-        if (rc != CONDENSA_OK) return rc;
-        PhaseTimer timer(CONDENSA_PHASE_RESOLVE, st, cfg);
-        hipLaunchKernelGGL((k_small_collect<LC, VEC>), dim3(static_cast<unsigned>(a.n_chunks < 1024 ? a.n_chunks : 1024)), dim3(kBlock), 0, st, a);
-        CONDENSA_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_small_finish, dim3(n_slots), dim3(kSmallFinishThreads), 0, st, a, results, bits_for(a.N - 1));
-        CONDENSA_LAUNCH_CHECK();
-        return CONDENSA_OK;
-    }
     rc = launch_radix_levels<LC, VEC>(a, n_slots, st, cfg);
     if (rc != CONDENSA_OK) return rc;
     return launch_ties_and_results<LC, VEC>(a, n_slots, n_groups, results, st, cfg);
 }
 
-// Sampled window or radix levels?  Measured (one MI355X, 2^24..2^30 weights, 1/4/10 densities): the radix
-// levels cost three sweeps whatever the number of densities and ~50 us of fixed work; the window path
-// costs one sweep, ~0.2 ms of small kernels, and candidate lists and a sweep that grow with the number
-// of densities.  One density breaks even near 2^26 element reads, four near 2^27.5, ten near 2^30.
-static bool want_window(u64 N, bool per_tensor, int J, bool lc, const Config& cfg) {
-    if (per_tensor) return false;
-    if ((N >> kCandTensorShift) != 0) return false;        // candidates carry their tensor above a 44-bit flat index
-    const int64_t mode = cfg[CONDENSA_OPT_SELECT_PATH];
-    if (mode == 1) return false;
-    if (mode == 2) return N >= 1;
-    u64 need = static_cast<u64>(J) << 26;
-    if (J > 4) need = need * static_cast<u64>(J) / 4;
-    return N * (lc ? 2u : 1u) >= need;
+// The listed windows (k_listed.h).  With `write` the one pass over the weights writes the outputs; without it (an
+// output that overwrites its input, or two sweeps asked for) the caller's apply sweep follows.
+struct ListRequest {
+    const OutDesc* out;    // device output table
+    bool vec_out;          // every output pointer allows 128-bit accesses
+    bool pq;
+    bool write;
+    u64* nnz_out;
+    bool wide;             // masks only, each 16-byte aligned
+};
+
+// Host tables of the path: one ListRank per ranking, then (PER_TENSOR) the tensor of every sampling workgroup.
+static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors, int J, bool per_tensor, bool lc, const Config& cfg,
+                               std::vector<char>* table, u32* groups, bool* bounds) {
+    const size_t n_groups = per_tensor ? static_cast<size_t>(n_tensors) : 1;
+    std::vector<u32> group_of;
+    table->assign(n_groups * J * sizeof(ListRank), 0);
+    ListRank* rk = reinterpret_cast<ListRank*>(table->data());
+    u64 base = 0;
+    u32 first = 0;
+    *bounds = false;
+    for (size_t g = 0; g < n_groups; ++g) {
+        const u64 n = per_tensor ? tb.td[g].n : tb.N;
+        const u32 w = list_groups(n, cfg);
+        u32 segs = list_segments(n, list_wave_elems(J, lc), L.l_max_segs);
+        for (int j = 0; j < J; ++j) {
+            ListRank& r = rk[g * J + j];
+            const u64 entries = n ? list_entries(n, segs, cfg) : 0;
+            r.base = base;
+            r.n_segs = segs;
+            r.seg_cap = static_cast<u32>(entries / segs);
+            r.group0 = first;
+            r.n_groups = w;
+            base += entries;
+        }
+        if (per_tensor) group_of.insert(group_of.end(), w, static_cast<u32>(g));
+        if (w > 1) *bounds = true;
+        first += w;
+    }
+    *groups = first;
+    if (per_tensor) {
+        const size_t at0 = table->size();
+        table->resize(align_up(at0 + group_of.size() * sizeof(u32), 16), 0);
+        std::memcpy(table->data() + at0, group_of.data(), group_of.size() * sizeof(u32));
+    }
+    return table->size();
+}
+
+static ListArgs list_args(const Layout& L, void* ws, int n_slots, const ListRequest& rq, const Config& cfg) {
+    ListArgs w{};
+    w.rank = at<ListRank>(ws, L.l_rank);
+    w.group_of = reinterpret_cast<const u32*>(w.rank + n_slots);
+    w.local = at<ListWin>(ws, L.l_local);
+    w.win = at<ListWin>(ws, L.l_win);
+    w.sorted = at<ListSorted>(ws, L.l_sorted);
+    w.max_segs = L.l_max_segs;
+    w.n_rankings = n_slots;
+    w.hist = at<u32>(ws, L.l_hist);
+    w.gathered = at<u32>(ws, L.l_gathered);
+    w.bin_want = at<u32>(ws, L.l_want);
+    w.gkey = at<u32>(ws, L.l_gkey);
+    w.gidx = at<u32>(ws, L.l_gidx);
+    w.gather_cap = L.l_gather_cap;
+    w.parts = n_slots >= 512 ? 1u : (512u / n_slots > 64u ? 64u : 512u / n_slots);
+    w.cnt = at<u64>(ws, L.l_cnt);
+    w.nnz = at<u32>(ws, L.l_nnz);
+    w.key = at<u32>(ws, L.l_key);
+    w.idx = at<u32>(ws, L.l_idx);
+    w.fb = at<FallbackCtl>(ws, L.l_fb);
+    w.fail_list = at<u32>(ws, L.l_fail);
+    w.fb_hist = at<u32>(ws, L.l_fb_hist);
+    w.out = rq.out;
+    w.nnz_out = rq.nnz_out;
+    w.margin16 = static_cast<int>(cfg[CONDENSA_OPT_WINDOW_MARGIN]);
+    w.write = rq.write ? 1 : 0;
+    return w;
+}
+
+// Begins the call and takes the sample in one launch; false when the call is not of that form.
+template <bool LC, bool VEC>
+static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n_tensors, const OutDesc* out, size_t n_out, const Slot* slots,
+                                        int J, float mu, void* ws, hipStream_t st, const std::vector<char>& lists, u32 groups,
+                                        const ListRequest& rq, const Config& cfg, bool* begun) {
+    *begun = false;
+    const size_t td_bytes = static_cast<size_t>(tb.n_td) * sizeof(TensorDesc), out_bytes = n_out * sizeof(OutDesc),
+                 slot_bytes = static_cast<size_t>(J) * sizeof(Slot);
+    if (n_tensors > kBeginSampleTensors || td_bytes + out_bytes + slot_bytes + lists.size() > kStageBytes) return CONDENSA_OK;
+    PhaseTimer timer(CONDENSA_PHASE_SAMPLE, st, cfg);
+    StageImage img;
+    const condensa_status rc = img.acquire(td_bytes + out_bytes + slot_bytes + lists.size(), st);
+    if (rc != CONDENSA_OK) return rc;
+    BeginSampleArgs b{};
+    b.up = fill_image(img, L, ws, tb, out, out_bytes, slots, slot_bytes, lists.data(), lists.size());
+    b.zero = at<uint4>(ws, L.zero_begin);
+    b.n_zero = L.zero_bytes / 16;
+    b.chunk_map = at<u32>(ws, L.chunk_map);
+    b.n_chunks = static_cast<u32>(tb.n_chunks);
+    b.n_tensors = n_tensors;
+    b.groups = groups;
+    b.J = J;
+    b.mu = mu;
+    b.N = tb.N;
+    for (int j = 0; j < J; ++j) b.k[j] = slots[j].k;
+    for (int t = 0; t < n_tensors; ++t) {
+        b.w[t] = tb.td[t].w;
+        b.lam[t] = tb.td[t].lam;
+        b.n[t] = static_cast<u32>(tb.td[t].n);
+    }
+    for (int t = 0; t <= n_tensors; ++t) b.chunk_start[t] = static_cast<u32>(tb.td[t].chunk_start);
+    const u64 blocks = begin_blocks(b.n_zero, tb.n_chunks) + 1 + groups;
+    hipLaunchKernelGGL((k_begin_sample<LC, VEC>), dim3(static_cast<unsigned>(blocks)), dim3(kListThreads), 0, st, b,
+                       list_args(L, ws, J, rq, cfg));
+    CONDENSA_LAUNCH_CHECK();
+    img.commit();
+    *begun = true;
+    return CONDENSA_OK;
+}
+
+template <bool LC, bool VEC>
+static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* ws, u32 groups, bool bounds, int n_slots, int n_groups,
+                                     condensa_select* results, const ListRequest& rq, bool sampled, hipStream_t st, const Config& cfg) {
+    ListArgs w = list_args(L, ws, n_slots, rq, cfg);
+    const bool vec = VEC && rq.vec_out;
+    {
+        PhaseTimer timer(CONDENSA_PHASE_SAMPLE, st, cfg);
+        if (!sampled) {
+            hipLaunchKernelGGL((k_list_sample<LC, VEC>), dim3(groups), dim3(kListThreads), 0, st, a, w);
+            CONDENSA_LAUNCH_CHECK();
+        }
+        if (bounds) {
+            hipLaunchKernelGGL(k_list_bounds, dim3(static_cast<unsigned>(n_groups)), dim3(kBoundsThreads), 0, st, a, w);
+            CONDENSA_LAUNCH_CHECK();
+        }
+    }
+    {
+        PhaseTimer timer(CONDENSA_PHASE_SWEEP, st, cfg);
+        constexpr int Q = LC ? kFusedQuadsLC : kFusedQuadsPrune;
+        const dim3 grid(static_cast<unsigned>(a.n_chunks * (kChunk / (256 * Q))));
+        if constexpr (LC) {
+            if (rq.pq && vec)  hipLaunchKernelGGL((k_list_sweep<true, true, Q, true>), grid, dim3(64), 0, st, a, w);
+            else if (rq.pq)    hipLaunchKernelGGL((k_list_sweep<true, false, Q, true>), grid, dim3(64), 0, st, a, w);
+            else if (vec)      hipLaunchKernelGGL((k_list_sweep<true, true, Q, false>), grid, dim3(64), 0, st, a, w);
+            else               hipLaunchKernelGGL((k_list_sweep<true, false, Q, false>), grid, dim3(64), 0, st, a, w);
+        } else if (a.J == 1) {
+            if (vec) hipLaunchKernelGGL((k_list_sweep<false, true, Q, false>), grid, dim3(64), 0, st, a, w);
+            else     hipLaunchKernelGGL((k_list_sweep<false, false, Q, false>), grid, dim3(64), 0, st, a, w);
+        } else {
+            const dim3 gm(static_cast<unsigned>(a.n_chunks * (kChunk / (256 * kListMultiQuads))));
+            if (vec && rq.wide) hipLaunchKernelGGL((k_list_sweep_multi<true, true>), gm, dim3(64), 0, st, a, w);
+            else if (vec)       hipLaunchKernelGGL((k_list_sweep_multi<true, false>), gm, dim3(64), 0, st, a, w);
+            else                hipLaunchKernelGGL((k_list_sweep_multi<false, false>), gm, dim3(64), 0, st, a, w);
+        }
+        CONDENSA_LAUNCH_CHECK();
+    }
+    PhaseTimer timer(CONDENSA_PHASE_RESOLVE, st, cfg);
+    const dim3 walk(static_cast<unsigned>(n_slots) * w.parts), fb(kSettleGrid);
+    const int vo = rq.vec_out ? 1 : 0;
+    hipLaunchKernelGGL(k_list_hist, walk, dim3(kBlock), 0, st, a, w);
+    CONDENSA_LAUNCH_CHECK();
+    if constexpr (LC) {
+        if (rq.pq) {
+            hipLaunchKernelGGL((k_list_gather<true, true>), walk, dim3(kBlock), 0, st, a, w);
+            CONDENSA_LAUNCH_CHECK();
+            hipLaunchKernelGGL((k_list_settle<true, VEC, true>), fb, dim3(kBlock), 0, st, a, w, results, n_groups, vo);
+        } else {
+            hipLaunchKernelGGL((k_list_gather<true, false>), walk, dim3(kBlock), 0, st, a, w);
+            CONDENSA_LAUNCH_CHECK();
+            hipLaunchKernelGGL((k_list_settle<true, VEC, false>), fb, dim3(kBlock), 0, st, a, w, results, n_groups, vo);
+        }
+    } else {
+        hipLaunchKernelGGL((k_list_gather<false, false>), walk, dim3(kBlock), 0, st, a, w);
+        CONDENSA_LAUNCH_CHECK();
+        hipLaunchKernelGGL((k_list_settle<false, VEC, false>), fb, dim3(kBlock), 0, st, a, w, results, n_groups, vo);
+    }
+    CONDENSA_LAUNCH_CHECK();
+    return CONDENSA_OK;
 }
 
 }  // namespace condensa
@@ -661,7 +913,7 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
     ByteRange* ranges = arena.array<ByteRange>(static_cast<size_t>(n_tensors) * (1 + 3 * J) + 2);
     if (!out || !ranges) return CONDENSA_ERR_SIZE;
     size_t n_ranges = 0;
-    bool vec = tb.vec;
+    bool vec = tb.vec, masks_wide = true;
     bool in_place_any = false;
     for (int t = 0; t < n_tensors; ++t) {
         const u64 n = tb.td[t].n;
@@ -684,6 +936,7 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
             if (o.theta && !aligned16(o.theta)) vec = false;
             if (o.theta16 && (reinterpret_cast<uintptr_t>(o.theta16) & 7u)) vec = false;
             if (o.mask && (reinterpret_cast<uintptr_t>(o.mask) & 3u)) vec = false;
+            if (!aligned16(o.mask)) masks_wide = false;
         }
         ranges[n_ranges++] = byte_range(tb.td[t].w, n * 4, in_place);
         in_place_any = in_place_any || in_place;
@@ -701,13 +954,25 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
     for (int g = 0; g < L.n_groups; ++g)
         for (int j = 0; j < J; ++j) {
             const u64 n = per_tensor ? tb.td[g].n : tb.N;
-            init_slot(&slots[static_cast<size_t>(g) * J + j], n, kept_count(densities[j], n), window ? 2u : 1u);
+            init_slot(&slots[static_cast<size_t>(g) * J + j], n, kept_count(densities[j], n), window || L.listed ? 2u : 1u);
         }
     const size_t n_up_slots = static_cast<size_t>(L.n_slots) + ((window && J == 1) ? 3 : 0);
     if (window && J == 1) init_sample_slots(slots + L.n_slots, slots[0], cfg[CONDENSA_OPT_WINDOW_MARGIN]);
 
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = begin_call(L, tb, n_tensors, out, n_out, slots, n_up_slots, workspace_dev, st, fixed);
+    std::vector<char> lists;
+    u32 list_group_count = 0;
+    bool list_bounds = false;
+    const size_t list_bytes = L.listed ? build_list_table(tb, L, n_tensors, J, per_tensor, false, cfg, &lists, &list_group_count, &list_bounds) : 0;
+    const OutDesc* od = at<OutDesc>(workspace_dev, L.out);
+    const bool listed_write = L.listed && any_out && !in_place_any && cfg[CONDENSA_OPT_FUSED_SWEEP] == 0;
+    const ListRequest rq{od, vec, false, listed_write, nullptr, masks_wide && !theta && !theta_f16};
+    bool sampled = false;
+    if (L.listed && !per_tensor)
+        rc = tb.vec ? begin_and_sample<false, true>(L, tb, n_tensors, out, n_out, slots, J, 0.0f, workspace_dev, st, lists, list_group_count, rq, cfg, &sampled)
+                    : begin_and_sample<false, false>(L, tb, n_tensors, out, n_out, slots, J, 0.0f, workspace_dev, st, lists, list_group_count, rq, cfg, &sampled);
+    if (rc == CONDENSA_OK && !sampled)
+        rc = begin_call(L, tb, n_tensors, out, n_out, slots, n_up_slots, workspace_dev, st, fixed, lists.data(), list_bytes);
     if (rc != CONDENSA_OK) return rc;
 
     DataArgs a{};
@@ -722,7 +987,6 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
         a.tl_cnt = at<u64>(workspace_dev, L.tl_cnt);
         a.tl_key = at<u32>(workspace_dev, L.tl_key);
         a.tl_idx = at<u64>(workspace_dev, L.tl_idx);
-        a.small_cap = L.small_cap;
     }
     a.ctl = at<Control>(workspace_dev, L.ctl);
     a.chunk_map = at<u32>(workspace_dev, L.chunk_map);
@@ -736,18 +1000,23 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
     a.mu = 0.0f;
     a.merged = per_tensor ? 0 : 1;
 
+    if (L.listed) {
+        rc = tb.vec ? launch_listed<false, true>(a, L, workspace_dev, list_group_count, list_bounds, L.n_slots, L.n_groups, results_dev, rq, sampled, st, cfg)
+                    : launch_listed<false, false>(a, L, workspace_dev, list_group_count, list_bounds, L.n_slots, L.n_groups, results_dev, rq, sampled, st, cfg);
+        if (rc != CONDENSA_OK || listed_write) return rc;
+    }
     // One density on the window path: selection and apply share one sweep unless theta overwrites the weights.
     const bool fuse = window && J == 1 && any_out && tb.n_chunks > 0 && slots[0].k > 0 && !in_place_any &&
                       cfg[CONDENSA_OPT_FUSED_SWEEP] == 0;
     WindowArgs wargs{};
-    FusedRequest fr{at<OutDesc>(workspace_dev, L.out), vec, false, &wargs};
-    rc = tb.vec ? run_selection<false, true>(a, L, workspace_dev, window, L.n_slots, L.n_groups, results_dev, st, cfg, fuse ? &fr : nullptr)
-                : run_selection<false, false>(a, L, workspace_dev, window, L.n_slots, L.n_groups, results_dev, st, cfg, fuse ? &fr : nullptr);
+    FusedRequest fr{od, vec, false, &wargs};
+    if (!L.listed)
+        rc = tb.vec ? run_selection<false, true>(a, L, workspace_dev, window, L.n_slots, L.n_groups, results_dev, st, cfg, fuse ? &fr : nullptr)
+                    : run_selection<false, false>(a, L, workspace_dev, window, L.n_slots, L.n_groups, results_dev, st, cfg, fuse ? &fr : nullptr);
     if (rc != CONDENSA_OK) return rc;
 
     if (fuse) {
         PhaseTimer timer(CONDENSA_PHASE_APPLY, st, cfg);
-        const OutDesc* od = at<OutDesc>(workspace_dev, L.out);
         hipLaunchKernelGGL((k_window_fixup<false, false>), dim3(wargs.n_segs * kFixupParts), dim3(kBlock), 0, st, a, wargs);
         CONDENSA_LAUNCH_CHECK();
         const u64 n_tiles = tb.n_chunks * kSubPerChunk;
@@ -757,7 +1026,6 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
         CONDENSA_LAUNCH_CHECK();
     } else if (any_out && tb.n_chunks > 0) {
         PhaseTimer timer(CONDENSA_PHASE_APPLY, st, cfg);
-        const OutDesc* od = at<OutDesc>(workspace_dev, L.out);
         if (vec) hipLaunchKernelGGL((k_prune_apply<true>), dim3(static_cast<unsigned>(tb.n_chunks * kSubPerChunk)), dim3(kBlock), 0, st, a, od);
         else     hipLaunchKernelGGL((k_prune_apply<false>), dim3(static_cast<unsigned>(tb.n_chunks * kSubPerChunk)), dim3(kBlock), 0, st, a, od);
         CONDENSA_LAUNCH_CHECK();
@@ -911,11 +1179,26 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
     const bool window = want_window(tb.N, false, 1, true, cfg);
     Slot slot4[4];
     Slot& slot = slot4[0];
-    init_slot(&slot, tb.N, kept_count(density, tb.N), window ? 2u : 1u);
+    init_slot(&slot, tb.N, kept_count(density, tb.N), window || L.listed ? 2u : 1u);
     if (window) init_sample_slots(slot4 + 1, slot, cfg[CONDENSA_OPT_WINDOW_MARGIN]);
 
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slot4, window ? 4 : 1, workspace_dev, st);
+    std::vector<char> lists;
+    u32 list_group_count = 0;
+    bool list_bounds = false;
+    const size_t list_bytes = L.listed ? build_list_table(tb, L, n_tensors, 1, false, true, cfg, &lists, &list_group_count, &list_bounds) : 0;
+    // the selection sweeps read w and lambda only, so their vector path depends on those alone
+    bool vec_in = tb.vec;
+    for (int t = 0; t < n_tensors; ++t)
+        if (tb.td[t].n > 0 && !aligned16(tb.td[t].lam)) vec_in = false;
+    const OutDesc* od = at<OutDesc>(workspace_dev, L.out);
+    const ListRequest rq{od, vec, pq, !in_place_any && cfg[CONDENSA_OPT_FUSED_SWEEP] == 0, pq ? nnz_dev : nullptr, false};
+    bool sampled = false;
+    if (L.listed)
+        rc = vec_in ? begin_and_sample<true, true>(L, tb, n_tensors, out.data(), out.size(), slot4, 1, mu, workspace_dev, st, lists, list_group_count, rq, cfg, &sampled)
+                    : begin_and_sample<true, false>(L, tb, n_tensors, out.data(), out.size(), slot4, 1, mu, workspace_dev, st, lists, list_group_count, rq, cfg, &sampled);
+    if (rc == CONDENSA_OK && !sampled)
+        rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slot4, window ? 4 : 1, workspace_dev, st, nullptr, lists.data(), list_bytes);
     if (rc != CONDENSA_OK) return rc;
 
     DataArgs a{};
@@ -930,7 +1213,6 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
         a.tl_cnt = at<u64>(workspace_dev, L.tl_cnt);
         a.tl_key = at<u32>(workspace_dev, L.tl_key);
         a.tl_idx = at<u64>(workspace_dev, L.tl_idx);
-        a.small_cap = L.small_cap;
     }
     a.ctl = at<Control>(workspace_dev, L.ctl);
     a.chunk_map = at<u32>(workspace_dev, L.chunk_map);
@@ -945,24 +1227,25 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
     a.merged = 1;
     // counters of the apply sweeps' non-zero codes: the last row of the segment counters (rows 1.. belong to the
     // sweeps of several densities, which the L-C step never runs)
-    a.nnz_seg = (pq && nnz_dev) ? at<u64>(workspace_dev, L.seg) + static_cast<size_t>(kSegs) * (1 + kMaxJ) : nullptr;
+    // (listed windows: the one row that their workspace holds)
+    a.nnz_seg = (pq && nnz_dev) ? at<u64>(workspace_dev, L.seg) + (L.listed ? 0 : static_cast<size_t>(kSegs) * (1 + kMaxJ)) : nullptr;
 
-    // the selection sweeps read w and lambda only, so their vector path depends on those alone
-    bool vec_in = tb.vec;
-    for (int t = 0; t < n_tensors; ++t)
-        if (tb.td[t].n > 0 && !aligned16(tb.td[t].lam)) vec_in = false;
     // Window path: selection and apply share one sweep unless lambda is updated in place (a failed window
     // needs the inputs again).
     const bool fuse = window && tb.n_chunks > 0 && slot.k > 0 && !in_place_any && cfg[CONDENSA_OPT_FUSED_SWEEP] == 0;
     WindowArgs wargs{};
-    FusedRequest fr{at<OutDesc>(workspace_dev, L.out), vec, pq, &wargs};
-    rc = vec_in ? run_selection<true, true>(a, L, workspace_dev, window, 1, 1, result_dev, st, cfg, fuse ? &fr : nullptr)
-                : run_selection<true, false>(a, L, workspace_dev, window, 1, 1, result_dev, st, cfg, fuse ? &fr : nullptr);
+    FusedRequest fr{od, vec, pq, &wargs};
+    if (L.listed) {
+        rc = vec_in ? launch_listed<true, true>(a, L, workspace_dev, list_group_count, list_bounds, 1, 1, result_dev, rq, sampled, st, cfg)
+                    : launch_listed<true, false>(a, L, workspace_dev, list_group_count, list_bounds, 1, 1, result_dev, rq, sampled, st, cfg);
+        if (rc != CONDENSA_OK || rq.write) return rc;
+    } else
+        rc = vec_in ? run_selection<true, true>(a, L, workspace_dev, window, 1, 1, result_dev, st, cfg, fuse ? &fr : nullptr)
+                    : run_selection<true, false>(a, L, workspace_dev, window, 1, 1, result_dev, st, cfg, fuse ? &fr : nullptr);
     if (rc != CONDENSA_OK) return rc;
 
     if (fuse) {
         PhaseTimer timer(CONDENSA_PHASE_APPLY, st, cfg);
-        const OutDesc* od = at<OutDesc>(workspace_dev, L.out);
         if (pq) hipLaunchKernelGGL((k_window_fixup<true, true>), dim3(wargs.n_segs * kFixupParts), dim3(kBlock), 0, st, a, wargs);
         else    hipLaunchKernelGGL((k_window_fixup<true, false>), dim3(wargs.n_segs * kFixupParts), dim3(kBlock), 0, st, a, wargs);
         CONDENSA_LAUNCH_CHECK();
@@ -975,7 +1258,6 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
         CONDENSA_LAUNCH_CHECK();
     } else if (tb.n_chunks > 0) {
         PhaseTimer timer(CONDENSA_PHASE_APPLY, st, cfg);
-        const OutDesc* od = at<OutDesc>(workspace_dev, L.out);
         const int64_t at_opt = cfg[CONDENSA_OPT_APPLY_THREADS];
         const unsigned nc = static_cast<unsigned>(tb.n_chunks);
         // measured on the 1.2 G-weight workload: 64 threads 3.94 ms, 256 threads 4.28 ms, 128 threads 4.55 ms

@@ -142,7 +142,10 @@ struct Layout {
     size_t ctl = 0, hist0 = 0, histx = 0, histc = 0, seg = 0;   // histc: coarse sums; seg: window-path segment counters
     size_t tiecnt = 0, tiehit = 0, chunk_map = 0;
     size_t tl_cnt = 0, tl_key = 0, tl_idx = 0;              // short lists of the keys that reach the last radix level's bins
-    u64 small_cap = 0;                                      // small calls: entries of the one list that replaces them (0: not a small call)
+    bool listed = false;                                    // the call takes the listed windows (k_listed.h): its regions are
+    size_t l_rank = 0, l_cnt = 0, l_nnz = 0, l_fb = 0, l_fb_hist = 0, l_fail = 0, l_local = 0, l_win = 0, l_key = 0, l_idx = 0;
+    size_t l_sorted = 0, l_hist = 0, l_gathered = 0, l_want = 0, l_gkey = 0, l_gidx = 0;
+    u32 l_max_segs = 0, l_gather_cap = 0;
     size_t skeys = 0, sblock = 0, smask = 0;                // structure keys, per-block kept counts, keep flags
     size_t sample = 0, cand_key = 0, cand_idx = 0;          // window path
     size_t cand_w = 0, cand_lam = 0;                        // inputs of the candidates (fused sweep)

@@ -50,8 +50,6 @@ struct DataArgs {
     u64* tl_cnt;           // [kMaxJ] entries offered per ranking; above kTieListCap: the list is incomplete
     u32* tl_key;           // [J][kTieListCap]
     u64* tl_idx;           // [J][kTieListCap]
-    u64 small_cap;         // > 0: a small call (k_small.h) - tl_key / tl_idx hold this many entries as ONE list of the
-                           // keys that share their leading digit with a threshold, counted by tl_cnt[0]
 };
 constexpr u32 kTieListCap = 4096;      // entries per ranking's list
 constexpr u32 kTieListGroup = 128;     // entries one workgroup may offer to the lists.  It buffers them in LDS and reserves
@@ -116,6 +114,30 @@ __device__ inline u64 block_excl_scan_u64(u64 v, u64* s_wave, u64* total) {
     }
     *total = all;
     return before + incl - v;
+}
+
+// inclusive scan of one u32 per thread over the workgroup; *total = workgroup sum.  Ends with a barrier.
+template <int THREADS>
+__device__ inline u32 wg_incl_scan_u32(u32 v, u32* s_wave, u32* total) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    u32 inc = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const u32 o = __shfl_up(inc, off);
+        if (lane >= off) inc += o;
+    }
+    if (lane == 63) s_wave[wv] = inc;
+    __syncthreads();
+    u32 before = 0, tot = 0;
+#pragma unroll
+    for (int j = 0; j < THREADS / 64; ++j) {
+        const u32 x = s_wave[j];
+        if (j < wv) before += x;
+        tot += x;
+    }
+    __syncthreads();
+    *total = tot;
+    return before + inc;
 }
 
 __device__ inline SlotStep slot_canonical(const Slot& s) {
@@ -209,22 +231,22 @@ __device__ inline SlotStep wave_enter_level(const Slot& s, int L, int key_bits, 
 // The tables of a call lie in pinned host memory (StageImage) and are fetched over the host link by the kernel that
 // begins the call; the last thing that kernel does with the image is to store its ticket, which frees the slot.
 struct UploadArgs {
-    const uint4* src;      // pinned image: tensor table, output table, rankings, one after the other
-    uint4* dst[3];         // where each goes
-    u32 end[3];            // 16-byte words up to the end of each
+    const uint4* src;      // pinned image: tensor table, output table, rankings, list table, one after the other
+    uint4* dst[4];         // where each goes
+    u32 end[4];            // 16-byte words up to the end of each
     u64* done;             // pinned: receives ticket (NULL: nothing)
     u64 ticket;
 };
 __device__ inline void upload_words(const UploadArgs& u, u32 first, u32 stride) {
-    for (u32 i0 = first; i0 < u.end[2]; i0 += 4 * stride) {          // four loads in flight: a round trip is about a microsecond
+    for (u32 i0 = first; i0 < u.end[3]; i0 += 4 * stride) {          // four loads in flight: a round trip is about a microsecond
         uint4 v[4];
 #pragma unroll
-        for (u32 k = 0; k < 4; ++k) if (i0 + k * stride < u.end[2]) v[k] = u.src[i0 + k * stride];
+        for (u32 k = 0; k < 4; ++k) if (i0 + k * stride < u.end[3]) v[k] = u.src[i0 + k * stride];
 #pragma unroll
         for (u32 k = 0; k < 4; ++k) {
             const u32 i = i0 + k * stride;
-            if (i >= u.end[2]) break;
-            const int part = i < u.end[0] ? 0 : (i < u.end[1] ? 1 : 2);
+            if (i >= u.end[3]) break;
+            const int part = i < u.end[0] ? 0 : (i < u.end[1] ? 1 : (i < u.end[2] ? 2 : 3));
             u.dst[part][i - (part ? u.end[part - 1] : 0)] = v[k];
         }
     }

@@ -1,13 +1,4 @@
-// Small calls (up to kSmallCallElems elements, GLOBAL scope): two launches after the first radix level.
-//
-// A call on a single layer or a small model is bound by its launches: three histogram sweeps, the tie sweep
-// and the tie search are five dependent launches around a few microseconds of work each.  After the first
-// level (11 of 31 key bits) the bins that hold the thresholds contain a few percent of the keys at most, so
-// the second sweep lists those keys with their flat indices instead of counting them (k_small_collect), and
-// one workgroup per ranking finishes on the list: the two remaining levels, the tie rule and the result
-// record (k_small_finish).  The list can hold every element of the call, so nothing can overflow: a
-// degenerate input (all keys in one bin) is only slower, never wrong.
-// Section 3.1 (a sparsity turned into a magnitude threshold); Results (up to ten samples per search).
+// Bin searches of one wavefront in an LDS histogram, and the rest of a ranking on a short list by one workgroup.
 #pragma once
 #include "k_select.h"
 
@@ -71,106 +62,6 @@ __device__ inline void wave_pick_asc(const u32* s_hist, int nb, u64 r, u32* bin,
                 *found = 1u;
             }
             before += c[i];
-        }
-    }
-}
-
-// Second sweep of a small call: every workgroup folds in level 0 for each ranking, then appends the (key, flat
-// index) of every key whose leading digit is the leading digit of some threshold to the call's list
-// (tl_key / tl_idx, counter tl_cnt[0]).  One reservation per workgroup and chunk; the order of the list does not
-// matter to what is computed from it.
-template <bool LC, bool VEC>
-__global__ __launch_bounds__(kBlock) void k_small_collect(DataArgs a) {
-    __shared__ u16 s_tab[kBins];
-    __shared__ u32 s_prefix[kMaxJ];
-    __shared__ u32 s_active[kMaxJ];
-    __shared__ u64 s_wave[kBlock / 64];
-    __shared__ u64 s_base;
-    const int tid = threadIdx.x;
-    for (int j = tid >> 6; j < a.J; j += kBlock / 64) {
-        const SlotStep e = wave_enter_level(a.slots[j], 1, 31, a.hist0, coarse_of(a.hist0, a.coarse, a.hist0));
-        if ((tid & 63) == 0) {
-            s_prefix[j] = static_cast<u32>(e.prefix);
-            s_active[j] = (e.state == kSelecting) ? 1u : 0u;
-        }
-    }
-    __syncthreads();
-    build_digit_table(s_tab, s_prefix, s_active, a.J, tid);
-    __syncthreads();
-    const Level L0 = level_of(31, 0);
-    for (u64 c = blockIdx.x; c < a.n_chunks; c += gridDim.x) {
-        const int t = static_cast<int>(a.chunk_map[c]);
-        const TensorDesc& td = a.td[t];
-        const u64 base = (c - td.chunk_start) * kChunk;
-        const u64 n = td.n;
-        u32 key[kQuadsPerThread * 4];
-        u32 listed = 0;                                    // bit q * 4 + k: element q * 1024 + tid * 4 + k of the chunk
-        if (VEC && base + kChunk <= n) {                   // whole chunk inside the tensor: loads first
-            constexpr int kHalf = LC ? kQuadsPerThread / 2 : kQuadsPerThread;
-#pragma unroll
-            for (int h = 0; h < kQuadsPerThread / kHalf; ++h) {
-                float4 wv[kHalf], lv[kHalf];
-#pragma unroll
-                for (int q = 0; q < kHalf; ++q) {
-                    const u64 e0 = base + static_cast<u64>(h * kHalf + q) * (kBlock * 4) + tid * 4;
-                    wv[q] = *reinterpret_cast<const float4*>(td.w + e0);
-                    if (LC) lv[q] = *reinterpret_cast<const float4*>(td.lam + e0);
-                }
-#pragma unroll
-                for (int q = 0; q < kHalf; ++q) {
-                    float v[4] = {wv[q].x, wv[q].y, wv[q].z, wv[q].w};
-                    if (LC) {
-                        const float l[4] = {lv[q].x, lv[q].y, lv[q].z, lv[q].w};
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) v[k] = lc_shift(v[k], l[k], a.mu);
-                    }
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const int i = (h * kHalf + q) * 4 + k;
-                        key[i] = mag_key(v[k]);
-                        if (s_tab[key[i] >> L0.shift] != 0) listed |= 1u << i;
-                    }
-                }
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < kQuadsPerThread; ++q) {
-                const u64 e0 = base + static_cast<u64>(q) * (kBlock * 4) + tid * 4;
-                float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (e0 < n) {
-                    load4<VEC>(td.w, e0, n, v);
-                    if (LC) {
-                        float l[4];
-                        load4<VEC>(td.lam, e0, n, l);
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) v[k] = lc_shift(v[k], l[k], a.mu);
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int i = q * 4 + k;
-                    key[i] = mag_key(v[k]);
-                    if (e0 + k < n && s_tab[key[i] >> L0.shift] != 0) listed |= 1u << i;
-                }
-            }
-        }
-        u64 total;
-        const u64 before = block_excl_scan_u64(static_cast<u64>(__popc(listed)), s_wave, &total);
-        if (total != 0) {                                  // uniform over the workgroup
-            if (tid == 0) s_base = atomicAdd(reinterpret_cast<unsigned long long*>(&a.tl_cnt[0]), static_cast<unsigned long long>(total));
-            __syncthreads();
-            u64 pos = s_base + before;
-#pragma unroll
-            for (int i = 0; i < kQuadsPerThread * 4; ++i) {
-                if (listed & (1u << i)) {
-                    if (pos < a.small_cap) {
-                        a.tl_key[pos] = key[i];
-                        a.tl_idx[pos] = td.flat_start + base + static_cast<u64>(i / 4) * (kBlock * 4) + tid * 4 + (i % 4);
-                    }
-                    ++pos;
-                }
-            }
-            __syncthreads();                               // s_base is rewritten for the next chunk
         }
     }
 }
@@ -284,21 +175,6 @@ __device__ inline void finish_on_list(Slot& slot, SlotStep e, const KEY* __restr
     }
     out.path = slot.path;
     *record = out;
-}
-
-// One workgroup per ranking: level 0 is folded in, the rest happens on the list.
-__global__ __launch_bounds__(kSmallFinishThreads) void k_small_finish(DataArgs a, condensa_select* results, int idx_bits) {
-    __shared__ SlotStep s_e;
-    const int j = blockIdx.x;
-    Slot& slot = a.slots[j];
-    if (threadIdx.x < 64) {
-        const SlotStep e = wave_enter_level(slot, 1, 31, a.hist0, coarse_of(a.hist0, a.coarse, a.hist0));
-        if (threadIdx.x == 0) s_e = e;
-    }
-    __syncthreads();
-    u64 n_list = a.tl_cnt[0];
-    if (n_list > a.small_cap) n_list = a.small_cap;        // (cannot happen: the list holds every element)
-    finish_on_list<u32, u64>(slot, s_e, a.tl_key, a.tl_idx, n_list, 31, 1, idx_bits, results + j);
 }
 
 }  // namespace condensa

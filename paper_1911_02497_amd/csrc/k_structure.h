@@ -774,30 +774,6 @@ constexpr int kMaskPer = 4;
 constexpr int kMaskTile = kBlock * kMaskPer;
 constexpr int kScanThreads = 1024;
 
-// inclusive scan of one u32 per thread over the workgroup; *total = workgroup sum.  Ends with a barrier.
-template <int THREADS>
-__device__ inline u32 wg_incl_scan_u32(u32 v, u32* s_wave, u32* total) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    u32 inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const u32 o = __shfl_up(inc, off);
-        if (lane >= off) inc += o;
-    }
-    if (lane == 63) s_wave[wv] = inc;
-    __syncthreads();
-    u32 before = 0, tot = 0;
-#pragma unroll
-    for (int j = 0; j < THREADS / 64; ++j) {
-        const u32 x = s_wave[j];
-        if (j < wv) before += x;
-        tot += x;
-    }
-    __syncthreads();
-    *total = tot;
-    return before + inc;
-}
-
 // keep flag of every structure and the number of kept structures of every tile of kMaskTile.
 // The one-sweep form of block pruning (k_struct_fused.h) leaves the flags in `smask` itself: its sweep decides
 // every block outside the window, its fix-up the listed ones.  There kMaskFromFlags only counts and copies

@@ -1,0 +1,132 @@
+"""GPU parity of the listed windows (what the automatic choice takes for ordinary calls): sizes at the edges of the
+rules (sampling workgroups, tiles, list segments), windows that miss or overlap, populations that crowd into a few
+values, all rankings of both scopes; against the oracle, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1911_02497_amd as P
+from gpu_util import assert_bits_equal, assert_select_equal, check_prune_against_oracle, DEV, up
+
+pytestmark = pytest.mark.gpu
+
+MISS = {"window_margin": 0}                       # windows of almost no width: the rankings go to the fallback
+
+
+def _check_lc(arrs, lams, density, config=None, in_place=False, pq=False):
+    mu = 1e-3
+    dev, lam = up(arrs), up(lams)
+    call = P.condensa_lc_step_pq if pq else P.condensa_lc_step
+    res = call(dev, lam, mu, density, in_place=in_place, config=config, **({"nnz": True} if pq else {}))
+    torch.cuda.synchronize()
+    ora = (oracle.lc_step_pq if pq else oracle.lc_step)(arrs, lams, mu, density)
+    assert_select_equal(P.select_records(res["results"])[0], ora["select"])
+    for i in range(len(arrs)):
+        for name in ("theta", "lambda", "grad"):
+            assert_bits_equal(res[name][i], ora[name][i], f"{name} {i}")
+        assert np.array_equal(res["mask"][i].cpu().numpy(), ora["mask"][i])
+    if pq:
+        codes = [res["theta_f16"][i].cpu().numpy().view(np.uint16) for i in range(len(arrs))]
+        assert int(res["nnz"].item()) == sum(int(((c & 0x7FFF) != 0).sum()) for c in codes)
+
+
+@pytest.mark.parametrize("n", [1, 255, 4096, 4097, 16384, (1 << 20), (1 << 20) + 3, (1 << 21), (1 << 21) + 5, (1 << 22) + 1])
+@pytest.mark.parametrize("config", [None, MISS], ids=["window", "miss"])
+def test_population_sizes(n, config):
+    w = np.random.default_rng(n).standard_normal(n).astype(np.float32)
+    for ds in ([0.3], [0.01, 0.2, 0.6]):
+        res = P.condensa_prune(up([w]), ds, theta_f16=True, config=config)
+        torch.cuda.synchronize()
+        check_prune_against_oracle(res, oracle.prune([w], ds, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1, str(n))
+
+
+@pytest.mark.parametrize("ds", [[0.1, 0.1], [0.1, 0.1001, 0.1002, 0.5], [1.0, 0.0, 0.5], [0.0, 0.0], [1.0, 1.0, 0.9999999],
+                                [0.5 - 0.03 * j for j in range(16)]], ids=str)
+@pytest.mark.parametrize("scope", [P.SCOPE_GLOBAL, P.SCOPE_PER_TENSOR])
+@pytest.mark.parametrize("outputs", ["mask", "all"])
+def test_windows_that_overlap_and_rankings_without_a_threshold(ds, scope, outputs):
+    rng = np.random.default_rng(3)
+    arrs = [rng.standard_normal(s).astype(np.float32) for s in ((300, 1111), (7,), (64, 32, 3, 3), (0,), (1 << 20,))]
+    res = P.condensa_prune(up(arrs), ds, scope=scope, theta=outputs == "all", theta_f16=outputs == "all")
+    torch.cuda.synchronize()
+    check_prune_against_oracle(res, oracle.prune(arrs, ds, scope), scope, len(arrs))
+
+
+@pytest.mark.parametrize("kind", ["zeros", "two_values", "all_equal", "levels", "edge"])
+@pytest.mark.parametrize("scope", [P.SCOPE_GLOBAL, P.SCOPE_PER_TENSOR])
+@pytest.mark.parametrize("ds", [[0.2], [0.05, 0.2, 0.7]], ids=["one", "three"])
+def test_populations_that_crowd_into_few_values(kind, scope, ds):
+    """Lists that overflow, bins that hold more than the gathering allows, thousands of ties cut in the middle."""
+    rng = np.random.default_rng(4)
+    w = rng.standard_normal((3, 400001)).astype(np.float32)
+    if kind == "zeros":
+        w[np.abs(w) < 1.6] = 0.0
+    elif kind == "two_values":
+        w = np.where(rng.random(w.shape) < 0.2, np.float32(0.5), np.float32(-0.25)).astype(np.float32)
+    elif kind == "all_equal":
+        w[:] = -3.0
+    elif kind == "levels":
+        w = (np.round(w * 16) / 16).astype(np.float32)
+    else:
+        w.reshape(-1)[: w.size // 3] = np.float32(1.2816)          # an atom right at one of the thresholds
+    arrs = [np.ascontiguousarray(r) for r in w]
+    res = P.condensa_prune(up(arrs), ds, scope=scope)
+    torch.cuda.synchronize()
+    check_prune_against_oracle(res, oracle.prune(arrs, ds, scope), scope, len(arrs), kind)
+
+
+@pytest.mark.parametrize("config", [None, MISS, {"fused_sweep": 1}, {"cand_shift": 12}, {"sample_log2": 20}], ids=["window", "miss", "two_sweeps", "short_lists", "large_sample"])
+@pytest.mark.parametrize("pq", [False, True])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_lc_step(config, pq, in_place):
+    rng = np.random.default_rng(5)
+    shapes = [(64, 3, 3, 3), (513, 1027), (10, 512), (0,), (300001,)]
+    arrs = [rng.standard_normal(s).astype(np.float32) * np.float32(0.05) for s in shapes]
+    lams = [rng.standard_normal(s).astype(np.float32) * np.float32(2e-5) for s in shapes]
+    _check_lc(arrs, lams, 0.1, config, in_place, pq)
+    if pq:                                                           # kept values that underflow to zero in binary16
+        _check_lc([a * np.float32(1e-7) for a in arrs], [l * np.float32(1e-7) for l in lams], 0.4, config, in_place, pq)
+
+
+@pytest.mark.parametrize("config", [None, MISS], ids=["window", "miss"])
+def test_per_tensor_population_sizes_in_one_call(config):
+    """Lone sampling workgroups beside populations with many, one density and several; misaligned weights too."""
+    rng = np.random.default_rng(6)
+    arrs = [rng.standard_normal(n).astype(np.float32) for n in (5, (1 << 20) + 1, 0, 9000, (1 << 22) + 77, 1)]
+    for ds in ([0.15], [0.02, 0.5]):
+        want = oracle.prune(arrs, ds, P.SCOPE_PER_TENSOR)
+        res = P.condensa_prune(up(arrs), ds, scope=P.SCOPE_PER_TENSOR, config=config)
+        torch.cuda.synchronize()
+        check_prune_against_oracle(res, want, P.SCOPE_PER_TENSOR, len(arrs))
+        shifted = [torch.empty(a.size + 1, dtype=torch.float32, device=DEV)[1:] for a in arrs]
+        for s, a in zip(shifted, arrs):
+            s.copy_(torch.from_numpy(a))
+        res = P.condensa_prune(shifted, ds, scope=P.SCOPE_PER_TENSOR, config=config)
+        torch.cuda.synchronize()
+        check_prune_against_oracle(res, want, P.SCOPE_PER_TENSOR, len(arrs))
+
+
+def test_in_place_theta():
+    w = np.random.default_rng(7).standard_normal(700001).astype(np.float32)
+    dev = up([w])
+    res = P.condensa_prune(dev, [0.25], in_place=True)
+    torch.cuda.synchronize()
+    check_prune_against_oracle(res, oracle.prune([w], [0.25], P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1)
+
+
+def test_special_values():
+    """Infinities, NaN patterns, zeros and subnormals among ordinary weights, thresholds in every region."""
+    rng = np.random.default_rng(8)
+    w = rng.standard_normal(300000).astype(np.float32)
+    w[:1000] = np.inf
+    w[1000:2000] = -np.inf
+    w[2000:2500] = np.nan
+    w.view(np.uint32)[2500:3000] = 0xFFC12345
+    w[3000:60000] = 0.0
+    w[60000:120000] = -1e-42
+    rng.shuffle(w)
+    for ds in ([0.001], [0.005], [0.3], [0.7], [0.99], [0.001, 0.005, 0.3, 0.7, 0.99]):
+        res = P.condensa_prune(up([w]), ds, theta_f16=True)
+        torch.cuda.synchronize()
+        check_prune_against_oracle(res, oracle.prune([w], ds, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1)
