@@ -312,7 +312,7 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
         L.tiecnt = off;    off += align_up(static_cast<size_t>(L.max_chunks) * sizeof(u32));
         L.l_fail = off;    off += align_up(static_cast<size_t>(L.n_slots) * sizeof(u32));
         L.l_want = off;    off += align_up(static_cast<size_t>(L.n_slots) * sizeof(u32));
-        L.l_gather_cap = (1u << 22) / L.n_slots > kListGather ? kListGather : ((1u << 22) / L.n_slots < kListRanked ? kListRanked : (1u << 22) / L.n_slots);
+        L.l_gather_cap = (1u << 20) / L.n_slots > kListGather ? kListGather : ((1u << 20) / L.n_slots < kListRanked ? kListRanked : (1u << 20) / L.n_slots);
         L.l_gkey = off;    off += align_up(static_cast<size_t>(L.n_slots) * L.l_gather_cap * sizeof(u32));
         L.l_gidx = off;    off += align_up(static_cast<size_t>(L.n_slots) * L.l_gather_cap * sizeof(u32));
         L.l_win = off;     off += align_up(static_cast<size_t>(L.n_slots) * sizeof(ListWin));
@@ -667,16 +667,23 @@ struct ListRequest {
     bool wide;             // masks only, each 16-byte aligned
 };
 
+// What a call's populations ask for.
+struct ListShape {
+    u32 groups = 0;        // sampling workgroups
+    bool bounds = false;   // some population has several
+    bool lone = true;      // no population is larger than kListLone
+};
+
 // Host tables of the path: one ListRank per ranking, then (PER_TENSOR) the tensor of every sampling workgroup.
 static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors, int J, bool per_tensor, bool lc, const Config& cfg,
-                               std::vector<char>* table, u32* groups, bool* bounds) {
+                               std::vector<char>* table, ListShape* shape) {
     const size_t n_groups = per_tensor ? static_cast<size_t>(n_tensors) : 1;
     std::vector<u32> group_of;
     table->assign(n_groups * J * sizeof(ListRank), 0);
     ListRank* rk = reinterpret_cast<ListRank*>(table->data());
     u64 base = 0;
     u32 first = 0;
-    *bounds = false;
+    *shape = ListShape{};
     for (size_t g = 0; g < n_groups; ++g) {
         const u64 n = per_tensor ? tb.td[g].n : tb.N;
         const u32 w = list_groups(n, cfg);
@@ -692,10 +699,11 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
             base += entries;
         }
         if (per_tensor) group_of.insert(group_of.end(), w, static_cast<u32>(g));
-        if (w > 1) *bounds = true;
+        if (w > 1) shape->bounds = true;
+        if (n > kListLone) shape->lone = false;
         first += w;
     }
-    *groups = first;
+    shape->groups = first;
     if (per_tensor) {
         const size_t at0 = table->size();
         table->resize(align_up(at0 + group_of.size() * sizeof(u32), 16), 0);
@@ -719,7 +727,7 @@ static ListArgs list_args(const Layout& L, void* ws, int n_slots, const ListRequ
     w.gkey = at<u32>(ws, L.l_gkey);
     w.gidx = at<u32>(ws, L.l_gidx);
     w.gather_cap = L.l_gather_cap;
-    w.parts = n_slots >= 512 ? 1u : (512u / n_slots > 64u ? 64u : 512u / n_slots);
+    w.parts = n_slots >= 1024 ? 1u : (1024u / n_slots > 64u ? 64u : 1024u / n_slots);
     w.cnt = at<u64>(ws, L.l_cnt);
     w.nnz = at<u32>(ws, L.l_nnz);
     w.key = at<u32>(ws, L.l_key);
@@ -775,17 +783,17 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
 }
 
 template <bool LC, bool VEC>
-static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* ws, u32 groups, bool bounds, int n_slots, int n_groups,
+static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* ws, const ListShape& shape, int n_slots, int n_groups,
                                      condensa_select* results, const ListRequest& rq, bool sampled, hipStream_t st, const Config& cfg) {
     ListArgs w = list_args(L, ws, n_slots, rq, cfg);
     const bool vec = VEC && rq.vec_out;
     {
         PhaseTimer timer(CONDENSA_PHASE_SAMPLE, st, cfg);
         if (!sampled) {
-            hipLaunchKernelGGL((k_list_sample<LC, VEC>), dim3(groups), dim3(kListThreads), 0, st, a, w);
+            hipLaunchKernelGGL((k_list_sample<LC, VEC>), dim3(shape.groups), dim3(kListThreads), 0, st, a, w);
             CONDENSA_LAUNCH_CHECK();
         }
-        if (bounds) {
+        if (shape.bounds) {
             hipLaunchKernelGGL(k_list_bounds, dim3(static_cast<unsigned>(n_groups)), dim3(kBoundsThreads), 0, st, a, w);
             CONDENSA_LAUNCH_CHECK();
         }
@@ -813,6 +821,13 @@ static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* w
     PhaseTimer timer(CONDENSA_PHASE_RESOLVE, st, cfg);
     const dim3 walk(static_cast<unsigned>(n_slots) * w.parts), fb(kSettleGrid);
     const int vo = rq.vec_out ? 1 : 0;
+    if (shape.lone) {
+        const dim3 fin(static_cast<unsigned>(n_slots));
+        if (LC && rq.pq) hipLaunchKernelGGL((k_list_finish<LC, LC>), fin, dim3(kListThreads), 0, st, a, w, results, n_groups);
+        else             hipLaunchKernelGGL((k_list_finish<LC, false>), fin, dim3(kListThreads), 0, st, a, w, results, n_groups);
+        CONDENSA_LAUNCH_CHECK();
+        return CONDENSA_OK;
+    }
     hipLaunchKernelGGL(k_list_hist, walk, dim3(kBlock), 0, st, a, w);
     CONDENSA_LAUNCH_CHECK();
     if constexpr (LC) {
@@ -961,16 +976,15 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::vector<char> lists;
-    u32 list_group_count = 0;
-    bool list_bounds = false;
-    const size_t list_bytes = L.listed ? build_list_table(tb, L, n_tensors, J, per_tensor, false, cfg, &lists, &list_group_count, &list_bounds) : 0;
+    ListShape list_shape;
+    const size_t list_bytes = L.listed ? build_list_table(tb, L, n_tensors, J, per_tensor, false, cfg, &lists, &list_shape) : 0;
     const OutDesc* od = at<OutDesc>(workspace_dev, L.out);
     const bool listed_write = L.listed && any_out && !in_place_any && cfg[CONDENSA_OPT_FUSED_SWEEP] == 0;
     const ListRequest rq{od, vec, false, listed_write, nullptr, masks_wide && !theta && !theta_f16};
     bool sampled = false;
     if (L.listed && !per_tensor)
-        rc = tb.vec ? begin_and_sample<false, true>(L, tb, n_tensors, out, n_out, slots, J, 0.0f, workspace_dev, st, lists, list_group_count, rq, cfg, &sampled)
-                    : begin_and_sample<false, false>(L, tb, n_tensors, out, n_out, slots, J, 0.0f, workspace_dev, st, lists, list_group_count, rq, cfg, &sampled);
+        rc = tb.vec ? begin_and_sample<false, true>(L, tb, n_tensors, out, n_out, slots, J, 0.0f, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled)
+                    : begin_and_sample<false, false>(L, tb, n_tensors, out, n_out, slots, J, 0.0f, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled);
     if (rc == CONDENSA_OK && !sampled)
         rc = begin_call(L, tb, n_tensors, out, n_out, slots, n_up_slots, workspace_dev, st, fixed, lists.data(), list_bytes);
     if (rc != CONDENSA_OK) return rc;
@@ -1001,8 +1015,8 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
     a.merged = per_tensor ? 0 : 1;
 
     if (L.listed) {
-        rc = tb.vec ? launch_listed<false, true>(a, L, workspace_dev, list_group_count, list_bounds, L.n_slots, L.n_groups, results_dev, rq, sampled, st, cfg)
-                    : launch_listed<false, false>(a, L, workspace_dev, list_group_count, list_bounds, L.n_slots, L.n_groups, results_dev, rq, sampled, st, cfg);
+        rc = tb.vec ? launch_listed<false, true>(a, L, workspace_dev, list_shape, L.n_slots, L.n_groups, results_dev, rq, sampled, st, cfg)
+                    : launch_listed<false, false>(a, L, workspace_dev, list_shape, L.n_slots, L.n_groups, results_dev, rq, sampled, st, cfg);
         if (rc != CONDENSA_OK || listed_write) return rc;
     }
     // One density on the window path: selection and apply share one sweep unless theta overwrites the weights.
@@ -1184,9 +1198,8 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::vector<char> lists;
-    u32 list_group_count = 0;
-    bool list_bounds = false;
-    const size_t list_bytes = L.listed ? build_list_table(tb, L, n_tensors, 1, false, true, cfg, &lists, &list_group_count, &list_bounds) : 0;
+    ListShape list_shape;
+    const size_t list_bytes = L.listed ? build_list_table(tb, L, n_tensors, 1, false, true, cfg, &lists, &list_shape) : 0;
     // the selection sweeps read w and lambda only, so their vector path depends on those alone
     bool vec_in = tb.vec;
     for (int t = 0; t < n_tensors; ++t)
@@ -1195,8 +1208,8 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
     const ListRequest rq{od, vec, pq, !in_place_any && cfg[CONDENSA_OPT_FUSED_SWEEP] == 0, pq ? nnz_dev : nullptr, false};
     bool sampled = false;
     if (L.listed)
-        rc = vec_in ? begin_and_sample<true, true>(L, tb, n_tensors, out.data(), out.size(), slot4, 1, mu, workspace_dev, st, lists, list_group_count, rq, cfg, &sampled)
-                    : begin_and_sample<true, false>(L, tb, n_tensors, out.data(), out.size(), slot4, 1, mu, workspace_dev, st, lists, list_group_count, rq, cfg, &sampled);
+        rc = vec_in ? begin_and_sample<true, true>(L, tb, n_tensors, out.data(), out.size(), slot4, 1, mu, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled)
+                    : begin_and_sample<true, false>(L, tb, n_tensors, out.data(), out.size(), slot4, 1, mu, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled);
     if (rc == CONDENSA_OK && !sampled)
         rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slot4, window ? 4 : 1, workspace_dev, st, nullptr, lists.data(), list_bytes);
     if (rc != CONDENSA_OK) return rc;
@@ -1236,8 +1249,8 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
     WindowArgs wargs{};
     FusedRequest fr{od, vec, pq, &wargs};
     if (L.listed) {
-        rc = vec_in ? launch_listed<true, true>(a, L, workspace_dev, list_group_count, list_bounds, 1, 1, result_dev, rq, sampled, st, cfg)
-                    : launch_listed<true, false>(a, L, workspace_dev, list_group_count, list_bounds, 1, 1, result_dev, rq, sampled, st, cfg);
+        rc = vec_in ? launch_listed<true, true>(a, L, workspace_dev, list_shape, 1, 1, result_dev, rq, sampled, st, cfg)
+                    : launch_listed<true, false>(a, L, workspace_dev, list_shape, 1, 1, result_dev, rq, sampled, st, cfg);
         if (rc != CONDENSA_OK || rq.write) return rc;
     } else
         rc = vec_in ? run_selection<true, true>(a, L, workspace_dev, window, 1, 1, result_dev, st, cfg, fuse ? &fr : nullptr)

@@ -1,4 +1,4 @@
-// Listed windows: the selection of ordinary calls (the rule is want_list, either scope) in six or seven launches.
+// Listed windows: the selection of ordinary calls (the rule is want_list, either scope) in three to seven launches.
 //
 // Up to some ten million weights a call is bound by its dependent launches (about 4.5 us each, however little they
 // do) and by how often it reads the weights, which the three histogram sweeps of the radix levels make four times.
@@ -18,7 +18,9 @@
 //   4. k_list_settle ranks these, applies the tie rule, writes state and record and settles them too.  If some ranking
 //      failed (its rank is not inside the window, or a list overflowed) it ranks that population by radix levels over
 //      the weights instead and applies every result again.
-// One workgroup draws some 25 GB/s from memory it did not write, so the lists (10^5 entries) are walked by many.
+// One workgroup draws some 25 GB/s from memory it did not write, so the lists (10^5 entries) are walked by many.  When
+// no population exceeds kListLone elements, its list is short enough for one workgroup to do 3 and 4 alone
+// (k_list_finish): three launches, and a failed ranking stays within that workgroup.
 // Results never depend on the sample.  Section 3.1 (a sparsity turned into a magnitude threshold), Section 3.3 (the
 // C step and the multiplier update), Results (up to ten samples per search share a pass).
 #pragma once
@@ -34,9 +36,11 @@ constexpr int kListSegs = 1024;                  // segments of a ranking's list
 constexpr int kListMaxW = 256;                   // sampling workgroups of one population at most
 constexpr int kListMaxRankings = 4096;
 constexpr int kListBins = 256;                   // bins over a window
-constexpr u32 kListRanked = 1024;                // gathered entries that are ranked by comparing all pairs
-constexpr u32 kListGather = 16384;               // gathered entries of a ranking at most; with more (ties) it fails
+constexpr u32 kListRanked = 1024;                // gathered entries that are held in LDS
+constexpr u32 kListGather = 1u << 18;            // gathered entries of a ranking at most; with more (ties) it fails
 constexpr u32 kListRow = 64;                     // segments are multiples of this many entries
+
+constexpr u64 kListLone = static_cast<u64>(1) << 18;       // populations up to here are finished by one workgroup
 
 // Sampling workgroups of a population of n elements: the window is narrowed as the population grows.  One workgroup leaves a window of up to 8 % of it (10 sd of its rank);
 // 32 about 2 %, 64 about 1 %, 256 about 0.4 % at the cost of one more launch.
@@ -215,15 +219,20 @@ __device__ inline void list_sample(const ListArgs& w, int J, float mu, u32 W, u3
     __shared__ u32 s_want[3 * kMaxJ], s_bin[3 * kMaxJ], s_rem[3 * kMaxJ], s_key[3 * kMaxJ];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int R = 3 * J;
-    const int units = W == 1 ? kListUnits : 1;
-    const int logu = 31 - __clz(static_cast<int>(units * kListThreads * W));     // a power of two
+    // A lone workgroup reads single float4; one of several reads 64-byte lines, four lanes each: the same traffic for four
+    // times the keys (262144 scattered float4 of two arrays took 11 us), and order statistics do not mind neighbours that
+    // resemble each other.
+    const int units = W == 1 ? kListUnits : 1, lanes = W == 1 ? 1 : 4;
+    const int logu = 31 - __clz(static_cast<int>(units * (kListThreads / lanes) * W));     // a power of two
+    const u64 places = (quads + lanes - 1) / lanes;
 
     u32 key[4 * kListUnits], valid = 0;
 #pragma unroll
     for (int i = 0; i < kListUnits; ++i) {
         if (i >= units) break;                   // uniform
-        const u64 u = static_cast<u64>(i * kListThreads + tid) * W + me;
-        const u64 p = quads <= (static_cast<u64>(1) << logu) ? u : (u * quads + __umul64hi(static_cast<u64>(mix32(static_cast<u32>(u))) << 32, quads)) >> logu;
+        const u64 u = static_cast<u64>(i * kListThreads + tid / lanes) * W + me;
+        u64 p = places <= (static_cast<u64>(1) << logu) ? u : (u * places + __umul64hi(static_cast<u64>(mix32(static_cast<u32>(u))) << 32, places)) >> logu;
+        p = p * lanes + tid % lanes;
         float v[4] = {0.f, 0.f, 0.f, 0.f};
         if (p < quads) {
             const u64 c = first_chunk + p / (kChunk / 4);
@@ -417,7 +426,7 @@ __global__ __launch_bounds__(kListThreads) void k_begin_sample(BeginSampleArgs b
 // rank are as many independent draws around the threshold; order statistics W/2 -+ z sqrt(W)/2 of them bound its
 // location with the confidence of z standard deviations, whatever their distribution.  A wavefront finds one order
 // statistic bit by bit, with all W values in its registers.
-constexpr int kBoundsThreads = 512;
+constexpr int kBoundsThreads = 1024;
 __global__ __launch_bounds__(kBoundsThreads) void k_list_bounds(DataArgs a, ListArgs w) {
     __shared__ u32 s_out[3 * kMaxJ];
     __shared__ ListWin s_win[kMaxJ];
@@ -864,8 +873,9 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
 
 // ---- the threshold among the listed keys ---------------------------------------------------------------
 
-// f(there, key, entry) for the entries of ranking s that this wavefront takes: every `stride`-th segment, four at a time
-// (their loads in flight together); called by all lanes, `there` says which hold an entry.
+// f(there, key, entry) for the entries of ranking s that this wavefront takes: every `stride`-th segment, kListDeep rows
+// of four segments at a time (their loads in flight together); called by all lanes, `there` says which hold an entry.
+constexpr u32 kListDeep = 4;
 template <typename F>
 __device__ inline void list_walk(const ListArgs& w, u32 s, const ListRank& rk, u32 first_seg, u32 stride, F&& f) {
     const u32 lane = threadIdx.x & 63u;
@@ -882,14 +892,22 @@ __device__ inline void list_walk(const ListArgs& w, u32 s, const ListRank& rk, u
                 first[b] = rk.base + static_cast<u64>(seg0 + (l + b) * stride) * rk.seg_cap;
                 most = cnt[b] > most ? cnt[b] : most;
             }
-            for (u32 i0 = 0; i0 < most; i0 += 64) {
-                const u32 i = i0 + lane;
-                u32 x[4];
+            for (u32 i0 = 0; i0 < most; i0 += 64 * kListDeep) {
+                u32 x[kListDeep][4];
 #pragma unroll
-                for (u32 b = 0; b < 4; ++b) x[b] = i < cnt[b] ? w.key[first[b] + i] : 0u;
+                for (u32 d = 0; d < kListDeep; ++d)
 #pragma unroll
-                for (u32 b = 0; b < 4; ++b)
-                    if (i0 < cnt[b]) f(i < cnt[b], x[b], first[b] + i);            // uniform
+                    for (u32 b = 0; b < 4; ++b) {
+                        const u32 i = i0 + 64 * d + lane;
+                        x[d][b] = i < cnt[b] ? w.key[first[b] + i] : 0u;
+                    }
+#pragma unroll
+                for (u32 d = 0; d < kListDeep; ++d)
+#pragma unroll
+                    for (u32 b = 0; b < 4; ++b) {
+                        const u32 i = i0 + 64 * d + lane;
+                        if (i0 + 64 * d < cnt[b]) f(i < cnt[b], x[d][b], first[b] + i);           // uniform
+                    }
             }
         }
     }
@@ -914,36 +932,93 @@ __global__ __launch_bounds__(kBlock) void k_list_hist(DataArgs a, ListArgs w) {
     if (v) atomicAdd(&w.hist[static_cast<u64>(s) * kListBins + threadIdx.x], v);
 }
 
-// The outputs of one listed element, with the decision it should have had.
-template <bool LC, bool PQ>
-__device__ inline void list_fix(const DataArgs& a, const ListArgs& w, u32 j, u32 idx, bool keep, int* nz) {
-    const u32 c = idx / kChunk;
-    const u32 t = a.chunk_map[c];
-    const TensorDesc& td = a.td[t];
-    const u64 e = static_cast<u64>(idx) - td.chunk_start * kChunk;
-    const OutDesc o = w.out[static_cast<u64>(j) * a.n_tensors + t];
-    const float wv = td.w[e];
-    if (LC) {
-        const float lv = td.lam[e];
-        const float x = lc_shift(wv, lv, a.mu);
-        float th = keep ? x : 0.0f;
-        if (PQ) {
-            const u16 hv = f32_to_f16_rne(x), h = keep ? hv : static_cast<u16>(0);
-            th = f16_bits_to_f32(h);
-            if (o.theta16) o.theta16[e] = h;
-            if ((hv & 0x7FFFu) != 0) *nz += keep ? 1 : -1;
-        }
-        const float p = __fmul_rn(a.mu, __fsub_rn(wv, th));
-        const float ln = __fsub_rn(lv, p);
-        if (o.theta) o.theta[e] = th;
-        td.lam_out[e] = ln;
-        if (td.grad) td.grad[e] = __fsub_rn(p, ln);
-    } else {
-        const float th = keep ? wv : 0.0f;
-        if (o.theta) o.theta[e] = th;
-        if (o.theta16) o.theta16[e] = f32_to_f16_rne(th);
+// The outputs of up to B listed elements, with the decision each should have had.  The dependent loads of the elements
+// (tensor, its pointers, the inputs) are issued side by side: one after the other they take some 3 us an element.
+template <bool LC, bool PQ, int B>
+__device__ inline void list_fix(const DataArgs& a, const ListArgs& w, u32 j, const u32 (&idx)[B], const bool (&keep)[B], const bool (&on)[B], int* nz) {
+    u32 t[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) t[b] = on[b] ? a.chunk_map[idx[b] / kChunk] : 0u;
+    const float* wp[B];
+    const float* lp[B];
+    float* lo[B];
+    float* gr[B];
+    u64 e[B];
+    OutDesc o[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        const TensorDesc& td = a.td[t[b]];
+        wp[b] = td.w;
+        if (LC) { lp[b] = td.lam; lo[b] = td.lam_out; gr[b] = td.grad; }
+        e[b] = static_cast<u64>(idx[b]) - td.chunk_start * kChunk;
+        o[b] = w.out[static_cast<u64>(j) * a.n_tensors + t[b]];
     }
-    if (o.mask) o.mask[e] = keep ? 1 : 0;
+    float wv[B], lv[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        wv[b] = on[b] ? wp[b][e[b]] : 0.0f;
+        lv[b] = LC && on[b] ? lp[b][e[b]] : 0.0f;
+    }
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        if (!on[b]) continue;
+        if (LC) {
+            const float x = lc_shift(wv[b], lv[b], a.mu);
+            float th = keep[b] ? x : 0.0f;
+            if (PQ) {
+                const u16 hv = f32_to_f16_rne(x), h = keep[b] ? hv : static_cast<u16>(0);
+                th = f16_bits_to_f32(h);
+                if (o[b].theta16) o[b].theta16[e[b]] = h;
+                if ((hv & 0x7FFFu) != 0) *nz += keep[b] ? 1 : -1;
+            }
+            const float p = __fmul_rn(a.mu, __fsub_rn(wv[b], th));
+            const float ln = __fsub_rn(lv[b], p);
+            if (o[b].theta) o[b].theta[e[b]] = th;
+            lo[b][e[b]] = ln;
+            if (gr[b]) gr[b][e[b]] = __fsub_rn(p, ln);
+        } else {
+            const float th = keep[b] ? wv[b] : 0.0f;
+            if (o[b].theta) o[b].theta[e[b]] = th;
+            if (o[b].theta16) o[b].theta16[e[b]] = f32_to_f16_rne(th);
+        }
+        if (o[b].mask) o[b].mask[e[b]] = keep[b] ? 1 : 0;
+    }
+}
+template <bool LC, bool PQ>
+__device__ inline void list_fix_one(const DataArgs& a, const ListArgs& w, u32 j, u32 idx, bool keep, int* nz) {
+    const u32 i1[1] = {idx};
+    const bool k1[1] = {keep}, on1[1] = {true};
+    list_fix<LC, PQ, 1>(a, w, j, i1, k1, on1, nz);
+}
+// Places in an LDS queue for the lanes that want one: one update of its counter per wavefront.
+__device__ inline u32 wave_push(u32* counter, bool wanted) {
+    const u64 m = __ballot(wanted);
+    u32 at = 0;
+    if (m != 0) {                                          // uniform
+        const int leader = __ffsll(static_cast<long long>(m)) - 1;
+        if (static_cast<int>(threadIdx.x & 63u) == leader) at = atomicAdd(counter, static_cast<u32>(__popcll(m)));
+        at = __shfl(at, leader, 64);
+    }
+    return at + lanes_below(m);
+}
+
+// The queued wrong decisions of a workgroup: entry of the ranking's list, top bit = the right decision.
+template <bool LC, bool PQ, int THREADS>
+__device__ inline void list_fix_queue(const DataArgs& a, const ListArgs& w, u32 j, const u32* __restrict__ ids, const u32* queue, u32 n_q, int* nz) {
+    constexpr int B = 4;
+    for (u32 q0 = threadIdx.x; q0 < n_q; q0 += THREADS * B) {
+        u32 idx[B];
+        bool keep[B], on[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const u32 q = q0 + b * THREADS;
+            on[b] = q < n_q;
+            const u32 v = on[b] ? queue[q] : 0u;
+            keep[b] = (v >> 31) != 0;
+            idx[b] = on[b] ? ids[v & 0x7FFFFFFFu] : 0u;
+        }
+        list_fix<LC, PQ, B>(a, w, j, idx, keep, on, nz);
+    }
 }
 
 // Every workgroup finds the bin of rank k - above from the counts.  Elements in the bins beside it are settled here:
@@ -998,10 +1073,10 @@ __global__ __launch_bounds__(kBlock) void k_list_gather(DataArgs a, ListArgs w) 
     u32* gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
     u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
     list_walk(w, s, rk, part * (kBlock / 64) + (tid >> 6), w.parts * (kBlock / 64), [&](bool there, u32 key, u64 at) {
-        if (!there) return;
         const u32 b = (key - lo) >> shift;
-        if (b == bin) {
-            const u32 f = atomicAdd(&s_f, 1u);
+        const bool found = there && b == bin, wrong = w.write && there && b != bin && (b > bin) != (b >= mid_bin);
+        const u32 f = wave_push(&s_f, found);
+        if (found) {
             if (f < kFound) {
                 s_fkey[f] = key;
                 s_fidx[f] = static_cast<u32>(at - rk.base);
@@ -1009,16 +1084,17 @@ __global__ __launch_bounds__(kBlock) void k_list_gather(DataArgs a, ListArgs w) 
                 const u32 to = atomicAdd(&w.gathered[s], 1u);
                 if (to < w.gather_cap) { gkey[to] = key; gidx[to] = w.idx[at]; }
             }
-        } else if (w.write && (b > bin) != (b >= mid_bin)) {
-            const u32 q = atomicAdd(&s_n, 1u);
+        }
+        const u32 q = wave_push(&s_n, wrong);
+        if (wrong) {
             if (q < kQueue) s_queue[q] = static_cast<u32>(at - rk.base) | (b > bin ? 0x80000000u : 0u);
-            else            list_fix<LC, PQ>(a, w, j, w.idx[at], b > bin, &nz);
+            else            list_fix_one<LC, PQ>(a, w, j, w.idx[at], b > bin, &nz);
         }
     });
     __syncthreads();
     const u32 n_f = s_f < kFound ? s_f : kFound, n_q = s_n < kQueue ? s_n : kQueue;
     if (tid == 0 && n_f) s_base = atomicAdd(&w.gathered[s], n_f);
-    for (u32 q = tid; q < n_q; q += kBlock) list_fix<LC, PQ>(a, w, j, w.idx[rk.base + (s_queue[q] & 0x7FFFFFFFu)], (s_queue[q] >> 31) != 0, &nz);
+    list_fix_queue<LC, PQ, kBlock>(a, w, j, w.idx + rk.base, s_queue, n_q, &nz);
     __syncthreads();
     for (u32 f = tid; f < n_f; f += kBlock) {
         const u32 to = s_base + f;
@@ -1047,20 +1123,41 @@ __device__ inline condensa_select select_record(const Slot& slot, bool ranked, u
     return out;
 }
 
+constexpr u32 kListPairs = 256;                  // entries ranked by comparing all pairs
 struct ListShared {        // LDS of list_rank
-    u32 key[kListRanked], idx[kListRanked];
-    u32 hist[kBlock];
-    u64 wave[kBlock / 64];
+    u32 key[kListRanked], idx[kListRanked];      // the gathered entries, when they fit
+    u32 pkey[kListPairs], pidx[kListPairs];
+    __align__(16) u32 hist[kListBins];
+    u32 wave[kListThreads / 64];
     u32 T, r, n_tie, last, pick, rem, n;
 };
 
 // The bin of sh.hist that holds rank r (from the top, or from the bottom), the rank inside it and its count.
 __device__ inline void list_pick(ListShared& sh, bool from_top, u32 r, u32* bin, u32* rem, u32* count) {
-    const u32 b = from_top ? kBlock - 1 - threadIdx.x : threadIdx.x;
-    const u32 c = sh.hist[b];
-    u64 total;
-    const u64 before = block_excl_scan_u64(c, sh.wave, &total);
-    if (before < r && r <= before + c) { sh.pick = b; sh.rem = r - static_cast<u32>(before); sh.n = c; }
+    if (threadIdx.x < 64) {
+        const u32 lane = threadIdx.x;
+        const uint4 c4 = *reinterpret_cast<const uint4*>(sh.hist + (from_top ? 252 - 4 * lane : 4 * lane));
+        const u32 c[4] = {from_top ? c4.w : c4.x, from_top ? c4.z : c4.y, from_top ? c4.y : c4.z, from_top ? c4.x : c4.w};
+        u32 incl = c[0] + c[1] + c[2] + c[3];
+        const u32 sum = incl;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const u32 up = __shfl_up(incl, d, 64);
+            if (static_cast<int>(lane) >= d) incl += up;
+        }
+        u32 before = incl - sum;
+        if (before < r && r <= incl) {
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) {
+                if (before < r && r <= before + c[i]) {
+                    sh.pick = from_top ? 255 - 4 * lane - i : 4 * lane + i;
+                    sh.rem = r - before;
+                    sh.n = c[i];
+                }
+                before += c[i];
+            }
+        }
+    }
     __syncthreads();
     *bin = sh.pick;
     *rem = sh.rem;
@@ -1071,66 +1168,72 @@ __device__ inline void list_pick(ListShared& sh, bool from_top, u32 r, u32* bin,
 // One workgroup: the element at rank `want` of the gathered ones (key descending, then index ascending) is the last
 // one kept; state, record and the outputs of gathered elements whose decision was wrong.  One more counting level leaves
 // a handful, which are ranked by comparing all pairs.
-template <bool LC, bool PQ>
-__device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShared& sh, u32 s, condensa_select* results, int n_groups) {
+// `want` 0: the ranking failed.  `n` gathered entries: in sh.key / sh.idx when `in_lds`, else at gkey / gidx.  `nz`: this
+// thread's corrections so far of the count of non-zero codes.
+template <bool LC, bool PQ, int THREADS>
+__device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShared& sh, u32 s, u32 want, u32 n, bool in_lds, int nz,
+                                 condensa_select* results, int n_groups) {
     const u32 tid = threadIdx.x;
     Slot& slot = a.slots[s];
     const u32 g = s / a.J, j = s - g * a.J;
     condensa_select* record = results + static_cast<u64>(j) * n_groups + g;
-    int nz = 0;
-    u32 want = w.bin_want[s];
-    if (slot.state != kSelecting) {                        // k == 0: nothing is kept, and the sweep kept nothing
+    const u32 want_all = want;
+    const bool slot_selecting = slot.state == kSelecting;
+    if (!slot_selecting) {                                 // k == 0: nothing is kept, and the sweep kept nothing
         if (tid == 0) *record = select_record(slot, false, 0, 0, 0, 0, slot.path);
     } else if (want != 0) {                                // 0: it failed
-        const u32 n = w.gathered[s];
-        const u32* __restrict__ keys = w.gkey + static_cast<u64>(s) * w.gather_cap;
-        const u32* __restrict__ ids = w.gidx + static_cast<u64>(s) * w.gather_cap;
+        const u32* __restrict__ gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
+        const u32* __restrict__ gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
+        if (!in_lds && n <= kListRanked) {
+            for (u32 i = tid; i < n; i += THREADS) { sh.key[i] = gkey[i]; sh.idx[i] = gidx[i]; }
+            in_lds = true;
+        }
+        auto key_of = [&](u32 i) { return in_lds ? sh.key[i] : gkey[i]; };
+        auto idx_of = [&](u32 i) { return in_lds ? sh.idx[i] : gidx[i]; };
         const ListWin win = w.win[s];
         const u32 bits = win.bins & 0xFFu;                 // low bits of key - lo that the window's bins leave open
         const u32 sub = bits > 8 ? bits - 8 : 0;
-        sh.hist[tid] = 0;
+        const u32 mask = (1u << (bits - sub)) - 1u;        // at most eight bits
+        if (tid < static_cast<u32>(kListBins)) sh.hist[tid] = 0;
+        if (tid == 0) sh.r = 0;
         __syncthreads();
-        for (u32 i = tid; i < n; i += kBlock) atomicAdd(&sh.hist[((keys[i] - win.lo) >> sub) & ((1u << (bits - sub)) - 1u)], 1u);
+        for (u32 i = tid; i < n; i += THREADS) atomicAdd(&sh.hist[((key_of(i) - win.lo) >> sub) & mask], 1u);
         __syncthreads();
         u32 bin, in_bin;
         list_pick(sh, true, want, &bin, &want, &in_bin);
-        const u32 mask = (1u << (bits - sub)) - 1u;        // at most eight bits
-        if (tid == 0) sh.n = 0;
-        __syncthreads();
-        const bool pairs = in_bin <= kListRanked;          // uniform
-        if (pairs) {
-            for (u32 i = tid; i < n; i += kBlock) {
-                const u32 key = keys[i];
+        if (in_bin <= kListPairs) {                        // uniform
+            for (u32 i = tid; i < n; i += THREADS) {
+                const u32 key = key_of(i);
                 if ((((key - win.lo) >> sub) & mask) == bin) {
-                    const u32 p = atomicAdd(&sh.n, 1u);
-                    sh.key[p] = key;
-                    sh.idx[p] = ids[i];
+                    const u32 p = atomicAdd(&sh.r, 1u);
+                    sh.pkey[p] = key;
+                    sh.pidx[p] = idx_of(i);
                 }
             }
             __syncthreads();
-            for (u32 i = tid; i < in_bin; i += kBlock) {
-                const u32 key = sh.key[i], idx = sh.idx[i];
+            if (tid < in_bin) {
+                const u32 key = sh.pkey[tid], idx = sh.pidx[tid];
                 u32 higher = 0, same = 0, same_before = 0;
                 for (u32 e = 0; e < in_bin; ++e) {
-                    const u32 k2 = sh.key[e];
+                    const u32 k2 = sh.pkey[e];
                     higher += k2 > key ? 1u : 0u;
                     same += k2 == key ? 1u : 0u;
-                    same_before += (k2 == key && sh.idx[e] < idx) ? 1u : 0u;
+                    same_before += (k2 == key && sh.pidx[e] < idx) ? 1u : 0u;
                 }
-                if (higher + same_before + 1 == want) { sh.T = key; sh.r = want - higher; sh.n_tie = same; sh.last = idx; }
+                if (higher + same_before + 1 == want) { sh.T = key; sh.rem = want - higher; sh.n_tie = same; sh.last = idx; }
             }
         } else {
             // many share those bits too (ties above all): radix levels on the whole key, then on the index
-            u32 prefix[2] = {0, 0}, rem = w.bin_want[s], n_eq = 0, b;
+            u32 prefix[2] = {0, 0}, rem = want_all, n_eq = 0, b;
             for (int part = 0; part < 2; ++part) {         // 0: key, highest first; 1: index among equal keys, lowest first
                 if (part == 1 && tid == 0) { sh.T = prefix[0]; sh.r = rem; sh.n_tie = n_eq; }
                 for (int shift = 24; shift >= 0; shift -= 8) {
-                    sh.hist[tid] = 0;
+                    if (tid < static_cast<u32>(kListBins)) sh.hist[tid] = 0;
                     __syncthreads();
-                    for (u32 i = tid; i < n; i += kBlock) {
-                        const u32 key = keys[i];
+                    for (u32 i = tid; i < n; i += THREADS) {
+                        const u32 key = key_of(i);
                         if (part == 1 && key != prefix[0]) continue;
-                        const u32 v = part == 0 ? key : ids[i];
+                        const u32 v = part == 0 ? key : idx_of(i);
                         if (shift == 24 || (v >> (shift + 8)) == (prefix[part] >> (shift + 8))) atomicAdd(&sh.hist[(v >> shift) & 255u], 1u);
                     }
                     __syncthreads();
@@ -1138,36 +1241,205 @@ __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShare
                     prefix[part] |= b << shift;
                 }
             }
-            if (tid == 0) sh.last = prefix[1];
+            if (tid == 0) { sh.last = prefix[1]; sh.rem = sh.r; }
         }
         __syncthreads();
         const u32 T = sh.T, last = sh.last;
-        if (w.write)
-            for (u32 i = tid; i < n; i += kBlock) {
-                const u32 key = keys[i];
-                if (key >= win.mid ? key > T : key < T) continue;        // decided without the index
-                const u32 idx = ids[i];
-                const bool keep = key > T || (key == T && idx <= last);
-                if (keep != (key >= win.mid)) list_fix<LC, PQ>(a, w, j, idx, keep, &nz);
+        if (w.write) {
+            constexpr int B = 4;
+            for (u32 i0 = tid; i0 < n; i0 += THREADS * B) {
+                u32 idx[B];
+                bool keep[B], on[B];
+#pragma unroll
+                for (int b = 0; b < B; ++b) {
+                    const u32 i = i0 + b * THREADS;
+                    on[b] = i < n;
+                    const u32 key = on[b] ? key_of(i) : 0u;
+                    idx[b] = on[b] ? idx_of(i) : 0u;
+                    keep[b] = key > T || (key == T && idx[b] <= last);
+                    on[b] = on[b] && keep[b] != (key >= win.mid);
+                }
+                list_fix<LC, PQ, B>(a, w, j, idx, keep, on, &nz);
             }
+        }
         if (tid == 0) {
             u64 tie_end = slot.n;
-            if (sh.r < sh.n_tie) {
+            if (sh.rem < sh.n_tie) {
                 const TensorDesc& td = a.td[a.chunk_map[last / kChunk]];
                 tie_end = static_cast<u64>(last) - td.chunk_start * kChunk + (a.per_tensor ? 0 : td.flat_start) + 1;
             }
-            slot.prefix = T; slot.remaining = sh.r; slot.n_tie = sh.n_tie; slot.need_tie = 0; slot.tie_end = tie_end; slot.state = kDone;
-            *record = select_record(slot, true, T, sh.r, sh.n_tie, tie_end, slot.path);
+            slot.prefix = T; slot.remaining = sh.rem; slot.n_tie = sh.n_tie; slot.need_tie = 0; slot.tie_end = tie_end; slot.state = kDone;
+            *record = select_record(slot, true, T, sh.rem, sh.n_tie, tie_end, slot.path);
         }
     }
-    if (PQ && w.nnz_out && w.write) {                      // the sweep's count, corrected by the two passes over the list
-        u64 v = static_cast<u64>(static_cast<long long>(nz)), total;
-        for (u32 i = tid; i < static_cast<u32>(kListSegs); i += kBlock) v += w.nnz[i];
+    if (PQ && w.nnz_out && w.write && (slot_selecting ? want_all != 0 : true)) {     // the sweep's count, corrected by the passes over the list
+        u32 v = static_cast<u32>(nz), total;               // modulo 2^32: the sum itself is smaller
+        for (u32 i = tid; i < static_cast<u32>(kListSegs); i += THREADS) v += w.nnz[i];
         __syncthreads();
-        block_excl_scan_u64(v, sh.wave, &total);
-        if (tid == 0) *w.nnz_out = total + a.ctl->nnz_delta;
+        wg_incl_scan_u32<THREADS>(v, sh.wave, &total);
+        if (tid == 0) *w.nnz_out = static_cast<u64>(total + static_cast<u32>(a.ctl->nnz_delta));
     }
     __syncthreads();                                       // the shared words are free for the next ranking
+}
+
+// Rankings of populations of at most kListLone elements: one workgroup each does the counting, the gathering and the
+// ranking on its list, and a failed ranking by itself (it reads the population a few times over: a megabyte or so).
+// 22 thousand listed keys of a 1024x1024 matrix: see the measurements beside the launch rule.
+template <bool LC, bool PQ>
+__global__ __launch_bounds__(kListThreads) void k_list_finish(DataArgs a, ListArgs w, condensa_select* results, int n_groups) {
+    constexpr u32 kQueue = 4096;
+    __shared__ ListShared sh;
+    __shared__ __align__(8) u32 s_big[kQueue];             // queue of wrong decisions; the failed case: a histogram of kBins
+    __shared__ u32 s_n, s_f, s_over, s_want, s_bin, s_found;
+    __shared__ u64 s_rem, s_cnt;
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    constexpr u32 kWaves = kListThreads / 64;
+    const u32 s = blockIdx.x;
+    const ListRank rk = w.rank[s];
+    const ListWin win = w.win[s];
+    const u32 g = s / a.J, j = s - g * a.J;
+    Slot& slot = a.slots[s];
+    int nz = 0;
+    u32 want = 0, n = 0;
+    bool in_lds = false;
+    const bool selecting = slot.state == kSelecting;
+    if (selecting) {                                       // uniform
+        const u64 cw = tid < rk.n_segs ? w.cnt[static_cast<u64>(s) * w.max_segs + tid] : 0;       // n_segs <= kListSegs == kListThreads
+        const u32 k = static_cast<u32>(slot.k);
+        if (tid < static_cast<u32>(kListBins)) sh.hist[tid] = 0;
+        if (tid == 0) { s_n = 0; s_f = 0; s_over = 0; s_want = 0; }
+        __syncthreads();
+        if (static_cast<u32>(cw) > rk.seg_cap) s_over = 1;
+        u32 kept, listed;
+        wg_incl_scan_u32<kListThreads>(static_cast<u32>(cw >> 32), sh.wave, &kept);
+        wg_incl_scan_u32<kListThreads>(static_cast<u32>(cw), sh.wave, &listed);
+        const u32 lo = win.lo, shift = win.bins & 0xFFu, mid_bin = win.bins >> 8;
+        list_walk(w, s, rk, wave, kWaves, [&](bool there, u32 key, u64) {
+            if (there) atomicAdd(&sh.hist[(key - lo) >> shift], 1u);
+        });
+        __syncthreads();
+        if (wave == 0) {                                   // listed keys from the estimate on
+            u32 gt = 0;
+            for (u32 b = lane; b < static_cast<u32>(kListBins); b += 64) gt += b >= mid_bin ? sh.hist[b] : 0u;
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) gt += __shfl_xor(gt, d, 64);
+            const u32 above = kept - gt;                   // keys above the window
+            if (lane == 0 && s_over == 0 && kept >= gt && above < k && k - above <= listed) s_want = k - above;
+        }
+        __syncthreads();
+        want = s_want;
+        if (want != 0) {                                   // uniform
+            u32 bin;
+            list_pick(sh, true, want, &bin, &want, &n);
+            if (n > w.gather_cap) want = 0;
+            u32* gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
+            u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
+            const u32* __restrict__ ids = w.idx + rk.base;
+            in_lds = n <= kListRanked;
+            if (want != 0) {
+                list_walk(w, s, rk, wave, kWaves, [&](bool there, u32 key, u64 at) {
+                    const u32 b = (key - lo) >> shift, entry = static_cast<u32>(at - rk.base);
+                    const bool found = there && b == bin, wrong = w.write && there && b != bin && (b > bin) != (b >= mid_bin);
+                    const u32 f = wave_push(&s_f, found);  // n of them; their indices are fetched below, side by side
+                    if (found) {
+                        if (in_lds) { sh.key[f] = key; sh.idx[f] = entry; }
+                        else        { gkey[f] = key; gidx[f] = entry; }
+                    }
+                    const u32 q = wave_push(&s_n, wrong);
+                    if (wrong) {
+                        if (q < kQueue) s_big[q] = entry | (b > bin ? 0x80000000u : 0u);
+                        else            list_fix_one<LC, PQ>(a, w, j, ids[entry], b > bin, &nz);
+                    }
+                });
+                __syncthreads();
+                if (in_lds) for (u32 f = tid; f < n; f += kListThreads) sh.idx[f] = ids[sh.idx[f]];
+                else        for (u32 f = tid; f < n; f += kListThreads) gidx[f] = ids[gidx[f]];
+                list_fix_queue<LC, PQ, kListThreads>(a, w, j, ids, s_big, s_n < kQueue ? s_n : kQueue, &nz);
+                __threadfence_block();                     // the gathered entries are read by other threads below
+                __syncthreads();
+            }
+        }
+    }
+    list_rank<LC, PQ, kListThreads>(a, w, sh, s, want, n, in_lds, nz, results, n_groups);
+    if (!selecting || want != 0) return;
+    // failed: radix levels over the population, the tie rule, and every output again
+    const u64 cb = a.per_tensor ? a.td[g].chunk_start : 0, ce = a.per_tensor ? a.td[g + 1].chunk_start : a.n_chunks;
+    constexpr int kRun = kChunk / kListThreads;            // consecutive elements per thread
+    auto keys_of = [&](u64 c, u32* key) -> int {           // keys of this thread's run of chunk c; how many exist
+        const TensorDesc& td = a.td[a.chunk_map[c]];
+        const u64 e0 = (c - td.chunk_start) * kChunk + tid * kRun;
+        int have = 0;
+#pragma unroll
+        for (int i = 0; i < kRun; ++i)
+            if (e0 + i < td.n) { key[i] = mag_key(LC ? lc_shift(td.w[e0 + i], td.lam[e0 + i], a.mu) : td.w[e0 + i]); have = i + 1; }
+        return have;
+    };
+    u64 rem = slot.k, n_tie = 0;
+    u32 T = 0;
+    for (int level = 0; level < n_levels(31); ++level) {
+        const Level L = level_of(31, level);
+        const int nb = 1 << L.bits;
+        for (int i = tid; i < kBins; i += kListThreads) s_big[i] = 0;
+        if (tid == 0) s_found = 0;
+        __syncthreads();
+        for (u64 c = cb; c < ce; ++c) {
+            u32 key[kRun];
+            const int have = keys_of(c, key);
+            for (int i = 0; i < have; ++i)
+                if (((static_cast<u64>(key[i]) ^ T) >> L.hi_shift) == 0) atomicAdd(&s_big[(key[i] >> L.shift) & (nb - 1)], 1u);
+        }
+        __syncthreads();
+        if (wave == 0) wave_pick_desc(s_big, nb, rem, &s_bin, &s_rem, &s_cnt, &s_found);
+        __syncthreads();
+        T |= s_bin << L.shift;
+        rem = s_rem;
+        n_tie = s_cnt;
+        __syncthreads();
+    }
+    u64 tie_end = slot.n;
+    if (rem < n_tie) {                                     // uniform: the chunk and the element that end the kept ties
+        u64 cum = 0;
+        for (u64 c = cb; c < ce; ++c) {
+            u32 key[kRun], hits = 0, total;
+            const int have = keys_of(c, key);
+            for (int i = 0; i < have; ++i) hits += key[i] == T ? 1u : 0u;
+            const u32 before = wg_incl_scan_u32<kListThreads>(hits, sh.wave, &total) - hits;
+            if (cum + total >= rem) {                      // uniform
+                u64 seen = cum + before;
+                const TensorDesc& td = a.td[a.chunk_map[c]];
+                for (int i = 0; i < have; ++i)
+                    if (key[i] == T && ++seen == rem) s_rem = (c - td.chunk_start) * kChunk + tid * kRun + i + (a.per_tensor ? 0 : td.flat_start) + 1;
+                break;
+            }
+            cum += total;
+        }
+        __syncthreads();
+        tie_end = s_rem;
+    }
+    u32 codes = 0;
+    if (w.write)
+        for (u64 c = cb; c < ce; ++c) {
+            u32 key[kRun];
+            const int have = keys_of(c, key);
+            const TensorDesc& td = a.td[a.chunk_map[c]];
+            const u64 e0 = (c - td.chunk_start) * kChunk + tid * kRun, flat = e0 + (a.per_tensor ? 0 : td.flat_start);
+            for (int i = 0; i < have; ++i) {
+                const bool keep = keep_rule(key[i], T, flat + i, tie_end);
+                int dummy = 0;
+                list_fix_one<LC, PQ>(a, w, j, static_cast<u32>(c) * kChunk + tid * kRun + i, keep, &dummy);
+                if (PQ && keep && (f32_to_f16_rne(lc_shift(td.w[e0 + i], td.lam[e0 + i], a.mu)) & 0x7FFFu) != 0) ++codes;
+            }
+        }
+    __syncthreads();
+    if (PQ && w.nnz_out && w.write) {
+        u32 total;
+        wg_incl_scan_u32<kListThreads>(codes, sh.wave, &total);
+        if (tid == 0) *w.nnz_out = total;
+    }
+    if (tid == 0) {
+        slot.prefix = T; slot.remaining = rem; slot.n_tie = n_tie; slot.need_tie = 0; slot.tie_end = tie_end; slot.state = kDone;
+        results[static_cast<u64>(j) * n_groups + g] = select_record(slot, true, T, rem, n_tie, tie_end, 3);
+    }
 }
 
 // The failed case: ranks the populations that the windows did not resolve by three radix levels over the weights, then applies every
@@ -1208,7 +1480,7 @@ __global__ __launch_bounds__(kBlock) void k_list_settle(DataArgs a, ListArgs w, 
     __shared__ ListShared s_rank;
     const u32 n_fail = w.fb->failed;                       // final: an earlier kernel counted
     if (n_fail == 0) {
-        for (u32 s = blockIdx.x; s < static_cast<u32>(w.n_rankings); s += gridDim.x) list_rank<LC, PQ>(a, w, s_rank, s, results, n_groups);
+        for (u32 s = blockIdx.x; s < static_cast<u32>(w.n_rankings); s += gridDim.x) list_rank<LC, PQ, kBlock>(a, w, s_rank, s, w.bin_want[s], w.gathered[s], false, 0, results, n_groups);
         return;
     }
     const int tid = threadIdx.x;
@@ -1230,7 +1502,7 @@ __global__ __launch_bounds__(kBlock) void k_list_settle(DataArgs a, ListArgs w, 
         const u32 phase = s_ticket / G, piece = s_ticket % G;
         if (phase >= phases) return;                       // every workgroup gets here: tickets only grow
         if (phase == 0) {
-            for (u32 s = piece; s < static_cast<u32>(w.n_rankings); s += G) list_rank<LC, PQ>(a, w, s_rank, s, results, n_groups);
+            for (u32 s = piece; s < static_cast<u32>(w.n_rankings); s += G) list_rank<LC, PQ, kBlock>(a, w, s_rank, s, w.bin_want[s], w.gathered[s], false, 0, results, n_groups);
         } else if (phase < rank_phases) {
             const u32 f = (phase - 1) / 5, step = (phase - 1) % 5;
             const u32 r = w.fail_list[f];
