@@ -221,28 +221,31 @@ static u64 window_cand_capacity(u64 N, int J, const Config& cfg) {
     return c;
 }
 
-// Which selection a call takes.  GLOBAL scope: sampled window or radix levels?  Measured (one MI355X, 2^24..2^30
-// weights, 1/4/10 densities): the radix levels cost three sweeps whatever the number of densities and ~50 us of
-// fixed work; the window path costs one sweep, ~0.2 ms of small kernels, and candidate lists and a sweep that grow
-// with the number of densities.  One density breaks even near 2^26 element reads, four near 2^27.5, ten near 2^30.
-static bool want_window(u64 N, bool per_tensor, int J, bool lc, const Config& cfg) {
+// Which selection a call takes when its configuration does not say.  Listed windows (k_listed.h): PER_TENSOR scope and
+// several densities while the lists' 32-bit indices last (four densities: 2^26 weights 209 us against 461 with the
+// windows of several densities and 417-500 with radix levels, 2^28 weights 726 against 1152 and 1954).  One density: up to
+// the size where its lists, in proportion to the population, cost more than the sampled window's deeper ranking does
+// (L-C step of 2^27 weights 509-531 us against 550-566, of 2^28 1004-1036 against 972-1003; pruning 295 against 315 and
+// 561 against 511).  Sampled window (k_window.h, k_fused.h): one density beyond that, several beyond 32-bit indices.
+// Radix levels: where neither applies, and for more densities than two on few weights, where each list is short and its
+// ranking's launches are not (10 densities: 46 thousand weights 66 us listed, 56 by levels; 93 thousand 67 and 58; 233 thousand
+// 68 and 72.  4 densities: 17 thousand 46 and 42; 46 thousand 45.7 and 46.3.  2: 17 thousand 37 and 40).
+static bool list_fits(u64 N, int n_tensors, int n_slots) {
+    return N > 0 && n_slots <= kListMaxRankings && N + static_cast<u64>(n_tensors) * kChunk < (static_cast<u64>(1) << 32);
+}
+static bool want_list(u64 N, int n_tensors, int n_slots, bool per_tensor, int J, const Config& cfg) {
+    if (cfg[CONDENSA_OPT_SELECT_PATH] != 0 || !list_fits(N, n_tensors, n_slots)) return false;
+    if (per_tensor || J <= 2) return per_tensor || J == 2 || N < (static_cast<u64>(3) << 26);
+    return N >= static_cast<u64>(J) << 14;
+}
+static bool want_window(u64 N, int n_tensors, bool per_tensor, int J, const Config& cfg) {
     if (per_tensor) return false;
     if ((N >> kCandTensorShift) != 0) return false;        // candidates carry their tensor above a 44-bit flat index
     const int64_t mode = cfg[CONDENSA_OPT_SELECT_PATH];
     if (mode == 1) return false;
     if (mode == 2) return N >= 1;
-    u64 need = static_cast<u64>(J) << 26;
-    if (J > 4) need = need * static_cast<u64>(J) / 4;
-    return N * (lc ? 2u : 1u) >= need;
-}
-
-// On the automatic path the calls below the window path's sizes, and those of PER_TENSOR scope, take the listed
-// windows (k_listed.h), whose lists hold 32-bit indices.
-static bool want_list(u64 N, int n_tensors, int n_slots, bool per_tensor, int J, bool lc, const Config& cfg) {
-    if (cfg[CONDENSA_OPT_SELECT_PATH] != 0 || N == 0) return false;
-    if (N + static_cast<u64>(n_tensors) * kChunk >= (static_cast<u64>(1) << 32)) return false;
-    if (n_slots > kListMaxRankings) return false;
-    return per_tensor || !want_window(N, per_tensor, J, lc, cfg);
+    if (list_fits(N, n_tensors, J) && J > 1) return false; // listed, or too few weights for either
+    return N > 0 && !want_list(N, n_tensors, J, per_tensor, J, cfg);
 }
 
 // Segments of the rankings' lists: what their sweep's wavefronts call for (elements per wavefront).
@@ -267,9 +270,9 @@ static u64 list_entries_bound(u64 N, int n_tensors, bool per_tensor, u32 max_seg
     if (shift <= 0 && N < most) most = N;
     return most + static_cast<u64>(kListRow) * max_segs * nt;
 }
-static u32 list_groups(u64 n, const Config& cfg) {         // sampling workgroups of a population
+static u32 list_groups(u64 n, int J, const Config& cfg) {         // sampling workgroups of a population
     const int64_t opt = cfg[CONDENSA_OPT_SAMPLE_LOG2];
-    if (opt <= 0) return list_sample_groups(n);
+    if (opt <= 0) return list_sample_groups(n, J);
     if ((static_cast<u64>(1) << opt) <= static_cast<u64>(kListThreads) * kListUnits * kSampleUnit) return 1;
     u32 w = 32;                                            // fewer draws would leave order statistics no room
     while (w < static_cast<u32>(kListMaxW) && static_cast<u64>(w) * kListThreads * kSampleUnit < (static_cast<u64>(1) << opt)) w *= 2;
@@ -291,9 +294,9 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
     L.slots = off;  off += align_up(static_cast<size_t>(L.n_slots) * sizeof(Slot) + (structure ? 3 : 2 * kMaxJ) * sizeof(Slot));
     L.upload_bytes = off;
     const bool element = op == CONDENSA_OP_PRUNE || op == CONDENSA_OP_LC_STEP;
-    if (element && !no_window && want_list(N, n_tensors, L.n_slots, per_tensor, J, op == CONDENSA_OP_LC_STEP, cfg)) {
+    if (element && !no_window && want_list(N, n_tensors, L.n_slots, per_tensor, J, cfg)) {
         const u64 nt = static_cast<u64>(n_tensors);
-        const u64 groups = per_tensor ? (cfg[CONDENSA_OPT_SAMPLE_LOG2] > 0 ? nt * kListMaxW : nt + (N >> 14) + kListMaxW) : list_groups(N, cfg);
+        const u64 groups = per_tensor ? (cfg[CONDENSA_OPT_SAMPLE_LOG2] > 0 ? nt * kListMaxW : nt + (N >> (J > 1 ? 11 : 13)) + kListMaxW) : list_groups(N, J, cfg);
         L.l_max_segs = list_max_segs(N, L.n_slots, J, op == CONDENSA_OP_LC_STEP);
         const u64 entries = static_cast<u64>(J) * list_entries_bound(N, n_tensors, per_tensor, L.l_max_segs, cfg);
         L.listed = true;
@@ -671,7 +674,7 @@ struct ListRequest {
 struct ListShape {
     u32 groups = 0;        // sampling workgroups
     bool bounds = false;   // some population has several
-    bool lone = true;      // no population is larger than kListLone
+    bool lone = true;      // no population is larger than list_lone
 };
 
 // Host tables of the path: one ListRank per ranking, then (PER_TENSOR) the tensor of every sampling workgroup.
@@ -686,7 +689,7 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
     *shape = ListShape{};
     for (size_t g = 0; g < n_groups; ++g) {
         const u64 n = per_tensor ? tb.td[g].n : tb.N;
-        const u32 w = list_groups(n, cfg);
+        const u32 w = list_groups(n, J, cfg);
         u32 segs = list_segments(n, list_wave_elems(J, lc), L.l_max_segs);
         for (int j = 0; j < J; ++j) {
             ListRank& r = rk[g * J + j];
@@ -700,7 +703,7 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
         }
         if (per_tensor) group_of.insert(group_of.end(), w, static_cast<u32>(g));
         if (w > 1) shape->bounds = true;
-        if (n > kListLone) shape->lone = false;
+        if (n > list_lone(J)) shape->lone = false;
         first += w;
     }
     shape->groups = first;
@@ -712,7 +715,7 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
     return table->size();
 }
 
-static ListArgs list_args(const Layout& L, void* ws, int n_slots, const ListRequest& rq, const Config& cfg) {
+static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const ListRequest& rq, const Config& cfg) {
     ListArgs w{};
     w.rank = at<ListRank>(ws, L.l_rank);
     w.group_of = reinterpret_cast<const u32*>(w.rank + n_slots);
@@ -727,7 +730,11 @@ static ListArgs list_args(const Layout& L, void* ws, int n_slots, const ListRequ
     w.gkey = at<u32>(ws, L.l_gkey);
     w.gidx = at<u32>(ws, L.l_gidx);
     w.gather_cap = L.l_gather_cap;
-    w.parts = n_slots >= 1024 ? 1u : (1024u / n_slots > 64u ? 64u : 1024u / n_slots);
+    // workgroups that walk each list: about a thousand in all, up to 256 for one ranking (20 M weights: 64 take 4.8 us to count
+    // 80 thousand keys, 256 take 7.5; 134 M weights want them all)
+    const u64 by_size = (N >> 19) < 16 ? 16 : ((N >> 19) > 256 ? 256 : N >> 19);
+    const u64 share = n_slots >= 1024 ? 1 : 1024 / static_cast<u64>(n_slots);
+    w.parts = static_cast<u32>(by_size < share ? by_size : share);
     w.cnt = at<u64>(ws, L.l_cnt);
     w.nnz = at<u32>(ws, L.l_nnz);
     w.key = at<u32>(ws, L.l_key);
@@ -745,12 +752,12 @@ static ListArgs list_args(const Layout& L, void* ws, int n_slots, const ListRequ
 // Begins the call and takes the sample in one launch; false when the call is not of that form.
 template <bool LC, bool VEC>
 static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n_tensors, const OutDesc* out, size_t n_out, const Slot* slots,
-                                        int J, float mu, void* ws, hipStream_t st, const std::vector<char>& lists, u32 groups,
-                                        const ListRequest& rq, const Config& cfg, bool* begun) {
+                                        const double* densities, int J, bool per_tensor, float mu, void* ws, hipStream_t st,
+                                        const std::vector<char>& lists, u32 groups, const ListRequest& rq, const Config& cfg, bool* begun) {
     *begun = false;
     const size_t td_bytes = static_cast<size_t>(tb.n_td) * sizeof(TensorDesc), out_bytes = n_out * sizeof(OutDesc),
-                 slot_bytes = static_cast<size_t>(J) * sizeof(Slot);
-    if (n_tensors > kBeginSampleTensors || td_bytes + out_bytes + slot_bytes + lists.size() > kStageBytes) return CONDENSA_OK;
+                 slot_bytes = static_cast<size_t>(L.n_slots) * sizeof(Slot);
+    if (n_tensors > kBeginSampleTensors || groups > 0xFFFFu || td_bytes + out_bytes + slot_bytes + lists.size() > kStageBytes) return CONDENSA_OK;
     PhaseTimer timer(CONDENSA_PHASE_SAMPLE, st, cfg);
     StageImage img;
     const condensa_status rc = img.acquire(td_bytes + out_bytes + slot_bytes + lists.size(), st);
@@ -766,7 +773,11 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
     b.J = J;
     b.mu = mu;
     b.N = tb.N;
-    for (int j = 0; j < J; ++j) b.k[j] = slots[j].k;
+    b.per_tensor = per_tensor ? 1 : 0;
+    for (int j = 0; j < J; ++j) b.density[j] = densities[j];
+    const ListRank* rk = reinterpret_cast<const ListRank*>(lists.data());
+    for (int t = 0; per_tensor && t < n_tensors; ++t) b.group0[t] = static_cast<u16>(rk[static_cast<size_t>(t) * J].group0);
+    b.group0[per_tensor ? n_tensors : 0] = static_cast<u16>(groups);
     for (int t = 0; t < n_tensors; ++t) {
         b.w[t] = tb.td[t].w;
         b.lam[t] = tb.td[t].lam;
@@ -775,7 +786,7 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
     for (int t = 0; t <= n_tensors; ++t) b.chunk_start[t] = static_cast<u32>(tb.td[t].chunk_start);
     const u64 blocks = begin_blocks(b.n_zero, tb.n_chunks) + 1 + groups;
     hipLaunchKernelGGL((k_begin_sample<LC, VEC>), dim3(static_cast<unsigned>(blocks)), dim3(kListThreads), 0, st, b,
-                       list_args(L, ws, J, rq, cfg));
+                       list_args(L, ws, tb.N, L.n_slots, rq, cfg));
     CONDENSA_LAUNCH_CHECK();
     img.commit();
     *begun = true;
@@ -785,7 +796,7 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
 template <bool LC, bool VEC>
 static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* ws, const ListShape& shape, int n_slots, int n_groups,
                                      condensa_select* results, const ListRequest& rq, bool sampled, hipStream_t st, const Config& cfg) {
-    ListArgs w = list_args(L, ws, n_slots, rq, cfg);
+    ListArgs w = list_args(L, ws, a.N, n_slots, rq, cfg);
     const bool vec = VEC && rq.vec_out;
     {
         PhaseTimer timer(CONDENSA_PHASE_SAMPLE, st, cfg);
@@ -962,7 +973,7 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
     rc = check_workspace(workspace_dev, workspace_bytes, L);
     if (rc != CONDENSA_OK) return no_alloc ? CONDENSA_ERR_SIZE : rc;
 
-    const bool window = !no_alloc && want_window(tb.N, per_tensor, J, false, cfg);
+    const bool window = !no_alloc && want_window(tb.N, n_tensors, per_tensor, J, cfg);
     Slot* slots = arena.array<Slot>(static_cast<size_t>(L.n_slots) + 3);
     char* fixed = no_alloc ? arena.array<char>(L.upload_bytes) : nullptr;
     if (!slots || (no_alloc && !fixed)) return CONDENSA_ERR_SIZE;
@@ -982,9 +993,9 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
     const bool listed_write = L.listed && any_out && !in_place_any && cfg[CONDENSA_OPT_FUSED_SWEEP] == 0;
     const ListRequest rq{od, vec, false, listed_write, nullptr, masks_wide && !theta && !theta_f16};
     bool sampled = false;
-    if (L.listed && !per_tensor)
-        rc = tb.vec ? begin_and_sample<false, true>(L, tb, n_tensors, out, n_out, slots, J, 0.0f, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled)
-                    : begin_and_sample<false, false>(L, tb, n_tensors, out, n_out, slots, J, 0.0f, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled);
+    if (L.listed)
+        rc = tb.vec ? begin_and_sample<false, true>(L, tb, n_tensors, out, n_out, slots, densities, J, per_tensor, 0.0f, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled)
+                    : begin_and_sample<false, false>(L, tb, n_tensors, out, n_out, slots, densities, J, per_tensor, 0.0f, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled);
     if (rc == CONDENSA_OK && !sampled)
         rc = begin_call(L, tb, n_tensors, out, n_out, slots, n_up_slots, workspace_dev, st, fixed, lists.data(), list_bytes);
     if (rc != CONDENSA_OK) return rc;
@@ -1190,7 +1201,7 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
     if (ranges_conflict(ranges.data(), ranges.size())) return CONDENSA_ERR_ARG;
     rc = check_workspace(workspace_dev, workspace_bytes, L);
     if (rc != CONDENSA_OK) return rc;
-    const bool window = want_window(tb.N, false, 1, true, cfg);
+    const bool window = want_window(tb.N, n_tensors, false, 1, cfg);
     Slot slot4[4];
     Slot& slot = slot4[0];
     init_slot(&slot, tb.N, kept_count(density, tb.N), window || L.listed ? 2u : 1u);
@@ -1208,8 +1219,8 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
     const ListRequest rq{od, vec, pq, !in_place_any && cfg[CONDENSA_OPT_FUSED_SWEEP] == 0, pq ? nnz_dev : nullptr, false};
     bool sampled = false;
     if (L.listed)
-        rc = vec_in ? begin_and_sample<true, true>(L, tb, n_tensors, out.data(), out.size(), slot4, 1, mu, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled)
-                    : begin_and_sample<true, false>(L, tb, n_tensors, out.data(), out.size(), slot4, 1, mu, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled);
+        rc = vec_in ? begin_and_sample<true, true>(L, tb, n_tensors, out.data(), out.size(), slot4, &density, 1, false, mu, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled)
+                    : begin_and_sample<true, false>(L, tb, n_tensors, out.data(), out.size(), slot4, &density, 1, false, mu, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled);
     if (rc == CONDENSA_OK && !sampled)
         rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slot4, window ? 4 : 1, workspace_dev, st, nullptr, lists.data(), list_bytes);
     if (rc != CONDENSA_OK) return rc;

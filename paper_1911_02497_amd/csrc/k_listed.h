@@ -19,7 +19,7 @@
 //      failed (its rank is not inside the window, or a list overflowed) it ranks that population by radix levels over
 //      the weights instead and applies every result again.
 // One workgroup draws some 25 GB/s from memory it did not write, so the lists (10^5 entries) are walked by many.  When
-// no population exceeds kListLone elements, its list is short enough for one workgroup to do 3 and 4 alone
+// no population exceeds list_lone elements, its list is short enough for one workgroup to do 3 and 4 alone
 // (k_list_finish): three launches, and a failed ranking stays within that workgroup.
 // Results never depend on the sample.  Section 3.1 (a sparsity turned into a magnitude threshold), Section 3.3 (the
 // C step and the multiplier update), Results (up to ten samples per search share a pass).
@@ -36,16 +36,20 @@ constexpr int kListSegs = 1024;                  // segments of a ranking's list
 constexpr int kListMaxW = 256;                   // sampling workgroups of one population at most
 constexpr int kListMaxRankings = 4096;
 constexpr int kListBins = 256;                   // bins over a window
-constexpr u32 kListRanked = 1024;                // gathered entries that are held in LDS
+constexpr u32 kListRanked = 2048;                // gathered entries that are held in LDS
 constexpr u32 kListGather = 1u << 18;            // gathered entries of a ranking at most; with more (ties) it fails
 constexpr u32 kListRow = 64;                     // segments are multiples of this many entries
 
-constexpr u64 kListLone = static_cast<u64>(1) << 18;       // populations up to here are finished by one workgroup
+// Populations up to here are finished by one workgroup.  Several densities: the windows of one sampling workgroup overlap,
+// and the sweep's general path is slow.
+__host__ __device__ inline u64 list_lone(int J) { return static_cast<u64>(1) << (J > 1 ? 16 : 18); }
 
-// Sampling workgroups of a population of n elements: the window is narrowed as the population grows.  One workgroup leaves a window of up to 8 % of it (10 sd of its rank);
-// 32 about 2 %, 64 about 1 %, 256 about 0.4 % at the cost of one more launch.
-__host__ __device__ inline u32 list_sample_groups(u64 n) {
-    if (n <= (static_cast<u64>(1) << 20)) return 1;
+// Sampling workgroups of a population of n elements: the window is narrowed as the population grows.  One workgroup leaves
+// a window of up to 8 % of it (10 sd of its rank); 32 about 2 %, 64 about 1 %, 256 about 0.4 % at the cost of one more
+// launch (4 us).  Above list_lone that launch is earned back at once: 295 thousand weights in two densities 52.3 us with one,
+// 37.7 with 32; 600 thousand 59.7 and 39.5; pruning 700 thousand in one density 37.3 and 36.5.
+__host__ __device__ inline u32 list_sample_groups(u64 n, int J) {
+    if (n <= list_lone(J)) return 1;
     if (n <= (static_cast<u64>(1) << 21)) return 32;
     if (n <= (static_cast<u64>(1) << 23)) return 64;
     return kListMaxW;
@@ -59,10 +63,12 @@ inline u64 list_capacity(u64 n, int cand_shift) {
     return c < least ? least : c;
 }
 // Segments of a list that wavefronts of `per_wave` elements append to: updates of one counter that return a value
-// take turns (some 0.15 us each under contention), so a counter serves sixteen wavefronts while segments last.
+// take turns (some 0.15 us each under contention), so a counter serves four wavefronts while segments last.  Always an
+// odd number: a workgroup takes the segment of its number, and tensors that leave the same part of every chunk empty
+// would otherwise leave the same segments empty.
 inline u32 list_segments(u64 n, u64 per_wave, u32 most) {
-    const u64 s = n / (16 * per_wave);
-    return s < 1 ? 1u : (s > most ? most : static_cast<u32>(s));
+    const u64 s = n / (4 * per_wave);
+    return s < 1 ? 1u : ((s >= most ? most - 1 : static_cast<u32>(s)) | 1u);
 }
 
 // Window of a ranking.  Its keys fall into bins (key - lo) >> shift; the estimate `mid` is the lower edge of bin mid_bin.
@@ -356,9 +362,9 @@ __global__ __launch_bounds__(kListThreads) void k_list_sample(DataArgs a, ListAr
                          [&](int j, u64* k, u64* n) { *k = a.slots[r0 + j].k; *n = a.slots[r0 + j].n; });
 }
 
-// The sample as part of the launch that begins the call (GLOBAL scope, few tensors): what the sampling workgroups need
+// The sample as part of the launch that begins the call (few tensors): what the sampling workgroups need
 // of the tables comes as kernel arguments, so they need not wait for the upload.  One launch less: 4 us.
-constexpr int kBeginSampleTensors = 112;
+constexpr int kBeginSampleTensors = 96;
 struct BeginSampleArgs {
     UploadArgs up;
     uint4* zero;
@@ -368,13 +374,15 @@ struct BeginSampleArgs {
     int n_tensors;
     u32 groups;            // sampling workgroups: the first of the grid
     int J;
+    int per_tensor;
     float mu;
     u64 N;
-    u64 k[kMaxJ];
+    double density[kMaxJ];
     const float* w[kBeginSampleTensors];
     const float* lam[kBeginSampleTensors];
     u32 n[kBeginSampleTensors];
     u32 chunk_start[kBeginSampleTensors + 1];
+    u16 group0[kBeginSampleTensors + 1];   // PER_TENSOR: first sampling workgroup of each tensor
 };
 static_assert(sizeof(BeginSampleArgs) + sizeof(ListArgs) <= 3584, "kernel arguments");
 template <bool LC, bool VEC>
@@ -406,12 +414,32 @@ __global__ __launch_bounds__(kListThreads) void k_begin_sample(BeginSampleArgs b
             if (LC) s_lam[tid] = b.lam[tid];
         }
         __syncthreads();
-        list_sample<LC, VEC>(w, b.J, b.mu, b.groups, blockIdx.x, blockIdx.x, 0, 0, static_cast<u64>(b.n_chunks) * (kChunk / 4),
+        u32 g = 0, W = b.groups, me = blockIdx.x;
+        u64 first_chunk = 0, quads = static_cast<u64>(b.n_chunks) * (kChunk / 4), n_pop = b.N;
+        if (b.per_tensor) {
+            int lo = 0, hi = b.n_tensors - 1;              // the tensor this workgroup samples: the last with group0 <= its number
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (b.group0[mid] <= blockIdx.x) lo = mid; else hi = mid - 1;
+            }
+            g = static_cast<u32>(lo);
+            W = static_cast<u32>(b.group0[g + 1]) - b.group0[g];
+            me = blockIdx.x - b.group0[g];
+            first_chunk = s_start[g];
+            n_pop = s_n[g];
+            quads = (n_pop + 3) / 4;
+        }
+        list_sample<LC, VEC>(w, b.J, b.mu, W, me, blockIdx.x, static_cast<u64>(g) * b.J, first_chunk, quads,
                              [&](u64 c) {
-                                 const int t = tensor_of_chunk_lds(static_cast<u32>(c));
+                                 const int t = b.per_tensor ? static_cast<int>(g) : tensor_of_chunk_lds(static_cast<u32>(c));
                                  return SampleTensor{s_w[t], LC ? s_lam[t] : nullptr, s_n[t], s_start[t]};
                              },
-                             [&](int j, u64* k, u64* n) { *k = b.k[j]; *n = b.N; });
+                             [&](int j, u64* k, u64* n) {  // as the host rounds: llround of the binary64 product, clamped
+                                 const double x = b.density[j] * static_cast<double>(n_pop);
+                                 const u64 kk = static_cast<u64>(llround(x));
+                                 *k = kk > n_pop ? n_pop : kk;
+                                 *n = n_pop;
+                             });
         return;
     }
     __syncthreads();
@@ -614,14 +642,14 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
 // updates ranking j), so their latency is paid once, and the entries leave in runs.  Masks alone leave as 16 bytes per
 // lane, the regions having changed places in LDS.
 constexpr int kListMultiQuads = 4;
-constexpr u32 kListMultiBuf = 32;                // buffered entries per ranking and wavefront; more are written one by one
+constexpr u32 kListMultiBuf = 1024;              // buffered entries of a wavefront: an equal share for each ranking; more are written at once
 struct ListMultiShared {
-    u32 key[kMaxJ][kListMultiBuf];
+    u32 key[kListMultiBuf];
     u32 tile[256 * kListMultiQuads];             // the tile's keys, then its regions
     u32 count[kMaxJ];
     u32 gap[2 * (kMaxJ + 1)];
     u32 ranking[kMaxJ];
-    u16 off[kMaxJ][kListMultiBuf];
+    u16 off[kListMultiBuf];
 };
 
 __device__ inline u32 list_reserve(const ListArgs& w, u64 r, const ListRank& rk, u32 count, u32 kept) {
@@ -647,15 +675,17 @@ __device__ inline void list_multi_flush(const DataArgs& a, const ListArgs& w, co
         at = list_reserve(w, r0 + lane, rk, static_cast<u32>(mine), static_cast<u32>(mine >> 32));
     }
     const u64 first = rk.base + (rk.n_segs ? static_cast<u64>(blockIdx.x % rk.n_segs) * rk.seg_cap : 0);
+    const u32 share = kListMultiBuf / static_cast<u32>(a.J);
     __syncthreads();                                                    // one wavefront: orders the LDS buffer
     for (int j = 0; j < a.J; ++j) {
         const u32 count = __shfl(static_cast<u32>(mine), j, 64);
-        const u32 pos = __shfl(at, j, 64) + lane, cap = __shfl(rk.seg_cap, j, 64);
+        const u32 pos = __shfl(at, j, 64), cap = __shfl(rk.seg_cap, j, 64);
         const u64 to = ((static_cast<u64>(__shfl(static_cast<u32>(first >> 32), j, 64)) << 32) | __shfl(static_cast<u32>(first), j, 64)) + pos;
-        if (static_cast<u32>(lane) < count && pos < cap) {
-            w.key[to] = sh.key[j][lane];
-            w.idx[to] = i0 + sh.off[j][lane];
-        }
+        for (u32 i = lane; i < count; i += 64)
+            if (pos + i < cap) {
+                w.key[to + i] = sh.key[j * share + i];
+                w.idx[to + i] = i0 + sh.off[j * share + i];
+            }
     }
 }
 
@@ -690,6 +720,7 @@ __device__ inline void list_multi_general(const DataArgs& a, const ListArgs& w, 
         }
     }
     const u32 i0 = static_cast<u32>(c) * kChunk + sub * kWaveElems;
+    const u32 share = kListMultiBuf / static_cast<u32>(a.J);
     u64 mine = 0;                                                       // lane j: ranking j's buffered entries and kept keys
     for (int j = 0; j < a.J; ++j) {
         const ListWin win = w.win[r0 + j];
@@ -714,14 +745,22 @@ __device__ inline void list_multi_general(const DataArgs& a, const ListArgs& w, 
                 if (hit != 0) {                                         // uniform
                     const u32 n_hit = static_cast<u32>(__popcll(hit));
                     const bool me = (hit >> lane) & 1u;
-                    if (count + n_hit <= kListMultiBuf) {
+                    if (count + n_hit <= share) {
                         if (me) {
-                            sh.key[j][count + lanes_below(hit)] = x;
-                            sh.off[j][count + lanes_below(hit)] = static_cast<u16>(q * 256 + lane * 4 + k);
+                            sh.key[j * share + count + lanes_below(hit)] = x;
+                            sh.off[j * share + count + lanes_below(hit)] = static_cast<u16>(q * 256 + lane * 4 + k);
                         }
                         count += n_hit;
                     } else {                                            // full buffer: straight to the list
-                        if (me) list_multi_append(w, r0 + j, x, i0 + q * 256 + lane * 4 + k);
+                        const ListRank rk = w.rank[r0 + j];
+                        u32 at = 0;
+                        if (lane == 0) at = list_reserve(w, r0 + j, rk, n_hit, 0);
+                        at = __shfl(at, 0, 64) + lanes_below(hit);
+                        if (me && at < rk.seg_cap) {
+                            const u64 to = rk.base + static_cast<u64>(blockIdx.x % rk.n_segs) * rk.seg_cap + at;
+                            w.key[to] = x;
+                            w.idx[to] = i0 + q * 256 + lane * 4 + k;
+                        }
                     }
                 }
             }
@@ -804,7 +843,7 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
     u32 packed[Q];                                                      // regions of a float4's elements, a byte each
 #pragma unroll
     for (int q = 0; q < Q; ++q) packed[q] = region[q][0] | (region[q][1] << 8) | (region[q][2] << 16) | (region[q][3] << 24);
-    const u32 i0 = static_cast<u32>(c) * kChunk + sub * kWaveElems;
+    const u32 i0 = static_cast<u32>(c) * kChunk + sub * kWaveElems, share = kListMultiBuf / static_cast<u32>(a.J);
     while (inside) {
         const u32 i = static_cast<u32>(__ffs(inside)) - 1u, off = (i >> 2) * 256 + lane * 4 + (i & 3u);
         inside &= inside - 1u;
@@ -815,9 +854,9 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
         // below the gap of its region: the window of the highest estimate it reaches; else the next one up
         const u32 j = sh.ranking[x < sh.gap[2 * r] ? n - r : n - r - 1u];
         const u32 at = atomicAdd(&sh.count[j], 1u);
-        if (at < kListMultiBuf) {
-            sh.key[j][at] = x;
-            sh.off[j][at] = static_cast<u16>(off);
+        if (at < share) {
+            sh.key[j * share + at] = x;
+            sh.off[j * share + at] = static_cast<u16>(off);
         } else {
             list_multi_append(w, r0 + j, x, i0 + off);
         }
@@ -867,7 +906,7 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
         if (lane == j) kept_of_lane = kept;
     }
     __syncthreads();
-    const u32 buffered = lane < a.J ? (sh.count[lane] < kListMultiBuf ? sh.count[lane] : kListMultiBuf) : 0u;
+    const u32 buffered = lane < a.J ? (sh.count[lane] < share ? sh.count[lane] : share) : 0u;
     list_multi_flush(a, w, sh, r0, (static_cast<u64>(kept_of_lane) << 32) | buffered, i0);
 }
 
@@ -1037,6 +1076,12 @@ __global__ __launch_bounds__(kBlock) void k_list_gather(DataArgs a, ListArgs w) 
     const ListWin win = w.win[s];
     const Slot& slot = a.slots[s];
     if (part != 0 && part * (kBlock / 64) >= rk.n_segs) return;          // uniform
+    if (PQ && w.nnz_out && w.write && part == 0) {         // the sweep's count of non-zero codes, corrected by k_list_settle
+        u64 v = 0, total;
+        for (u32 i = tid; i < static_cast<u32>(kListSegs); i += kBlock) v += w.nnz[i];
+        block_excl_scan_u64(v, s_wave, &total);
+        if (tid == 0) *w.nnz_out = total;
+    }
     if (slot.state != kSelecting) {                        // k == 0: nothing listed
         if (part == 0 && tid == 0) w.bin_want[s] = 0;
         return;
@@ -1169,18 +1214,20 @@ __device__ inline void list_pick(ListShared& sh, bool from_top, u32 r, u32* bin,
 // one kept; state, record and the outputs of gathered elements whose decision was wrong.  One more counting level leaves
 // a handful, which are ranked by comparing all pairs.
 // `want` 0: the ranking failed.  `n` gathered entries: in sh.key / sh.idx when `in_lds`, else at gkey / gidx.  `nz`: this
-// thread's corrections so far of the count of non-zero codes.
+// thread's corrections so far of the count of non-zero codes.  Several workgroups (`shares`) may rank the same ranking:
+// each settles its share of the entries (scattered accesses to six arrays: one workgroup took 21 us over 700 of them), and
+// number 0 writes state and record.  What they read of the ranking's state is never written here.
 template <bool LC, bool PQ, int THREADS>
 __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShared& sh, u32 s, u32 want, u32 n, bool in_lds, int nz,
-                                 condensa_select* results, int n_groups) {
+                                 u32 share, u32 shares, condensa_select* results, int n_groups) {
     const u32 tid = threadIdx.x;
     Slot& slot = a.slots[s];
     const u32 g = s / a.J, j = s - g * a.J;
     condensa_select* record = results + static_cast<u64>(j) * n_groups + g;
     const u32 want_all = want;
-    const bool slot_selecting = slot.state == kSelecting;
-    if (!slot_selecting) {                                 // k == 0: nothing is kept, and the sweep kept nothing
-        if (tid == 0) *record = select_record(slot, false, 0, 0, 0, 0, slot.path);
+    const bool nothing = slot.k == 0;                      // nothing is kept, and the sweep kept nothing
+    if (nothing) {
+        if (tid == 0 && share == 0) *record = select_record(slot, false, 0, 0, 0, 0, slot.path);
     } else if (want != 0) {                                // 0: it failed
         const u32* __restrict__ gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
         const u32* __restrict__ gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
@@ -1247,12 +1294,12 @@ __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShare
         const u32 T = sh.T, last = sh.last;
         if (w.write) {
             constexpr int B = 4;
-            for (u32 i0 = tid; i0 < n; i0 += THREADS * B) {
+            for (u32 i0 = tid * shares + share; i0 < n; i0 += THREADS * B * shares) {
                 u32 idx[B];
                 bool keep[B], on[B];
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
-                    const u32 i = i0 + b * THREADS;
+                    const u32 i = i0 + b * THREADS * shares;
                     on[b] = i < n;
                     const u32 key = on[b] ? key_of(i) : 0u;
                     idx[b] = on[b] ? idx_of(i) : 0u;
@@ -1262,7 +1309,7 @@ __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShare
                 list_fix<LC, PQ, B>(a, w, j, idx, keep, on, &nz);
             }
         }
-        if (tid == 0) {
+        if (tid == 0 && share == 0) {
             u64 tie_end = slot.n;
             if (sh.rem < sh.n_tie) {
                 const TensorDesc& td = a.td[a.chunk_map[last / kChunk]];
@@ -1272,17 +1319,23 @@ __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShare
             *record = select_record(slot, true, T, sh.rem, sh.n_tie, tie_end, slot.path);
         }
     }
-    if (PQ && w.nnz_out && w.write && (slot_selecting ? want_all != 0 : true)) {     // the sweep's count, corrected by the passes over the list
+    if (PQ && w.nnz_out && w.write && (nothing || want_all != 0)) {
         u32 v = static_cast<u32>(nz), total;               // modulo 2^32: the sum itself is smaller
-        for (u32 i = tid; i < static_cast<u32>(kListSegs); i += THREADS) v += w.nnz[i];
+        if (THREADS == kListThreads)                       // alone: the sweep's count, corrected by the passes over the list
+            for (u32 i = tid; i < static_cast<u32>(kListSegs); i += THREADS) v += w.nnz[i];
         __syncthreads();
         wg_incl_scan_u32<THREADS>(v, sh.wave, &total);
-        if (tid == 0) *w.nnz_out = static_cast<u64>(total + static_cast<u32>(a.ctl->nnz_delta));
+        if (tid == 0 && THREADS == kListThreads) {
+            *w.nnz_out = total;
+        } else if (tid == 0) {                             // one of several: corrections of what k_list_gather stored
+            const long long d = static_cast<int>(total) + (share == 0 ? static_cast<long long>(a.ctl->nnz_delta) : 0ll);
+            if (d != 0) atomicAdd(reinterpret_cast<unsigned long long*>(w.nnz_out), static_cast<unsigned long long>(d));
+        }
     }
     __syncthreads();                                       // the shared words are free for the next ranking
 }
 
-// Rankings of populations of at most kListLone elements: one workgroup each does the counting, the gathering and the
+// Rankings of populations of at most list_lone elements: one workgroup each does the counting, the gathering and the
 // ranking on its list, and a failed ranking by itself (it reads the population a few times over: a megabyte or so).
 // 22 thousand listed keys of a 1024x1024 matrix: see the measurements beside the launch rule.
 template <bool LC, bool PQ>
@@ -1360,7 +1413,7 @@ __global__ __launch_bounds__(kListThreads) void k_list_finish(DataArgs a, ListAr
             }
         }
     }
-    list_rank<LC, PQ, kListThreads>(a, w, sh, s, want, n, in_lds, nz, results, n_groups);
+    list_rank<LC, PQ, kListThreads>(a, w, sh, s, want, n, in_lds, nz, 0, 1, results, n_groups);
     if (!selecting || want != 0) return;
     // failed: radix levels over the population, the tie rule, and every output again
     const u64 cb = a.per_tensor ? a.td[g].chunk_start : 0, ce = a.per_tensor ? a.td[g + 1].chunk_start : a.n_chunks;
@@ -1480,7 +1533,9 @@ __global__ __launch_bounds__(kBlock) void k_list_settle(DataArgs a, ListArgs w, 
     __shared__ ListShared s_rank;
     const u32 n_fail = w.fb->failed;                       // final: an earlier kernel counted
     if (n_fail == 0) {
-        for (u32 s = blockIdx.x; s < static_cast<u32>(w.n_rankings); s += gridDim.x) list_rank<LC, PQ, kBlock>(a, w, s_rank, s, w.bin_want[s], w.gathered[s], false, 0, results, n_groups);
+        const u32 n_r = static_cast<u32>(w.n_rankings), shares = n_r * 16 <= gridDim.x ? 16u : (n_r <= gridDim.x ? gridDim.x / n_r : 1u);
+        for (u32 v = blockIdx.x; v < n_r * shares; v += gridDim.x)
+            list_rank<LC, PQ, kBlock>(a, w, s_rank, v / shares, w.bin_want[v / shares], w.gathered[v / shares], false, 0, v % shares, shares, results, n_groups);
         return;
     }
     const int tid = threadIdx.x;
@@ -1502,7 +1557,7 @@ __global__ __launch_bounds__(kBlock) void k_list_settle(DataArgs a, ListArgs w, 
         const u32 phase = s_ticket / G, piece = s_ticket % G;
         if (phase >= phases) return;                       // every workgroup gets here: tickets only grow
         if (phase == 0) {
-            for (u32 s = piece; s < static_cast<u32>(w.n_rankings); s += G) list_rank<LC, PQ, kBlock>(a, w, s_rank, s, w.bin_want[s], w.gathered[s], false, 0, results, n_groups);
+            for (u32 s = piece; s < static_cast<u32>(w.n_rankings); s += G) list_rank<LC, PQ, kBlock>(a, w, s_rank, s, w.bin_want[s], w.gathered[s], false, 0, 0, 1, results, n_groups);
         } else if (phase < rank_phases) {
             const u32 f = (phase - 1) / 5, step = (phase - 1) % 5;
             const u32 r = w.fail_list[f];
