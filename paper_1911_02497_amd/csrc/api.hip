@@ -1560,10 +1560,14 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
         }
         // moderate rankings on the automatic path: two levels over all aggregates, then a list (k_struct_list.h)
         const bool listed = !per_tensor && !small && !fused && tb.F <= kSmallCallElems && cfg[CONDENSA_OPT_SELECT_PATH] == 0;
-        u64 blocks = tb.n_schunks < 1024 ? tb.n_schunks : 1024;
-        const u64 cpb = (tb.n_schunks + blocks - 1) / blocks;
-        blocks = (tb.n_schunks + cpb - 1) / cpb;
+        const u64 pieces = a.merged ? (tb.F + kKeyPiece - 1) / kKeyPiece : tb.n_schunks;
         for (int level = 0; level < (listed ? kStructListLevels : n_levels(63)) && !small; ++level) {
+            // level 0 separates little, so that a workgroup adds a few bins to the ranking's histogram; the next ones add
+            // most of 2048 each (688 128 keys, level 1: 336 workgroups 16.4 us, 120 of them 10.7)
+            const u64 most = listed ? (level == 0 ? 256 : 96) : 1024;
+            u64 blocks = pieces < most ? pieces : most;
+            const u64 cpb = (pieces + blocks - 1) / blocks;
+            blocks = (pieces + cpb - 1) / cpb;
             hipLaunchKernelGGL(k_hist_keys, dim3(static_cast<unsigned>(blocks)), dim3(kBlock), 0, st, a, level, cpb);
             CONDENSA_LAUNCH_CHECK();
             if (a.merged) continue;                            // the next kernel folds this level in itself
@@ -1577,7 +1581,7 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
             l.key = at<u64>(workspace_dev, L.cand_idx);
             l.id = at<u32>(workspace_dev, L.cand_key);
             l.cap = L.cand_cap;
-            hipLaunchKernelGGL(k_struct_list_collect, dim3(static_cast<unsigned>(tb.n_schunks < 1024 ? tb.n_schunks : 1024)), dim3(kBlock), 0, st, a, l);
+            hipLaunchKernelGGL(k_struct_list_collect, dim3(static_cast<unsigned>(pieces < 1024 ? pieces : 1024)), dim3(kBlock), 0, st, a, l);
             CONDENSA_LAUNCH_CHECK();
             hipLaunchKernelGGL(k_struct_list_finish, dim3(1), dim3(kSmallFinishThreads), 0, st, a, l, results_dev, bits_for(tb.F - 1));
             CONDENSA_LAUNCH_CHECK();
@@ -1606,10 +1610,14 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
             hipLaunchKernelGGL(k_struct_mask, dim3(mtiles), dim3(kBlock), 0, st, a, structure_mask_dev, static_cast<int>(kMaskFromKeys));
             CONDENSA_LAUNCH_CHECK();
         }
-        if (keep_idx_dev && !small) {
+        const bool scanned = mtiles > kIdTilesDirect, apply = !fused && (theta || mask) && tb.n_chunks > 0;
+        const u32 id_tiles = keep_idx_dev && !small ? mtiles : 0;
+        if (id_tiles && scanned) {
             hipLaunchKernelGGL(k_struct_scan_blocks, dim3(1), dim3(kScanThreads), 0, st, a.sblock, static_cast<u64>(mtiles));
             CONDENSA_LAUNCH_CHECK();
-            hipLaunchKernelGGL(k_struct_keep_idx, dim3(mtiles), dim3(kBlock), 0, st, a, keep_idx_dev);
+        }
+        if (id_tiles && !apply) {                           // otherwise in the apply sweep's launch
+            hipLaunchKernelGGL(k_struct_keep_idx, dim3(id_tiles), dim3(kBlock), 0, st, a, keep_idx_dev, scanned ? 1 : 0);
             CONDENSA_LAUNCH_CHECK();
         }
         if (fused) {
@@ -1618,11 +1626,12 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
             const u64 n_tiles = tb.n_chunks * kSubPerChunk;
             hipLaunchKernelGGL((k_struct_apply_gated<true>), dim3(static_cast<unsigned>(n_tiles < 4096 ? n_tiles : 4096)), dim3(kBlock), 0, st, a, od, n_tiles);
             CONDENSA_LAUNCH_CHECK();
-        } else if ((theta || mask) && tb.n_chunks > 0) {
+        } else if (apply) {
             PhaseTimer timer(CONDENSA_PHASE_APPLY, st, cfg);
             const OutDesc* od = at<OutDesc>(workspace_dev, L.out);
-            if (vec) hipLaunchKernelGGL((k_struct_apply<true>), dim3(static_cast<unsigned>(tb.n_chunks * kSubPerChunk)), dim3(kBlock), 0, st, a, od);
-            else     hipLaunchKernelGGL((k_struct_apply<false>), dim3(static_cast<unsigned>(tb.n_chunks * kSubPerChunk)), dim3(kBlock), 0, st, a, od);
+            const dim3 grid(static_cast<unsigned>(tb.n_chunks * kSubPerChunk + id_tiles));
+            if (vec) hipLaunchKernelGGL((k_struct_apply<true>), grid, dim3(kBlock), 0, st, a, od, keep_idx_dev, id_tiles, scanned ? 1 : 0);
+            else     hipLaunchKernelGGL((k_struct_apply<false>), grid, dim3(kBlock), 0, st, a, od, keep_idx_dev, id_tiles, scanned ? 1 : 0);
             CONDENSA_LAUNCH_CHECK();
         }
     }

@@ -1261,6 +1261,7 @@ __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShare
             if (tid < in_bin) {
                 const u32 key = sh.pkey[tid], idx = sh.pidx[tid];
                 u32 higher = 0, same = 0, same_before = 0;
+#pragma unroll 8
                 for (u32 e = 0; e < in_bin; ++e) {
                     const u32 k2 = sh.pkey[e];
                     higher += k2 > key ? 1u : 0u;

@@ -66,115 +66,108 @@ __device__ inline void wave_pick_asc(const u32* s_hist, int nb, u64 r, u32* bin,
     }
 }
 
-// A 1024-thread workgroup finishes one ranking on a list of (key, index) entries that holds every key sharing the
-// ranking's digits above `first_level` (and possibly other keys): `e` is the ranking's state on entering that
-// level.  The remaining levels are counted in LDS over the matching entries, the tie rule picks the r-th lowest
-// index among the entries equal to the threshold, and the outcome becomes the ranking's stored state and its
-// result record.  Called by every thread of the workgroup with the same arguments.
-template <typename KEY, typename IDX>
-__device__ inline void finish_on_list(Slot& slot, SlotStep e, const KEY* __restrict__ keys, const IDX* __restrict__ ids,
-                                      u64 n_list, int key_bits, int first_level, int idx_bits, condensa_select* record) {
-    __shared__ __align__(8) u32 s_hist[kBins];
-    __shared__ u32 s_bin, s_found, s_n;
-    __shared__ u64 s_rem, s_cnt;
-    const int tid = threadIdx.x;
-    u64 tie_end = slot.n;                                  // every tie kept, unless found otherwise below
-    if (e.state == kSelecting) {                           // uniform over the workgroup
-        u64 prefix = e.prefix, r = e.remaining, n_tie = 0;
-        bool ok = true;
-        for (int level = first_level; level < n_levels(key_bits) && ok; ++level) {
-            const Level lv = level_of(key_bits, level);
-            const int nb = 1 << lv.bits;
-            for (int i = tid; i < nb; i += kSmallFinishThreads) s_hist[i] = 0;
-            if (tid == 0) s_found = 0;
-            __syncthreads();
-            for (u64 i = tid; i < n_list; i += kSmallFinishThreads) {
-                const u64 key = keys[i];
-                if (((key ^ prefix) >> lv.hi_shift) == 0) atomicAdd(&s_hist[static_cast<u32>(key >> lv.shift) & (nb - 1)], 1u);
-            }
-            __syncthreads();
-            if (tid < 64) wave_pick_desc(s_hist, nb, r, &s_bin, &s_rem, &s_cnt, &s_found);
-            __syncthreads();
-            ok = s_found != 0;
-            if (ok) {
-                prefix |= static_cast<u64>(s_bin) << lv.shift;
-                r = s_rem;
-                n_tie = s_cnt;
-            }
-            __syncthreads();
+__device__ inline u32 wave_incl_scan_u32(u32 v) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const u32 up = __shfl_up(v, d, 64);
+        if (lane >= d) v += up;
+    }
+    return v;
+}
+
+// Ranking of n keys of at most 63 bits by one workgroup.  Radix levels of eight bits from the highest bit in which the keys
+// differ (aggregates of one model share their sign and most exponent bits), until at most kRankPairs share the digits
+// found; those are ranked by comparing all pairs, four threads to a key.  A lone workgroup is bound by latency: one search
+// of 2048 bins takes a wavefront 3.7 us, one of 256 bins 0.5 and its counts 0.6; 255 keys in pairs take 3.2 us (64-bit
+// compares are quarter rate), 64 keys 0.8.
+constexpr u32 kRankPairs = 64;
+struct RankShared {
+    __align__(16) u32 hist[kBins];                         // rank_keys uses the first 256
+    u64 pair[kRankPairs];
+    u32 any, all;          // OR and AND of the keys' upper halves
+    u64 key, rem, n_tie;   // result: the key at the rank, how many of its equals are kept, how many there are
+    u32 n, bin, found;
+};
+
+// sh.key = the key at descending rank `rank` (1-based) of key_of(0..n-1), sh.rem, sh.n_tie; false when there are fewer.
+// Every thread of the THREADS (at least 4 kRankPairs) calls it and gets the same value; it ends with a barrier.
+template <int THREADS, typename KeyOf>
+__device__ inline bool rank_keys(RankShared& sh, u32 n, KeyOf key_of, u64 rank64) {
+    static_assert(THREADS >= 4 * static_cast<int>(kRankPairs), "four threads to a key");
+    const u32 tid = threadIdx.x;
+    u32 any = 0, all = ~0u;
+    for (u32 i = tid; i < n; i += THREADS) { const u32 hi = static_cast<u32>(key_of(i) >> 32); any |= hi; all &= hi; }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) { any |= __shfl_xor(any, d, 64); all &= __shfl_xor(all, d, 64); }
+    if (tid == 0) { sh.any = 0; sh.all = ~0u; sh.found = (rank64 >= 1 && rank64 <= n) ? 1u : 0u; }
+    if (tid < 256) sh.hist[tid] = 0;
+    __syncthreads();
+    if ((tid & 63u) == 0) {
+        atomicOr(&sh.any, any);
+        atomicAnd(&sh.all, all);
+    }
+    __syncthreads();
+    if (sh.found == 0) return false;                       // uniform
+    const u32 diff = sh.any ^ sh.all;
+    int top = diff == 0 ? 32 : 64 - __clz(static_cast<int>(diff));             // bits below which the keys may differ
+    u64 prefix = ((static_cast<u64>(sh.all) << 32) >> top) << top;
+    u32 rank = static_cast<u32>(rank64), n_in = n;
+    while (top > 0 && n_in > kRankPairs) {                 // uniform; the 256 counts are clear here
+        const int bits = top < 8 ? top : 8, shift = top - bits;
+        const u32 mask = (1u << bits) - 1u;
+        for (u32 i = tid; i < n; i += THREADS) {
+            const u64 key = key_of(i);
+            if (((key ^ prefix) >> top) == 0) atomicAdd(&sh.hist[static_cast<u32>(key >> shift) & mask], 1u);
         }
-        if (!ok) {
-            e.state = kFailed;                             // the counts of the levels and the list disagree: reported, not hidden
-        } else {
-            e.prefix = prefix; e.remaining = r; e.n_tie = n_tie; e.state = kDone; e.need_tie = 0;
-            const u64 T = prefix;
-            if (r < n_tie && n_tie <= static_cast<u64>(kSmallFinishThreads)) {
-                // a handful of ties: their indices in LDS, each ranked by counting the lower ones
-                u64* s_idx = reinterpret_cast<u64*>(s_hist);
-                if (tid == 0) { s_n = 0; s_rem = slot.n - 1; }
-                __syncthreads();
-                for (u64 i = tid; i < n_list; i += kSmallFinishThreads)
-                    if (static_cast<u64>(keys[i]) == T) {
-                        const u32 p = atomicAdd(&s_n, 1u);
-                        if (p < static_cast<u32>(kSmallFinishThreads)) s_idx[p] = static_cast<u64>(ids[i]);
-                    }
-                __syncthreads();
-                const u32 m = s_n < static_cast<u32>(kSmallFinishThreads) ? s_n : static_cast<u32>(kSmallFinishThreads);
-                if (static_cast<u32>(tid) < m) {
-                    const u64 mine = s_idx[tid];
-                    u64 lower = 0;
-                    for (u32 i = 0; i < m; ++i) lower += (s_idx[i] < mine) ? 1u : 0u;
-                    if (lower + 1 == r) s_rem = mine;      // indices are distinct: one thread
-                }
-                __syncthreads();
-                tie_end = s_rem + 1;
-            } else if (r < n_tie) {
-                // many ties: radix levels on the index over the entries equal to the threshold, lowest first
-                u64 iprefix = 0, ir = r;
-                for (int level = 0; level < n_levels(idx_bits); ++level) {     // uniform
-                    const Level lv = level_of(idx_bits, level);
-                    const int nb = 1 << lv.bits;
-                    for (int i = tid; i < nb; i += kSmallFinishThreads) s_hist[i] = 0;
-                    if (tid == 0) s_found = 0;
-                    __syncthreads();
-                    for (u64 i = tid; i < n_list; i += kSmallFinishThreads) {
-                        if (static_cast<u64>(keys[i]) != T) continue;
-                        const u64 idx = static_cast<u64>(ids[i]);
-                        if (((idx ^ iprefix) >> lv.hi_shift) == 0) atomicAdd(&s_hist[static_cast<u32>(idx >> lv.shift) & (nb - 1)], 1u);
-                    }
-                    __syncthreads();
-                    if (tid < 64) wave_pick_asc(s_hist, nb, ir, &s_bin, &s_rem, &s_found);
-                    __syncthreads();
-                    iprefix |= static_cast<u64>(s_bin) << lv.shift;
-                    ir = s_rem;
-                    __syncthreads();
-                }
-                tie_end = iprefix + 1;
+        __syncthreads();
+        if (tid < 64) {                                    // four bins a lane, from the top
+            const uint4 c4 = *reinterpret_cast<const uint4*>(sh.hist + 252 - 4 * tid);
+            const u32 c[4] = {c4.w, c4.z, c4.y, c4.x};
+            u32 before = wave_incl_scan_u32(c[0] + c[1] + c[2] + c[3]) - (c[0] + c[1] + c[2] + c[3]);
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) {
+                if (before < rank && rank <= before + c[i]) { sh.bin = 255 - 4 * tid - i; sh.rem = rank - before; sh.n = c[i]; }
+                before += c[i];
             }
         }
+        __syncthreads();
+        if (tid < 256) sh.hist[tid] = 0;
+        prefix |= static_cast<u64>(sh.bin) << shift;
+        rank = static_cast<u32>(sh.rem);
+        n_in = sh.n;
+        top = shift;
+        __syncthreads();
     }
-    if (tid != 0) return;
-    if (slot.state == kSelecting) {
-        slot.prefix = e.prefix; slot.remaining = e.remaining; slot.n_tie = e.n_tie;
-        slot.state = e.state; slot.need_tie = 0;
-        slot.tie_end = tie_end;
+    if (top == 0) {
+        if (tid == 0) { sh.key = prefix; sh.rem = rank; sh.n_tie = n_in; }
+    } else {
+        if (tid == 0) sh.n = 0;
+        __syncthreads();
+        for (u32 i = tid; i < n; i += THREADS) {
+            const u64 key = key_of(i);
+            if (((key ^ prefix) >> top) == 0) sh.pair[atomicAdd(&sh.n, 1u)] = key;        // n_in of them
+        }
+        __syncthreads();
+        const u32 mine = tid >> 2;
+        if (tid < 4 * kRankPairs) {                        // whole wavefronts: the lanes of a key trade their counts
+            const u64 key = sh.pair[mine < n_in ? mine : 0];
+            u32 higher = 0, same = 0;
+#pragma unroll 8
+            for (u32 e = tid & 3u; e < n_in; e += 4) {
+                const u64 k2 = sh.pair[e];
+                higher += k2 > key ? 1u : 0u;
+                same += k2 == key ? 1u : 0u;
+            }
+            higher += __shfl_xor(higher, 1, 64); same += __shfl_xor(same, 1, 64);
+            higher += __shfl_xor(higher, 2, 64); same += __shfl_xor(same, 2, 64);
+            if (mine < n_in && higher < rank && rank <= higher + same) {       // equals write the same
+                sh.key = key; sh.rem = rank - higher; sh.n_tie = same;
+            }
+        }
     }
-    condensa_select out;
-    out.n = slot.n;
-    out.k = slot.k;
-    if (e.state == kDone) {
-        out.n_gt = slot.k - e.remaining;
-        out.n_tie_kept = e.remaining;
-        out.n_tie = e.n_tie;
-        out.threshold_key = e.prefix;
-        out.tie_end = slot.tie_end;
-    } else {                                               // k == 0: nothing is kept
-        out.n_gt = 0; out.n_tie_kept = 0; out.n_tie = 0;
-        out.threshold_key = ~static_cast<u64>(0);
-        out.tie_end = 0;
-    }
-    out.path = slot.path;
-    *record = out;
+    __syncthreads();
+    return true;
 }
 
 }  // namespace condensa

@@ -4,9 +4,7 @@
 // The six levels of a 63-bit ranking are six dependent launches plus the tie search.  Aggregates of one model share
 // their sign and most exponent bits, so level 0 barely separates them; after level 1 (22 of 63 bits) the threshold's
 // bin holds a few hundred structures.  k_struct_list_collect lists those (key, structure id) pairs and
-// k_struct_list_finish, one workgroup, finishes on the list as k_small_finish does for element pruning: the four
-// remaining levels in LDS, the lowest-id rule among equal aggregates, the stored state and the record.  The list
-// can hold every structure, so nothing overflows.  A Transformer's 688 128 blocks of 8x8: 14 -> 10 launches.
+// k_struct_list_finish, one workgroup, finishes on the list.  The list can hold every structure, so nothing overflows.  A Transformer's 688 128 blocks of 8x8: 14 -> 10 launches.
 // Table 1 (FilterPrune, BlockPrune: structures are aggregated and pruned); Section 3.1.
 #pragma once
 #include "k_small.h"
@@ -37,13 +35,10 @@ __global__ __launch_bounds__(kBlock) void k_struct_list_collect(StructArgs a, St
     if (s_e.state != kSelecting) return;                   // uniform: k == 0, nothing to rank
     const u64 prefix = s_e.prefix;
     const Level L = level_of(63, kStructListLevels - 1);   // entries agree with the prefix down to this level's digit
-    for (u64 c = blockIdx.x; c < a.n_schunks; c += gridDim.x) {
-        const int t = tensor_of_schunk(a.td, a.n_tensors, c);
-        const TensorDesc& td = a.td[t];
-        const u64 base = (c - td.pad) * kChunk;
-        const u64 end = (base + kChunk < td.n_struct) ? base + kChunk : td.n_struct;
-        const u64* __restrict__ kp = a.keys + td.struct_start;
-        constexpr int kPer = kChunk / kBlock;              // 32 keys per thread and chunk, strided by the workgroup
+    for (u64 base = static_cast<u64>(blockIdx.x) * kKeyPiece; base < a.F; base += static_cast<u64>(gridDim.x) * kKeyPiece) {
+        const u64 end = (base + kKeyPiece < a.F) ? base + kKeyPiece : a.F;
+        const u64* __restrict__ kp = a.keys;               // the ranking is over all structures: their keys are one array
+        constexpr int kPer = static_cast<int>(kKeyPiece) / kBlock;             // keys per thread, strided by the workgroup
         u64 key[kPer];
         u32 listed = 0;
 #pragma unroll
@@ -65,7 +60,7 @@ __global__ __launch_bounds__(kBlock) void k_struct_list_collect(StructArgs a, St
                 if (listed & (1u << u)) {
                     if (pos < l.cap) {
                         l.key[pos] = key[u];
-                        l.id[pos] = static_cast<u32>(td.struct_start + base + tid + static_cast<u64>(u) * kBlock);
+                        l.id[pos] = static_cast<u32>(base + tid + static_cast<u64>(u) * kBlock);
                     }
                     ++pos;
                 }
@@ -75,19 +70,97 @@ __global__ __launch_bounds__(kBlock) void k_struct_list_collect(StructArgs a, St
     }
 }
 
+constexpr u32 kListHeld = 4096;           // list entries held in LDS
+
+// One workgroup ranks the list, applies the lowest-id rule among equal aggregates and writes state and record.  A lone
+// workgroup is bound by latency: four more levels over a list in memory took 22 us for the 688 128 blocks, one level
+// and pairs in LDS %(FINISH)s.
 __global__ __launch_bounds__(kSmallFinishThreads) void k_struct_list_finish(StructArgs a, StructListArgs l, condensa_select* results,
                                                                            int id_bits) {
     __shared__ SlotStep s_e;
+    __shared__ RankShared sh;
+    __shared__ u64 s_key[kListHeld];
+    __shared__ u32 s_tie[kSmallFinishThreads];
+    __shared__ u32 s_n;
+    __shared__ u64 s_last;
     Slot& slot = a.slots[0];
-    if (threadIdx.x < 64) {
+    const u32 tid = threadIdx.x;
+    u64 n64 = *l.count;
+    if (n64 > l.cap) n64 = l.cap;                          // (cannot happen: the list holds every structure)
+    const u32 n = static_cast<u32>(n64);
+    const bool held = n <= kListHeld;
+    if (held) for (u32 i = tid; i < n; i += kSmallFinishThreads) s_key[i] = l.key[i];
+    if (tid == 0) s_n = 0;
+    if (tid < 64) {
         const SlotStep e = wave_enter_level(slot, kStructListLevels, 63, struct_hist(a, kStructListLevels - 1),
                                             struct_coarse(a, kStructListLevels - 1));
-        if (threadIdx.x == 0) s_e = e;
+        if (tid == 0) s_e = e;
     }
     __syncthreads();
-    u64 n_list = *l.count;
-    if (n_list > l.cap) n_list = l.cap;                    // (cannot happen: the list holds every structure)
-    finish_on_list<u64, u32>(slot, s_e, l.key, l.id, n_list, 63, kStructListLevels, id_bits, results);
+    SlotStep e = s_e;
+    u64 tie_end = slot.n;                                  // every tie kept, unless found otherwise below
+    if (e.state == kSelecting) {                           // uniform
+        auto key_of = [&](u32 i) { return held ? s_key[i] : l.key[i]; };
+        if (!rank_keys<kSmallFinishThreads>(sh, n, key_of, e.remaining)) {
+            e.state = kFailed;                             // the counts of the levels and the list disagree: reported, not hidden
+        } else {
+            const u64 T = sh.key, r = sh.rem;
+            e.prefix = T; e.remaining = r; e.n_tie = sh.n_tie; e.state = kDone; e.need_tie = 0;
+            if (r < e.n_tie && e.n_tie <= static_cast<u64>(kSmallFinishThreads)) {
+                // their ids in LDS, each ranked by counting the lower ones
+                for (u32 i = tid; i < n; i += kSmallFinishThreads)
+                    if (key_of(i) == T) s_tie[atomicAdd(&s_n, 1u)] = l.id[i];
+                __syncthreads();
+                const u32 m = static_cast<u32>(e.n_tie);
+                if (tid < m) {
+                    const u32 mine = s_tie[tid];
+                    u32 lower = 0;
+                    for (u32 i = 0; i < m; ++i) lower += (s_tie[i] < mine) ? 1u : 0u;
+                    if (lower + 1 == r) s_last = mine;     // ids are distinct: one thread
+                }
+                __syncthreads();
+                tie_end = s_last + 1;
+            } else if (r < e.n_tie) {
+                // many ties: radix levels on the id over the entries equal to the threshold, lowest first
+                u64 iprefix = 0, ir = r;
+                for (int level = 0; level < n_levels(id_bits); ++level) {      // uniform
+                    const Level lv = level_of(id_bits, level);
+                    const int nb = 1 << lv.bits;
+                    for (int i = tid; i < nb; i += kSmallFinishThreads) sh.hist[i] = 0;
+                    __syncthreads();
+                    for (u32 i = tid; i < n; i += kSmallFinishThreads) {
+                        if (key_of(i) != T) continue;
+                        const u64 idx = l.id[i];
+                        if (((idx ^ iprefix) >> lv.hi_shift) == 0) atomicAdd(&sh.hist[static_cast<u32>(idx >> lv.shift) & (nb - 1)], 1u);
+                    }
+                    __syncthreads();
+                    if (tid < 64) wave_pick_asc(sh.hist, nb, ir, &sh.bin, &sh.rem, &sh.found);
+                    __syncthreads();
+                    iprefix |= static_cast<u64>(sh.bin) << lv.shift;
+                    ir = sh.rem;
+                    __syncthreads();
+                }
+                tie_end = iprefix + 1;
+            }
+        }
+    }
+    if (tid != 0) return;
+    if (slot.state == kSelecting) {
+        slot.prefix = e.prefix; slot.remaining = e.remaining; slot.n_tie = e.n_tie;
+        slot.state = e.state; slot.need_tie = 0;
+        slot.tie_end = tie_end;
+    }
+    condensa_select out;
+    const bool done = e.state == kDone;                    // else k == 0: nothing is kept
+    out.n = slot.n;
+    out.k = slot.k;
+    out.n_gt = done ? slot.k - e.remaining : 0;
+    out.n_tie_kept = done ? e.remaining : 0;
+    out.n_tie = done ? e.n_tie : 0;
+    out.threshold_key = done ? e.prefix : ~static_cast<u64>(0);
+    out.tie_end = done ? slot.tie_end : 0;
+    out.path = slot.path;
+    *results = out;
 }
 
 }  // namespace condensa

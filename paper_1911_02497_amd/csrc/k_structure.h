@@ -5,6 +5,7 @@
 #pragma once
 #include "k_apply.h"
 #include "k_select.h"
+#include "k_small.h"
 
 namespace condensa {
 
@@ -302,27 +303,42 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows(StructArgs a, doub
 // 256 rows per workgroup would leave most of the chip idle and every 32-element piece costs a load
 // latency, so here a workgroup takes kFewRows rows and stages kFewTile elements of each per step: one
 // wavefront fetches one row's piece per load instruction (1 KB contiguous), eight loads per thread are in
-// flight, the next piece is requested before the current one is added up, and the first kFewRows threads
-// add their rows' pieces in memory order.  Rows of any length and alignment: a float4 that lies inside
+// flight, the next two pieces are requested before the current one is added up, and the first kFewRows threads
+// add their rows' pieces in memory order.  That chain bounds a call of few rows: 15 ns per element while its threads also
+// converted to binary64 (a quarter-rate instruction), so the staging threads convert and
+// square (the square of a binary32 is exact in binary64).  Rows of any length and alignment: a float4 that lies inside
 // an aligned row is one 128-bit load, anything else is fetched element by element.
 constexpr int kFewRows = 32;
 constexpr int kFewTile = 256;
+constexpr int kFewStarts = 512;
 
 __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows_few(StructArgs a, double* sumsq, float* norms) {
-    __shared__ float s_tile[kFewRows][kFewTile + 1];
+    __shared__ __align__(16) double s_tile[kFewRows][kFewTile + 2];
     __shared__ const float* s_row[kFewRows];
     __shared__ u32 s_len[kFewRows];
     __shared__ u32 s_vec[kFewRows];
     __shared__ u32 s_maxlen;
+    __shared__ u64 s_start[kFewStarts];
     const int tid = threadIdx.x;
     const u64 u = static_cast<u64>(blockIdx.x) * kFewRows + tid;          // the row of thread tid < kFewRows
     if (tid == 0) s_maxlen = 0;
+    const bool starts = a.n_tensors <= kFewStarts;                        // the search in LDS: its steps depend on one another
+    if (starts) for (int t = tid; t < a.n_tensors; t += kBlock) s_start[t] = a.td[t].struct_start;
     __syncthreads();
     u32 len = 0;
     if (tid < kFewRows) {
         const float* row = nullptr;
         if (u < a.F) {
-            const int t = tensor_of_struct(a.td, a.n_tensors, u);
+            int t = 0;
+            if (starts) {
+                int hi = a.n_tensors - 1;
+                while (t < hi) {
+                    const int mid = (t + hi + 1) >> 1;
+                    if (s_start[mid] <= u) t = mid; else hi = mid - 1;
+                }
+            } else {
+                t = tensor_of_struct(a.td, a.n_tensors, u);
+            }
             const TensorDesc& td = a.td[t];
             len = td.d[3];
             row = td.w + (u - td.struct_start) * len;
@@ -335,8 +351,7 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows_few(StructArgs a, 
     __syncthreads();
     const u32 maxlen = s_maxlen;
     const int col = (tid & 63) * 4, wave = tid >> 6;                      // wavefront `wave` fetches rows 4 p + wave
-    float4 v[8];
-    auto fetch = [&](u32 cb) {
+    auto fetch = [&](u32 cb, float4 (&v)[8]) {
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
             const int st = p * 4 + wave;
@@ -355,35 +370,45 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows_few(StructArgs a, 
             v[p] = t;
         }
     };
+    auto exact_square = [](float x) { const double d = static_cast<double>(x); return d * d; };      // 48 bits: no rounding
     double acc = 0.0;
-    if (maxlen > 0) fetch(0);
-    for (u32 cb = 0; cb < maxlen; cb += kFewTile) {
+    auto step = [&](u32 cb, float4 (&v)[8]) {                             // one piece: stage, request the one after the next, add
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
-            float* dst = &s_tile[p * 4 + wave][col];
-            dst[0] = v[p].x; dst[1] = v[p].y; dst[2] = v[p].z; dst[3] = v[p].w;
+            double2* dst = reinterpret_cast<double2*>(&s_tile[p * 4 + wave][col]);
+            dst[0] = make_double2(exact_square(v[p].x), exact_square(v[p].y));
+            dst[1] = make_double2(exact_square(v[p].z), exact_square(v[p].w));
         }
-        if (cb + kFewTile < maxlen) fetch(cb + kFewTile);
+        if (cb + 2 * kFewTile < maxlen) fetch(cb + 2 * kFewTile, v);
         __syncthreads();
         if (tid < kFewRows && len > cb) {
             const u32 m = (len - cb < static_cast<u32>(kFewTile)) ? len - cb : static_cast<u32>(kFewTile);
             u32 j = 0;
-            for (; j + 16 <= m; j += 16) {                // sixteen LDS reads at a time ahead of the addition chain
-                float t[16];
+            if (m >= 16) {                                // sixteen LDS reads in flight while the sixteen before are added up
+                double t[16];
 #pragma unroll
-                for (int k = 0; k < 16; ++k) t[k] = s_tile[tid][j + k];
+                for (int k = 0; k < 16; ++k) t[k] = s_tile[tid][k];
+                for (; j + 16 <= m; j += 16) {
+                    double next[16];
+                    const u32 ahead = j + 32 <= m ? j + 16 : j;
 #pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    const double x = static_cast<double>(t[k]);
-                    acc = acc + x * x;
+                    for (int k = 0; k < 16; ++k) next[k] = s_tile[tid][ahead + k];
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) acc = acc + t[k];
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) t[k] = next[k];
                 }
             }
-            for (; j < m; ++j) {
-                const double x = static_cast<double>(s_tile[tid][j]);
-                acc = acc + x * x;
-            }
+            for (; j < m; ++j) acc = acc + s_tile[tid][j];
         }
         __syncthreads();
+    };
+    float4 va[8], vb[8];
+    if (maxlen > 0) fetch(0, va);
+    if (maxlen > kFewTile) fetch(kFewTile, vb);
+    for (u32 cb = 0; cb < maxlen; cb += 2 * kFewTile) {    // uniform
+        step(cb, va);
+        if (cb + kFewTile < maxlen) step(cb + kFewTile, vb);
     }
     if (tid < kFewRows && u < a.F) {
         a.keys[u] = static_cast<u64>(__double_as_longlong(acc)) & 0x7FFFFFFFFFFFFFFFull;
@@ -396,6 +421,9 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows_few(StructArgs a, 
 // first levels take 50-65 us and the last ones 31 us because the keys come from HBM the first time and from the
 // last-level cache afterwards; 1024-thread workgroups (fewer flushes) and adding a wavefront's equal digits with
 // one LDS atomic changed nothing at the upper levels and cost 7 us at the lower ones.
+// Merged form: the keys of the one ranking are one array, cut into pieces of kKeyPiece (one batch of loads per thread; with
+// chunks of 8192 keys and a search for each chunk's owner 688 128 keys took 13 + 11 us and their list 9).
+constexpr u64 kKeyPiece = 8 * kBlock;
 __global__ __launch_bounds__(kBlock) void k_hist_keys(StructArgs a, int level, u64 chunks_per_block) {
     __shared__ u32 s_hist[kBins];
     __shared__ u64 s_prefix;
@@ -404,8 +432,9 @@ __global__ __launch_bounds__(kBlock) void k_hist_keys(StructArgs a, int level, u
     __shared__ u32 s_mactive;
     if (a.only_failed && a.ctl->window_failed == 0) return;
     const u64 c0 = static_cast<u64>(blockIdx.x) * chunks_per_block;
-    if (c0 >= a.n_schunks) return;
-    const u64 c1 = (c0 + chunks_per_block < a.n_schunks) ? c0 + chunks_per_block : a.n_schunks;
+    const u64 pieces = a.merged ? (a.F + kKeyPiece - 1) / kKeyPiece : a.n_schunks;
+    if (c0 >= pieces) return;
+    const u64 c1 = (c0 + chunks_per_block < pieces) ? c0 + chunks_per_block : pieces;
     const Level L = level_of(63, level);
     const int nb = 1 << L.bits;
     const int tid = threadIdx.x;
@@ -436,7 +465,7 @@ __global__ __launch_bounds__(kBlock) void k_hist_keys(StructArgs a, int level, u
     };
     long long cur_group = -1;
     for (u64 c = c0; c < c1; ++c) {
-        const int t = tensor_of_schunk(a.td, a.n_tensors, c);
+        const int t = a.merged ? 0 : tensor_of_schunk(a.td, a.n_tensors, c);
         const long long g = a.per_tensor ? t : 0;
         if (g != cur_group) {
             if (cur_group >= 0) {
@@ -458,10 +487,11 @@ __global__ __launch_bounds__(kBlock) void k_hist_keys(StructArgs a, int level, u
         }
         if (!s_active) continue;
         const TensorDesc& td = a.td[t];
-        const u64 base = (c - td.pad) * kChunk;
+        const u64 base = a.merged ? c * kKeyPiece : (c - td.pad) * kChunk;
         const u64 prefix = s_prefix;
-        const u64 end = (base + kChunk < td.n_struct) ? base + kChunk : td.n_struct;
-        const u64* __restrict__ kp = a.keys + td.struct_start;
+        const u64 piece = a.merged ? kKeyPiece : kChunk, all = a.merged ? a.F : td.n_struct;
+        const u64 end = (base + piece < all) ? base + piece : all;
+        const u64* __restrict__ kp = a.merged ? a.keys : a.keys + td.struct_start;
         // eight keys per step so that their loads overlap (a chunk is 32 keys per thread)
         for (u64 i0 = base + tid; i0 < end; i0 += 8 * kBlock) {
             u64 key[8];
@@ -625,8 +655,8 @@ __global__ __launch_bounds__(kBlock) void k_tie_locate_keys(StructArgs a, conden
 //
 // A CIFAR ResNet has 2 032 filters, its layers 16 to 64 each: rankings of that size are
 // bound by launch latency (six histogram + scan launch pairs, tie kernels, mask, scan, compaction: 19
-// launches of ~4.5 us).  One workgroup of 1024 threads per group does the same steps back to back: six
-// radix levels with an LDS histogram, the index search among tied aggregates, keep flags and the ordered
+// launches of ~4.5 us).  One workgroup of 1024 threads per group does the same steps back to back: the keys
+// in LDS and ranked there (rank_keys), the index search among tied aggregates, keep flags and the ordered
 // list of kept ids (every thread owns a contiguous run of structures, so a workgroup scan orders them).
 // Used when no group has more than kSmallGroup structures.
 
@@ -654,17 +684,18 @@ __device__ inline u64 small_excl_scan(u64 v, u64* s_part, u64* total) {
 
 __global__ __launch_bounds__(kSmallThreads) void k_struct_small(StructArgs a, u8* user_mask, int32_t* keep_idx,
                                                                 condensa_select* results) {
-    __shared__ u32 s_hist[kBins];
+    __shared__ RankShared sh;
+    __shared__ u64 s_key[kSmallGroup];
     __shared__ u64 s_part[kSmallThreads / 64];
-    __shared__ u64 s_sel[3];                               // bin, rank inside it, entries in it
-    __shared__ u64 s_tie_end;
+    __shared__ u32 s_wave[kSmallThreads / 64];
+    __shared__ u32 s_tie_end;
     const int g = blockIdx.x;
-    const int tid = threadIdx.x;
+    const u32 tid = threadIdx.x;
     Slot& slot = a.slots[g];
     const u64 first = a.per_tensor ? a.td[g].struct_start : 0;
-    const u64 n = a.per_tensor ? a.td[g + 1].struct_start - first : a.F;
+    const u32 n = static_cast<u32>(a.per_tensor ? a.td[g + 1].struct_start - first : a.F);     // at most kSmallGroup
     const u64 k = slot.k;
-    const u64* __restrict__ keys = a.keys + first;
+    for (u32 i = tid; i < n; i += kSmallThreads) s_key[i] = a.keys[first + i];
 
     // kept structures of the groups before this one: their kept counts are fixed by the density
     u64 kept_before = 0;
@@ -675,85 +706,49 @@ __global__ __launch_bounds__(kSmallThreads) void k_struct_small(StructArgs a, u8
         small_excl_scan(part, s_part, &tot);
         kept_before = tot;
     }
+    __syncthreads();
 
-    u64 T = ~static_cast<u64>(0), keep_ties = 0, n_tie = 0, tie_end = 0;
-    if (k > 0) {                                           // uniform over the workgroup
-        u64 prefix = 0, remaining = k;
-        for (int level = 0; level < n_levels(63); ++level) {
-            const Level L = level_of(63, level);
-            const int nb = 1 << L.bits;
-            for (int i = tid; i < nb; i += kSmallThreads) s_hist[i] = 0;
-            __syncthreads();
-            for (u64 i = tid; i < n; i += kSmallThreads) {
-                const u64 key = keys[i];
-                if (((key ^ prefix) >> L.hi_shift) == 0) atomicAdd(&s_hist[(key >> L.shift) & (nb - 1)], 1u);
-            }
-            __syncthreads();
-            // two bins per thread, from the top
-            u64 cnt[2], sum = 0;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int b = nb - 1 - (tid * 2 + j);
-                cnt[j] = (b >= 0) ? s_hist[b] : 0;
-                sum += cnt[j];
-            }
-            u64 total;
-            u64 cum = small_excl_scan(sum, s_part, &total);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int b = nb - 1 - (tid * 2 + j);
-                if (b >= 0 && cum < remaining && remaining <= cum + cnt[j]) {
-                    s_sel[0] = static_cast<u64>(b);
-                    s_sel[1] = remaining - cum;
-                    s_sel[2] = cnt[j];
-                }
-                cum += cnt[j];
-            }
-            __syncthreads();                               // k <= n, so exactly one thread wrote s_sel
-            prefix |= s_sel[0] << L.shift;
-            remaining = s_sel[1];
-            n_tie = s_sel[2];
-            __syncthreads();
-        }
-        T = prefix;
-        keep_ties = remaining;
+    u64 T = ~static_cast<u64>(0), keep_ties = 0, n_tie = 0;
+    if (k > 0) {                                           // uniform over the workgroup; k <= n
+        rank_keys<kSmallThreads>(sh, n, [&](u32 i) { return s_key[i]; }, k);
+        T = sh.key;
+        keep_ties = sh.rem;
+        n_tie = sh.n_tie;
     }
 
     // every thread owns the contiguous run [i0, i1) of the group
-    const u64 per = (n + kSmallThreads - 1) / kSmallThreads;
-    const u64 i0 = per * tid < n ? per * tid : n;
-    const u64 i1 = i0 + per < n ? i0 + per : n;
-    if (k > 0) {
-        tie_end = n;
-        if (keep_ties < n_tie) {                           // uniform: find the keep_ties-th tie in index order
-            u64 mine = 0;
-            for (u64 i = i0; i < i1; ++i) mine += (keys[i] == T) ? 1u : 0u;
-            u64 total;
-            const u64 before = small_excl_scan(mine, s_part, &total);
-            if (before < keep_ties && keep_ties <= before + mine) {
-                u64 seen = before;
-                for (u64 i = i0; i < i1; ++i) {
-                    if (keys[i] == T && ++seen == keep_ties) { s_tie_end = i + 1; break; }
-                }
+    const u32 per = (n + kSmallThreads - 1) / kSmallThreads;
+    const u32 i0 = per * tid < n ? per * tid : n;
+    const u32 i1 = i0 + per < n ? i0 + per : n;
+    u32 tie_end = k > 0 ? n : 0;
+    if (keep_ties < n_tie) {                               // uniform: find the keep_ties-th tie in index order
+        u32 mine = 0, total;
+        for (u32 i = i0; i < i1; ++i) mine += (s_key[i] == T) ? 1u : 0u;
+        const u32 before = wg_incl_scan_u32<kSmallThreads>(mine, s_wave, &total) - mine;
+        if (before < keep_ties && keep_ties <= before + mine) {
+            u32 seen = before;
+            for (u32 i = i0; i < i1; ++i) {
+                if (s_key[i] == T && ++seen == keep_ties) { s_tie_end = i + 1; break; }
             }
-            __syncthreads();
-            tie_end = s_tie_end;
         }
+        __syncthreads();
+        tie_end = s_tie_end;
     }
     // keep flags and the ordered list of kept ids
-    u64 kept = 0;
-    for (u64 i = i0; i < i1; ++i) {
-        const u64 key = keys[i];
+    u32 kept = 0, flags = 0;
+    for (u32 i = i0; i < i1; ++i) {                        // at most four
+        const u64 key = s_key[i];
         const u32 keep = (k > 0 && (key > T || (key == T && i < tie_end))) ? 1u : 0u;
         a.smask[first + i] = static_cast<u8>(keep);
         if (user_mask) user_mask[first + i] = static_cast<u8>(keep);
         kept += keep;
+        flags |= keep << (i - i0);
     }
     if (keep_idx) {
-        u64 total;
-        u64 pos = kept_before + small_excl_scan(kept, s_part, &total);
-        for (u64 i = i0; i < i1; ++i)
-            if (a.smask[first + i]) keep_idx[pos++] = static_cast<int32_t>(first + i);
+        u32 total;
+        u64 pos = kept_before + wg_incl_scan_u32<kSmallThreads>(kept, s_wave, &total) - kept;
+        for (u32 i = i0; i < i1; ++i)
+            if ((flags >> (i - i0)) & 1u) keep_idx[pos++] = static_cast<int32_t>(first + i);
     }
     if (tid == 0) {
         condensa_select out;
@@ -874,10 +869,12 @@ __global__ __launch_bounds__(kScanThreads) void k_struct_scan_blocks(u32* sblock
     }
 }
 
-// ascending ids of the kept structures
-__global__ __launch_bounds__(kBlock) void k_struct_keep_idx(StructArgs a, int32_t* keep_idx) {
+// Ascending ids of the kept structures of one tile.  Up to kIdTilesDirect tiles each workgroup adds up the counts of the
+// tiles before it; beyond, k_struct_scan_blocks has scanned them (a launch of 4.5 us, less than 2048 x 2048 loads cost).
+constexpr u64 kIdTilesDirect = 2048;
+__device__ inline void struct_keep_idx_tile(const StructArgs& a, int32_t* keep_idx, u32 tile, bool scanned) {
     __shared__ u32 s_wave[kBlock / 64];
-    const u64 u0 = (static_cast<u64>(blockIdx.x) * kBlock + threadIdx.x) * kMaskPer;
+    const u64 u0 = (static_cast<u64>(tile) * kBlock + threadIdx.x) * kMaskPer;
     u32 m[kMaskPer] = {0, 0, 0, 0};
     if (u0 + kMaskPer <= a.F) {
         const uchar4 x = *reinterpret_cast<const uchar4*>(a.smask + u0);
@@ -885,15 +882,29 @@ __global__ __launch_bounds__(kBlock) void k_struct_keep_idx(StructArgs a, int32_
     } else {
         for (int k = 0; k < kMaskPer; ++k) if (u0 + k < a.F) m[k] = a.smask[u0 + k];
     }
+    u32 before = 0;
+    if (scanned) {
+        before = a.sblock[tile];
+    } else {
+        u32 part = 0;
+        for (u32 i = threadIdx.x; i < tile; i += kBlock) part += a.sblock[i];
+        wg_incl_scan_u32<kBlock>(part, s_wave, &before);
+        __syncthreads();                                   // s_wave is used again
+    }
     const u32 sum = m[0] + m[1] + m[2] + m[3];
     u32 total;
-    u64 pos = static_cast<u64>(a.sblock[blockIdx.x]) + wg_incl_scan_u32<kBlock>(sum, s_wave, &total) - sum;
+    u64 pos = static_cast<u64>(before) + wg_incl_scan_u32<kBlock>(sum, s_wave, &total) - sum;
 #pragma unroll
     for (int k = 0; k < kMaskPer; ++k)
         if (m[k]) keep_idx[pos++] = static_cast<int32_t>(u0 + k);
 }
 
-// theta = w on kept structures, +0 elsewhere; element mask = structure mask broadcast
+__global__ __launch_bounds__(kBlock) void k_struct_keep_idx(StructArgs a, int32_t* keep_idx, int scanned) {
+    struct_keep_idx_tile(a, keep_idx, blockIdx.x, scanned != 0);
+}
+
+// theta = w on kept structures, +0 elsewhere; element mask = structure mask broadcast.  The list of kept ids depends on
+// nothing that the sweep writes, so its tiles ride in the same launch, first.
 template <bool VEC>
 __device__ inline void struct_apply_tile(const StructArgs& a, const OutDesc* __restrict__ out, u64 tile) {
     const u64 c = tile / kSubPerChunk;
@@ -977,8 +988,10 @@ __device__ inline void struct_apply_tile(const StructArgs& a, const OutDesc* __r
 }
 
 template <bool VEC>
-__global__ __launch_bounds__(kBlock) void k_struct_apply(StructArgs a, const OutDesc* __restrict__ out) {
-    struct_apply_tile<VEC>(a, out, blockIdx.x);
+__global__ __launch_bounds__(kBlock) void k_struct_apply(StructArgs a, const OutDesc* __restrict__ out, int32_t* keep_idx, u32 id_tiles,
+                                                         int scanned) {
+    if (blockIdx.x < id_tiles) struct_keep_idx_tile(a, keep_idx, blockIdx.x, scanned != 0);
+    else                       struct_apply_tile<VEC>(a, out, blockIdx.x - id_tiles);
 }
 
 // Thinning gather: out[o', i', r] = w[keep_out[o'] - off_out, keep_in[i'] - off_in, r]; NULL list = identity.
