@@ -4,6 +4,7 @@ torch is used for device memory and the current stream; no arithmetic happens he
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 from typing import Dict, List, Optional, Sequence
@@ -204,13 +205,12 @@ def _cached(tensors, key, make):
 
 
 def _ptr_table(tensors: Optional[Sequence]):
-    """Host array of device pointers (None entries become NULL); None -> NULL table."""
+    """Host array of device pointers (None entries and tensors without elements become NULL); None -> NULL table.
+    The first value owns the memory that the second points to."""
     if tensors is None:
         return None, None
-    arr = (ctypes.c_void_p * max(len(tensors), 1))()
-    for i, t in enumerate(tensors):
-        arr[i] = None if (t is None or t.numel() == 0) else t.data_ptr()
-    return arr, ctypes.cast(arr, ctypes.c_void_p)
+    arr = array.array("Q", [0 if t is None else t.data_ptr() for t in tensors] or [0])     # data_ptr of an empty tensor is 0
+    return arr, ctypes.c_void_p(arr.buffer_info()[0])
 
 
 def condensa_config(**fields) -> Config:
