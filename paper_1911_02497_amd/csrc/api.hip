@@ -1955,10 +1955,32 @@ condensa_status condensa_lc_sgd_step(const condensa_tensor* tensors, int n_tenso
     rc = check_workspace(workspace_dev, workspace_bytes, L);
     if (rc != CONDENSA_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (tb.n_chunks == 0) return CONDENSA_OK;
+    const unsigned grid = static_cast<unsigned>(tb.n_chunks * (kChunk / 256));
+    bool few = n_tensors <= kSgdFewTensors;                 // chunks are numbered in 32 bits by the launch already
+    for (int t = 0; t < n_tensors && few; ++t) few = tb.td[t].n <= 0xFFFFFFFFull;
+    if (few) {
+        SgdFewArgs f;
+        for (int t = 0; t < kSgdFewTensors; ++t) {
+            const bool there = t < n_tensors;
+            f.w[t] = there ? const_cast<float*>(tb.td[t].w) : nullptr;
+            f.grad[t] = there ? tb.td[t].grad : nullptr;
+            f.theta[t] = there ? out[t].theta : nullptr;
+            f.lam[t] = there ? tb.td[t].lam : nullptr;
+            f.mom[t] = there ? tb.td[t].lam_out : nullptr;
+            f.n[t] = there ? static_cast<u32>(tb.td[t].n) : 0;
+            f.chunk_start[t] = there ? static_cast<u32>(tb.td[t].chunk_start) : ~0u;
+        }
+        f.mu = mu; f.lr = lr; f.momentum = momentum;
+        PhaseTimer timer(CONDENSA_PHASE_APPLY, st, cfg);
+        if (vec) hipLaunchKernelGGL((k_lc_sgd_few<true>), dim3(grid), dim3(64), 0, st, f);
+        else     hipLaunchKernelGGL((k_lc_sgd_few<false>), dim3(grid), dim3(64), 0, st, f);
+        CONDENSA_LAUNCH_CHECK();
+        return CONDENSA_OK;
+    }
     rc = begin_call(L, tb, n_tensors, out.data(), out.size(), nullptr, 0, workspace_dev, st);
     if (rc != CONDENSA_OK) return rc;
 
-    if (tb.n_chunks == 0) return CONDENSA_OK;
     DataArgs a{};
     a.td = at<TensorDesc>(workspace_dev, L.td);
     a.chunk_map = at<u32>(workspace_dev, L.chunk_map);
@@ -1968,7 +1990,6 @@ condensa_status condensa_lc_sgd_step(const condensa_tensor* tensors, int n_tenso
     a.mu = mu;
     PhaseTimer timer(CONDENSA_PHASE_APPLY, st, cfg);
     const OutDesc* od = at<OutDesc>(workspace_dev, L.out);
-    const unsigned grid = static_cast<unsigned>(tb.n_chunks * (kChunk / 256));
     if (vec) hipLaunchKernelGGL((k_lc_sgd<true>), dim3(grid), dim3(64), 0, st, a, od, lr, momentum);
     else     hipLaunchKernelGGL((k_lc_sgd<false>), dim3(grid), dim3(64), 0, st, a, od, lr, momentum);
     CONDENSA_LAUNCH_CHECK();

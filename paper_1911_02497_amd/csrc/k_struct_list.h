@@ -74,7 +74,7 @@ constexpr u32 kListHeld = 4096;           // list entries held in LDS
 
 // One workgroup ranks the list, applies the lowest-id rule among equal aggregates and writes state and record.  A lone
 // workgroup is bound by latency: four more levels over a list in memory took 22 us for the 688 128 blocks, one level
-// and pairs in LDS %(FINISH)s.
+// and pairs in LDS 5.9.
 __global__ __launch_bounds__(kSmallFinishThreads) void k_struct_list_finish(StructArgs a, StructListArgs l, condensa_select* results,
                                                                            int id_bits) {
     __shared__ SlotStep s_e;
