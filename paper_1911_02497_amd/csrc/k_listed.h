@@ -642,7 +642,7 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
 // updates ranking j), so their latency is paid once, and the entries leave in runs.  Masks alone leave as 16 bytes per
 // lane, the regions having changed places in LDS.
 constexpr int kListMultiQuads = 4;
-constexpr u32 kListMultiBuf = 1024;              // buffered entries of a wavefront: an equal share for each ranking; more are written at once
+constexpr u32 kListMultiBuf = 512;               // buffered entries of a wavefront: an equal share for each ranking; more are written at once
 struct ListMultiShared {
     u32 key[kListMultiBuf];
     u32 tile[256 * kListMultiQuads];             // the tile's keys, then its regions
