@@ -1428,9 +1428,10 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
     }
     // One sweep for aggregation AND apply (k_struct_fused.h): 8x8 blocks, every matrix a whole number of 64-block
     // runs wide, 128-bit accesses everywhere, outputs apart from the weights, a threshold strictly inside the
-    // population, and enough blocks for the sample to pay (or the form asked for).
+    // population, and enough blocks for the sample to pay (or the form asked for): 2^20 blocks take 218 us this way and
+    // 181 with the aggregates first and a list (k_struct_list.h), 1.5 M blocks 262 and 258, 3.7 M blocks 487 and 606.
     bool fused = !per_tensor && (theta || mask) && vec && tb.F > kSmallGroup && slots[0].k > 0 && slots[0].k < tb.F &&
-                 (cfg[CONDENSA_OPT_SELECT_PATH] == 2 || (cfg[CONDENSA_OPT_SELECT_PATH] == 0 && tb.F >= (static_cast<u64>(1) << 20))) &&
+                 (cfg[CONDENSA_OPT_SELECT_PATH] == 2 || (cfg[CONDENSA_OPT_SELECT_PATH] == 0 && tb.F >= (static_cast<u64>(3) << 19))) &&
                  cfg[CONDENSA_OPT_FUSED_SWEEP] == 0;
     for (int t = 0; t < n_tensors && fused; ++t) {
         const TensorDesc& d = tb.td[t];
@@ -1558,16 +1559,13 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
             }
             a.only_failed = 1;
         }
-        // moderate rankings on the automatic path: two levels over all aggregates, then a list (k_struct_list.h)
+        // moderate rankings on the automatic path: one histogram over all aggregates, then a list (k_struct_list.h)
         const bool listed = !per_tensor && !small && !fused && tb.F <= kSmallCallElems && cfg[CONDENSA_OPT_SELECT_PATH] == 0;
         const u64 pieces = a.merged ? (tb.F + kKeyPiece - 1) / kKeyPiece : tb.n_schunks;
-        for (int level = 0; level < (listed ? kStructListLevels : n_levels(63)) && !small; ++level) {
-            // level 0 separates little, so that a workgroup adds a few bins to the ranking's histogram; the next ones add
-            // most of 2048 each (688 128 keys, level 1: 336 workgroups 16.4 us, 120 of them 10.7)
-            const u64 most = listed ? (level == 0 ? 256 : 96) : 1024;
-            u64 blocks = pieces < most ? pieces : most;
-            const u64 cpb = (pieces + blocks - 1) / blocks;
-            blocks = (pieces + cpb - 1) / cpb;
+        u64 cpb = (pieces + 1023) / 1024;
+        if (a.merged && cpb < 4) cpb = 4;                    // fewer workgroups, fewer of them adding to the same 2048 counters
+        const u64 blocks = (pieces + cpb - 1) / (cpb ? cpb : 1);
+        for (int level = 0; level < n_levels(63) && !small && !listed; ++level) {
             hipLaunchKernelGGL(k_hist_keys, dim3(static_cast<unsigned>(blocks)), dim3(kBlock), 0, st, a, level, cpb);
             CONDENSA_LAUNCH_CHECK();
             if (a.merged) continue;                            // the next kernel folds this level in itself
@@ -1581,6 +1579,14 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
             l.key = at<u64>(workspace_dev, L.cand_idx);
             l.id = at<u32>(workspace_dev, L.cand_key);
             l.cap = L.cand_cap;
+            l.window = reinterpret_cast<u32*>(l.count + 1);
+            // each workgroup adds most of 2048 bins to the ranking's histogram (688 128 keys of one radix level: 336 workgroups
+            // took 16.4 us, 120 of them 10.7)
+            u64 hb = pieces < 96 ? pieces : 96;
+            const u64 ppb = (pieces + hb - 1) / hb;
+            hb = (pieces + ppb - 1) / ppb;
+            hipLaunchKernelGGL(k_struct_list_hist, dim3(static_cast<unsigned>(hb)), dim3(kBlock), 0, st, a, l, ppb);
+            CONDENSA_LAUNCH_CHECK();
             hipLaunchKernelGGL(k_struct_list_collect, dim3(static_cast<unsigned>(pieces < 1024 ? pieces : 1024)), dim3(kBlock), 0, st, a, l);
             CONDENSA_LAUNCH_CHECK();
             hipLaunchKernelGGL(k_struct_list_finish, dim3(1), dim3(kSmallFinishThreads), 0, st, a, l, results_dev, bits_for(tb.F - 1));

@@ -112,6 +112,20 @@ __device__ inline bool rank_keys(RankShared& sh, u32 n, KeyOf key_of, u64 rank64
     const u32 diff = sh.any ^ sh.all;
     int top = diff == 0 ? 32 : 64 - __clz(static_cast<int>(diff));             // bits below which the keys may differ
     u64 prefix = ((static_cast<u64>(sh.all) << 32) >> top) << top;
+    if (diff == 0 && n > kRankPairs) {                     // uniform: the same for the lower halves (ties above all)
+        any = 0; all = ~0u;
+        for (u32 i = tid; i < n; i += THREADS) { const u32 low = static_cast<u32>(key_of(i)); any |= low; all &= low; }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) { any |= __shfl_xor(any, d, 64); all &= __shfl_xor(all, d, 64); }
+        __syncthreads();
+        if (tid == 0) { sh.any = 0; sh.all = ~0u; }
+        __syncthreads();
+        if ((tid & 63u) == 0) { atomicOr(&sh.any, any); atomicAnd(&sh.all, all); }
+        __syncthreads();
+        const u32 low_diff = sh.any ^ sh.all;
+        top = low_diff == 0 ? 0 : 32 - __clz(static_cast<int>(low_diff));
+        prefix |= (static_cast<u64>(sh.all) >> top) << top;
+    }
     u32 rank = static_cast<u32>(rank64), n_in = n;
     while (top > 0 && n_in > kRankPairs) {                 // uniform; the 256 counts are clear here
         const int bits = top < 8 ? top : 8, shift = top - bits;

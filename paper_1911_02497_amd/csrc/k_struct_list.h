@@ -1,10 +1,14 @@
 // Structure rankings of moderate size (more than k_struct_small's 4096 structures, at most kSmallCallElems, GLOBAL
-// scope): two radix levels over the aggregates, then a list.
+// scope): one histogram over a window of the aggregates, then a list.
 //
-// The six levels of a 63-bit ranking are six dependent launches plus the tie search.  Aggregates of one model share
-// their sign and most exponent bits, so level 0 barely separates them; after level 1 (22 of 63 bits) the threshold's
-// bin holds a few hundred structures.  k_struct_list_collect lists those (key, structure id) pairs and
-// k_struct_list_finish, one workgroup, finishes on the list.  The list can hold every structure, so nothing overflows.  A Transformer's 688 128 blocks of 8x8: 14 -> 10 launches.
+// The six levels of a 63-bit ranking are six dependent launches plus the tie search, and the first of them separate little:
+// aggregates of one model share their sign and most exponent bits.  So every workgroup of k_struct_list_hist first takes the
+// same 256 aggregates and bounds the threshold by two of their order statistics, six standard deviations of its rank to
+// either side; 2047 equal steps between them are the bins, and what lies outside belongs to the first or last one.
+// k_struct_list_collect lists the (key, id) pairs of the threshold's bin, a hundred or so, and k_struct_list_finish, one
+// workgroup, finishes on the list.  The list can hold every structure, so nothing overflows, and a sample that misleads
+// makes it longer, never wrong.  Two radix levels instead of the window took 13 + 11 us for a Transformer's 688 128 blocks
+// of 8x8 and 12 + 10 for 270 400 blocks of 5x5; this one 11.4 and 8.2.
 // Table 1 (FilterPrune, BlockPrune: structures are aggregated and pruned); Section 3.1.
 #pragma once
 #include "k_small.h"
@@ -12,29 +16,111 @@
 
 namespace condensa {
 
-constexpr int kStructListLevels = 2;      // radix levels counted over all aggregates before the list takes over
+constexpr u32 kStructSample = 256;        // aggregates of the sample, one per thread
 
 struct StructListArgs {
     u64* count;            // entries offered (never more than cap: the list holds every structure)
     u64* key;              // [cap]
     u32* id;               // [cap] global structure ids
     u64 cap;
+    u32* window;           // its lower end (upper halves of the keys) and the shift of its bins
 };
 
+__device__ inline u32 struct_window_bin(u64 key, u32 lo, u32 shift) {
+    const u32 hi = static_cast<u32>(key >> 32);
+    const u32 b = hi < lo ? 0u : (hi - lo) >> shift;
+    return b < static_cast<u32>(kBins) ? b : static_cast<u32>(kBins) - 1u;
+}
+
+// The bin of the threshold: the histogram stands where that of radix level 0 would, whose digit has as many values.
+__device__ inline SlotStep struct_window_step(const StructArgs& a, u32* bin) {
+    const SlotStep e = wave_enter_level(a.slots[0], 1, 63, struct_hist(a, 0), struct_coarse(a, 0));
+    *bin = static_cast<u32>(e.prefix >> level_of(63, 0).shift);
+    return e;
+}
+static_assert(kBins == 1 << 11, "radix level 0 of 63 bits has 11 bits");
+
+__global__ __launch_bounds__(kBlock) void k_struct_list_hist(StructArgs a, StructListArgs l, u64 pieces_per_block) {
+    static_assert(kStructSample == kBlock, "one sampled aggregate per thread");
+    __shared__ __align__(16) u32 s_hist[kBins];
+    __shared__ u32 s_sample[kStructSample];
+    __shared__ u32 s_end[2];
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const Slot& slot = a.slots[0];
+    if (slot_canonical(slot).state != kSelecting) return;  // uniform: k == 0, nothing to rank
+    s_sample[tid] = static_cast<u32>(a.keys[static_cast<u64>(tid) * a.F / kStructSample] >> 32);
+    for (int i = tid; i < kBins; i += kBlock) s_hist[i] = 0;
+    __syncthreads();
+    if (wave < 2) {                                        // wavefront 0: the upper end, 1: the lower end
+        const double p = static_cast<double>(slot.k) / static_cast<double>(a.F), S = kStructSample;
+        const double off = 6.0 * sqrt(S * p * (1.0 - p)) + 2.0, at = p * S + (wave == 0 ? -off : off);
+        const u32 want = at < 1.0 ? 1u : (at > S ? kStructSample : static_cast<u32>(at));
+        u32 v[4], found = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = s_sample[lane + 64 * i];
+        for (int bit = 30; bit >= 0; --bit) {              // the want-th largest, bit by bit
+            const u32 c = found | (1u << bit);
+            u32 n = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) n += __popcll(__ballot(v[i] >= c));
+            if (n >= want) found = c;
+        }
+        if (found == 0 && wave == 1) {                     // zeros (weights pruned before): a window from there on would leave
+            u32 least = 0xFFFFFFFFu;                       // a bin half an octave wide; what lies four octaves below the least
+#pragma unroll                                             // sampled value goes with the zeros
+            for (int i = 0; i < 4; ++i) least = v[i] != 0 && v[i] < least ? v[i] : least;
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) { const u32 o = __shfl_xor(least, d, 64); least = o < least ? o : least; }
+            if (least != 0xFFFFFFFFu && least > (4u << 20)) found = least - (4u << 20);
+        }
+        if (lane == 0) s_end[wave] = found;
+    }
+    __syncthreads();
+    const u32 hi = s_end[0], lo = s_end[1] < hi ? s_end[1] : hi, span = hi - lo;
+    const u32 shift = span < static_cast<u32>(kBins) ? 0u : 21u - static_cast<u32>(__clz(static_cast<int>(span)));
+    if (blockIdx.x == 0 && tid == 0) { l.window[0] = lo; l.window[1] = shift; }
+    const u64 base = static_cast<u64>(blockIdx.x) * pieces_per_block * kKeyPiece;
+    const u64 stop = base + pieces_per_block * kKeyPiece < a.F ? base + pieces_per_block * kKeyPiece : a.F;
+    for (u64 i0 = base + tid; i0 < stop; i0 += kKeyPiece) {
+        constexpr int kPer = static_cast<int>(kKeyPiece) / kBlock;
+        u64 key[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const u64 i = i0 + static_cast<u64>(u) * kBlock;
+            key[u] = i < stop ? a.keys[i] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kPer; ++u)
+            if (i0 + static_cast<u64>(u) * kBlock < stop) atomicAdd(&s_hist[struct_window_bin(key[u], lo, shift)], 1u);
+    }
+    __syncthreads();
+    u64* hist = struct_hist(a, 0);
+    for (int i = tid; i < kBins; i += kBlock) {
+        const u32 v = s_hist[i];
+        if (v) atomicAdd(reinterpret_cast<unsigned long long*>(hist + i), static_cast<unsigned long long>(v));
+    }
+    static_assert(kBins / kCoarse == 32 && kBins / kBlock == 8, "four threads add up the bins of a coarse sum");
+    const uint4 x = *reinterpret_cast<const uint4*>(s_hist + 8 * tid), y = *reinterpret_cast<const uint4*>(s_hist + 8 * tid + 4);
+    u32 sum = x.x + x.y + x.z + x.w + y.x + y.y + y.z + y.w;
+    sum += __shfl_xor(sum, 1, 64);
+    sum += __shfl_xor(sum, 2, 64);
+    if ((tid & 3u) == 0 && sum)
+        atomicAdd(reinterpret_cast<unsigned long long*>(struct_coarse(a, 0) + tid / 4), static_cast<unsigned long long>(sum));
+}
+
 __global__ __launch_bounds__(kBlock) void k_struct_list_collect(StructArgs a, StructListArgs l) {
-    __shared__ SlotStep s_e;
+    __shared__ u32 s_bin, s_selecting;
     __shared__ u64 s_wave[kBlock / 64];
     __shared__ u64 s_base;
     const int tid = threadIdx.x;
     if (tid < 64) {
-        const SlotStep e = wave_enter_level(a.slots[0], kStructListLevels, 63, struct_hist(a, kStructListLevels - 1),
-                                            struct_coarse(a, kStructListLevels - 1));
-        if (tid == 0) s_e = e;
+        u32 bin;
+        const SlotStep e = struct_window_step(a, &bin);
+        if (tid == 0) { s_bin = bin; s_selecting = e.state == kSelecting ? 1u : 0u; }
     }
     __syncthreads();
-    if (s_e.state != kSelecting) return;                   // uniform: k == 0, nothing to rank
-    const u64 prefix = s_e.prefix;
-    const Level L = level_of(63, kStructListLevels - 1);   // entries agree with the prefix down to this level's digit
+    if (s_selecting == 0) return;                          // uniform: k == 0, nothing to rank
+    const u32 bin = s_bin, lo = l.window[0], shift = l.window[1];
     for (u64 base = static_cast<u64>(blockIdx.x) * kKeyPiece; base < a.F; base += static_cast<u64>(gridDim.x) * kKeyPiece) {
         const u64 end = (base + kKeyPiece < a.F) ? base + kKeyPiece : a.F;
         const u64* __restrict__ kp = a.keys;               // the ranking is over all structures: their keys are one array
@@ -44,11 +130,11 @@ __global__ __launch_bounds__(kBlock) void k_struct_list_collect(StructArgs a, St
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const u64 i = base + tid + static_cast<u64>(u) * kBlock;
-            key[u] = (i < end) ? kp[i] : ~prefix;          // a filler that fails the prefix test
+            key[u] = (i < end) ? kp[i] : 0;
         }
 #pragma unroll
         for (int u = 0; u < kPer; ++u)
-            if (base + tid + static_cast<u64>(u) * kBlock < end && ((key[u] ^ prefix) >> L.shift) == 0) listed |= 1u << u;
+            if (base + tid + static_cast<u64>(u) * kBlock < end && struct_window_bin(key[u], lo, shift) == bin) listed |= 1u << u;
         u64 total;
         const u64 before = block_excl_scan_u64(static_cast<u64>(__popc(listed)), s_wave, &total);
         if (total != 0) {                                  // uniform over the workgroup
@@ -73,8 +159,8 @@ __global__ __launch_bounds__(kBlock) void k_struct_list_collect(StructArgs a, St
 constexpr u32 kListHeld = 4096;           // list entries held in LDS
 
 // One workgroup ranks the list, applies the lowest-id rule among equal aggregates and writes state and record.  A lone
-// workgroup is bound by latency: four more levels over a list in memory took 22 us for the 688 128 blocks, one level
-// and pairs in LDS 5.9.
+// workgroup is bound by latency: four radix levels over a list in memory took 22 us for the 688 128 blocks, one level of
+// eight bits and pairs in LDS 5.9.
 __global__ __launch_bounds__(kSmallFinishThreads) void k_struct_list_finish(StructArgs a, StructListArgs l, condensa_select* results,
                                                                            int id_bits) {
     __shared__ SlotStep s_e;
@@ -92,8 +178,8 @@ __global__ __launch_bounds__(kSmallFinishThreads) void k_struct_list_finish(Stru
     if (held) for (u32 i = tid; i < n; i += kSmallFinishThreads) s_key[i] = l.key[i];
     if (tid == 0) s_n = 0;
     if (tid < 64) {
-        const SlotStep e = wave_enter_level(slot, kStructListLevels, 63, struct_hist(a, kStructListLevels - 1),
-                                            struct_coarse(a, kStructListLevels - 1));
+        u32 bin;
+        const SlotStep e = struct_window_step(a, &bin);
         if (tid == 0) s_e = e;
     }
     __syncthreads();

@@ -67,3 +67,18 @@ def test_kept_ids_of_many_tiles(rows):
     rng = np.random.default_rng(rows)
     w = rng.choice(np.array([0.25, 0.5, 1.0], np.float32), (rows, 2048)) * rng.standard_normal((rows, 2048)).astype(np.float32)
     _compare(block_prune(up([w]), 1, 2, 0.31, P.SCOPE_GLOBAL), oracle.block_prune([w], 1, 2, 0.31, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], f"rows={rows}")
+
+
+@pytest.mark.parametrize("zeros", [0.5, 0.9, 0.999, 1.0])
+def test_ranking_of_rows_pruned_before(zeros):
+    n = 20000
+    rng = np.random.default_rng(17)
+    v = rng.lognormal(0.0, 0.2, n).astype(np.float32)
+    v[rng.random(n) < zeros] = 0.0
+    if zeros < 1.0:
+        v[::1999] = 1e-18          # far below what a sample of the others shows
+    w = _neurons(v, 3)
+    kept = float(np.count_nonzero(v)) / n
+    for d in (0.8 * kept, kept - 2.0 / n, kept, kept + 3.0 / n, 0.5 + 0.5 * kept):
+        d = min(max(d, 0.0), 1.0)
+        _compare(neuron_prune(up([w]), d, P.SCOPE_GLOBAL), oracle.neuron_prune([w], d, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], f"zeros={zeros} d={d}")
