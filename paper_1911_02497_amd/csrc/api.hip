@@ -1531,8 +1531,10 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
                 hipLaunchKernelGGL((k_struct_tiles_fused<128>), dim3(static_cast<unsigned>((tb.F + 127) / 128)), dim3(128), 0, st, a, sw, sumsq_dev, norms_dev);
             else if (fused)
                 hipLaunchKernelGGL((k_struct_tiles_fused<64>), dim3(static_cast<unsigned>((tb.F + 63) / 64)), dim3(64), 0, st, a, sw, sumsq_dev, norms_dev);
+            else if (rows && tb.F <= 512 * kFewRows)
+                hipLaunchKernelGGL((k_struct_sumsq_rows_few<true>), dim3(static_cast<unsigned>((tb.F + kFewRows - 1) / kFewRows)), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
             else if (rows && tb.F <= kFewRowsMax)
-                hipLaunchKernelGGL(k_struct_sumsq_rows_few, dim3(static_cast<unsigned>((tb.F + kFewRows - 1) / kFewRows)), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
+                hipLaunchKernelGGL((k_struct_sumsq_rows_few<false>), dim3(static_cast<unsigned>((tb.F + kFewRows - 1) / kFewRows)), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
             else if (rows) hipLaunchKernelGGL(k_struct_sumsq_rows, dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
             else if (tiles && tile_w == 4)  hipLaunchKernelGGL((k_struct_sumsq_tiles<1>), dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
             else if (tiles && tile_w == 8)  hipLaunchKernelGGL((k_struct_sumsq_tiles<2>), dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);

@@ -3,6 +3,7 @@
 // Table 1: FilterPrune (filters, seen as 3-D blocks, are aggregated and pruned), BlockPrune (blocks of any
 // dimensionality and a given size); Section 3.1: the schemes aggregate filters, neurons and blocks.
 #pragma once
+#include <type_traits>
 #include "k_apply.h"
 #include "k_select.h"
 #include "k_small.h"
@@ -306,14 +307,18 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows(StructArgs a, doub
 // flight, the next two pieces are requested before the current one is added up, and the first kFewRows threads
 // add their rows' pieces in memory order.  That chain bounds a call of few rows: 15 ns per element while its threads also
 // converted to binary64 (a quarter-rate instruction), so the staging threads convert and
-// square (the square of a binary32 is exact in binary64).  Rows of any length and alignment: a float4 that lies inside
+// square (the square of a binary32 is exact in binary64).  SQUARED: that form, two workgroups to a compute unit; beyond two
+// of them each, binary32 tiles let four be resident, and the sweep is bound by memory (28 186 rows of 7767: a whole call
+// 657 us with these, 815 with the others).  Rows of any length and alignment: a float4 that lies inside
 // an aligned row is one 128-bit load, anything else is fetched element by element.
 constexpr int kFewRows = 32;
 constexpr int kFewTile = 256;
 constexpr int kFewStarts = 512;
 
+template <bool SQUARED>
 __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows_few(StructArgs a, double* sumsq, float* norms) {
-    __shared__ __align__(16) double s_tile[kFewRows][kFewTile + 2];
+    using Staged = typename std::conditional<SQUARED, double, float>::type;
+    __shared__ __align__(16) Staged s_tile[kFewRows][kFewTile + (SQUARED ? 2 : 1)];
     __shared__ const float* s_row[kFewRows];
     __shared__ u32 s_len[kFewRows];
     __shared__ u32 s_vec[kFewRows];
@@ -371,13 +376,19 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows_few(StructArgs a, 
         }
     };
     auto exact_square = [](float x) { const double d = static_cast<double>(x); return d * d; };      // 48 bits: no rounding
+    auto square_of = [&](Staged x) { if constexpr (SQUARED) return x; else return exact_square(x); };
     double acc = 0.0;
     auto step = [&](u32 cb, float4 (&v)[8]) {                             // one piece: stage, request the one after the next, add
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
-            double2* dst = reinterpret_cast<double2*>(&s_tile[p * 4 + wave][col]);
-            dst[0] = make_double2(exact_square(v[p].x), exact_square(v[p].y));
-            dst[1] = make_double2(exact_square(v[p].z), exact_square(v[p].w));
+            if constexpr (SQUARED) {
+                double2* dst = reinterpret_cast<double2*>(&s_tile[p * 4 + wave][col]);
+                dst[0] = make_double2(exact_square(v[p].x), exact_square(v[p].y));
+                dst[1] = make_double2(exact_square(v[p].z), exact_square(v[p].w));
+            } else {
+                float* dst = &s_tile[p * 4 + wave][col];
+                dst[0] = v[p].x; dst[1] = v[p].y; dst[2] = v[p].z; dst[3] = v[p].w;
+            }
         }
         if (cb + 2 * kFewTile < maxlen) fetch(cb + 2 * kFewTile, v);
         __syncthreads();
@@ -385,21 +396,21 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows_few(StructArgs a, 
             const u32 m = (len - cb < static_cast<u32>(kFewTile)) ? len - cb : static_cast<u32>(kFewTile);
             u32 j = 0;
             if (m >= 16) {                                // sixteen LDS reads in flight while the sixteen before are added up
-                double t[16];
+                Staged t[16];
 #pragma unroll
                 for (int k = 0; k < 16; ++k) t[k] = s_tile[tid][k];
                 for (; j + 16 <= m; j += 16) {
-                    double next[16];
+                    Staged next[16];
                     const u32 ahead = j + 32 <= m ? j + 16 : j;
 #pragma unroll
                     for (int k = 0; k < 16; ++k) next[k] = s_tile[tid][ahead + k];
 #pragma unroll
-                    for (int k = 0; k < 16; ++k) acc = acc + t[k];
+                    for (int k = 0; k < 16; ++k) acc = acc + square_of(t[k]);
 #pragma unroll
                     for (int k = 0; k < 16; ++k) t[k] = next[k];
                 }
             }
-            for (; j < m; ++j) acc = acc + s_tile[tid][j];
+            for (; j < m; ++j) acc = acc + square_of(s_tile[tid][j]);
         }
         __syncthreads();
     };

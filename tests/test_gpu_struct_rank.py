@@ -82,3 +82,10 @@ def test_ranking_of_rows_pruned_before(zeros):
     for d in (0.8 * kept, kept - 2.0 / n, kept, kept + 3.0 / n, 0.5 + 0.5 * kept):
         d = min(max(d, 0.0), 1.0)
         _compare(neuron_prune(up([w]), d, P.SCOPE_GLOBAL), oracle.neuron_prune([w], d, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], f"zeros={zeros} d={d}")
+
+
+@pytest.mark.parametrize("rows", [16384, 16385, 32768, 32769])      # where the staged sums of rows change their form
+def test_sums_of_many_rows(rows):
+    rng = np.random.default_rng(rows)
+    w = rng.standard_normal((rows, 277)).astype(np.float32)
+    _compare(neuron_prune(up([w]), 0.2, P.SCOPE_GLOBAL), oracle.neuron_prune([w], 0.2, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], f"rows={rows}")
