@@ -227,16 +227,13 @@ static u64 window_cand_capacity(u64 N, int J, const Config& cfg) {
 // the size where its lists, in proportion to the population, cost more than the sampled window's deeper ranking does
 // (L-C step of 2^27 weights 509-531 us against 550-566, of 2^28 1004-1036 against 972-1003; pruning 295 against 315 and
 // 561 against 511).  Sampled window (k_window.h, k_fused.h): one density beyond that, several beyond 32-bit indices.
-// Radix levels: where neither applies, and for more densities than two on few weights, where each list is short and its
-// ranking's launches are not (10 densities: 46 thousand weights 66 us listed, 56 by levels; 93 thousand 67 and 58; 233 thousand
-// 68 and 72.  4 densities: 17 thousand 46 and 42; 46 thousand 45.7 and 46.3.  2: 17 thousand 37 and 40).
+// Radix levels: where neither applies.
 static bool list_fits(u64 N, int n_tensors, int n_slots) {
     return N > 0 && n_slots <= kListMaxRankings && N + static_cast<u64>(n_tensors) * kChunk < (static_cast<u64>(1) << 32);
 }
 static bool want_list(u64 N, int n_tensors, int n_slots, bool per_tensor, int J, const Config& cfg) {
     if (cfg[CONDENSA_OPT_SELECT_PATH] != 0 || !list_fits(N, n_tensors, n_slots)) return false;
-    if (per_tensor || J <= 2) return per_tensor || J == 2 || N < (static_cast<u64>(3) << 26);
-    return N >= static_cast<u64>(J) << 14;
+    return per_tensor || J > 1 || N < (static_cast<u64>(3) << 26);
 }
 static bool want_window(u64 N, int n_tensors, bool per_tensor, int J, const Config& cfg) {
     if (per_tensor) return false;
@@ -244,16 +241,15 @@ static bool want_window(u64 N, int n_tensors, bool per_tensor, int J, const Conf
     const int64_t mode = cfg[CONDENSA_OPT_SELECT_PATH];
     if (mode == 1) return false;
     if (mode == 2) return N >= 1;
-    if (list_fits(N, n_tensors, J) && J > 1) return false; // listed, or too few weights for either
     return N > 0 && !want_list(N, n_tensors, J, per_tensor, J, cfg);
 }
 
 // Segments of the rankings' lists: what their sweep's wavefronts call for (elements per wavefront).
-static u64 list_wave_elems(int J, bool lc) { return 256u * static_cast<u64>(J > 1 ? kListMultiQuads : (lc ? kFusedQuadsLC : kFusedQuadsPrune)); }
+static u64 list_wave_elems(u64 N, int J, bool lc) { return 256u * static_cast<u64>(J > 1 ? list_multi_quads(N) : (lc ? kFusedQuadsLC : kFusedQuadsPrune)); }
 static u32 list_max_segs(u64 n, int n_slots, int J, bool lc) {
     u32 most = J > 1 ? 256u : static_cast<u32>(kListSegs);
     while (most > 16 && static_cast<u64>(most) * n_slots > (1u << 16)) most /= 2;        // many rankings share the atomics' rate
-    return list_segments(n, list_wave_elems(J, lc), most);
+    return list_segments(n, list_wave_elems(n, J, lc), most);
 }
 // List entries of one ranking, a multiple of kListRow n_segs; and the most that the rankings of one density can add up
 // to when the tensors' sizes are not known yet.
@@ -690,7 +686,7 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
     for (size_t g = 0; g < n_groups; ++g) {
         const u64 n = per_tensor ? tb.td[g].n : tb.N;
         const u32 w = list_groups(n, J, cfg);
-        u32 segs = list_segments(n, list_wave_elems(J, lc), L.l_max_segs);
+        u32 segs = list_segments(n, list_wave_elems(tb.N, J, lc), L.l_max_segs);
         for (int j = 0; j < J; ++j) {
             ListRank& r = rk[g * J + j];
             const u64 entries = n ? list_entries(n, segs, cfg) : 0;
@@ -822,10 +818,14 @@ static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* w
             if (vec) hipLaunchKernelGGL((k_list_sweep<false, true, Q, false>), grid, dim3(64), 0, st, a, w);
             else     hipLaunchKernelGGL((k_list_sweep<false, false, Q, false>), grid, dim3(64), 0, st, a, w);
         } else {
-            const dim3 gm(static_cast<unsigned>(a.n_chunks * (kChunk / (256 * kListMultiQuads))));
-            if (vec && rq.wide) hipLaunchKernelGGL((k_list_sweep_multi<true, true>), gm, dim3(64), 0, st, a, w);
-            else if (vec)       hipLaunchKernelGGL((k_list_sweep_multi<true, false>), gm, dim3(64), 0, st, a, w);
-            else                hipLaunchKernelGGL((k_list_sweep_multi<false, false>), gm, dim3(64), 0, st, a, w);
+            const int quads = list_multi_quads(a.N);
+            const dim3 gm(static_cast<unsigned>(a.n_chunks * (kChunk / (256 * static_cast<unsigned>(quads)))));
+            constexpr int QM = kListMultiQuads;
+            if (quads == 1 && vec)  hipLaunchKernelGGL((k_list_sweep_multi<true, false, 1>), gm, dim3(64), 0, st, a, w);
+            else if (quads == 1)    hipLaunchKernelGGL((k_list_sweep_multi<false, false, 1>), gm, dim3(64), 0, st, a, w);
+            else if (vec && rq.wide) hipLaunchKernelGGL((k_list_sweep_multi<true, true, QM>), gm, dim3(64), 0, st, a, w);
+            else if (vec)           hipLaunchKernelGGL((k_list_sweep_multi<true, false, QM>), gm, dim3(64), 0, st, a, w);
+            else                    hipLaunchKernelGGL((k_list_sweep_multi<false, false, QM>), gm, dim3(64), 0, st, a, w);
         }
         CONDENSA_LAUNCH_CHECK();
     }

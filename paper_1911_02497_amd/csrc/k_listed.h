@@ -642,6 +642,10 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
 // updates ranking j), so their latency is paid once, and the entries leave in runs.  Masks alone leave as 16 bytes per
 // lane, the regions having changed places in LDS.
 constexpr int kListMultiQuads = 4;
+// Calls of few weights take a quarter of that per wavefront: each ranking costs a wavefront some 3 us of latency (ten
+// densities of 46 thousand weights 66 us with 1024 elements to a wavefront, 45.9 with 256; of 233 thousand 67.7 and 53.4).
+constexpr u64 kListMultiFew = static_cast<u64>(1) << 18;
+__host__ __device__ inline int list_multi_quads(u64 N) { return N <= kListMultiFew ? 1 : kListMultiQuads; }
 constexpr u32 kListMultiBuf = 512;               // buffered entries of a wavefront: an equal share for each ranking; more are written at once
 struct ListMultiShared {
     u32 key[kListMultiBuf];
@@ -690,10 +694,9 @@ __device__ inline void list_multi_flush(const DataArgs& a, const ListArgs& w, co
 }
 
 // The general form: a tile that is ragged, or windows that overlap.  The rankings are walked one by one.
-template <bool VEC>
+template <bool VEC, int Q>
 __device__ inline void list_multi_general(const DataArgs& a, const ListArgs& w, ListMultiShared& sh, const TensorDesc& td, int t, u64 c, u32 sub,
                                           u64 base, bool full) {
-    constexpr int Q = kListMultiQuads;
     constexpr int kWaveElems = 256 * Q;
     const int lane = threadIdx.x;
     const u64 n = td.n;
@@ -786,9 +789,8 @@ __device__ inline void list_multi_general(const DataArgs& a, const ListArgs& w, 
 }
 
 // WIDE: masks only, each 16-byte aligned.
-template <bool VEC, bool WIDE>
+template <bool VEC, bool WIDE, int Q>
 __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w) {
-    constexpr int Q = kListMultiQuads;
     constexpr int kWaveElems = 256 * Q;
     constexpr u32 kSub = kChunk / kWaveElems;
     __shared__ __align__(16) ListMultiShared sh;
@@ -804,7 +806,7 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
     const bool full = VEC && base + kWaveElems <= td.n;                 // uniform over the wavefront
     const ListSorted& srt = w.sorted[a.per_tensor ? t : 0];
     if (!full || !srt.disjoint) {
-        list_multi_general<VEC>(a, w, sh, td, t, c, sub, base, full);
+        list_multi_general<VEC, Q>(a, w, sh, td, t, c, sub, base, full);
         return;
     }
     float v[Q][4];
@@ -861,7 +863,7 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
             list_multi_append(w, r0 + j, x, i0 + off);
         }
     }
-    if (WIDE) {                                                         // lane l takes the regions of elements 16 l .. 16 l + 15
+    if constexpr (WIDE) {                                               // lane l takes the regions of elements 16 l .. 16 l + 15
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < Q; ++q) sh.tile[q * 64 + lane] = packed[q];
@@ -880,7 +882,7 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
             m[q] = ((packed[q] + bias) >> 7) & 0x01010101u;
             kept = __builtin_amdgcn_udot4(m[q], 0x01010101u, kept, false);
         }
-        if (WIDE) {
+        if constexpr (WIDE) {
             if (o.mask) {
                 u32x4 t4;
                 t4.x = m[0]; t4.y = m[1]; t4.z = m[2]; t4.w = m[3];
