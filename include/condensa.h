@@ -174,7 +174,7 @@ condensa_status condensa_prune(const condensa_tensor* tensors, int n_tensors,
  * stack and reach the device as kernel arguments, and no timing events are created.  Limits
  * (CONDENSA_ERR_SIZE beyond them): at most CONDENSA_STATIC_MAX_ELEMS elements in total, at most
  * CONDENSA_STATIC_MAX_TENSORS tensors and CONDENSA_STATIC_MAX_DENSITIES densities.  The selection always
- * runs the radix levels over the weights (the form condensa_prune picks by itself below 2^26 elements).
+ * runs the radix levels over the weights.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams, two
  * threads) race; order them on one stream.  The first call on a device looks up the array's address.
  */
