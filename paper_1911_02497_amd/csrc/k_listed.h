@@ -643,8 +643,9 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
 // lane, the regions having changed places in LDS.
 constexpr int kListMultiQuads = 4;
 // Calls of few weights take a quarter of that per wavefront: each ranking costs a wavefront some 3 us of latency (ten
-// densities of 46 thousand weights 66 us with 1024 elements to a wavefront, 45.9 with 256; of 233 thousand 67.7 and 53.4).
-constexpr u64 kListMultiFew = static_cast<u64>(1) << 18;
+// densities of 46 thousand weights 66 us with 1024 elements to a wavefront, 45.9 with 256; of 295 thousand 67.5
+// and 53.7; two of 295 thousand 37.4 and 36.9, of 2.3 M 42.3 and 47.5).
+constexpr u64 kListMultiFew = static_cast<u64>(1) << 19;
 __host__ __device__ inline int list_multi_quads(u64 N) { return N <= kListMultiFew ? 1 : kListMultiQuads; }
 constexpr u32 kListMultiBuf = 512;               // buffered entries of a wavefront: an equal share for each ranking; more are written at once
 struct ListMultiShared {
