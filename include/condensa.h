@@ -18,7 +18,8 @@
  *    memory and frees none.  (It keeps a small pool of pinned host memory for the tables.)
  *  - All device work is enqueued on `stream` (a hipStream_t, NULL = the default stream) and the
  *    call returns without waiting.  Results, including condensa_select records, are in device
- *    memory once the stream has reached that point.
+ *    memory once the stream has reached that point.  A call on a stream that is being captured becomes
+ *    part of the graph together with its tables; the graph refers to the caller's buffers only.
  *  - Return value: CONDENSA_OK or a negative error code.  Argument errors are found before
  *    anything is enqueued, so a failing call has no side effect.
  *  - Tensors are fp32, row-major, contiguous.  16-byte aligned pointers get 128-bit accesses,

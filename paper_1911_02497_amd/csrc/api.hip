@@ -86,8 +86,11 @@ u64* stage_done(int i) { return reinterpret_cast<u64*>(g_stage_block + static_ca
 }  // namespace
 
 condensa_status StageImage::acquire(size_t bytes, hipStream_t stream) {
+    if (tried_) return CONDENSA_OK;
+    tried_ = true;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
+    if (capture != hipStreamCaptureStatusNone) return CONDENSA_OK;
     std::unique_lock<std::mutex> lock(g_stage_mu);
     if (g_stage_block == nullptr) {
         void* p = nullptr;
@@ -122,7 +125,7 @@ condensa_status StageImage::acquire(size_t bytes, hipStream_t stream) {
     s.filling = true;
     slot_ = found;
     data_ = bytes > kStageBytes ? s.big : g_stage_block + kStageSlots * 64 + static_cast<size_t>(found) * kStageBytes;
-    done_ = capture == hipStreamCaptureStatusNone ? stage_done(found) : nullptr;
+    done_ = stage_done(found);
     ticket_ = s.ticket + 1;
     return CONDENSA_OK;
 }
@@ -131,7 +134,7 @@ void StageImage::commit() {
     if (slot_ < 0) return;
     std::lock_guard<std::mutex> lock(g_stage_mu);
     g_stage[slot_].filling = false;
-    if (done_) g_stage[slot_].ticket = ticket_;
+    g_stage[slot_].ticket = ticket_;
     slot_ = -1;
 }
 
@@ -537,19 +540,27 @@ static u64 begin_blocks(u64 n_zero, u64 n_chunks) {
 
 // What every call starts with: the tables [tensors | outputs | rankings] reach the front of the workspace, the
 // counter and histogram region is cleared and the chunk -> tensor map is written.  One launch while the tables are
-// small (kBeginTensors tensors, one staging slot), two beyond that.  `fixed`: for callers that cannot allocate, the
-// memory to build the tables' image in; they then travel as kernel arguments.
+// small (kBeginTensors tensors, one staging slot), two beyond that.  Without a slot (`img`: a captured call) and for
+// callers that cannot allocate (no `img`, but `fixed`: memory to build the image in) the tables travel as kernel
+// arguments, which a graph copies.
 static condensa_status begin_call(const Layout& L, const Tables& tb, int n_tensors, const OutDesc* out, size_t n_out,
-                                  const Slot* slots, size_t n_slots, void* ws, hipStream_t st, char* fixed = nullptr,
-                                  const void* lists = nullptr, size_t list_bytes = 0) {
+                                  const Slot* slots, size_t n_slots, void* ws, hipStream_t st, StageImage* img,
+                                  const void* lists = nullptr, size_t list_bytes = 0, char* fixed = nullptr) {
     const size_t td_bytes = static_cast<size_t>(tb.n_td) * sizeof(TensorDesc), out_bytes = n_out * sizeof(OutDesc),
                  slot_bytes = n_slots * sizeof(Slot);
     const u64 n_words = L.zero_bytes / 8;
-    if (fixed) {
+    if (img) {
+        const condensa_status rc = img->acquire(td_bytes + out_bytes + slot_bytes + list_bytes, st);    // each a multiple of 16 bytes
+        if (rc != CONDENSA_OK) return rc;
+    }
+    if (img == nullptr || img->data() == nullptr) {
+        std::vector<char> own;
+        if (!fixed) { own.resize(L.upload_bytes); fixed = own.data(); }
         std::memcpy(fixed + L.td, tb.td, td_bytes);
         if (out_bytes) std::memcpy(fixed + L.out, out, out_bytes);
         if (slot_bytes) std::memcpy(fixed + L.slots, slots, slot_bytes);
-        const condensa_status rc = poke_upload(ws, fixed, L.upload_bytes, st);
+        condensa_status rc = poke_upload(ws, fixed, L.upload_bytes, st);
+        if (rc == CONDENSA_OK) rc = poke_upload(at<char>(ws, L.l_rank), static_cast<const char*>(lists), list_bytes, st);
         if (rc != CONDENSA_OK) return rc;
         hipLaunchKernelGGL(k_prepare, dim3(fill_grid(n_words)), dim3(kBlock), 0, st, at<u64>(ws, L.zero_begin), n_words,
                            at<TensorDesc>(ws, L.td), n_tensors, at<u32>(ws, L.chunk_map), tb.n_chunks,
@@ -557,10 +568,7 @@ static condensa_status begin_call(const Layout& L, const Tables& tb, int n_tenso
         CONDENSA_LAUNCH_CHECK();
         return CONDENSA_OK;
     }
-    StageImage img;
-    const condensa_status rc = img.acquire(td_bytes + out_bytes + slot_bytes + list_bytes, st);    // each a multiple of 16 bytes
-    if (rc != CONDENSA_OK) return rc;
-    const UploadArgs up = fill_image(img, L, ws, tb, out, out_bytes, slots, slot_bytes, lists, list_bytes);
+    const UploadArgs up = fill_image(*img, L, ws, tb, out, out_bytes, slots, slot_bytes, lists, list_bytes);
     if (n_tensors <= kBeginTensors && td_bytes + out_bytes + slot_bytes + list_bytes <= kStageBytes) {
         BeginArgs b{};
         b.up = up;
@@ -573,18 +581,18 @@ static condensa_status begin_call(const Layout& L, const Tables& tb, int n_tenso
         const u64 blocks = begin_blocks(b.n_zero, tb.n_chunks) + 1;
         hipLaunchKernelGGL(k_begin, dim3(static_cast<unsigned>(blocks)), dim3(kBeginThreads), 0, st, b);
         CONDENSA_LAUNCH_CHECK();
-        img.commit();
+        img->commit();
         return CONDENSA_OK;
     }
     const u32 up_blocks = (up.end[3] + 4 * kBlock - 1) / (4 * kBlock);
     hipLaunchKernelGGL(k_upload, dim3(up_blocks ? up_blocks : 1), dim3(kBlock), 0, st, up);
     CONDENSA_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_prepare, dim3(fill_grid(n_words)), dim3(kBlock), 0, st, at<u64>(ws, L.zero_begin), n_words,
-                       at<TensorDesc>(ws, L.td), n_tensors, at<u32>(ws, L.chunk_map), tb.n_chunks, img.done(), img.ticket());
+                       at<TensorDesc>(ws, L.td), n_tensors, at<u32>(ws, L.chunk_map), tb.n_chunks, img->done(), img->ticket());
     // the upload is in the stream: were this launch to fail, its slot could not be handed out before the upload has run
     const hipError_t launched = hipGetLastError();
     if (launched != hipSuccess) (void)hipStreamSynchronize(st);
-    else img.commit();
+    else img->commit();
     g_launches.fetch_add(1, std::memory_order_relaxed);
     CONDENSA_HIP(launched);
     return CONDENSA_OK;
@@ -749,17 +757,16 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const L
 template <bool LC, bool VEC>
 static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n_tensors, const OutDesc* out, size_t n_out, const Slot* slots,
                                         const double* densities, int J, bool per_tensor, float mu, void* ws, hipStream_t st,
-                                        const std::vector<char>& lists, u32 groups, const ListRequest& rq, const Config& cfg, bool* begun) {
+                                        const std::vector<char>& lists, u32 groups, const ListRequest& rq, const Config& cfg, StageImage* img, bool* begun) {
     *begun = false;
     const size_t td_bytes = static_cast<size_t>(tb.n_td) * sizeof(TensorDesc), out_bytes = n_out * sizeof(OutDesc),
                  slot_bytes = static_cast<size_t>(L.n_slots) * sizeof(Slot);
     if (n_tensors > kBeginSampleTensors || groups > 0xFFFFu || td_bytes + out_bytes + slot_bytes + lists.size() > kStageBytes) return CONDENSA_OK;
+    const condensa_status rc = img->acquire(td_bytes + out_bytes + slot_bytes + lists.size(), st);
+    if (rc != CONDENSA_OK || img->data() == nullptr) return rc;
     PhaseTimer timer(CONDENSA_PHASE_SAMPLE, st, cfg);
-    StageImage img;
-    const condensa_status rc = img.acquire(td_bytes + out_bytes + slot_bytes + lists.size(), st);
-    if (rc != CONDENSA_OK) return rc;
     BeginSampleArgs b{};
-    b.up = fill_image(img, L, ws, tb, out, out_bytes, slots, slot_bytes, lists.data(), lists.size());
+    b.up = fill_image(*img, L, ws, tb, out, out_bytes, slots, slot_bytes, lists.data(), lists.size());
     b.zero = at<uint4>(ws, L.zero_begin);
     b.n_zero = L.zero_bytes / 16;
     b.chunk_map = at<u32>(ws, L.chunk_map);
@@ -784,7 +791,7 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
     hipLaunchKernelGGL((k_begin_sample<LC, VEC>), dim3(static_cast<unsigned>(blocks)), dim3(kListThreads), 0, st, b,
                        list_args(L, ws, tb.N, L.n_slots, rq, cfg));
     CONDENSA_LAUNCH_CHECK();
-    img.commit();
+    img->commit();
     *begun = true;
     return CONDENSA_OK;
 }
@@ -901,7 +908,7 @@ __global__ __launch_bounds__(kBlock) void k_poke(u64* dst, PokeWords src, u32 n)
 static condensa_status poke_upload(void* dst_dev, const char* src_host, size_t bytes, hipStream_t st) {
     constexpr size_t kPiece = sizeof(PokeWords);
     for (size_t off = 0; off < bytes; off += kPiece) {
-        const size_t n = bytes - off < kPiece ? bytes - off : kPiece;      // bytes is a multiple of 256
+        const size_t n = bytes - off < kPiece ? bytes - off : kPiece;      // bytes is a multiple of 16
         PokeWords pw;
         std::memcpy(pw.w, src_host + off, n);
         hipLaunchKernelGGL(k_poke, dim3(1), dim3(kBlock), 0, st, reinterpret_cast<u64*>(static_cast<char*>(dst_dev) + off),
@@ -993,11 +1000,12 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
     const bool listed_write = L.listed && any_out && !in_place_any && cfg[CONDENSA_OPT_FUSED_SWEEP] == 0;
     const ListRequest rq{od, vec, false, listed_write, nullptr, masks_wide && !theta && !theta_f16};
     bool sampled = false;
+    StageImage img;
     if (L.listed)
-        rc = tb.vec ? begin_and_sample<false, true>(L, tb, n_tensors, out, n_out, slots, densities, J, per_tensor, 0.0f, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled)
-                    : begin_and_sample<false, false>(L, tb, n_tensors, out, n_out, slots, densities, J, per_tensor, 0.0f, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled);
+        rc = tb.vec ? begin_and_sample<false, true>(L, tb, n_tensors, out, n_out, slots, densities, J, per_tensor, 0.0f, workspace_dev, st, lists, list_shape.groups, rq, cfg, &img, &sampled)
+                    : begin_and_sample<false, false>(L, tb, n_tensors, out, n_out, slots, densities, J, per_tensor, 0.0f, workspace_dev, st, lists, list_shape.groups, rq, cfg, &img, &sampled);
     if (rc == CONDENSA_OK && !sampled)
-        rc = begin_call(L, tb, n_tensors, out, n_out, slots, n_up_slots, workspace_dev, st, fixed, lists.data(), list_bytes);
+        rc = begin_call(L, tb, n_tensors, out, n_out, slots, n_up_slots, workspace_dev, st, no_alloc ? nullptr : &img, lists.data(), list_bytes, fixed);
     if (rc != CONDENSA_OK) return rc;
 
     DataArgs a{};
@@ -1218,11 +1226,12 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
     const OutDesc* od = at<OutDesc>(workspace_dev, L.out);
     const ListRequest rq{od, vec, pq, !in_place_any && cfg[CONDENSA_OPT_FUSED_SWEEP] == 0, pq ? nnz_dev : nullptr, false};
     bool sampled = false;
+    StageImage img;
     if (L.listed)
-        rc = vec_in ? begin_and_sample<true, true>(L, tb, n_tensors, out.data(), out.size(), slot4, &density, 1, false, mu, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled)
-                    : begin_and_sample<true, false>(L, tb, n_tensors, out.data(), out.size(), slot4, &density, 1, false, mu, workspace_dev, st, lists, list_shape.groups, rq, cfg, &sampled);
+        rc = vec_in ? begin_and_sample<true, true>(L, tb, n_tensors, out.data(), out.size(), slot4, &density, 1, false, mu, workspace_dev, st, lists, list_shape.groups, rq, cfg, &img, &sampled)
+                    : begin_and_sample<true, false>(L, tb, n_tensors, out.data(), out.size(), slot4, &density, 1, false, mu, workspace_dev, st, lists, list_shape.groups, rq, cfg, &img, &sampled);
     if (rc == CONDENSA_OK && !sampled)
-        rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slot4, window ? 4 : 1, workspace_dev, st, nullptr, lists.data(), list_bytes);
+        rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slot4, window ? 4 : 1, workspace_dev, st, &img, lists.data(), list_bytes);
     if (rc != CONDENSA_OK) return rc;
 
     DataArgs a{};
@@ -1351,7 +1360,8 @@ condensa_status condensa_count_nonzero(const condensa_tensor* tensors, int n_ten
     ranges.push_back(byte_range(count_dev, sizeof(uint64_t), true));
     if (ranges_conflict(ranges.data(), ranges.size())) return CONDENSA_ERR_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = begin_call(L, tb, n_tensors, nullptr, 0, nullptr, 0, workspace_dev, st);
+    StageImage img;
+    rc = begin_call(L, tb, n_tensors, nullptr, 0, nullptr, 0, workspace_dev, st, &img);
     if (rc != CONDENSA_OK) return rc;
 
     DataArgs a{};
@@ -1445,7 +1455,8 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
         slots[0].path = 2;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slots.data(), static_cast<size_t>(L.n_slots) + (fused ? 3 : 0), workspace_dev, st);
+    StageImage img;
+    rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slots.data(), static_cast<size_t>(L.n_slots) + (fused ? 3 : 0), workspace_dev, st, &img);
     if (rc != CONDENSA_OK) return rc;
 
     StructArgs a{};
@@ -1986,7 +1997,8 @@ condensa_status condensa_lc_sgd_step(const condensa_tensor* tensors, int n_tenso
         CONDENSA_LAUNCH_CHECK();
         return CONDENSA_OK;
     }
-    rc = begin_call(L, tb, n_tensors, out.data(), out.size(), nullptr, 0, workspace_dev, st);
+    StageImage img;
+    rc = begin_call(L, tb, n_tensors, out.data(), out.size(), nullptr, 0, workspace_dev, st, &img);
     if (rc != CONDENSA_OK) return rc;
 
     DataArgs a{};

@@ -61,20 +61,22 @@ inline bool density_ok(double d) { return d >= 0.0 && d <= 1.0; }   // false for
 // itself (k_begin, k_upload), so that no copy command is queued -- measured, a blit of 4 us in front of every call,
 // and 30 us and more where the runtime chose a DMA engine (tables beyond 16 KB).  The kernel that has read the image
 // stores `ticket` in *done (pinned too), which is what frees the slot: no event either.  A slot that is not
-// committed returns to the pool by itself.
+// committed returns to the pool by itself.  A captured call gets none (data() stays NULL): its kernels read the tables
+// again at every replay, whenever that is, so they have to be part of the graph.
 class StageImage {
 public:
     StageImage() = default;
     ~StageImage();
     StageImage(const StageImage&) = delete;
     StageImage& operator=(const StageImage&) = delete;
-    condensa_status acquire(size_t bytes, hipStream_t stream);
+    condensa_status acquire(size_t bytes, hipStream_t stream);     // the first call only; later ones find what it found
     void commit();                            // the kernel that will store the ticket is in the stream
     char* data() const { return data_; }
-    u64* done() const { return done_; }       // NULL while the stream is captured: replays store nothing
+    u64* done() const { return done_; }
     u64 ticket() const { return ticket_; }
 private:
     int slot_ = -1;
+    bool tried_ = false;
     char* data_ = nullptr;
     u64* done_ = nullptr;
     u64 ticket_ = 0;

@@ -300,8 +300,8 @@ __global__ __launch_bounds__(kBeginThreads) void k_begin(BeginArgs b) {
 }
 
 // Many tensors (or tables beyond one staging slot): the upload, then the clearing and the map as a second launch,
-// which also frees the slot -- it starts when the upload has ended.  The entry point for callers that cannot
-// allocate brings its tables as kernel arguments (k_poke) and uses the second part only.
+// which also frees the slot -- it starts when the upload has ended.  Captured calls and the entry point for callers that
+// cannot allocate bring their tables as kernel arguments (k_poke) and use the second part only.
 __global__ __launch_bounds__(kBlock) void k_upload(UploadArgs u) { upload_words(u, blockIdx.x * kBlock + threadIdx.x, gridDim.x * kBlock); }
 
 __global__ __launch_bounds__(kBlock) void k_prepare(u64* zero, u64 n_words, const TensorDesc* td, int n_tensors,
