@@ -67,9 +67,11 @@ condensa_status resolve_config(const condensa_config* c, Config* out) {
 namespace {
 // The slots' words and their first kStageBytes each are one pinned block, allocated on the first call; a larger image
 // gets a buffer of its own, which stays with the slot.  A slot is free when it is not being filled and the device
-// has stored the ticket of its last use.
+// has stored the ticket of its last use.  A call that finds none waits (the host is 32 calls ahead), but not for ever: its
+// tables then travel as kernel arguments, whose launches report an error of the device.
 constexpr int kStageSlots = 32;
 constexpr size_t kStageBytes = 64u << 10;
+constexpr std::chrono::milliseconds kStageWait{100};
 constexpr unsigned kStageFlags = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
 struct Stage {
     char* big = nullptr;
@@ -99,17 +101,24 @@ condensa_status StageImage::acquire(size_t bytes, hipStream_t stream) {
         g_stage_block = static_cast<char*>(p);
     }
     int found = -1;
-    for (int tries = 0; found < 0; ++tries) {
-        for (int k = 0; k < kStageSlots && found < 0; ++k) {
+    const auto give_up = std::chrono::steady_clock::now() + kStageWait;
+    for (int tries = 0;; ++tries) {
+        for (int k = 0; k < kStageSlots; ++k) {
             const int i = (g_stage_next + k) % kStageSlots;
-            if (!g_stage[i].filling && __atomic_load_n(stage_done(i), __ATOMIC_ACQUIRE) == g_stage[i].ticket) found = i;
+            if (g_stage[i].filling || __atomic_load_n(stage_done(i), __ATOMIC_ACQUIRE) != g_stage[i].ticket) continue;
+            if (found < 0) found = i;
+            if (bytes <= kStageBytes || g_stage[i].big_cap >= bytes) { found = i; break; }     // one that needs no new buffer
         }
-        if (found < 0) {                      // every slot is in flight: the call waits for the device to catch up
-            lock.unlock();
-            if (tries < 2000) std::this_thread::yield();
-            else std::this_thread::sleep_for(std::chrono::microseconds(20));
-            lock.lock();
+        if (found >= 0) break;
+        // every slot is in flight: the device is behind, or does not answer
+        lock.unlock();
+        if (tries < 2000) {
+            std::this_thread::yield();
+        } else {
+            if (std::chrono::steady_clock::now() > give_up) return CONDENSA_OK;
+            std::this_thread::sleep_for(std::chrono::microseconds(20));
         }
+        lock.lock();
     }
     Stage& s = g_stage[found];
     if (bytes > kStageBytes && s.big_cap < bytes) {
@@ -121,7 +130,7 @@ condensa_status StageImage::acquire(size_t bytes, hipStream_t stream) {
         s.big = static_cast<char*>(p);
         s.big_cap = align_up(bytes, 4096);
     }
-    g_stage_next = (found + 1) % kStageSlots;
+    if (bytes <= kStageBytes) g_stage_next = (found + 1) % kStageSlots;      // large images keep to the slots that have a buffer
     s.filling = true;
     slot_ = found;
     data_ = bytes > kStageBytes ? s.big : g_stage_block + kStageSlots * 64 + static_cast<size_t>(found) * kStageBytes;
@@ -138,9 +147,15 @@ void StageImage::commit() {
     slot_ = -1;
 }
 
-StageImage::~StageImage() {                   // not committed: nothing on the device refers to the slot
+// Not committed.  Once a launch was attempted the kernel may be in the stream whatever was reported: the error can be one
+// that the thread had left behind.  The slot is then free when the stream has been waited for, at whichever ticket the
+// device left; if the stream itself has failed, it stays out of the pool.
+StageImage::~StageImage() {
     if (slot_ < 0) return;
+    const bool drained = !launched_ || hipStreamSynchronize(stream_) == hipSuccess;
+    if (!drained) { (void)hipGetLastError(); return; }
     std::lock_guard<std::mutex> lock(g_stage_mu);
+    g_stage[slot_].ticket = __atomic_load_n(stage_done(slot_), __ATOMIC_ACQUIRE);
     g_stage[slot_].filling = false;
 }
 
@@ -540,7 +555,7 @@ static u64 begin_blocks(u64 n_zero, u64 n_chunks) {
 
 // What every call starts with: the tables [tensors | outputs | rankings] reach the front of the workspace, the
 // counter and histogram region is cleared and the chunk -> tensor map is written.  One launch while the tables are
-// small (kBeginTensors tensors, one staging slot), two beyond that.  Without a slot (`img`: a captured call) and for
+// small (kBeginTensors tensors, one staging slot), two beyond that.  Without a slot (`img`: a captured call, or none free) and for
 // callers that cannot allocate (no `img`, but `fixed`: memory to build the image in) the tables travel as kernel
 // arguments, which a graph copies.
 static condensa_status begin_call(const Layout& L, const Tables& tb, int n_tensors, const OutDesc* out, size_t n_out,
@@ -579,22 +594,20 @@ static condensa_status begin_call(const Layout& L, const Tables& tb, int n_tenso
         b.n_tensors = n_tensors;
         for (int t = 0; t <= n_tensors; ++t) b.chunk_start[t] = static_cast<u32>(tb.td[t].chunk_start);
         const u64 blocks = begin_blocks(b.n_zero, tb.n_chunks) + 1;
+        img->launching(st);
         hipLaunchKernelGGL(k_begin, dim3(static_cast<unsigned>(blocks)), dim3(kBeginThreads), 0, st, b);
         CONDENSA_LAUNCH_CHECK();
         img->commit();
         return CONDENSA_OK;
     }
     const u32 up_blocks = (up.end[3] + 4 * kBlock - 1) / (4 * kBlock);
+    img->launching(st);
     hipLaunchKernelGGL(k_upload, dim3(up_blocks ? up_blocks : 1), dim3(kBlock), 0, st, up);
     CONDENSA_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_prepare, dim3(fill_grid(n_words)), dim3(kBlock), 0, st, at<u64>(ws, L.zero_begin), n_words,
                        at<TensorDesc>(ws, L.td), n_tensors, at<u32>(ws, L.chunk_map), tb.n_chunks, img->done(), img->ticket());
-    // the upload is in the stream: were this launch to fail, its slot could not be handed out before the upload has run
-    const hipError_t launched = hipGetLastError();
-    if (launched != hipSuccess) (void)hipStreamSynchronize(st);
-    else img->commit();
-    g_launches.fetch_add(1, std::memory_order_relaxed);
-    CONDENSA_HIP(launched);
+    CONDENSA_LAUNCH_CHECK();
+    img->commit();
     return CONDENSA_OK;
 }
 
@@ -788,6 +801,7 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
     }
     for (int t = 0; t <= n_tensors; ++t) b.chunk_start[t] = static_cast<u32>(tb.td[t].chunk_start);
     const u64 blocks = begin_blocks(b.n_zero, tb.n_chunks) + 1 + groups;
+    img->launching(st);
     hipLaunchKernelGGL((k_begin_sample<LC, VEC>), dim3(static_cast<unsigned>(blocks)), dim3(kListThreads), 0, st, b,
                        list_args(L, ws, tb.N, L.n_slots, rq, cfg));
     CONDENSA_LAUNCH_CHECK();

@@ -62,7 +62,8 @@ inline bool density_ok(double d) { return d >= 0.0 && d <= 1.0; }   // false for
 // and 30 us and more where the runtime chose a DMA engine (tables beyond 16 KB).  The kernel that has read the image
 // stores `ticket` in *done (pinned too), which is what frees the slot: no event either.  A slot that is not
 // committed returns to the pool by itself.  A captured call gets none (data() stays NULL): its kernels read the tables
-// again at every replay, whenever that is, so they have to be part of the graph.
+// again at every replay, whenever that is, so they have to be part of the graph.  Nor does a call that finds none free for
+// long.
 class StageImage {
 public:
     StageImage() = default;
@@ -70,13 +71,15 @@ public:
     StageImage(const StageImage&) = delete;
     StageImage& operator=(const StageImage&) = delete;
     condensa_status acquire(size_t bytes, hipStream_t stream);     // the first call only; later ones find what it found
+    void launching(hipStream_t stream) { launched_ = true; stream_ = stream; }     // before the first kernel that reads the image
     void commit();                            // the kernel that will store the ticket is in the stream
     char* data() const { return data_; }
     u64* done() const { return done_; }
     u64 ticket() const { return ticket_; }
 private:
     int slot_ = -1;
-    bool tried_ = false;
+    bool tried_ = false, launched_ = false;
+    hipStream_t stream_ = nullptr;
     char* data_ = nullptr;
     u64* done_ = nullptr;
     u64 ticket_ = 0;

@@ -1,5 +1,6 @@
 """GPU parity of what every call starts with: tables of one launch and of two (more than 256 tensors, or tables beyond
-one staging slot), and more calls in flight than there are staging slots, from several threads and streams."""
+one staging slot), more calls in flight than there are staging slots, from several threads and streams, behind a stream
+that is busy for long, and after calls that failed once their first kernel was queued."""
 import threading
 
 import numpy as np
@@ -62,3 +63,37 @@ def test_threads_and_streams_share_the_slots():
     for m, w, rs in zip(models, want, got):
         for r in rs:
             check_prune_against_oracle(r, w, P.SCOPE_GLOBAL, 5)
+
+
+@pytest.mark.parametrize("n_tensors", [3, 700])
+def test_a_busy_stream_holds_no_call_back_for_good(n_tensors):
+    models = [_model(n_tensors, 500 + i) for i in range(3)]
+    dev = [up(m) for m in models]
+    torch.cuda.synchronize()
+    torch.cuda._sleep(600_000_000)                           # some tenths of a second, longer than a call waits for a slot
+    out = [P.condensa_prune(dev[i % 3], [0.25]) for i in range(40)]
+    torch.cuda.synchronize()
+    for i in (0, 1, 2, 37, 38, 39):
+        check_prune_against_oracle(out[i], oracle.prune(models[i % 3], [0.25], P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, n_tensors)
+
+
+def test_calls_that_fail_after_their_launch_give_their_slots_back():
+    """An error that the thread left behind (here: a device number that does not exist) is reported by the call's first launch
+    check, after the kernel that reads the slot was queued.  More of these than there are slots, then ordinary calls."""
+    m = _model(3, 7)
+    d = up(m)
+    res = P.condensa_prune(d, [0.25])
+    again = lambda: P.condensa_prune(d, [0.25], outputs=res, workspace=res["workspace"])  # noqa: E731  (no launch but the library's)
+    failed = 0
+    for _ in range(40):
+        P.library().hipSetDevice(9999)
+        try:
+            again()
+        except P.CondensaError:
+            failed += 1
+    torch.cuda.synchronize()
+    res["mask"][0][0].zero_()
+    for _ in range(40):
+        again()
+    torch.cuda.synchronize()
+    check_prune_against_oracle(res, oracle.prune(m, [0.25], P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 3, f"{failed} calls failed")
