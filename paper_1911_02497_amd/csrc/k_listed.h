@@ -647,7 +647,7 @@ constexpr int kListMultiQuads = 4;
 // and 53.7; two of 295 thousand 37.4 and 36.9, of 2.3 M 42.3 and 47.5).
 constexpr u64 kListMultiFew = static_cast<u64>(1) << 19;
 __host__ __device__ inline int list_multi_quads(u64 N) { return N <= kListMultiFew ? 1 : kListMultiQuads; }
-constexpr u32 kListMultiBuf = 512;               // buffered entries of a wavefront: an equal share for each ranking; more are written at once
+constexpr u32 kListMultiBuf = 512;               // buffered entries of a wavefront: an equal share for each ranking; with more, they come from the tile
 struct ListMultiShared {
     u32 key[kListMultiBuf];
     u32 tile[256 * kListMultiQuads];             // the tile's keys, then its regions
@@ -660,15 +660,6 @@ struct ListMultiShared {
 __device__ inline u32 list_reserve(const ListArgs& w, u64 r, const ListRank& rk, u32 count, u32 kept) {
     return static_cast<u32>(atomicAdd(reinterpret_cast<unsigned long long*>(&w.cnt[r * w.max_segs + blockIdx.x % rk.n_segs]),
                                       (static_cast<unsigned long long>(kept) << 32) | count));
-}
-__device__ inline void list_multi_append(const ListArgs& w, u64 r, u32 key, u32 idx) {      // past a full buffer
-    const ListRank rk = w.rank[r];
-    const u32 at = list_reserve(w, r, rk, 1, 0);
-    if (at < rk.seg_cap) {
-        const u64 to = rk.base + static_cast<u64>(blockIdx.x % rk.n_segs) * rk.seg_cap + at;
-        w.key[to] = key;
-        w.idx[to] = idx;
-    }
 }
 // `mine`: in lane j, ranking j's buffered entries and (upper half) its keys from the estimate on.
 __device__ inline void list_multi_flush(const DataArgs& a, const ListArgs& w, const ListMultiShared& sh, u64 r0, u64 mine, u32 i0) {
@@ -847,6 +838,7 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
 #pragma unroll
     for (int q = 0; q < Q; ++q) packed[q] = region[q][0] | (region[q][1] << 8) | (region[q][2] << 16) | (region[q][3] << 24);
     const u32 i0 = static_cast<u32>(c) * kChunk + sub * kWaveElems, share = kListMultiBuf / static_cast<u32>(a.J);
+    bool full_buffer = false;
     while (inside) {
         const u32 i = static_cast<u32>(__ffs(inside)) - 1u, off = (i >> 2) * 256 + lane * 4 + (i & 3u);
         inside &= inside - 1u;
@@ -860,8 +852,27 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
         if (at < share) {
             sh.key[j * share + at] = x;
             sh.off[j * share + at] = static_cast<u16>(off);
-        } else {
-            list_multi_append(w, r0 + j, x, i0 + off);
+        }
+        full_buffer = full_buffer || at >= share;
+    }
+    u64 full_buffers = __ballot(full_buffer);
+    if (full_buffers != 0) full_buffers = __ballot(lane < a.J && sh.count[lane < a.J ? lane : 0] > share);
+    while (full_buffers != 0) {                                         // uniform.  All of that ranking's entries from the tile,
+        const u32 j = static_cast<u32>(__ffsll(static_cast<long long>(full_buffers))) - 1u;            // with one reservation
+        full_buffers &= full_buffers - 1u;
+        const ListWin win = w.win[r0 + j];
+        const ListRank rk = w.rank[r0 + j];
+        u32 pos = 0;
+        if (lane == 0) pos = list_reserve(w, r0 + j, rk, sh.count[j], 0);
+        pos = __shfl(pos, 0, 64);
+        const u64 first = rk.base + static_cast<u64>(blockIdx.x % rk.n_segs) * rk.seg_cap;
+        for (u32 off = lane; off < static_cast<u32>(kWaveElems); off += 64) {
+            const u32 x = sh.tile[off];
+            const bool me = x - win.lo <= win.hi - win.lo;
+            const u64 m = __ballot(me);
+            const u32 at = pos + lanes_below(m);
+            if (me && at < rk.seg_cap) { w.key[first + at] = x; w.idx[first + at] = i0 + off; }
+            pos += static_cast<u32>(__popcll(m));
         }
     }
     if constexpr (WIDE) {                                               // lane l takes the regions of elements 16 l .. 16 l + 15
@@ -909,7 +920,7 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
         if (lane == j) kept_of_lane = kept;
     }
     __syncthreads();
-    const u32 buffered = lane < a.J ? (sh.count[lane] < share ? sh.count[lane] : share) : 0u;
+    const u32 buffered = lane < a.J && sh.count[lane] <= share ? sh.count[lane] : 0u;
     list_multi_flush(a, w, sh, r0, (static_cast<u64>(kept_of_lane) << 32) | buffered, i0);
 }
 
