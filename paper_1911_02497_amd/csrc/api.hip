@@ -284,9 +284,17 @@ static u64 list_entries_bound(u64 N, int n_tensors, bool per_tensor, u32 max_seg
     if (shift <= 0 && N < most) most = N;
     return most + static_cast<u64>(kListRow) * max_segs * nt;
 }
-static u32 list_groups(u64 n, int J, const Config& cfg) {         // sampling workgroups of a population
+// Bins of list_fallback's histograms: all of one population's in 48 KB of LDS, all rankings' in 12 MB, and no more than a
+// workgroup searches quickly (an interval ends at the keys that are there, so ties take one level whatever the number).
+static u32 list_fallback_bins(int n_slots, int J) {
+    u32 bins = 1024;
+    while (3 * bins * static_cast<u32>(J) > kFallbackWords) bins /= 2;
+    while (bins > 256 && static_cast<u64>(bins) * static_cast<u64>(n_slots) > (1u << 20)) bins /= 2;
+    return bins;
+}
+static u32 list_groups(u64 n, int J, bool per_tensor, const Config& cfg) {         // sampling workgroups of a population
     const int64_t opt = cfg[CONDENSA_OPT_SAMPLE_LOG2];
-    if (opt <= 0) return list_sample_groups(n, J);
+    if (opt <= 0) return list_sample_groups(n, J, per_tensor);
     if ((static_cast<u64>(1) << opt) <= static_cast<u64>(kListThreads) * kListUnits * kSampleUnit) return 1;
     u32 w = 32;                                            // fewer draws would leave order statistics no room
     while (w < static_cast<u32>(kListMaxW) && static_cast<u64>(w) * kListThreads * kSampleUnit < (static_cast<u64>(1) << opt)) w *= 2;
@@ -310,7 +318,7 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
     const bool element = op == CONDENSA_OP_PRUNE || op == CONDENSA_OP_LC_STEP;
     if (element && !no_window && want_list(N, n_tensors, L.n_slots, per_tensor, J, cfg)) {
         const u64 nt = static_cast<u64>(n_tensors);
-        const u64 groups = per_tensor ? (cfg[CONDENSA_OPT_SAMPLE_LOG2] > 0 ? nt * kListMaxW : nt + (N >> (J > 1 ? 11 : 13)) + kListMaxW) : list_groups(N, J, cfg);
+        const u64 groups = per_tensor ? (cfg[CONDENSA_OPT_SAMPLE_LOG2] > 0 ? nt * kListMaxW : nt + (N >> (J > 1 ? 11 : 13)) + kListMaxW) : list_groups(N, J, per_tensor, cfg);
         L.l_max_segs = list_max_segs(N, L.n_slots, J, op == CONDENSA_OP_LC_STEP);
         const u64 entries = static_cast<u64>(J) * list_entries_bound(N, n_tensors, per_tensor, L.l_max_segs, cfg);
         L.listed = true;
@@ -323,11 +331,16 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
         L.l_hist = off;    off += align_up(static_cast<size_t>(L.n_slots) * kListBins * sizeof(u32));
         L.l_gathered = off; off += align_up(static_cast<size_t>(L.n_slots) * sizeof(u32));
         L.l_fb = off;      off += align_up(sizeof(FallbackCtl));
-        L.l_fb_hist = off; off += align_up(static_cast<size_t>(2 * 3) * kBins * sizeof(u32));
+        L.l_gmax = off;    off += align_up(2 * static_cast<size_t>(L.n_slots) * sizeof(u32));
+        L.l_masks = off;   off += align_up(3 * static_cast<size_t>(L.n_groups) * sizeof(u32));
+        L.l_meet = off;    off += align_up(kMeetWords * sizeof(u32));
         L.zero_bytes = off - L.zero_begin;
         L.chunk_map = off; off += align_up(static_cast<size_t>(L.max_chunks + 1) * sizeof(u32));
-        L.tiecnt = off;    off += align_up(static_cast<size_t>(L.max_chunks) * sizeof(u32));
-        L.l_fail = off;    off += align_up(static_cast<size_t>(L.n_slots) * sizeof(u32));
+        L.tiecnt = off;    off += align_up(static_cast<size_t>(J) * L.max_chunks * sizeof(u32));
+        L.l_special = off; off += align_up(2 * static_cast<size_t>(L.n_slots) * sizeof(u32));
+        L.l_state = off;   off += align_up(static_cast<size_t>(L.n_slots) * sizeof(ListState));
+        L.l_fb_bins = list_fallback_bins(L.n_slots, J);
+        L.l_fb_hist = off; off += align_up(3 * static_cast<size_t>(L.n_slots) * L.l_fb_bins * sizeof(u32));
         L.l_want = off;    off += align_up(static_cast<size_t>(L.n_slots) * sizeof(u32));
         L.l_gather_cap = (1u << 20) / L.n_slots > kListGather ? kListGather : ((1u << 20) / L.n_slots < kListRanked ? kListRanked : (1u << 20) / L.n_slots);
         L.l_gkey = off;    off += align_up(static_cast<size_t>(L.n_slots) * L.l_gather_cap * sizeof(u32));
@@ -706,7 +719,7 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
     *shape = ListShape{};
     for (size_t g = 0; g < n_groups; ++g) {
         const u64 n = per_tensor ? tb.td[g].n : tb.N;
-        const u32 w = list_groups(n, J, cfg);
+        const u32 w = list_groups(n, J, per_tensor, cfg);
         u32 segs = list_segments(n, list_wave_elems(tb.N, J, lc), L.l_max_segs);
         for (int j = 0; j < J; ++j) {
             ListRank& r = rk[g * J + j];
@@ -720,7 +733,7 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
         }
         if (per_tensor) group_of.insert(group_of.end(), w, static_cast<u32>(g));
         if (w > 1) shape->bounds = true;
-        if (n > list_lone(J)) shape->lone = false;
+        if (n > list_lone(J, per_tensor)) shape->lone = false;
         first += w;
     }
     shape->groups = first;
@@ -749,16 +762,26 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const L
     w.gather_cap = L.l_gather_cap;
     // workgroups that walk each list: about a thousand in all, up to 256 for one ranking (20 M weights: 64 take 4.8 us to count
     // 80 thousand keys, 256 take 7.5; 134 M weights want them all)
-    const u64 by_size = (N >> 19) < 16 ? 16 : ((N >> 19) > 256 ? 256 : N >> 19);
+    const u64 by_size = (N >> 19) < 32 ? 32 : ((N >> 19) > 256 ? 256 : N >> 19);
     const u64 share = n_slots >= 1024 ? 1 : 1024 / static_cast<u64>(n_slots);
     w.parts = static_cast<u32>(by_size < share ? by_size : share);
     w.cnt = at<u64>(ws, L.l_cnt);
     w.nnz = at<u32>(ws, L.l_nnz);
     w.key = at<u32>(ws, L.l_key);
     w.idx = at<u32>(ws, L.l_idx);
+    w.gmax = at<u32>(ws, L.l_gmax);
+    w.gmaxc = w.gmax + n_slots;
     w.fb = at<FallbackCtl>(ws, L.l_fb);
-    w.fail_list = at<u32>(ws, L.l_fail);
+    w.special = at<u32>(ws, L.l_special);
+    w.fb_above = w.special + n_slots;
+    w.state = at<ListState>(ws, L.l_state);
+    w.open_of = at<u32>(ws, L.l_masks);
+    w.tie_of = w.open_of + L.n_groups;
+    w.apply_of = w.tie_of + L.n_groups;
     w.fb_hist = at<u32>(ws, L.l_fb_hist);
+    w.fb_bins = L.l_fb_bins;
+    w.meet = at<u32>(ws, L.l_meet);
+    w.cand_shift = static_cast<int>(cfg[CONDENSA_OPT_CAND_SHIFT]);
     w.out = rq.out;
     w.nnz_out = rq.nnz_out;
     w.margin16 = static_cast<int>(cfg[CONDENSA_OPT_WINDOW_MARGIN]);
@@ -855,8 +878,8 @@ static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* w
     const int vo = rq.vec_out ? 1 : 0;
     if (shape.lone) {
         const dim3 fin(static_cast<unsigned>(n_slots));
-        if (LC && rq.pq) hipLaunchKernelGGL((k_list_finish<LC, LC>), fin, dim3(kListThreads), 0, st, a, w, results, n_groups);
-        else             hipLaunchKernelGGL((k_list_finish<LC, false>), fin, dim3(kListThreads), 0, st, a, w, results, n_groups);
+        if (LC && rq.pq) hipLaunchKernelGGL((k_list_finish<LC, VEC, LC>), fin, dim3(kListThreads), 0, st, a, w, results, n_groups, vo);
+        else             hipLaunchKernelGGL((k_list_finish<LC, VEC, false>), fin, dim3(kListThreads), 0, st, a, w, results, n_groups, vo);
         CONDENSA_LAUNCH_CHECK();
         return CONDENSA_OK;
     }
@@ -866,16 +889,16 @@ static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* w
         if (rq.pq) {
             hipLaunchKernelGGL((k_list_gather<true, true>), walk, dim3(kBlock), 0, st, a, w);
             CONDENSA_LAUNCH_CHECK();
-            hipLaunchKernelGGL((k_list_settle<true, VEC, true>), fb, dim3(kBlock), 0, st, a, w, results, n_groups, vo);
+            hipLaunchKernelGGL((k_list_settle<true, VEC, true>), fb, dim3(kSettleThreads), 0, st, a, w, results, n_groups, vo);
         } else {
             hipLaunchKernelGGL((k_list_gather<true, false>), walk, dim3(kBlock), 0, st, a, w);
             CONDENSA_LAUNCH_CHECK();
-            hipLaunchKernelGGL((k_list_settle<true, VEC, false>), fb, dim3(kBlock), 0, st, a, w, results, n_groups, vo);
+            hipLaunchKernelGGL((k_list_settle<true, VEC, false>), fb, dim3(kSettleThreads), 0, st, a, w, results, n_groups, vo);
         }
     } else {
         hipLaunchKernelGGL((k_list_gather<false, false>), walk, dim3(kBlock), 0, st, a, w);
         CONDENSA_LAUNCH_CHECK();
-        hipLaunchKernelGGL((k_list_settle<false, VEC, false>), fb, dim3(kBlock), 0, st, a, w, results, n_groups, vo);
+        hipLaunchKernelGGL((k_list_settle<false, VEC, false>), fb, dim3(kSettleThreads), 0, st, a, w, results, n_groups, vo);
     }
     CONDENSA_LAUNCH_CHECK();
     return CONDENSA_OK;

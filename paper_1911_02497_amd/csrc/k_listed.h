@@ -10,17 +10,22 @@
 //      their keys: a confidence interval for the threshold that needs no assumption about how neighbours correlate.
 //      Either way: a window [lo, hi] that holds the threshold unless the sample was unlucky, and an estimate `mid`.
 //   2. k_list_sweep / k_list_sweep_multi: ONE pass over the weights writes the outputs (final outside the windows,
-//      provisional -- kept from `mid` on -- inside), counts the keys from `mid` on and lists the keys inside each
-//      window with their indices.
+//      provisional -- kept from `mid` on -- inside), counts the keys above each window and lists the keys inside it
+//      with their indices.
 //   3. k_list_hist counts each list in kListBins bins over its window; k_list_gather finds the bin of rank k - above,
 //      settles the listed elements outside it (their outputs are rewritten where the provisional decision was wrong)
 //      and gathers those inside, a few hundred.
-//   4. k_list_settle ranks these, applies the tie rule, writes state and record and settles them too.  If some ranking
-//      failed (its rank is not inside the window, or a list overflowed) it ranks that population by radix levels over
-//      the weights instead and applies every result again.
+//   4. k_list_settle ranks these, applies the tie rule, writes state and record and settles them too.  Rankings that the
+//      lists leave open (the window missed, or the list overflowed, or thousands of ties) go on from there, all of them
+//      together in a few passes over the weights that the whole grid takes (list_fallback).
+// Weights with many equal magnitudes -- pruned before, widened from 8-bit codes -- are such rankings as a rule, so the
+// sample also says when a list could not hold its window (kListCrowded): the sweep then leaves that ranking out.
+// Microseconds at the threshold density 0.1 to 0.2, radix levels / one ranking after the other, by tickets / now: 20 M
+// weights of a VGG-19, nine tenths zeros 409 / 1052 / 176, E4M3 values 180 / 1000 / 166; layer by layer, zeros 365 / 7859 /
+// 250, E4M3 values 185 / 4453 / 240; ten densities, E4M3 values 269 / 6941 / 408; 2^18 weights, zeros 680 / 1227 / 71.
 // One workgroup draws some 25 GB/s from memory it did not write, so the lists (10^5 entries) are walked by many.  When
 // no population exceeds list_lone elements, its list is short enough for one workgroup to do 3 and 4 alone
-// (k_list_finish): three launches, and a failed ranking stays within that workgroup.
+// (k_list_finish): three launches, and a ranking that it leaves open stays with that workgroup (list_alone).
 // Results never depend on the sample.  Section 3.1 (a sparsity turned into a magnitude threshold), Section 3.3 (the
 // C step and the multiplier update), Results (up to ten samples per search share a pass).
 #pragma once
@@ -37,25 +42,27 @@ constexpr int kListMaxW = 256;                   // sampling workgroups of one p
 constexpr int kListMaxRankings = 4096;
 constexpr int kListBins = 256;                   // bins over a window
 constexpr u32 kListRanked = 2048;                // gathered entries that are held in LDS
-constexpr u32 kListGather = 1u << 18;            // gathered entries of a ranking at most; with more (ties) it fails
+constexpr u32 kListGather = 1u << 18;            // gathered entries of a ranking at most; with more (ties) it is left open
 constexpr u32 kListRow = 64;                     // segments are multiples of this many entries
 
-// Populations up to here are finished by one workgroup.  Several densities: the windows of one sampling workgroup overlap,
-// and the sweep's general path is slow.
-__host__ __device__ inline u64 list_lone(int J) { return static_cast<u64>(1) << (J > 1 ? 16 : 18); }
+// Populations up to here are sampled and finished by one workgroup.  Several densities: the windows of one sampling workgroup
+// overlap, and the sweep's general path is slow.  One ranking alone: 2^18 weights take 38-46 us that way (tied ones up to
+// 250), 39 with the lists walked by many (tied ones 65-90).  One of many rankings: the workgroups of the others fill the
+// chip (96 matrices of 2^18 and 2^20 weights 160 us, 203 with 32 sampling workgroups for each).
+inline u64 list_lone(int J, bool per_tensor) { return static_cast<u64>(1) << (J > 1 ? 16 : (per_tensor ? 18 : 17)); }
 
 // Sampling workgroups of a population of n elements: the window is narrowed as the population grows.  One workgroup leaves
 // a window of up to 8 % of it (10 sd of its rank); 32 about 2 %, 64 about 1 %, 256 about 0.4 % at the cost of one more
 // launch (4 us).  Above list_lone that launch is earned back at once: 295 thousand weights in two densities 52.3 us with one,
 // 37.7 with 32; 600 thousand 59.7 and 39.5; pruning 700 thousand in one density 37.3 and 36.5.
-__host__ __device__ inline u32 list_sample_groups(u64 n, int J) {
-    if (n <= list_lone(J)) return 1;
+inline u32 list_sample_groups(u64 n, int J, bool per_tensor) {
+    if (n <= list_lone(J, per_tensor)) return 1;
     if (n <= (static_cast<u64>(1) << 21)) return 32;
     if (n <= (static_cast<u64>(1) << 23)) return 64;
     return kListMaxW;
 }
 // Entries of a ranking's list: several times what its window is expected to hold, every element of a tiny one.
-inline u64 list_capacity(u64 n, int cand_shift) {
+__host__ __device__ inline u64 list_capacity(u64 n, int cand_shift) {
     if (cand_shift > 0) return (n >> cand_shift) < 4096 ? 4096 : n >> cand_shift;
     if (n <= 4096) return n;
     u64 c = n <= (static_cast<u64>(1) << 21) ? n / 4 : n / 16;
@@ -72,8 +79,14 @@ inline u32 list_segments(u64 n, u64 per_wave, u32 most) {
 }
 
 // Window of a ranking.  Its keys fall into bins (key - lo) >> shift; the estimate `mid` is the lower edge of bin mid_bin.
-// lo = hi = mid = 2^32 - 1: nothing is kept, nothing listed.
-struct ListWin { u32 lo, hi, mid, bins; };       // bins: shift | mid_bin << 8
+// lo = hi = mid = 2^32 - 1: nothing is kept, nothing listed.  kListCrowded: the sample holds so many keys like those at
+// the window's ends or its estimate (zeros of a pruned model, values on a grid) that the list could not hold them.  No
+// sweep is spent on such a ranking; the fallback takes it from there.
+struct ListWin { u32 lo, hi, mid, bins; };       // bins: shift | mid_bin << 8 | kListCrowded
+constexpr u32 kListCrowded = 0x80000000u;
+__host__ __device__ inline u32 win_shift(const ListWin& w) { return w.bins & 0xFFu; }
+__host__ __device__ inline u32 win_mid_bin(const ListWin& w) { return (w.bins >> 8) & 0xFFu; }
+__host__ __device__ inline bool win_crowded(const ListWin& w) { return (w.bins & kListCrowded) != 0; }
 
 // Several rankings of one population: their windows in descending order, for k_list_sweep_multi.  A key's region is the
 // number of estimates `mid` that it reaches; while no two windows overlap it tells every decision, and the key can only be
@@ -86,7 +99,8 @@ struct ListSorted {
     u32 bias[kMaxJ];       // by ranking: 127 - c, where the region must exceed c for the key to be kept
     u32 n;
     u32 disjoint;
-    u32 unused[2];
+    u32 idle;              // 1: every ranking is crowded
+    u32 unused;
 };
 
 struct ListRank {          // one ranking: filled by the host
@@ -99,12 +113,28 @@ struct ListRank {          // one ranking: filled by the host
 };
 static_assert(sizeof(ListRank) == 32, "ListRank layout");
 
-struct FallbackCtl {       // cleared at the start of every call
-    u32 failed;            // rankings that the window path did not resolve
-    u32 ticket;
-    u32 done;
-    u32 unused;
+// What the lists leave open (list_fallback).  Cleared at the start of every call.
+constexpr int kFallbackLevels = 6;
+struct FallbackCtl {
+    u32 special;           // rankings in the list of those that may need it
+    u32 ties;              // of these: ties have to be searched (those only suspected are not counted)
+    u32 apply;             // of these: outputs have to be written again (the same)
+    u32 open[kFallbackLevels + 1];   // rankings whose interval still holds several keys, by level
+    u32 unused[6];
 };
+static_assert(sizeof(FallbackCtl) == 64, "FallbackCtl layout");
+
+struct ListState {         // a ranking that the list did not resolve
+    u32 a, b;              // its threshold lies between these, ends included (a == b: it is a)
+    u32 rank;              // at this rank from the top
+    u32 n;                 // keys there
+    u32 flags;
+    u32 last;              // when found: last tie kept, as chunk * kChunk + place in the chunk
+    u32 unused[2];
+};
+constexpr u32 kStateUnsure = 1;      // the interval is the sample's alone; `rank` counts from the top of the population
+constexpr u32 kStateMaybe = 2;       // the gathered entries are many: if all are equal they are the ties, else list_rank takes them
+constexpr u32 kStateTied = 4;        // the ties are the gathered entries, and the outputs are right but for theirs
 
 struct ListArgs {
     const ListRank* rank;  // [rankings]
@@ -112,7 +142,7 @@ struct ListArgs {
     ListWin* local;        // [sampling workgroups][J]
     ListWin* win;          // [rankings]
     ListSorted* sorted;    // [populations], J > 1
-    u64* cnt;              // [rankings][max_segs] entries offered | keys at or above `mid` << 32
+    u64* cnt;              // [rankings][max_segs] entries offered | keys above the window << 32
     u32* hist;             // [rankings][kListBins]
     u32* gathered;         // [rankings] entries in the threshold's bin
     u32* bin_want;         // [rankings] rank to find among them
@@ -126,9 +156,19 @@ struct ListArgs {
     u32* key;
     u32* idx;              // element as chunk * kChunk + place in the chunk: the order of flat indices, and the
                            // tensor is one look-up away
+    u32* gmax;             // [rankings] largest gathered key, kept where they are many
+    u32* gmaxc;            // [rankings] ... and the complement of the smallest
     FallbackCtl* fb;
-    u32* fail_list;        // [rankings]
-    u32* fb_hist;          // [2][3][kBins]
+    u32* special;          // [rankings] those that list_fallback may have to take
+    ListState* state;      // [rankings]
+    u32* open_of;          // [populations] bit j: ranking j's interval still holds several keys
+    u32* tie_of;           // [populations] bit j: its ties have to be searched
+    u32* apply_of;         // [populations] bit j: its outputs have to be written again
+    u32* fb_hist;          // [rankings][3][fb_bins]: keys of an interval by bin, and the range of each bin's
+    u32* fb_above;         // [rankings] keys above an unsure interval
+    u32 fb_bins;           // a power of two
+    u32* meet;             // [kMeetWords] where list_fallback's workgroups meet
+    int cand_shift;
     const OutDesc* out;
     u64* nnz_out;
     int margin16;
@@ -150,16 +190,18 @@ __device__ inline ListWin list_window(u32 hi, u32 lo, u32 mid) {
     return x;
 }
 
-// One wavefront, J <= kMaxJ windows (in LDS), `by_rank` kMaxJ + 1 words of LDS.  Lane j places window j.
+// One wavefront, J <= kMaxJ windows (in LDS), `by_rank` kMaxJ + 1 words of LDS.  Lane j places window j; crowded ones are
+// left out.
 __device__ inline void list_sort(const ListWin* win, int J, u32* by_rank, ListSorted* out) {
     const int lane = threadIdx.x & 63;
     const ListWin mine = lane < J ? win[lane] : ListWin{};
-    const bool active = lane < J && mine.hi != 0xFFFFFFFFu;
+    const bool active = lane < J && mine.hi != 0xFFFFFFFFu && !win_crowded(mine);
     const u32 n = static_cast<u32>(__popcll(__ballot(active)));
+    const int n_crowded = __popcll(__ballot(lane < J && win_crowded(mine)));
     u32 p = 0;                                             // windows before this one: higher, or equal and earlier
     for (int i = 0; i < J; ++i) {
         const u32 h = win[i].hi;
-        if (h != 0xFFFFFFFFu && (h > mine.hi || (h == mine.hi && i < lane))) ++p;
+        if (h != 0xFFFFFFFFu && !win_crowded(win[i]) && (h > mine.hi || (h == mine.hi && i < lane))) ++p;
     }
     if (active) by_rank[p] = static_cast<u32>(lane);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
@@ -178,6 +220,7 @@ __device__ inline void list_sort(const ListWin* win, int J, u32* by_rank, ListSo
     if (lane == 0) {
         if (n == 0) { out->gap_lo[0] = 0; out->gap_len[0] = 0xFFFFFFFFu; }
         out->n = n;
+        out->idle = n_crowded == J ? 1u : 0u;
         out->disjoint = overlap == 0 ? 1u : 0u;
     }
 }
@@ -222,7 +265,7 @@ __device__ inline void list_sample(const ListArgs& w, int J, float mu, u32 W, u3
     __shared__ u8 s_tab[kBins];                  // leading digit -> 1 + histogram of level 1
     __shared__ ListWin s_win[kMaxJ];
     __shared__ u32 s_wave[kListThreads / 64];
-    __shared__ u32 s_want[3 * kMaxJ], s_bin[3 * kMaxJ], s_rem[3 * kMaxJ], s_key[3 * kMaxJ];
+    __shared__ u32 s_want[3 * kMaxJ], s_bin[3 * kMaxJ], s_rem[3 * kMaxJ], s_key[3 * kMaxJ], s_like[3 * kMaxJ];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int R = 3 * J;
     // A lone workgroup reads single float4; one of several reads 64-byte lines, four lanes each: the same traffic for four
@@ -296,6 +339,7 @@ __device__ inline void list_sample(const ListArgs& w, int J, float mu, u32 W, u3
         }
         s_want[tid] = want;
         s_key[tid] = none;
+        s_like[tid] = 0;
     }
     __syncthreads();
     {
@@ -328,14 +372,22 @@ __device__ inline void list_sample(const ListArgs& w, int J, float mu, u32 W, u3
     for (int r = wave; r < R; r += kListThreads / 64) {
         if (s_want[r] == 0) continue;
         u32 bin = 0;
-        if (wave_pick256(s_hist + (s_tab[s_bin[r]] - 1) * kBins2, s_rem[r], &bin)) {     // one lane
+        const u32* hist = s_hist + (s_tab[s_bin[r]] - 1) * kBins2;
+        if (wave_pick256(hist, s_rem[r], &bin)) {          // one lane
+            s_like[r] = hist[bin];
             const u32 key0 = (s_bin[r] << kShift0) | (bin << kShift2), low = (1u << kShift2) - 1u;
             s_key[r] = r % 3 == 0 ? key0 | low : (r % 3 == 1 ? key0 : key0 | ((low + 1u) >> 1));
         }
     }
     __syncthreads();
     if (tid < J) {
-        const ListWin x = list_window(s_key[3 * tid], s_key[3 * tid + 1], s_key[3 * tid + 2]);
+        ListWin x = list_window(s_key[3 * tid], s_key[3 * tid + 1], s_key[3 * tid + 2]);
+        u32 like = s_like[3 * tid];                        // sample keys that share 19 bits with an end or the estimate
+        like = s_like[3 * tid + 1] > like ? s_like[3 * tid + 1] : like;
+        like = s_like[3 * tid + 2] > like ? s_like[3 * tid + 2] : like;
+        u64 rk_k, rk_n;
+        rank_of(tid, &rk_k, &rk_n);
+        if (static_cast<u64>(like) * rk_n > list_capacity(rk_n, w.cand_shift) * S) x.bins |= kListCrowded;
         if (W == 1) w.win[first_ranking + tid] = x;
         else        w.local[static_cast<u64>(at_local) * J + tid] = x;
         s_win[tid] = x;
@@ -456,7 +508,7 @@ __global__ __launch_bounds__(kListThreads) void k_begin_sample(BeginSampleArgs b
 // statistic bit by bit, with all W values in its registers.
 constexpr int kBoundsThreads = 1024;
 __global__ __launch_bounds__(kBoundsThreads) void k_list_bounds(DataArgs a, ListArgs w) {
-    __shared__ u32 s_out[3 * kMaxJ];
+    __shared__ u32 s_out[3 * kMaxJ], s_crowded[kMaxJ];
     __shared__ ListWin s_win[kMaxJ];
     const u64 r0 = static_cast<u64>(blockIdx.x) * a.J;
     const ListRank rk = w.rank[r0];
@@ -467,14 +519,20 @@ __global__ __launch_bounds__(kBoundsThreads) void k_list_bounds(DataArgs a, List
     const u32 off = d >= static_cast<double>(W / 2) ? W / 2 : static_cast<u32>(ceil(d));
     for (u32 task = threadIdx.x >> 6; task < 3u * a.J; task += kBoundsThreads / 64) {
         const u32 j = task / 3, i = task % 3;    // i: upper bound, lower bound, estimate
-        u32 v[kPer];
+        u32 v[kPer], crowded = 0;
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
             v[q] = 0xFFFFFFFFu;                  // past the end: above every key (and every bound looked for)
             if (64 * q + lane < W) {
                 const ListWin x = w.local[static_cast<u64>(rk.group0 + 64 * q + lane) * a.J + j];
                 v[q] = i == 0 ? x.hi : (i == 1 ? x.lo : x.mid);
+                crowded += win_crowded(x) ? 1u : 0u;
             }
+        }
+        if (i == 2) {                            // most of the workgroups say so
+#pragma unroll
+            for (int d2 = 32; d2 >= 1; d2 >>= 1) crowded += __shfl_xor(crowded, d2, 64);
+            if (lane == 0) s_crowded[j] = 2 * crowded > W ? 1u : 0u;
         }
         const u32 pick = i == 0 ? (W / 2 + off < W ? W / 2 + off : W - 1) : (i == 1 ? (W / 2 - 1 >= off ? W / 2 - 1 - off : 0) : W / 2);
         u32 x = 0;                               // the largest x with at most `pick` values below it
@@ -489,7 +547,8 @@ __global__ __launch_bounds__(kBoundsThreads) void k_list_bounds(DataArgs a, List
     }
     __syncthreads();
     if (threadIdx.x < static_cast<u32>(a.J)) {
-        const ListWin x = list_window(s_out[3 * threadIdx.x], s_out[3 * threadIdx.x + 1], s_out[3 * threadIdx.x + 2]);
+        ListWin x = list_window(s_out[3 * threadIdx.x], s_out[3 * threadIdx.x + 1], s_out[3 * threadIdx.x + 2]);
+        if (s_crowded[threadIdx.x]) x.bins |= kListCrowded;
         s_win[threadIdx.x] = x;
         w.win[r0 + threadIdx.x] = x;
     }
@@ -504,8 +563,8 @@ __device__ inline u32 lanes_below(u64 m) {       // set bits of m below this lan
 
 // ---- the one pass over the weights: one density ------------------------------------------------------------
 //
-// As k_window_fused, with one list per ranking and one counter update per wavefront (entries and keys above `mid` in
-// the halves of a word).  One float4 per lane and array for the L-C forms, four for pruning (measured there).
+// As k_window_fused, with one list per ranking and one counter update per wavefront (entries and keys above the window in
+// the halves of a word; they stay right when the list is full).  One float4 per lane and array for the L-C forms, four for pruning (measured there).
 template <bool LC, bool VEC, int QUADS, bool PQ>
 __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
     constexpr int kWaveElems = 256 * QUADS;
@@ -521,6 +580,7 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
     if (base >= n) return;
     const u32 r = a.per_tensor ? static_cast<u32>(t) : 0u;
     const ListWin win = w.win[r];
+    if (win_crowded(win)) return;                                       // uniform
     const u32 lo = win.lo, span = win.hi - win.lo, mid = win.mid;
     OutDesc o{};
     if (w.write) o = w.out[t];
@@ -541,7 +601,7 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
     }
     u32 key[QUADS][4];
     u64 in_window[QUADS][4];                                            // lanes whose element is inside the window
-    u32 total = 0, kept = 0, nz = 0;                                    // sums over the wavefront
+    u32 total = 0, above = 0, nz = 0;                                   // sums over the wavefront
 #pragma unroll
     for (int q = 0; q < QUADS; ++q) {
         const u64 e0 = base + static_cast<u64>(q) * 256 + lane * 4;
@@ -563,8 +623,8 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
             key[q][k] = x;
             const bool in = full || e0 + k < n;
             const bool keep = x >= mid;                                 // final outside the window, provisional inside
-            kept += static_cast<u32>(__popcll(__ballot(keep && in)));
             in_window[q][k] = __ballot(in && x - lo <= span);
+            above += static_cast<u32>(__popcll(__ballot(keep && in) & ~in_window[q][k]));       // the estimate lies in the window
             total += static_cast<u32>(__popcll(in_window[q][k]));
             m[k] = keep ? 1 : 0;
             th[k] = keep ? v : 0.0f;
@@ -609,11 +669,11 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
     const ListRank rk = w.rank[r];
     const u32 seg = blockIdx.x % rk.n_segs;
     if (PQ && lane == 1 && nz) atomicAdd(&w.nnz[seg], nz);
-    if ((total | kept) == 0) return;
+    if ((total | above) == 0) return;
     u64 b = 0;
     if (lane == 0)
         b = atomicAdd(reinterpret_cast<unsigned long long*>(&w.cnt[static_cast<u64>(r) * w.max_segs + seg]),
-                      (static_cast<unsigned long long>(kept) << 32) | total);
+                      (static_cast<unsigned long long>(above) << 32) | total);
     if (total == 0) return;
     u32 pos = __shfl(static_cast<u32>(b), 0, 64);
     const u64 first = rk.base + static_cast<u64>(seg) * rk.seg_cap;
@@ -651,17 +711,17 @@ constexpr u32 kListMultiBuf = 512;               // buffered entries of a wavefr
 struct ListMultiShared {
     u32 key[kListMultiBuf];
     u32 tile[256 * kListMultiQuads];             // the tile's keys, then its regions
-    u32 count[kMaxJ];
+    u32 count[kMaxJ];                            // entries | those from the estimate on << 16
     u32 gap[2 * (kMaxJ + 1)];
     u32 ranking[kMaxJ];
     u16 off[kListMultiBuf];
 };
 
-__device__ inline u32 list_reserve(const ListArgs& w, u64 r, const ListRank& rk, u32 count, u32 kept) {
+__device__ inline u32 list_reserve(const ListArgs& w, u64 r, const ListRank& rk, u32 count, u32 above) {
     return static_cast<u32>(atomicAdd(reinterpret_cast<unsigned long long*>(&w.cnt[r * w.max_segs + blockIdx.x % rk.n_segs]),
-                                      (static_cast<unsigned long long>(kept) << 32) | count));
+                                      (static_cast<unsigned long long>(above) << 32) | count));
 }
-// `mine`: in lane j, ranking j's buffered entries and (upper half) its keys from the estimate on.
+// `mine`: in lane j, ranking j's buffered entries and (upper half) its keys above the window.
 __device__ inline void list_multi_flush(const DataArgs& a, const ListArgs& w, const ListMultiShared& sh, u64 r0, u64 mine, u32 i0) {
     const int lane = threadIdx.x;
     ListRank rk{};
@@ -716,13 +776,14 @@ __device__ inline void list_multi_general(const DataArgs& a, const ListArgs& w, 
     }
     const u32 i0 = static_cast<u32>(c) * kChunk + sub * kWaveElems;
     const u32 share = kListMultiBuf / static_cast<u32>(a.J);
-    u64 mine = 0;                                                       // lane j: ranking j's buffered entries and kept keys
+    u64 mine = 0;                                                       // lane j: ranking j's buffered entries and keys above
     for (int j = 0; j < a.J; ++j) {
         const ListWin win = w.win[r0 + j];
+        if (win_crowded(win)) continue;                                 // uniform
         const u32 lo = win.lo, span = win.hi - win.lo, mid = win.mid;
         OutDesc o{};
         if (w.write) o = w.out[static_cast<u64>(j) * a.n_tensors + t];
-        u32 count = 0, kept = 0;
+        u32 count = 0, above = 0;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const u64 e0 = base + static_cast<u64>(q) * 256 + lane * 4;
@@ -733,10 +794,10 @@ __device__ inline void list_multi_general(const DataArgs& a, const ListArgs& w, 
                 const u32 x = mag_key(v[q][k]);
                 const bool there = full || ((in >> (4 * q + k)) & 1u);
                 const bool keep = x >= mid;
-                kept += static_cast<u32>(__popcll(__ballot(keep && there)));
                 m[k] = keep ? 1 : 0;
                 th[k] = keep ? v[q][k] : 0.0f;
                 const u64 hit = __ballot(there && x - lo <= span);
+                above += static_cast<u32>(__popcll(__ballot(keep && there) & ~hit));
                 if (hit != 0) {                                         // uniform
                     const u32 n_hit = static_cast<u32>(__popcll(hit));
                     const bool me = (hit >> lane) & 1u;
@@ -775,7 +836,7 @@ __device__ inline void list_multi_general(const DataArgs& a, const ListArgs& w, 
                 }
             }
         }
-        if (lane == j) mine = (static_cast<u64>(kept) << 32) | count;
+        if (lane == j) mine = (static_cast<u64>(above) << 32) | count;
     }
     list_multi_flush(a, w, sh, r0, mine, i0);
 }
@@ -797,6 +858,7 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
     const u64 r0 = a.per_tensor ? static_cast<u64>(t) * a.J : 0;
     const bool full = VEC && base + kWaveElems <= td.n;                 // uniform over the wavefront
     const ListSorted& srt = w.sorted[a.per_tensor ? t : 0];
+    if (srt.idle) return;                                               // uniform
     if (!full || !srt.disjoint) {
         list_multi_general<VEC, Q>(a, w, sh, td, t, c, sub, base, full);
         return;
@@ -847,8 +909,9 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
         for (int q = 1; q < Q; ++q) word = (i >> 2) == static_cast<u32>(q) ? packed[q] : word;
         const u32 r = (word >> (8 * (i & 3u))) & 0xFFu, x = sh.tile[off];
         // below the gap of its region: the window of the highest estimate it reaches; else the next one up
-        const u32 j = sh.ranking[x < sh.gap[2 * r] ? n - r : n - r - 1u];
-        const u32 at = atomicAdd(&sh.count[j], 1u);
+        const bool reaches = x < sh.gap[2 * r];
+        const u32 j = sh.ranking[reaches ? n - r : n - r - 1u];
+        const u32 at = atomicAdd(&sh.count[j], reaches ? 0x10001u : 1u) & 0xFFFFu;
         if (at < share) {
             sh.key[j * share + at] = x;
             sh.off[j * share + at] = static_cast<u16>(off);
@@ -856,14 +919,14 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
         full_buffer = full_buffer || at >= share;
     }
     u64 full_buffers = __ballot(full_buffer);
-    if (full_buffers != 0) full_buffers = __ballot(lane < a.J && sh.count[lane < a.J ? lane : 0] > share);
-    while (full_buffers != 0) {                                         // uniform.  All of that ranking's entries from the tile,
-        const u32 j = static_cast<u32>(__ffsll(static_cast<long long>(full_buffers))) - 1u;            // with one reservation
+    if (full_buffers != 0) full_buffers = __ballot(lane < a.J && (sh.count[lane < a.J ? lane : 0] & 0xFFFFu) > share);
+    while (full_buffers != 0) {                                         // uniform.  All of that ranking's entries from the tile
+        const u32 j = static_cast<u32>(__ffsll(static_cast<long long>(full_buffers))) - 1u;
         full_buffers &= full_buffers - 1u;
         const ListWin win = w.win[r0 + j];
         const ListRank rk = w.rank[r0 + j];
         u32 pos = 0;
-        if (lane == 0) pos = list_reserve(w, r0 + j, rk, sh.count[j], 0);
+        if (lane == 0) pos = list_reserve(w, r0 + j, rk, sh.count[j] & 0xFFFFu, 0);
         pos = __shfl(pos, 0, 64);
         const u64 first = rk.base + static_cast<u64>(blockIdx.x % rk.n_segs) * rk.seg_cap;
         for (u32 off = lane; off < static_cast<u32>(kWaveElems); off += 64) {
@@ -920,8 +983,8 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
         if (lane == j) kept_of_lane = kept;
     }
     __syncthreads();
-    const u32 buffered = lane < a.J && sh.count[lane] <= share ? sh.count[lane] : 0u;
-    list_multi_flush(a, w, sh, r0, (static_cast<u64>(kept_of_lane) << 32) | buffered, i0);
+    const u32 offered = lane < a.J ? sh.count[lane] & 0xFFFFu : 0u, reached = lane < a.J ? sh.count[lane] >> 16 : 0u;
+    list_multi_flush(a, w, sh, r0, (static_cast<u64>(kept_of_lane - reached) << 32) | (offered <= share ? offered : 0u), i0);
 }
 
 // ---- the threshold among the listed keys ---------------------------------------------------------------
@@ -966,22 +1029,41 @@ __device__ inline void list_walk(const ListArgs& w, u32 s, const ListRank& rk, u
     }
 }
 
+// hist[bin] += 1 for the lanes that are `there`; all lanes call it.  Lanes that meet on a counter take turns, and listed keys
+// often are equal (weights on a grid), so the two commonest-looking bins are added up across the wavefront first.
+__device__ inline void wave_count(u32* hist, bool there, u32 bin) {
+    u64 rest = __ballot(there);
+#pragma unroll
+    for (int round = 0; round < 2; ++round) {
+        if (rest == 0) return;                             // uniform
+        const int leader = __ffsll(static_cast<long long>(rest)) - 1;
+        const u32 b = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(bin), leader));
+        const u64 same = __ballot(there && bin == b);
+        if (static_cast<int>(threadIdx.x & 63u) == leader) atomicAdd(&hist[b], static_cast<u32>(__popcll(same)));
+        there = there && bin != b;
+        rest &= ~same;
+    }
+    if (there) atomicAdd(&hist[bin], 1u);
+}
+
 // Counts of a ranking's listed keys per bin of its window; `parts` workgroups per ranking.
 __global__ __launch_bounds__(kBlock) void k_list_hist(DataArgs a, ListArgs w) {
-    __shared__ u32 s_hist[kListBins];
+    constexpr int kCopies = 8;                             // by lane: listed keys often are equal (weights on a grid), and lanes
+    __shared__ __align__(16) u32 s_hist[kListBins * kCopies];            // that meet on a counter take turns
     const u32 s = blockIdx.x / w.parts, part = blockIdx.x % w.parts;
     const ListRank rk = w.rank[s];
     const ListWin win = w.win[s];
     const u32 wave = threadIdx.x >> 6, first = part * (kBlock / 64) + wave, stride = w.parts * (kBlock / 64);
-    if (part * (kBlock / 64) >= rk.n_segs) return;         // uniform: nothing for this workgroup
-    s_hist[threadIdx.x] = 0;                               // kListBins == kBlock
+    if (part * (kBlock / 64) >= rk.n_segs || win_crowded(win)) return;   // uniform: nothing for this workgroup
+    for (u32 i = threadIdx.x; i < static_cast<u32>(kListBins * kCopies) / 4; i += kBlock) reinterpret_cast<uint4*>(s_hist)[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    const u32 lo = win.lo, shift = win.bins & 0xFFu;
+    const u32 lo = win.lo, shift = win_shift(win), copy = threadIdx.x & (kCopies - 1);
     list_walk(w, s, rk, first, stride, [&](bool there, u32 key, u64) {
-        if (there) atomicAdd(&s_hist[(key - lo) >> shift], 1u);
+        if (there) atomicAdd(&s_hist[((key - lo) >> shift) * kCopies + copy], 1u);
     });
     __syncthreads();
-    const u32 v = s_hist[threadIdx.x];
+    const uint4 v0 = reinterpret_cast<const uint4*>(s_hist)[2 * threadIdx.x], v1 = reinterpret_cast<const uint4*>(s_hist)[2 * threadIdx.x + 1];
+    const u32 v = v0.x + v0.y + v0.z + v0.w + v1.x + v1.y + v1.z + v1.w;          // kListBins == kBlock
     if (v) atomicAdd(&w.hist[static_cast<u64>(s) * kListBins + threadIdx.x], v);
 }
 
@@ -1074,6 +1156,55 @@ __device__ inline void list_fix_queue(const DataArgs& a, const ListArgs& w, u32 
     }
 }
 
+// What one phase of list_fallback hands to the next is written and read with device-scope operations.
+__device__ inline u32 ld_dev(const u32* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void st_dev(u32* p, u32 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline u32 add_dev(u32* p, u32 v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void max_dev(u32* p, u32 v) { __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline u64 ld_dev64(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void st_dev64(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void or_dev(u32* p, u32 v) { __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void st_state(ListState* to, u32 a, u32 b, u32 rank, u32 n, u32 flags) {
+    st_dev(&to->a, a); st_dev(&to->b, b); st_dev(&to->rank, rank); st_dev(&to->n, n); st_dev(&to->flags, flags);
+}
+__device__ inline ListState ld_state(const ListState* from) {
+    ListState x{};
+    x.a = ld_dev(&from->a); x.b = ld_dev(&from->b); x.rank = ld_dev(&from->rank); x.n = ld_dev(&from->n); x.flags = ld_dev(&from->flags);
+    return x;
+}
+
+// Where a threshold is that is not in its list, or whose list is incomplete: `inside` keys in the window, `above` above it, all
+// counted by the sweep.
+__device__ inline ListState list_window_state(const ListWin& win, u32 n, u32 k, u32 above, u32 inside) {
+    ListState x{};
+    if (above >= k)               { x.a = win.hi + 1u; x.b = 0x7FFFFFFFu; x.rank = k; x.n = above; }
+    else if (k - above <= inside) { x.a = win.lo; x.b = win.hi; x.rank = k - above; x.n = inside; }
+    else                          { x.a = 0; x.b = win.lo - 1u; x.rank = k - above - inside; x.n = n - above - inside; }
+    return x;
+}
+// Ranking s goes to list_fallback: `rank` from the top between a and b, where there are n keys.  All threads of one
+// workgroup; its histogram is cleared here.
+__device__ inline void list_leave(const DataArgs& a, const ListArgs& w, u32 s, u32 lo, u32 hi, u32 rank, u32 n, u32 flags) {
+    for (u32 i = threadIdx.x; i < 3 * w.fb_bins; i += kBlock) st_dev(w.fb_hist + static_cast<u64>(s) * 3 * w.fb_bins + i, 0u);
+    if (threadIdx.x != 0) return;
+    const u32 g = s / a.J, j = s - g * a.J;
+    st_dev(w.fb_above + s, 0u);
+    st_state(w.state + s, lo, hi, rank, n, flags);
+    st_dev(w.special + add_dev(&w.fb->special, 1u), s);
+    if (flags & kStateMaybe) {
+        if (rank < n) or_dev(w.tie_of + g, 1u << j);
+        return;
+    }
+    add_dev(&w.fb->apply, 1u);
+    or_dev(w.apply_of + g, 1u << j);
+    if (lo < hi || (flags & kStateUnsure)) {
+        or_dev(w.open_of + g, 1u << j);
+        add_dev(&w.fb->open[0], 1u);
+    } else if (rank < n) {
+        or_dev(w.tie_of + g, 1u << j);
+        add_dev(&w.fb->ties, 1u);
+    }
+}
 // Every workgroup finds the bin of rank k - above from the counts.  Elements in the bins beside it are settled here:
 // wrong decisions are queued in LDS, so that their chains of dependent loads run side by side.
 template <bool LC, bool PQ>
@@ -1084,7 +1215,7 @@ __global__ __launch_bounds__(kBlock) void k_list_gather(DataArgs a, ListArgs w) 
     __shared__ u32 s_queue[kQueue];                        // wrong decisions: entry, top bit = the right one
     __shared__ u32 s_fkey[kFound], s_fidx[kFound];         // entries in the bin (one reservation per workgroup: updates of
                                                            // one counter that return a value take turns)
-    __shared__ u32 s_over, s_gtmid, s_bin, s_want, s_in, s_n, s_f, s_base;
+    __shared__ u32 s_over, s_bin, s_want, s_in, s_n, s_f, s_base, s_max, s_maxc;
     const u32 s = blockIdx.x / w.parts, part = blockIdx.x % w.parts, tid = threadIdx.x, lane = tid & 63u;
     const ListRank rk = w.rank[s];
     const ListWin win = w.win[s];
@@ -1096,11 +1227,13 @@ __global__ __launch_bounds__(kBlock) void k_list_gather(DataArgs a, ListArgs w) 
         block_excl_scan_u64(v, s_wave, &total);
         if (tid == 0) *w.nnz_out = total;
     }
-    if (slot.state != kSelecting) {                        // k == 0: nothing listed
-        if (part == 0 && tid == 0) w.bin_want[s] = 0;
+    if (slot.state != kSelecting || win_crowded(win)) {    // uniform; k == 0: nothing listed
+        if (part != 0) return;
+        if (tid == 0) w.bin_want[s] = 0;
+        if (slot.state == kSelecting) list_leave(a, w, s, win.lo, win.hi, static_cast<u32>(slot.k), 0, kStateUnsure);
         return;
     }
-    if (tid == 0) { s_over = 0; s_n = 0; s_f = 0; s_in = 0; s_want = 0; }
+    if (tid == 0) { s_over = 0; s_n = 0; s_f = 0; s_in = 0; s_want = 0; s_max = 0; s_maxc = 0; }
     __syncthreads();
     u64 cnt = 0;
     for (u32 seg = tid; seg < rk.n_segs; seg += kBlock) {
@@ -1113,46 +1246,72 @@ __global__ __launch_bounds__(kBlock) void k_list_gather(DataArgs a, ListArgs w) 
     u64 sums, listed;
     block_excl_scan_u64(cnt, s_wave, &sums);
     const u64 higher = block_excl_scan_u64(h, s_wave, &listed);
-    const u32 shift = win.bins & 0xFFu, mid_bin = win.bins >> 8;
-    if (bin_of_tid == mid_bin) s_gtmid = static_cast<u32>(higher) + h;
-    __syncthreads();
-    const u64 above = (sums >> 32) - s_gtmid;              // keys above the window
+    const u32 shift = win_shift(win), mid_bin = win_mid_bin(win);
+    const u32 k = static_cast<u32>(slot.k), above = static_cast<u32>(sums >> 32);
     const u64 want = slot.k - above;
-    if (above < slot.k && higher < want && want <= higher + h) { s_bin = bin_of_tid; s_want = static_cast<u32>(want - higher); s_in = h; }
+    if (above < k && higher < want && want <= higher + h) { s_bin = bin_of_tid; s_want = static_cast<u32>(want - higher); s_in = h; }
     __syncthreads();
-    const bool ok = s_over == 0 && s_want != 0 && s_in <= w.gather_cap;
-    if (part == 0 && tid == 0) {
-        w.bin_want[s] = ok ? s_want : 0;
-        if (!ok) w.fail_list[atomicAdd(&w.fb->failed, 1u)] = s;
+    const u32 n_in = s_in, lo = win.lo, bin = s_bin;
+    const bool found_bin = s_over == 0 && s_want != 0, ok = found_bin && n_in <= w.gather_cap;
+    if (part == 0) {
+        if (tid == 0) w.bin_want[s] = ok ? s_want : 0;
+        const u32 from = lo + (bin << shift), to = from + ((1u << shift) - 1u);
+        if (!found_bin) {
+            const ListState x = list_window_state(win, static_cast<u32>(slot.n), k, above, static_cast<u32>(sums));
+            list_leave(a, w, s, x.a, x.b, x.rank, x.n, 0);
+        } else if (!ok || n_in > kListRanked) {
+            list_leave(a, w, s, from, to < win.hi ? to : win.hi, s_want, n_in, ok ? kStateMaybe : 0);
+        }
     }
     if (!ok) return;                                       // uniform over all workgroups of the ranking
-    const u32 lo = win.lo, bin = s_bin;
     const u32 g = s / a.J, j = s - g * a.J;
     int nz = 0;
+    u32 most = 0, mostc = 0;
+    const bool many = n_in > kFound;                       // uniform
     u32* gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
     u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
-    list_walk(w, s, rk, part * (kBlock / 64) + (tid >> 6), w.parts * (kBlock / 64), [&](bool there, u32 key, u64 at) {
+    const u32 first_seg = part * (kBlock / 64) + (tid >> 6), stride = w.parts * (kBlock / 64);
+    u32 next = 0;
+    if (many) {                                            // one reservation for all that this wavefront will find
+        list_walk(w, s, rk, first_seg, stride, [&](bool there, u32 key, u64) {
+            next += static_cast<u32>(__popcll(__ballot(there && ((key - lo) >> shift) == bin)));
+        });
+        if (lane == 0 && next) next = atomicAdd(&w.gathered[s], next);
+        next = __shfl(next, 0, 64);
+    }
+    list_walk(w, s, rk, first_seg, stride, [&](bool there, u32 key, u64 at) {
         const u32 b = (key - lo) >> shift;
         const bool found = there && b == bin, wrong = w.write && there && b != bin && (b > bin) != (b >= mid_bin);
-        const u32 f = wave_push(&s_f, found);
-        if (found) {
-            if (f < kFound) {
-                s_fkey[f] = key;
-                s_fidx[f] = static_cast<u32>(at - rk.base);
-            } else {                                       // a full buffer: straight to the list
-                const u32 to = atomicAdd(&w.gathered[s], 1u);
-                if (to < w.gather_cap) { gkey[to] = key; gidx[to] = w.idx[at]; }
-            }
-        }
         const u32 q = wave_push(&s_n, wrong);
         if (wrong) {
             if (q < kQueue) s_queue[q] = static_cast<u32>(at - rk.base) | (b > bin ? 0x80000000u : 0u);
             else            list_fix_one<LC, PQ>(a, w, j, w.idx[at], b > bin, &nz);
         }
+        if (!many) {
+            const u32 f = wave_push(&s_f, found);          // fewer than kFound
+            if (found) {
+                s_fkey[f] = key;
+                s_fidx[f] = static_cast<u32>(at - rk.base);
+            }
+        } else {                                           // places of this wavefront
+            const u64 m = __ballot(found);
+            const u32 to = next + lanes_below(m);
+            if (found) {
+                most = key > most ? key : most;
+                mostc = ~key > mostc ? ~key : mostc;
+                if (to < w.gather_cap) { gkey[to] = key; gidx[to] = w.idx[at]; }
+            }
+            next += static_cast<u32>(__popcll(m));
+        }
     });
+    if (many) {                                            // are they all equal?
+        atomicMax(&s_max, most);
+        atomicMax(&s_maxc, mostc);
+    }
     __syncthreads();
-    const u32 n_f = s_f < kFound ? s_f : kFound, n_q = s_n < kQueue ? s_n : kQueue;
+    const u32 n_f = s_f, n_q = s_n < kQueue ? s_n : kQueue;
     if (tid == 0 && n_f) s_base = atomicAdd(&w.gathered[s], n_f);
+    if (tid == 0 && s_maxc) { atomicMax(&w.gmax[s], s_max); atomicMax(&w.gmaxc[s], s_maxc); }
     list_fix_queue<LC, PQ, kBlock>(a, w, j, w.idx + rk.base, s_queue, n_q, &nz);
     __syncthreads();
     for (u32 f = tid; f < n_f; f += kBlock) {
@@ -1252,7 +1411,7 @@ __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShare
         auto key_of = [&](u32 i) { return in_lds ? sh.key[i] : gkey[i]; };
         auto idx_of = [&](u32 i) { return in_lds ? sh.idx[i] : gidx[i]; };
         const ListWin win = w.win[s];
-        const u32 bits = win.bins & 0xFFu;                 // low bits of key - lo that the window's bins leave open
+        const u32 bits = win_shift(win);                   // low bits of key - lo that the window's bins leave open
         const u32 sub = bits > 8 ? bits - 8 : 0;
         const u32 mask = (1u << (bits - sub)) - 1u;        // at most eight bits
         if (tid < static_cast<u32>(kListBins)) sh.hist[tid] = 0;
@@ -1292,11 +1451,11 @@ __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShare
                 for (int shift = 24; shift >= 0; shift -= 8) {
                     if (tid < static_cast<u32>(kListBins)) sh.hist[tid] = 0;
                     __syncthreads();
-                    for (u32 i = tid; i < n; i += THREADS) {
-                        const u32 key = key_of(i);
-                        if (part == 1 && key != prefix[0]) continue;
-                        const u32 v = part == 0 ? key : idx_of(i);
-                        if (shift == 24 || (v >> (shift + 8)) == (prefix[part] >> (shift + 8))) atomicAdd(&sh.hist[(v >> shift) & 255u], 1u);
+                    for (u32 i0 = 0; i0 < n; i0 += THREADS) {
+                        const u32 i = i0 + tid, key = i < n ? key_of(i) : 0u;
+                        const bool there = i < n && (part == 0 || key == prefix[0]);
+                        const u32 v = there && part == 1 ? idx_of(i) : key;
+                        wave_count(sh.hist, there && (shift == 24 || (v >> (shift + 8)) == (prefix[part] >> (shift + 8))), (v >> shift) & 255u);
                     }
                     __syncthreads();
                     list_pick(sh, part == 0, rem, &b, &rem, &n_eq);
@@ -1350,17 +1509,343 @@ __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShare
     __syncthreads();                                       // the shared words are free for the next ranking
 }
 
+// ---- what the lists leave open ----------------------------------------------------------------------------------
+//
+// Rankings whose threshold is not in their list (the window missed it, the list is full), whose window is crowded, or whose
+// threshold has more ties than one workgroup should rank: counts of the keys in an interval (one read of the population), the
+// bin that becomes the next interval until it is a single key, ties per chunk (another read), the tie rule, and the outputs (a
+// third read, or the ties alone where everything else is right).
+
+// A chunk's elements, kPer per thread, and their keys: 0xFFFFFFFF past the tensor's end (above every interval and equal to no
+// threshold).
+template <bool LC, bool VEC, int THREADS>
+struct ChunkKeys {
+    static constexpr int kQuads = kChunk / (4 * THREADS), kPer = 4 * kQuads;
+    float v[kQuads][4], l[LC ? kQuads : 1][4];
+    u32 there;
+    float mu;
+    // The loads.  Those of a whole chunk stay in flight (their number is the same for every lane, so whoever needs older ones
+    // need not wait for these); a ragged one waits for its own.
+    __device__ inline void fetch(const DataArgs& a, u64 c) {
+        const TensorDesc& td = a.td[a.chunk_map[c]];
+        const u64 base = (c - td.chunk_start) * kChunk, n = td.n;
+        mu = a.mu;
+        if (VEC && base + kChunk <= n) {                   // uniform
+            there = 0xFFFFFFFFu;
+#pragma unroll
+            for (int q = 0; q < kQuads; ++q) {
+                const u64 e0 = base + static_cast<u64>(q) * (4 * THREADS) + threadIdx.x * 4;
+                const float4 x = *reinterpret_cast<const float4*>(td.w + e0);
+                v[q][0] = x.x; v[q][1] = x.y; v[q][2] = x.z; v[q][3] = x.w;
+                if (LC) {
+                    const float4 y = *reinterpret_cast<const float4*>(td.lam + e0);
+                    l[q][0] = y.x; l[q][1] = y.y; l[q][2] = y.z; l[q][3] = y.w;
+                }
+            }
+            return;
+        }
+        there = 0;
+#pragma unroll
+        for (int q = 0; q < kQuads; ++q) {
+            const u64 e0 = base + static_cast<u64>(q) * (4 * THREADS) + threadIdx.x * 4;
+            if (e0 < n) {
+                load4<VEC>(td.w, e0, n, v[q]);
+                if (LC) load4<VEC>(td.lam, e0, n, l[q]);
+                there |= ((1u << (n - e0 < 4 ? static_cast<u32>(n - e0) : 4u)) - 1u) << (4 * q);
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+    }
+    __device__ inline u32 key(int e) const {
+        const float x = LC ? lc_shift(v[e / 4][e % 4], l[LC ? e / 4 : 0][e % 4], mu) : v[e / 4][e % 4];
+        return (there >> e) & 1u ? mag_key(x) : 0xFFFFFFFFu;
+    }
+    // words: B counts, B largest distances from lo (plus one), B smallest ones (their complements)
+    __device__ inline void count(u32* words, u32 B, u32 lo, u32 span, u32 shift) const {
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+            const u32 d = key(e) - lo, b = d >> shift;
+            const bool in = d <= span;
+            const u64 all = __ballot(in);
+            if (all == 0) continue;                        // uniform
+            bool mine = in;
+            if (__popcll(all) > 12) {                      // lanes that meet on a counter take turns: ties are added up first
+                const int leader = __ffsll(static_cast<long long>(all)) - 1;
+                const u32 d0 = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(d), leader));
+                const u64 same = __ballot(in && d == d0);
+                if (static_cast<int>(threadIdx.x & 63u) == leader) atomicAdd(&words[b], static_cast<u32>(__popcll(same)) - 1u);
+                mine = in && (d != d0 || static_cast<int>(threadIdx.x & 63u) == leader);
+            }
+            if (mine) {
+                atomicAdd(&words[b], 1u);
+                if (words[B + b] < d + 1u) atomicMax(&words[B + b], d + 1u);           // seldom: a plain look first
+                if (words[2 * B + b] < ~d) atomicMax(&words[2 * B + b], ~d);
+            }
+        }
+    }
+    // The same for several intervals at once, a[j] .. a[j] + span[j]: tab[leading 11 bits of a key] are those (a bit each) that
+    // hold keys of that kind, so that a key costs a look-up and its own intervals.
+    __device__ inline void count_many(u32* words, u32 B, const u16* tab, const u32* a, const u32* span, const u32* shift) const {
+        const u32 lane = threadIdx.x & 63u;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+            const u32 x = key(e);
+            u32 of = x <= 0x7FFFFFFFu ? tab[x >> 20] : 0u;
+            const u64 all = __ballot(of != 0);
+            if (all == 0) continue;                        // uniform
+            const int leader = __ffsll(static_cast<long long>(all)) - 1;
+            const u32 x0 = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(x), leader));
+            const u64 same = __ballot(x == x0);
+            u32 n = 1;
+            if (__popcll(same) > 12) {                     // ties are added up first
+                n = static_cast<int>(lane) == leader ? static_cast<u32>(__popcll(same)) : 1u;
+                if (x == x0 && static_cast<int>(lane) != leader) of = 0;
+            }
+            while (of) {
+                const u32 j = static_cast<u32>(__ffs(of)) - 1u, d = x - a[j];
+                of &= of - 1u;
+                if (d > span[j]) continue;
+                u32* to = words + j * 3 * B + (d >> (shift[j] & 0xFFu));
+                atomicAdd(to, n);
+                if (to[B] < d + 1u) atomicMax(to + B, d + 1u);
+                if (to[2 * B] < ~d) atomicMax(to + 2 * B, ~d);
+            }
+        }
+    }
+    // The outputs of chunk c for the rankings in `rankings` (L-C step: the one), whose thresholds are T and ends of kept ties `end`;
+    // adds this thread's non-zero codes to *nz.
+    template <bool PQ>
+    __device__ inline void apply(const DataArgs& a, const OutDesc* out, u64 c, u32 rankings, const u32* T, const u64* end, bool vec, u32* nz) const {
+        const u32 t = a.chunk_map[c];
+        const TensorDesc& td = a.td[t];
+        const u64 base = (c - td.chunk_start) * kChunk, n = td.n, idx0 = a.per_tensor ? 0 : td.flat_start;
+        vec = vec && VEC;
+        for (u32 js = rankings; js != 0; js &= js - 1u) {  // uniform
+            const u32 j = static_cast<u32>(__ffs(js)) - 1u, Tj = T[j];
+            const u64 endj = end[j];
+            const OutDesc o = out[static_cast<u64>(j) * a.n_tensors + t];
+#pragma unroll
+            for (int q = 0; q < kQuads; ++q) {
+                const u64 e0 = base + static_cast<u64>(q) * (4 * THREADS) + threadIdx.x * 4;
+                if (e0 >= n) continue;
+                float th[4], ln[4], gr[4];
+                u8 m[4];
+                u16 h[4] = {0, 0, 0, 0};
+                if constexpr (LC) {
+                    lc_update4<PQ>(v[q], l[q], a.mu, Tj, idx0 + e0, endj, th, ln, gr, m, h);
+                    if (PQ)
+                        for (int k = 0; k < 4; ++k) *nz += (e0 + k < n) && (h[k] & 0x7FFFu) != 0 ? 1u : 0u;
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        m[k] = keep_rule(key(4 * q + k), Tj, idx0 + e0 + k, endj) ? 1 : 0;
+                        th[k] = m[k] ? v[q][k] : 0.0f;
+                    }
+                    if (o.theta16)
+                        for (int k = 0; k < 4; ++k) h[k] = f32_to_f16_rne(th[k]);
+                }
+                if (vec && e0 + 4 <= n) {
+                    if (o.theta) st4_stream(o.theta + e0, th[0], th[1], th[2], th[3]);
+                    if ((!LC || PQ) && o.theta16) st_code4_stream(o.theta16 + e0, h[0], h[1], h[2], h[3]);
+                    if (LC) st4_stream(td.lam_out + e0, ln[0], ln[1], ln[2], ln[3]);
+                    if (LC && td.grad) st4_stream(td.grad + e0, gr[0], gr[1], gr[2], gr[3]);
+                    if (o.mask) st_mask4_stream(o.mask + e0, m[0], m[1], m[2], m[3]);
+                } else {
+                    if (o.theta) store4<false>(o.theta, e0, n, th);
+                    if ((!LC || PQ) && o.theta16) store4_u16<false>(o.theta16, e0, n, h);
+                    if (LC) store4<false>(td.lam_out, e0, n, ln);
+                    if (LC && td.grad) store4<false>(td.grad, e0, n, gr);
+                    if (o.mask) store4_u8<false>(o.mask, e0, n, m);
+                }
+            }
+        }
+    }
+    __device__ inline u32 above(u32 hi) const {            // of the wavefront
+        u32 n = 0;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) n += static_cast<u32>(__popcll(__ballot(key(e) - hi - 1u < 0x7FFFFFFFu - hi)));
+        return n;
+    }
+    __device__ inline u32 equal(u32 T) const {             // of the wavefront
+        u32 n = 0;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) n += static_cast<u32>(__popcll(__ballot(key(e) == T)));
+        return n;
+    }
+};
+// f(c, chunk) for the chunks c0 .. c1 that `want` asks for, until it returns true; the next one's loads are in flight meanwhile.
+template <bool LC, bool VEC, int THREADS, typename Want, typename F>
+__device__ inline void for_chunks(const DataArgs& a, u64 c0, u64 c1, Want&& want, F&& f) {
+    ChunkKeys<LC, VEC, THREADS> x;
+    auto next = [&](u64 c) { while (c < c1 && !want(c)) ++c; return c; };
+    u64 c = next(c0);
+    if constexpr (LC) {                                    // (two chunks of two arrays do not fit the registers)
+        for (; c < c1; c = next(c + 1)) {
+            x.fetch(a, c);
+            if (f(c, x)) return;
+        }
+    } else {
+        ChunkKeys<LC, VEC, THREADS> y;
+        if (c < c1) x.fetch(a, c);
+        while (c < c1) {                                   // uniform
+            const u64 d = next(c + 1);
+            if (d < c1) y.fetch(a, d);
+            if (f(c, x)) return;
+            if (d >= c1) return;
+            c = next(d + 1);
+            if (c < c1) x.fetch(a, c);
+            if (f(d, y)) return;
+        }
+    }
+}
+
+__device__ inline u32 bins_shift(u32 span, u32 bins) {     // (d >> shift) < bins for every d <= span
+    const u32 bits = 32u - static_cast<u32>(__builtin_clz(span | 1u)), have = 31u - static_cast<u32>(__builtin_clz(bins));
+    return bits > have ? bits - have : 0u;
+}
+
+// The next interval, from the keys that lie in the bin of the rank: word(b) keys in bin b of B over st's interval, word(B + b) and
+// word(2 B + b) their range (as ChunkKeys::count leaves them), `above` keys above the interval (needed when it is unsure).
+// All threads; pick: three words of LDS.  Ends with a barrier, after the last use of the words.
+template <int THREADS, typename Word>
+__device__ inline ListState next_interval(const ListState& st, u32 B, u32 above, u32 n_all, u32* s_wave, u32* pick, Word&& word) {
+    const u32 per = (B + THREADS - 1) / THREADS, first = threadIdx.x * per;            // this thread's bins, from the top
+    u32 sum = 0, all;
+    for (u32 i = first; i < first + per && i < B; ++i) sum += word(B - 1 - i);
+    if (threadIdx.x < 3) pick[threadIdx.x] = 0;
+    u32 before = wg_incl_scan_u32<THREADS>(sum, s_wave, &all) - sum;
+    const bool unsure = (st.flags & kStateUnsure) != 0;
+    const bool inside = !unsure || (above < st.rank && st.rank - above <= all);
+    const u32 rank = unsure ? st.rank - above : st.rank;
+    if (inside)
+        for (u32 i = first; i < first + per && i < B; ++i) {
+            const u32 v = word(B - 1 - i);
+            if (before < rank && rank <= before + v) { pick[0] = B - 1 - i; pick[1] = rank - before; pick[2] = v; }
+            before += v;
+        }
+    __syncthreads();
+    ListState x{};
+    if (inside) {
+        x.a = st.a + ~word(2 * B + pick[0]);
+        x.b = st.a + word(B + pick[0]) - 1u;
+        x.rank = pick[1];
+        x.n = pick[2];
+    } else if (above >= st.rank) {
+        x.a = st.b + 1u; x.b = 0x7FFFFFFFu; x.rank = st.rank; x.n = above;
+    } else {
+        x.a = 0; x.b = st.a - 1u; x.rank = st.rank - above - all; x.n = n_all - above - all;
+    }
+    __syncthreads();
+    return x;
+}
+
+constexpr u32 kFallbackWords = 3 * 4096;         // histograms of one population's rankings in LDS
+
+// One ranking by one workgroup (k_list_finish): `st` says where its threshold is, `nz` are this thread's corrections so far of
+// the count of non-zero codes.
+template <bool LC, bool VEC, bool PQ>
+__device__ inline void list_alone(const DataArgs& a, const ListArgs& w, u32* words, u32* s_wave, u32* s_pick, u64* s_end, u32 s, ListState st, int nz,
+                                  condensa_select* results, int n_groups, int vec_out) {
+    constexpr int THREADS = kListThreads;
+    const u32 tid = threadIdx.x, lane = tid & 63u, g = s / a.J, j = s - g * a.J;
+    Slot& slot = a.slots[s];
+    const u64 cb = a.per_tensor ? a.td[g].chunk_start : 0, ce = a.per_tensor ? a.td[g + 1].chunk_start : a.n_chunks;
+    const bool tied = (st.flags & kStateTied) != 0;
+    auto any = [](u64) { return true; };
+    constexpr u32 B = kFallbackWords / 3;
+    for (int level = 0; level < kFallbackLevels && (st.a < st.b || (st.flags & kStateUnsure)); ++level) {
+        for (u32 i = tid; i < kFallbackWords; i += THREADS) words[i] = 0;
+        if (tid == 0) s_pick[3] = 0;
+        __syncthreads();
+        const u32 span = st.b - st.a, shift = bins_shift(span, B);
+        for_chunks<LC, VEC, THREADS>(a, cb, ce, any, [&](u64, const auto& ck) {
+            ck.count(words, B, st.a, span, shift);
+            if (!(st.flags & kStateUnsure)) return false;  // uniform
+            const u32 above = ck.above(st.b);
+            if (lane == 0 && above) atomicAdd(&s_pick[3], above);
+            return false;
+        });
+        __syncthreads();
+        st = next_interval<THREADS>(st, B, s_pick[3], static_cast<u32>(slot.n), s_wave, s_pick, [&](u32 i) { return words[i]; });
+    }
+    const u32 T = st.a;
+    u32 last = 0xFFFFFFFFu;
+    u64 tie_end = slot.n;
+    if (st.rank < st.n) {                                  // uniform: the chunk, then the element that ends the kept ties
+        u32 cum = 0;
+        for_chunks<LC, VEC, THREADS>(a, cb, ce, any, [&](u64 c, const auto& ck) {
+#pragma unroll
+            for (int q = 0; q < ck.kQuads; ++q) {          // elements ascend with q, then the thread, then k
+                u32 eq = 0, total;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) eq |= ck.key(4 * q + k) == T ? 1u << k : 0u;
+                const u32 mine = static_cast<u32>(__popc(eq)), upto = cum + wg_incl_scan_u32<THREADS>(mine, s_wave, &total);
+                if (upto - mine < st.rank && st.rank <= upto) {
+                    for (u32 skip = st.rank - (upto - mine) - 1; skip > 0; --skip) eq &= eq - 1;
+                    s_pick[0] = q * (4 * THREADS) + tid * 4 + static_cast<u32>(__ffs(eq)) - 1u;
+                }
+                cum += total;
+                if (cum < st.rank) continue;               // uniform
+                __syncthreads();
+                const TensorDesc& td = a.td[a.chunk_map[c]];
+                last = static_cast<u32>(c) * kChunk + s_pick[0];
+                tie_end = (c - td.chunk_start) * kChunk + s_pick[0] + (a.per_tensor ? 0 : td.flat_start) + 1;
+                return true;
+            }
+            return false;
+        });
+        __syncthreads();
+    }
+    if (tid == 0) {
+        slot.prefix = T; slot.remaining = st.rank; slot.n_tie = st.n; slot.need_tie = 0; slot.tie_end = tie_end; slot.state = kDone;
+        results[static_cast<u64>(j) * n_groups + g] = select_record(slot, true, T, st.rank, st.n, tie_end, tied ? slot.path : 3);
+    }
+    if (!w.write) return;
+    u32 codes = 0;
+    if (tied) {                                            // the ties alone
+        const bool kept = T >= w.win[s].mid;
+        const u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
+        constexpr int kB = 4;
+        for (u32 i0 = tid; i0 < st.n; i0 += THREADS * kB) {
+            u32 idx[kB];
+            bool keep[kB], on[kB];
+#pragma unroll
+            for (int b = 0; b < kB; ++b) {
+                const u32 i = i0 + b * THREADS;
+                idx[b] = i < st.n ? gidx[i] : 0u;
+                keep[b] = idx[b] <= last;
+                on[b] = i < st.n && keep[b] != kept;
+            }
+            list_fix<LC, PQ, kB>(a, w, j, idx, keep, on, &nz);
+        }
+    } else {
+        if (tid == 0) { s_pick[j] = T; s_end[j] = tie_end; }
+        __syncthreads();
+        for_chunks<LC, VEC, THREADS>(a, cb, ce, any, [&](u64 c, const auto& ck) {
+            ck.template apply<PQ>(a, w.out, c, 1u << j, s_pick, s_end, vec_out != 0, &codes);
+            return false;
+        });
+    }
+    if (PQ && w.nnz_out) {                                 // modulo 2^32: the sums themselves are smaller
+        u32 v = tied ? static_cast<u32>(nz) : codes, total;
+        if (tied) for (u32 i = tid; i < static_cast<u32>(kListSegs); i += THREADS) v += w.nnz[i];
+        __syncthreads();
+        wg_incl_scan_u32<THREADS>(v, s_wave, &total);
+        if (tid == 0) *w.nnz_out = total;
+    }
+}
+
 // Rankings of populations of at most list_lone elements: one workgroup each does the counting, the gathering and the
-// ranking on its list, and a failed ranking by itself (it reads the population a few times over: a megabyte or so).
-// 22 thousand listed keys of a 1024x1024 matrix: see the measurements beside the launch rule.
-template <bool LC, bool PQ>
-__global__ __launch_bounds__(kListThreads) void k_list_finish(DataArgs a, ListArgs w, condensa_select* results, int n_groups) {
+// ranking on its list, and what that leaves open (65 536 weights, nine tenths zeros: 83-92 us the call, 317-358 when elements
+// were ranked and written one at a time).
+template <bool LC, bool VEC, bool PQ>
+__global__ __launch_bounds__(kListThreads) void k_list_finish(DataArgs a, ListArgs w, condensa_select* results, int n_groups, int vec_out) {
     constexpr u32 kQueue = 4096;
     __shared__ ListShared sh;
-    __shared__ __align__(8) u32 s_big[kQueue];             // queue of wrong decisions; the failed case: a histogram of kBins
-    __shared__ u32 s_n, s_f, s_over, s_want, s_bin, s_found;
-    __shared__ u64 s_rem, s_cnt;
-    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    __shared__ __align__(8) u32 s_big[kFallbackWords];             // queue of wrong decisions; list_alone's histogram
+    __shared__ u32 s_n, s_f, s_over, s_max, s_maxc, s_pick[kMaxJ];
+    __shared__ u64 s_end[kMaxJ];
+    const u32 tid = threadIdx.x, wave = tid >> 6;
     constexpr u32 kWaves = kListThreads / 64;
     const u32 s = blockIdx.x;
     const ListRank rk = w.rank[s];
@@ -1369,47 +1854,47 @@ __global__ __launch_bounds__(kListThreads) void k_list_finish(DataArgs a, ListAr
     Slot& slot = a.slots[s];
     int nz = 0;
     u32 want = 0, n = 0;
-    bool in_lds = false;
-    const bool selecting = slot.state == kSelecting;
-    if (selecting) {                                       // uniform
+    bool in_lds = false, left = false;
+    ListState st{};
+    if (slot.state == kSelecting && win_crowded(win)) {    // uniform
+        left = true;
+        st.a = win.lo; st.b = win.hi; st.rank = static_cast<u32>(slot.k); st.flags = kStateUnsure;
+    } else if (slot.state == kSelecting) {
         const u64 cw = tid < rk.n_segs ? w.cnt[static_cast<u64>(s) * w.max_segs + tid] : 0;       // n_segs <= kListSegs == kListThreads
         const u32 k = static_cast<u32>(slot.k);
         if (tid < static_cast<u32>(kListBins)) sh.hist[tid] = 0;
-        if (tid == 0) { s_n = 0; s_f = 0; s_over = 0; s_want = 0; }
+        if (tid == 0) { s_n = 0; s_f = 0; s_over = 0; s_max = 0; s_maxc = 0; }
         __syncthreads();
         if (static_cast<u32>(cw) > rk.seg_cap) s_over = 1;
-        u32 kept, listed;
-        wg_incl_scan_u32<kListThreads>(static_cast<u32>(cw >> 32), sh.wave, &kept);
+        u32 above, listed;
+        wg_incl_scan_u32<kListThreads>(static_cast<u32>(cw >> 32), sh.wave, &above);
         wg_incl_scan_u32<kListThreads>(static_cast<u32>(cw), sh.wave, &listed);
-        const u32 lo = win.lo, shift = win.bins & 0xFFu, mid_bin = win.bins >> 8;
-        list_walk(w, s, rk, wave, kWaves, [&](bool there, u32 key, u64) {
-            if (there) atomicAdd(&sh.hist[(key - lo) >> shift], 1u);
-        });
-        __syncthreads();
-        if (wave == 0) {                                   // listed keys from the estimate on
-            u32 gt = 0;
-            for (u32 b = lane; b < static_cast<u32>(kListBins); b += 64) gt += b >= mid_bin ? sh.hist[b] : 0u;
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) gt += __shfl_xor(gt, d, 64);
-            const u32 above = kept - gt;                   // keys above the window
-            if (lane == 0 && s_over == 0 && kept >= gt && above < k && k - above <= listed) s_want = k - above;
-        }
-        __syncthreads();
-        want = s_want;
-        if (want != 0) {                                   // uniform
+        const u32 lo = win.lo, shift = win_shift(win), mid_bin = win_mid_bin(win);
+        if (s_over != 0 || above >= k || k - above > listed) {           // uniform
+            left = true;
+            st = list_window_state(win, static_cast<u32>(slot.n), k, above, listed);
+        } else {
+            list_walk(w, s, rk, wave, kWaves, [&](bool there, u32 key, u64) { wave_count(sh.hist, there, there ? (key - lo) >> shift : 0u); });
+            __syncthreads();
             u32 bin;
-            list_pick(sh, true, want, &bin, &want, &n);
-            if (n > w.gather_cap) want = 0;
-            u32* gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
-            u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
-            const u32* __restrict__ ids = w.idx + rk.base;
-            in_lds = n <= kListRanked;
-            if (want != 0) {
+            list_pick(sh, true, k - above, &bin, &want, &n);
+            if (n > w.gather_cap) {
+                left = true;
+                st.a = lo + (bin << shift); st.b = st.a + ((1u << shift) - 1u); st.rank = want; st.n = n;
+                st.b = st.b < win.hi ? st.b : win.hi;
+            } else {
+                u32* gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
+                u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
+                const u32* __restrict__ ids = w.idx + rk.base;
+                in_lds = n <= kListRanked;
+                u32 most = 0, mostc = 0;
                 list_walk(w, s, rk, wave, kWaves, [&](bool there, u32 key, u64 at) {
                     const u32 b = (key - lo) >> shift, entry = static_cast<u32>(at - rk.base);
                     const bool found = there && b == bin, wrong = w.write && there && b != bin && (b > bin) != (b >= mid_bin);
                     const u32 f = wave_push(&s_f, found);  // n of them; their indices are fetched below, side by side
                     if (found) {
+                        most = key > most ? key : most;
+                        mostc = ~key > mostc ? ~key : mostc;
                         if (in_lds) { sh.key[f] = key; sh.idx[f] = entry; }
                         else        { gkey[f] = key; gidx[f] = entry; }
                     }
@@ -1419,292 +1904,419 @@ __global__ __launch_bounds__(kListThreads) void k_list_finish(DataArgs a, ListAr
                         else            list_fix_one<LC, PQ>(a, w, j, ids[entry], b > bin, &nz);
                     }
                 });
+                if (!in_lds) { atomicMax(&s_max, most); atomicMax(&s_maxc, mostc); }
                 __syncthreads();
                 if (in_lds) for (u32 f = tid; f < n; f += kListThreads) sh.idx[f] = ids[sh.idx[f]];
                 else        for (u32 f = tid; f < n; f += kListThreads) gidx[f] = ids[gidx[f]];
                 list_fix_queue<LC, PQ, kListThreads>(a, w, j, ids, s_big, s_n < kQueue ? s_n : kQueue, &nz);
                 __threadfence_block();                     // the gathered entries are read by other threads below
                 __syncthreads();
+                if (!in_lds && s_max == ~s_maxc) {         // uniform: thousands of ties
+                    left = true;
+                    st.a = st.b = s_max; st.rank = want; st.n = n; st.flags = kStateTied;
+                }
             }
         }
     }
-    list_rank<LC, PQ, kListThreads>(a, w, sh, s, want, n, in_lds, nz, 0, 1, results, n_groups);
-    if (!selecting || want != 0) return;
-    // failed: radix levels over the population, the tie rule, and every output again
-    const u64 cb = a.per_tensor ? a.td[g].chunk_start : 0, ce = a.per_tensor ? a.td[g + 1].chunk_start : a.n_chunks;
-    constexpr int kRun = kChunk / kListThreads;            // consecutive elements per thread
-    auto keys_of = [&](u64 c, u32* key) -> int {           // keys of this thread's run of chunk c; how many exist
-        const TensorDesc& td = a.td[a.chunk_map[c]];
-        const u64 e0 = (c - td.chunk_start) * kChunk + tid * kRun;
-        int have = 0;
-#pragma unroll
-        for (int i = 0; i < kRun; ++i)
-            if (e0 + i < td.n) { key[i] = mag_key(LC ? lc_shift(td.w[e0 + i], td.lam[e0 + i], a.mu) : td.w[e0 + i]); have = i + 1; }
-        return have;
-    };
-    u64 rem = slot.k, n_tie = 0;
-    u32 T = 0;
-    for (int level = 0; level < n_levels(31); ++level) {
-        const Level L = level_of(31, level);
-        const int nb = 1 << L.bits;
-        for (int i = tid; i < kBins; i += kListThreads) s_big[i] = 0;
-        if (tid == 0) s_found = 0;
-        __syncthreads();
-        for (u64 c = cb; c < ce; ++c) {
-            u32 key[kRun];
-            const int have = keys_of(c, key);
-            for (int i = 0; i < have; ++i)
-                if (((static_cast<u64>(key[i]) ^ T) >> L.hi_shift) == 0) atomicAdd(&s_big[(key[i] >> L.shift) & (nb - 1)], 1u);
-        }
-        __syncthreads();
-        if (wave == 0) wave_pick_desc(s_big, nb, rem, &s_bin, &s_rem, &s_cnt, &s_found);
-        __syncthreads();
-        T |= s_bin << L.shift;
-        rem = s_rem;
-        n_tie = s_cnt;
-        __syncthreads();
-    }
-    u64 tie_end = slot.n;
-    if (rem < n_tie) {                                     // uniform: the chunk and the element that end the kept ties
-        u64 cum = 0;
-        for (u64 c = cb; c < ce; ++c) {
-            u32 key[kRun], hits = 0, total;
-            const int have = keys_of(c, key);
-            for (int i = 0; i < have; ++i) hits += key[i] == T ? 1u : 0u;
-            const u32 before = wg_incl_scan_u32<kListThreads>(hits, sh.wave, &total) - hits;
-            if (cum + total >= rem) {                      // uniform
-                u64 seen = cum + before;
-                const TensorDesc& td = a.td[a.chunk_map[c]];
-                for (int i = 0; i < have; ++i)
-                    if (key[i] == T && ++seen == rem) s_rem = (c - td.chunk_start) * kChunk + tid * kRun + i + (a.per_tensor ? 0 : td.flat_start) + 1;
-                break;
-            }
-            cum += total;
-        }
-        __syncthreads();
-        tie_end = s_rem;
-    }
-    u32 codes = 0;
-    if (w.write)
-        for (u64 c = cb; c < ce; ++c) {
-            u32 key[kRun];
-            const int have = keys_of(c, key);
-            const TensorDesc& td = a.td[a.chunk_map[c]];
-            const u64 e0 = (c - td.chunk_start) * kChunk + tid * kRun, flat = e0 + (a.per_tensor ? 0 : td.flat_start);
-            for (int i = 0; i < have; ++i) {
-                const bool keep = keep_rule(key[i], T, flat + i, tie_end);
-                int dummy = 0;
-                list_fix_one<LC, PQ>(a, w, j, static_cast<u32>(c) * kChunk + tid * kRun + i, keep, &dummy);
-                if (PQ && keep && (f32_to_f16_rne(lc_shift(td.w[e0 + i], td.lam[e0 + i], a.mu)) & 0x7FFFu) != 0) ++codes;
-            }
-        }
-    __syncthreads();
-    if (PQ && w.nnz_out && w.write) {
-        u32 total;
-        wg_incl_scan_u32<kListThreads>(codes, sh.wave, &total);
-        if (tid == 0) *w.nnz_out = total;
-    }
-    if (tid == 0) {
-        slot.prefix = T; slot.remaining = rem; slot.n_tie = n_tie; slot.need_tie = 0; slot.tie_end = tie_end; slot.state = kDone;
-        results[static_cast<u64>(j) * n_groups + g] = select_record(slot, true, T, rem, n_tie, tie_end, 3);
-    }
+    if (left) list_alone<LC, VEC, PQ>(a, w, s_big, sh.wave, s_pick, s_end, s, st, nz, results, n_groups, vec_out);
+    else      list_rank<LC, PQ, kListThreads>(a, w, sh, s, want, n, in_lds, nz, 0, 1, results, n_groups);
 }
 
-// The failed case: ranks the populations that the windows did not resolve by three radix levels over the weights, then applies every
-// result again: one phase for the
-// others, 5 phases per failed ranking and one or two at the end, each cut into gridDim.x pieces.  The pieces are
-// handed out in order by a ticket counter, and a piece of phase p first waits until every piece of the phases before
-// it is done.  All of those were handed out earlier, to workgroups that are running or have ended, and the earliest
-// unfinished phase waits for nothing, so every wait ends whatever part of the grid the device holds at a time.
-// What one phase hands to the next is written and read with device-scope operations.
-constexpr int kSettleGrid = 512;
-
-__device__ inline u32 ld_dev(const u32* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline void st_dev(u32* p, u32 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// The bin (of kBins, walked from the top) that holds descending rank r; all kBlock threads, returns with a barrier.
-__device__ inline void fallback_pick(const u32* hist, u64 r, u64* s_wave, u64* s_pick) {
-    constexpr int kPer = kBins / kBlock;
-    u32 c[kPer];
-    u64 sum = 0;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) { c[i] = ld_dev(hist + kBins - 1 - (threadIdx.x * kPer + i)); sum += c[i]; }
-    u64 total;
-    u64 before = block_excl_scan_u64(sum, s_wave, &total);
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        if (before < r && r <= before + c[i]) { s_pick[0] = kBins - 1 - (threadIdx.x * kPer + i); s_pick[1] = r - before; s_pick[2] = c[i]; }
-        before += c[i];
-    }
-    __syncthreads();
-}
-
-template <bool LC, bool VEC, bool PQ>
-__global__ __launch_bounds__(kBlock) void k_list_settle(DataArgs a, ListArgs w, condensa_select* results, int n_groups, int vec_out) {
-    __shared__ u32 s_hist[kBins];
-    __shared__ u64 s_wave[kBlock / 64], s_pick[3], s_at[3];
-    __shared__ u32 s_ticket;
-    __shared__ ListShared s_rank;
-    const u32 n_fail = w.fb->failed;                       // final: an earlier kernel counted
-    if (n_fail == 0) {
-        const u32 n_r = static_cast<u32>(w.n_rankings), shares = n_r * 16 <= gridDim.x ? 16u : (n_r <= gridDim.x ? gridDim.x / n_r : 1u);
-        for (u32 v = blockIdx.x; v < n_r * shares; v += gridDim.x)
-            list_rank<LC, PQ, kBlock>(a, w, s_rank, v / shares, w.bin_want[v / shares], w.gathered[v / shares], false, 0, v % shares, shares, results, n_groups);
-        return;
-    }
-    const int tid = threadIdx.x;
-    const u32 G = gridDim.x;
-    const bool nnz = PQ && w.write && w.nnz_out != nullptr;
-    const u32 rank_phases = 1 + 5 * n_fail;               // phase 0: the rankings that did not fail
-    const u32 phases = rank_phases + (w.write ? 1 : 0) + (nnz ? 1 : 0);
-    for (;;) {
-        __syncthreads();
+// ---- the whole grid on what the lists leave open -------------------------------------------------------------------
+//
+// All rankings of a call that are left open go through the phases together, however many there are.  A workgroup that takes
+// part takes the same share of every phase, and all of them meet between two phases.  For that they must all be running:
+// each one registers, and when all have, or some time has passed, the first one closes the register and tells those in it
+// how many they are.  Who comes too late leaves.  So nobody ever waits for a workgroup that is not running.
+// A register, a counter or a flag that hundreds of workgroups update or poll costs some 0.1 us for each of them, so there are
+// kMeetGroups of each, in cache lines of their own.
+// What one phase hands to the next goes through device-scope loads, stores and atomics alone (ld_dev and its like), which
+// pass the caches of compute units and dies; waiting for them (s_waitcnt) before the workgroup counts as arrived is all they
+// need.  A fence of device scope would write back and invalidate a die's whole cache: with one per wavefront a phase took 100 us.
+constexpr u32 kMeetGroups = 16, kMeetLine = 32;  // words of a 128-byte line
+constexpr u32 kMeetClosed = 0x80000000u;
+constexpr u32 kMeetWords = (3 * kMeetGroups + 2) * kMeetLine;
+struct Meet {
+    u32* word;
+    u32 rank, size, met;       // this workgroup's number, how many take part, meetings so far
+    __device__ inline u32* joined(u32 g) const { return word + g * kMeetLine; }                            // registered | kMeetClosed
+    __device__ inline u32* arrived(u32 g) const { return word + (kMeetGroups + g) * kMeetLine; }
+    __device__ inline u32* told(u32 g) const { return word + (2 * kMeetGroups + g) * kMeetLine; }          // [0] meetings over, [1] first number | kMeetClosed, [2] size
+    __device__ inline u32* root(u32 i) const { return word + (3 * kMeetGroups + i) * kMeetLine; }          // 0: who is first, 1: groups arrived
+};
+// All threads; false: too late.  sh: three words of LDS.
+__device__ inline bool meet_join(Meet& m, u32* words, u32* sh) {
+    m.word = words;
+    m.met = 0;
+    const u32 tid = threadIdx.x;
+    if (tid < 64) {
+        const u32 g = blockIdx.x % kMeetGroups;
+        u32 mine = 0, first = 0;
         if (tid == 0) {
-            const u32 ticket = __hip_atomic_fetch_add(&w.fb->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const u32 phase = ticket / G;
-            if (phase < phases)
-                while (ld_dev(&w.fb->done) < phase * G) __builtin_amdgcn_s_sleep(8);
-            s_ticket = ticket;
+            mine = add_dev(m.joined(g), 1u);
+            first = mine == 0 && add_dev(m.root(0), 1u) == 0 ? 1u : 0u;
         }
-        __syncthreads();
-        __threadfence();                                   // nothing read below may come from before the wait
-        const u32 phase = s_ticket / G, piece = s_ticket % G;
-        if (phase >= phases) return;                       // every workgroup gets here: tickets only grow
-        if (phase == 0) {
-            for (u32 s = piece; s < static_cast<u32>(w.n_rankings); s += G) list_rank<LC, PQ, kBlock>(a, w, s_rank, s, w.bin_want[s], w.gathered[s], false, 0, 0, 1, results, n_groups);
-        } else if (phase < rank_phases) {
-            const u32 f = (phase - 1) / 5, step = (phase - 1) % 5;
-            const u32 r = w.fail_list[f];
-            const u32 g = r / a.J, j = r % a.J;
-            const u64 k = a.slots[r].k;
-            u32* hist = w.fb_hist + static_cast<u64>(f & 1) * 3 * kBins;
-            const u64 cb = a.per_tensor ? a.td[g].chunk_start : 0, ce = a.per_tensor ? a.td[g + 1].chunk_start : a.n_chunks;
-            // digits decided by the levels before this step
-            u32 prefix = 0;
-            u64 rem = k, n_tie = 0;
-            const u32 decided = step < 3 ? step : 3;
-            for (u32 l = 0; l < decided; ++l) {
-                fallback_pick(hist + l * kBins, rem, s_wave, s_pick);
-                prefix |= static_cast<u32>(s_pick[0]) << level_of(31, l).shift;
-                rem = s_pick[1];
-                n_tie = s_pick[2];
-                __syncthreads();
+        mine = __shfl(mine, 0, 64);
+        first = __shfl(first, 0, 64);
+        if (first) {                                       // wavefront 0 of the workgroup that was first: lane g minds group g
+            for (int polls = 0; polls < 200; ++polls) {    // some 100 us at most
+                u32 here = tid < kMeetGroups ? ld_dev(m.joined(tid)) : 0u;
+#pragma unroll
+                for (int d = 32; d >= 1; d >>= 1) here += __shfl_xor(here, d, 64);
+                if (here == gridDim.x) break;
+                __builtin_amdgcn_s_sleep(4);
             }
-            if (step < 3) {
-                const Level L = level_of(31, step);
-                const int nb = 1 << L.bits;
-                for (int i = tid; i < kBins; i += kBlock) s_hist[i] = 0;
-                __syncthreads();
-                for (u64 c = cb + piece; c < ce; c += G) {
-                    const TensorDesc& td = a.td[a.chunk_map[c]];
-                    const u64 base = (c - td.chunk_start) * kChunk;
-                    for (int q = 0; q < kQuadsPerThread; ++q) {
-                        const u64 e0 = base + static_cast<u64>(q) * (kBlock * 4) + tid * 4;
-                        if (e0 >= td.n) break;
-                        float v[4], l[4];
-                        load4<VEC>(td.w, e0, td.n, v);
-                        if (LC) load4<VEC>(td.lam, e0, td.n, l);
+            u32 n = 0;
+            if (tid < kMeetGroups) n = __hip_atomic_fetch_or(m.joined(tid), kMeetClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            u32 upto = n;
 #pragma unroll
-                        for (int x = 0; x < 4; ++x) {
-                            if (e0 + x >= td.n) break;
-                            const u32 key = mag_key(LC ? lc_shift(v[x], l[x], a.mu) : v[x]);
-                            if (((static_cast<u64>(key) ^ prefix) >> L.hi_shift) == 0) atomicAdd(&s_hist[(key >> L.shift) & (nb - 1)], 1u);
-                        }
-                    }
+            for (int d = 1; d < 64; d <<= 1) { const u32 o = __shfl_up(upto, d, 64); if (static_cast<int>(tid) >= d) upto += o; }
+            const u32 all = __shfl(upto, 63, 64);
+            if (tid < kMeetGroups) {
+                st_dev(m.told(tid) + 2, all);
+                __builtin_amdgcn_s_waitcnt(0);             // the size is there before the flag
+                st_dev(m.told(tid) + 1, (upto - n) | kMeetClosed);
+            }
+        }
+        if (tid == 0) {
+            sh[0] = 0;
+            if (!(mine & kMeetClosed)) {                   // registered in time: the first one is running and will say so
+                u32 from;
+                while (((from = ld_dev(m.told(g) + 1)) & kMeetClosed) == 0) __builtin_amdgcn_s_sleep(2);
+                sh[0] = 1;
+                sh[1] = (from & ~kMeetClosed) + mine;
+                sh[2] = ld_dev(m.told(g) + 2);
+            }
+        }
+    }
+    __syncthreads();
+    const bool in = sh[0] != 0;
+    m.rank = sh[1];
+    m.size = sh[2];
+    __syncthreads();
+    return in;
+}
+// All threads of all workgroups that joined.
+__device__ inline void meet(Meet& m) {
+    __builtin_amdgcn_s_waitcnt(0);                         // every thread's stores have reached the device
+    __syncthreads();
+    ++m.met;
+    if (threadIdx.x == 0) {
+        const u32 g = m.rank % kMeetGroups, groups = m.size < kMeetGroups ? m.size : kMeetGroups;
+        const u32 in_group = (m.size - g + kMeetGroups - 1) / kMeetGroups;
+        bool over = false;
+        if (add_dev(m.arrived(g), 1u) + 1 == in_group * m.met) over = add_dev(m.root(1), 1u) + 1 == groups * m.met;
+        if (over) for (u32 i = 0; i < groups; ++i) st_dev(m.told(i), m.met);
+        else      while (ld_dev(m.told(g)) < m.met) __builtin_amdgcn_s_sleep(2);
+    }
+    __syncthreads();
+}
+
+struct FallbackShared {
+    u64 end[kMaxJ];
+    u32 a[kMaxJ], span[kMaxJ], shift[kMaxJ], count[kMaxJ];
+    u32 wave[kListThreads / 64];
+    u32 pick[4];
+    u16 tab[2048];
+};
+
+// Gathered entries that are many and all equal are ties (whose number and rank are known): list_fallback takes them.
+__device__ inline bool list_tied(const ListArgs& w, u32 s) {
+    return w.bin_want[s] != 0 && w.gathered[s] > kListRanked && w.gmax[s] == ~w.gmaxc[s];
+}
+// State of a special ranking; false: list_rank takes it.
+__device__ inline bool list_state(const ListArgs& w, u32 s, ListState* st) {
+    *st = ld_state(w.state + s);
+    if (!(st->flags & kStateMaybe)) return true;
+    if (!list_tied(w, s)) return false;
+    st->a = st->b = w.gmax[s];
+    st->n = w.gathered[s];
+    st->flags = kStateTied;
+    return true;
+}
+
+// `words`: kFallbackWords of LDS.  `tied`: some suspected ties are ties; `search`: some of those have to be searched.
+template <bool LC, bool VEC, bool PQ, int THREADS>
+__device__ inline void list_fallback(const DataArgs& a, const ListArgs& w, Meet& m, FallbackShared& sh, u32* words, condensa_select* results, int n_groups,
+                                     int vec_out, bool tied, bool search) {
+    const u32 tid = threadIdx.x, lane = tid & 63u;
+    const u32 n_special = w.fb->special, B = w.fb_bins, n_apply = w.fb->apply;         // of an earlier kernel
+    const u64 c0 = a.n_chunks * m.rank / m.size, c1 = a.n_chunks * (m.rank + 1) / m.size;      // this workgroup's chunks
+    auto group_of = [&](u64 c) { return a.per_tensor ? a.chunk_map[c] : 0u; };
+    // the rankings (a bit each) of chunk c's population in one of the masks, looked up where the population changes
+    u32 seen = 0xFFFFFFFFu, seen_mask = 0;
+    auto wanted = [&](const u32* masks) {
+        seen = 0xFFFFFFFFu;
+        return [&, masks](u64 c) {
+            const u32 g = group_of(c);
+            if (g != seen) { seen = g; seen_mask = ld_dev(masks + g); }
+            return seen_mask != 0;
+        };
+    };
+
+    for (int level = 0; level < kFallbackLevels && ld_dev(&w.fb->open[level]) != 0; ++level) {
+        // ---- counts of the keys in the intervals
+        u32 cur = 0xFFFFFFFFu, mask = 0, unsure = 0;
+        bool several = false;                              // the leading digits of the keys say whose they can be
+        auto flush = [&]() {
+            __syncthreads();
+            for (u32 js = mask; js != 0; js &= js - 1u) {
+                const u32 j = static_cast<u32>(__ffs(js)) - 1u;
+                const u64 s = static_cast<u64>(cur) * a.J + j;
+                const u32* from = words + j * 3 * B;
+                u32* to = w.fb_hist + s * 3 * B;
+                for (u32 i = tid; i < B; i += THREADS) {
+                    if (from[i] == 0) continue;
+                    add_dev(&to[i], from[i]);
+                    max_dev(&to[B + i], from[B + i]);
+                    max_dev(&to[2 * B + i], from[2 * B + i]);
+                }
+                if (tid == 0 && sh.count[j]) add_dev(&w.fb_above[s], sh.count[j]);
+            }
+            __syncthreads();
+        };
+        for_chunks<LC, VEC, THREADS>(a, c0, c1, wanted(w.open_of), [&](u64 c, const auto& ck) {
+            const u32 g = group_of(c);
+            if (g != cur) {                                // uniform
+                if (mask) flush();
+                cur = g;
+                mask = ld_dev(&w.open_of[g]);
+                unsure = 0;
+                for (u32 i = tid; i < 3 * B * static_cast<u32>(a.J); i += THREADS) words[i] = 0;
+                if (tid < static_cast<u32>(a.J)) {
+                    const ListState st = ld_state(w.state + static_cast<u64>(g) * a.J + tid);
+                    sh.a[tid] = st.a;
+                    sh.span[tid] = st.b - st.a;
+                    sh.shift[tid] = bins_shift(st.b - st.a, B) | (st.flags & kStateUnsure ? 0x100u : 0u);
+                    sh.count[tid] = 0;
                 }
                 __syncthreads();
-                for (int i = tid; i < nb; i += kBlock)
-                    if (s_hist[i]) __hip_atomic_fetch_add(&hist[step * kBins + i], s_hist[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else if (step == 3) {
-                // ties per chunk; piece 0 also clears the other set of histograms, whose ranking is finished
-                if (piece == 0)
-                    for (int i = tid; i < 3 * kBins; i += kBlock) st_dev(w.fb_hist + static_cast<u64>((f + 1) & 1) * 3 * kBins + i, 0u);
-                for (u64 c = cb + piece; c < ce; c += G) {
-                    const TensorDesc& td = a.td[a.chunk_map[c]];
-                    const u64 base = (c - td.chunk_start) * kChunk;
-                    u64 mine = 0;
-                    for (int q = 0; q < kQuadsPerThread; ++q) {
-                        const u64 e0 = base + static_cast<u64>(q) * (kBlock * 4) + tid * 4;
-                        if (e0 >= td.n) break;
-                        float v[4], l[4];
-                        load4<VEC>(td.w, e0, td.n, v);
-                        if (LC) load4<VEC>(td.lam, e0, td.n, l);
-#pragma unroll
-                        for (int x = 0; x < 4; ++x) {
-                            if (e0 + x >= td.n) break;
-                            mine += mag_key(LC ? lc_shift(v[x], l[x], a.mu) : v[x]) == prefix ? 1u : 0u;
+                for (u32 j = 0; j < static_cast<u32>(a.J); ++j) unsure |= sh.shift[j] & 0x100u ? 1u << j : 0u;
+                several = __popc(mask) > 2;
+                if (several) {
+                    for (u32 i = tid; i < 2048; i += THREADS) {
+                        u32 of = 0;
+                        for (u32 js = mask; js != 0; js &= js - 1u) {
+                            const u32 j = static_cast<u32>(__ffs(js)) - 1u;
+                            if (i >= sh.a[j] >> 20 && i <= (sh.a[j] + sh.span[j]) >> 20) of |= 1u << j;
                         }
-                    }
-                    u64 total;
-                    block_excl_scan_u64(mine, s_wave, &total);
-                    if (tid == 0) st_dev(&a.tiecnt[c], static_cast<u32>(total));
-                }
-            } else if (piece == 0) {
-                // the index that ends the kept ties, then state and record
-                u64 tie_end = a.slots[r].n;
-                if (rem < n_tie) {                         // uniform
-                    if (tid == 0) s_at[2] = 0;
-                    u64 cum = 0;
-                    for (u64 c0 = cb; c0 < ce; c0 += kBlock) {           // uniform trip count
-                        const u64 c = c0 + tid;
-                        const u64 x = c < ce ? ld_dev(&a.tiecnt[c]) : 0;
-                        u64 total;
-                        const u64 ex = cum + block_excl_scan_u64(x, s_wave, &total);
-                        if (ex < rem && rem <= ex + x) { s_at[0] = c; s_at[1] = rem - ex; s_at[2] = 1; }
-                        cum += total;
+                        sh.tab[i] = static_cast<u16>(of);
                     }
                     __syncthreads();
-                    if (s_at[2]) {
-                        const u64 c = s_at[0], want = s_at[1];
-                        const TensorDesc& td = a.td[a.chunk_map[c]];
-                        constexpr int kRun = kChunk / kBlock;            // consecutive elements per thread
-                        const u64 e0 = (c - td.chunk_start) * kChunk + static_cast<u64>(tid) * kRun;
-                        u32 eq = 0;
-                        for (int x = 0; x < kRun; ++x)
-                            if (e0 + x < td.n && mag_key(LC ? lc_shift(td.w[e0 + x], td.lam[e0 + x], a.mu) : td.w[e0 + x]) == prefix) eq |= 1u << x;
-                        u64 total;
-                        const u64 before = block_excl_scan_u64(__popc(eq), s_wave, &total);
-                        if (before < want && want <= before + __popc(eq)) {
-                            for (u64 skip = want - before - 1; skip > 0; --skip) eq &= eq - 1;
-                            s_at[0] = (a.per_tensor ? 0 : td.flat_start) + e0 + (__ffs(eq) - 1) + 1;
-                        }
-                        __syncthreads();
-                        tie_end = s_at[0];
-                    }
-                }
-                if (tid == 0) {
-                    Slot& slot = a.slots[r];
-                    slot.prefix = prefix; slot.remaining = rem; slot.n_tie = n_tie; slot.need_tie = 0; slot.tie_end = tie_end;
-                    slot.state = kDone;
-                    results[static_cast<u64>(j) * n_groups + g] = select_record(slot, true, prefix, rem, n_tie, tie_end, 3);
                 }
             }
-        } else if (w.write && phase == rank_phases) {
-            if (LC) {
-                constexpr u32 kPer = kChunk / (kBlock * 4);
-                for (u64 tile = piece; tile < a.n_chunks * kPer; tile += G) {
-                    if (VEC && vec_out) lc_apply_tile<true, kBlock, PQ, 1>(a, w.out, tile);
-                    else                lc_apply_tile<false, kBlock, PQ, 1>(a, w.out, tile);
-                }
+            if (several) ck.count_many(words, B, sh.tab, sh.a, sh.span, sh.shift);
+            for (u32 js = several ? unsure & mask : mask; js != 0; js &= js - 1u) {            // uniform
+                const u32 j = static_cast<u32>(__ffs(js)) - 1u;
+                if (!several) ck.count(words + j * 3 * B, B, sh.a[j], sh.span[j], sh.shift[j] & 0xFFu);
+                if (!((unsure >> j) & 1u)) continue;
+                const u32 above = ck.above(sh.a[j] + sh.span[j]);
+                if (lane == 0 && above) atomicAdd(&sh.count[j], above);
+            }
+            return false;
+        });
+        if (mask) flush();
+        meet(m);
+        // ---- the next intervals
+        for (u32 f = m.rank; f < n_special; f += m.size) {
+            const u32 s = w.special[f], g = s / a.J, j = s - g * a.J;
+            if (((ld_dev(&w.open_of[g]) >> j) & 1u) == 0) continue;      // uniform: this bit is this workgroup's to change
+            const ListState st = ld_state(w.state + s);
+            u32* hist = w.fb_hist + static_cast<u64>(s) * 3 * B;
+            const ListState x = next_interval<THREADS>(st, B, ld_dev(&w.fb_above[s]), static_cast<u32>(a.slots[s].n), sh.wave, sh.pick, [&](u32 i) { return ld_dev(&hist[i]); });
+            for (u32 i = tid; i < 3 * B; i += THREADS) st_dev(&hist[i], 0u);
+            if (tid != 0) continue;
+            st_state(w.state + s, x.a, x.b, x.rank, x.n, 0);
+            if (x.a == x.b) {
+                __hip_atomic_fetch_and(&w.open_of[g], ~(1u << j), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (x.rank < x.n) { or_dev(w.tie_of + g, 1u << j); add_dev(&w.fb->ties, 1u); }
             } else {
-                for (u64 tile = piece; tile < a.n_chunks * kSubPerChunk; tile += G) {
-                    if (VEC && vec_out) prune_apply_tile<true>(a, w.out, tile);
-                    else                prune_apply_tile<false>(a, w.out, tile);
-                    __syncthreads();                       // the tile's LDS tables are rewritten by the next one
+                add_dev(&w.fb->open[level + 1], 1u);
+            }
+        }
+        meet(m);
+    }
+
+    if (search || ld_dev(&w.fb->ties) != 0) {              // ---- ties per chunk
+        u32 cur = 0xFFFFFFFFu, mask = 0;
+        for_chunks<LC, VEC, THREADS>(a, c0, c1, wanted(w.tie_of), [&](u64 c, const auto& ck) {
+            const u32 g = group_of(c);
+            if (g != cur) {                                // uniform
+                cur = g;
+                mask = ld_dev(&w.tie_of[g]);
+                if (tid < static_cast<u32>(a.J)) {
+                    ListState st{};
+                    sh.a[tid] = ((mask >> tid) & 1u) && list_state(w, g * a.J + tid, &st) ? st.a : 0xFFFFFFFEu;
                 }
             }
-        } else if (piece == 0) {
-            u64 v = 0, total;
-            for (int i = tid; i < kNnzSegs; i += kBlock)
-                v += __hip_atomic_load(&a.nnz_seg[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            block_excl_scan_u64(v, s_wave, &total);
-            if (tid == 0) *w.nnz_out = total;
-        }
-        __threadfence();                                   // every thread's stores reach the device before the piece counts as done
-        __syncthreads();
-        if (tid == 0) __hip_atomic_fetch_add(&w.fb->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid < static_cast<u32>(a.J)) sh.count[tid] = 0;
+            __syncthreads();
+            for (u32 js = mask; js != 0; js &= js - 1u) {
+                const u32 j = static_cast<u32>(__ffs(js)) - 1u, T = sh.a[j];
+                if (T > 0x7FFFFFFFu) continue;             // uniform: no ties after all
+                const u32 n = ck.equal(T);
+                if (lane == 0 && n) atomicAdd(&sh.count[j], n);
+            }
+            __syncthreads();
+            if (tid < static_cast<u32>(a.J)) st_dev(&a.tiecnt[static_cast<u64>(tid) * a.n_chunks + c], sh.count[tid]);
+            __syncthreads();
+            return false;
+        });
+        meet(m);
     }
+
+    for (u32 f = m.rank; f < n_special; f += m.size) {     // ---- the tie rule, states and records
+        const u32 s = w.special[f], g = s / a.J, j = s - g * a.J;
+        ListState st;
+        if (!list_state(w, s, &st)) continue;              // uniform
+        const u32 T = st.a;
+        Slot& slot = a.slots[s];
+        u64 tie_end = slot.n;
+        u32 last = 0xFFFFFFFFu;
+        if (st.rank < st.n) {                              // uniform
+            const u64 cb = a.per_tensor ? a.td[g].chunk_start : 0, ce = a.per_tensor ? a.td[g + 1].chunk_start : a.n_chunks;
+            const u32* cnt = a.tiecnt + static_cast<u64>(j) * a.n_chunks;
+            u32 cum = 0;
+            if (tid == 0) { sh.pick[0] = static_cast<u32>(cb); sh.pick[1] = 0; sh.pick[2] = 0; }           // (found below; never out of range)
+            __syncthreads();
+            for (u64 b = cb; b < ce && cum < st.rank; b += THREADS) {    // uniform
+                const u64 c = b + tid;
+                const u32 x = c < ce ? ld_dev(&cnt[c]) : 0u;
+                u32 total;
+                const u32 upto = cum + wg_incl_scan_u32<THREADS>(x, sh.wave, &total);
+                if (upto - x < st.rank && st.rank <= upto) { sh.pick[0] = static_cast<u32>(c); sh.pick[1] = st.rank - (upto - x); }
+                cum += total;
+            }
+            __syncthreads();
+            const u64 c = sh.pick[0];
+            const u32 want = sh.pick[1];
+            const TensorDesc& td = a.td[a.chunk_map[c]];
+            constexpr int kRun = kChunk / THREADS;         // consecutive elements per thread
+            const u64 e0 = (c - td.chunk_start) * kChunk + static_cast<u64>(tid) * kRun;
+            u32 eq = 0;
+#pragma unroll
+            for (int x = 0; x < kRun; ++x)
+                if (e0 + x < td.n && mag_key(LC ? lc_shift(td.w[e0 + x], td.lam[e0 + x], a.mu) : td.w[e0 + x]) == T) eq |= 1u << x;
+            u32 total;
+            const u32 mine = static_cast<u32>(__popc(eq)), before = wg_incl_scan_u32<THREADS>(mine, sh.wave, &total) - mine;
+            if (before < want && want <= before + mine) {
+                for (u32 skip = want - before - 1; skip > 0; --skip) eq &= eq - 1;
+                sh.pick[2] = tid * kRun + static_cast<u32>(__ffs(eq)) - 1u;
+            }
+            __syncthreads();
+            last = static_cast<u32>(c) * kChunk + sh.pick[2];
+            tie_end = (c - td.chunk_start) * kChunk + sh.pick[2] + (a.per_tensor ? 0 : td.flat_start) + 1;
+            __syncthreads();
+        }
+        if (tid == 0) {
+            slot.remaining = st.rank; slot.n_tie = st.n; slot.need_tie = 0; slot.state = kDone;
+            st_dev64(&slot.prefix, T);                     // the next phase reads these
+            st_dev64(&slot.tie_end, tie_end);
+            st_dev(&w.state[s].last, last);
+            results[static_cast<u64>(j) * n_groups + g] = select_record(slot, true, T, st.rank, st.n, tie_end, (st.flags & kStateTied) ? slot.path : 3);
+        }
+    }
+    if (!w.write) return;
+    meet(m);
+
+    const bool nnz = PQ && w.nnz_out != nullptr;
+    if (n_apply != 0) {                                    // ---- the outputs
+        u32 cur = 0xFFFFFFFFu, mask = 0, codes = 0;
+        for_chunks<LC, VEC, THREADS>(a, c0, c1, wanted(w.apply_of), [&](u64 c, const auto& ck) {
+            const u32 g = group_of(c);
+            if (g != cur) {                                // uniform
+                mask = ld_dev(&w.apply_of[g]);
+                __syncthreads();
+                if (tid < static_cast<u32>(a.J)) {
+                    const Slot& slot = a.slots[static_cast<u64>(g) * a.J + tid];
+                    sh.a[tid] = static_cast<u32>(ld_dev64(&slot.prefix));
+                    sh.end[tid] = ld_dev64(&slot.tie_end);
+                }
+                __syncthreads();
+                cur = g;
+            }
+            ck.template apply<PQ>(a, w.out, c, mask, sh.a, sh.end, vec_out != 0, &codes);
+            return false;
+        });
+        if (nnz) {
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) codes += __shfl_xor(codes, d, 64);
+            if (lane == 0 && codes != 0)
+                __hip_atomic_fetch_add(&a.nnz_seg[(m.rank * (THREADS / 64) + (tid >> 6)) % kNnzSegs], static_cast<u64>(codes), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    if (tied) {                                            // ---- or the ties alone
+        int nz = 0;
+        const u32 per = n_special < m.size ? m.size / n_special : 1u, sub = m.rank % per;              // workgroups for each of them
+        for (u32 f = m.rank / per; f < n_special && m.rank / per < m.size / per; f += m.size / per) {
+            const u32 s = w.special[f], g = s / a.J, j = s - g * a.J;
+            ListState st;
+            if (!list_state(w, s, &st) || !(st.flags & kStateTied)) continue;          // uniform
+            const u32 last = ld_dev(&w.state[s].last);
+            const bool kept = st.a >= w.win[s].mid;        // what the sweep wrote for the ties
+            const u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
+            constexpr int kB = 4;
+            for (u32 i0 = sub * THREADS + tid; i0 < st.n; i0 += per * THREADS * kB) {
+                u32 idx[kB];
+                bool keep[kB], on[kB];
+#pragma unroll
+                for (int b = 0; b < kB; ++b) {
+                    const u32 i = i0 + b * per * THREADS;
+                    idx[b] = i < st.n ? gidx[i] : 0u;
+                    keep[b] = idx[b] <= last;
+                    on[b] = i < st.n && keep[b] != kept;
+                }
+                list_fix<LC, PQ, kB>(a, w, j, idx, keep, on, &nz);
+            }
+        }
+        if (nnz && n_apply == 0) {
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) nz += __shfl_xor(nz, d, 64);
+            if (lane == 0 && nz != 0)
+                __hip_atomic_fetch_add(w.nnz_out, static_cast<u64>(static_cast<long long>(nz)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    if (nnz && n_apply != 0) {                             // ---- the count of non-zero codes
+        meet(m);
+        if (m.rank != 0) return;
+        u32 v = 0, total;                                  // fewer than 2^32 together
+        for (u32 i = tid; i < static_cast<u32>(kNnzSegs); i += THREADS) v += static_cast<u32>(ld_dev64(&a.nnz_seg[i]));
+        wg_incl_scan_u32<THREADS>(v, sh.wave, &total);
+        if (tid == 0) *w.nnz_out = total;
+    }
+}
+
+constexpr int kSettleGrid = 512, kSettleThreads = 512;
+template <bool LC, bool VEC, bool PQ>
+__global__ __launch_bounds__(kSettleThreads, 4) void k_list_settle(DataArgs a, ListArgs w, condensa_select* results, int n_groups, int vec_out) {
+    __shared__ ListShared sh;
+    __shared__ FallbackShared fs;
+    __shared__ u32 s_words[kFallbackWords];
+    __shared__ u32 s_tied, s_search;
+    const u32 n_special = w.fb->special;                   // final: an earlier kernel counted
+    const u32 n_r = static_cast<u32>(w.n_rankings), shares = n_r * 16 <= gridDim.x ? 16u : (n_r <= gridDim.x ? gridDim.x / n_r : 1u);
+    for (u32 v = blockIdx.x; v < n_r * shares; v += gridDim.x) {
+        const u32 s = v / shares;
+        const u32 want = n_special != 0 && list_tied(w, s) ? 0u : w.bin_want[s];
+        list_rank<LC, PQ, kSettleThreads>(a, w, sh, s, want, w.gathered[s], false, 0, v % shares, shares, results, n_groups);
+    }
+    if (n_special == 0) return;
+    if (threadIdx.x == 0) { s_tied = 0; s_search = 0; }
+    __syncthreads();
+    for (u32 f = threadIdx.x; f < n_special; f += kSettleThreads) {
+        const u32 s = w.special[f];
+        if (!list_tied(w, s)) continue;
+        s_tied = 1;
+        if (w.state[s].rank < w.gathered[s]) s_search = 1;
+    }
+    __syncthreads();
+    const bool tied = s_tied != 0, search = s_search != 0;
+    if (!tied && w.fb->apply == 0) return;                 // the same in every workgroup
+    Meet m;
+    if (!meet_join(m, w.meet, fs.pick)) return;
+    if (PQ && w.nnz_out && w.write && m.rank == 0 && threadIdx.x == 0 && w.fb->apply == 0 && a.ctl->nnz_delta != 0)
+        __hip_atomic_fetch_add(w.nnz_out, a.ctl->nnz_delta, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    list_fallback<LC, VEC, PQ, kSettleThreads>(a, w, m, fs, s_words, results, n_groups, vec_out, tied, search);
 }
 
 }  // namespace condensa
