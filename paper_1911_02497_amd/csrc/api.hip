@@ -279,9 +279,9 @@ static u64 list_entries_bound(u64 N, int n_tensors, bool per_tensor, u32 max_seg
     if (!per_tensor) return list_entries(N, max_segs, cfg);
     const u64 nt = static_cast<u64>(n_tensors);
     const int64_t shift = cfg[CONDENSA_OPT_CAND_SHIFT];
-    u64 most = shift > 0 ? (N >> shift) + 4096 * nt : N / 4 + 4096 * nt;
-    if (shift <= 0 && N / 16 + (nt << 19) < most) most = N / 16 + (nt << 19);
-    if (shift <= 0 && N < most) most = N;
+    u64 most = shift > 0 ? (N >> shift) + 4096 * nt : N / 4 + 4096 * nt;          // list_capacity is at most n / 4 + 4096,
+    if (shift <= 0 && N / 48 + (nt << 18) < most) most = N / 48 + (nt << 18);     // at most n / 48 + 2^18,
+    if (shift <= 0 && N < most) most = N;                                         // and at most n
     return most + static_cast<u64>(kListRow) * max_segs * nt;
 }
 // Bins of list_fallback's histograms: all of one population's in 48 KB of LDS, all rankings' in 12 MB, and no more than a

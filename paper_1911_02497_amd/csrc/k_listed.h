@@ -61,12 +61,14 @@ inline u32 list_sample_groups(u64 n, int J, bool per_tensor) {
     if (n <= (static_cast<u64>(1) << 23)) return 64;
     return kListMaxW;
 }
-// Entries of a ranking's list: several times what its window is expected to hold, every element of a tiny one.
+// Entries of a ranking's list: some four times what its window is expected to hold (list_sample_groups), every element of a
+// tiny one.
 __host__ __device__ inline u64 list_capacity(u64 n, int cand_shift) {
     if (cand_shift > 0) return (n >> cand_shift) < 4096 ? 4096 : n >> cand_shift;
     if (n <= 4096) return n;
-    u64 c = n <= (static_cast<u64>(1) << 21) ? n / 4 : n / 16;
-    const u64 least = n <= (static_cast<u64>(1) << 21) ? 4096 : (static_cast<u64>(1) << 19);
+    const u64 e1 = static_cast<u64>(1) << 18, e2 = static_cast<u64>(1) << 21, e3 = static_cast<u64>(1) << 23;
+    const u64 c = n <= e1 ? n / 4 : (n <= e2 ? n / 12 : (n <= e3 ? n / 24 : n / 48));
+    const u64 least = n <= e1 ? 4096 : (n <= e2 ? e1 / 4 : (n <= e3 ? e2 / 12 : e3 / 24));
     return c < least ? least : c;
 }
 // Segments of a list that wavefronts of `per_wave` elements append to: updates of one counter that return a value
@@ -523,17 +525,15 @@ __global__ __launch_bounds__(kBoundsThreads) void k_list_bounds(DataArgs a, List
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
             v[q] = 0xFFFFFFFFu;                  // past the end: above every key (and every bound looked for)
+            bool says_crowded = false;
             if (64 * q + lane < W) {
                 const ListWin x = w.local[static_cast<u64>(rk.group0 + 64 * q + lane) * a.J + j];
                 v[q] = i == 0 ? x.hi : (i == 1 ? x.lo : x.mid);
-                crowded += win_crowded(x) ? 1u : 0u;
+                says_crowded = win_crowded(x);
             }
+            crowded += static_cast<u32>(__popcll(__ballot(says_crowded)));
         }
-        if (i == 2) {                            // most of the workgroups say so
-#pragma unroll
-            for (int d2 = 32; d2 >= 1; d2 >>= 1) crowded += __shfl_xor(crowded, d2, 64);
-            if (lane == 0) s_crowded[j] = 2 * crowded > W ? 1u : 0u;
-        }
+        if (i == 2 && lane == 0) s_crowded[j] = 2 * crowded > W ? 1u : 0u;             // most of the workgroups say so
         const u32 pick = i == 0 ? (W / 2 + off < W ? W / 2 + off : W - 1) : (i == 1 ? (W / 2 - 1 >= off ? W / 2 - 1 - off : 0) : W / 2);
         u32 x = 0;                               // the largest x with at most `pick` values below it
         for (int bit = 31; bit >= 0; --bit) {
@@ -1267,49 +1267,72 @@ __global__ __launch_bounds__(kBlock) void k_list_gather(DataArgs a, ListArgs w) 
     const u32 g = s / a.J, j = s - g * a.J;
     int nz = 0;
     u32 most = 0, mostc = 0;
-    const bool many = n_in > kFound;                       // uniform
+    // uniform.  Many: a walk over the list to count them first is cheaper than a reservation for every 64 (4 M weights widened
+    // from 8 bits, 60 to 200 thousand ties: 25 us, 50 without); few: it is not (2 to 4 thousand of 20 M weights: 20 us, 31 with).
+    const bool many = n_in > 8 * kFound;
     u32* gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
     u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
     const u32 first_seg = part * (kBlock / 64) + (tid >> 6), stride = w.parts * (kBlock / 64);
-    u32 next = 0;
-    if (many) {                                            // one reservation for all that this wavefront will find
-        list_walk(w, s, rk, first_seg, stride, [&](bool there, u32 key, u64) {
-            next += static_cast<u32>(__popcll(__ballot(there && ((key - lo) >> shift) == bin)));
-        });
-        if (lane == 0 && next) next = atomicAdd(&w.gathered[s], next);
-        next = __shfl(next, 0, 64);
-    }
-    list_walk(w, s, rk, first_seg, stride, [&](bool there, u32 key, u64 at) {
+    auto settle_beside = [&](bool there, u32 key, u64 at, bool* found) {
         const u32 b = (key - lo) >> shift;
-        const bool found = there && b == bin, wrong = w.write && there && b != bin && (b > bin) != (b >= mid_bin);
+        const bool wrong = w.write && there && b != bin && (b > bin) != (b >= mid_bin);
+        *found = there && b == bin;
         const u32 q = wave_push(&s_n, wrong);
         if (wrong) {
             if (q < kQueue) s_queue[q] = static_cast<u32>(at - rk.base) | (b > bin ? 0x80000000u : 0u);
             else            list_fix_one<LC, PQ>(a, w, j, w.idx[at], b > bin, &nz);
         }
-        if (!many) {
-            const u32 f = wave_push(&s_f, found);          // fewer than kFound
+    };
+    if (n_in <= kFound) {                                  // the buffer holds them wherever they are found
+        list_walk(w, s, rk, first_seg, stride, [&](bool there, u32 key, u64 at) {
+            bool found;
+            settle_beside(there, key, at, &found);
+            const u32 f = wave_push(&s_f, found);
             if (found) {
                 s_fkey[f] = key;
                 s_fidx[f] = static_cast<u32>(at - rk.base);
             }
-        } else {                                           // places of this wavefront
-            const u64 m = __ballot(found);
-            const u32 to = next + lanes_below(m);
+        });
+    } else {
+        u32 next = 0;
+        if (many) {                                        // one reservation for all that this wavefront will find
+            list_walk(w, s, rk, first_seg, stride, [&](bool there, u32 key, u64) {
+                next += static_cast<u32>(__popcll(__ballot(there && ((key - lo) >> shift) == bin)));
+            });
+            if (lane == 0 && next) next = atomicAdd(&w.gathered[s], next);
+            next = __shfl(next, 0, 64);
+        }
+        list_walk(w, s, rk, first_seg, stride, [&](bool there, u32 key, u64 at) {
+            bool found;
+            settle_beside(there, key, at, &found);
             if (found) {
                 most = key > most ? key : most;
                 mostc = ~key > mostc ? ~key : mostc;
-                if (to < w.gather_cap) { gkey[to] = key; gidx[to] = w.idx[at]; }
             }
-            next += static_cast<u32>(__popcll(m));
-        }
-    });
-    if (many) {                                            // are they all equal?
+            const u32 f = many ? kFound : wave_push(&s_f, found);
+            if (found && f < kFound) {
+                s_fkey[f] = key;
+                s_fidx[f] = static_cast<u32>(at - rk.base);
+            }
+            const u64 direct = __ballot(found && f >= kFound);           // straight to the list
+            if (direct == 0) return;
+            u32 to = next;
+            if (!many) {
+                const int leader = __ffsll(static_cast<long long>(direct)) - 1;
+                if (static_cast<int>(lane) == leader) to = atomicAdd(&w.gathered[s], static_cast<u32>(__popcll(direct)));
+                to = __shfl(to, leader, 64);
+            }
+            next += static_cast<u32>(__popcll(direct));
+            to += lanes_below(direct);
+            if (((direct >> lane) & 1u) && to < w.gather_cap) { gkey[to] = key; gidx[to] = w.idx[at]; }
+        });
+    }
+    if (n_in > kListRanked) {                              // are they all equal?
         atomicMax(&s_max, most);
         atomicMax(&s_maxc, mostc);
     }
     __syncthreads();
-    const u32 n_f = s_f, n_q = s_n < kQueue ? s_n : kQueue;
+    const u32 n_f = s_f < kFound ? s_f : kFound, n_q = s_n < kQueue ? s_n : kQueue;
     if (tid == 0 && n_f) s_base = atomicAdd(&w.gathered[s], n_f);
     if (tid == 0 && s_maxc) { atomicMax(&w.gmax[s], s_max); atomicMax(&w.gmaxc[s], s_maxc); }
     list_fix_queue<LC, PQ, kBlock>(a, w, j, w.idx + rk.base, s_queue, n_q, &nz);
@@ -2289,9 +2312,10 @@ __device__ inline void list_fallback(const DataArgs& a, const ListArgs& w, Meet&
 constexpr int kSettleGrid = 512, kSettleThreads = 512;
 template <bool LC, bool VEC, bool PQ>
 __global__ __launch_bounds__(kSettleThreads, 4) void k_list_settle(DataArgs a, ListArgs w, condensa_select* results, int n_groups, int vec_out) {
-    __shared__ ListShared sh;
+    __shared__ union { ListShared rank; u32 words[kFallbackWords]; } s_mem;           // one after the other
+    ListShared& sh = s_mem.rank;
+    u32* s_words = s_mem.words;
     __shared__ FallbackShared fs;
-    __shared__ u32 s_words[kFallbackWords];
     __shared__ u32 s_tied, s_search;
     const u32 n_special = w.fb->special;                   // final: an earlier kernel counted
     const u32 n_r = static_cast<u32>(w.n_rankings), shares = n_r * 16 <= gridDim.x ? 16u : (n_r <= gridDim.x ? gridDim.x / n_r : 1u);
