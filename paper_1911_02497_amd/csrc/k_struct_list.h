@@ -13,6 +13,7 @@
 #pragma once
 #include "k_small.h"
 #include "k_structure.h"
+#include "k_window.h"
 
 namespace condensa {
 
@@ -48,7 +49,10 @@ __global__ __launch_bounds__(kBlock) void k_struct_list_hist(StructArgs a, Struc
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const Slot& slot = a.slots[0];
     if (slot_canonical(slot).state != kSelecting) return;  // uniform: k == 0, nothing to rank
-    s_sample[tid] = static_cast<u32>(a.keys[static_cast<u64>(tid) * a.F / kStructSample] >> 32);
+    // one from each of as many equal stretches, at a place of its own in it: evenly spaced ones can all lie in one column of
+    // blocks (every 1024th or 4096th of a matrix whose rows of blocks are powers of two), whose scale need not be the others'
+    const u64 place = (static_cast<u64>(tid) * a.F + __umul64hi(static_cast<u64>(mix32(tid + 1)) << 32, a.F)) / kStructSample;
+    s_sample[tid] = static_cast<u32>(a.keys[place] >> 32);
     for (int i = tid; i < kBins; i += kBlock) s_hist[i] = 0;
     __syncthreads();
     if (wave < 2) {                                        // wavefront 0: the upper end, 1: the lower end

@@ -1,0 +1,76 @@
+"""GPU parity and time of rankings of 4097 to 2^21 structures where the aggregates follow the layout of the matrix: scales that
+go with the column or the row of blocks, two halves far apart; against the oracle (bit exact) and against a matrix whose
+blocks are alike."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1911_02497_amd as P
+from gpu_util import DEV, up, with_form
+from test_gpu_structure import _compare
+
+pytestmark = pytest.mark.gpu
+
+block_prune = with_form(P.condensa_block_prune, fill_keep_idx=True)
+
+
+def _scales(kind, rows, cols, seed=1):
+    """One scale for each block of a grid of rows x cols."""
+    rng = np.random.default_rng(seed)
+    s = np.ones((rows, cols), np.float32)
+    if kind == "first_column_small":
+        s[:, 0] = 0.01
+    elif kind == "first_column_large":
+        s[:, 0] = 100.0
+    elif kind == "columns":
+        s *= np.exp(rng.standard_normal((1, cols))).astype(np.float32)
+    elif kind == "rows":
+        s *= np.exp(rng.standard_normal((rows, 1))).astype(np.float32)
+    elif kind == "halves":
+        s[:, cols // 2:] = 0.001
+    return s
+
+
+KINDS = ["alike", "first_column_small", "first_column_large", "columns", "rows", "halves"]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("density", [0.05, 0.25, 0.5])
+def test_scales_that_follow_the_layout(kind, density):
+    rng = np.random.default_rng(7)
+    w = rng.standard_normal((512, 1024)).astype(np.float32) * np.kron(_scales(kind, 128, 256), np.ones((4, 4), np.float32))
+    _compare(block_prune(up([w]), 4, 4, density, P.SCOPE_GLOBAL), oracle.block_prune([w], 4, 4, density, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], kind)
+
+
+def _seconds(call):
+    call()
+    torch.cuda.synchronize()
+    best = 1e9
+    for _ in range(5):
+        t0 = time.perf_counter()
+        for _ in range(4):
+            call()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t0) / 4)
+    return best
+
+
+def _time_of(scales, block, density=0.25):
+    g = torch.Generator(device=DEV).manual_seed(3)
+    s = torch.from_numpy(scales).to(DEV).repeat_interleave(block, 0).repeat_interleave(block, 1)
+    w = (torch.empty(s.shape, dtype=torch.float32, device=DEV).normal_(generator=g) * s).contiguous()
+    table = P.TensorTable([w])
+    res = P.condensa_block_prune(table, block, block, density)
+    return _seconds(lambda: P.condensa_block_prune(table, block, block, density, outputs=res, workspace=res["workspace"]))
+
+
+@pytest.mark.parametrize("kind", KINDS[1:])
+@pytest.mark.parametrize("density", [0.25, 0.5])
+def test_the_layout_does_not_set_the_time(kind, density):
+    """2^20 blocks of 4x4: a sample that sees one column of blocks puts the threshold outside its window and hundreds of thousands
+    of blocks on the list of one workgroup, 5 to 25 times the time; the bound leaves room for noise and wider windows."""
+    alike, this = _time_of(_scales("alike", 1024, 1024), 4, density), _time_of(_scales(kind, 1024, 1024), 4, density)
+    assert this < 2.5 * alike, (alike, this)
