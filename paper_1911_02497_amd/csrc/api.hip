@@ -1630,6 +1630,9 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
             l.id = at<u32>(workspace_dev, L.cand_key);
             l.cap = L.cand_cap;
             l.window = reinterpret_cast<u32*>(l.count + 1);
+            l.piece = at<StructPiece>(workspace_dev, L.sample);          // (the sample of the one-sweep form, unused here)
+            static_assert(kMaxPieces * sizeof(StructPiece) <= (kSmallCallElems / 8) * sizeof(u32) && 2 * sizeof(StructPiece) <= (sizeof(u32) << 12),
+                          "a piece for every kKeyPiece structures fits a sample of an eighth of them, 4096 at least");
             // each workgroup adds most of 2048 bins to the ranking's histogram (688 128 keys of one radix level: 336 workgroups
             // took 16.4 us, 120 of them 10.7)
             u64 hb = pieces < 96 ? pieces : 96;

@@ -7,7 +7,8 @@
 // either side; 2047 equal steps between them are the bins, and what lies outside belongs to the first or last one.
 // k_struct_list_collect lists the (key, id) pairs of the threshold's bin, a hundred or so, and k_struct_list_finish, one
 // workgroup, finishes on the list.  The list can hold every structure, so nothing overflows, and a sample that misleads
-// makes it longer, never wrong.  Two radix levels instead of the window took 13 + 11 us for a Transformer's 688 128 blocks
+// makes it longer, never wrong.  A long list is equal aggregates as a rule, and those at its ends are found without ranking
+// it (2^20 blocks of 4x4, nine tenths of them pruned before: 1812 us ranked, 120 now).  Two radix levels instead of the window took 13 + 11 us for a Transformer's 688 128 blocks
 // of 8x8 and 12 + 10 for 270 400 blocks of 5x5; this one 11.4 and 8.2.
 // Table 1 (FilterPrune, BlockPrune: structures are aggregated and pruned); Section 3.1.
 #pragma once
@@ -25,7 +26,15 @@ struct StructListArgs {
     u32* id;               // [cap] global structure ids
     u64 cap;
     u32* window;           // its lower end (upper halves of the keys) and the shift of its bins
+    struct StructPiece* piece;       // [F / kKeyPiece, rounded up] of a long list: what each piece of the aggregates adds to it
 };
+struct StructPiece {
+    u64 least, most;       // of its listed keys (none: ~0 and 0)
+    u32 n_least, n_most;   // how many are equal to these
+};
+constexpr u32 kListHeld = 4096;           // list entries held in LDS; a list with more is long
+constexpr u64 kMaxPieces = kSmallCallElems / kKeyPiece;
+static_assert(kMaxPieces <= kSmallFinishThreads && kKeyPiece == 2 * kSmallFinishThreads, "k_struct_list_finish: a thread a piece, two keys a thread");
 
 __device__ inline u32 struct_window_bin(u64 key, u32 lo, u32 shift) {
     const u32 hi = static_cast<u32>(key >> 32);
@@ -113,14 +122,15 @@ __global__ __launch_bounds__(kBlock) void k_struct_list_hist(StructArgs a, Struc
 }
 
 __global__ __launch_bounds__(kBlock) void k_struct_list_collect(StructArgs a, StructListArgs l) {
-    __shared__ u32 s_bin, s_selecting;
+    __shared__ u32 s_bin, s_selecting, s_long;
     __shared__ u64 s_wave[kBlock / 64];
     __shared__ u64 s_base;
+    __shared__ StructPiece s_piece;
     const int tid = threadIdx.x;
     if (tid < 64) {
         u32 bin;
         const SlotStep e = struct_window_step(a, &bin);
-        if (tid == 0) { s_bin = bin; s_selecting = e.state == kSelecting ? 1u : 0u; }
+        if (tid == 0) { s_bin = bin; s_selecting = e.state == kSelecting ? 1u : 0u; s_long = e.n_tie > kListHeld ? 1u : 0u; }
     }
     __syncthreads();
     if (s_selecting == 0) return;                          // uniform: k == 0, nothing to rank
@@ -141,6 +151,27 @@ __global__ __launch_bounds__(kBlock) void k_struct_list_collect(StructArgs a, St
             if (base + tid + static_cast<u64>(u) * kBlock < end && struct_window_bin(key[u], lo, shift) == bin) listed |= 1u << u;
         u64 total;
         const u64 before = block_excl_scan_u64(static_cast<u64>(__popc(listed)), s_wave, &total);
+        if (s_long) {                                      // uniform
+            if (tid == 0) s_piece = StructPiece{~static_cast<u64>(0), 0, 0, 0};
+            __syncthreads();
+            u64 least = ~static_cast<u64>(0), most = 0;
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if (listed & (1u << u)) { least = key[u] < least ? key[u] : least; most = key[u] > most ? key[u] : most; }
+            if (listed) {
+                atomicMin(reinterpret_cast<unsigned long long*>(&s_piece.least), static_cast<unsigned long long>(least));
+                atomicMax(reinterpret_cast<unsigned long long*>(&s_piece.most), static_cast<unsigned long long>(most));
+            }
+            __syncthreads();
+            u32 n_least = 0, n_most = 0;
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if (listed & (1u << u)) { n_least += key[u] == s_piece.least ? 1u : 0u; n_most += key[u] == s_piece.most ? 1u : 0u; }
+            if (n_least) atomicAdd(&s_piece.n_least, n_least);
+            if (n_most) atomicAdd(&s_piece.n_most, n_most);
+            __syncthreads();
+            if (tid == 0) l.piece[base / kKeyPiece] = s_piece;
+        }
         if (total != 0) {                                  // uniform over the workgroup
             if (tid == 0) s_base = atomicAdd(reinterpret_cast<unsigned long long*>(l.count), static_cast<unsigned long long>(total));
             __syncthreads();
@@ -160,7 +191,6 @@ __global__ __launch_bounds__(kBlock) void k_struct_list_collect(StructArgs a, St
     }
 }
 
-constexpr u32 kListHeld = 4096;           // list entries held in LDS
 
 // One workgroup ranks the list, applies the lowest-id rule among equal aggregates and writes state and record.  A lone
 // workgroup is bound by latency: four radix levels over a list in memory took 22 us for the 688 128 blocks, one level of
@@ -173,6 +203,8 @@ __global__ __launch_bounds__(kSmallFinishThreads) void k_struct_list_finish(Stru
     __shared__ u32 s_tie[kSmallFinishThreads];
     __shared__ u32 s_n;
     __shared__ u64 s_last;
+    __shared__ StructPiece s_ends;
+    __shared__ u32 s_wave[kSmallFinishThreads / 64], s_at[2];
     Slot& slot = a.slots[0];
     const u32 tid = threadIdx.x;
     u64 n64 = *l.count;
@@ -191,7 +223,44 @@ __global__ __launch_bounds__(kSmallFinishThreads) void k_struct_list_finish(Stru
     u64 tie_end = slot.n;                                  // every tie kept, unless found otherwise below
     if (e.state == kSelecting) {                           // uniform
         auto key_of = [&](u32 i) { return held ? s_key[i] : l.key[i]; };
-        if (!rank_keys<kSmallFinishThreads>(sh, n, key_of, e.remaining)) {
+        // A long list is ties as a rule (blocks pruned before), at one end of it: then nothing in it needs to be ranked.  The
+        // pieces say how many there are and, one after the other, where the last one kept lies.
+        bool at_end = false;
+        if (!held) {                                       // uniform
+            const u32 pieces = static_cast<u32>((a.F + kKeyPiece - 1) / kKeyPiece);
+            const StructPiece mine = tid < pieces ? l.piece[tid] : StructPiece{~static_cast<u64>(0), 0, 0, 0};
+            if (tid == 0) s_ends = StructPiece{~static_cast<u64>(0), 0, 0, 0};
+            __syncthreads();
+            atomicMin(reinterpret_cast<unsigned long long*>(&s_ends.least), static_cast<unsigned long long>(mine.least));
+            atomicMax(reinterpret_cast<unsigned long long*>(&s_ends.most), static_cast<unsigned long long>(mine.most));
+            __syncthreads();
+            const u32 n_least = mine.least == s_ends.least ? mine.n_least : 0u, n_most = mine.most == s_ends.most ? mine.n_most : 0u;
+            if (n_least) atomicAdd(&s_ends.n_least, n_least);
+            if (n_most) atomicAdd(&s_ends.n_most, n_most);
+            __syncthreads();
+            const u32 r = static_cast<u32>(e.remaining), beyond = n - s_ends.n_least;          // keys above the least one
+            const bool top = r <= s_ends.n_most;
+            at_end = top || r > beyond;
+            if (at_end) {                                  // uniform
+                const u64 T = top ? s_ends.most : s_ends.least;
+                const u32 rank = top ? r : r - beyond, ties = top ? s_ends.n_most : s_ends.n_least, here = top ? n_most : n_least;
+                e.prefix = T; e.remaining = rank; e.n_tie = ties; e.state = kDone; e.need_tie = 0;
+                if (rank < ties) {
+                    u32 total;
+                    const u32 upto = wg_incl_scan_u32<kSmallFinishThreads>(here, s_wave, &total);
+                    if (upto - here < rank && rank <= upto) { s_at[0] = tid; s_at[1] = rank - (upto - here); }
+                    __syncthreads();
+                    const u64 i0 = s_at[0] * kKeyPiece + 2 * tid;
+                    const u32 e0 = i0 < a.F && a.keys[i0] == T ? 1u : 0u, e1 = i0 + 1 < a.F && a.keys[i0 + 1] == T ? 1u : 0u;
+                    const u32 before = wg_incl_scan_u32<kSmallFinishThreads>(e0 + e1, s_wave, &total) - e0 - e1, want = s_at[1];
+                    if (before < want && want <= before + e0 + e1) s_last = i0 + (e0 && want == before + 1 ? 0 : 1);
+                    __syncthreads();
+                    tie_end = s_last + 1;
+                }
+            }
+        }
+        if (at_end) {
+        } else if (!rank_keys<kSmallFinishThreads>(sh, n, key_of, e.remaining)) {
             e.state = kFailed;                             // the counts of the levels and the list disagree: reported, not hidden
         } else {
             const u64 T = sh.key, r = sh.rem;

@@ -1,5 +1,5 @@
 """GPU parity and time of rankings of 4097 to 2^21 structures where the aggregates follow the layout of the matrix: scales that
-go with the column or the row of blocks, two halves far apart; against the oracle (bit exact) and against a matrix whose
+go with the column or the row of blocks, two halves far apart, blocks pruned before; against the oracle (bit exact) and against a matrix whose
 blocks are alike."""
 import time
 
@@ -31,6 +31,8 @@ def _scales(kind, rows, cols, seed=1):
         s *= np.exp(rng.standard_normal((rows, 1))).astype(np.float32)
     elif kind == "halves":
         s[:, cols // 2:] = 0.001
+    elif kind == "pruned":
+        s[rng.random(s.shape) < 0.9] = 0.0
     return s
 
 
@@ -43,6 +45,20 @@ def test_scales_that_follow_the_layout(kind, density):
     rng = np.random.default_rng(7)
     w = rng.standard_normal((512, 1024)).astype(np.float32) * np.kron(_scales(kind, 128, 256), np.ones((4, 4), np.float32))
     _compare(block_prune(up([w]), 4, 4, density, P.SCOPE_GLOBAL), oracle.block_prune([w], 4, 4, density, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], kind)
+
+
+@pytest.mark.parametrize("rows,cols", [(128, 256), (300, 301), (1024, 515)])
+@pytest.mark.parametrize("common", [0.0, 0.5, 3.0])          # many equal aggregates at one end of the list, or in its middle
+@pytest.mark.parametrize("share", [0.4, 0.97])
+def test_long_lists_of_ties(rows, cols, common, share):
+    rng = np.random.default_rng(rows)
+    w = rng.uniform(0.4, 2.0, (rows, cols * 3)).astype(np.float32)
+    same = np.repeat(rng.random((rows, cols)) < share, 3, axis=1)
+    w[same] = common
+    tied = float(same.mean())
+    for d in (0.3 * (1 - tied), 1 - tied - 1.5 / (rows * cols), 1 - tied, 1 - 0.7 * tied, 0.6 * tied, tied, 1.0 - 0.5 / (rows * cols)):
+        d = min(max(d, 0.0), 1.0)
+        _compare(block_prune(up([w]), 1, 3, d, P.SCOPE_GLOBAL), oracle.block_prune([w], 1, 3, d, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], f"{common} {share} {d}")
 
 
 def _seconds(call):
@@ -67,10 +83,11 @@ def _time_of(scales, block, density=0.25):
     return _seconds(lambda: P.condensa_block_prune(table, block, block, density, outputs=res, workspace=res["workspace"]))
 
 
-@pytest.mark.parametrize("kind", KINDS[1:])
+@pytest.mark.parametrize("kind", KINDS[1:] + ["pruned"])
 @pytest.mark.parametrize("density", [0.25, 0.5])
 def test_the_layout_does_not_set_the_time(kind, density):
     """2^20 blocks of 4x4: a sample that sees one column of blocks puts the threshold outside its window and hundreds of thousands
-    of blocks on the list of one workgroup, 5 to 25 times the time; the bound leaves room for noise and wider windows."""
+    of blocks on the list of one workgroup, 5 to 25 times the time, and so do blocks pruned before; the bound leaves room
+    for noise and wider windows."""
     alike, this = _time_of(_scales("alike", 1024, 1024), 4, density), _time_of(_scales(kind, 1024, 1024), 4, density)
     assert this < 2.5 * alike, (alike, this)
