@@ -102,8 +102,8 @@ typedef struct {
     uint64_t n_tie;         /* keys equal to the threshold                                         */
     uint64_t threshold_key; /* the k-th largest key; UINT64_MAX when k == 0                        */
     uint64_t tie_end;       /* n when all ties are kept, else 1 + index of the last kept tie; 0 if k == 0 */
-    uint64_t path;          /* diagnostic: 1 = radix levels over the data, 2 = sampled window,
-                               3 = sampled window missed, radix levels as fallback                 */
+    uint64_t path;          /* diagnostic: 1 = radix levels over the data, 2 = window (sampled or
+                               listed), 3 = window missed or left out: found in further passes     */
 } condensa_select;
 
 /*

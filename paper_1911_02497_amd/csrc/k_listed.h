@@ -3,11 +3,11 @@
 // Up to some ten million weights a call is bound by its dependent launches (about 4.5 us each, however little they
 // do) and by how often it reads the weights, which the three histogram sweeps of the radix levels make four times.
 // Here
-//   1. k_list_sample: every workgroup ranks its own sample in LDS.  For a ranking it wants the sample keys at the
-//      expected rank of the threshold and a little to either side of it.  Small populations get one workgroup, whose
-//      bounds lie as many standard deviations of the sample rank apart as the call asks for.  Large ones get up to
-//      kListMaxW, each with a sample spread over the whole population, and k_list_bounds takes order statistics of
-//      their keys: a confidence interval for the threshold that needs no assumption about how neighbours correlate.
+//   1. k_begin_sample (or k_begin and k_list_sample): every workgroup ranks its own sample in LDS.  For a ranking it wants
+//      the sample keys at the expected rank of the threshold and a little to either side of it.  Small populations get one
+//      workgroup, whose bounds lie as many standard deviations of the sample rank apart as the call asks for.  Large ones
+//      get up to kListMaxW, each with a sample spread over the whole population, and k_list_bounds takes order statistics
+//      of their keys: a confidence interval for the threshold that needs no assumption about how neighbours correlate.
 //      Either way: a window [lo, hi] that holds the threshold unless the sample was unlucky, and an estimate `mid`.
 //   2. k_list_sweep / k_list_sweep_multi: ONE pass over the weights writes the outputs (final outside the windows,
 //      provisional -- kept from `mid` on -- inside), counts the keys above each window and lists the keys inside it
@@ -417,7 +417,8 @@ __global__ __launch_bounds__(kListThreads) void k_list_sample(DataArgs a, ListAr
 }
 
 // The sample as part of the launch that begins the call (few tensors): what the sampling workgroups need
-// of the tables comes as kernel arguments, so they need not wait for the upload.  One launch less: 4 us.
+// of the tables comes as kernel arguments, so they need not wait for the upload.  One launch less: 4 us.  26 bytes a tensor: the
+// argument budget would hold 117 next to the other fields, 96 leaves room for more of these.  Calls of more tensors pay the launch.
 constexpr int kBeginSampleTensors = 96;
 struct BeginSampleArgs {
     UploadArgs up;

@@ -7,38 +7,9 @@ namespace condensa {
 constexpr u64 kSmallCallElems = static_cast<u64>(1) << 21;
 constexpr int kSmallFinishThreads = 1024;
 
-// Wavefront 0 of a workgroup: the bin of an LDS histogram (nb <= kBins bins) that holds descending rank r, i.e.
-// #(keys in higher bins) < r <= #(keys in bins >= bin).  The lane that finds it writes bin, the rank inside
-// the bin, the bin's count and *found = 1; nothing is written when the histogram holds fewer than r keys.
-__device__ inline void wave_pick_desc(const u32* s_hist, int nb, u64 r, u32* bin, u64* rem, u64* cnt, u32* found) {
-    constexpr int kPerMax = kBins / 64;
-    const int lane = threadIdx.x & 63;
-    const int per = (nb + 63) / 64;
-    u32 c[kPerMax];
-    u64 sum = 0;
-#pragma unroll
-    for (int i = 0; i < kPerMax; ++i) {
-        const int b = nb - 1 - (lane * per + i);
-        c[i] = (i < per && b >= 0) ? s_hist[b] : 0u;
-        sum += c[i];
-    }
-    const u64 incl = wave_incl_scan_u64(sum);
-    u64 before = incl - sum;
-    if (before < r && r <= incl) {
-#pragma unroll
-        for (int i = 0; i < kPerMax; ++i) {
-            if (before < r && r <= before + c[i]) {
-                *bin = static_cast<u32>(nb - 1 - (lane * per + i));
-                *rem = r - before;
-                *cnt = c[i];
-                *found = 1u;
-            }
-            before += c[i];
-        }
-    }
-}
-
-// The same for ascending rank r (the r-th lowest), used for the index search among ties.
+// Wavefront 0 of a workgroup: the bin of an LDS histogram (nb <= kBins bins) that holds ascending rank r (the r-th lowest), used for
+// the index search among ties.  The lane that finds it writes bin, the rank inside the bin and *found = 1; nothing is written when
+// the histogram holds fewer than r keys.
 __device__ inline void wave_pick_asc(const u32* s_hist, int nb, u64 r, u32* bin, u64* rem, u32* found) {
     constexpr int kPerMax = kBins / 64;
     const int lane = threadIdx.x & 63;

@@ -8,8 +8,9 @@
 // k_struct_list_collect lists the (key, id) pairs of the threshold's bin, a hundred or so, and k_struct_list_finish, one
 // workgroup, finishes on the list.  The list can hold every structure, so nothing overflows, and a sample that misleads
 // makes it longer, never wrong.  A long list is equal aggregates as a rule, and those at its ends are found without ranking
-// it (2^20 blocks of 4x4, nine tenths of them pruned before: 1812 us ranked, 120 now).  Two radix levels instead of the window took 13 + 11 us for a Transformer's 688 128 blocks
-// of 8x8 and 12 + 10 for 270 400 blocks of 5x5; this one 11.4 and 8.2.
+// it (2^20 blocks of 4x4, nine tenths of them pruned before: 1812 us ranked, 120 now).  Two radix levels instead of the
+// window took 13 + 11 us for a Transformer's 688 128 blocks of 8x8 and 12 + 10 for 270 400 blocks of 5x5; this one 11.4 and
+// 8.2.
 // Table 1 (FilterPrune, BlockPrune: structures are aggregated and pruned); Section 3.1.
 #pragma once
 #include "k_small.h"

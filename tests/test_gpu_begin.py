@@ -28,6 +28,15 @@ def test_tables_of_every_size(n_tensors, densities):
     check_prune_against_oracle(res, oracle.prune(arrs, densities, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, n_tensors)
 
 
+@pytest.mark.parametrize("n_tensors", [96, 97])
+@pytest.mark.parametrize("scope", [P.SCOPE_GLOBAL, P.SCOPE_PER_TENSOR])
+def test_the_sample_in_the_first_launch_and_in_one_of_its_own(n_tensors, scope):
+    arrs = _model(n_tensors, n_tensors)
+    res = P.condensa_prune(up(arrs), [0.3], scope=scope)
+    torch.cuda.synchronize()
+    check_prune_against_oracle(res, oracle.prune(arrs, [0.3], scope), scope, n_tensors)
+
+
 def test_more_calls_in_flight_than_staging_slots():
     """Every call has its own table (and so its own image); none may be replaced before the device has read it."""
     models = [_model(3, 100 + i) for i in range(100)]
