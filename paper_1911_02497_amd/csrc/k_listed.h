@@ -1165,6 +1165,12 @@ __device__ inline void max_dev(u32* p, u32 v) { __hip_atomic_fetch_max(p, v, __A
 __device__ inline u64 ld_dev64(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline void st_dev64(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline void or_dev(u32* p, u32 v) { __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Waits until this wavefront's accesses are done.  The fences emit nothing: they keep the compiler from moving accesses across.
+__device__ inline void wait_dev() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "singlethread");
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "singlethread");
+}
 __device__ inline void st_state(ListState* to, u32 a, u32 b, u32 rank, u32 n, u32 flags) {
     st_dev(&to->a, a); st_dev(&to->b, b); st_dev(&to->rank, rank); st_dev(&to->n, n); st_dev(&to->flags, flags);
 }
@@ -1998,7 +2004,7 @@ __device__ inline bool meet_join(Meet& m, u32* words, u32* sh) {
             const u32 all = __shfl(upto, 63, 64);
             if (tid < kMeetGroups) {
                 st_dev(m.told(tid) + 2, all);
-                __builtin_amdgcn_s_waitcnt(0);             // the size is there before the flag
+                wait_dev();                                // the size is there before the flag
                 st_dev(m.told(tid) + 1, (upto - n) | kMeetClosed);
             }
         }
@@ -2007,6 +2013,7 @@ __device__ inline bool meet_join(Meet& m, u32* words, u32* sh) {
             if (!(mine & kMeetClosed)) {                   // registered in time: the first one is running and will say so
                 u32 from;
                 while (((from = ld_dev(m.told(g) + 1)) & kMeetClosed) == 0) __builtin_amdgcn_s_sleep(2);
+                wait_dev();
                 sh[0] = 1;
                 sh[1] = (from & ~kMeetClosed) + mine;
                 sh[2] = ld_dev(m.told(g) + 2);
@@ -2022,7 +2029,7 @@ __device__ inline bool meet_join(Meet& m, u32* words, u32* sh) {
 }
 // All threads of all workgroups that joined.
 __device__ inline void meet(Meet& m) {
-    __builtin_amdgcn_s_waitcnt(0);                         // every thread's stores have reached the device
+    wait_dev();                                            // every thread's stores have reached the device
     __syncthreads();
     ++m.met;
     if (threadIdx.x == 0) {
