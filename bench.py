@@ -184,7 +184,7 @@ def make_workload(name, args, P, workloads, torch, dev, resident=None):
         host = workloads.single_matrix()
         d = up(host)
         call = lambda: P.condensa_prune(d, [0.02], theta=False, theta_f16=True, mask=True, workspace=ws[0], outputs=prev[0], config=cfg)  # noqa: E731
-        op, bytes_per_elem, desc = P.binding.OP_PRUNE, 11, "prune d=0.02 fused with fp16 theta + mask"
+        op, bytes_per_elem, desc = P.binding.OP_PRUNE, 4 + 2 + 1, "prune d=0.02 fused with fp16 theta + mask"
         cpu = lambda hs: oracle.quantize_f16(oracle.prune(hs, [0.02])[0]["theta"][0])  # noqa: E731
     elif name in ("vgg_thresholds", "vgg_masks"):
         host = workloads.vgg19_cifar()
@@ -195,7 +195,7 @@ def make_workload(name, args, P, workloads, torch, dev, resident=None):
             bytes_per_elem, desc = 4, "thresholds of 10 densities from one sweep"
         else:
             call = lambda: P.condensa_prune(d, ds, theta=False, mask=True, workspace=ws[0], outputs=prev[0], config=cfg)  # noqa: E731
-            bytes_per_elem, desc = 4 + 4 + 10, "10 densities, one selection sweep + one apply sweep writing 10 masks"
+            bytes_per_elem, desc = 4 + 10, "10 densities, one sweep writing 10 masks"
         op, J = P.binding.OP_PRUNE, len(ds)
         cpu = lambda hs: oracle.prune(hs, ds)  # noqa: E731
     elif name.startswith("resnet_filter"):
@@ -416,7 +416,7 @@ def _trace_section(directory, command, bytes_per_launch, top):
             float(r["Percentage"])))
     if rows and "TotalDurationNs" in rows[0]:
         ours = [r for r in rows if "condensa::" in r["Name"]]
-        calls = max((int(r["Calls"]) for r in ours if "k_prepare" in r["Name"]), default=0)
+        calls = max((int(r["Calls"]) for r in ours if "k_prepare" in r["Name"] or "k_begin" in r["Name"]), default=0)
         total_us = sum(float(r["TotalDurationNs"]) for r in ours) / 1e3
         if calls:
             lines += ["", f"The library's kernels: {sum(int(r['Calls']) for r in ours) / calls:.0f} launches and {total_us / calls:.1f} us "
