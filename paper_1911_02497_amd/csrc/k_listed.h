@@ -21,8 +21,8 @@
 // Weights with many equal magnitudes -- pruned before, widened from 8-bit codes -- are such rankings as a rule, so the
 // sample also says when a list could not hold its window (kListCrowded): the sweep then leaves that ranking out.
 // Microseconds at the threshold density 0.1 to 0.2, radix levels / one ranking after the other, by tickets / now: 20 M
-// weights of a VGG-19, nine tenths zeros 409 / 1052 / 176, E4M3 values 180 / 1000 / 166; layer by layer, zeros 365 / 7859 /
-// 250, E4M3 values 185 / 4453 / 240; ten densities, E4M3 values 269 / 6941 / 408; 2^18 weights, zeros 680 / 1227 / 71.
+// weights of a VGG-19, nine tenths zeros 409 / 1052 / 151, E4M3 values 180 / 1000 / 136; layer by layer, zeros 365 / 7859 /
+// 226, E4M3 values 185 / 4453 / 241; ten densities, E4M3 values 269 / 6941 / 430; 2^18 weights, zeros 680 / 1227 / 71.
 // One workgroup draws some 25 GB/s from memory it did not write, so the lists (10^5 entries) are walked by many.  When
 // no population exceeds list_lone elements, its list is short enough for one workgroup to do 3 and 4 alone
 // (k_list_finish): three launches, and a ranking that it leaves open stays with that workgroup (list_alone).
