@@ -296,7 +296,7 @@ static u32 list_groups(u64 n, int J, bool per_tensor, const Config& cfg) {      
     const int64_t opt = cfg[CONDENSA_OPT_SAMPLE_LOG2];
     if (opt <= 0) return list_sample_groups(n, J, per_tensor);
     if ((static_cast<u64>(1) << opt) <= static_cast<u64>(kListThreads) * kListUnits * kSampleUnit) return 1;
-    u32 w = 32;                                            // fewer draws would leave order statistics no room
+    u32 w = 32;                                            // fewer draws would not tell their deviation
     while (w < static_cast<u32>(kListMaxW) && static_cast<u64>(w) * kListThreads * kSampleUnit < (static_cast<u64>(1) << opt)) w *= 2;
     return w;
 }
@@ -347,7 +347,7 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
         L.l_gidx = off;    off += align_up(static_cast<size_t>(L.n_slots) * L.l_gather_cap * sizeof(u32));
         L.l_win = off;     off += align_up(static_cast<size_t>(L.n_slots) * sizeof(ListWin));
         L.l_sorted = off;  off += J > 1 ? align_up(static_cast<size_t>(L.n_groups) * sizeof(ListSorted)) : 0;
-        L.l_local = off;   off += align_up(static_cast<size_t>(groups) * J * sizeof(ListWin));
+        L.l_local = off;   off += align_up(static_cast<size_t>(groups) * J * 3 * sizeof(u64));
         L.l_key = off;     off += align_up(static_cast<size_t>(entries) * sizeof(u32));
         L.l_idx = off;     off += align_up(static_cast<size_t>(entries) * sizeof(u32));
         L.cand_cap = entries;
@@ -717,9 +717,12 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
     u64 base = 0;
     u32 first = 0;
     *shape = ListShape{};
+    u64 asked = 0;                                         // sampling workgroups
+    for (size_t g = 0; per_tensor && g < n_groups; ++g) asked += list_groups(tb.td[g].n, J, true, cfg);
+    const u32 most = asked > kSampleResident && cfg[CONDENSA_OPT_SAMPLE_LOG2] <= 0 ? 32u : static_cast<u32>(kListMaxW);
     for (size_t g = 0; g < n_groups; ++g) {
         const u64 n = per_tensor ? tb.td[g].n : tb.N;
-        const u32 w = list_groups(n, J, per_tensor, cfg);
+        const u32 w = std::min(list_groups(n, J, per_tensor, cfg), most);
         u32 segs = list_segments(n, list_wave_elems(tb.N, J, lc), L.l_max_segs);
         for (int j = 0; j < J; ++j) {
             ListRank& r = rk[g * J + j];
@@ -745,11 +748,12 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
     return table->size();
 }
 
-static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const ListRequest& rq, const Config& cfg) {
+static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const ListShape& shape, const ListRequest& rq, const Config& cfg) {
     ListArgs w{};
     w.rank = at<ListRank>(ws, L.l_rank);
     w.group_of = reinterpret_cast<const u32*>(w.rank + n_slots);
-    w.local = at<ListWin>(ws, L.l_local);
+    w.local = at<u64>(ws, L.l_local);
+    w.n_local = shape.groups;
     w.win = at<ListWin>(ws, L.l_win);
     w.sorted = at<ListSorted>(ws, L.l_sorted);
     w.max_segs = L.l_max_segs;
@@ -789,12 +793,21 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const L
     return w;
 }
 
-// Begins the call and takes the sample in one launch; false when the call is not of that form.
+// Tag of a call's words in ListArgs::local: another one for each of 2^32 calls, and none that a workspace is likely to hold.
+static u32 call_tag(u32 call) {
+    u32 x = call + 0x9E3779B9u;
+    x = (x ^ (x >> 16)) * 0x85EBCA6Bu;
+    x = (x ^ (x >> 13)) * 0xC2B2AE35u;
+    return x ^ (x >> 16);
+}
+
+// Begins the call, takes the sample and bounds the windows in one launch; false when the call is not of that form.
 template <bool LC, bool VEC>
 static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n_tensors, const OutDesc* out, size_t n_out, const Slot* slots,
                                         const double* densities, int J, bool per_tensor, float mu, void* ws, hipStream_t st,
-                                        const std::vector<char>& lists, u32 groups, const ListRequest& rq, const Config& cfg, StageImage* img, bool* begun) {
+                                        const std::vector<char>& lists, const ListShape& shape, const ListRequest& rq, const Config& cfg, StageImage* img, bool* begun) {
     *begun = false;
+    const u32 groups = shape.groups;
     const size_t td_bytes = static_cast<size_t>(tb.n_td) * sizeof(TensorDesc), out_bytes = n_out * sizeof(OutDesc),
                  slot_bytes = static_cast<size_t>(L.n_slots) * sizeof(Slot);
     if (n_tensors > kBeginSampleTensors || groups > 0xFFFFu || td_bytes + out_bytes + slot_bytes + lists.size() > kStageBytes) return CONDENSA_OK;
@@ -823,10 +836,13 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
         b.n[t] = static_cast<u32>(tb.td[t].n);
     }
     for (int t = 0; t <= n_tensors; ++t) b.chunk_start[t] = static_cast<u32>(tb.td[t].chunk_start);
-    const u64 blocks = begin_blocks(b.n_zero, tb.n_chunks) + 1 + groups;
+    b.fillers = static_cast<u32>(begin_blocks(b.n_zero, tb.n_chunks));
+    const u32 bounds = shape.bounds ? (per_tensor ? static_cast<u32>(n_tensors) : 1u) : 0u;
+    ListArgs w = list_args(L, ws, tb.N, L.n_slots, shape, rq, cfg);
+    static std::atomic<u32> calls{0};
+    w.tag = call_tag(calls.fetch_add(1, std::memory_order_relaxed));
     img->launching(st);
-    hipLaunchKernelGGL((k_begin_sample<LC, VEC>), dim3(static_cast<unsigned>(blocks)), dim3(kListThreads), 0, st, b,
-                       list_args(L, ws, tb.N, L.n_slots, rq, cfg));
+    hipLaunchKernelGGL((k_begin_sample<LC, VEC>), dim3(1 + groups + b.fillers + bounds), dim3(kListThreads), sample_lds(J), st, b, w);
     CONDENSA_LAUNCH_CHECK();
     img->commit();
     *begun = true;
@@ -836,14 +852,12 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
 template <bool LC, bool VEC>
 static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* ws, const ListShape& shape, int n_slots, int n_groups,
                                      condensa_select* results, const ListRequest& rq, bool sampled, hipStream_t st, const Config& cfg) {
-    ListArgs w = list_args(L, ws, a.N, n_slots, rq, cfg);
+    ListArgs w = list_args(L, ws, a.N, n_slots, shape, rq, cfg);
     const bool vec = VEC && rq.vec_out;
-    {
+    if (!sampled) {
         PhaseTimer timer(CONDENSA_PHASE_SAMPLE, st, cfg);
-        if (!sampled) {
-            hipLaunchKernelGGL((k_list_sample<LC, VEC>), dim3(shape.groups), dim3(kListThreads), 0, st, a, w);
-            CONDENSA_LAUNCH_CHECK();
-        }
+        hipLaunchKernelGGL((k_list_sample<LC, VEC>), dim3(shape.groups), dim3(kListThreads), sample_lds(a.J), st, a, w);
+        CONDENSA_LAUNCH_CHECK();
         if (shape.bounds) {
             hipLaunchKernelGGL(k_list_bounds, dim3(static_cast<unsigned>(n_groups)), dim3(kBoundsThreads), 0, st, a, w);
             CONDENSA_LAUNCH_CHECK();
@@ -1039,8 +1053,8 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
     bool sampled = false;
     StageImage img;
     if (L.listed)
-        rc = tb.vec ? begin_and_sample<false, true>(L, tb, n_tensors, out, n_out, slots, densities, J, per_tensor, 0.0f, workspace_dev, st, lists, list_shape.groups, rq, cfg, &img, &sampled)
-                    : begin_and_sample<false, false>(L, tb, n_tensors, out, n_out, slots, densities, J, per_tensor, 0.0f, workspace_dev, st, lists, list_shape.groups, rq, cfg, &img, &sampled);
+        rc = tb.vec ? begin_and_sample<false, true>(L, tb, n_tensors, out, n_out, slots, densities, J, per_tensor, 0.0f, workspace_dev, st, lists, list_shape, rq, cfg, &img, &sampled)
+                    : begin_and_sample<false, false>(L, tb, n_tensors, out, n_out, slots, densities, J, per_tensor, 0.0f, workspace_dev, st, lists, list_shape, rq, cfg, &img, &sampled);
     if (rc == CONDENSA_OK && !sampled)
         rc = begin_call(L, tb, n_tensors, out, n_out, slots, n_up_slots, workspace_dev, st, no_alloc ? nullptr : &img, lists.data(), list_bytes, fixed);
     if (rc != CONDENSA_OK) return rc;
@@ -1265,8 +1279,8 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
     bool sampled = false;
     StageImage img;
     if (L.listed)
-        rc = vec_in ? begin_and_sample<true, true>(L, tb, n_tensors, out.data(), out.size(), slot4, &density, 1, false, mu, workspace_dev, st, lists, list_shape.groups, rq, cfg, &img, &sampled)
-                    : begin_and_sample<true, false>(L, tb, n_tensors, out.data(), out.size(), slot4, &density, 1, false, mu, workspace_dev, st, lists, list_shape.groups, rq, cfg, &img, &sampled);
+        rc = vec_in ? begin_and_sample<true, true>(L, tb, n_tensors, out.data(), out.size(), slot4, &density, 1, false, mu, workspace_dev, st, lists, list_shape, rq, cfg, &img, &sampled)
+                    : begin_and_sample<true, false>(L, tb, n_tensors, out.data(), out.size(), slot4, &density, 1, false, mu, workspace_dev, st, lists, list_shape, rq, cfg, &img, &sampled);
     if (rc == CONDENSA_OK && !sampled)
         rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slot4, window ? 4 : 1, workspace_dev, st, &img, lists.data(), list_bytes);
     if (rc != CONDENSA_OK) return rc;

@@ -142,12 +142,7 @@ __global__ __launch_bounds__(64) void k_window_fused(DataArgs a, WindowArgs w) {
     if (lane == 0 && s64)
         atomicAdd(reinterpret_cast<unsigned long long*>(&w.seg_region[seg]), static_cast<unsigned long long>(s64));
     const u32 cnt = __popc(cmask);
-    u32 incl = cnt;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const u32 up = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += up;
-    }
+    const u32 incl = wave_incl_scan_u32(cnt);
     const u32 total = __shfl(incl, 63, 64);
     if (total == 0) return;
     u64 b = 0;

@@ -6,8 +6,9 @@
 //   1. k_begin_sample (or k_begin and k_list_sample): every workgroup ranks its own sample in LDS.  For a ranking it wants
 //      the sample keys at the expected rank of the threshold and a little to either side of it.  Small populations get one
 //      workgroup, whose bounds lie as many standard deviations of the sample rank apart as the call asks for.  Large ones
-//      get up to kListMaxW, each with a sample spread over the whole population, and k_list_bounds takes order statistics
-//      of their keys: a confidence interval for the threshold that needs no assumption about how neighbours correlate.
+//      get up to kListMaxW, each with a sample spread over the whole population, and list_bounds (a workgroup at the end of
+//      the same launch, or k_list_bounds) takes mean and deviation of their keys: a confidence interval for the threshold that
+//      needs no assumption about how neighbours correlate.
 //      Either way: a window [lo, hi] that holds the threshold unless the sample was unlucky, and an estimate `mid`.
 //   2. k_list_sweep / k_list_sweep_multi: ONE pass over the weights writes the outputs (final outside the windows,
 //      provisional -- kept from `mid` on -- inside), counts the keys above each window and lists the keys inside it
@@ -41,6 +42,7 @@ constexpr int kListSegs = 1024;                  // segments of a ranking's list
 constexpr int kListMaxW = 256;                   // sampling workgroups of one population at most
 constexpr int kListMaxRankings = 4096;
 constexpr int kListBins = 256;                   // bins over a window
+static_assert(kListBins == 1 << 8, "list_window: 32 - 8 bits");
 constexpr u32 kListRanked = 2048;                // gathered entries that are held in LDS
 constexpr u32 kListGather = 1u << 18;            // gathered entries of a ranking at most; with more (ties) it is left open
 constexpr u32 kListRow = 64;                     // segments are multiples of this many entries
@@ -52,15 +54,18 @@ constexpr u32 kListRow = 64;                     // segments are multiples of th
 inline u64 list_lone(int J, bool per_tensor) { return static_cast<u64>(1) << (J > 1 ? 16 : (per_tensor ? 18 : 17)); }
 
 // Sampling workgroups of a population of n elements: the window is narrowed as the population grows.  One workgroup leaves
-// a window of up to 8 % of it (10 sd of its rank); 32 about 2 %, 64 about 1 %, 256 about 0.4 % at the cost of one more
-// launch (4 us).  Above list_lone that launch is earned back at once: 295 thousand weights in two densities 52.3 us with one,
-// 37.7 with 32; 600 thousand 59.7 and 39.5; pruning 700 thousand in one density 37.3 and 36.5.
+// a window of up to 8 % of it (10 sd of its rank); 32 about 1 %, 64 about 0.7 %, 256 about 0.3 %, at the cost of some 3 us (their
+// bounds).  Above list_lone that is earned back at once: 295 thousand weights in two densities 52.3 us with one, 37.7 with 32;
+// 600 thousand 59.7 and 39.5; pruning 700 thousand in one density 37.3 and 36.5 (when the bounds were a launch of 4.5 us).
 inline u32 list_sample_groups(u64 n, int J, bool per_tensor) {
     if (n <= list_lone(J, per_tensor)) return 1;
     if (n <= (static_cast<u64>(1) << 21)) return 32;
     if (n <= (static_cast<u64>(1) << 23)) return 64;
     return kListMaxW;
 }
+// Sampling workgroups that are resident at once (two to a compute unit, less those that begin the call and bound the windows): what
+// goes beyond that waits for another round of 8 us, so PER_TENSOR populations that ask for more get 32 each.
+constexpr u32 kSampleResident = 480;
 // Entries of a ranking's list: some four times what its window is expected to hold (list_sample_groups), every element of a
 // tiny one.
 __host__ __device__ inline u64 list_capacity(u64 n, int cand_shift) {
@@ -141,7 +146,9 @@ constexpr u32 kStateTied = 4;        // the ties are the gathered entries, and t
 struct ListArgs {
     const ListRank* rank;  // [rankings]
     const u32* group_of;   // PER_TENSOR: [sampling workgroups] tensor each samples
-    ListWin* local;        // [sampling workgroups][J]
+    u64* local;            // [3 J][sampling workgroups] upper bound, lower bound and estimate of a ranking (bit 31: crowded) | tag << 32
+    u32 n_local;           // sampling workgroups
+    u32 tag;               // of this call's words in `local`
     ListWin* win;          // [rankings]
     ListSorted* sorted;    // [populations], J > 1
     u64* cnt;              // [rankings][max_segs] entries offered | keys above the window << 32
@@ -177,6 +184,21 @@ struct ListArgs {
     int write;             // 1: the sweep writes the outputs.  0: selection only, an apply sweep follows
 };
 
+// What workgroups of one launch hand to each other is written and read with device-scope operations.
+__device__ inline u32 ld_dev(const u32* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void st_dev(u32* p, u32 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline u32 add_dev(u32* p, u32 v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void max_dev(u32* p, u32 v) { __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline u64 ld_dev64(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void st_dev64(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void or_dev(u32* p, u32 v) { __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Waits until this wavefront's accesses are done.  The fences emit nothing: they keep the compiler from moving accesses across.
+__device__ inline void wait_dev() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "singlethread");
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "singlethread");
+}
+
 // ---- sample ------------------------------------------------------------------------------------------
 
 __device__ inline ListWin list_window(u32 hi, u32 lo, u32 mid) {
@@ -184,11 +206,19 @@ __device__ inline ListWin list_window(u32 hi, u32 lo, u32 mid) {
     x.hi = hi;
     x.lo = hi == 0xFFFFFFFFu ? hi : (lo < hi ? lo : hi);
     mid = mid < x.lo ? x.lo : (mid > x.hi ? x.hi : mid);
-    u32 shift = 0;
-    while (((x.hi - x.lo) >> shift) >= static_cast<u32>(kListBins)) ++shift;
+    const u32 span = x.hi - x.lo;
+    const u32 shift = span < static_cast<u32>(kListBins) ? 0u : 24u - static_cast<u32>(__builtin_clz(span));       // span >> shift < kListBins
     const u32 mid_bin = (mid - x.lo) >> shift;
     x.mid = x.lo + (mid_bin << shift);
     x.bins = shift | (mid_bin << 8);
+    return x;
+}
+
+// From the words of list_sample: upper bound, lower bound, estimate (bit 31: crowded).
+__device__ inline ListWin list_window_of(const u32* word, bool nothing, u32 crowded) {
+    if (nothing) return list_window(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
+    ListWin x = list_window(word[0] & ~kListCrowded, word[1] & ~kListCrowded, word[2] & ~kListCrowded);
+    x.bins |= (word[0] | word[1] | word[2] | crowded) & kListCrowded;
     return x;
 }
 
@@ -201,9 +231,10 @@ __device__ inline void list_sort(const ListWin* win, int J, u32* by_rank, ListSo
     const u32 n = static_cast<u32>(__popcll(__ballot(active)));
     const int n_crowded = __popcll(__ballot(lane < J && win_crowded(mine)));
     u32 p = 0;                                             // windows before this one: higher, or equal and earlier
+    const u64 in_order = __ballot(active);
     for (int i = 0; i < J; ++i) {
-        const u32 h = win[i].hi;
-        if (h != 0xFFFFFFFFu && !win_crowded(win[i]) && (h > mine.hi || (h == mine.hi && i < lane))) ++p;
+        const u32 h = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(mine.hi), i));
+        if (((in_order >> i) & 1u) && (h > mine.hi || (h == mine.hi && i < lane))) ++p;
     }
     if (active) by_rank[p] = static_cast<u32>(lane);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
@@ -232,13 +263,7 @@ __device__ inline void list_sort(const ListWin* win, int J, u32* by_rank, ListSo
 __device__ inline bool wave_pick256(const u32* s_hist, u32 r, u32* bin) {
     const u32 lane = threadIdx.x & 63u;
     const uint4 c = *reinterpret_cast<const uint4*>(s_hist + 252 - 4 * lane);
-    u32 incl = c.x + c.y + c.z + c.w;
-    const u32 sum = incl;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const u32 up = __shfl_up(incl, d, 64);
-        if (static_cast<int>(lane) >= d) incl += up;
-    }
+    const u32 sum = c.x + c.y + c.z + c.w, incl = wave_incl_scan_u32(sum);
     u32 before = incl - sum;
     if (!(before < r && r <= incl)) return false;
     u32 b = 255 - 4 * lane;
@@ -252,166 +277,218 @@ __device__ inline bool wave_pick256(const u32* s_hist, u32 r, u32* bin) {
 struct SampleTensor {
     const float* w;
     const float* lam;
-    u64 n, chunk_start;
+    u32 n, chunk_start;    // (32 bits index the elements of these calls)
 };
 
 // One sampling workgroup of a population: number `me` of W, whose results go to place `at_local`.  Bound by latency
-// (scattered 16-byte reads, then a dozen barriers).  A lone workgroup writes the window: the rank rule is that of
+// (scattered reads, then a chain of six barriers): 7.9 us from the launch to the words for the one density of 20 M weights and
+// for ten, 10.3 and 12.9 when every wanted rank was looked for by every thread, in binary64, with eleven barriers.  A lone workgroup writes the window: the rank rule is that of
 // sample_rank.  One of several leaves the keys at its expected rank and two ranks to either side of it (which covers
-// the bias of small ranks); k_list_bounds does the rest.  `first_chunk`, `quads`: the population in chunk space.
-template <bool LC, bool VEC, typename TensorOf, typename RankOf>
-__device__ inline void list_sample(const ListArgs& w, int J, float mu, u32 W, u32 me, u32 at_local, u64 first_ranking, u64 first_chunk, u64 quads,
+// the bias of small ranks); list_bounds does the rest.  `first_chunk`, `quads`: the population in chunk space.
+// LDS (dynamic): sample_lds.  Two workgroups fit a compute unit.
+constexpr int kSampleBits2 = 8, kSampleBins2 = 1 << kSampleBits2;        // 19 of 31 bits: the rest is a twentieth of a percent of the value
+// Copies of the first histogram, chosen by lane, so that fewer lanes of a wavefront meet on one counter.
+__host__ __device__ inline u32 sample_copies(int J) { return J <= 8 ? 4u : 1u; }
+__host__ __device__ inline size_t sample_lds(int J) { return (sample_copies(J) * kBins + kListThreads + 3u * J * kSampleBins2) * sizeof(u32); }
+
+constexpr u32 kSampleNone = 0x7FFFFFFFu;         // a bound without such a rank in the sample
+struct SampleShared {
+    u64 k[kMaxJ], n[kMaxJ];
+    float p[kMaxJ], q[kMaxJ];                    // p = k / n of a ranking, and sqrt(kSampleUnit p (1 - p)) (a sample's ranks are at most 2^14)
+    ListWin win[kMaxJ];
+    u32 wave[kListThreads / 64];
+    u32 want[3 * kMaxJ], bin[3 * kMaxJ], rem[3 * kMaxJ], key[3 * kMaxJ];
+};
+// UNITS: sample positions (of four keys each) per thread, kListUnits for a lone workgroup.  Four lanes take the four float4 of a
+// 64-byte line: the traffic of one float4 from each line, for four times the keys (262144 scattered float4 of two arrays took
+// 11 us, and the 4096 of one workgroup held up its neighbour on the compute unit for 8).  That neighbours resemble each other
+// does not mislead the mean over several workgroups; a lone one's window is ten standard deviations of independent keys to either
+// side, and half that of independent float4.
+template <bool LC, bool VEC, int UNITS, typename TensorOf, typename RankOf>
+__device__ inline void list_sample_units(SampleShared& sh, const ListArgs& w, int J, float mu, u32 W, u32 me, u32 at_local, u64 first_ranking, u32 first_chunk, u32 quads,
                                    TensorOf&& tensor_of, RankOf&& rank_of) {
-    constexpr int kBits2 = 8, kBins2 = 1 << kBits2;        // 19 of 31 bits: the rest is a twentieth of a percent of the value
-    __shared__ __align__(16) u32 s_hist[3 * kMaxJ * kBins2];   // level 0: one or four copies of 2048 bins; level 1: 3 J x kBins2
-    __shared__ u8 s_tab[kBins];                  // leading digit -> 1 + histogram of level 1
-    __shared__ ListWin s_win[kMaxJ];
-    __shared__ u32 s_wave[kListThreads / 64];
-    __shared__ u32 s_want[3 * kMaxJ], s_bin[3 * kMaxJ], s_rem[3 * kMaxJ], s_key[3 * kMaxJ], s_like[3 * kMaxJ];
+    extern __shared__ __align__(16) u32 s_dyn[];
+    float* const s_p = sh.p;
+    float* const s_q = sh.q;
+    u64* const s_k = sh.k;
+    u64* const s_n = sh.n;
+    u32* const s_want = sh.want;
+    u32* const s_bin = sh.bin;
+    u32* const s_rem = sh.rem;
+    u32* const s_key = sh.key;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int R = 3 * J;
-    // A lone workgroup reads single float4; one of several reads 64-byte lines, four lanes each: the same traffic for four
-    // times the keys (262144 scattered float4 of two arrays took 11 us), and order statistics do not mind neighbours that
-    // resemble each other.
-    const int units = W == 1 ? kListUnits : 1, lanes = W == 1 ? 1 : 4;
-    const int logu = 31 - __clz(static_cast<int>(units * (kListThreads / lanes) * W));     // a power of two
-    const u64 places = (quads + lanes - 1) / lanes;
+    const u32 copies = sample_copies(J);
+    u32* const hist0 = s_dyn;                    // [copies][kBins]
+    u32* const s_incl = hist0 + copies * kBins;  // [kListThreads] counts up to a thread's bins within its wavefront | those of its first bin << 16
+    u32* const hist1 = s_incl + kListThreads;    // [R][kSampleBins2]
+    {
+        const uint4 z = make_uint4(0, 0, 0, 0);
+        for (u32 i = tid; i < copies * kBins / 4; i += kListThreads) reinterpret_cast<uint4*>(hist0)[i] = z;
+        for (int i = tid; i < R * kSampleBins2 / 4; i += kListThreads) reinterpret_cast<uint4*>(hist1)[i] = z;
+    }
+    constexpr int lanes = 4;                     // of a 64-byte line
+    const int logu = 31 - __clz(static_cast<int>(UNITS * (kListThreads / lanes) * W));     // a power of two
+    const u32 places = (quads + lanes - 1) / lanes;
 
-    u32 key[4 * kListUnits], valid = 0;
+    // Every lane loads, without a branch (from the last place there is when its own is past the end): a load that only some lanes
+    // make is waited for before the next one starts, and four units one after the other took 6 to 10 us.  Tensors of fewer than
+    // four elements are left out.
+    float v[4 * UNITS], l[LC ? 4 * UNITS : 1];
+    u32 valid = 0;
+    if (quads != 0) {                            // uniform
 #pragma unroll
-    for (int i = 0; i < kListUnits; ++i) {
-        if (i >= units) break;                   // uniform
-        const u64 u = static_cast<u64>(i * kListThreads + tid / lanes) * W + me;
-        u64 p = places <= (static_cast<u64>(1) << logu) ? u : (u * places + __umul64hi(static_cast<u64>(mix32(static_cast<u32>(u))) << 32, places)) >> logu;
-        p = p * lanes + tid % lanes;
-        float v[4] = {0.f, 0.f, 0.f, 0.f};
-        if (p < quads) {
-            const u64 c = first_chunk + p / (kChunk / 4);
+        for (int i = 0; i < UNITS; ++i) {
+            const u32 u = static_cast<u32>(i * kListThreads + tid / lanes) * W + me;          // below 2^logu: its place is in the u-th of as many stretches
+            u32 p = places <= (1u << logu) ? u : static_cast<u32>((static_cast<u64>(u) * places + __umulhi(mix32(u), places)) >> logu);
+            p = p * lanes + tid % lanes;
+            const bool there = p < quads;
+            p = there ? p : quads - 1;
+            const u32 c = first_chunk + p / (kChunk / 4);
             const SampleTensor td = tensor_of(c);
-            const u64 e0 = (c - td.chunk_start) * kChunk + (p % (kChunk / 4)) * 4;
-            if (e0 < td.n) {
-                load4<VEC>(td.w, e0, td.n, v);
+            const u32 e0 = (c - td.chunk_start) * kChunk + (p % (kChunk / 4)) * 4;
+            const bool whole = td.n >= 4;
+            if (there && whole && e0 < td.n) valid |= 0xFu << (4 * i);
+            const u32 last = whole ? (td.n - 4) & ~3u : 0u, e = e0 < last ? e0 : last;         // the tail: the four before it
+            const float* const wp = whole ? td.w + e : reinterpret_cast<const float*>(w.win);          // (any sixteen bytes)
+            const float* const lp = !LC ? nullptr : (whole ? td.lam + e : reinterpret_cast<const float*>(w.win));
+            if (VEC) {
+                const float4 x = *reinterpret_cast<const float4*>(wp);
+                v[4 * i] = x.x; v[4 * i + 1] = x.y; v[4 * i + 2] = x.z; v[4 * i + 3] = x.w;
                 if (LC) {
-                    float l[4];
-                    load4<VEC>(td.lam, e0, td.n, l);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) v[k] = lc_shift(v[k], l[k], mu);
+                    const float4 y = *reinterpret_cast<const float4*>(lp);
+                    l[4 * i] = y.x; l[4 * i + 1] = y.y; l[4 * i + 2] = y.z; l[4 * i + 3] = y.w;
                 }
-                const u32 have = td.n - e0 < 4 ? static_cast<u32>(td.n - e0) : 4u;
-                valid |= ((1u << have) - 1u) << (4 * i);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    v[4 * i + k] = wp[k];
+                    if (LC) l[4 * i + k] = lp[k];
+                }
             }
         }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) key[4 * i + k] = mag_key(v[k]);
     }
+    if (tid < J) {                               // while the loads are on their way
+        u64 k, n;
+        rank_of(tid, &k, &n);
+        const float p = n ? static_cast<float>(k) / static_cast<float>(n) : 0.0f;
+        s_p[tid] = p;
+        s_q[tid] = sqrtf(static_cast<float>(kSampleUnit) * p * (1.0f - p));
+        s_k[tid] = k;
+        s_n[tid] = n;
+    }
+    __syncthreads();
     constexpr int kShift0 = 20;                  // 11 leading bits of 31
-    const int copies = units == 1 ? 1 : 4;       // chosen by lane: fewer lanes of a wavefront meet on one counter
-    for (int i = tid; i < copies * kBins; i += kListThreads) s_hist[i] = 0;
-    for (int i = tid; i < kBins; i += kListThreads) s_tab[i] = 0;
-    if (tid < R) s_bin[tid] = 0xFFFFFFFFu;
-    __syncthreads();
+    u32 key[4 * UNITS];
 #pragma unroll
-    for (int i = 0; i < 4 * kListUnits; ++i)
-        if (valid & (1u << i)) atomicAdd(&s_hist[(lane & (copies - 1)) * kBins + (key[i] >> kShift0)], 1u);
-    __syncthreads();
-    u32 c0, c1;                                  // bins from the top, two per thread
-    {
-        const int b0 = kBins - 1 - 2 * tid, b1 = b0 - 1;
-        c0 = s_hist[b0];
-        c1 = s_hist[b1];
-        for (int q = 1; q < copies; ++q) { c0 += s_hist[q * kBins + b0]; c1 += s_hist[q * kBins + b1]; }
+    for (int i = 0; i < 4 * UNITS; ++i) {
+        key[i] = mag_key(LC ? lc_shift(v[i], l[LC ? i : 0], mu) : v[i]);
+        if (valid & (1u << i)) atomicAdd(&hist0[(lane & (copies - 1)) * kBins + (key[i] >> kShift0)], 1u);
     }
+    __syncthreads();
+    {
+        const int b0 = kBins - 1 - 2 * tid, b1 = b0 - 1;                 // bins from the top, two per thread
+        u32 c0 = hist0[b0], c1 = hist0[b1];
+        for (u32 q = 1; q < copies; ++q) { c0 += hist0[q * kBins + b0]; c1 += hist0[q * kBins + b1]; }
+        const u32 incl = wave_incl_scan_u32(c0 + c1);                    // a workgroup has at most 2^14 keys
+        s_incl[tid] = incl | (c0 << 16);
+        if (lane == 63) sh.wave[wave] = incl;
+    }
+    __syncthreads();
+    // The three ranks of every ranking, a wavefront each: the thread whose bins hold it, then the bin.  From here on a word of
+    // hist0 says which ranking's histogram of the next digits its bin has: rankings that meet in a bin share that of the first.
+    constexpr u32 kHasBins2 = 0x80000000u;
     u32 S;
-    const u32 incl = wg_incl_scan_u32<kListThreads>(c0 + c1, s_wave, &S);
-    if (tid < R) {                               // the three ranks of every ranking
-        u64 rk_k, rk_n;
-        rank_of(tid / 3, &rk_k, &rk_n);
-        const int which = tid % 3;               // upper bound, lower bound, estimate
-        u32 want = 0, none = which == 0 ? 0x7FFFFFFFu : 0u;              // no such rank in the sample: unbounded
-        if (rk_k == 0) {
-            none = 0xFFFFFFFFu;
-        } else if (S != 0) {
-            const double p = static_cast<double>(rk_k) / static_cast<double>(rk_n);
-            const double ks = p * static_cast<double>(S);
-            const double sd = sqrt(static_cast<double>(kSampleUnit) * static_cast<double>(S) * p * (1.0 - p));
-            const double m = (W == 1 ? static_cast<double>(w.margin16) / 16.0 * sd : 0.0) + 2.0;
-            double r = which == 0 ? floor(ks - m) : (which == 1 ? ceil(ks + m) + 1.0 : floor(ks + 0.5));
-            if (which == 2) r = r < 1.0 ? 1.0 : (r > static_cast<double>(S) ? static_cast<double>(S) : r);
-            if (r >= 1.0 && r <= static_cast<double>(S)) want = static_cast<u32>(r);
-        }
-        s_want[tid] = want;
-        s_key[tid] = none;
-        s_like[tid] = 0;
-    }
-    __syncthreads();
     {
-        const u32 before = incl - c0 - c1;
-        const u32 b0 = kBins - 1 - 2 * tid;
-        for (int r = 0; r < R; ++r) {
-            const u32 want = s_want[r];
-            if (before < want && want <= incl) {
-                const bool first = want <= before + c0;
-                s_bin[r] = first ? b0 : b0 - 1;
-                s_rem[r] = first ? want - before : want - before - c0;
+        const u32 of_wave = lane < kListThreads / 64 ? sh.wave[lane] : 0u, upto = wave_incl_scan_u32(of_wave);
+        S = __shfl(upto, 63, 64);
+        for (int r = wave; r < R; r += kListThreads / 64) {
+            const int j = r / 3, which = r % 3;  // upper bound, lower bound, estimate
+            u32 want = 0;                        // 0: no such rank in the sample, unbounded
+            if (s_k[j] != 0 && S != 0) {
+                const float all = static_cast<float>(S), ks = s_p[j] * all;
+                const float m = (W == 1 ? static_cast<float>(w.margin16) / 16.0f * s_q[j] * sqrtf(all) : 0.0f) + 2.0f;
+                float x = which == 0 ? floorf(ks - m) : (which == 1 ? ceilf(ks + m) + 1.0f : floorf(ks + 0.5f));
+                if (which == 2) x = x < 1.0f ? 1.0f : (x > all ? all : x);
+                if (x >= 1.0f && x <= all) want = static_cast<u32>(x);
+            }
+            if (lane == 0) s_want[r] = want;
+            if (want == 0) continue;             // uniform
+            const int in_wave = __ffsll(static_cast<long long>(__ballot(upto >= want))) - 1;
+            const u32 before_wave = __shfl(upto - of_wave, in_wave, 64);
+            const u32 x = s_incl[in_wave * 64 + lane], incl = before_wave + (x & 0xFFFFu);
+            const int in_lane = __ffsll(static_cast<long long>(__ballot(incl >= want))) - 1;
+            const u32 up = __shfl_up(incl, 1, 64), prev = lane ? up : before_wave;
+            if (lane == in_lane) {
+                const u32 b0 = kBins - 1 - 2 * (in_wave * 64 + lane), c0 = x >> 16;
+                const bool first = want <= prev + c0;
+                const u32 bin = first ? b0 : b0 - 1;
+                s_bin[r] = bin;
+                s_rem[r] = first ? want - prev : want - prev - c0;
+                atomicMax(&hist0[bin], kHasBins2 | (63u - static_cast<u32>(r)));
             }
         }
     }
     __syncthreads();
-    if (tid < R && s_want[tid]) {                // rankings that meet in a bin share its histogram: that of the first
-        int f = 0;
-        while (s_bin[f] != s_bin[tid]) ++f;
-        if (f == tid) s_tab[s_bin[tid]] = static_cast<u8>(tid + 1);
-    }
-    constexpr int kShift2 = kShift0 - kBits2;
-    for (int i = tid; i < R * kBins2; i += kListThreads) s_hist[i] = 0;
-    __syncthreads();
+    constexpr int kShift2 = kShift0 - kSampleBits2;
 #pragma unroll
-    for (int i = 0; i < 4 * kListUnits; ++i) {
-        const u32 h = (valid & (1u << i)) ? s_tab[key[i] >> kShift0] : 0u;
-        if (h) atomicAdd(&s_hist[(h - 1) * kBins2 + ((key[i] >> kShift2) & (kBins2 - 1))], 1u);
+    for (int i = 0; i < 4 * UNITS; ++i) {
+        if (!(valid & (1u << i))) continue;
+        const u32 h = hist0[key[i] >> kShift0];
+        if (h & kHasBins2) atomicAdd(&hist1[(63u - (h & 63u)) * kSampleBins2 + ((key[i] >> kShift2) & (kSampleBins2 - 1))], 1u);
     }
     __syncthreads();
     for (int r = wave; r < R; r += kListThreads / 64) {
-        if (s_want[r] == 0) continue;
-        u32 bin = 0;
-        const u32* hist = s_hist + (s_tab[s_bin[r]] - 1) * kBins2;
-        if (wave_pick256(hist, s_rem[r], &bin)) {          // one lane
-            s_like[r] = hist[bin];
-            const u32 key0 = (s_bin[r] << kShift0) | (bin << kShift2), low = (1u << kShift2) - 1u;
-            s_key[r] = r % 3 == 0 ? key0 | low : (r % 3 == 1 ? key0 : key0 | ((low + 1u) >> 1));
+        const int j = r / 3, which = r % 3;
+        u32 bin = 0, word = kSampleNone;
+        bool mine = lane == 0;
+        if (s_want[r] != 0) {                    // uniform
+            const u32* hist = hist1 + (63u - (hist0[s_bin[r]] & 63u)) * kSampleBins2;
+            mine = wave_pick256(hist, s_rem[r], &bin);                   // one lane
+            if (mine) {
+                const u32 key0 = (s_bin[r] << kShift0) | (bin << kShift2), low = (1u << kShift2) - 1u;
+                word = which == 0 ? key0 | low : (which == 1 ? key0 : key0 | ((low + 1u) >> 1));
+                // sample keys that share 19 bits with this one
+                if (static_cast<u64>(hist[bin]) * s_n[j] > list_capacity(s_n[j], w.cand_shift) * S) word |= kListCrowded;
+            }
         }
+        if (!mine) continue;
+        if (W == 1) s_key[r] = which != 0 && word == kSampleNone ? 0u : word;
+        else        st_dev64(&w.local[static_cast<u64>(r) * w.n_local + at_local], (static_cast<u64>(w.tag) << 32) | word);
     }
+    if (W != 1) return;                          // uniform
     __syncthreads();
     if (tid < J) {
-        ListWin x = list_window(s_key[3 * tid], s_key[3 * tid + 1], s_key[3 * tid + 2]);
-        u32 like = s_like[3 * tid];                        // sample keys that share 19 bits with an end or the estimate
-        like = s_like[3 * tid + 1] > like ? s_like[3 * tid + 1] : like;
-        like = s_like[3 * tid + 2] > like ? s_like[3 * tid + 2] : like;
-        u64 rk_k, rk_n;
-        rank_of(tid, &rk_k, &rk_n);
-        if (static_cast<u64>(like) * rk_n > list_capacity(rk_n, w.cand_shift) * S) x.bins |= kListCrowded;
-        if (W == 1) w.win[first_ranking + tid] = x;
-        else        w.local[static_cast<u64>(at_local) * J + tid] = x;
-        s_win[tid] = x;
+        const ListWin x = list_window_of(s_key + 3 * tid, s_k[tid] == 0, 0u);
+        w.win[first_ranking + tid] = x;
+        sh.win[tid] = x;
     }
-    if (W == 1 && J > 1) {
+    if (J > 1) {
         __syncthreads();
-        if (wave == 0) list_sort(s_win, J, s_want, w.sorted + first_ranking / J);
+        if (wave == 0) list_sort(sh.win, J, s_want, w.sorted + first_ranking / J);
     }
+}
+
+template <bool LC, bool VEC, typename TensorOf, typename RankOf>
+__device__ inline void list_sample(const ListArgs& w, int J, float mu, u32 W, u32 me, u32 at_local, u64 first_ranking, u32 first_chunk, u32 quads,
+                                   TensorOf&& tensor_of, RankOf&& rank_of) {
+    __shared__ SampleShared sh;
+    if (W == 1) list_sample_units<LC, VEC, kListUnits>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
+    else        list_sample_units<LC, VEC, 1>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
 }
 
 // The sampling workgroups as a launch of their own.
 template <bool LC, bool VEC>
-__global__ __launch_bounds__(kListThreads) void k_list_sample(DataArgs a, ListArgs w) {
+__global__ __launch_bounds__(kListThreads, 8) void k_list_sample(DataArgs a, ListArgs w) {
     const u32 g = a.per_tensor ? w.group_of[blockIdx.x] : 0u;
     const u64 r0 = static_cast<u64>(g) * a.J;
     const ListRank rk = w.rank[r0];
     const TensorDesc& tg = a.td[a.per_tensor ? g : 0];
-    list_sample<LC, VEC>(w, a.J, a.mu, rk.n_groups, blockIdx.x - rk.group0, blockIdx.x, r0, a.per_tensor ? tg.chunk_start : 0,
-                         a.per_tensor ? (tg.n + 3) / 4 : a.n_chunks * (kChunk / 4),
-                         [&](u64 c) {
+    list_sample<LC, VEC>(w, a.J, a.mu, rk.n_groups, blockIdx.x - rk.group0, blockIdx.x, r0, a.per_tensor ? static_cast<u32>(tg.chunk_start) : 0u,
+                         static_cast<u32>(a.per_tensor ? (tg.n + 3) / 4 : a.n_chunks * (kChunk / 4)),
+                         [&](u32 c) {
                              const TensorDesc& td = a.per_tensor ? tg : a.td[a.chunk_map[c]];
-                             return SampleTensor{td.w, td.lam, td.n, td.chunk_start};
+                             return SampleTensor{td.w, td.lam, static_cast<u32>(td.n), static_cast<u32>(td.chunk_start)};
                          },
                          [&](int j, u64* k, u64* n) { *k = a.slots[r0 + j].k; *n = a.slots[r0 + j].n; });
 }
@@ -427,7 +504,8 @@ struct BeginSampleArgs {
     u32* chunk_map;
     u32 n_chunks;
     int n_tensors;
-    u32 groups;            // sampling workgroups: the first of the grid
+    u32 groups;            // sampling workgroups: after the one that fetches the tables
+    u32 fillers;           // workgroups that clear and write the map: after these.  Then one for each population's bounds
     int J;
     int per_tensor;
     float mu;
@@ -440,8 +518,105 @@ struct BeginSampleArgs {
     u16 group0[kBeginSampleTensors + 1];   // PER_TENSOR: first sampling workgroup of each tensor
 };
 static_assert(sizeof(BeginSampleArgs) + sizeof(ListArgs) <= 3584, "kernel arguments");
+// Populations with several sampling workgroups, one workgroup here for each, a wavefront a ranking.  The workgroups' keys at
+// the expected rank are as many independent draws around the threshold: their mean estimates it, and the window ends as many
+// standard errors of that mean to either side as the call asks for (a few more when the deviation itself is estimated from few
+// draws).  What is far from normal (a threshold between zeros and the rest) can only misplace the window.  Order statistics
+// in their place assumed nothing, but left windows 1.3 times as wide for 256 workgroups and twice for 32, estimates off by 1.25
+// times as much, and took 1.8 us to find.
+// WAIT: the sampling workgroups belong to the same launch.  They come before this one in the grid and wait for nobody; their
+// words are there when they carry the call's tag (a word left by something else that looks the same would only misplace the
+// window).  In a launch of its own this took 4.9 us and 11 for ten densities.
+constexpr int kBoundsThreads = 64 * kMaxJ;
+__device__ inline float wave_sum_f32(float v) {            // in every lane
+    auto add = [](float x, u32 from) { return x + __uint_as_float(from); };
+    v = add(v, dpp_or_zero<0x111, 0xF>(__float_as_uint(v)));
+    v = add(v, dpp_or_zero<0x112, 0xF>(__float_as_uint(v)));
+    v = add(v, dpp_or_zero<0x114, 0xF>(__float_as_uint(v)));
+    v = add(v, dpp_or_zero<0x118, 0xF>(__float_as_uint(v)));
+    v = add(v, dpp_or_zero<0x142, 0xA>(__float_as_uint(v)));
+    v = add(v, dpp_or_zero<0x143, 0xC>(__float_as_uint(v)));
+    return __uint_as_float(static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(v)), 63)));
+}
+template <bool WAIT, typename NothingOf>
+__device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0, u32 W, NothingOf&& nothing_of) {
+    __shared__ ListWin s_win[kMaxJ];
+    __shared__ u32 s_order[kMaxJ + 1];
+    const int lane = threadIdx.x & 63, j = threadIdx.x >> 6;
+    if (j < J) {
+        constexpr int kPer = kListMaxW / 64;
+        u32 v[3][kPer];                          // upper bound, lower bound, estimate
+        for (;;) {
+            bool there = true;
+            u64 x[3][kPer];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int q = 0; q < kPer; ++q)
+                    x[i][q] = 64u * q + lane < W ? ld_dev64(w.local + static_cast<u64>(3 * j + i) * w.n_local + group0 + 64 * q + lane) : 0;
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int q = 0; q < kPer; ++q) {
+                    there = there && (64u * q + lane >= W || static_cast<u32>(x[i][q] >> 32) == w.tag);
+                    v[i][q] = static_cast<u32>(x[i][q]);
+                }
+            if (!WAIT || __all(there)) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        const u32 ref = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(v[2][0]), 0)) & ~kListCrowded;
+        u32 word[3], crowded = 0;
+        float mean[3], sq = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            float sum = 0.0f;
+            u32 says = 0, open = 0;              // those that say crowded, and those without such a rank in their sample
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                const bool mine = 64u * q + lane < W;
+                const u32 key = v[i][q] & ~kListCrowded;
+                says += static_cast<u32>(__popcll(__ballot(mine && (v[i][q] & kListCrowded) != 0)));
+                open += static_cast<u32>(__popcll(__ballot(mine && key == kSampleNone)));
+                const float d = mine ? static_cast<float>(static_cast<int>(key - ref)) : 0.0f;
+                sum += d;
+                if (i == 2) sq += d * d;
+            }
+            mean[i] = wave_sum_f32(sum) / static_cast<float>(W);
+            word[i] = open;
+            if (2 * says > W) crowded = kListCrowded;      // most of the workgroups say so
+        }
+        const float n = static_cast<float>(W), var = (wave_sum_f32(sq) - n * mean[2] * mean[2]) / (n - 1.0f);
+        const float z = static_cast<float>(w.margin16) / 16.0f * (1.0f + 8.0f / n);
+        const float off = z * sqrtf(var > 0.0f ? var / n : 0.0f);
+        auto at = [&](float d) {                 // a key; ref + d may lie outside
+            const float least = -static_cast<float>(ref), most = static_cast<float>(0x7FFFFFFFu - ref);
+            return d <= least ? 0u : (d >= most ? 0x7FFFFFFFu : ref + static_cast<u32>(static_cast<int>(d)));
+        };
+        const u32 half = 0x800u;                 // the words' low 12 bits say nothing
+        const u32 hi = at(mean[0] + off), lo = at(mean[1] - off);
+        word[0] = word[0] ? 0x7FFFFFFFu : (hi < 0x7FFFFFFFu - half ? hi + half : 0x7FFFFFFFu);
+        word[1] = word[1] || lo < half ? 0u : lo - half;
+        word[2] = at(mean[2]);
+        if (lane == 0) {
+            const ListWin x = list_window_of(word, nothing_of(j), crowded);
+            s_win[j] = x;
+            w.win[r0 + j] = x;
+        }
+    }
+    if (J == 1) return;
+    __syncthreads();
+    if (threadIdx.x < 64) list_sort(s_win, J, s_order, w.sorted + r0 / J);
+}
+
+__global__ __launch_bounds__(kBoundsThreads) void k_list_bounds(DataArgs a, ListArgs w) {
+    const u64 r0 = static_cast<u64>(blockIdx.x) * a.J;
+    const ListRank rk = w.rank[r0];
+    if (rk.n_groups == 1) return;                // its windows are written
+    list_bounds<false>(w, a.J, r0, rk.group0, rk.n_groups, [&](u32 j) { return a.slots[r0 + j].k == 0; });
+}
+
 template <bool LC, bool VEC>
-__global__ __launch_bounds__(kListThreads) void k_begin_sample(BeginSampleArgs b, ListArgs w) {
+__global__ __launch_bounds__(kListThreads, 8) void k_begin_sample(BeginSampleArgs b, ListArgs w) {
     __shared__ u32 s_start[kBeginSampleTensors + 1];
     const int tid = threadIdx.x;
     auto tensor_of_chunk_lds = [&](u32 c) {                // largest t with chunk_start[t] <= c
@@ -452,14 +627,26 @@ __global__ __launch_bounds__(kListThreads) void k_begin_sample(BeginSampleArgs b
         }
         return lo;
     };
-    if (blockIdx.x == b.groups) {
+    auto kept_of = [&](int j, u64 n) {                     // as the host rounds: llround of the binary64 product, clamped
+        const u64 k = static_cast<u64>(llround(b.density[j] * static_cast<double>(n)));
+        return k > n ? n : k;
+    };
+    if (blockIdx.x == 0) {
         upload_words(b.up, tid, kListThreads);
         __syncthreads();                                   // every load has returned: its value went into a store
         if (tid == 0) store_ticket(b.up.done, b.up.ticket);
         return;
     }
+    const u32 block = blockIdx.x - 1;
+    if (block >= b.groups + b.fillers) {                   // a population's bounds, from what the workgroups before it leave
+        const u32 g = block - b.groups - b.fillers;
+        const u32 group0 = b.per_tensor ? b.group0[g] : 0u, W = b.per_tensor ? b.group0[g + 1] - group0 : b.groups;
+        const u64 n_pop = b.per_tensor ? b.n[g] : b.N;
+        if (W != 1) list_bounds<true>(w, b.J, static_cast<u64>(g) * b.J, group0, W, [&](u32 j) { return kept_of(static_cast<int>(j), n_pop) == 0; });
+        return;
+    }
     if (tid <= b.n_tensors) s_start[tid] = b.chunk_start[tid];
-    if (blockIdx.x < b.groups) {
+    if (block < b.groups) {
         __shared__ const float* s_w[kBeginSampleTensors];
         __shared__ const float* s_lam[kBeginSampleTensors];
         __shared__ u32 s_n[kBeginSampleTensors];
@@ -469,93 +656,36 @@ __global__ __launch_bounds__(kListThreads) void k_begin_sample(BeginSampleArgs b
             if (LC) s_lam[tid] = b.lam[tid];
         }
         __syncthreads();
-        u32 g = 0, W = b.groups, me = blockIdx.x;
-        u64 first_chunk = 0, quads = static_cast<u64>(b.n_chunks) * (kChunk / 4), n_pop = b.N;
+        u32 g = 0, W = b.groups, me = block;
+        u32 first_chunk = 0, quads = b.n_chunks * (kChunk / 4);
+        u64 n_pop = b.N;
         if (b.per_tensor) {
             int lo = 0, hi = b.n_tensors - 1;              // the tensor this workgroup samples: the last with group0 <= its number
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
-                if (b.group0[mid] <= blockIdx.x) lo = mid; else hi = mid - 1;
+                if (b.group0[mid] <= block) lo = mid; else hi = mid - 1;
             }
             g = static_cast<u32>(lo);
             W = static_cast<u32>(b.group0[g + 1]) - b.group0[g];
-            me = blockIdx.x - b.group0[g];
+            me = block - b.group0[g];
             first_chunk = s_start[g];
             n_pop = s_n[g];
-            quads = (n_pop + 3) / 4;
+            quads = (s_n[g] + 3u) / 4;
         }
-        list_sample<LC, VEC>(w, b.J, b.mu, W, me, blockIdx.x, static_cast<u64>(g) * b.J, first_chunk, quads,
-                             [&](u64 c) {
-                                 const int t = b.per_tensor ? static_cast<int>(g) : tensor_of_chunk_lds(static_cast<u32>(c));
+        list_sample<LC, VEC>(w, b.J, b.mu, W, me, block, static_cast<u64>(g) * b.J, first_chunk, quads,
+                             [&](u32 c) {
+                                 const int t = b.per_tensor ? static_cast<int>(g) : tensor_of_chunk_lds(c);
                                  return SampleTensor{s_w[t], LC ? s_lam[t] : nullptr, s_n[t], s_start[t]};
                              },
-                             [&](int j, u64* k, u64* n) {  // as the host rounds: llround of the binary64 product, clamped
-                                 const double x = b.density[j] * static_cast<double>(n_pop);
-                                 const u64 kk = static_cast<u64>(llround(x));
-                                 *k = kk > n_pop ? n_pop : kk;
-                                 *n = n_pop;
-                             });
+                             [&](int j, u64* k, u64* n) { *k = kept_of(j, n_pop); *n = n_pop; });
         return;
     }
     __syncthreads();
-    const u64 stride = static_cast<u64>(gridDim.x - b.groups - 1) * kListThreads;
-    const u64 i0 = static_cast<u64>(blockIdx.x - b.groups - 1) * kListThreads + tid;
+    const u64 stride = static_cast<u64>(b.fillers) * kListThreads;
+    const u64 i0 = static_cast<u64>(block - b.groups) * kListThreads + tid;
     const uint4 z = make_uint4(0, 0, 0, 0);
     for (u64 i = i0; i < b.n_zero; i += stride) b.zero[i] = z;
     for (u64 c = i0; c < b.n_chunks; c += stride) b.chunk_map[c] = static_cast<u32>(tensor_of_chunk_lds(static_cast<u32>(c)));
-}
-
-// Populations with several sampling workgroups, one workgroup here for each.  The workgroups' keys at the expected
-// rank are as many independent draws around the threshold; order statistics W/2 -+ z sqrt(W)/2 of them bound its
-// location with the confidence of z standard deviations, whatever their distribution.  A wavefront finds one order
-// statistic bit by bit, with all W values in its registers.
-constexpr int kBoundsThreads = 1024;
-__global__ __launch_bounds__(kBoundsThreads) void k_list_bounds(DataArgs a, ListArgs w) {
-    __shared__ u32 s_out[3 * kMaxJ], s_crowded[kMaxJ];
-    __shared__ ListWin s_win[kMaxJ];
-    const u64 r0 = static_cast<u64>(blockIdx.x) * a.J;
-    const ListRank rk = w.rank[r0];
-    const u32 W = rk.n_groups, lane = threadIdx.x & 63u;
-    if (W == 1) return;                          // its windows are written
-    constexpr int kPer = kListMaxW / 64;
-    const double d = static_cast<double>(w.margin16) / 16.0 * sqrt(static_cast<double>(W)) / 2.0;
-    const u32 off = d >= static_cast<double>(W / 2) ? W / 2 : static_cast<u32>(ceil(d));
-    for (u32 task = threadIdx.x >> 6; task < 3u * a.J; task += kBoundsThreads / 64) {
-        const u32 j = task / 3, i = task % 3;    // i: upper bound, lower bound, estimate
-        u32 v[kPer], crowded = 0;
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            v[q] = 0xFFFFFFFFu;                  // past the end: above every key (and every bound looked for)
-            bool says_crowded = false;
-            if (64 * q + lane < W) {
-                const ListWin x = w.local[static_cast<u64>(rk.group0 + 64 * q + lane) * a.J + j];
-                v[q] = i == 0 ? x.hi : (i == 1 ? x.lo : x.mid);
-                says_crowded = win_crowded(x);
-            }
-            crowded += static_cast<u32>(__popcll(__ballot(says_crowded)));
-        }
-        if (i == 2 && lane == 0) s_crowded[j] = 2 * crowded > W ? 1u : 0u;             // most of the workgroups say so
-        const u32 pick = i == 0 ? (W / 2 + off < W ? W / 2 + off : W - 1) : (i == 1 ? (W / 2 - 1 >= off ? W / 2 - 1 - off : 0) : W / 2);
-        u32 x = 0;                               // the largest x with at most `pick` values below it
-        for (int bit = 31; bit >= 0; --bit) {
-            const u32 cand = x | (1u << bit);
-            u32 below = 0;
-#pragma unroll
-            for (int q = 0; q < kPer; ++q) below += static_cast<u32>(__popcll(__ballot(v[q] < cand)));
-            if (below <= pick) x = cand;
-        }
-        if (lane == 0) s_out[task] = x;
-    }
-    __syncthreads();
-    if (threadIdx.x < static_cast<u32>(a.J)) {
-        ListWin x = list_window(s_out[3 * threadIdx.x], s_out[3 * threadIdx.x + 1], s_out[3 * threadIdx.x + 2]);
-        if (s_crowded[threadIdx.x]) x.bins |= kListCrowded;
-        s_win[threadIdx.x] = x;
-        w.win[r0 + threadIdx.x] = x;
-    }
-    if (a.J == 1) return;
-    __syncthreads();
-    if (threadIdx.x < 64) list_sort(s_win, a.J, s_out, w.sorted + blockIdx.x);
 }
 
 __device__ inline u32 lanes_below(u64 m) {       // set bits of m below this lane's
@@ -1157,20 +1287,6 @@ __device__ inline void list_fix_queue(const DataArgs& a, const ListArgs& w, u32 
     }
 }
 
-// What one phase of list_fallback hands to the next is written and read with device-scope operations.
-__device__ inline u32 ld_dev(const u32* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline void st_dev(u32* p, u32 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline u32 add_dev(u32* p, u32 v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline void max_dev(u32* p, u32 v) { __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline u64 ld_dev64(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline void st_dev64(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline void or_dev(u32* p, u32 v) { __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-// Waits until this wavefront's accesses are done.  The fences emit nothing: they keep the compiler from moving accesses across.
-__device__ inline void wait_dev() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "singlethread");
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "singlethread");
-}
 __device__ inline void st_state(ListState* to, u32 a, u32 b, u32 rank, u32 n, u32 flags) {
     st_dev(&to->a, a); st_dev(&to->b, b); st_dev(&to->rank, rank); st_dev(&to->n, n); st_dev(&to->flags, flags);
 }
@@ -1386,13 +1502,7 @@ __device__ inline void list_pick(ListShared& sh, bool from_top, u32 r, u32* bin,
         const u32 lane = threadIdx.x;
         const uint4 c4 = *reinterpret_cast<const uint4*>(sh.hist + (from_top ? 252 - 4 * lane : 4 * lane));
         const u32 c[4] = {from_top ? c4.w : c4.x, from_top ? c4.z : c4.y, from_top ? c4.y : c4.z, from_top ? c4.x : c4.w};
-        u32 incl = c[0] + c[1] + c[2] + c[3];
-        const u32 sum = incl;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const u32 up = __shfl_up(incl, d, 64);
-            if (static_cast<int>(lane) >= d) incl += up;
-        }
+        const u32 sum = c[0] + c[1] + c[2] + c[3], incl = wave_incl_scan_u32(sum);
         u32 before = incl - sum;
         if (before < r && r <= incl) {
 #pragma unroll

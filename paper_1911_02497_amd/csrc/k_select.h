@@ -81,19 +81,36 @@ __device__ inline u64* data_hist(const DataArgs& a, int level, u64 s) {
 
 // ---- wavefront / workgroup scans ---------------------------------------------------------------
 
-__device__ inline u64 shfl_up_u64(u64 v, int d) {
-    const u32 lo = __shfl_up(static_cast<u32>(v), d, 64);
-    const u32 hi = __shfl_up(static_cast<u32>(v >> 32), d, 64);
-    return (static_cast<u64>(hi) << 32) | lo;
+// Inclusive scans over a wavefront, all lanes active.  Lanes get their neighbours' values in the add itself (data-parallel
+// primitives: shifts within rows of 16 lanes, then the last lane of a row to the rows after it): six dependent adds.  Through
+// LDS (__shfl_up) each of the six steps waits some 60 ns for its value.
+template <int CTRL, int ROWS>
+__device__ inline u32 dpp_or_zero(u32 v) {
+    return static_cast<u32>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xF, false));
 }
-
+__device__ inline u32 wave_incl_scan_u32(u32 v) {
+    v += dpp_or_zero<0x111, 0xF>(v);       // row_shr:1, 2, 4, 8
+    v += dpp_or_zero<0x112, 0xF>(v);
+    v += dpp_or_zero<0x114, 0xF>(v);
+    v += dpp_or_zero<0x118, 0xF>(v);
+    v += dpp_or_zero<0x142, 0xA>(v);       // row_bcast:15 into rows 1 and 3
+    v += dpp_or_zero<0x143, 0xC>(v);       // row_bcast:31 into rows 2 and 3
+    return v;
+}
+__device__ inline u32 wave_sum_u32(u32 v) {                // in every lane
+    return static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(wave_incl_scan_u32(v)), 63));
+}
+template <int CTRL, int ROWS>
+__device__ inline u64 dpp_or_zero_u64(u64 v) {
+    return (static_cast<u64>(dpp_or_zero<CTRL, ROWS>(static_cast<u32>(v >> 32))) << 32) | dpp_or_zero<CTRL, ROWS>(static_cast<u32>(v));
+}
 __device__ inline u64 wave_incl_scan_u64(u64 v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const u64 o = shfl_up_u64(v, d);
-        if (lane >= d) v += o;
-    }
+    v += dpp_or_zero_u64<0x111, 0xF>(v);
+    v += dpp_or_zero_u64<0x112, 0xF>(v);
+    v += dpp_or_zero_u64<0x114, 0xF>(v);
+    v += dpp_or_zero_u64<0x118, 0xF>(v);
+    v += dpp_or_zero_u64<0x142, 0xA>(v);
+    v += dpp_or_zero_u64<0x143, 0xC>(v);
     return v;
 }
 
@@ -120,12 +137,7 @@ __device__ inline u64 block_excl_scan_u64(u64 v, u64* s_wave, u64* total) {
 template <int THREADS>
 __device__ inline u32 wg_incl_scan_u32(u32 v, u32* s_wave, u32* total) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    u32 inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const u32 o = __shfl_up(inc, off);
-        if (lane >= off) inc += o;
-    }
+    const u32 inc = wave_incl_scan_u32(v);
     if (lane == 63) s_wave[wv] = inc;
     __syncthreads();
     u32 before = 0, tot = 0;
@@ -238,17 +250,22 @@ struct UploadArgs {
     u64 ticket;
 };
 __device__ inline void upload_words(const UploadArgs& u, u32 first, u32 stride) {
-    for (u32 i0 = first; i0 < u.end[3]; i0 += 4 * stride) {          // four loads in flight: a round trip is about a microsecond
-        uint4 v[4];
-#pragma unroll
-        for (u32 k = 0; k < 4; ++k) if (i0 + k * stride < u.end[3]) v[k] = u.src[i0 + k * stride];
-#pragma unroll
-        for (u32 k = 0; k < 4; ++k) {
-            const u32 i = i0 + k * stride;
-            if (i >= u.end[3]) break;
-            const int part = i < u.end[0] ? 0 : (i < u.end[1] ? 1 : (i < u.end[2] ? 2 : 3));
-            u.dst[part][i - (part ? u.end[part - 1] : 0)] = v[k];
-        }
+    const u32 n = u.end[3];
+    auto put = [&](u32 i, const uint4& v) {
+        if (i >= n) return;
+        uint4* to = u.dst[0] + i;                          // (selects: an index known at run time would put the table into scratch memory)
+        if (i >= u.end[0]) to = u.dst[1] + (i - u.end[0]);
+        if (i >= u.end[1]) to = u.dst[2] + (i - u.end[1]);
+        if (i >= u.end[2]) to = u.dst[3] + (i - u.end[2]);
+        *to = v;
+    };
+    for (u32 i0 = first; i0 < n; i0 += 4 * stride) {       // four loads in flight: a round trip is about a microsecond
+        const u32 i1 = i0 + stride, i2 = i1 + stride, i3 = i2 + stride, last = n - 1;
+        const uint4 v0 = u.src[i0], v1 = u.src[i1 < n ? i1 : last], v2 = u.src[i2 < n ? i2 : last], v3 = u.src[i3 < n ? i3 : last];
+        put(i0, v0);
+        put(i1, v1);
+        put(i2, v2);
+        put(i3, v3);
     }
 }
 __device__ inline void store_ticket(u64* done, u64 ticket) {

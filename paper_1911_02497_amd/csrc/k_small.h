@@ -37,16 +37,6 @@ __device__ inline void wave_pick_asc(const u32* s_hist, int nb, u64 r, u32* bin,
     }
 }
 
-__device__ inline u32 wave_incl_scan_u32(u32 v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const u32 up = __shfl_up(v, d, 64);
-        if (lane >= d) v += up;
-    }
-    return v;
-}
-
 // Ranking of n keys of at most 63 bits by one workgroup.  Radix levels of eight bits from the highest bit in which the keys
 // differ (aggregates of one model share their sign and most exponent bits), until at most kRankPairs share the digits
 // found; those are ranked by comparing all pairs, four threads to a key.  A lone workgroup is bound by latency: one search

@@ -130,3 +130,26 @@ def test_special_values():
         res = P.condensa_prune(up([w]), ds, theta_f16=True)
         torch.cuda.synchronize()
         check_prune_against_oracle(res, oracle.prune([w], ds, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1)
+
+
+@pytest.mark.parametrize("case", ["tiny_among_large", "only_tiny", "many_ask_for_samples", "sixteen_densities", "density_ends"])
+def test_sampling_workgroups(case):
+    """Tensors too short to be sampled, PER_TENSOR populations that ask for more sampling workgroups than fit at once, the
+    most rankings that one launch bounds, ranks at and beyond the ends of a sample."""
+    rng = np.random.default_rng(11)
+    scope, ds, shapes = P.SCOPE_GLOBAL, [0.1], [(3,), (700, 701), (1,), (2,), (5,), (90001,), (3, 1)]
+    if case == "only_tiny":
+        shapes = [(3,)] * 90
+    elif case == "many_ask_for_samples":
+        scope, shapes = P.SCOPE_PER_TENSOR, [(600, 451 + i) for i in range(16)] + [(2,), (40,)]
+    elif case == "sixteen_densities":
+        ds, shapes = [0.01 + 0.06 * j for j in range(16)], [(1300, 1001), (17,)]
+    elif case == "density_ends":
+        ds, shapes = [1e-6, 3e-4, 9e-4, 0.9992, 0.999999], [(1300, 1001)]
+    arrs = [rng.standard_normal(s).astype(np.float32) for s in shapes]
+    for d in ([ds] if len(ds) > 1 else [ds, [0.1, 0.6]]):
+        res = P.condensa_prune(up(arrs), d, scope=scope)
+        torch.cuda.synchronize()
+        check_prune_against_oracle(res, oracle.prune(arrs, d, scope), scope, len(arrs), case)
+    for d in ds if case == "density_ends" else ds[:1]:
+        _check_lc(arrs, [rng.standard_normal(s).astype(np.float32) * np.float32(1e-4) for s in shapes], d)
