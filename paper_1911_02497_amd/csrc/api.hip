@@ -292,6 +292,12 @@ static u32 list_fallback_bins(int n_slots, int J) {
     while (bins > 256 && static_cast<u64>(bins) * static_cast<u64>(n_slots) > (1u << 20)) bins /= 2;
     return bins;
 }
+// Copies of a ranking's histogram (list_hist_copy): what the sweep's updates ask for, and 256 KB for all rankings.
+static u32 list_hist_copies(int n_slots) {
+    u32 c = 16;
+    while (c > 1 && c * static_cast<u32>(n_slots) > 256) c /= 2;
+    return c;
+}
 static u32 list_groups(u64 n, int J, bool per_tensor, const Config& cfg) {         // sampling workgroups of a population
     const int64_t opt = cfg[CONDENSA_OPT_SAMPLE_LOG2];
     if (opt <= 0) return list_sample_groups(n, J, per_tensor);
@@ -328,8 +334,9 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
         L.l_cnt = off;     off += align_up(static_cast<size_t>(L.n_slots) * L.l_max_segs * sizeof(u64));
         L.l_nnz = off;     off += align_up(kListSegs * sizeof(u32));
         L.seg = off;       off += op == CONDENSA_OP_LC_STEP ? align_up(kNnzSegs * sizeof(u64)) : 0;
-        L.l_hist = off;    off += align_up(static_cast<size_t>(L.n_slots) * kListBins * sizeof(u32));
-        L.l_gathered = off; off += align_up(static_cast<size_t>(L.n_slots) * sizeof(u32));
+        L.l_hist = off;    off += align_up(static_cast<size_t>(L.n_slots) * list_hist_copies(L.n_slots) * kListBins * sizeof(u32));
+        L.l_post = off;    off += L.n_slots == 1 ? align_up(256 + (kListFound + kMaxWalkers) * sizeof(u64) + kMaxWalkers * sizeof(u32)) : 0;
+        L.l_gathered = off; off += align_up(static_cast<size_t>(L.n_slots) * kListLine * sizeof(u32));
         L.l_fb = off;      off += align_up(sizeof(FallbackCtl));
         L.l_gmax = off;    off += align_up(2 * static_cast<size_t>(L.n_slots) * sizeof(u32));
         L.l_masks = off;   off += align_up(3 * static_cast<size_t>(L.n_groups) * sizeof(u32));
@@ -759,6 +766,13 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const L
     w.max_segs = L.l_max_segs;
     w.n_rankings = n_slots;
     w.hist = at<u32>(ws, L.l_hist);
+    w.hist_copies = list_hist_copies(n_slots);
+    w.count_in_sweep = !shape.lone && n_slots == 1 ? 1 : 0;
+    w.arrived = at<u32>(ws, L.l_post);
+    w.ended = w.arrived + kListLine;
+    w.picked = at<u64>(ws, L.l_post + 256);
+    w.verdict = w.picked + kListFound;
+    w.range = reinterpret_cast<u32*>(w.verdict + kMaxWalkers);
     w.gathered = at<u32>(ws, L.l_gathered);
     w.bin_want = at<u32>(ws, L.l_want);
     w.gkey = at<u32>(ws, L.l_gkey);
@@ -897,24 +911,20 @@ static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* w
         CONDENSA_LAUNCH_CHECK();
         return CONDENSA_OK;
     }
-    hipLaunchKernelGGL(k_list_hist, walk, dim3(kBlock), 0, st, a, w);
-    CONDENSA_LAUNCH_CHECK();
-    if constexpr (LC) {
-        if (rq.pq) {
-            hipLaunchKernelGGL((k_list_gather<true, true>), walk, dim3(kBlock), 0, st, a, w);
-            CONDENSA_LAUNCH_CHECK();
-            hipLaunchKernelGGL((k_list_settle<true, VEC, true>), fb, dim3(kSettleThreads), 0, st, a, w, results, n_groups, vo);
-        } else {
-            hipLaunchKernelGGL((k_list_gather<true, false>), walk, dim3(kBlock), 0, st, a, w);
-            CONDENSA_LAUNCH_CHECK();
-            hipLaunchKernelGGL((k_list_settle<true, VEC, false>), fb, dim3(kSettleThreads), 0, st, a, w, results, n_groups, vo);
-        }
-    } else {
-        hipLaunchKernelGGL((k_list_gather<false, false>), walk, dim3(kBlock), 0, st, a, w);
+    if (n_slots == 1) {
+        if (LC && rq.pq) hipLaunchKernelGGL((k_list_resolve<LC, VEC, LC>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
+        else             hipLaunchKernelGGL((k_list_resolve<LC, VEC, false>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
         CONDENSA_LAUNCH_CHECK();
-        hipLaunchKernelGGL((k_list_settle<false, VEC, false>), fb, dim3(kSettleThreads), 0, st, a, w, results, n_groups, vo);
+        return CONDENSA_OK;
     }
-    CONDENSA_LAUNCH_CHECK();
+    if constexpr (!LC) {                                   // (an L-C step has one ranking)
+        hipLaunchKernelGGL(k_list_hist, walk, dim3(kBlock), 0, st, w);
+        CONDENSA_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_list_gather, walk, dim3(kBlock), 0, st, a, w);
+        CONDENSA_LAUNCH_CHECK();
+        hipLaunchKernelGGL((k_list_settle<VEC>), fb, dim3(kSettleThreads), 0, st, a, w, results, n_groups, vo);
+        CONDENSA_LAUNCH_CHECK();
+    }
     return CONDENSA_OK;
 }
 

@@ -13,12 +13,13 @@
 //   2. k_list_sweep / k_list_sweep_multi: ONE pass over the weights writes the outputs (final outside the windows,
 //      provisional -- kept from `mid` on -- inside), counts the keys above each window and lists the keys inside it
 //      with their indices.
-//   3. k_list_hist counts each list in kListBins bins over its window; k_list_gather finds the bin of rank k - above,
-//      settles the listed elements outside it (their outputs are rewritten where the provisional decision was wrong)
-//      and gathers those inside, a few hundred.
+//   3. The lists are counted in kListBins bins over their windows (several rankings: k_list_hist; one: the sweep itself).
+//      k_list_gather finds the bin of rank k - above, settles the listed elements outside it (their outputs are rewritten
+//      where the provisional decision was wrong) and gathers those inside, a few hundred.
 //   4. k_list_settle ranks these, applies the tie rule, writes state and record and settles them too.  Rankings that the
 //      lists leave open (the window missed, or the list overflowed, or thousands of ties) go on from there, all of them
 //      together in a few passes over the weights that the whole grid takes (list_fallback).
+//      One ranking: 3 and 4 are one launch, k_list_resolve.
 // Weights with many equal magnitudes -- pruned before, widened from 8-bit codes -- are such rankings as a rule, so the
 // sample also says when a list could not hold its window (kListCrowded): the sweep then leaves that ranking out.
 // Microseconds at the threshold density 0.1 to 0.2, radix levels / one ranking after the other, by tickets / now: 20 M
@@ -30,6 +31,7 @@
 // Results never depend on the sample.  Section 3.1 (a sparsity turned into a magnitude threshold), Section 3.3 (the
 // C step and the multiplier update), Results (up to ten samples per search share a pass).
 #pragma once
+#include <type_traits>
 #include "k_apply.h"
 #include "k_small.h"
 #include "k_window.h"
@@ -45,6 +47,8 @@ constexpr int kListBins = 256;                   // bins over a window
 static_assert(kListBins == 1 << 8, "list_window: 32 - 8 bits");
 constexpr u32 kListRanked = 2048;                // gathered entries that are held in LDS
 constexpr u32 kListGather = 1u << 18;            // gathered entries of a ranking at most; with more (ties) it is left open
+constexpr u32 kListLine = 32;                    // words of a 128-byte line
+constexpr u32 kListFound = 2048;                 // entries of the threshold's bin that a workgroup holds in LDS
 constexpr u32 kListRow = 64;                     // segments are multiples of this many entries
 
 // Populations up to here are sampled and finished by one workgroup.  Several densities: the windows of one sampling workgroup
@@ -139,6 +143,10 @@ struct ListState {         // a ranking that the list did not resolve
     u32 last;              // when found: last tie kept, as chunk * kChunk + place in the chunk
     u32 unused[2];
 };
+constexpr u64 kPicked = static_cast<u64>(1) << 63;         // the entry is there
+constexpr u32 kRangeKnown = 0x80000000u;
+constexpr u64 kWalkerLeft = 1;
+constexpr u32 kMaxWalkers = kListSegs / 8;                 // a segment for each of a workgroup's eight wavefronts
 constexpr u32 kStateUnsure = 1;      // the interval is the sample's alone; `rank` counts from the top of the population
 constexpr u32 kStateMaybe = 2;       // the gathered entries are many: if all are equal they are the ties, else list_rank takes them
 constexpr u32 kStateTied = 4;        // the ties are the gathered entries, and the outputs are right but for theirs
@@ -152,8 +160,17 @@ struct ListArgs {
     ListWin* win;          // [rankings]
     ListSorted* sorted;    // [populations], J > 1
     u64* cnt;              // [rankings][max_segs] entries offered | keys above the window << 32
-    u32* hist;             // [rankings][kListBins]
-    u32* gathered;         // [rankings] entries in the threshold's bin
+    u32* hist;             // [rankings][hist_copies][kListBins] listed keys by bin of their window
+    u32 hist_copies;       // a power of two
+    u32 count_in_sweep;    // 1: the sweep counts them (one ranking: two launches less, and its one or two listed keys a wavefront cost it
+                           // nothing), 0: k_list_hist (several: 780 thousand updates for ten densities of 20 M weights took 30 us), or
+                           // k_list_finish for itself
+    u32* arrived;          // one ranking: workgroups that have walked their part of the list << 20 | entries they gathered
+    u32* ended;            // one ranking, prune + binary16 step: workgroups that are done
+    u64* picked;           // one ranking: [kListFound] gathered entries, index | key << 32 | kPicked
+    u32* range;            // one ranking: [kMaxWalkers] where a workgroup's entries stand among these, first | number << 16 | kRangeKnown
+    u64* verdict;          // one ranking: [kMaxWalkers] for each workgroup: the last entry kept (as in `picked`), or kWalkerLeft
+    u32* gathered;         // [rankings][kListLine] entries in the threshold's bin (a counter in a line of its own)
     u32* bin_want;         // [rankings] rank to find among them
     u32* gkey;             // [rankings][gather_cap]
     u32* gidx;
@@ -692,6 +709,36 @@ __device__ inline u32 lanes_below(u64 m) {       // set bits of m below this lan
     return __builtin_amdgcn_mbcnt_hi(static_cast<u32>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<u32>(m), 0));
 }
 
+// Where this workgroup counts ranking r's listed keys.  A line that many update takes some 10 ns for each of them, so there are
+// up to 16 copies, taken in turn.
+__device__ inline u32* list_hist_copy(const ListArgs& w, u64 r) {
+    return w.hist + (r * w.hist_copies + (blockIdx.x & (w.hist_copies - 1))) * kListBins;
+}
+
+// Counts of a wavefront's listed keys.  A few go straight to the histogram.  Where they are many, those of the first two bins met are
+// added up first: they may be equal (five layers of 2.4 M E4M3 values: 130 thousand updates of one counter; 595 us the call
+// without, 240 with).
+constexpr u32 kCountedAtOnce = 8;
+struct BinCounts {
+    u32 bin[2] = {0, 0}, n[2] = {0, 0};          // uniform
+    __device__ inline void add(u32* hist, bool there, u32 b) {           // all lanes
+        u64 rest = __ballot(there);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (rest == 0) return;               // uniform
+            if (n[i] == 0) bin[i] = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(b), __ffsll(static_cast<long long>(rest)) - 1));
+            const u64 same = __ballot(there && b == bin[i]) & rest;
+            n[i] += static_cast<u32>(__popcll(same));
+            rest &= ~same;
+        }
+        if ((rest >> (threadIdx.x & 63u)) & 1u) atomicAdd(hist + b, 1u);
+    }
+    __device__ inline void flush(u32* hist) const {
+        const u32 lane = threadIdx.x & 63u, mine = lane == 0 ? n[0] : n[1];
+        if (lane < 2 && mine) atomicAdd(hist + (lane == 0 ? bin[0] : bin[1]), mine);
+    }
+};
+
 // ---- the one pass over the weights: one density ------------------------------------------------------------
 //
 // As k_window_fused, with one list per ranking and one counter update per wavefront (entries and keys above the window in
@@ -731,8 +778,8 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
         }
     }
     u32 key[QUADS][4];
-    u64 in_window[QUADS][4];                                            // lanes whose element is inside the window
-    u32 total = 0, above = 0, nz = 0;                                   // sums over the wavefront
+    u32 inside = 0;                                                     // a bit for each of this lane's elements that is inside the window
+    u32 above = 0, nz = 0;                                              // sums over the wavefront
 #pragma unroll
     for (int q = 0; q < QUADS; ++q) {
         const u64 e0 = base + static_cast<u64>(q) * 256 + lane * 4;
@@ -754,9 +801,9 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
             key[q][k] = x;
             const bool in = full || e0 + k < n;
             const bool keep = x >= mid;                                 // final outside the window, provisional inside
-            in_window[q][k] = __ballot(in && x - lo <= span);
-            above += static_cast<u32>(__popcll(__ballot(keep && in) & ~in_window[q][k]));       // the estimate lies in the window
-            total += static_cast<u32>(__popcll(in_window[q][k]));
+            const bool hit = in && x - lo <= span;
+            inside |= hit ? 1u << (4 * q + k) : 0u;
+            above += static_cast<u32>(__popcll(__ballot(keep && in && !hit)));                  // the estimate lies in the window
             m[k] = keep ? 1 : 0;
             th[k] = keep ? v : 0.0f;
             if (PQ) {
@@ -800,29 +847,38 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
     const ListRank rk = w.rank[r];
     const u32 seg = blockIdx.x % rk.n_segs;
     if (PQ && lane == 1 && nz) atomicAdd(&w.nnz[seg], nz);
+    const u32 mine = static_cast<u32>(__popc(inside)), incl = wave_incl_scan_u32(mine);
+    const u32 total = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
     if ((total | above) == 0) return;
     u64 b = 0;
     if (lane == 0)
         b = atomicAdd(reinterpret_cast<unsigned long long*>(&w.cnt[static_cast<u64>(r) * w.max_segs + seg]),
                       (static_cast<unsigned long long>(above) << 32) | total);
     if (total == 0) return;
-    u32 pos = __shfl(static_cast<u32>(b), 0, 64);
+    u32* const hist = w.count_in_sweep ? list_hist_copy(w, r) : nullptr;
+    const u32 shift = win_shift(win);
+    BinCounts counts;
+    u32 at = incl - mine;
     const u64 first = rk.base + static_cast<u64>(seg) * rk.seg_cap;
-    const u32 i0 = static_cast<u32>(c) * kChunk + sub * kWaveElems + lane * 4;
+    const u32 i0 = static_cast<u32>(c) * kChunk + sub * kWaveElems + lane * 4, pos = __shfl(static_cast<u32>(b), 0, 64);
+    while (__any(inside != 0)) {                                        // every lane its next element (one or two of them, as a rule)
+        const bool there = inside != 0;
+        const u32 i = there ? static_cast<u32>(__ffs(inside)) - 1u : 0u;
+        inside &= inside - 1u;
+        u32 x = key[0][0];
 #pragma unroll
-    for (int q = 0; q < QUADS; ++q) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const u64 m = in_window[q][k];
-            if (m == 0) continue;                                       // uniform
-            const u32 at = pos + lanes_below(m);
-            if (((m >> lane) & 1u) && at < rk.seg_cap) {
-                w.key[first + at] = key[q][k];
-                w.idx[first + at] = i0 + q * 256 + k;
-            }
-            pos += static_cast<u32>(__popcll(m));
+        for (int e = 1; e < 4 * QUADS; ++e) x = i == static_cast<u32>(e) ? key[e / 4][e % 4] : x;
+        if (hist) {                                                     // uniform
+            if (total > kCountedAtOnce) counts.add(hist, there, (x - lo) >> shift);
+            else if (there)             atomicAdd(hist + ((x - lo) >> shift), 1u);
         }
+        if (there && pos + at < rk.seg_cap) {
+            w.key[first + pos + at] = x;
+            w.idx[first + pos + at] = i0 + (i >> 2) * 256 + (i & 3u);
+        }
+        ++at;
     }
+    if (hist) counts.flush(hist);
 }
 
 // ---- the one pass over the weights: several densities --------------------------------------------------------
@@ -1121,14 +1177,16 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
 // ---- the threshold among the listed keys ---------------------------------------------------------------
 
 // f(there, key, entry) for the entries of ranking s that this wavefront takes: every `stride`-th segment, kListDeep rows
-// of four segments at a time (their loads in flight together); called by all lanes, `there` says which hold an entry.
+// of four segments at a time (their loads in flight together); called by all lanes, `there` says which hold an entry.  The
+// segments' counts come from LDS (cnt_of) where the workgroup has them.
 constexpr u32 kListDeep = 4;
 template <typename F>
-__device__ inline void list_walk(const ListArgs& w, u32 s, const ListRank& rk, u32 first_seg, u32 stride, F&& f) {
+__device__ inline void list_walk(const ListArgs& w, u32 s, const ListRank& rk, u32 first_seg, u32 stride, const u32* cnt_of, F&& f) {
     const u32 lane = threadIdx.x & 63u;
     for (u32 seg0 = first_seg; seg0 < rk.n_segs; seg0 += 64 * stride) {
         const u32 my_seg = seg0 + lane * stride;
-        u32 my_cnt = my_seg < rk.n_segs ? static_cast<u32>(w.cnt[static_cast<u64>(s) * w.max_segs + my_seg]) : 0u;
+        u32 my_cnt = 0;
+        if (my_seg < rk.n_segs) my_cnt = cnt_of ? cnt_of[my_seg] : static_cast<u32>(w.cnt[static_cast<u64>(s) * w.max_segs + my_seg]);
         if (my_cnt > rk.seg_cap) my_cnt = rk.seg_cap;
         for (u32 l = 0; l < 64 && seg0 + l * stride < rk.n_segs; l += 4) {
             u32 cnt[4], most = 0;
@@ -1177,8 +1235,8 @@ __device__ inline void wave_count(u32* hist, bool there, u32 bin) {
     if (there) atomicAdd(&hist[bin], 1u);
 }
 
-// Counts of a ranking's listed keys per bin of its window; `parts` workgroups per ranking.
-__global__ __launch_bounds__(kBlock) void k_list_hist(DataArgs a, ListArgs w) {
+// Counts of a ranking's listed keys per bin of its window, where the sweep did not take them; `parts` workgroups per ranking.
+__global__ __launch_bounds__(kBlock) void k_list_hist(ListArgs w) {
     constexpr int kCopies = 8;                             // by lane: listed keys often are equal (weights on a grid), and lanes
     __shared__ __align__(16) u32 s_hist[kListBins * kCopies];            // that meet on a counter take turns
     const u32 s = blockIdx.x / w.parts, part = blockIdx.x % w.parts;
@@ -1189,66 +1247,81 @@ __global__ __launch_bounds__(kBlock) void k_list_hist(DataArgs a, ListArgs w) {
     for (u32 i = threadIdx.x; i < static_cast<u32>(kListBins * kCopies) / 4; i += kBlock) reinterpret_cast<uint4*>(s_hist)[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
     const u32 lo = win.lo, shift = win_shift(win), copy = threadIdx.x & (kCopies - 1);
-    list_walk(w, s, rk, first, stride, [&](bool there, u32 key, u64) {
+    list_walk(w, s, rk, first, stride, nullptr, [&](bool there, u32 key, u64) {
         if (there) atomicAdd(&s_hist[((key - lo) >> shift) * kCopies + copy], 1u);
     });
     __syncthreads();
     const uint4 v0 = reinterpret_cast<const uint4*>(s_hist)[2 * threadIdx.x], v1 = reinterpret_cast<const uint4*>(s_hist)[2 * threadIdx.x + 1];
     const u32 v = v0.x + v0.y + v0.z + v0.w + v1.x + v1.y + v1.z + v1.w;          // kListBins == kBlock
-    if (v) atomicAdd(&w.hist[static_cast<u64>(s) * kListBins + threadIdx.x], v);
+    if (v) atomicAdd(list_hist_copy(w, s) + threadIdx.x, v);
 }
 
-// The outputs of up to B listed elements, with the decision each should have had.  The dependent loads of the elements
-// (tensor, its pointers, the inputs) are issued side by side: one after the other they take some 3 us an element.
-template <bool LC, bool PQ, int B>
-__device__ inline void list_fix(const DataArgs& a, const ListArgs& w, u32 j, const u32 (&idx)[B], const bool (&keep)[B], const bool (&on)[B], int* nz) {
+// The outputs of up to B listed elements, with the decision each should have had: what has to be read (list_fix_load), which need
+// not wait for the decision, and the stores.  The dependent loads of the elements (tensor, its pointers, the inputs) are issued
+// side by side: one after the other they take some 3 us an element.
+template <bool LC, int B>
+struct FixLoads {
+    float wv[B], lv[B];
+    float* lo[B];
+    float* gr[B];
+    u64 e[B];
+    OutDesc o[B];
+};
+template <bool LC, int B>
+__device__ inline void list_fix_load(const DataArgs& a, const ListArgs& w, u32 j, const u32 (&idx)[B], const bool (&on)[B], FixLoads<LC, B>& x) {
     u32 t[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) t[b] = on[b] ? a.chunk_map[idx[b] / kChunk] : 0u;
     const float* wp[B];
     const float* lp[B];
-    float* lo[B];
-    float* gr[B];
-    u64 e[B];
-    OutDesc o[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) {
         const TensorDesc& td = a.td[t[b]];
         wp[b] = td.w;
-        if (LC) { lp[b] = td.lam; lo[b] = td.lam_out; gr[b] = td.grad; }
-        e[b] = static_cast<u64>(idx[b]) - td.chunk_start * kChunk;
-        o[b] = w.out[static_cast<u64>(j) * a.n_tensors + t[b]];
+        if (LC) { lp[b] = td.lam; x.lo[b] = td.lam_out; x.gr[b] = td.grad; }
+        x.e[b] = static_cast<u64>(idx[b]) - td.chunk_start * kChunk;
+        x.o[b] = w.out[static_cast<u64>(j) * a.n_tensors + t[b]];
     }
-    float wv[B], lv[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) {
-        wv[b] = on[b] ? wp[b][e[b]] : 0.0f;
-        lv[b] = LC && on[b] ? lp[b][e[b]] : 0.0f;
+        x.wv[b] = on[b] ? wp[b][x.e[b]] : 0.0f;
+        x.lv[b] = LC && on[b] ? lp[b][x.e[b]] : 0.0f;
     }
+}
+template <bool LC, bool PQ, int B>
+__device__ inline void list_fix_store(const DataArgs& a, const FixLoads<LC, B>& x, const bool (&keep)[B], const bool (&on)[B], int* nz) {
 #pragma unroll
     for (int b = 0; b < B; ++b) {
         if (!on[b]) continue;
+        const OutDesc& o = x.o[b];
+        const u64 e = x.e[b];
         if (LC) {
-            const float x = lc_shift(wv[b], lv[b], a.mu);
-            float th = keep[b] ? x : 0.0f;
+            const float v = lc_shift(x.wv[b], x.lv[b], a.mu);
+            float th = keep[b] ? v : 0.0f;
             if (PQ) {
-                const u16 hv = f32_to_f16_rne(x), h = keep[b] ? hv : static_cast<u16>(0);
+                const u16 hv = f32_to_f16_rne(v), h = keep[b] ? hv : static_cast<u16>(0);
                 th = f16_bits_to_f32(h);
-                if (o[b].theta16) o[b].theta16[e[b]] = h;
+                if (o.theta16) o.theta16[e] = h;
                 if ((hv & 0x7FFFu) != 0) *nz += keep[b] ? 1 : -1;
             }
-            const float p = __fmul_rn(a.mu, __fsub_rn(wv[b], th));
-            const float ln = __fsub_rn(lv[b], p);
-            if (o[b].theta) o[b].theta[e[b]] = th;
-            lo[b][e[b]] = ln;
-            if (gr[b]) gr[b][e[b]] = __fsub_rn(p, ln);
+            const float p = __fmul_rn(a.mu, __fsub_rn(x.wv[b], th));
+            const float ln = __fsub_rn(x.lv[b], p);
+            if (o.theta) o.theta[e] = th;
+            x.lo[b][e] = ln;
+            if (x.gr[b]) x.gr[b][e] = __fsub_rn(p, ln);
         } else {
-            const float th = keep[b] ? wv[b] : 0.0f;
-            if (o[b].theta) o[b].theta[e[b]] = th;
-            if (o[b].theta16) o[b].theta16[e[b]] = f32_to_f16_rne(th);
+            const float th = keep[b] ? x.wv[b] : 0.0f;
+            if (o.theta) o.theta[e] = th;
+            if (o.theta16) o.theta16[e] = f32_to_f16_rne(th);
         }
-        if (o[b].mask) o[b].mask[e[b]] = keep[b] ? 1 : 0;
+        if (o.mask) o.mask[e] = keep[b] ? 1 : 0;
     }
+}
+template <bool LC, bool PQ, int B>
+__device__ inline void list_fix(const DataArgs& a, const ListArgs& w, u32 j, const u32 (&idx)[B], const bool (&keep)[B], const bool (&on)[B], int* nz) {
+    FixLoads<LC, B> x;
+    list_fix_load<LC, B>(a, w, j, idx, on, x);
+    list_fix_store<LC, PQ, B>(a, x, keep, on, nz);
 }
 template <bool LC, bool PQ>
 __device__ inline void list_fix_one(const DataArgs& a, const ListArgs& w, u32 j, u32 idx, bool keep, int* nz) {
@@ -1307,8 +1380,9 @@ __device__ inline ListState list_window_state(const ListWin& win, u32 n, u32 k, 
 }
 // Ranking s goes to list_fallback: `rank` from the top between a and b, where there are n keys.  All threads of one
 // workgroup; its histogram is cleared here.
+template <int THREADS>
 __device__ inline void list_leave(const DataArgs& a, const ListArgs& w, u32 s, u32 lo, u32 hi, u32 rank, u32 n, u32 flags) {
-    for (u32 i = threadIdx.x; i < 3 * w.fb_bins; i += kBlock) st_dev(w.fb_hist + static_cast<u64>(s) * 3 * w.fb_bins + i, 0u);
+    for (u32 i = threadIdx.x; i < 3 * w.fb_bins; i += THREADS) st_dev(w.fb_hist + static_cast<u64>(s) * 3 * w.fb_bins + i, 0u);
     if (threadIdx.x != 0) return;
     const u32 g = s / a.J, j = s - g * a.J;
     st_dev(w.fb_above + s, 0u);
@@ -1328,148 +1402,77 @@ __device__ inline void list_leave(const DataArgs& a, const ListArgs& w, u32 s, u
         add_dev(&w.fb->ties, 1u);
     }
 }
-// Every workgroup finds the bin of rank k - above from the counts.  Elements in the bins beside it are settled here:
-// wrong decisions are queued in LDS, so that their chains of dependent loads run side by side.
-template <bool LC, bool PQ>
-__global__ __launch_bounds__(kBlock) void k_list_gather(DataArgs a, ListArgs w) {
-    constexpr u32 kQueue = 2048;
-    __shared__ u64 s_wave[kBlock / 64];
-    constexpr u32 kFound = 1024;
-    __shared__ u32 s_queue[kQueue];                        // wrong decisions: entry, top bit = the right one
-    __shared__ u32 s_fkey[kFound], s_fidx[kFound];         // entries in the bin (one reservation per workgroup: updates of
-                                                           // one counter that return a value take turns)
-    __shared__ u32 s_over, s_bin, s_want, s_in, s_n, s_f, s_base, s_max, s_maxc;
-    const u32 s = blockIdx.x / w.parts, part = blockIdx.x % w.parts, tid = threadIdx.x, lane = tid & 63u;
-    const ListRank rk = w.rank[s];
-    const ListWin win = w.win[s];
-    const Slot& slot = a.slots[s];
-    if (part != 0 && part * (kBlock / 64) >= rk.n_segs) return;          // uniform
-    if (PQ && w.nnz_out && w.write && part == 0) {         // the sweep's count of non-zero codes, corrected by k_list_settle
-        u64 v = 0, total;
-        for (u32 i = tid; i < static_cast<u32>(kListSegs); i += kBlock) v += w.nnz[i];
-        block_excl_scan_u64(v, s_wave, &total);
-        if (tid == 0) *w.nnz_out = total;
-    }
-    if (slot.state != kSelecting || win_crowded(win)) {    // uniform; k == 0: nothing listed
-        if (part != 0) return;
-        if (tid == 0) w.bin_want[s] = 0;
-        if (slot.state == kSelecting) list_leave(a, w, s, win.lo, win.hi, static_cast<u32>(slot.k), 0, kStateUnsure);
-        return;
-    }
-    if (tid == 0) { s_over = 0; s_n = 0; s_f = 0; s_in = 0; s_want = 0; s_max = 0; s_maxc = 0; }
-    __syncthreads();
-    u64 cnt = 0;
-    for (u32 seg = tid; seg < rk.n_segs; seg += kBlock) {
-        const u64 v = w.cnt[static_cast<u64>(s) * w.max_segs + seg];
-        if (static_cast<u32>(v) > rk.seg_cap) s_over = 1;
-        cnt += v;                                          // both halves: neither sum reaches 2^32
-    }
-    const u32 bin_of_tid = kListBins - 1 - tid;            // kListBins == kBlock: bins from the top
-    const u32 h = w.hist[static_cast<u64>(s) * kListBins + bin_of_tid];
-    u64 sums, listed;
-    block_excl_scan_u64(cnt, s_wave, &sums);
-    const u64 higher = block_excl_scan_u64(h, s_wave, &listed);
-    const u32 shift = win_shift(win), mid_bin = win_mid_bin(win);
-    const u32 k = static_cast<u32>(slot.k), above = static_cast<u32>(sums >> 32);
-    const u64 want = slot.k - above;
-    if (above < k && higher < want && want <= higher + h) { s_bin = bin_of_tid; s_want = static_cast<u32>(want - higher); s_in = h; }
-    __syncthreads();
-    const u32 n_in = s_in, lo = win.lo, bin = s_bin;
-    const bool found_bin = s_over == 0 && s_want != 0, ok = found_bin && n_in <= w.gather_cap;
-    if (part == 0) {
-        if (tid == 0) w.bin_want[s] = ok ? s_want : 0;
-        const u32 from = lo + (bin << shift), to = from + ((1u << shift) - 1u);
-        if (!found_bin) {
-            const ListState x = list_window_state(win, static_cast<u32>(slot.n), k, above, static_cast<u32>(sums));
-            list_leave(a, w, s, x.a, x.b, x.rank, x.n, 0);
-        } else if (!ok || n_in > kListRanked) {
-            list_leave(a, w, s, from, to < win.hi ? to : win.hi, s_want, n_in, ok ? kStateMaybe : 0);
-        }
-    }
-    if (!ok) return;                                       // uniform over all workgroups of the ranking
-    const u32 g = s / a.J, j = s - g * a.J;
-    int nz = 0;
-    u32 most = 0, mostc = 0;
-    // uniform.  Many: a walk over the list to count them first is cheaper than a reservation for every 64 (4 M weights widened
-    // from 8 bits, 60 to 200 thousand ties: 25 us, 50 without); few: it is not (2 to 4 thousand of 20 M weights: 20 us, 31 with).
-    const bool many = n_in > 8 * kFound;
-    u32* gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
-    u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
-    const u32 first_seg = part * (kBlock / 64) + (tid >> 6), stride = w.parts * (kBlock / 64);
-    auto settle_beside = [&](bool there, u32 key, u64 at, bool* found) {
-        const u32 b = (key - lo) >> shift;
-        const bool wrong = w.write && there && b != bin && (b > bin) != (b >= mid_bin);
-        *found = there && b == bin;
-        const u32 q = wave_push(&s_n, wrong);
-        if (wrong) {
-            if (q < kQueue) s_queue[q] = static_cast<u32>(at - rk.base) | (b > bin ? 0x80000000u : 0u);
-            else            list_fix_one<LC, PQ>(a, w, j, w.idx[at], b > bin, &nz);
-        }
-    };
-    if (n_in <= kFound) {                                  // the buffer holds them wherever they are found
-        list_walk(w, s, rk, first_seg, stride, [&](bool there, u32 key, u64 at) {
-            bool found;
-            settle_beside(there, key, at, &found);
-            const u32 f = wave_push(&s_f, found);
-            if (found) {
-                s_fkey[f] = key;
-                s_fidx[f] = static_cast<u32>(at - rk.base);
-            }
-        });
-    } else {
-        u32 next = 0;
-        if (many) {                                        // one reservation for all that this wavefront will find
-            list_walk(w, s, rk, first_seg, stride, [&](bool there, u32 key, u64) {
-                next += static_cast<u32>(__popcll(__ballot(there && ((key - lo) >> shift) == bin)));
-            });
-            if (lane == 0 && next) next = atomicAdd(&w.gathered[s], next);
-            next = __shfl(next, 0, 64);
-        }
-        list_walk(w, s, rk, first_seg, stride, [&](bool there, u32 key, u64 at) {
-            bool found;
-            settle_beside(there, key, at, &found);
-            if (found) {
-                most = key > most ? key : most;
-                mostc = ~key > mostc ? ~key : mostc;
-            }
-            const u32 f = many ? kFound : wave_push(&s_f, found);
-            if (found && f < kFound) {
-                s_fkey[f] = key;
-                s_fidx[f] = static_cast<u32>(at - rk.base);
-            }
-            const u64 direct = __ballot(found && f >= kFound);           // straight to the list
-            if (direct == 0) return;
-            u32 to = next;
-            if (!many) {
-                const int leader = __ffsll(static_cast<long long>(direct)) - 1;
-                if (static_cast<int>(lane) == leader) to = atomicAdd(&w.gathered[s], static_cast<u32>(__popcll(direct)));
-                to = __shfl(to, leader, 64);
-            }
-            next += static_cast<u32>(__popcll(direct));
-            to += lanes_below(direct);
-            if (((direct >> lane) & 1u) && to < w.gather_cap) { gkey[to] = key; gidx[to] = w.idx[at]; }
-        });
-    }
-    if (n_in > kListRanked) {                              // are they all equal?
-        atomicMax(&s_max, most);
-        atomicMax(&s_maxc, mostc);
-    }
-    __syncthreads();
-    const u32 n_f = s_f < kFound ? s_f : kFound, n_q = s_n < kQueue ? s_n : kQueue;
-    if (tid == 0 && n_f) s_base = atomicAdd(&w.gathered[s], n_f);
-    if (tid == 0 && s_maxc) { atomicMax(&w.gmax[s], s_max); atomicMax(&w.gmaxc[s], s_maxc); }
-    list_fix_queue<LC, PQ, kBlock>(a, w, j, w.idx + rk.base, s_queue, n_q, &nz);
-    __syncthreads();
-    for (u32 f = tid; f < n_f; f += kBlock) {
-        const u32 to = s_base + f;
-        if (to < w.gather_cap) { gkey[to] = s_fkey[f]; gidx[to] = w.idx[rk.base + s_fidx[f]]; }
-    }
-    if (PQ) {
+// Where the threshold of ranking s is in its list, from the counters and the histogram that the sweep left.  All threads; every
+// workgroup of the ranking finds the same.  The loads depend on nothing but the launch's arguments and are all in flight at once.
+template <int THREADS>
+struct ListFindShared {
+    u32 cnt[kListSegs];    // entries of each segment
+    u32 above[THREADS / 64], listed[THREADS / 64], over[THREADS / 64], counted[THREADS / 64];
+    u32 bin, want, in;
+};
+struct ListFound {
+    u32 above, listed;     // keys above the window and in it
+    u32 bin, want, n_in;   // the threshold's bin, its rank among the keys there, their number.  want 0: it is not in the list, or
+                           // the list is not complete
+};
+template <int THREADS>
+__device__ inline ListFound list_find(const ListArgs& w, ListFindShared<THREADS>& sh, u32 s, const ListRank& rk, u32 k) {
+    static_assert(kListSegs % THREADS == 0 && THREADS >= kListBins && kListBins % 64 == 0, "segments and bins by thread");
+    constexpr int kPer = kListSegs / THREADS;
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    u64 v[kPer];
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) nz += __shfl_xor(nz, d, 64);
-        if (lane == 0 && nz != 0)
-            atomicAdd(reinterpret_cast<unsigned long long*>(&a.ctl->nnz_delta), static_cast<unsigned long long>(static_cast<long long>(nz)));
+    for (int i = 0; i < kPer; ++i) {
+        const u32 seg = tid + i * THREADS;
+        v[i] = seg < w.max_segs ? w.cnt[static_cast<u64>(s) * w.max_segs + seg] : 0;           // none past n_segs
     }
+    u32 h = 0;
+    if (tid < static_cast<u32>(kListBins)) {               // bins from the top
+        const u32* from = w.hist + static_cast<u64>(s) * w.hist_copies * kListBins + (kListBins - 1 - tid);
+        if (w.hist_copies == 16) {
+#pragma unroll
+            for (int c = 0; c < 16; ++c) h += from[c * kListBins];
+        } else {
+            for (u32 c = 0; c < w.hist_copies; ++c) h += from[c * kListBins];
+        }
+    }
+    u32 above = 0, listed = 0;
+    bool over = false;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const u32 n = static_cast<u32>(v[i]);
+        above += static_cast<u32>(v[i] >> 32);             // neither sum reaches 2^32
+        listed += n;
+        over = over || n > rk.seg_cap;
+        sh.cnt[tid + i * THREADS] = n < rk.seg_cap ? n : rk.seg_cap;
+    }
+    above = wave_sum_u32(above);
+    listed = wave_sum_u32(listed);
+    const u32 incl = wave_incl_scan_u32(h);
+    const bool any_over = __any(over);
+    if (lane == 63) { sh.above[wave] = above; sh.listed[wave] = listed; sh.over[wave] = any_over ? 1u : 0u; sh.counted[wave] = incl; }
+    if (tid == 0) { sh.want = 0; sh.in = 0; sh.bin = 0; }
+    __syncthreads();
+    ListFound f{};
+    u32 any = 0, higher = incl - h;
+#pragma unroll
+    for (u32 i = 0; i < THREADS / 64; ++i) {
+        f.above += sh.above[i];
+        f.listed += sh.listed[i];
+        any |= sh.over[i];
+        higher += i < wave ? sh.counted[i] : 0u;
+    }
+    const u32 want = k - f.above;                          // (when that many are above, nothing below holds)
+    if (any == 0 && f.above < k && tid < static_cast<u32>(kListBins) && higher < want && want <= higher + h) {
+        sh.bin = kListBins - 1 - tid;
+        sh.want = want - higher;
+        sh.in = h;
+    }
+    __syncthreads();
+    f.bin = sh.bin;
+    f.want = sh.want;
+    f.n_in = sh.in;
+    return f;
 }
 
 // ---- settle -----------------------------------------------------------------------------------------------------
@@ -1542,14 +1545,14 @@ __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShare
     if (nothing) {
         if (tid == 0 && share == 0) *record = select_record(slot, false, 0, 0, 0, 0, slot.path);
     } else if (want != 0) {                                // 0: it failed
-        const u32* __restrict__ gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
-        const u32* __restrict__ gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
+        const u32* gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
+        const u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
         if (!in_lds && n <= kListRanked) {
-            for (u32 i = tid; i < n; i += THREADS) { sh.key[i] = gkey[i]; sh.idx[i] = gidx[i]; }
+            for (u32 i = tid; i < n; i += THREADS) { sh.key[i] = ld_dev(gkey + i); sh.idx[i] = ld_dev(gidx + i); }
             in_lds = true;
         }
-        auto key_of = [&](u32 i) { return in_lds ? sh.key[i] : gkey[i]; };
-        auto idx_of = [&](u32 i) { return in_lds ? sh.idx[i] : gidx[i]; };
+        auto key_of = [&](u32 i) { return in_lds ? sh.key[i] : ld_dev(gkey + i); };
+        auto idx_of = [&](u32 i) { return in_lds ? sh.idx[i] : ld_dev(gidx + i); };
         const ListWin win = w.win[s];
         const u32 bits = win_shift(win);                   // low bits of key - lo that the window's bins leave open
         const u32 sub = bits > 8 ? bits - 8 : 0;
@@ -1641,12 +1644,348 @@ __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShare
         wg_incl_scan_u32<THREADS>(v, sh.wave, &total);
         if (tid == 0 && THREADS == kListThreads) {
             *w.nnz_out = total;
-        } else if (tid == 0) {                             // one of several: corrections of what k_list_gather stored
-            const long long d = static_cast<int>(total) + (share == 0 ? static_cast<long long>(a.ctl->nnz_delta) : 0ll);
-            if (d != 0) atomicAdd(reinterpret_cast<unsigned long long*>(w.nnz_out), static_cast<unsigned long long>(d));
+        } else if (tid == 0) {                             // one of several: corrections of what is stored
+            const long long d = static_cast<int>(total) + (share == 0 ? static_cast<long long>(ld_dev64(&a.ctl->nnz_delta)) : 0ll);
+            if (d != 0) __hip_atomic_fetch_add(w.nnz_out, static_cast<u64>(d), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     __syncthreads();                                       // the shared words are free for the next ranking
+}
+
+// The same for the posted entries of k_list_resolve by the workgroup that posts last: at most kListFound, a few hundred as a rule.
+// Radix levels of eight bits on the key (from the top of its bin), then on the index, until all pairs of the rest can be compared.
+// The verdict goes to the workgroups that posted (one of them settling 800 entries of 44 M weights took 15 us: each touches a page
+// of its own in every array); only what belongs to none, or to one that has left, is settled here.
+constexpr u32 kShortPairs = 64;
+struct RankShort {
+    u64 entry[kListFound];                       // distance of the key from the top of its bin << 32 | index
+    u64 pair[kShortPairs];
+    u64 found;
+    __align__(16) u32 hist[256];
+    u32 bin, rem, in, n, n_tie, kept;
+    u8 owned[kListFound];                        // its workgroup settles it
+};
+template <bool LC, bool PQ, int THREADS>
+__device__ inline void list_rank_short(const DataArgs& a, const ListArgs& w, RankShort& sh, u32 want, u32 n, u32 bin, const ListWin& win, u32 walkers,
+                                       condensa_select* results, int* nz) {
+    static_assert(THREADS >= 256 && THREADS >= static_cast<int>(kMaxWalkers), "a thread a bin, a thread a workgroup");
+    const u32 tid = threadIdx.x, shift = win_shift(win), top_key = win.lo + (bin << shift) + ((1u << shift) - 1u);
+    for (u32 i = tid; i < n; i += THREADS) {     // (one round, as a rule)
+        u64 x;
+        while (((x = ld_dev64(w.picked + i)) & kPicked) == 0) __builtin_amdgcn_s_sleep(1);
+        sh.entry[i] = (static_cast<u64>(top_key - (static_cast<u32>(x >> 32) & 0x7FFFFFFFu)) << 32) | static_cast<u32>(x);
+        sh.owned[i] = 0;
+    }
+    if (tid < 256) sh.hist[tid] = 0;
+    if (tid == 0) { sh.n = 0; sh.n_tie = 0; sh.kept = 0; }
+    __syncthreads();
+    u64 prefix = 0;
+    u32 top = 32 + shift, in = n, r = want;      // the r-th from the bottom among the `in` entries whose bits from `top` on are the prefix
+    while (in > kShortPairs && top > 0) {        // uniform
+        const u32 width = top < 8 ? top : 8, low = top - width;
+        for (u32 i = tid; i < n; i += THREADS)
+            if ((sh.entry[i] >> top) == prefix) atomicAdd(&sh.hist[static_cast<u32>(sh.entry[i] >> low) & ((1u << width) - 1u)], 1u);
+        __syncthreads();
+        if (tid < 64) {                          // four bins a lane, from the bottom
+            const uint4 c4 = *reinterpret_cast<const uint4*>(sh.hist + 4 * tid);
+            const u32 c[4] = {c4.x, c4.y, c4.z, c4.w}, sum = c[0] + c[1] + c[2] + c[3];
+            u32 before = wave_incl_scan_u32(sum) - sum;
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) {
+                if (before < r && r <= before + c[i]) { sh.bin = 4 * tid + i; sh.rem = r - before; sh.in = c[i]; }
+                before += c[i];
+            }
+        }
+        __syncthreads();
+        prefix = (prefix << width) | sh.bin;
+        r = sh.rem;
+        in = sh.in;
+        top = low;
+        if (tid < 256) sh.hist[tid] = 0;
+        __syncthreads();
+    }
+    for (u32 i = tid; i < n; i += THREADS)
+        if ((sh.entry[i] >> top) == prefix) sh.pair[atomicAdd(&sh.n, 1u)] = sh.entry[i];       // `in` of them
+    __syncthreads();
+    if (tid < in) {
+        const u64 mine = sh.pair[tid];
+        u32 less = 0;
+#pragma unroll 4
+        for (u32 e = 0; e < in; ++e) less += sh.pair[e] < mine ? 1u : 0u;
+        if (less + 1 == r) sh.found = mine;      // entries differ: one thread
+    }
+    __syncthreads();
+    const u64 found = sh.found;
+    const u32 T = top_key - static_cast<u32>(found >> 32), last = static_cast<u32>(found);
+    if (tid < walkers) {
+        u32 range;
+        while (((range = ld_dev(w.range + tid)) & kRangeKnown) == 0) __builtin_amdgcn_s_sleep(1);        // on its way, as the entries were
+        const u64 was = __hip_atomic_exchange(w.verdict + tid, kPicked | (static_cast<u64>(T) << 32) | last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const u32 first = range & 0xFFFFu, count = (range & ~kRangeKnown) >> 16;
+        if (was != kWalkerLeft)
+            for (u32 i = 0; i < count && first + i < kListFound; ++i) sh.owned[first + i] = 1;
+    }
+    for (u32 i = tid; i < n; i += THREADS)
+        if ((sh.entry[i] >> 32) == (found >> 32)) {
+            atomicAdd(&sh.n_tie, 1u);
+            if (sh.entry[i] <= found) atomicAdd(&sh.kept, 1u);
+        }
+    __syncthreads();
+    if (w.write)
+        for (u32 i = tid; i < n; i += THREADS) {
+            const bool kept = sh.entry[i] <= found;
+            if (!sh.owned[i] && kept != (top_key - static_cast<u32>(sh.entry[i] >> 32) >= win.mid))
+                list_fix_one<LC, PQ>(a, w, 0, static_cast<u32>(sh.entry[i]), kept, nz);
+        }
+    if (tid == 0) {
+        Slot& slot = a.slots[0];
+        u64 tie_end = slot.n;
+        if (sh.kept < sh.n_tie) {
+            const TensorDesc& td = a.td[a.chunk_map[last / kChunk]];
+            tie_end = static_cast<u64>(last) - td.chunk_start * kChunk + (a.per_tensor ? 0 : td.flat_start) + 1;
+        }
+        slot.prefix = T; slot.remaining = sh.kept; slot.n_tie = sh.n_tie; slot.need_tie = 0; slot.tie_end = tie_end; slot.state = kDone;
+        *results = select_record(slot, true, T, sh.kept, sh.n_tie, tie_end, slot.path);
+    }
+}
+
+// Every workgroup finds the bin of rank k - above from the counts.  Elements in the bins beside it are settled here:
+// wrong decisions are queued in LDS, so that their chains of dependent loads run side by side.
+// (Several rankings: an L-C step has one.)
+__global__ __launch_bounds__(kBlock) void k_list_gather(DataArgs a, ListArgs w) {
+    constexpr u32 kQueue = 2048;
+    constexpr u32 kFound = 1024;
+    __shared__ ListFindShared<kBlock> find;
+    __shared__ u32 s_queue[kQueue];                        // wrong decisions: entry, top bit = the right one
+    __shared__ u32 s_fkey[kFound], s_fidx[kFound];         // entries in the bin (one reservation per workgroup: updates of
+                                                           // one counter that return a value take turns)
+    __shared__ u32 s_n, s_f, s_base, s_max, s_maxc;
+    const u32 s = blockIdx.x / w.parts, part = blockIdx.x % w.parts, tid = threadIdx.x, lane = tid & 63u;
+    const ListRank rk = w.rank[s];
+    const ListWin win = w.win[s];
+    const Slot& slot = a.slots[s];
+    if (part != 0 && part * (kBlock / 64) >= rk.n_segs) return;          // uniform
+    const u32 k = static_cast<u32>(slot.k), n_all = static_cast<u32>(slot.n);
+    const u32 state = slot.state;
+    const ListFound f = list_find<kBlock>(w, find, s, rk, k);
+    const bool crowded = win_crowded(win), ok = !crowded && f.want != 0 && f.n_in <= w.gather_cap;
+    if (part == 0 && tid == 0) w.bin_want[s] = state == kSelecting && ok ? f.want : 0;
+    if (state != kSelecting) return;                       // uniform; k == 0: nothing listed
+    if (tid == 0) { s_n = 0; s_f = 0; s_max = 0; s_maxc = 0; }
+    const u32 n_in = f.n_in, lo = win.lo, bin = f.bin, shift = win_shift(win), mid_bin = win_mid_bin(win);
+    if (part == 0) {
+        const u32 from = lo + (bin << shift), to = from + ((1u << shift) - 1u);
+        if (crowded) {
+            list_leave<kBlock>(a, w, s, lo, win.hi, k, 0, kStateUnsure);
+        } else if (f.want == 0) {
+            const ListState x = list_window_state(win, n_all, k, f.above, f.listed);
+            list_leave<kBlock>(a, w, s, x.a, x.b, x.rank, x.n, 0);
+        } else if (!ok || n_in > kListRanked) {
+            list_leave<kBlock>(a, w, s, from, to < win.hi ? to : win.hi, f.want, n_in, ok ? kStateMaybe : 0);
+        }
+    }
+    if (!ok) return;                                       // uniform over all workgroups of the ranking
+    __syncthreads();
+    const u32 g = s / a.J, j = s - g * a.J;
+    int nz = 0;
+    u32 most = 0, mostc = 0;
+    // uniform.  Many: a walk over the list to count them first is cheaper than a reservation for every 64 (4 M weights widened
+    // from 8 bits, 60 to 200 thousand ties: 25 us, 50 without); few: it is not (2 to 4 thousand of 20 M weights: 20 us, 31 with).
+    const bool many = n_in > 8 * kFound;
+    u32* gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
+    u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
+    const u32 first_seg = part * (kBlock / 64) + (tid >> 6), stride = w.parts * (kBlock / 64);
+    auto settle_beside = [&](bool there, u32 key, u64 at, bool* found) {
+        const u32 b = (key - lo) >> shift;
+        const bool wrong = w.write && there && b != bin && (b > bin) != (b >= mid_bin);
+        *found = there && b == bin;
+        const u32 q = wave_push(&s_n, wrong);
+        if (wrong) {
+            if (q < kQueue) s_queue[q] = static_cast<u32>(at - rk.base) | (b > bin ? 0x80000000u : 0u);
+            else            list_fix_one<false, false>(a, w, j, w.idx[at], b > bin, &nz);
+        }
+    };
+    if (n_in <= kFound) {                                  // the buffer holds them wherever they are found
+        list_walk(w, s, rk, first_seg, stride, find.cnt, [&](bool there, u32 key, u64 at) {
+            bool found;
+            settle_beside(there, key, at, &found);
+            const u32 f = wave_push(&s_f, found);
+            if (found) {
+                s_fkey[f] = key;
+                s_fidx[f] = static_cast<u32>(at - rk.base);
+            }
+        });
+    } else {
+        u32 next = 0;
+        if (many) {                                        // one reservation for all that this wavefront will find
+            list_walk(w, s, rk, first_seg, stride, find.cnt, [&](bool there, u32 key, u64) {
+                next += static_cast<u32>(__popcll(__ballot(there && ((key - lo) >> shift) == bin)));
+            });
+            if (lane == 0 && next) next = atomicAdd(&w.gathered[static_cast<u64>(s) * kListLine], next);
+            next = __shfl(next, 0, 64);
+        }
+        list_walk(w, s, rk, first_seg, stride, find.cnt, [&](bool there, u32 key, u64 at) {
+            bool found;
+            settle_beside(there, key, at, &found);
+            if (found) {
+                most = key > most ? key : most;
+                mostc = ~key > mostc ? ~key : mostc;
+            }
+            const u32 f = many ? kFound : wave_push(&s_f, found);
+            if (found && f < kFound) {
+                s_fkey[f] = key;
+                s_fidx[f] = static_cast<u32>(at - rk.base);
+            }
+            const u64 direct = __ballot(found && f >= kFound);           // straight to the list
+            if (direct == 0) return;
+            u32 to = next;
+            if (!many) {
+                const int leader = __ffsll(static_cast<long long>(direct)) - 1;
+                if (static_cast<int>(lane) == leader) to = atomicAdd(&w.gathered[static_cast<u64>(s) * kListLine], static_cast<u32>(__popcll(direct)));
+                to = __shfl(to, leader, 64);
+            }
+            next += static_cast<u32>(__popcll(direct));
+            to += lanes_below(direct);
+            if (((direct >> lane) & 1u) && to < w.gather_cap) { gkey[to] = key; gidx[to] = w.idx[at]; }
+        });
+    }
+    if (n_in > kListRanked) {                              // are they all equal?
+        atomicMax(&s_max, most);
+        atomicMax(&s_maxc, mostc);
+    }
+    __syncthreads();
+    const u32 n_f = s_f < kFound ? s_f : kFound, n_q = s_n < kQueue ? s_n : kQueue;
+    if (tid == 0 && n_f) s_base = atomicAdd(&w.gathered[static_cast<u64>(s) * kListLine], n_f);
+    if (tid == 0 && s_maxc) { atomicMax(&w.gmax[s], s_max); atomicMax(&w.gmaxc[s], s_maxc); }
+    list_fix_queue<false, false, kBlock>(a, w, j, w.idx + rk.base, s_queue, n_q, &nz);
+    __syncthreads();
+    for (u32 f = tid; f < n_f; f += kBlock) {
+        const u32 to = s_base + f;
+        if (to < w.gather_cap) { gkey[to] = s_fkey[f]; gidx[to] = w.idx[rk.base + s_fidx[f]]; }
+    }
+}
+
+// f(there, key, index) for the entries of the ranking that this wavefront takes: every `stride`-th segment, `cnt` entries each (in
+// LDS), kListDeep rows of two segments at a time with their loads in flight together; called by all lanes, `there` says which hold
+// an entry.
+template <typename F>
+__device__ inline void list_walk_own(const ListArgs& w, const ListRank& rk, const u32* cnt_of, u32 first_seg, u32 stride, F&& f) {
+    const u32 lane = threadIdx.x & 63u;
+    for (u32 seg0 = first_seg; seg0 < rk.n_segs; seg0 += 2 * stride) {
+        u32 cnt[2], most = 0;
+        u64 first[2];
+#pragma unroll
+        for (u32 b = 0; b < 2; ++b) {
+            const u32 seg = seg0 + b * stride;
+            cnt[b] = seg < rk.n_segs ? cnt_of[seg] : 0u;
+            first[b] = rk.base + static_cast<u64>(seg) * rk.seg_cap;
+            most = cnt[b] > most ? cnt[b] : most;
+        }
+        for (u32 i0 = 0; i0 < most; i0 += 64 * kListDeep) {              // uniform
+            u32 x[kListDeep][2], e[kListDeep][2];
+#pragma unroll
+            for (u32 d = 0; d < kListDeep; ++d)
+#pragma unroll
+                for (u32 b = 0; b < 2; ++b) {
+                    const u32 i = i0 + 64 * d + lane, last = cnt[b] ? cnt[b] - 1u : 0u;
+                    const u64 at = first[b] + (i < cnt[b] ? i : last);
+                    if (i0 + 64 * d < cnt[b]) { x[d][b] = w.key[at]; e[d][b] = w.idx[at]; }        // uniform
+                }
+#pragma unroll
+            for (u32 d = 0; d < kListDeep; ++d)
+#pragma unroll
+                for (u32 b = 0; b < 2; ++b)
+                    if (i0 + 64 * d < cnt[b]) f(i0 + 64 * d + lane < cnt[b], x[d][b], e[d][b]);    // uniform
+        }
+    }
+}
+
+// Wrong provisional decisions that a wavefront meets are queued in its own part of LDS, so that their chains of dependent loads run
+// side by side afterwards.  They are the listed elements between the estimate's bin and the threshold's (without it): all
+// kept where the estimate was too high, all dropped where it was too low.
+template <u32 ROOM>
+struct WaveQueue {
+    u32* at;
+    u32 n;                 // uniform
+    bool keep;
+    u32 lo, shift, bin, mid_bin;
+    template <bool LC, bool PQ>
+    __device__ inline bool offer(const DataArgs& a, const ListArgs& w, u32 j, bool there, u32 key, u32 idx, int* nz) {     // true: the entry is in the threshold's bin
+        const u32 b = (key - lo) >> shift;
+        const bool wrong = w.write && there && b != bin && (b > bin) != (b >= mid_bin);
+        const u64 m = __ballot(wrong);
+        if (m != 0) {                                      // uniform
+            const u32 q = n + lanes_below(m);
+            if (wrong) {
+                if (q < ROOM) at[q] = idx;
+                else          list_fix_one<LC, PQ>(a, w, j, idx, keep, nz);
+            }
+            n += static_cast<u32>(__popcll(m));
+        }
+        return there && b == bin;
+    }
+    template <bool LC, bool PQ>
+    __device__ inline void fix(const DataArgs& a, const ListArgs& w, u32 j, int* nz) const {
+        constexpr int B = 4;
+        const u32 lane = threadIdx.x & 63u, upto = n < ROOM ? n : ROOM;
+        for (u32 q0 = lane; q0 < upto; q0 += 64 * B) {
+            u32 idx[B];
+            bool to[B], on[B];
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                on[b] = q0 + 64 * b < upto;
+                idx[b] = on[b] ? at[q0 + 64 * b] : 0u;
+                to[b] = keep;
+            }
+            list_fix<LC, PQ, B>(a, w, j, idx, to, on, nz);
+        }
+    }
+};
+
+// All entries of a long bin (ties, as a rule) to the ranking's gathered ones: one reservation for what a wavefront will find, which
+// it counts first (4 M weights widened from 8 bits, 60 to 200 thousand ties: 25 us, 50 with a reservation for every 64).
+// *most, *mostc: the largest key found and the complement of the smallest.
+template <bool LC, bool PQ, u32 ROOM>
+__device__ inline void list_gather_many(const DataArgs& a, const ListArgs& w, u32 s, u32 j, const ListRank& rk, const u32* cnt_of, u32 first_seg, u32 stride,
+                                        WaveQueue<ROOM>& queue, u32* most, u32* mostc, int* nz) {
+    const u32 lane = threadIdx.x & 63u;
+    u32 next = 0;
+    list_walk_own(w, rk, cnt_of, first_seg, stride, [&](bool there, u32 key, u32) {
+        next += static_cast<u32>(__popcll(__ballot(there && ((key - queue.lo) >> queue.shift) == queue.bin)));
+    });
+    if (lane == 0 && next) next = add_dev(&w.gathered[static_cast<u64>(s) * kListLine], next);
+    next = __shfl(next, 0, 64);
+    u32* gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
+    u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
+    list_walk_own(w, rk, cnt_of, first_seg, stride, [&](bool there, u32 key, u32 idx) {
+        const bool found = queue.template offer<LC, PQ>(a, w, j, there, key, idx, nz);
+        const u64 m = __ballot(found);
+        if (m == 0) return;                                // uniform
+        const u32 to = next + lanes_below(m);
+        if (found) {
+            *most = key > *most ? key : *most;
+            *mostc = ~key > *mostc ? ~key : *mostc;
+            if (to < w.gather_cap) { st_dev(gkey + to, key); st_dev(gidx + to, idx); }
+        }
+        next += static_cast<u32>(__popcll(m));
+    });
+}
+
+// Where a ranking goes that its list does not settle: to list_fallback, by one workgroup.  True: the gathered entries will be ranked
+// there or in list_rank, so they have to be gathered.
+template <int THREADS>
+__device__ inline bool list_leave_open(const DataArgs& a, const ListArgs& w, u32 s, const ListWin& win, const ListFound& f, u32 n, u32 k, bool leave) {
+    const u32 from = win.lo + (f.bin << win_shift(win)), to = from + ((1u << win_shift(win)) - 1u);
+    const bool fits = f.n_in <= w.gather_cap;
+    if (leave) {
+        if (f.want == 0) {
+            const ListState x = list_window_state(win, n, k, f.above, f.listed);
+            list_leave<THREADS>(a, w, s, x.a, x.b, x.rank, x.n, 0);
+        } else {
+            list_leave<THREADS>(a, w, s, from, to < win.hi ? to : win.hi, f.want, f.n_in, fits ? kStateMaybe : 0);
+        }
+    }
+    return f.want != 0 && fits;
 }
 
 // ---- what the lists leave open ----------------------------------------------------------------------------------
@@ -2014,7 +2353,7 @@ __global__ __launch_bounds__(kListThreads) void k_list_finish(DataArgs a, ListAr
             left = true;
             st = list_window_state(win, static_cast<u32>(slot.n), k, above, listed);
         } else {
-            list_walk(w, s, rk, wave, kWaves, [&](bool there, u32 key, u64) { wave_count(sh.hist, there, there ? (key - lo) >> shift : 0u); });
+            list_walk(w, s, rk, wave, kWaves, nullptr, [&](bool there, u32 key, u64) { wave_count(sh.hist, there, there ? (key - lo) >> shift : 0u); });
             __syncthreads();
             u32 bin;
             list_pick(sh, true, k - above, &bin, &want, &n);
@@ -2028,7 +2367,7 @@ __global__ __launch_bounds__(kListThreads) void k_list_finish(DataArgs a, ListAr
                 const u32* __restrict__ ids = w.idx + rk.base;
                 in_lds = n <= kListRanked;
                 u32 most = 0, mostc = 0;
-                list_walk(w, s, rk, wave, kWaves, [&](bool there, u32 key, u64 at) {
+                list_walk(w, s, rk, wave, kWaves, nullptr, [&](bool there, u32 key, u64 at) {
                     const u32 b = (key - lo) >> shift, entry = static_cast<u32>(at - rk.base);
                     const bool found = there && b == bin, wrong = w.write && there && b != bin && (b > bin) != (b >= mid_bin);
                     const u32 f = wave_push(&s_f, found);  // n of them; their indices are fetched below, side by side
@@ -2163,15 +2502,15 @@ struct FallbackShared {
 
 // Gathered entries that are many and all equal are ties (whose number and rank are known): list_fallback takes them.
 __device__ inline bool list_tied(const ListArgs& w, u32 s) {
-    return w.bin_want[s] != 0 && w.gathered[s] > kListRanked && w.gmax[s] == ~w.gmaxc[s];
+    return ld_dev(w.bin_want + s) != 0 && ld_dev(&w.gathered[static_cast<u64>(s) * kListLine]) > kListRanked && ld_dev(w.gmax + s) == ~ld_dev(w.gmaxc + s);
 }
 // State of a special ranking; false: list_rank takes it.
 __device__ inline bool list_state(const ListArgs& w, u32 s, ListState* st) {
     *st = ld_state(w.state + s);
     if (!(st->flags & kStateMaybe)) return true;
     if (!list_tied(w, s)) return false;
-    st->a = st->b = w.gmax[s];
-    st->n = w.gathered[s];
+    st->a = st->b = ld_dev(w.gmax + s);
+    st->n = ld_dev(&w.gathered[static_cast<u64>(s) * kListLine]);
     st->flags = kStateTied;
     return true;
 }
@@ -2181,7 +2520,7 @@ template <bool LC, bool VEC, bool PQ, int THREADS>
 __device__ inline void list_fallback(const DataArgs& a, const ListArgs& w, Meet& m, FallbackShared& sh, u32* words, condensa_select* results, int n_groups,
                                      int vec_out, bool tied, bool search) {
     const u32 tid = threadIdx.x, lane = tid & 63u;
-    const u32 n_special = w.fb->special, B = w.fb_bins, n_apply = w.fb->apply;         // of an earlier kernel
+    const u32 n_special = ld_dev(&w.fb->special), B = w.fb_bins, n_apply = ld_dev(&w.fb->apply);       // final: counted before the last meeting
     const u64 c0 = a.n_chunks * m.rank / m.size, c1 = a.n_chunks * (m.rank + 1) / m.size;      // this workgroup's chunks
     auto group_of = [&](u64 c) { return a.per_tensor ? a.chunk_map[c] : 0u; };
     // the rankings (a bit each) of chunk c's population in one of the masks, looked up where the population changes
@@ -2260,7 +2599,7 @@ __device__ inline void list_fallback(const DataArgs& a, const ListArgs& w, Meet&
         meet(m);
         // ---- the next intervals
         for (u32 f = m.rank; f < n_special; f += m.size) {
-            const u32 s = w.special[f], g = s / a.J, j = s - g * a.J;
+            const u32 s = ld_dev(w.special + f), g = s / a.J, j = s - g * a.J;
             if (((ld_dev(&w.open_of[g]) >> j) & 1u) == 0) continue;      // uniform: this bit is this workgroup's to change
             const ListState st = ld_state(w.state + s);
             u32* hist = w.fb_hist + static_cast<u64>(s) * 3 * B;
@@ -2307,7 +2646,7 @@ __device__ inline void list_fallback(const DataArgs& a, const ListArgs& w, Meet&
     }
 
     for (u32 f = m.rank; f < n_special; f += m.size) {     // ---- the tie rule, states and records
-        const u32 s = w.special[f], g = s / a.J, j = s - g * a.J;
+        const u32 s = ld_dev(w.special + f), g = s / a.J, j = s - g * a.J;
         ListState st;
         if (!list_state(w, s, &st)) continue;              // uniform
         const u32 T = st.a;
@@ -2390,7 +2729,7 @@ __device__ inline void list_fallback(const DataArgs& a, const ListArgs& w, Meet&
         int nz = 0;
         const u32 per = n_special < m.size ? m.size / n_special : 1u, sub = m.rank % per;              // workgroups for each of them
         for (u32 f = m.rank / per; f < n_special && m.rank / per < m.size / per; f += m.size / per) {
-            const u32 s = w.special[f], g = s / a.J, j = s - g * a.J;
+            const u32 s = ld_dev(w.special + f), g = s / a.J, j = s - g * a.J;
             ListState st;
             if (!list_state(w, s, &st) || !(st.flags & kStateTied)) continue;          // uniform
             const u32 last = ld_dev(&w.state[s].last);
@@ -2403,7 +2742,7 @@ __device__ inline void list_fallback(const DataArgs& a, const ListArgs& w, Meet&
 #pragma unroll
                 for (int b = 0; b < kB; ++b) {
                     const u32 i = i0 + b * per * THREADS;
-                    idx[b] = i < st.n ? gidx[i] : 0u;
+                    idx[b] = i < st.n ? ld_dev(gidx + i) : 0u;
                     keep[b] = idx[b] <= last;
                     on[b] = i < st.n && keep[b] != kept;
                 }
@@ -2428,7 +2767,9 @@ __device__ inline void list_fallback(const DataArgs& a, const ListArgs& w, Meet&
 }
 
 constexpr int kSettleGrid = 512, kSettleThreads = 512;
-template <bool LC, bool VEC, bool PQ>
+
+// Several rankings, after k_list_gather.
+template <bool VEC>
 __global__ __launch_bounds__(kSettleThreads, 4) void k_list_settle(DataArgs a, ListArgs w, condensa_select* results, int n_groups, int vec_out) {
     __shared__ union { ListShared rank; u32 words[kFallbackWords]; } s_mem;           // one after the other
     ListShared& sh = s_mem.rank;
@@ -2440,7 +2781,7 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_settle(DataArgs a, L
     for (u32 v = blockIdx.x; v < n_r * shares; v += gridDim.x) {
         const u32 s = v / shares;
         const u32 want = n_special != 0 && list_tied(w, s) ? 0u : w.bin_want[s];
-        list_rank<LC, PQ, kSettleThreads>(a, w, sh, s, want, w.gathered[s], false, 0, v % shares, shares, results, n_groups);
+        list_rank<false, false, kSettleThreads>(a, w, sh, s, want, w.gathered[static_cast<u64>(s) * kListLine], false, 0, v % shares, shares, results, n_groups);
     }
     if (n_special == 0) return;
     if (threadIdx.x == 0) { s_tied = 0; s_search = 0; }
@@ -2449,16 +2790,179 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_settle(DataArgs a, L
         const u32 s = w.special[f];
         if (!list_tied(w, s)) continue;
         s_tied = 1;
-        if (w.state[s].rank < w.gathered[s]) s_search = 1;
+        if (w.state[s].rank < w.gathered[static_cast<u64>(s) * kListLine]) s_search = 1;
     }
     __syncthreads();
     const bool tied = s_tied != 0, search = s_search != 0;
     if (!tied && w.fb->apply == 0) return;                 // the same in every workgroup
     Meet m;
     if (!meet_join(m, w.meet, fs.pick)) return;
-    if (PQ && w.nnz_out && w.write && m.rank == 0 && threadIdx.x == 0 && w.fb->apply == 0 && a.ctl->nnz_delta != 0)
-        __hip_atomic_fetch_add(w.nnz_out, a.ctl->nnz_delta, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    list_fallback<LC, VEC, PQ, kSettleThreads>(a, w, m, fs, s_words, results, n_groups, vec_out, tied, search);
+    list_fallback<false, VEC, false, kSettleThreads>(a, w, m, fs, s_words, results, n_groups, vec_out, tied, search);
+}
+
+// One ranking: everything after the sweep in one launch (k_list_hist, k_list_gather and k_list_settle took 22 us for the L-C step of
+// 20 M weights, 18 for 2^20 weights pruned; this 14 and 11).  Every workgroup finds
+// the threshold's bin for itself.  As a rule the bin's entries are few: the workgroups whose wavefronts have a segment of the
+// list walk it, post the entries of the bin and settle those beside it, whichever posts last ranks them, and each settles its own; the
+// others have left at once.  Otherwise (the list is incomplete, thousands of ties, a crowded window) all of them stay, register and
+// go through the phases of list_fallback.
+// Posting is one update that counts workgroups and entries both; the entries follow it, each with a bit that says it is there, and the
+// last workgroup waits for those still on their way (their workgroups wait for nobody).
+// Bound by latency: a launch and some ten dependent accesses.
+template <bool LC, bool VEC, bool PQ>
+__global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, ListArgs w, condensa_select* results, int vec_out) {
+    constexpr u32 kWaves = kSettleThreads / 64, kRoom = 256, kFound = 64;              // for each wavefront
+    static_assert(kMaxWalkers == kListSegs / kWaves, "a segment a wavefront");
+    __shared__ union {                                     // one after the other
+        ListShared rank;
+        RankShort few;
+        u32 words[kFallbackWords];
+    } s_mem;
+    __shared__ ListFindShared<kSettleThreads> find;
+    __shared__ u32 s_queue[kWaves * kRoom], s_fkey[kWaves * kFound], s_fidx[kWaves * kFound];
+    __shared__ FallbackShared fs;
+    __shared__ u32 s_found[kWaves + 1];
+    __shared__ u64 s_verdict[kWaves + 1];
+    ListShared& sh = s_mem.rank;
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const ListRank rk = w.rank[0];
+    const ListWin win = w.win[0];
+    const Slot& slot = a.slots[0];
+    const u32 k = static_cast<u32>(slot.k), n_all = static_cast<u32>(slot.n);
+    const ListFound f = list_find<kSettleThreads>(w, find, 0, rk, k);
+    const bool nnz = PQ && w.nnz_out != nullptr && w.write;
+    auto sweep_codes = [&]() {                             // the sweep's count of non-zero codes, in thread 0
+        u32 v = 0, total;                                  // fewer than 2^32
+        for (u32 i = tid; i < static_cast<u32>(kListSegs); i += kSettleThreads) v += w.nnz[i];
+        wg_incl_scan_u32<kSettleThreads>(v, find.above, &total);
+        return total;
+    };
+    auto add_corrections = [&](int nz, u64* to) {
+        const u32 sum = wave_sum_u32(static_cast<u32>(nz));                            // modulo 2^32: the sum of a wavefront's is small
+        if (lane == 0 && sum != 0)
+            __hip_atomic_fetch_add(to, static_cast<u64>(static_cast<long long>(static_cast<int>(sum))), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (slot.state != kSelecting) {                        // uniform: k == 0, nothing is kept and the sweep kept nothing
+        if (blockIdx.x != 0) return;
+        if (nnz) { const u32 codes = sweep_codes(); if (tid == 0) *w.nnz_out = codes; }
+        if (tid == 0) *results = select_record(slot, false, 0, 0, 0, 0, slot.path);
+        return;
+    }
+    const bool crowded = win_crowded(win);
+    int nz = 0;
+    WaveQueue<kRoom> queue{s_queue + wave * kRoom, 0, win_mid_bin(win) > f.bin, win.lo, win_shift(win), f.bin, win_mid_bin(win)};
+    if (!crowded && f.want != 0 && f.n_in <= kListRanked) {              // the same in every workgroup
+        const u32 walkers = (rk.n_segs + kWaves - 1) / kWaves;           // at most kMaxWalkers, fewer than the grid
+        if (blockIdx.x >= walkers) return;
+        u32* const fkey = s_fkey + wave * kFound;
+        u32* const fidx = s_fidx + wave * kFound;
+        auto post = [&](u32 at, u32 key, u32 idx) {
+            if (at < kListRanked) st_dev64(w.picked + at, kPicked | (static_cast<u64>(key) << 32) | idx);
+        };
+        u32 n_found = 0;                                   // uniform
+        list_walk_own(w, rk, find.cnt, blockIdx.x * kWaves + wave, gridDim.x * kWaves, [&](bool there, u32 key, u32 idx) {
+            const bool found = queue.template offer<LC, PQ>(a, w, 0, there, key, idx, &nz);
+            const u64 m = __ballot(found);
+            if (m == 0) return;                            // uniform
+            const u32 count = static_cast<u32>(__popcll(m));
+            if (n_found + count <= kFound) {
+                if (found) { fkey[n_found + lanes_below(m)] = key; fidx[n_found + lanes_below(m)] = idx; }
+                n_found += count;
+                return;
+            }
+            u32 base = 0;                                  // no room
+            if (lane == 0) base = add_dev(w.arrived, count) & 0xFFFFFu;
+            if (found) post(__shfl(base, 0, 64) + lanes_below(m), key, idx);
+        });
+        if (lane == 0) s_found[wave] = n_found;
+        __syncthreads();
+        u32 before = 0, all = 0;
+#pragma unroll
+        for (u32 i = 0; i < kWaves; ++i) { before += i < wave ? s_found[i] : 0u; all += s_found[i]; }
+        if (tid == 0) s_found[kWaves] = add_dev(w.arrived, (1u << 20) | all);
+        __syncthreads();
+        const u32 ticket = s_found[kWaves], base = (ticket & 0xFFFFFu) + before;
+        if (lane < n_found) post(base + lane, fkey[lane], fidx[lane]);
+        if (tid == 0) st_dev(w.range + blockIdx.x, kRangeKnown | (all << 16) | ((ticket & 0xFFFFu) < kListFound ? ticket & 0xFFFFu : kListFound));
+        queue.template fix<LC, PQ>(a, w, 0, &nz);
+        // what settling its own entries will read is on its way meanwhile
+        const u32 idx1[1] = {lane < n_found ? fidx[lane] : 0u};
+        bool on1[1] = {lane < n_found};
+        FixLoads<LC, 1> loads;
+        if (w.write && n_found != 0) list_fix_load<LC, 1>(a, w, 0, idx1, on1, loads);
+        if ((ticket >> 20) + 1 == walkers)                 // uniform: the last one
+            list_rank_short<LC, PQ, kSettleThreads>(a, w, s_mem.few, f.want, (ticket & 0xFFFFFu) + all, f.bin, win, walkers, results, &nz);
+        if (w.write && n_found != 0) {                     // uniform over the wavefront
+            // The verdict comes from a workgroup that is running once all have posted; if some of them are not even running yet (another
+            // launch holds the chip), this one does not keep them from it for long.
+            u64 v = 0;
+            if (lane == 0) {
+                for (int polls = 0; polls < 64 && ((v = ld_dev64(w.verdict + blockIdx.x)) & kPicked) == 0; ++polls) __builtin_amdgcn_s_sleep(4);
+            }
+            v = (static_cast<u64>(__shfl(static_cast<u32>(v >> 32), 0, 64)) << 32) | __shfl(static_cast<u32>(v), 0, 64);
+            s_verdict[wave] = v;
+        } else if (lane == 0) {
+            s_verdict[wave] = kPicked;                     // asks for nothing
+        }
+        __syncthreads();
+        bool stay = true;
+#pragma unroll
+        for (u32 i = 0; i < kWaves; ++i) stay = stay && (s_verdict[i] & kPicked) != 0;
+        if (!stay) {                                       // uniform: leave the entries to the workgroup that ranks, unless it has just spoken
+            if (tid == 0) {
+                u64 was = 0;
+                __hip_atomic_compare_exchange_strong(w.verdict + blockIdx.x, &was, kWalkerLeft, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s_verdict[kWaves] = was;
+            }
+            __syncthreads();
+            stay = (s_verdict[kWaves] & kPicked) != 0;
+            if (stay) s_verdict[wave] = s_verdict[kWaves];
+        }
+        if (stay && w.write && n_found != 0) {
+            const u64 v = s_verdict[wave];
+            const u32 key = lane < n_found ? fkey[lane] : 0u, T = static_cast<u32>(v >> 32) & 0x7FFFFFFFu;
+            const bool keep1[1] = {key > T || (key == T && idx1[0] <= static_cast<u32>(v))};
+            on1[0] = on1[0] && keep1[0] != (key >= win.mid);
+            list_fix_store<LC, PQ, 1>(a, loads, keep1, on1, &nz);
+        }
+        if (!nnz) return;
+        add_corrections(nz, &a.ctl->nnz_delta);
+        wait_dev();
+        __syncthreads();
+        if (tid == 0) s_found[0] = add_dev(w.ended, 1u);
+        __syncthreads();
+        if (s_found[0] + 1 != walkers) return;             // uniform: the last one adds up
+        const u32 codes = sweep_codes();
+        if (tid == 0) *w.nnz_out = codes + ld_dev64(&a.ctl->nnz_delta);
+        return;
+    }
+    Meet m;
+    if (!meet_join(m, w.meet, fs.pick)) return;
+    const bool first = m.rank == 0;
+    bool gather = false;
+    if (crowded) {
+        if (first) list_leave<kSettleThreads>(a, w, 0, win.lo, win.hi, k, 0, kStateUnsure);
+    } else {
+        gather = list_leave_open<kSettleThreads>(a, w, 0, win, f, n_all, k, first);
+    }
+    if (first && tid == 0) st_dev(w.bin_want, gather ? f.want : 0u);
+    if (first && nnz && gather) { const u32 codes = sweep_codes(); if (tid == 0) st_dev64(w.nnz_out, codes); }
+    if (gather) {
+        u32 most = 0, mostc = 0;
+        list_gather_many<LC, PQ, kRoom>(a, w, 0, 0, rk, find.cnt, m.rank * kWaves + wave, m.size * kWaves, queue, &most, &mostc, &nz);
+        if (mostc) { max_dev(w.gmax, most); max_dev(w.gmaxc, mostc); }
+        queue.template fix<LC, PQ>(a, w, 0, &nz);
+        if (nnz) add_corrections(nz, &a.ctl->nnz_delta);
+    }
+    meet(m);
+    if (gather && !list_tied(w, 0)) {                      // the same in every workgroup
+        const u32 shares = m.size < 16 ? m.size : 16u;
+        if (m.rank < shares) list_rank<LC, PQ, kSettleThreads>(a, w, sh, 0, f.want, f.n_in, false, 0, m.rank, shares, results, 1);
+        return;
+    }
+    if (first && nnz && gather && tid == 0) __hip_atomic_fetch_add(w.nnz_out, ld_dev64(&a.ctl->nnz_delta), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool tied = gather;
+    list_fallback<LC, VEC, PQ, kSettleThreads>(a, w, m, fs, s_mem.words, results, 1, vec_out, tied, tied && f.want < f.n_in);
 }
 
 }  // namespace condensa

@@ -153,3 +153,22 @@ def test_sampling_workgroups(case):
         check_prune_against_oracle(res, oracle.prune(arrs, d, scope), scope, len(arrs), case)
     for d in ds if case == "density_ends" else ds[:1]:
         _check_lc(arrs, [rng.standard_normal(s).astype(np.float32) * np.float32(1e-4) for s in shapes], d)
+
+
+@pytest.mark.parametrize("n", [131073, 262144, 300001, 4300007])
+@pytest.mark.parametrize("ties", [0, 3, 60, 900, 2040, 2060, 9000])
+def test_one_ranking_settled_by_the_launch_after_the_sweep(n, ties):
+    """Bins of one entry and of as many as that launch ranks by itself, fewer and more; ties at the threshold that are cut in the
+    middle, alone in their bin or among others."""
+    rng = np.random.default_rng(n + ties)
+    w = rng.standard_normal(n).astype(np.float32)
+    order = np.argsort(-np.abs(w), kind="stable")
+    k = n // 7
+    w[order[k - ties // 2:k + (ties + 1) // 2]] = np.abs(w[order[k]])      # the values next to the threshold become equal
+    lam = (rng.standard_normal(n) * 1e-7).astype(np.float32)
+    for d in (k / n, (k - 1) / n, (k + ties // 3) / n):
+        res = P.condensa_prune(up([w]), [d], theta_f16=True)
+        torch.cuda.synchronize()
+        check_prune_against_oracle(res, oracle.prune([w], [d], P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1, str((n, ties)))
+    _check_lc([w], [np.zeros_like(lam)], k / n, pq=True)
+    _check_lc([w], [lam], k / n, pq=ties % 2 == 0)
