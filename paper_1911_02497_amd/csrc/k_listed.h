@@ -356,7 +356,7 @@ __device__ inline void list_sample_units(SampleShared& sh, const ListArgs& w, in
     if (quads != 0) {                            // uniform
 #pragma unroll
         for (int i = 0; i < UNITS; ++i) {
-            const u32 u = static_cast<u32>(i * kListThreads + tid / lanes) * W + me;          // below 2^logu: its place is in the u-th of as many stretches
+            const u32 u = static_cast<u32>((i * kListThreads + tid) / lanes) * W + me;          // below 2^logu: its place is in the u-th of as many stretches
             u32 p = places <= (1u << logu) ? u : static_cast<u32>((static_cast<u64>(u) * places + __umulhi(mix32(u), places)) >> logu);
             p = p * lanes + tid % lanes;
             const bool there = p < quads;
