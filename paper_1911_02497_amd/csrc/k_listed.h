@@ -2872,7 +2872,8 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
             }
             u32 base = 0;                                  // no room
             if (lane == 0) base = add_dev(w.arrived, count) & 0xFFFFFu;
-            if (found) post(__shfl(base, 0, 64) + lanes_below(m), key, idx);
+            base = __shfl(base, 0, 64);                    // by all lanes: one that lane 0 does not take part in returns 0
+            if (found) post(base + lanes_below(m), key, idx);
         });
         if (lane == 0) s_found[wave] = n_found;
         __syncthreads();

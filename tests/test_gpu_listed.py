@@ -172,3 +172,16 @@ def test_one_ranking_settled_by_the_launch_after_the_sweep(n, ties):
         check_prune_against_oracle(res, oracle.prune([w], [d], P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1, str((n, ties)))
     _check_lc([w], [np.zeros_like(lam)], k / n, pq=True)
     _check_lc([w], [lam], k / n, pq=ties % 2 == 0)
+
+
+@pytest.mark.parametrize("n", [140001, 1 << 20])               # 35 segments of the list: more of the bin's entries than a wavefront holds, and 257
+@pytest.mark.parametrize("ties", [1900, 2049, 4000, 4097])     # the room for the entries of the threshold's bin: 4096
+def test_threshold_bins_about_as_large_as_their_room(n, ties):
+    rng = np.random.default_rng(ties)
+    w = rng.standard_normal(n).astype(np.float32)
+    w[rng.choice(n, ties, replace=False)] = np.float32(-1.25)
+    above = int((np.abs(w) > 1.25).sum())
+    for k in (above + 5, above + ties // 2):                   # at the first of the ties the list holds as many other elements
+        res = P.condensa_prune(up([w]), [k / n], theta_f16=True)
+        torch.cuda.synchronize()
+        check_prune_against_oracle(res, oracle.prune([w], [k / n], P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1, f"n={n} ties={ties} k={k}")
