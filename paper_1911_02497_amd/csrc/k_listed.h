@@ -39,7 +39,7 @@
 namespace condensa {
 
 constexpr int kListThreads = 1024;
-constexpr int kListUnits = 4;                    // sample positions (of four keys each) per thread of a lone workgroup; one of several takes one
+constexpr int kListUnits = 4;                    // sample positions (of four keys each) per thread of a lone workgroup (and of large populations: kSampleDeep); one of several takes one
 constexpr int kListSegs = 1024;                  // segments of a ranking's list at most
 constexpr int kListMaxW = 256;                   // sampling workgroups of one population at most
 constexpr int kListMaxRankings = 4096;
@@ -48,7 +48,7 @@ static_assert(kListBins == 1 << 8, "list_window: 32 - 8 bits");
 constexpr u32 kListRanked = 2048;                // gathered entries that are held in LDS
 constexpr u32 kListGather = 1u << 18;            // gathered entries of a ranking at most; with more (ties) it is left open
 constexpr u32 kListLine = 32;                    // words of a 128-byte line
-constexpr u32 kListFound = 2048;                 // entries of the threshold's bin that a workgroup holds in LDS
+constexpr u32 kListFound = 4096;                 // entries of the threshold's bin that k_list_resolve ranks from LDS
 constexpr u32 kListRow = 64;                     // segments are multiples of this many entries
 
 // Populations up to here are sampled and finished by one workgroup.  Several densities: the windows of one sampling workgroup
@@ -486,12 +486,16 @@ __device__ inline void list_sample_units(SampleShared& sh, const ListArgs& w, in
     }
 }
 
+// Beyond 2^26 elements (in quads) each of several workgroups takes the units of a lone one: half the window for 6 us more.  A window of
+// 256 sampling workgroups of one unit left more than kListFound entries in the threshold's bin of 2^27 weights at density 0.6, and the
+// whole grid ranked them (65 us where hist, gather and settle took 52); now 20.
+constexpr u32 kSampleDeep = 1u << 24;
 template <bool LC, bool VEC, typename TensorOf, typename RankOf>
 __device__ inline void list_sample(const ListArgs& w, int J, float mu, u32 W, u32 me, u32 at_local, u64 first_ranking, u32 first_chunk, u32 quads,
                                    TensorOf&& tensor_of, RankOf&& rank_of) {
     __shared__ SampleShared sh;
-    if (W == 1) list_sample_units<LC, VEC, kListUnits>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
-    else        list_sample_units<LC, VEC, 1>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
+    if (W == 1 || quads > kSampleDeep) list_sample_units<LC, VEC, kListUnits>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
+    else                               list_sample_units<LC, VEC, 1>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
 }
 
 // The sampling workgroups as a launch of their own.
@@ -2851,13 +2855,13 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
     const bool crowded = win_crowded(win);
     int nz = 0;
     WaveQueue<kRoom> queue{s_queue + wave * kRoom, 0, win_mid_bin(win) > f.bin, win.lo, win_shift(win), f.bin, win_mid_bin(win)};
-    if (!crowded && f.want != 0 && f.n_in <= kListRanked) {              // the same in every workgroup
+    if (!crowded && f.want != 0 && f.n_in <= kListFound) {               // the same in every workgroup
         const u32 walkers = (rk.n_segs + kWaves - 1) / kWaves;           // at most kMaxWalkers, fewer than the grid
         if (blockIdx.x >= walkers) return;
         u32* const fkey = s_fkey + wave * kFound;
         u32* const fidx = s_fidx + wave * kFound;
         auto post = [&](u32 at, u32 key, u32 idx) {
-            if (at < kListRanked) st_dev64(w.picked + at, kPicked | (static_cast<u64>(key) << 32) | idx);
+            if (at < kListFound) st_dev64(w.picked + at, kPicked | (static_cast<u64>(key) << 32) | idx);
         };
         u32 n_found = 0;                                   // uniform
         list_walk_own(w, rk, find.cnt, blockIdx.x * kWaves + wave, gridDim.x * kWaves, [&](bool there, u32 key, u32 idx) {

@@ -185,3 +185,10 @@ def test_threshold_bins_about_as_large_as_their_room(n, ties):
         res = P.condensa_prune(up([w]), [k / n], theta_f16=True)
         torch.cuda.synchronize()
         check_prune_against_oracle(res, oracle.prune([w], [k / n], P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1, f"n={n} ties={ties} k={k}")
+
+
+def test_a_population_whose_samplers_take_several_units():
+    w = np.random.default_rng(26).standard_normal((1 << 26) + 4099).astype(np.float32)
+    res = P.condensa_prune(up([w]), [0.6])
+    torch.cuda.synchronize()
+    check_prune_against_oracle(res, oracle.prune([w], [0.6], P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1)
