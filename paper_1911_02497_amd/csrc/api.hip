@@ -1581,9 +1581,11 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
             // every structure one contiguous row (filters, neurons) of some length: staged, coalesced reads
             constexpr u64 kFewRowsMax = 32768;           // up to 1024 workgroups of kFewRows rows
             bool rows = tb.N / tb.F >= 16;
+            bool rows16 = true;                          // ... and every row 16-byte aligned (k_struct_sumsq_rows)
             for (int t = 0; t < n_tensors && rows; ++t) {
                 const TensorDesc& d = tb.td[t];
                 if (d.n > 0 && !(d.d[1] == 1 && d.d[2] == 1 && d.b[0] == 1 && d.b[3] == d.d[3])) rows = false;
+                if (d.n > 0 && (d.d[3] % 4 != 0 || !aligned16(d.w))) rows16 = false;
             }
             // every tensor a matrix tiled exactly by 2-D blocks of one width of 4, 8, 16 or 32, rows 16-byte aligned
             u32 tile_w = 0;
@@ -1604,10 +1606,11 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
             else if (fused)
                 hipLaunchKernelGGL((k_struct_tiles_fused<64>), dim3(static_cast<unsigned>((tb.F + 63) / 64)), dim3(64), 0, st, a, sw, sumsq_dev, norms_dev);
             else if (rows && tb.F <= 512 * kFewRows)
-                hipLaunchKernelGGL((k_struct_sumsq_rows_few<true>), dim3(static_cast<unsigned>((tb.F + kFewRows - 1) / kFewRows)), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
+                hipLaunchKernelGGL((k_struct_sumsq_rows_few<true, kFewRows>), dim3(static_cast<unsigned>((tb.F + kFewRows - 1) / kFewRows)), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
             else if (rows && tb.F <= kFewRowsMax)
-                hipLaunchKernelGGL((k_struct_sumsq_rows_few<false>), dim3(static_cast<unsigned>((tb.F + kFewRows - 1) / kFewRows)), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
-            else if (rows) hipLaunchKernelGGL(k_struct_sumsq_rows, dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
+                hipLaunchKernelGGL((k_struct_sumsq_rows_few<false, kFewRows>), dim3(static_cast<unsigned>((tb.F + kFewRows - 1) / kFewRows)), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
+            else if (rows && rows16) hipLaunchKernelGGL(k_struct_sumsq_rows, dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
+            else if (rows) hipLaunchKernelGGL((k_struct_sumsq_rows_few<false, kManyRows>), dim3(static_cast<unsigned>((tb.F + kManyRows - 1) / kManyRows)), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
             else if (tiles && tile_w == 4)  hipLaunchKernelGGL((k_struct_sumsq_tiles<1>), dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
             else if (tiles && tile_w == 8)  hipLaunchKernelGGL((k_struct_sumsq_tiles<2>), dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
             else if (tiles && tile_w == 16) hipLaunchKernelGGL((k_struct_sumsq_tiles<4>), dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);

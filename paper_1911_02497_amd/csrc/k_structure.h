@@ -210,37 +210,34 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_tiles(StructArgs a, dou
 }
 
 // Row structures (filters, neurons: structure s of a tensor is the contiguous run [s L, (s+1) L) of its
-// memory): thread-per-structure loads would touch one cache line per lane, so the workgroup stages
-// 32-element pieces of its 256 rows through LDS with coalesced 128-bit loads (8 lanes per row piece) and
+// memory), many of them and every row 16-byte aligned: thread-per-structure loads would touch one cache line per lane, so the
+// workgroup stages 32-element pieces of its 256 rows through LDS with coalesced 128-bit loads (8 lanes per row piece) and
 // every thread then adds its own row's piece in memory order -- the same additions in the same order as
-// k_struct_sumsq.  Rows are padded to 33 words so that the per-thread reads hit distinct banks.
+// k_struct_sumsq.  Rows are padded to 36 words, so that the 128-bit accesses of either side spread over the banks.  Bound by
+// memory (6.9 TB/s for 262 144 rows of 4608).  The last workgroup repeats the last row instead of guarding every load: 56 368 rows
+// of 3104 took 280 us when it did, now 128.
 constexpr int kRowTile = 32;
 
 __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows(StructArgs a, double* sumsq, float* norms) {
-    __shared__ float s_tile[kBlock][kRowTile + 1];
+    __shared__ __align__(16) float s_tile[kBlock][kRowTile + 4];
     __shared__ const float* s_row[kBlock];
     __shared__ u32 s_len[kBlock];
-    __shared__ u32 s_maxlen, s_minlen, s_aligned;
+    __shared__ u32 s_maxlen, s_minlen;
     const int tid = threadIdx.x;
     const u64 u = static_cast<u64>(blockIdx.x) * kBlock + tid;
-    if (tid == 0) { s_maxlen = 0; s_minlen = 0xFFFFFFFFu; s_aligned = 1; }
+    if (tid == 0) { s_maxlen = 0; s_minlen = 0xFFFFFFFFu; }
     __syncthreads();
-    u32 len = 0;
-    const float* row = nullptr;
-    if (u < a.F) {
-        const int t = tensor_of_struct(a.td, a.n_tensors, u);
-        const TensorDesc& td = a.td[t];
-        len = td.d[3];
-        row = td.w + (u - td.struct_start) * len;
-    }
-    s_row[tid] = row;
+    const u64 mine = u < a.F ? u : a.F - 1;               // past the end: the last row once more, which is not stored
+    const int t = tensor_of_struct(a.td, a.n_tensors, mine);
+    const TensorDesc& td = a.td[t];
+    const u32 len = td.d[3];
+    s_row[tid] = td.w + (mine - td.struct_start) * len;
     s_len[tid] = len;
     atomicMax(&s_maxlen, len);
-    atomicMin(&s_minlen, len);                            // 0 when the last workgroup is ragged
-    if (row && (reinterpret_cast<uintptr_t>(row) & 15u)) atomicAnd(&s_aligned, 0u);
+    atomicMin(&s_minlen, len);
     __syncthreads();
     const u32 maxlen = s_maxlen;
-    const u32 fast_end = s_aligned ? (s_minlen / kRowTile) * kRowTile : 0;   // pieces below it: unguarded loads
+    const u32 fast_end = (s_minlen / kRowTile) * kRowTile;                   // pieces below it: unguarded loads
     const int seg = tid & 7, sub = tid >> 3;              // 8 lanes per row piece, 32 rows per pass
     double acc = 0.0;
     // Pieces below fast_end are fetched one iteration ahead, so that the loads of piece i+1 are in flight
@@ -254,8 +251,7 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows(StructArgs a, doub
         if (cb < fast_end) {
 #pragma unroll
             for (int pass = 0; pass < 8; ++pass) {
-                float* dst = &s_tile[pass * 32 + sub][seg * 4];
-                dst[0] = v[pass].x; dst[1] = v[pass].y; dst[2] = v[pass].z; dst[3] = v[pass].w;
+                *reinterpret_cast<float4*>(&s_tile[pass * 32 + sub][seg * 4]) = v[pass];
             }
             if (cb + kRowTile < fast_end) {
 #pragma unroll
@@ -280,10 +276,7 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows(StructArgs a, doub
             const u32 m = (len - cb < static_cast<u32>(kRowTile)) ? len - cb : static_cast<u32>(kRowTile);
             if (m == kRowTile) {
 #pragma unroll
-                for (int j = 0; j < kRowTile; ++j) {
-                    const double x = static_cast<double>(s_tile[tid][j]);
-                    acc = acc + x * x;
-                }
+                for (int j = 0; j < kRowTile; j += 4) acc = add_squares(acc, *reinterpret_cast<const float4*>(&s_tile[tid][j]));
             } else {
                 for (u32 j = 0; j < m; ++j) {
                     const double x = static_cast<double>(s_tile[tid][j]);
@@ -300,39 +293,49 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows(StructArgs a, doub
     }
 }
 
-// The same aggregation for calls with few row structures (a CIFAR ResNet's 2 032 filters, a VGG's 5 504):
-// 256 rows per workgroup would leave most of the chip idle and every 32-element piece costs a load
-// latency, so here a workgroup takes kFewRows rows and stages kFewTile elements of each per step: one
-// wavefront fetches one row's piece per load instruction (1 KB contiguous), eight loads per thread are in
-// flight, the next two pieces are requested before the current one is added up, and the first kFewRows threads
-// add their rows' pieces in memory order.  That chain bounds a call of few rows: 15 ns per element while its threads also
-// converted to binary64 (a quarter-rate instruction), so the staging threads convert and
+// The same aggregation for calls with few row structures (a CIFAR ResNet's 2 032 filters, a VGG's 5 504) and for rows that are not
+// 16-byte aligned: 256 rows per workgroup would leave most of the chip idle and every 32-element piece costs a load
+// latency (and, not aligned, two lines for each), so here a workgroup takes ROWS rows and stages 8192 / ROWS elements of each per
+// step: eight loads per thread are in flight, the next two pieces are requested before the current one is added up, and the first
+// ROWS threads add their rows' pieces in memory order.  That chain bounds a call of few rows: 15 ns per element while its threads
+// also converted to binary64 (a quarter-rate instruction), so the staging threads convert and
 // square (the square of a binary32 is exact in binary64).  SQUARED: that form, two workgroups to a compute unit; beyond two
-// of them each, binary32 tiles let four be resident, and the sweep is bound by memory (28 186 rows of 7767: a whole call
-// 657 us with these, 815 with the others).  Rows of any length and alignment: a float4 that lies inside
-// an aligned row is one 128-bit load, anything else is fetched element by element.
-constexpr int kFewRows = 32;
-constexpr int kFewTile = 256;
+// of them each, binary32 tiles let four be resident.  Beyond 32 768 rows, 64 of them keep all lanes of the adding wavefront busy
+// (86 070 rows of 2059: 171 us; 256 rows a workgroup 191; 320 000 of 331: 106 and 129).  Choosing another adding wavefront in
+// every workgroup changed nothing.
+// Rows of any length and alignment: loads of sixteen bytes need no more than the alignment of a binary32, and every lane makes
+// its load.  Element by element where a row was not aligned, behind branches, 10 518 rows of 7758 took 230 us, now 119; 28 184 of
+// 7767: 314 and 221; 86 070 of 2059: 872 and 171; 320 000 of 331: 344 and 106.
+constexpr int kFewRows = 32, kManyRows = 64;
 constexpr int kFewStarts = 512;
 
-template <bool SQUARED>
-__global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows_few(StructArgs a, double* sumsq, float* norms) {
+// Four elements of a row.  Global loads of sixteen bytes need no more than the alignment of a binary32 here.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ inline float4 ld4_any(const float* p) {
+    const f32x4_any t = *reinterpret_cast<const f32x4_any*>(p);
+    return make_float4(t.x, t.y, t.z, t.w);
+}
+template <bool SQUARED, int ROWS>
+__global__ __launch_bounds__(kBlock, SQUARED ? 2 : 4) void k_struct_sumsq_rows_few(StructArgs a, double* sumsq, float* norms) {
     using Staged = typename std::conditional<SQUARED, double, float>::type;
-    __shared__ __align__(16) Staged s_tile[kFewRows][kFewTile + (SQUARED ? 2 : 1)];
-    __shared__ const float* s_row[kFewRows];
-    __shared__ u32 s_len[kFewRows];
-    __shared__ u32 s_vec[kFewRows];
+    using Words = typename std::conditional<SQUARED, double2, float>::type;       // read from a tile at once
+    constexpr int kTile = 8192 / ROWS;
+    __shared__ __align__(16) Staged s_tile[ROWS][kTile + (SQUARED ? 2 : 1)];
+    __shared__ const float* s_row[ROWS];
+    __shared__ u32 s_last[ROWS];                                      // offset of the last four elements that a lane may load, and 4
     __shared__ u32 s_maxlen;
     __shared__ u64 s_start[kFewStarts];
     const int tid = threadIdx.x;
-    const u64 u = static_cast<u64>(blockIdx.x) * kFewRows + tid;          // the row of thread tid < kFewRows
+    const u64 u = static_cast<u64>(blockIdx.x) * ROWS + tid;              // the row of thread tid < ROWS
     if (tid == 0) s_maxlen = 0;
     const bool starts = a.n_tensors <= kFewStarts;                        // the search in LDS: its steps depend on one another
     if (starts) for (int t = tid; t < a.n_tensors; t += kBlock) s_start[t] = a.td[t].struct_start;
     __syncthreads();
     u32 len = 0;
-    if (tid < kFewRows) {
-        const float* row = nullptr;
+    const float* tiny = nullptr;                                          // a row of a tensor of fewer than four elements
+    if (tid < ROWS) {
+        const float* row = reinterpret_cast<const float*>(a.td);          // (any sixteen bytes)
+        long long last = 0;                                               // at least -3
         if (u < a.F) {
             int t = 0;
             if (starts) {
@@ -345,35 +348,42 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows_few(StructArgs a, 
                 t = tensor_of_struct(a.td, a.n_tensors, u);
             }
             const TensorDesc& td = a.td[t];
+            const u64 at = (u - td.struct_start) * td.d[3];
             len = td.d[3];
-            row = td.w + (u - td.struct_start) * len;
+            if (td.n >= 4) {
+                row = td.w + at;
+                last = static_cast<long long>(td.n) - 4 - static_cast<long long>(at);      // the tensor's last four
+                last = last < static_cast<long long>(len) - 1 ? last : static_cast<long long>(len) - 1;
+            } else {
+                tiny = td.w + at;
+            }
         }
         s_row[tid] = row;
-        s_len[tid] = len;
-        s_vec[tid] = (row && (reinterpret_cast<uintptr_t>(row) & 15u) == 0) ? 1u : 0u;
+        s_last[tid] = static_cast<u32>(last + 4);
         atomicMax(&s_maxlen, len);
     }
     __syncthreads();
     const u32 maxlen = s_maxlen;
-    const int col = (tid & 63) * 4, wave = tid >> 6;                      // wavefront `wave` fetches rows 4 p + wave
+    constexpr int kLanes = kTile / 4;                                  // that fetch a row's piece
+    const int col = (tid % kLanes) * 4, row0 = tid / kLanes;              // this thread fetches for rows row0 + 4 p (64 lanes), ...
+    auto row_of = [&](int p) { return p * (kBlock / kLanes) + row0; };
+    // Every lane loads, without a branch (loads behind one are waited for before the next are made): where four elements would pass
+    // the tensor's end its last four, moved into place when they are staged.  What lies past a row's end is staged and not added;
+    // the lanes there all load from one place.
     auto fetch = [&](u32 cb, float4 (&v)[8]) {
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
-            const int st = p * 4 + wave;
-            const u32 L = s_len[st];
-            const u32 x = cb + col;
-            const float* src = s_row[st];
-            float4 t = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (x + 4 <= L && s_vec[st]) {
-                t = *reinterpret_cast<const float4*>(src + x);
-            } else if (x < L) {
-                t.x = src[x];
-                if (x + 1 < L) t.y = src[x + 1];
-                if (x + 2 < L) t.z = src[x + 2];
-                if (x + 3 < L) t.w = src[x + 3];
-            }
-            v[p] = t;
+            const int st = row_of(p);
+            const u32 x = cb + col + 4u, last = s_last[st];
+            v[p] = ld4_any(s_row[st] + static_cast<int>((x < last ? x : last) - 4u));
         }
+    };
+    auto in_place = [&](u32 cb, int st, const float4& v) {
+        const u32 x = cb + col + 4u, last = s_last[st], beyond = x > last ? x - last : 0u;
+        float4 t = v;
+        if (beyond & 1u) t = make_float4(t.y, t.z, t.w, t.w);
+        if (beyond & 2u) t = make_float4(t.z, t.w, t.w, t.w);
+        return t;
     };
     auto exact_square = [](float x) { const double d = static_cast<double>(x); return d * d; };      // 48 bits: no rounding
     auto square_of = [&](Staged x) { if constexpr (SQUARED) return x; else return exact_square(x); };
@@ -381,33 +391,39 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows_few(StructArgs a, 
     auto step = [&](u32 cb, float4 (&v)[8]) {                             // one piece: stage, request the one after the next, add
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
+            const float4 t = in_place(cb, row_of(p), v[p]);
             if constexpr (SQUARED) {
-                double2* dst = reinterpret_cast<double2*>(&s_tile[p * 4 + wave][col]);
-                dst[0] = make_double2(exact_square(v[p].x), exact_square(v[p].y));
-                dst[1] = make_double2(exact_square(v[p].z), exact_square(v[p].w));
+                double2* dst = reinterpret_cast<double2*>(&s_tile[row_of(p)][col]);
+                dst[0] = make_double2(exact_square(t.x), exact_square(t.y));
+                dst[1] = make_double2(exact_square(t.z), exact_square(t.w));
             } else {
-                float* dst = &s_tile[p * 4 + wave][col];
-                dst[0] = v[p].x; dst[1] = v[p].y; dst[2] = v[p].z; dst[3] = v[p].w;
+                float* dst = &s_tile[row_of(p)][col];
+                dst[0] = t.x; dst[1] = t.y; dst[2] = t.z; dst[3] = t.w;
             }
         }
-        if (cb + 2 * kFewTile < maxlen) fetch(cb + 2 * kFewTile, v);
+        if (cb + 2 * kTile < maxlen) fetch(cb + 2 * kTile, v);
         __syncthreads();
-        if (tid < kFewRows && len > cb) {
-            const u32 m = (len - cb < static_cast<u32>(kFewTile)) ? len - cb : static_cast<u32>(kFewTile);
+        if (tid < ROWS && len > cb && !tiny) {
+            const u32 m = (len - cb < static_cast<u32>(kTile)) ? len - cb : static_cast<u32>(kTile);
+            const Words* const words = reinterpret_cast<const Words*>(s_tile[tid]);
+            constexpr u32 kPer = sizeof(Words) / sizeof(Staged), kStep = 16, kAhead = kStep / kPer;
             u32 j = 0;
-            if (m >= 16) {                                // sixteen LDS reads in flight while the sixteen before are added up
-                Staged t[16];
+            if (m >= kStep) {                             // some elements are on their way from LDS while those before are added up
+                Words t[kAhead];
 #pragma unroll
-                for (int k = 0; k < 16; ++k) t[k] = s_tile[tid][k];
-                for (; j + 16 <= m; j += 16) {
-                    Staged next[16];
-                    const u32 ahead = j + 32 <= m ? j + 16 : j;
+                for (u32 k = 0; k < kAhead; ++k) t[k] = words[k];
+                for (; j + kStep <= m; j += kStep) {
+                    Words next[kAhead];
+                    const u32 ahead = (j + 2 * kStep <= m ? j + kStep : j) / kPer;
 #pragma unroll
-                    for (int k = 0; k < 16; ++k) next[k] = s_tile[tid][ahead + k];
+                    for (u32 k = 0; k < kAhead; ++k) next[k] = words[ahead + k];
 #pragma unroll
-                    for (int k = 0; k < 16; ++k) acc = acc + square_of(t[k]);
+                    for (u32 k = 0; k < kAhead; ++k) {
+                        if constexpr (SQUARED) acc = acc + t[k].x, acc = acc + t[k].y;
+                        else                   acc = acc + exact_square(t[k]);
+                    }
 #pragma unroll
-                    for (int k = 0; k < 16; ++k) t[k] = next[k];
+                    for (u32 k = 0; k < kAhead; ++k) t[k] = next[k];
                 }
             }
             for (; j < m; ++j) acc = acc + square_of(s_tile[tid][j]);
@@ -416,12 +432,13 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows_few(StructArgs a, 
     };
     float4 va[8], vb[8];
     if (maxlen > 0) fetch(0, va);
-    if (maxlen > kFewTile) fetch(kFewTile, vb);
-    for (u32 cb = 0; cb < maxlen; cb += 2 * kFewTile) {    // uniform
+    if (maxlen > kTile) fetch(kTile, vb);
+    for (u32 cb = 0; cb < maxlen; cb += 2 * kTile) {    // uniform
         step(cb, va);
-        if (cb + kFewTile < maxlen) step(cb + kFewTile, vb);
+        if (cb + kTile < maxlen) step(cb + kTile, vb);
     }
-    if (tid < kFewRows && u < a.F) {
+    if (tiny) for (u32 j = 0; j < len; ++j) acc = acc + exact_square(tiny[j]);
+    if (tid < ROWS && u < a.F) {
         a.keys[u] = static_cast<u64>(__double_as_longlong(acc)) & 0x7FFFFFFFFFFFFFFFull;
         if (sumsq) sumsq[u] = acc;
         if (norms) norms[u] = static_cast<float>(sqrt(acc));

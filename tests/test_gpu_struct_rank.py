@@ -89,3 +89,14 @@ def test_sums_of_many_rows(rows):
     rng = np.random.default_rng(rows)
     w = rng.standard_normal((rows, 277)).astype(np.float32)
     _compare(neuron_prune(up([w]), 0.2, P.SCOPE_GLOBAL), oracle.neuron_prune([w], 0.2, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], f"rows={rows}")
+
+
+@pytest.mark.parametrize("shapes", [
+    ((33, 40), (1, 1), (1, 2), (3, 1), (1, 3), (40, 64)),               # tensors of fewer than four elements
+    ((32769, 36), (7, 64), (300, 20)),                                  # aligned, several lengths in a workgroup, the last one ragged
+    ((33001, 19), (65, 17), (5, 131), (1, 18)),                         # not aligned, the last rows end within four elements of their tensor
+])
+def test_sums_of_rows_of_several_tensors(shapes):
+    rng = np.random.default_rng(len(shapes))
+    ts = [rng.standard_normal(s).astype(np.float32) for s in shapes]
+    _compare(neuron_prune(up(ts), 0.4, P.SCOPE_GLOBAL), oracle.neuron_prune(ts, 0.4, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, ts, f"{shapes}")
