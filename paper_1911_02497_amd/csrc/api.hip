@@ -724,9 +724,12 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
     u64 base = 0;
     u32 first = 0;
     *shape = ListShape{};
-    u64 asked = 0;                                         // sampling workgroups
-    for (size_t g = 0; per_tensor && g < n_groups; ++g) asked += list_groups(tb.td[g].n, J, true, cfg);
-    const u32 most = asked > kSampleResident && cfg[CONDENSA_OPT_SAMPLE_LOG2] <= 0 ? 32u : static_cast<u32>(kListMaxW);
+    u32 most = static_cast<u32>(kListMaxW);                // sampling workgroups of a population
+    for (u64 asked; per_tensor && most > 32 && cfg[CONDENSA_OPT_SAMPLE_LOG2] <= 0; most /= 2) {
+        asked = 0;
+        for (size_t g = 0; g < n_groups; ++g) asked += std::min(list_groups(tb.td[g].n, J, true, cfg), most);
+        if (asked <= kSampleResident) break;
+    }
     for (size_t g = 0; g < n_groups; ++g) {
         const u64 n = per_tensor ? tb.td[g].n : tb.N;
         const u32 w = std::min(list_groups(n, J, per_tensor, cfg), most);

@@ -68,7 +68,8 @@ inline u32 list_sample_groups(u64 n, int J, bool per_tensor) {
     return kListMaxW;
 }
 // Sampling workgroups that are resident at once (two to a compute unit, less those that begin the call and bound the windows): what
-// goes beyond that waits for another round of 8 us, so PER_TENSOR populations that ask for more get 32 each.
+// goes beyond that waits for another round of 8 us, so PER_TENSOR populations that ask for more get half as many at most, and again,
+// down to 32 each.
 constexpr u32 kSampleResident = 480;
 // Entries of a ranking's list: some four times what its window is expected to hold (list_sample_groups), every element of a
 // tiny one.
