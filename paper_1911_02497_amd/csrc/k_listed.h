@@ -1,4 +1,4 @@
-// Listed windows: the selection of ordinary calls (the rule is want_list, either scope) in three to seven launches.
+// Listed windows: the selection of ordinary calls (the rule is want_list, either scope) in three to seven launches (one ranking: three).
 //
 // Up to some ten million weights a call is bound by its dependent launches (about 4.5 us each, however little they
 // do) and by how often it reads the weights, which the three histogram sweeps of the radix levels make four times.
