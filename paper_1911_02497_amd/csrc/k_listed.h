@@ -2932,12 +2932,22 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
             list_fix_store<LC, PQ, 1>(a, loads, keep1, on1, &nz);
         }
         if (!nnz) return;
-        add_corrections(nz, &a.ctl->nnz_delta);
-        wait_dev();
+        // one update a workgroup: with one a wavefront, up to 1024 took turns at the counter (44 M weights: 31.6 us
+        // for this launch, now 22.1)
+        const u32 corrections = wave_sum_u32(static_cast<u32>(nz));                    // modulo 2^32: the workgroup's sum is small
+        if (lane == 0) s_found[wave] = corrections;
         __syncthreads();
-        if (tid == 0) s_found[0] = add_dev(w.ended, 1u);
+        if (tid == 0) {
+            u32 sum = 0;
+#pragma unroll
+            for (u32 i = 0; i < kWaves; ++i) sum += s_found[i];
+            if (sum != 0)
+                __hip_atomic_fetch_add(&a.ctl->nnz_delta, static_cast<u64>(static_cast<long long>(static_cast<int>(sum))), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            wait_dev();                                    // it is there before this workgroup counts as done
+            s_found[kWaves] = add_dev(w.ended, 1u);
+        }
         __syncthreads();
-        if (s_found[0] + 1 != walkers) return;             // uniform: the last one adds up
+        if (s_found[kWaves] + 1 != walkers) return;        // uniform: the last one adds up
         const u32 codes = sweep_codes();
         if (tid == 0) *w.nnz_out = codes + ld_dev64(&a.ctl->nnz_delta);
         return;
