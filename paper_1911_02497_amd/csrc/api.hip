@@ -19,6 +19,7 @@ namespace condensa {
 
 std::atomic<int> g_last_hip_error{0};
 std::atomic<uint64_t> g_launches{0};
+static thread_local u32 t_force = 0;
 
 // ---- configuration ---------------------------------------------------------------------------------
 
@@ -915,9 +916,11 @@ static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* w
         return CONDENSA_OK;
     }
     if (n_slots == 1) {
-        if (LC && rq.pq) hipLaunchKernelGGL((k_list_resolve<LC, VEC, LC>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
-        else             hipLaunchKernelGGL((k_list_resolve<LC, VEC, false>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
-        CONDENSA_LAUNCH_CHECK();
+        for (int late = 0; late <= ((t_force & kForceLate) ? 1 : 0); ++late) {
+            if (LC && rq.pq) hipLaunchKernelGGL((k_list_resolve<LC, VEC, LC>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
+            else             hipLaunchKernelGGL((k_list_resolve<LC, VEC, false>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
+            CONDENSA_LAUNCH_CHECK();
+        }
         return CONDENSA_OK;
     }
     if constexpr (!LC) {                                   // (an L-C step has one ranking)
@@ -2154,5 +2157,7 @@ int condensa_last_hip_error(void) { return g_last_hip_error.load(); }
 uint64_t condensa_launch_count(void) { return g_launches.load(); }
 
 int condensa_version(void) { return 200; }
+
+void condensa_test_force(unsigned what) { t_force = what; }      // host.h: for tests
 
 }  // extern "C"

@@ -18,6 +18,12 @@ namespace condensa {
 extern std::atomic<int> g_last_hip_error;
 extern std::atomic<uint64_t> g_launches;        // kernels enqueued since the library was loaded (diagnostic)
 
+// What a test has the calls of its own thread go through although the device is idle (condensa_test_force, not part of the
+// interface; 0: nothing).  All of it can happen by itself where other streams hold the chip, and no result depends on it.
+enum : u32 {
+    kForceLate = 1,        // the workgroups of k_list_resolve start once more when all of its work is done
+};
+
 // The knobs of one call, resolved once at the entry point: the caller's condensa_config, or the
 // process-wide defaults when it passes NULL.  Everything below the entry point reads this copy only.
 struct Config {

@@ -2847,7 +2847,9 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
         if (lane == 0 && sum != 0)
             __hip_atomic_fetch_add(to, static_cast<u64>(static_cast<long long>(static_cast<int>(sum))), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    if (slot.state != kSelecting) {                        // uniform: k == 0, nothing is kept and the sweep kept nothing
+    // Nothing is kept, and the sweep kept nothing.  Not by slot.state: that is written in this launch, and a workgroup that starts
+    // after the others are done would find it changed.
+    if (k == 0) {                                          // uniform
         if (blockIdx.x != 0) return;
         if (nnz) { const u32 codes = sweep_codes(); if (tid == 0) *w.nnz_out = codes; }
         if (tid == 0) *results = select_record(slot, false, 0, 0, 0, 0, slot.path);
