@@ -808,6 +808,7 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const L
     w.nnz_out = rq.nnz_out;
     w.margin16 = static_cast<int>(cfg[CONDENSA_OPT_WINDOW_MARGIN]);
     w.write = rq.write ? 1 : 0;
+    w.force = t_force;
     return w;
 }
 

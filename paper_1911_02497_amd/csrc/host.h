@@ -22,6 +22,7 @@ extern std::atomic<uint64_t> g_launches;        // kernels enqueued since the li
 // interface; 0: nothing).  All of it can happen by itself where other streams hold the chip, and no result depends on it.
 enum : u32 {
     kForceLate = 1,        // the workgroups of k_list_resolve start once more when all of its work is done
+    kForceNoSample = 2,    // the workgroups that bound windows give up on the samples without a look
 };
 
 // The knobs of one call, resolved once at the entry point: the caller's condensa_config, or the

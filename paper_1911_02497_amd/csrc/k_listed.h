@@ -32,6 +32,7 @@
 // C step and the multiplier update), Results (up to ten samples per search share a pass).
 #pragma once
 #include <type_traits>
+#include "host.h"
 #include "k_apply.h"
 #include "k_small.h"
 #include "k_window.h"
@@ -200,6 +201,7 @@ struct ListArgs {
     u64* nnz_out;
     int margin16;
     int write;             // 1: the sweep writes the outputs.  0: selection only, an apply sweep follows
+    u32 force;             // kForce...
 };
 
 // What workgroups of one launch hand to each other is written and read with device-scope operations.
@@ -548,8 +550,11 @@ static_assert(sizeof(BeginSampleArgs) + sizeof(ListArgs) <= 3584, "kernel argume
 // times as much, and took 1.8 us to find.
 // WAIT: the sampling workgroups belong to the same launch.  They come before this one in the grid and wait for nobody; their
 // words are there when they carry the call's tag (a word left by something else that looks the same would only misplace the
-// window).  In a launch of its own this took 4.9 us and 11 for ten densities.
+// window).  In a launch of its own this took 4.9 us and 11 for ten densities.  The wait is bounded: where several such launches share
+// the chip, the workgroups that wait may hold the places that others' sampling workgroups need.  Who gives up leaves the ranking to
+// list_fallback, as a crowded one.
 constexpr int kBoundsThreads = 64 * kMaxJ;
+constexpr u32 kBoundsPolls = 8192;               // some 10 ms: longer than what this library's other kernels hold the chip for
 __device__ inline float wave_sum_f32(float v) {            // in every lane
     auto add = [](float x, u32 from) { return x + __uint_as_float(from); };
     v = add(v, dpp_or_zero<0x111, 0xF>(__float_as_uint(v)));
@@ -568,7 +573,8 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
     if (j < J) {
         constexpr int kPer = kListMaxW / 64;
         u32 v[3][kPer];                          // upper bound, lower bound, estimate
-        for (;;) {
+        bool given_up = WAIT && (w.force & kForceNoSample);
+        for (u32 polls = 0; !given_up; ++polls) {          // uniform
             bool there = true;
             u64 x[3][kPer];
 #pragma unroll
@@ -584,7 +590,12 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
                     v[i][q] = static_cast<u32>(x[i][q]);
                 }
             if (!WAIT || __all(there)) break;
+            given_up = polls == kBoundsPolls;
             __builtin_amdgcn_s_sleep(1);
+        }
+        if (given_up) {
+#pragma unroll
+            for (int q = 0; q < 3 * kPer; ++q) v[q / kPer][q % kPer] = 0;
         }
         const u32 ref = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(v[2][0]), 0)) & ~kListCrowded;
         u32 word[3], crowded = 0;
@@ -619,6 +630,7 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
         word[0] = word[0] ? 0x7FFFFFFFu : (hi < 0x7FFFFFFFu - half ? hi + half : 0x7FFFFFFFu);
         word[1] = word[1] || lo < half ? 0u : lo - half;
         word[2] = at(mean[2]);
+        if (given_up) { word[0] = 0x7FFFFFFFu; word[1] = 0; crowded = kListCrowded; }
         if (lane == 0) {
             const ListWin x = list_window_of(word, nothing_of(j), crowded);
             s_win[j] = x;

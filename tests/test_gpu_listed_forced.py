@@ -1,5 +1,5 @@
 """GPU parity of the listed windows through events that an idle device does not show by itself: workgroups that start after the
-others are done.  Every kernel of these calls ends as in any other call.  Against the oracle, bit for bit."""
+others are done, waits that run out.  Every kernel of these calls ends as in any other call.  Against the oracle, bit for bit."""
 import contextlib
 
 import numpy as np
@@ -12,7 +12,7 @@ from gpu_util import assert_bits_equal, assert_select_equal, check_prune_against
 
 pytestmark = pytest.mark.gpu
 
-LATE = 1                                          # csrc/host.h
+LATE, NO_SAMPLE = 1, 2                            # csrc/host.h
 
 
 @contextlib.contextmanager
@@ -66,3 +66,18 @@ def test_workgroups_that_start_when_the_ranking_is_done(kind, density, config, n
     """Records and counts of what the lists leave open stay as they were written."""
     with forced(LATE):
         _check_all_calls(_weights(kind, n), density, config)
+
+
+@pytest.mark.parametrize("sizes", [[200003], [(1 << 21) + 3, 777], [300001, 9, 700000, 0, 66000]], ids=str)
+@pytest.mark.parametrize("kind", ["normal", "zeros"])
+def test_windows_whose_samples_do_not_come(sizes, kind):
+    """The whole population is searched, beside populations with a lone sampling workgroup, which has nobody to wait for."""
+    arrs = [_weights(kind, n) for n in sizes]
+    for scope in (P.SCOPE_GLOBAL, P.SCOPE_PER_TENSOR):
+        for ds in ([0.1], [0.02, 0.0, 0.1, 0.5, 1.0]):
+            with forced(NO_SAMPLE):
+                res = P.condensa_prune(up(arrs), ds, scope=scope, theta_f16=True)
+            torch.cuda.synchronize()
+            check_prune_against_oracle(res, oracle.prune(arrs, ds, scope), scope, len(arrs), f"{sizes} {kind} {ds}")
+    with forced(NO_SAMPLE):
+        _check_all_calls(arrs[0], 0.1)
