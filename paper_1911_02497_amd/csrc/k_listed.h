@@ -548,6 +548,7 @@ static_assert(sizeof(BeginSampleArgs) + sizeof(ListArgs) <= 3584, "kernel argume
 // draws).  What is far from normal (a threshold between zeros and the rest) can only misplace the window.  Order statistics
 // in their place assumed nothing, but left windows 1.3 times as wide for 256 workgroups and twice for 32, estimates off by 1.25
 // times as much, and took 1.8 us to find.
+// Workgroups whose sample is empty (all of its places are tensors too short to be sampled) have no part in it.
 // WAIT: the sampling workgroups belong to the same launch.  They come before this one in the grid and wait for nobody; their
 // words are there when they carry the call's tag (a word left by something else that looks the same would only misplace the
 // window).  In a launch of its own this took 4.9 us and 11 for ten densities.  The wait is bounded: where several such launches share
@@ -597,40 +598,46 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
 #pragma unroll
             for (int q = 0; q < 3 * kPer; ++q) v[q / kPer][q % kPer] = 0;
         }
-        const u32 ref = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(v[2][0]), 0)) & ~kListCrowded;
-        u32 word[3], crowded = 0;
+        bool drew[kPer];                         // this lane's workgroups whose sample holds anything
+        u32 n_drew = 0, ref = 0;                 // uniform
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            drew[q] = 64u * q + lane < W && (v[2][q] & ~kListCrowded) != kSampleNone;
+            const u64 m = __ballot(drew[q]);
+            if (n_drew == 0 && m != 0) ref = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(v[2][q]), __ffsll(static_cast<long long>(m)) - 1)) & ~kListCrowded;
+            n_drew += static_cast<u32>(__popcll(m));
+        }
+        u32 word[3], crowded = 0, open[3] = {0, 0, 0};     // open: workgroups without such a rank in their sample
         float mean[3], sq = 0.0f;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             float sum = 0.0f;
-            u32 says = 0, open = 0;              // those that say crowded, and those without such a rank in their sample
+            u32 says = 0;                        // those that say crowded
 #pragma unroll
             for (int q = 0; q < kPer; ++q) {
-                const bool mine = 64u * q + lane < W;
                 const u32 key = v[i][q] & ~kListCrowded;
-                says += static_cast<u32>(__popcll(__ballot(mine && (v[i][q] & kListCrowded) != 0)));
-                open += static_cast<u32>(__popcll(__ballot(mine && key == kSampleNone)));
-                const float d = mine ? static_cast<float>(static_cast<int>(key - ref)) : 0.0f;
+                says += static_cast<u32>(__popcll(__ballot(drew[q] && (v[i][q] & kListCrowded) != 0)));
+                open[i] += static_cast<u32>(__popcll(__ballot(drew[q] && key == kSampleNone)));
+                const float d = drew[q] ? static_cast<float>(static_cast<int>(key - ref)) : 0.0f;
                 sum += d;
                 if (i == 2) sq += d * d;
             }
-            mean[i] = wave_sum_f32(sum) / static_cast<float>(W);
-            word[i] = open;
-            if (2 * says > W) crowded = kListCrowded;      // most of the workgroups say so
+            mean[i] = wave_sum_f32(sum) / static_cast<float>(n_drew);
+            if (2 * says > n_drew) crowded = kListCrowded;             // most of the workgroups say so
         }
-        const float n = static_cast<float>(W), var = (wave_sum_f32(sq) - n * mean[2] * mean[2]) / (n - 1.0f);
-        const float z = static_cast<float>(w.margin16) / 16.0f * (1.0f + 8.0f / n);
-        const float off = z * sqrtf(var > 0.0f ? var / n : 0.0f);
+        const float n = static_cast<float>(n_drew), var = (wave_sum_f32(sq) - n * mean[2] * mean[2]) / (n - 1.0f);
+        const float z = static_cast<float>(w.margin16) / 16.0f;
+        const float off = z * (1.0f + 8.0f / n) * sqrtf(var > 0.0f ? var / n : 0.0f);
         auto at = [&](float d) {                 // a key; ref + d may lie outside
             const float least = -static_cast<float>(ref), most = static_cast<float>(0x7FFFFFFFu - ref);
             return d <= least ? 0u : (d >= most ? 0x7FFFFFFFu : ref + static_cast<u32>(static_cast<int>(d)));
         };
         const u32 half = 0x800u;                 // the words' low 12 bits say nothing
         const u32 hi = at(mean[0] + off), lo = at(mean[1] - off);
-        word[0] = word[0] ? 0x7FFFFFFFu : (hi < 0x7FFFFFFFu - half ? hi + half : 0x7FFFFFFFu);
-        word[1] = word[1] || lo < half ? 0u : lo - half;
+        word[0] = open[0] ? 0x7FFFFFFFu : (hi < 0x7FFFFFFFu - half ? hi + half : 0x7FFFFFFFu);
+        word[1] = open[1] || lo < half ? 0u : lo - half;
         word[2] = at(mean[2]);
-        if (given_up) { word[0] = 0x7FFFFFFFu; word[1] = 0; crowded = kListCrowded; }
+        if (given_up || n_drew < 2) { word[0] = 0x7FFFFFFFu; word[1] = 0; crowded = kListCrowded; }
         if (lane == 0) {
             const ListWin x = list_window_of(word, nothing_of(j), crowded);
             s_win[j] = x;

@@ -192,3 +192,23 @@ def test_a_population_whose_samplers_take_several_units():
     res = P.condensa_prune(up([w]), [0.6])
     torch.cuda.synchronize()
     check_prune_against_oracle(res, oracle.prune([w], [0.6], P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1)
+
+
+def test_sampling_workgroups_with_an_empty_sample():
+    """A tensor among so many tensors too short to be sampled that only some of the 32 sampling workgroups meet it: the window is
+    that of these alone, and its list (half of the population) holds it."""
+    rng = np.random.default_rng(27)
+    n_tiny = 8000                                            # 25 of 32 stretches of the population hold weights that are sampled
+    tiny = rng.standard_normal((n_tiny, 4)).astype(np.float32)
+    big = rng.standard_normal(200003).astype(np.float32)
+    arrs = [big] + [t[:3] for t in tiny]
+    dev = up([tiny])[0]
+    config = {"cand_shift": 1, "window_margin": 16}
+    res = P.condensa_prune(up([big]) + [dev[i, :3] for i in range(n_tiny)], [0.5], config=config)
+    torch.cuda.synchronize()
+    want = oracle.prune(arrs, [0.5], P.SCOPE_GLOBAL)
+    rec = P.select_records(res["results"])[0]
+    assert_select_equal(rec, want[0]["select"])
+    assert rec["path"] == 2, "the window was opened by workgroups that sampled nothing"
+    for t in range(0, len(arrs), 97):
+        assert np.array_equal(res["mask"][0][t].cpu().numpy(), want[0]["mask"][t])
