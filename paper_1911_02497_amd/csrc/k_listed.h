@@ -234,11 +234,11 @@ __device__ inline ListWin list_window(u32 hi, u32 lo, u32 mid) {
     return x;
 }
 
-// From the words of list_sample: upper bound, lower bound, estimate (bit 31: crowded).
-__device__ inline ListWin list_window_of(const u32* word, bool nothing, u32 crowded) {
+// From the words of list_sample: upper bound, lower bound, estimate (bit 31: crowded).  marks: kListCrowded.
+__device__ inline ListWin list_window_of(const u32* word, bool nothing, u32 marks) {
     if (nothing) return list_window(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
     ListWin x = list_window(word[0] & ~kListCrowded, word[1] & ~kListCrowded, word[2] & ~kListCrowded);
-    x.bins |= (word[0] | word[1] | word[2] | crowded) & kListCrowded;
+    x.bins |= ((word[0] | word[1] | word[2]) & kListCrowded) | marks;
     return x;
 }
 
@@ -545,10 +545,14 @@ static_assert(sizeof(BeginSampleArgs) + sizeof(ListArgs) <= 3584, "kernel argume
 // Populations with several sampling workgroups, one workgroup here for each, a wavefront a ranking.  The workgroups' keys at
 // the expected rank are as many independent draws around the threshold: their mean estimates it, and the window ends as many
 // standard errors of that mean to either side as the call asks for (a few more when the deviation itself is estimated from few
-// draws).  What is far from normal (a threshold between zeros and the rest) can only misplace the window.  Order statistics
-// in their place assumed nothing, but left windows 1.3 times as wide for 256 workgroups and twice for 32, estimates off by 1.25
-// times as much, and took 1.8 us to find.
-// Workgroups whose sample is empty (all of its places are tensors too short to be sampled) have no part in it.
+// draws).  That holds for draws from something like a normal distribution.  Where they are not -- a model close to its compressed
+// form, whose threshold lies at a gap; weights on a grid; workgroups without such a rank in their sample -- the mean can lie where
+// no keys are, the interval can end before them, or a few draws far off stretch it.  So the share of the draws beyond either end
+// has to be what it is in a normal distribution, give or take three of its deviations (and not nothing).  Else order
+// statistics W/2 -+ z sqrt(W)/2, which assume nothing, take its place.  Elsewhere they would leave windows 1.3 times as wide for 256
+// workgroups and twice for 32, estimates off by 1.25 times as much, and take 1.8 us to find.
+// L-C step of VGG-19 whose kept weights stand apart from the others, at their share: 262 us by the mean alone, 103 so.
+// Workgroups whose sample is empty (all of its places are tensors too short to be sampled) have no part in either.
 // WAIT: the sampling workgroups belong to the same launch.  They come before this one in the grid and wait for nobody; their
 // words are there when they carry the call's tag (a word left by something else that looks the same would only misplace the
 // window).  In a launch of its own this took 4.9 us and 11 for ten densities.  The wait is bounded: where several such launches share
@@ -574,6 +578,10 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
     if (j < J) {
         constexpr int kPer = kListMaxW / 64;
         u32 v[3][kPer];                          // upper bound, lower bound, estimate
+        // what does not depend on the words: shares of the draws that may lie beyond an end
+        const float z = static_cast<float>(w.margin16) / 16.0f, all = static_cast<float>(W), due = 0.5f * erfcf(z * (1.0f + 8.0f / all) * rsqrtf(2.0f * all));
+        const float tolerance = 3.0f * sqrtf(due * (1.0f - due) / all);
+        const float least_beyond = due - tolerance > 0.0f ? due - tolerance : (due * all >= 3.0f ? 1.0f / all : 0.0f), most_beyond = due + tolerance;
         bool given_up = WAIT && (w.force & kForceNoSample);
         for (u32 polls = 0; !given_up; ++polls) {          // uniform
             bool there = true;
@@ -607,7 +615,7 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
             if (n_drew == 0 && m != 0) ref = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(v[2][q]), __ffsll(static_cast<long long>(m)) - 1)) & ~kListCrowded;
             n_drew += static_cast<u32>(__popcll(m));
         }
-        u32 word[3], crowded = 0, open[3] = {0, 0, 0};     // open: workgroups without such a rank in their sample
+        u32 word[3], marks = 0, open = 0;        // open: workgroups without such a rank in their sample
         float mean[3], sq = 0.0f;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
@@ -615,31 +623,67 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
             u32 says = 0;                        // those that say crowded
 #pragma unroll
             for (int q = 0; q < kPer; ++q) {
+                if (64u * q >= W) break;         // uniform
                 const u32 key = v[i][q] & ~kListCrowded;
                 says += static_cast<u32>(__popcll(__ballot(drew[q] && (v[i][q] & kListCrowded) != 0)));
-                open[i] += static_cast<u32>(__popcll(__ballot(drew[q] && key == kSampleNone)));
+                open += static_cast<u32>(__popcll(__ballot(drew[q] && key == kSampleNone)));
                 const float d = drew[q] ? static_cast<float>(static_cast<int>(key - ref)) : 0.0f;
                 sum += d;
                 if (i == 2) sq += d * d;
             }
             mean[i] = wave_sum_f32(sum) / static_cast<float>(n_drew);
-            if (2 * says > n_drew) crowded = kListCrowded;             // most of the workgroups say so
+            if (2 * says > n_drew) marks = kListCrowded;               // most of the workgroups say so
         }
         const float n = static_cast<float>(n_drew), var = (wave_sum_f32(sq) - n * mean[2] * mean[2]) / (n - 1.0f);
-        const float z = static_cast<float>(w.margin16) / 16.0f;
         const float off = z * (1.0f + 8.0f / n) * sqrtf(var > 0.0f ? var / n : 0.0f);
-        auto at = [&](float d) {                 // a key; ref + d may lie outside
-            const float least = -static_cast<float>(ref), most = static_cast<float>(0x7FFFFFFFu - ref);
-            return d <= least ? 0u : (d >= most ? 0x7FFFFFFFu : ref + static_cast<u32>(static_cast<int>(d)));
-        };
-        const u32 half = 0x800u;                 // the words' low 12 bits say nothing
-        const u32 hi = at(mean[0] + off), lo = at(mean[1] - off);
-        word[0] = open[0] ? 0x7FFFFFFFu : (hi < 0x7FFFFFFFu - half ? hi + half : 0x7FFFFFFFu);
-        word[1] = open[1] || lo < half ? 0u : lo - half;
-        word[2] = at(mean[2]);
-        if (given_up || n_drew < 2) { word[0] = 0x7FFFFFFFu; word[1] = 0; crowded = kListCrowded; }
+        u32 above = 0, below = 0;                // draws of the estimate beyond the interval's ends
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            if (64u * q >= W) break;             // uniform
+            const float d = static_cast<float>(static_cast<int>((v[2][q] & ~kListCrowded) - ref)) - mean[2];
+            above += static_cast<u32>(__popcll(__ballot(drew[q] && d > off)));
+            below += static_cast<u32>(__popcll(__ballot(drew[q] && d < -off)));
+        }
+        const u32 fewer = above < below ? above : below, more = above < below ? below : above;
+        const bool even = static_cast<float>(fewer) >= n * least_beyond && static_cast<float>(more) <= n * most_beyond;
+        const bool all_equal = !(var > 0.0f);
+        if (open == 0 && (even || all_equal)) {
+            auto at = [&](float d) {             // a key; ref + d may lie outside
+                const float least = -static_cast<float>(ref), most = static_cast<float>(0x7FFFFFFFu - ref);
+                return d <= least ? 0u : (d >= most ? 0x7FFFFFFFu : ref + static_cast<u32>(static_cast<int>(d)));
+            };
+            const u32 half = 0x800u;             // the words' low 12 bits say nothing
+            const u32 hi = at(mean[0] + off), lo = at(mean[1] - off);
+            word[0] = hi < 0x7FFFFFFFu - half ? hi + half : 0x7FFFFFFFu;
+            word[1] = lo < half ? 0u : lo - half;
+            word[2] = at(mean[2]);
+        } else {
+            const u32 h = n_drew / 2, d = static_cast<u32>(fminf(ceilf(z * 0.5f * sqrtf(n)), static_cast<float>(h)));
+            const u32 pick[3] = {h + d < n_drew ? h + d : n_drew - 1, h > d ? h - 1 - d : 0u, h};
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                word[i] = 0;
+#pragma unroll
+                for (int q = 0; q < kPer; ++q) {
+                    v[i][q] &= ~kListCrowded;
+                    if (i == 1 && v[i][q] == kSampleNone) v[i][q] = 0;
+                    if (!drew[q]) v[i][q] = 0xFFFFFFFFu;
+                }
+            }
+            for (u32 bit = 0x40000000u; bit > 0xFFFu; bit >>= 1)         // the largest keys with at most that many of them below
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    u32 n_below = 0;
+#pragma unroll
+                    for (int q = 0; q < kPer; ++q) n_below += static_cast<u32>(__popcll(__ballot(v[i][q] < (word[i] | bit))));
+                    if (n_below <= pick[i]) word[i] |= bit;
+                }
+            word[0] |= 0xFFFu;                   // the words' low bits (list_sample)
+            word[2] |= 0x800u;
+        }
+        if (given_up || n_drew < 2) { word[0] = 0x7FFFFFFFu; word[1] = 0; marks = kListCrowded; }
         if (lane == 0) {
-            const ListWin x = list_window_of(word, nothing_of(j), crowded);
+            const ListWin x = list_window_of(word, nothing_of(j), marks);
             s_win[j] = x;
             w.win[r0 + j] = x;
         }

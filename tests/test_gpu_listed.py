@@ -212,3 +212,26 @@ def test_sampling_workgroups_with_an_empty_sample():
     assert rec["path"] == 2, "the window was opened by workgroups that sampled nothing"
     for t in range(0, len(arrs), 97):
         assert np.array_equal(res["mask"][0][t].cpu().numpy(), want[0]["mask"][t])
+
+
+@pytest.mark.parametrize("n", [150001, 700001, (1 << 20) + 3, (1 << 22) + 1, (1 << 23) + 5])        # 32, 64 and 256 sampling workgroups
+@pytest.mark.parametrize("kind", ["apart", "few_apart", "near_the_compressed"])
+def test_windows_at_a_gap(n, kind):
+    """Thresholds at the edge of a gap between the kept weights and the others, as a model has that is close to its compressed
+    form: the window still holds them, though the mean of the samples' keys lies where no weights are."""
+    rng = np.random.default_rng(n)
+    kept = rng.random(n) < (0.1 if kind != "few_apart" else 0.003)
+    if kind == "near_the_compressed":
+        w = rng.standard_normal(n).astype(np.float32) * np.float32(0.02)
+        kept = np.abs(w) > 0.0329
+        w = np.where(kept, w, 0) + rng.standard_normal(n) * 2e-4
+    else:
+        w = np.where(kept, 0.05 + 0.05 * rng.random(n), 2e-4 * rng.random(n)) * rng.choice([-1.0, 1.0], n)
+    w = w.astype(np.float32)
+    share = int(kept.sum()) / n
+    for ds in ([share], [share + 0.004], [share, 0.3, 0.5]):
+        res = P.condensa_prune(up([w]), ds)
+        torch.cuda.synchronize()
+        check_prune_against_oracle(res, oracle.prune([w], ds, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1, f"{n} {kind} {ds}")
+        assert [r["path"] for r in P.select_records(res["results"])] == [2] * len(ds), (n, kind, ds)
+    _check_lc([w], [np.zeros_like(w)], share, pq=True)
