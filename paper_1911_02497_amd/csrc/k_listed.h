@@ -1600,8 +1600,9 @@ __device__ inline void list_pick(ListShared& sh, bool from_top, u32 r, u32* bin,
 // `want` 0: the ranking failed.  `n` gathered entries: in sh.key / sh.idx when `in_lds`, else at gkey / gidx.  `nz`: this
 // thread's corrections so far of the count of non-zero codes.  Several workgroups (`shares`) may rank the same ranking:
 // each settles its share of the entries (scattered accesses to six arrays: one workgroup took 21 us over 700 of them), and
-// number 0 writes state and record.  What they read of the ranking's state is never written here.
-template <bool LC, bool PQ, int THREADS>
+// number 0 writes state and record.  What they read of the ranking's state is never written here.  SAME: other workgroups of
+// this launch gathered the entries; their loads pass the caches, so several are in flight at a time.
+template <bool LC, bool PQ, int THREADS, bool SAME>
 __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShared& sh, u32 s, u32 want, u32 n, bool in_lds, int nz,
                                  u32 share, u32 shares, condensa_select* results, int n_groups) {
     const u32 tid = threadIdx.x;
@@ -1615,32 +1616,60 @@ __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShare
     } else if (want != 0) {                                // 0: it failed
         const u32* gkey = w.gkey + static_cast<u64>(s) * w.gather_cap;
         const u32* gidx = w.gidx + static_cast<u64>(s) * w.gather_cap;
+        auto ld_gathered = [](const u32* p) { if constexpr (SAME) return ld_dev(p); else return *p; };
         if (!in_lds && n <= kListRanked) {
-            for (u32 i = tid; i < n; i += THREADS) { sh.key[i] = ld_dev(gkey + i); sh.idx[i] = ld_dev(gidx + i); }
+            for (u32 i = tid; i < n; i += THREADS) { sh.key[i] = ld_gathered(gkey + i); sh.idx[i] = ld_gathered(gidx + i); }
             in_lds = true;
         }
-        auto key_of = [&](u32 i) { return in_lds ? sh.key[i] : ld_dev(gkey + i); };
-        auto idx_of = [&](u32 i) { return in_lds ? sh.idx[i] : ld_dev(gidx + i); };
-        const ListWin win = w.win[s];
-        const u32 bits = win_shift(win);                   // low bits of key - lo that the window's bins leave open
-        const u32 sub = bits > 8 ? bits - 8 : 0;
-        const u32 mask = (1u << (bits - sub)) - 1u;        // at most eight bits
-        if (tid < static_cast<u32>(kListBins)) sh.hist[tid] = 0;
+        auto key_of = [&](u32 i) { return in_lds ? sh.key[i] : ld_gathered(gkey + i); };
+        auto idx_of = [&](u32 i) { return in_lds ? sh.idx[i] : ld_gathered(gidx + i); };
+        auto for_keys = [&](auto&& f) {                    // f(there, i, key) for this thread's entries; called by all lanes
+            constexpr u32 kAhead = SAME ? 8 : 1;
+            for (u32 i0 = 0; i0 < n; i0 += kAhead * THREADS) {           // uniform
+                u32 key[kAhead];
+#pragma unroll
+                for (u32 b = 0; b < kAhead; ++b) { const u32 i = i0 + b * THREADS + tid; key[b] = i < n ? key_of(i) : 0u; }
+#pragma unroll
+                for (u32 b = 0; b < kAhead; ++b) { const u32 i = i0 + b * THREADS + tid; f(i < n, i, key[b]); }
+            }
+        };
         if (tid == 0) sh.r = 0;
         __syncthreads();
-        for (u32 i = tid; i < n; i += THREADS) atomicAdd(&sh.hist[((key_of(i) - win.lo) >> sub) & mask], 1u);
-        __syncthreads();
-        u32 bin, in_bin;
-        list_pick(sh, true, want, &bin, &want, &in_bin);
+        // The threshold is one of the keys from .. from + 2^bits - 1: of the window's bin, or of the gathered keys' range where that
+        // was kept (many may lie in a small part of the bin).  Levels of 256 bins until all pairs of the rest can be compared or
+        // they are equal.  (17 rankings of VGG-19 at a gap, some 20 thousand entries each: 136 us with eight bits of the bin, then radix
+        // levels on the whole key and the index; 57 so.)
+        const ListWin win = w.win[s];
+        u32 bits = win_shift(win), from = 0;
+        if (THREADS != kListThreads && n > kListRanked) {
+            from = ~ld_dev(w.gmaxc + s);
+            bits = 32u - static_cast<u32>(__builtin_clz((ld_dev(w.gmax + s) - from) | 1u));
+        } else {
+            from = win.lo + (((key_of(0) - win.lo) >> bits) << bits);
+        }
+        u32 in_bin = n, bin;
+        do {
+            const u32 sub = bits > 8 ? bits - 8 : 0;
+            if (tid < static_cast<u32>(kListBins)) sh.hist[tid] = 0;
+            __syncthreads();
+            for_keys([&](bool there, u32, u32 key) {
+                const u32 b = (key - from) >> sub;
+                if (in_bin != n)                                  wave_count(sh.hist, there && ((key - from) >> bits) == 0, b);
+                else if (there && ((key - from) >> bits) == 0)    atomicAdd(&sh.hist[b], 1u);
+            });
+            __syncthreads();
+            list_pick(sh, true, want, &bin, &want, &in_bin);
+            from += bin << sub;
+            bits = sub;
+        } while (in_bin > kListPairs && bits > 0);         // uniform
         if (in_bin <= kListPairs) {                        // uniform
-            for (u32 i = tid; i < n; i += THREADS) {
-                const u32 key = key_of(i);
-                if ((((key - win.lo) >> sub) & mask) == bin) {
+            for_keys([&](bool there, u32 i, u32 key) {
+                if (there && ((key - from) >> bits) == 0) {
                     const u32 p = atomicAdd(&sh.r, 1u);
                     sh.pkey[p] = key;
                     sh.pidx[p] = idx_of(i);
                 }
-            }
+            });
             __syncthreads();
             if (tid < in_bin) {
                 const u32 key = sh.pkey[tid], idx = sh.pidx[tid];
@@ -1654,26 +1683,21 @@ __device__ inline void list_rank(const DataArgs& a, const ListArgs& w, ListShare
                 }
                 if (higher + same_before + 1 == want) { sh.T = key; sh.rem = want - higher; sh.n_tie = same; sh.last = idx; }
             }
-        } else {
-            // many share those bits too (ties above all): radix levels on the whole key, then on the index
-            u32 prefix[2] = {0, 0}, rem = want_all, n_eq = 0, b;
-            for (int part = 0; part < 2; ++part) {         // 0: key, highest first; 1: index among equal keys, lowest first
-                if (part == 1 && tid == 0) { sh.T = prefix[0]; sh.r = rem; sh.n_tie = n_eq; }
-                for (int shift = 24; shift >= 0; shift -= 8) {
-                    if (tid < static_cast<u32>(kListBins)) sh.hist[tid] = 0;
-                    __syncthreads();
-                    for (u32 i0 = 0; i0 < n; i0 += THREADS) {
-                        const u32 i = i0 + tid, key = i < n ? key_of(i) : 0u;
-                        const bool there = i < n && (part == 0 || key == prefix[0]);
-                        const u32 v = there && part == 1 ? idx_of(i) : key;
-                        wave_count(sh.hist, there && (shift == 24 || (v >> (shift + 8)) == (prefix[part] >> (shift + 8))), (v >> shift) & 255u);
-                    }
-                    __syncthreads();
-                    list_pick(sh, part == 0, rem, &b, &rem, &n_eq);
-                    prefix[part] |= b << shift;
-                }
+        } else {                                           // ties: radix levels on the index, lowest first
+            u32 prefix = 0, rem = want, n_eq, b;
+            for (int shift = 24; shift >= 0; shift -= 8) {
+                if (tid < static_cast<u32>(kListBins)) sh.hist[tid] = 0;
+                __syncthreads();
+                for_keys([&](bool there, u32 i, u32 key) {
+                    const bool tie = there && key == from;
+                    const u32 idx = tie ? idx_of(i) : 0u;
+                    wave_count(sh.hist, tie && (shift == 24 || (idx >> (shift + 8)) == (prefix >> (shift + 8))), (idx >> shift) & 255u);
+                });
+                __syncthreads();
+                list_pick(sh, false, rem, &b, &rem, &n_eq);
+                prefix |= b << shift;
             }
-            if (tid == 0) { sh.last = prefix[1]; sh.rem = sh.r; }
+            if (tid == 0) { sh.T = from; sh.rem = want; sh.n_tie = in_bin; sh.last = prefix; }
         }
         __syncthreads();
         const u32 T = sh.T, last = sh.last;
@@ -2466,7 +2490,7 @@ __global__ __launch_bounds__(kListThreads) void k_list_finish(DataArgs a, ListAr
         }
     }
     if (left) list_alone<LC, VEC, PQ>(a, w, s_big, sh.wave, s_pick, s_end, s, st, nz, results, n_groups, vec_out);
-    else      list_rank<LC, PQ, kListThreads>(a, w, sh, s, want, n, in_lds, nz, 0, 1, results, n_groups);
+    else      list_rank<LC, PQ, kListThreads, false>(a, w, sh, s, want, n, in_lds, nz, 0, 1, results, n_groups);
 }
 
 // ---- the whole grid on what the lists leave open -------------------------------------------------------------------
@@ -2849,7 +2873,7 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_settle(DataArgs a, L
     for (u32 v = blockIdx.x; v < n_r * shares; v += gridDim.x) {
         const u32 s = v / shares;
         const u32 want = n_special != 0 && list_tied(w, s) ? 0u : w.bin_want[s];
-        list_rank<false, false, kSettleThreads>(a, w, sh, s, want, w.gathered[static_cast<u64>(s) * kListLine], false, 0, v % shares, shares, results, n_groups);
+        list_rank<false, false, kSettleThreads, false>(a, w, sh, s, want, w.gathered[static_cast<u64>(s) * kListLine], false, 0, v % shares, shares, results, n_groups);
     }
     if (n_special == 0) return;
     if (threadIdx.x == 0) { s_tied = 0; s_search = 0; }
@@ -3038,7 +3062,7 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
     meet(m);
     if (gather && !list_tied(w, 0)) {                      // the same in every workgroup
         const u32 shares = m.size < 16 ? m.size : 16u;
-        if (m.rank < shares) list_rank<LC, PQ, kSettleThreads>(a, w, sh, 0, f.want, f.n_in, false, 0, m.rank, shares, results, 1);
+        if (m.rank < shares) list_rank<LC, PQ, kSettleThreads, true>(a, w, sh, 0, f.want, f.n_in, false, 0, m.rank, shares, results, 1);
         return;
     }
     if (first && nnz && gather && tid == 0) __hip_atomic_fetch_add(w.nnz_out, ld_dev64(&a.ctl->nnz_delta), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -235,3 +235,27 @@ def test_windows_at_a_gap(n, kind):
         check_prune_against_oracle(res, oracle.prune([w], ds, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1, f"{n} {kind} {ds}")
         assert [r["path"] for r in P.select_records(res["results"])] == [2] * len(ds), (n, kind, ds)
     _check_lc([w], [np.zeros_like(w)], share, pq=True)
+
+
+@pytest.mark.parametrize("distinct", [2, 40, 3000, 1 << 20])
+@pytest.mark.parametrize("n", [100001, 262149, 3000001])       # one workgroup a ranking; all rankings together
+def test_threshold_bins_of_many_entries(n, distinct):
+    """Tens of thousands of keys in a small part of the threshold's bin, with few and with many values among them: the levels that
+    rank them end at comparable pairs, at one value, and at the first and last of them."""
+    rng = np.random.default_rng(n + distinct)
+    w = rng.standard_normal(n).astype(np.float32)
+    m = n // 6
+    near = np.float32(1.5).view(np.uint32) + rng.integers(0, distinct, m).astype(np.uint32)
+    at = rng.choice(n, m, replace=False)
+    w[at] = near.view(np.float32) * rng.choice([-1.0, 1.0], m).astype(np.float32)
+    above = int((np.abs(w) >= 1.5).sum()) - int(((np.abs(w) >= 1.5) & (np.abs(w).view(np.uint32) < np.float32(1.5).view(np.uint32) + distinct)).sum())
+    ks = [above + 1, above + m // 3, above + m - 1]
+    for ds in ([k / n for k in ks[:1]], [k / n for k in ks[1:2]], [k / n for k in ks]):
+        res = P.condensa_prune(up([w]), ds, theta_f16=True)
+        torch.cuda.synchronize()
+        check_prune_against_oracle(res, oracle.prune([w], ds, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1, f"{n} {distinct} {ds}")
+    _check_lc([w], [np.zeros_like(w)], ks[1] / n, pq=True)
+    arrs = [w, w[: n // 2].copy(), w[n // 3:].copy()]
+    res = P.condensa_prune(up(arrs), [ks[1] / n], scope=P.SCOPE_PER_TENSOR)
+    torch.cuda.synchronize()
+    check_prune_against_oracle(res, oracle.prune(arrs, [ks[1] / n], P.SCOPE_PER_TENSOR), P.SCOPE_PER_TENSOR, 3, f"{n} {distinct}")
