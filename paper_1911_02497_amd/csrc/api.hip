@@ -299,6 +299,7 @@ static u32 list_hist_copies(int n_slots) {
     while (c > 1 && c * static_cast<u32>(n_slots) > 256) c /= 2;
     return c;
 }
+static u32 list_uneven_copies(int n_slots) { return n_slots == 1 ? 64u : list_hist_copies(n_slots); }
 static u32 list_groups(u64 n, int J, bool per_tensor, const Config& cfg) {         // sampling workgroups of a population
     const int64_t opt = cfg[CONDENSA_OPT_SAMPLE_LOG2];
     if (opt <= 0) return list_sample_groups(n, J, per_tensor);
@@ -335,7 +336,7 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
         L.l_cnt = off;     off += align_up(static_cast<size_t>(L.n_slots) * L.l_max_segs * sizeof(u64));
         L.l_nnz = off;     off += align_up(kListSegs * sizeof(u32));
         L.seg = off;       off += op == CONDENSA_OP_LC_STEP ? align_up(kNnzSegs * sizeof(u64)) : 0;
-        L.l_hist = off;    off += align_up(static_cast<size_t>(L.n_slots) * list_hist_copies(L.n_slots) * kListBins * sizeof(u32));
+        L.l_hist = off;    off += align_up(static_cast<size_t>(L.n_slots) * list_uneven_copies(L.n_slots) * kListBins * sizeof(u32));
         L.l_post = off;    off += L.n_slots == 1 ? align_up(256 + (kListFound + kMaxWalkers) * sizeof(u64) + kMaxWalkers * sizeof(u32)) : 0;
         L.l_gathered = off; off += align_up(static_cast<size_t>(L.n_slots) * kListLine * sizeof(u32));
         L.l_fb = off;      off += align_up(sizeof(FallbackCtl));
@@ -771,6 +772,7 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const L
     w.n_rankings = n_slots;
     w.hist = at<u32>(ws, L.l_hist);
     w.hist_copies = list_hist_copies(n_slots);
+    w.uneven_copies = list_uneven_copies(n_slots);
     w.count_in_sweep = !shape.lone && n_slots == 1 ? 1 : 0;
     w.arrived = at<u32>(ws, L.l_post);
     w.ended = w.arrived + kListLine;

@@ -95,11 +95,14 @@ inline u32 list_segments(u64 n, u64 per_wave, u32 most) {
 // lo = hi = mid = 2^32 - 1: nothing is kept, nothing listed.  kListCrowded: the sample holds so many keys like those at
 // the window's ends or its estimate (zeros of a pruned model, values on a grid) that the list could not hold them.  No
 // sweep is spent on such a ranking; the fallback takes it from there.
-struct ListWin { u32 lo, hi, mid, bins; };       // bins: shift | mid_bin << 8 | kListCrowded
+struct ListWin { u32 lo, hi, mid, bins; };       // bins: shift | mid_bin << 8 | kListUneven | kListCrowded
 constexpr u32 kListCrowded = 0x80000000u;
+// kListUneven: its keys may meet in few bins (list_bounds).
+constexpr u32 kListUneven = 0x40000000u;
 __host__ __device__ inline u32 win_shift(const ListWin& w) { return w.bins & 0xFFu; }
 __host__ __device__ inline u32 win_mid_bin(const ListWin& w) { return (w.bins >> 8) & 0xFFu; }
 __host__ __device__ inline bool win_crowded(const ListWin& w) { return (w.bins & kListCrowded) != 0; }
+__host__ __device__ inline bool win_uneven(const ListWin& w) { return (w.bins & kListUneven) != 0; }
 
 // Several rankings of one population: their windows in descending order, for k_list_sweep_multi.  A key's region is the
 // number of estimates `mid` that it reaches; while no two windows overlap it tells every decision, and the key can only be
@@ -164,6 +167,7 @@ struct ListArgs {
     u64* cnt;              // [rankings][max_segs] entries offered | keys above the window << 32
     u32* hist;             // [rankings][hist_copies][kListBins] listed keys by bin of their window
     u32 hist_copies;       // a power of two
+    u32 uneven_copies;     // the same for a window whose keys may meet in few bins
     u32 count_in_sweep;    // 1: the sweep counts them (one ranking: two launches less, and its one or two listed keys a wavefront cost it
                            // nothing), 0: k_list_hist (several: 780 thousand updates for ten densities of 20 M weights took 30 us), or
                            // k_list_finish for itself
@@ -234,7 +238,7 @@ __device__ inline ListWin list_window(u32 hi, u32 lo, u32 mid) {
     return x;
 }
 
-// From the words of list_sample: upper bound, lower bound, estimate (bit 31: crowded).  marks: kListCrowded.
+// From the words of list_sample: upper bound, lower bound, estimate (bit 31: crowded).  marks: kListCrowded, kListUneven.
 __device__ inline ListWin list_window_of(const u32* word, bool nothing, u32 marks) {
     if (nothing) return list_window(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
     ListWin x = list_window(word[0] & ~kListCrowded, word[1] & ~kListCrowded, word[2] & ~kListCrowded);
@@ -646,6 +650,15 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
         }
         const u32 fewer = above < below ? above : below, more = above < below ? below : above;
         const bool even = static_cast<float>(fewer) >= n * least_beyond && static_cast<float>(more) <= n * most_beyond;
+        // or some draws of the first 64 are many: weights on a grid.  (A loop: what is executed once is bound by fetching its
+        // instructions; unrolled over all draws this took 1.2 us.)
+        bool alike = open != 0 || !even;
+#pragma unroll 1
+        for (int c = 0; c < 32 && w.uneven_copies != w.hist_copies && !alike; c += 8) {
+            const u32 x = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(v[2][0]), c));
+            alike = __popcll(__ballot(drew[0] && ((v[2][0] ^ x) & ~kListCrowded) == 0)) >= 6;
+        }
+        if (alike) marks |= kListUneven;
         const bool all_equal = !(var > 0.0f);
         if (open == 0 && (even || all_equal)) {
             auto at = [&](float d) {             // a key; ref + d may lie outside
@@ -778,9 +791,12 @@ __device__ inline u32 lanes_below(u64 m) {       // set bits of m below this lan
 }
 
 // Where this workgroup counts ranking r's listed keys.  A line that many update takes some 10 ns for each of them, so there are
-// up to 16 copies, taken in turn.
-__device__ inline u32* list_hist_copy(const ListArgs& w, u64 r) {
-    return w.hist + (r * w.hist_copies + (blockIdx.x & (w.hist_copies - 1))) * kListBins;
+// up to 16 copies, taken in turn, and 64 where the keys may meet in few bins (pruning VGG-19 at a gap, some 100 thousand keys in a
+// few bins: the sweep 70 us with 16 copies, 38 with 64, 32 where it does not count them; on 8-bit integers 44, 33 and 31).
+__device__ inline u32 list_copies(const ListArgs& w, const ListWin& win) { return win_uneven(win) ? w.uneven_copies : w.hist_copies; }
+__device__ inline u32* list_hist(const ListArgs& w, u64 r) { return w.hist + r * w.uneven_copies * kListBins; }
+__device__ inline u32* list_hist_copy(const ListArgs& w, u64 r, const ListWin& win) {
+    return list_hist(w, r) + (blockIdx.x & (list_copies(w, win) - 1)) * kListBins;
 }
 
 // Counts of a wavefront's listed keys.  A few go straight to the histogram.  Where they are many, those of the first two bins met are
@@ -923,8 +939,9 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
         b = atomicAdd(reinterpret_cast<unsigned long long*>(&w.cnt[static_cast<u64>(r) * w.max_segs + seg]),
                       (static_cast<unsigned long long>(above) << 32) | total);
     if (total == 0) return;
-    u32* const hist = w.count_in_sweep ? list_hist_copy(w, r) : nullptr;
+    u32* const hist = w.count_in_sweep ? list_hist_copy(w, r, win) : nullptr;
     const u32 shift = win_shift(win);
+    const bool add_up = total > kCountedAtOnce || win_uneven(win);
     BinCounts counts;
     u32 at = incl - mine;
     const u64 first = rk.base + static_cast<u64>(seg) * rk.seg_cap;
@@ -937,7 +954,7 @@ __global__ __launch_bounds__(64) void k_list_sweep(DataArgs a, ListArgs w) {
 #pragma unroll
         for (int e = 1; e < 4 * QUADS; ++e) x = i == static_cast<u32>(e) ? key[e / 4][e % 4] : x;
         if (hist) {                                                     // uniform
-            if (total > kCountedAtOnce) counts.add(hist, there, (x - lo) >> shift);
+            if (add_up) counts.add(hist, there, (x - lo) >> shift);
             else if (there)             atomicAdd(hist + ((x - lo) >> shift), 1u);
         }
         if (there && pos + at < rk.seg_cap) {
@@ -1321,7 +1338,7 @@ __global__ __launch_bounds__(kBlock) void k_list_hist(ListArgs w) {
     __syncthreads();
     const uint4 v0 = reinterpret_cast<const uint4*>(s_hist)[2 * threadIdx.x], v1 = reinterpret_cast<const uint4*>(s_hist)[2 * threadIdx.x + 1];
     const u32 v = v0.x + v0.y + v0.z + v0.w + v1.x + v1.y + v1.z + v1.w;          // kListBins == kBlock
-    if (v) atomicAdd(list_hist_copy(w, s) + threadIdx.x, v);
+    if (v) atomicAdd(list_hist_copy(w, s, win) + threadIdx.x, v);
 }
 
 // The outputs of up to B listed elements, with the decision each should have had: what has to be read (list_fix_load), which need
@@ -1471,12 +1488,13 @@ __device__ inline void list_leave(const DataArgs& a, const ListArgs& w, u32 s, u
     }
 }
 // Where the threshold of ranking s is in its list, from the counters and the histogram that the sweep left.  All threads; every
-// workgroup of the ranking finds the same.  The loads depend on nothing but the launch's arguments and are all in flight at once.
+// workgroup of the ranking finds the same, and every wavefront of it once the copies of the histogram are added up.  The loads depend
+// on nothing but the launch's arguments and are all in flight at once.
 template <int THREADS>
 struct ListFindShared {
     u32 cnt[kListSegs];    // entries of each segment
-    u32 above[THREADS / 64], listed[THREADS / 64], over[THREADS / 64], counted[THREADS / 64];
-    u32 bin, want, in;
+    uint4 hist[THREADS / 64][64];                // sums over a wavefront's copies, four bins a lane, from the top
+    u32 above[THREADS / 64], listed[THREADS / 64], over[THREADS / 64], scratch[THREADS / 64];
 };
 struct ListFound {
     u32 above, listed;     // keys above the window and in it
@@ -1484,8 +1502,8 @@ struct ListFound {
                            // the list is not complete
 };
 template <int THREADS>
-__device__ inline ListFound list_find(const ListArgs& w, ListFindShared<THREADS>& sh, u32 s, const ListRank& rk, u32 k) {
-    static_assert(kListSegs % THREADS == 0 && THREADS >= kListBins && kListBins % 64 == 0, "segments and bins by thread");
+__device__ inline ListFound list_find(const ListArgs& w, ListFindShared<THREADS>& sh, u32 s, const ListRank& rk, const ListWin& win, u32 k) {
+    static_assert(kListSegs % THREADS == 0 && kListBins == 4 * 64, "segments by thread, bins by lane");
     constexpr int kPer = kListSegs / THREADS;
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     u64 v[kPer];
@@ -1494,16 +1512,18 @@ __device__ inline ListFound list_find(const ListArgs& w, ListFindShared<THREADS>
         const u32 seg = tid + i * THREADS;
         v[i] = seg < w.max_segs ? w.cnt[static_cast<u64>(s) * w.max_segs + seg] : 0;           // none past n_segs
     }
-    u32 h = 0;
-    if (tid < static_cast<u32>(kListBins)) {               // bins from the top
-        const u32* from = w.hist + static_cast<u64>(s) * w.hist_copies * kListBins + (kListBins - 1 - tid);
-        if (w.hist_copies == 16) {
-#pragma unroll
-            for (int c = 0; c < 16; ++c) h += from[c * kListBins];
-        } else {
-            for (u32 c = 0; c < w.hist_copies; ++c) h += from[c * kListBins];
-        }
-    }
+    uint4 h = make_uint4(0, 0, 0, 0);
+    const u32* from = list_hist(w, s) + (kListBins - 4 - 4 * lane);
+    auto add_copy = [&](u32 c) {
+        const uint4 x = *reinterpret_cast<const uint4*>(from + c * kListBins);
+        h.x += x.x; h.y += x.y; h.z += x.z; h.w += x.w;
+    };
+#pragma unroll 2
+    for (u32 c = wave; c < w.hist_copies; c += THREADS / 64) add_copy(c);
+    if (win_uneven(win))                                   // uniform; the others do not wait for the window
+#pragma unroll 6
+        for (u32 c = w.hist_copies + wave; c < w.uneven_copies; c += THREADS / 64) add_copy(c);
+    sh.hist[wave][lane] = h;
     u32 above = 0, listed = 0;
     bool over = false;
 #pragma unroll
@@ -1516,30 +1536,34 @@ __device__ inline ListFound list_find(const ListArgs& w, ListFindShared<THREADS>
     }
     above = wave_sum_u32(above);
     listed = wave_sum_u32(listed);
-    const u32 incl = wave_incl_scan_u32(h);
     const bool any_over = __any(over);
-    if (lane == 63) { sh.above[wave] = above; sh.listed[wave] = listed; sh.over[wave] = any_over ? 1u : 0u; sh.counted[wave] = incl; }
-    if (tid == 0) { sh.want = 0; sh.in = 0; sh.bin = 0; }
+    if (lane == 63) { sh.above[wave] = above; sh.listed[wave] = listed; sh.over[wave] = any_over ? 1u : 0u; }
     __syncthreads();
     ListFound f{};
-    u32 any = 0, higher = incl - h;
+    u32 any = 0;
+    h = make_uint4(0, 0, 0, 0);
 #pragma unroll
     for (u32 i = 0; i < THREADS / 64; ++i) {
         f.above += sh.above[i];
         f.listed += sh.listed[i];
         any |= sh.over[i];
-        higher += i < wave ? sh.counted[i] : 0u;
+        const uint4 x = sh.hist[i][lane];
+        h.x += x.x; h.y += x.y; h.z += x.z; h.w += x.w;
     }
+    const u32 c[4] = {h.w, h.z, h.y, h.x}, sum = h.x + h.y + h.z + h.w, incl = wave_incl_scan_u32(sum);
     const u32 want = k - f.above;                          // (when that many are above, nothing below holds)
-    if (any == 0 && f.above < k && tid < static_cast<u32>(kListBins) && higher < want && want <= higher + h) {
-        sh.bin = kListBins - 1 - tid;
-        sh.want = want - higher;
-        sh.in = h;
+    u32 before = incl - sum, bin = 0, rem = 0, in = 0;
+    const u64 here = __ballot(any == 0 && f.above < k && before < want && want <= incl);
+    if (here == 0) return f;                               // uniform
+#pragma unroll
+    for (u32 i = 0; i < 4; ++i) {
+        if (before < want && want <= before + c[i]) { bin = kListBins - 1 - 4 * lane - i; rem = want - before; in = c[i]; }
+        before += c[i];
     }
-    __syncthreads();
-    f.bin = sh.bin;
-    f.want = sh.want;
-    f.n_in = sh.in;
+    const int at = __ffsll(static_cast<long long>(here)) - 1;
+    f.bin = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(bin), at));
+    f.want = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(rem), at));
+    f.n_in = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(in), at));
     return f;
 }
 
@@ -1859,7 +1883,7 @@ __global__ __launch_bounds__(kBlock) void k_list_gather(DataArgs a, ListArgs w) 
     if (part != 0 && part * (kBlock / 64) >= rk.n_segs) return;          // uniform
     const u32 k = static_cast<u32>(slot.k), n_all = static_cast<u32>(slot.n);
     const u32 state = slot.state;
-    const ListFound f = list_find<kBlock>(w, find, s, rk, k);
+    const ListFound f = list_find<kBlock>(w, find, s, rk, win, k);
     const bool crowded = win_crowded(win), ok = !crowded && f.want != 0 && f.n_in <= w.gather_cap;
     if (part == 0 && tid == 0) w.bin_want[s] = state == kSelecting && ok ? f.want : 0;
     if (state != kSelecting) return;                       // uniform; k == 0: nothing listed
@@ -2921,12 +2945,12 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
     const ListWin win = w.win[0];
     const Slot& slot = a.slots[0];
     const u32 k = static_cast<u32>(slot.k), n_all = static_cast<u32>(slot.n);
-    const ListFound f = list_find<kSettleThreads>(w, find, 0, rk, k);
+    const ListFound f = list_find<kSettleThreads>(w, find, 0, rk, win, k);
     const bool nnz = PQ && w.nnz_out != nullptr && w.write;
     auto sweep_codes = [&]() {                             // the sweep's count of non-zero codes, in thread 0
         u32 v = 0, total;                                  // fewer than 2^32
         for (u32 i = tid; i < static_cast<u32>(kListSegs); i += kSettleThreads) v += w.nnz[i];
-        wg_incl_scan_u32<kSettleThreads>(v, find.above, &total);
+        wg_incl_scan_u32<kSettleThreads>(v, find.scratch, &total);
         return total;
     };
     auto add_corrections = [&](int nz, u64* to) {
