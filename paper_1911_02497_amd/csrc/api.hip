@@ -727,14 +727,18 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
     u32 first = 0;
     *shape = ListShape{};
     u32 most = static_cast<u32>(kListMaxW);                // sampling workgroups of a population
+    auto groups_of = [&](u64 n) {
+        const u32 asked = list_groups(n, J, per_tensor, cfg);
+        return per_tensor && cfg[CONDENSA_OPT_SAMPLE_LOG2] <= 0 ? list_fewer_groups(asked, most) : asked;
+    };
     for (u64 asked; per_tensor && most > 32 && cfg[CONDENSA_OPT_SAMPLE_LOG2] <= 0; most /= 2) {
         asked = 0;
-        for (size_t g = 0; g < n_groups; ++g) asked += std::min(list_groups(tb.td[g].n, J, true, cfg), most);
+        for (size_t g = 0; g < n_groups; ++g) asked += groups_of(tb.td[g].n);
         if (asked <= kSampleResident) break;
     }
     for (size_t g = 0; g < n_groups; ++g) {
         const u64 n = per_tensor ? tb.td[g].n : tb.N;
-        const u32 w = std::min(list_groups(n, J, per_tensor, cfg), most);
+        const u32 w = groups_of(n);
         u32 segs = list_segments(n, list_wave_elems(tb.N, J, lc), L.l_max_segs);
         for (int j = 0; j < J; ++j) {
             ListRank& r = rk[g * J + j];
@@ -760,7 +764,7 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
     return table->size();
 }
 
-static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const ListShape& shape, const ListRequest& rq, const Config& cfg) {
+static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, bool per_tensor, const ListShape& shape, const ListRequest& rq, const Config& cfg) {
     ListArgs w{};
     w.rank = at<ListRank>(ws, L.l_rank);
     w.group_of = reinterpret_cast<const u32*>(w.rank + n_slots);
@@ -811,6 +815,7 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const L
     w.margin16 = static_cast<int>(cfg[CONDENSA_OPT_WINDOW_MARGIN]);
     w.write = rq.write ? 1 : 0;
     w.force = t_force;
+    w.fewer = per_tensor && cfg[CONDENSA_OPT_SAMPLE_LOG2] <= 0 ? 1 : 0;
     return w;
 }
 
@@ -859,7 +864,7 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
     for (int t = 0; t <= n_tensors; ++t) b.chunk_start[t] = static_cast<u32>(tb.td[t].chunk_start);
     b.fillers = static_cast<u32>(begin_blocks(b.n_zero, tb.n_chunks));
     const u32 bounds = shape.bounds ? (per_tensor ? static_cast<u32>(n_tensors) : 1u) : 0u;
-    ListArgs w = list_args(L, ws, tb.N, L.n_slots, shape, rq, cfg);
+    ListArgs w = list_args(L, ws, tb.N, L.n_slots, per_tensor, shape, rq, cfg);
     static std::atomic<u32> calls{0};
     w.tag = call_tag(calls.fetch_add(1, std::memory_order_relaxed));
     img->launching(st);
@@ -873,7 +878,7 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
 template <bool LC, bool VEC>
 static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* ws, const ListShape& shape, int n_slots, int n_groups,
                                      condensa_select* results, const ListRequest& rq, bool sampled, hipStream_t st, const Config& cfg) {
-    ListArgs w = list_args(L, ws, a.N, n_slots, shape, rq, cfg);
+    ListArgs w = list_args(L, ws, a.N, n_slots, a.per_tensor != 0, shape, rq, cfg);
     const bool vec = VEC && rq.vec_out;
     if (!sampled) {
         PhaseTimer timer(CONDENSA_PHASE_SAMPLE, st, cfg);

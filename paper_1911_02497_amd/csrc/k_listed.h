@@ -40,7 +40,6 @@
 namespace condensa {
 
 constexpr int kListThreads = 1024;
-constexpr int kListUnits = 4;                    // sample positions (of four keys each) per thread of a lone workgroup (and of large populations: kSampleDeep); one of several takes one
 constexpr int kListSegs = 1024;                  // segments of a ranking's list at most
 constexpr int kListMaxW = 256;                   // sampling workgroups of one population at most
 constexpr int kListMaxRankings = 4096;
@@ -70,10 +69,26 @@ inline u32 list_sample_groups(u64 n, int J, bool per_tensor) {
 }
 // Sampling workgroups that are resident at once (two to a compute unit, less those that begin the call and bound the windows): what
 // goes beyond that waits for another round of 8 us, so PER_TENSOR populations that ask for more get half as many at most, and again,
-// down to 32 each.
+// down to a quarter of what list_sample_groups says, and 32.
 constexpr u32 kSampleResident = 480;
-// Entries of a ranking's list: some four times what its window is expected to hold (list_sample_groups), every element of a
-// tiny one.
+inline u32 list_fewer_groups(u32 asked, u32 most) {
+    const u32 least = asked / 4 < 32 ? 32 : asked / 4;
+    return asked < most ? asked : (most < least ? (least < asked ? least : asked) : most);
+}
+// Sample positions per thread: 1 where several workgroups sample, 4 where one does alone.  Also 4 beyond 2^26 elements (in quads): half the window for
+// 6 us more.  A window of 256 sampling workgroups of one unit left more than kListFound entries in the threshold's bin of 2^27 weights at
+// density 0.6, and the whole grid ranked them (65 us where hist, gather and settle took 52); now 20.  And 4 for populations that got
+// fewer workgroups than list_sample_groups says: neighbours resemble each other where rows differ in size, so what narrows a window
+// is the number of lines that are read, and the lists are sized for it.  With 1 unit, 16 matrices of 9 M weights whose rows' sizes
+// vary (normally distributed logarithms, deviation 0.5) overflowed 8 of their lists: 1065 us the call, now 257; 16 of 2.4 M 268 and 105.
+constexpr u32 kListUnits = 4;
+constexpr u32 kSampleDeep = 1u << 24;
+__host__ __device__ inline u32 list_units(u32 W, u32 quads, bool fewer) {
+    if (W == 1 || quads > kSampleDeep) return kListUnits;
+    return fewer && ((quads > (1u << 21) && W < static_cast<u32>(kListMaxW)) || (quads > (1u << 19) && W < 64)) ? kListUnits : 1;
+}
+// Entries of a ranking's list: some four times what its window is expected to hold where weights are independent, every element
+// of a tiny one.
 __host__ __device__ inline u64 list_capacity(u64 n, int cand_shift) {
     if (cand_shift > 0) return (n >> cand_shift) < 4096 ? 4096 : n >> cand_shift;
     if (n <= 4096) return n;
@@ -206,6 +221,7 @@ struct ListArgs {
     int margin16;
     int write;             // 1: the sweep writes the outputs.  0: selection only, an apply sweep follows
     u32 force;             // kForce...
+    u32 fewer;             // 1: populations may have fewer sampling workgroups than they ask for
 };
 
 // What workgroups of one launch hand to each other is written and read with device-scope operations.
@@ -323,7 +339,7 @@ struct SampleShared {
     u32 wave[kListThreads / 64];
     u32 want[3 * kMaxJ], bin[3 * kMaxJ], rem[3 * kMaxJ], key[3 * kMaxJ];
 };
-// UNITS: sample positions (of four keys each) per thread, kListUnits for a lone workgroup.  Four lanes take the four float4 of a
+// UNITS: sample positions (of four keys each) per thread (list_units).  Four lanes take the four float4 of a
 // 64-byte line: the traffic of one float4 from each line, for four times the keys (262144 scattered float4 of two arrays took
 // 11 us, and the 4096 of one workgroup held up its neighbour on the compute unit for 8).  That neighbours resemble each other
 // does not mislead the mean over several workgroups; a lone one's window is ten standard deviations of independent keys to either
@@ -493,16 +509,12 @@ __device__ inline void list_sample_units(SampleShared& sh, const ListArgs& w, in
     }
 }
 
-// Beyond 2^26 elements (in quads) each of several workgroups takes the units of a lone one: half the window for 6 us more.  A window of
-// 256 sampling workgroups of one unit left more than kListFound entries in the threshold's bin of 2^27 weights at density 0.6, and the
-// whole grid ranked them (65 us where hist, gather and settle took 52); now 20.
-constexpr u32 kSampleDeep = 1u << 24;
 template <bool LC, bool VEC, typename TensorOf, typename RankOf>
 __device__ inline void list_sample(const ListArgs& w, int J, float mu, u32 W, u32 me, u32 at_local, u64 first_ranking, u32 first_chunk, u32 quads,
                                    TensorOf&& tensor_of, RankOf&& rank_of) {
     __shared__ SampleShared sh;
-    if (W == 1 || quads > kSampleDeep) list_sample_units<LC, VEC, kListUnits>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
-    else                               list_sample_units<LC, VEC, 1>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
+    if (list_units(W, quads, w.fewer) != 1) list_sample_units<LC, VEC, kListUnits>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
+    else                                    list_sample_units<LC, VEC, 1>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
 }
 
 // The sampling workgroups as a launch of their own.

@@ -259,3 +259,18 @@ def test_threshold_bins_of_many_entries(n, distinct):
     res = P.condensa_prune(up(arrs), [ks[1] / n], scope=P.SCOPE_PER_TENSOR)
     torch.cuda.synchronize()
     check_prune_against_oracle(res, oracle.prune(arrs, [ks[1] / n], P.SCOPE_PER_TENSOR), P.SCOPE_PER_TENSOR, 3, f"{n} {distinct}")
+
+
+@pytest.mark.parametrize("ds", [[0.1], [0.02, 0.3]], ids=["one", "two"])
+def test_populations_with_fewer_sampling_workgroups_than_they_ask_for(ds):
+    """PER_TENSOR populations of every size class whose workgroups are cut to a quarter, or to 32, with rows of very different
+    sizes: their lists still hold the windows."""
+    rng = np.random.default_rng(31)
+    shapes = [(3000, 3001)] + [(4608, 500 + 7 * i) for i in range(3)] + [(600, 451 + i) for i in range(12)] + [(9, 50)]
+    arrs = [rng.standard_normal(s).astype(np.float32) * np.exp(rng.standard_normal((s[0], 1))).astype(np.float32) for s in shapes]
+    res = P.condensa_prune(up(arrs), ds, scope=P.SCOPE_PER_TENSOR, theta=False)
+    torch.cuda.synchronize()
+    check_prune_against_oracle(res, oracle.prune(arrs, ds, P.SCOPE_PER_TENSOR), P.SCOPE_PER_TENSOR, len(arrs))
+    paths = [r["path"] for r in P.select_records(res["results"])]
+    for j in range(len(ds)):
+        assert paths[j * len(arrs):j * len(arrs) + 4] == [2] * 4, paths
