@@ -599,7 +599,15 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
         const float tolerance = 3.0f * sqrtf(due * (1.0f - due) / all);
         const float least_beyond = due - tolerance > 0.0f ? due - tolerance : (due * all >= 3.0f ? 1.0f / all : 0.0f), most_beyond = due + tolerance;
         bool given_up = WAIT && (w.force & kForceNoSample);
-        for (u32 polls = 0; !given_up; ++polls) {          // uniform
+        // What is executed once is bound by fetching its instructions, so it is executed once before the words are there (all zero).
+        u32 dry = WAIT ? 1 : 0;
+        asm volatile("" : "+s"(dry));            // (the compiler would take the loop apart)
+        for (;; --dry) {                         // uniform
+        if (dry != 0 || given_up) {
+#pragma unroll
+            for (int q = 0; q < 3 * kPer; ++q) v[q / kPer][q % kPer] = 0;
+        }
+        for (u32 polls = 0; dry == 0 && !given_up; ++polls) {            // uniform
             bool there = true;
             u64 x[3][kPer];
 #pragma unroll
@@ -618,10 +626,6 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
             given_up = polls == kBoundsPolls;
             __builtin_amdgcn_s_sleep(1);
         }
-        if (given_up) {
-#pragma unroll
-            for (int q = 0; q < 3 * kPer; ++q) v[q / kPer][q % kPer] = 0;
-        }
         bool drew[kPer];                         // this lane's workgroups whose sample holds anything
         u32 n_drew = 0, ref = 0;                 // uniform
 #pragma unroll
@@ -631,40 +635,44 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
             if (n_drew == 0 && m != 0) ref = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(v[2][q]), __ffsll(static_cast<long long>(m)) - 1)) & ~kListCrowded;
             n_drew += static_cast<u32>(__popcll(m));
         }
-        u32 word[3], marks = 0, open = 0;        // open: workgroups without such a rank in their sample
+        u32 word[3], marks = 0, says = 0;        // says: how many say crowded, ten bits for each word
+        bool none = false;                       // a workgroup without such a rank in its sample
         float mean[3], sq = 0.0f;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             float sum = 0.0f;
-            u32 says = 0;                        // those that say crowded
 #pragma unroll
             for (int q = 0; q < kPer; ++q) {
                 if (64u * q >= W) break;         // uniform
                 const u32 key = v[i][q] & ~kListCrowded;
-                says += static_cast<u32>(__popcll(__ballot(drew[q] && (v[i][q] & kListCrowded) != 0)));
-                open += static_cast<u32>(__popcll(__ballot(drew[q] && key == kSampleNone)));
+                says += (v[i][q] >> 31) << (10 * i);
+                none = none || (drew[q] && key == kSampleNone);
                 const float d = drew[q] ? static_cast<float>(static_cast<int>(key - ref)) : 0.0f;
                 sum += d;
                 if (i == 2) sq += d * d;
             }
             mean[i] = wave_sum_f32(sum) / static_cast<float>(n_drew);
-            if (2 * says > n_drew) marks = kListCrowded;               // most of the workgroups say so
         }
+        says = wave_sum_u32(says);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) if (2 * ((says >> (10 * i)) & 1023u) > n_drew) marks = kListCrowded;      // most of the workgroups say so
+        const bool open = __any(none);
         const float n = static_cast<float>(n_drew), var = (wave_sum_f32(sq) - n * mean[2] * mean[2]) / (n - 1.0f);
         const float off = z * (1.0f + 8.0f / n) * sqrtf(var > 0.0f ? var / n : 0.0f);
-        u32 above = 0, below = 0;                // draws of the estimate beyond the interval's ends
+        u32 beyond = 0;                          // draws of the estimate beyond the interval's ends: above | below << 16
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
             if (64u * q >= W) break;             // uniform
             const float d = static_cast<float>(static_cast<int>((v[2][q] & ~kListCrowded) - ref)) - mean[2];
-            above += static_cast<u32>(__popcll(__ballot(drew[q] && d > off)));
-            below += static_cast<u32>(__popcll(__ballot(drew[q] && d < -off)));
+            beyond += drew[q] ? (d > off ? 1u : 0u) + (d < -off ? 0x10000u : 0u) : 0u;
         }
+        beyond = wave_sum_u32(beyond);
+        const u32 above = beyond & 0xFFFFu, below = beyond >> 16;
         const u32 fewer = above < below ? above : below, more = above < below ? below : above;
         const bool even = static_cast<float>(fewer) >= n * least_beyond && static_cast<float>(more) <= n * most_beyond;
         // or some draws of the first 64 are many: weights on a grid.  (A loop: what is executed once is bound by fetching its
         // instructions; unrolled over all draws this took 1.2 us.)
-        bool alike = open != 0 || !even;
+        bool alike = open || !even;
 #pragma unroll 1
         for (int c = 0; c < 32 && w.uneven_copies != w.hist_copies && !alike; c += 8) {
             const u32 x = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(v[2][0]), c));
@@ -672,7 +680,7 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
         }
         if (alike) marks |= kListUneven;
         const bool all_equal = !(var > 0.0f);
-        if (open == 0 && (even || all_equal)) {
+        if (!open && (even || all_equal)) {
             auto at = [&](float d) {             // a key; ref + d may lie outside
                 const float least = -static_cast<float>(ref), most = static_cast<float>(0x7FFFFFFFu - ref);
                 return d <= least ? 0u : (d >= most ? 0x7FFFFFFFu : ref + static_cast<u32>(static_cast<int>(d)));
@@ -707,10 +715,13 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
             word[2] |= 0x800u;
         }
         if (given_up || n_drew < 2) { word[0] = 0x7FFFFFFFu; word[1] = 0; marks = kListCrowded; }
+        const ListWin x = list_window_of(word, nothing_of(j), marks);
+        if (dry != 0) continue;
         if (lane == 0) {
-            const ListWin x = list_window_of(word, nothing_of(j), marks);
             s_win[j] = x;
             w.win[r0 + j] = x;
+        }
+        break;
         }
     }
     if (J == 1) return;
