@@ -714,6 +714,7 @@ struct ListShape {
     u32 groups = 0;        // sampling workgroups
     bool bounds = false;   // some population has several
     bool lone = true;      // no population is larger than list_lone
+    u32 fewer = kFewerNone;
 };
 
 // Host tables of the path: one ListRank per ranking, then (PER_TENSOR) the tensor of every sampling workgroup.
@@ -736,13 +737,21 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
         for (size_t g = 0; g < n_groups; ++g) asked += groups_of(tb.td[g].n);
         if (asked <= kSampleResident) break;
     }
+    auto segments_of = [&](u64 n) { return list_segments(n, list_wave_elems(tb.N, J, lc), L.l_max_segs); };
+    // twice the room for populations of up to 2^23 elements that get fewer, where the workspace has it (list_units)
+    auto room_of = [&](u64 n, u32 times) {
+        return n ? (times == 2 && n <= (1u << 23) && list_fewer(groups_of(n), n) ? 2 : 1) * list_entries(n, segments_of(n), cfg) : 0;
+    };
+    u64 room = 0;
+    for (size_t g = 0; per_tensor && g < n_groups; ++g) room += static_cast<u64>(J) * room_of(tb.td[g].n, 2);
+    const u32 times = per_tensor && room <= L.cand_cap ? 2 : 1;
+    shape->fewer = !per_tensor || cfg[CONDENSA_OPT_SAMPLE_LOG2] > 0 ? kFewerNone : (times == 2 ? kFewerLong : kFewerDeep);
     for (size_t g = 0; g < n_groups; ++g) {
         const u64 n = per_tensor ? tb.td[g].n : tb.N;
-        const u32 w = groups_of(n);
-        u32 segs = list_segments(n, list_wave_elems(tb.N, J, lc), L.l_max_segs);
+        const u32 w = groups_of(n), segs = segments_of(n);
         for (int j = 0; j < J; ++j) {
             ListRank& r = rk[g * J + j];
-            const u64 entries = n ? list_entries(n, segs, cfg) : 0;
+            const u64 entries = room_of(n, times);
             r.base = base;
             r.n_segs = segs;
             r.seg_cap = static_cast<u32>(entries / segs);
@@ -764,7 +773,7 @@ static size_t build_list_table(const Tables& tb, const Layout& L, int n_tensors,
     return table->size();
 }
 
-static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, bool per_tensor, const ListShape& shape, const ListRequest& rq, const Config& cfg) {
+static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const ListShape& shape, const ListRequest& rq, const Config& cfg) {
     ListArgs w{};
     w.rank = at<ListRank>(ws, L.l_rank);
     w.group_of = reinterpret_cast<const u32*>(w.rank + n_slots);
@@ -815,7 +824,7 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, bool pe
     w.margin16 = static_cast<int>(cfg[CONDENSA_OPT_WINDOW_MARGIN]);
     w.write = rq.write ? 1 : 0;
     w.force = t_force;
-    w.fewer = per_tensor && cfg[CONDENSA_OPT_SAMPLE_LOG2] <= 0 ? 1 : 0;
+    w.fewer = shape.fewer;
     return w;
 }
 
@@ -864,7 +873,7 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
     for (int t = 0; t <= n_tensors; ++t) b.chunk_start[t] = static_cast<u32>(tb.td[t].chunk_start);
     b.fillers = static_cast<u32>(begin_blocks(b.n_zero, tb.n_chunks));
     const u32 bounds = shape.bounds ? (per_tensor ? static_cast<u32>(n_tensors) : 1u) : 0u;
-    ListArgs w = list_args(L, ws, tb.N, L.n_slots, per_tensor, shape, rq, cfg);
+    ListArgs w = list_args(L, ws, tb.N, L.n_slots, shape, rq, cfg);
     static std::atomic<u32> calls{0};
     w.tag = call_tag(calls.fetch_add(1, std::memory_order_relaxed));
     img->launching(st);
@@ -878,7 +887,7 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
 template <bool LC, bool VEC>
 static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* ws, const ListShape& shape, int n_slots, int n_groups,
                                      condensa_select* results, const ListRequest& rq, bool sampled, hipStream_t st, const Config& cfg) {
-    ListArgs w = list_args(L, ws, a.N, n_slots, a.per_tensor != 0, shape, rq, cfg);
+    ListArgs w = list_args(L, ws, a.N, n_slots, shape, rq, cfg);
     const bool vec = VEC && rq.vec_out;
     if (!sampled) {
         PhaseTimer timer(CONDENSA_PHASE_SAMPLE, st, cfg);

@@ -80,12 +80,16 @@ inline u32 list_fewer_groups(u32 asked, u32 most) {
 // density 0.6, and the whole grid ranked them (65 us where hist, gather and settle took 52); now 20.  And 4 for populations that got
 // fewer workgroups than list_sample_groups says: neighbours resemble each other where rows differ in size, so what narrows a window
 // is the number of lines that are read, and the lists are sized for it.  With 1 unit, 16 matrices of 9 M weights whose rows' sizes
-// vary (normally distributed logarithms, deviation 0.5) overflowed 8 of their lists: 1065 us the call, now 257; 16 of 2.4 M 268 and 105.
+// vary (normally distributed logarithms, deviation 0.5) overflowed 8 of their lists: 1065 us the call, now 257; 16 of 2.4 M 268 and 98.
+// 2 do for those of up to 2^23 elements where the workspace has room for lists twice as long (4: VGG-19 per layer 3 us more).
 constexpr u32 kListUnits = 4;
 constexpr u32 kSampleDeep = 1u << 24;
-__host__ __device__ inline u32 list_units(u32 W, u32 quads, bool fewer) {
+enum : u32 { kFewerNone = 0, kFewerLong = 1, kFewerDeep = 2 };   // which of these: none are fewer, those have longer lists, they have not
+__host__ __device__ inline bool list_fewer(u32 W, u64 n) { return W != 1 && ((n > (1u << 23) && W < static_cast<u32>(kListMaxW)) || (n > (1u << 21) && W < 64)); }
+__host__ __device__ inline u32 list_units(u32 W, u32 quads, u32 fewer) {
     if (W == 1 || quads > kSampleDeep) return kListUnits;
-    return fewer && ((quads > (1u << 21) && W < static_cast<u32>(kListMaxW)) || (quads > (1u << 19) && W < 64)) ? kListUnits : 1;
+    if (fewer == kFewerNone || !list_fewer(W, static_cast<u64>(quads) * 4)) return 1;
+    return fewer == kFewerLong && quads <= (1u << 21) ? 2 : kListUnits;
 }
 // Entries of a ranking's list: some four times what its window is expected to hold where weights are independent, every element
 // of a tiny one.
@@ -221,7 +225,7 @@ struct ListArgs {
     int margin16;
     int write;             // 1: the sweep writes the outputs.  0: selection only, an apply sweep follows
     u32 force;             // kForce...
-    u32 fewer;             // 1: populations may have fewer sampling workgroups than they ask for
+    u32 fewer;             // kFewer...: populations that have fewer sampling workgroups than they ask for
 };
 
 // What workgroups of one launch hand to each other is written and read with device-scope operations.
@@ -513,8 +517,10 @@ template <bool LC, bool VEC, typename TensorOf, typename RankOf>
 __device__ inline void list_sample(const ListArgs& w, int J, float mu, u32 W, u32 me, u32 at_local, u64 first_ranking, u32 first_chunk, u32 quads,
                                    TensorOf&& tensor_of, RankOf&& rank_of) {
     __shared__ SampleShared sh;
-    if (list_units(W, quads, w.fewer) != 1) list_sample_units<LC, VEC, kListUnits>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
-    else                                    list_sample_units<LC, VEC, 1>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
+    const u32 units = list_units(W, quads, w.fewer);
+    if (units == kListUnits) list_sample_units<LC, VEC, kListUnits>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
+    else if (units == 2)     list_sample_units<LC, VEC, 2>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
+    else                     list_sample_units<LC, VEC, 1>(sh, w, J, mu, W, me, at_local, first_ranking, first_chunk, quads, tensor_of, rank_of);
 }
 
 // The sampling workgroups as a launch of their own.
