@@ -1604,12 +1604,20 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
             // every structure one contiguous row (filters, neurons) of some length: staged, coalesced reads
             constexpr u64 kFewRowsMax = 32768;           // up to 1024 workgroups of kFewRows rows
             bool rows = tb.N / tb.F >= 16;
-            bool rows16 = true;                          // ... and every row 16-byte aligned (k_struct_sumsq_rows)
+            u64 loose = 0;                               // elements of tensors whose rows are not all 16-byte aligned
             for (int t = 0; t < n_tensors && rows; ++t) {
                 const TensorDesc& d = tb.td[t];
                 if (d.n > 0 && !(d.d[1] == 1 && d.d[2] == 1 && d.b[0] == 1 && d.b[3] == d.d[3])) rows = false;
-                if (d.n > 0 && (d.d[3] % 4 != 0 || !aligned16(d.w))) rows16 = false;
+                if (d.n > 0 && (d.d[3] % 4 != 0 || !aligned16(d.w))) loose += d.n;
             }
+            // Not all of them aligned, 256 rows to a workgroup or 64.  256: rows of one piece (a million of 17 elements 132 us the call, 149
+            // with 64; of 33, 140 and 175; 40 thousand 39 and 37), and few loose ones among short ones of which there are very many (a
+            // million of 256 and 40 of 33: 604 and 618) or among short and long ones where no compute unit gets a workgroup more than the
+            // others (65 536 of 4608 and 40 of 33: 645 and 674; 100 thousand of 512: 192 and 137; 262 144 of 1024: 644 and 605).
+            const u64 by_256 = (tb.F + 255) / 256 % 256, len = tb.N / tb.F;
+            const bool even = by_256 <= 8 || by_256 >= 248;
+            const bool mixed_by_256 = (len <= 33 && tb.F >= (1u << 16)) ||
+                                      (loose <= tb.N / 12 && ((len <= 256 && (even || tb.F >= (1u << 19))) || (len >= 4096 && even)));
             // every tensor a matrix tiled exactly by 2-D blocks of one width of 4, 8, 16 or 32, rows 16-byte aligned
             u32 tile_w = 0;
             bool tiles = !rows;
@@ -1632,7 +1640,8 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
                 hipLaunchKernelGGL((k_struct_sumsq_rows_few<true, kFewRows>), dim3(static_cast<unsigned>((tb.F + kFewRows - 1) / kFewRows)), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
             else if (rows && tb.F <= kFewRowsMax)
                 hipLaunchKernelGGL((k_struct_sumsq_rows_few<false, kFewRows>), dim3(static_cast<unsigned>((tb.F + kFewRows - 1) / kFewRows)), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
-            else if (rows && rows16) hipLaunchKernelGGL(k_struct_sumsq_rows, dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
+            else if (rows && loose == 0) hipLaunchKernelGGL(k_struct_sumsq_rows<false>, dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
+            else if (rows && mixed_by_256) hipLaunchKernelGGL(k_struct_sumsq_rows<true>, dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
             else if (rows) hipLaunchKernelGGL((k_struct_sumsq_rows_few<false, kManyRows>), dim3(static_cast<unsigned>((tb.F + kManyRows - 1) / kManyRows)), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
             else if (tiles && tile_w == 4)  hipLaunchKernelGGL((k_struct_sumsq_tiles<1>), dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);
             else if (tiles && tile_w == 8)  hipLaunchKernelGGL((k_struct_sumsq_tiles<2>), dim3(sblocks), dim3(kBlock), 0, st, a, sumsq_dev, norms_dev);

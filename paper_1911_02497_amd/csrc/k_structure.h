@@ -209,23 +209,32 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_tiles(StructArgs a, dou
     if (norms) norms[u] = static_cast<float>(sqrt(acc));
 }
 
+// Four elements of a row.  Global loads of sixteen bytes need no more than the alignment of a binary32 here.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ inline float4 ld4_any(const float* p) {
+    const f32x4_any t = *reinterpret_cast<const f32x4_any*>(p);
+    return make_float4(t.x, t.y, t.z, t.w);
+}
 // Row structures (filters, neurons: structure s of a tensor is the contiguous run [s L, (s+1) L) of its
-// memory), many of them and every row 16-byte aligned: thread-per-structure loads would touch one cache line per lane, so the
+// memory), many of them and as a rule 16-byte aligned: thread-per-structure loads would touch one cache line per lane, so the
 // workgroup stages 32-element pieces of its 256 rows through LDS with coalesced 128-bit loads (8 lanes per row piece) and
 // every thread then adds its own row's piece in memory order -- the same additions in the same order as
 // k_struct_sumsq.  Rows are padded to 36 words, so that the 128-bit accesses of either side spread over the banks.  Bound by
 // memory (6.9 TB/s for 262 144 rows of 4608).  The last workgroup repeats the last row instead of guarding every load: 56 368 rows
 // of 3104 took 280 us when it did, now 128.
+// MIXED: some rows are not aligned; their workgroups load sixteen bytes at any alignment (without the choice, 65 536 rows of 4608 take
+// 630 us the call, with it 644).
 constexpr int kRowTile = 32;
 
+template <bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows(StructArgs a, double* sumsq, float* norms) {
     __shared__ __align__(16) float s_tile[kBlock][kRowTile + 4];
     __shared__ const float* s_row[kBlock];
     __shared__ u32 s_len[kBlock];
-    __shared__ u32 s_maxlen, s_minlen;
+    __shared__ u32 s_maxlen, s_minlen, s_loose;
     const int tid = threadIdx.x;
     const u64 u = static_cast<u64>(blockIdx.x) * kBlock + tid;
-    if (tid == 0) { s_maxlen = 0; s_minlen = 0xFFFFFFFFu; }
+    if (tid == 0) { s_maxlen = 0; s_minlen = 0xFFFFFFFFu; s_loose = 0; }
     __syncthreads();
     const u64 mine = u < a.F ? u : a.F - 1;               // past the end: the last row once more, which is not stored
     const int t = tensor_of_struct(a.td, a.n_tensors, mine);
@@ -233,19 +242,22 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows(StructArgs a, doub
     const u32 len = td.d[3];
     s_row[tid] = td.w + (mine - td.struct_start) * len;
     s_len[tid] = len;
+    if (MIXED && (reinterpret_cast<uintptr_t>(s_row[tid]) & 15u) != 0) s_loose = 1;
     atomicMax(&s_maxlen, len);
     atomicMin(&s_minlen, len);
     __syncthreads();
     const u32 maxlen = s_maxlen;
     const u32 fast_end = (s_minlen / kRowTile) * kRowTile;                   // pieces below it: unguarded loads
     const int seg = tid & 7, sub = tid >> 3;              // 8 lanes per row piece, 32 rows per pass
+    const bool loose = MIXED && s_loose != 0;             // uniform
+    auto load = [&](const float* p) { return MIXED && loose ? ld4_any(p) : ld4_stream(p); };
     double acc = 0.0;
     // Pieces below fast_end are fetched one iteration ahead, so that the loads of piece i+1 are in flight
     // while piece i is added up.
     float4 v[8];
     if (fast_end > 0) {
 #pragma unroll
-        for (int pass = 0; pass < 8; ++pass) v[pass] = ld4_stream(s_row[pass * 32 + sub] + seg * 4);
+        for (int pass = 0; pass < 8; ++pass) v[pass] = load(s_row[pass * 32 + sub] + seg * 4);
     }
     for (u32 cb = 0; cb < maxlen; cb += kRowTile) {
         if (cb < fast_end) {
@@ -256,7 +268,7 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows(StructArgs a, doub
             if (cb + kRowTile < fast_end) {
 #pragma unroll
                 for (int pass = 0; pass < 8; ++pass)
-                    v[pass] = ld4_stream(s_row[pass * 32 + sub] + cb + kRowTile + seg * 4);
+                    v[pass] = load(s_row[pass * 32 + sub] + cb + kRowTile + seg * 4);
             }
         } else {
             for (int pass = 0; pass < 8; ++pass) {
@@ -309,12 +321,6 @@ __global__ __launch_bounds__(kBlock) void k_struct_sumsq_rows(StructArgs a, doub
 constexpr int kFewRows = 32, kManyRows = 64;
 constexpr int kFewStarts = 512;
 
-// Four elements of a row.  Global loads of sixteen bytes need no more than the alignment of a binary32 here.
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-__device__ inline float4 ld4_any(const float* p) {
-    const f32x4_any t = *reinterpret_cast<const f32x4_any*>(p);
-    return make_float4(t.x, t.y, t.z, t.w);
-}
 template <bool SQUARED, int ROWS>
 __global__ __launch_bounds__(kBlock, SQUARED ? 2 : 4) void k_struct_sumsq_rows_few(StructArgs a, double* sumsq, float* norms) {
     using Staged = typename std::conditional<SQUARED, double, float>::type;

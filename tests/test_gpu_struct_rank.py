@@ -95,6 +95,9 @@ def test_sums_of_many_rows(rows):
     ((33, 40), (1, 1), (1, 2), (3, 1), (1, 3), (40, 64)),               # tensors of fewer than four elements
     ((32769, 36), (7, 64), (300, 20)),                                  # aligned, several lengths in a workgroup, the last one ragged
     ((33001, 19), (65, 17), (5, 131), (1, 18)),                         # not aligned, the last rows end within four elements of their tensor
+    ((70001, 17), (300, 33), (1, 130)),                                 # rows of one piece, 256 to a workgroup
+    ((65400, 64), (41, 33), (7, 131), (95, 2)),                         # few that are not aligned among many, in workgroups of both
+    ((65537, 36), (3, 5001)),                                           # ... and long ones
 ])
 def test_sums_of_rows_of_several_tensors(shapes):
     rng = np.random.default_rng(len(shapes))
