@@ -23,6 +23,8 @@ extern std::atomic<uint64_t> g_launches;        // kernels enqueued since the li
 enum : u32 {
     kForceLate = 1,        // the workgroups of k_list_resolve start once more when all of its work is done
     kForceNoSample = 2,    // the workgroups that bound windows give up on the samples without a look
+    kForceNoVerdict = 4,   // the workgroups that posted entries in k_list_resolve do not wait for the verdict on them
+    kForceAsk = 8,         // ... wait, but take no notice, so that they learn of it when they want to leave
 };
 
 // The knobs of one call, resolved once at the entry point: the caller's condensa_config, or the

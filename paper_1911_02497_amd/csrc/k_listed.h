@@ -3045,7 +3045,8 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
             // launch holds the chip), this one does not keep them from it for long.
             u64 v = 0;
             if (lane == 0) {
-                for (int polls = 0; polls < 64 && ((v = ld_dev64(w.verdict + blockIdx.x)) & kPicked) == 0; ++polls) __builtin_amdgcn_s_sleep(4);
+                for (int polls = 0; polls < ((w.force & kForceNoVerdict) ? 0 : 64) && ((v = ld_dev64(w.verdict + blockIdx.x)) & kPicked) == 0; ++polls) __builtin_amdgcn_s_sleep(4);
+                if (w.force & kForceAsk) v = 0;
             }
             v = (static_cast<u64>(__shfl(static_cast<u32>(v >> 32), 0, 64)) << 32) | __shfl(static_cast<u32>(v), 0, 64);
             s_verdict[wave] = v;

@@ -12,7 +12,7 @@ from gpu_util import assert_bits_equal, assert_select_equal, check_prune_against
 
 pytestmark = pytest.mark.gpu
 
-LATE, NO_SAMPLE = 1, 2                            # csrc/host.h
+LATE, NO_SAMPLE, NO_VERDICT, ASK = 1, 2, 4, 8     # csrc/host.h
 
 
 @contextlib.contextmanager
@@ -81,3 +81,23 @@ def test_windows_whose_samples_do_not_come(sizes, kind):
             check_prune_against_oracle(res, oracle.prune(arrs, ds, scope), scope, len(arrs), f"{sizes} {kind} {ds}")
     with forced(NO_SAMPLE):
         _check_all_calls(arrs[0], 0.1)
+
+
+@pytest.mark.parametrize("what", [NO_VERDICT, ASK], ids=["leave", "ask"])
+@pytest.mark.parametrize("n", [140001, 300007, (1 << 21) + 3])
+@pytest.mark.parametrize("ties", [0, 60, 900, 2040])
+def test_entries_of_workgroups_that_do_not_stay(n, ties, what):
+    """The entries of the threshold's bin are settled by the workgroups that posted them and by the one that ranks them when those
+    have left: every decision, multiplier and code the same."""
+    w = np.random.default_rng(n + ties).standard_normal(n).astype(np.float32)
+    order = np.argsort(-np.abs(w), kind="stable")
+    k = n // 7
+    w[order[k - ties // 2:k + (ties + 1) // 2]] = np.abs(w[order[k]])      # the values next to the threshold become equal
+    with forced(what):
+        for d in (k / n, (k + ties // 3) / n):
+            _check_all_calls(w, d * n / (n + 777))
+        shifted = torch.empty(n + 1, dtype=torch.float32, device="cuda:0")[1:]
+        shifted.copy_(torch.from_numpy(w))
+        res = P.condensa_prune([shifted], [k / n], theta_f16=True)
+        torch.cuda.synchronize()
+        check_prune_against_oracle(res, oracle.prune([w], [k / n], P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1, f"{n} {ties} {what}")
