@@ -25,6 +25,7 @@ enum : u32 {
     kForceNoSample = 2,    // the workgroups that bound windows give up on the samples without a look
     kForceNoVerdict = 4,   // the workgroups that posted entries in k_list_resolve do not wait for the verdict on them
     kForceAsk = 8,         // ... wait, but take no notice, so that they learn of it when they want to leave
+    kForceNoPosts = 16,    // the workgroup that ranks them gives up on the entries without a look
 };
 
 // The knobs of one call, resolved once at the entry point: the caller's condensa_config, or the

@@ -1807,23 +1807,39 @@ struct RankShort {
     u64 pair[kShortPairs];
     u64 found;
     __align__(16) u32 hist[256];
-    u32 bin, rem, in, n, n_tie, kept;
+    u32 bin, rem, in, n, n_tie, kept, missing[kMaxWalkers / 8];
     u8 owned[kListFound];                        // its workgroup settles it
 };
+// Posts are on their way when they are waited for (their workgroups are running), so this bound, some 0.1 s, is not met.  If it were, the
+// workgroup would search the whole population itself (list_search) instead of waiting for ever.
+constexpr u32 kPostPolls = 1u << 16;
+// False: entries are missing.
 template <bool LC, bool PQ, int THREADS>
-__device__ inline void list_rank_short(const DataArgs& a, const ListArgs& w, RankShort& sh, u32 want, u32 n, u32 bin, const ListWin& win, u32 walkers,
+__device__ inline bool list_rank_short(const DataArgs& a, const ListArgs& w, RankShort& sh, u32 want, u32 n, u32 bin, const ListWin& win, u32 walkers,
                                        condensa_select* results, int* nz) {
     static_assert(THREADS >= 256 && THREADS >= static_cast<int>(kMaxWalkers), "a thread a bin, a thread a workgroup");
     const u32 tid = threadIdx.x, shift = win_shift(win), top_key = win.lo + (bin << shift) + ((1u << shift) - 1u);
-    for (u32 i = tid; i < n; i += THREADS) {     // (one round, as a rule)
+    static_assert(THREADS / 64 <= static_cast<int>(kMaxWalkers / 8), "a word a wavefront");
+    bool missing = (w.force & kForceNoPosts) != 0;
+    u32 polls = 0;
+    for (u32 i = tid; i < n && !missing; i += THREADS) {   // (one round, as a rule)
         u64 x;
-        while (((x = ld_dev64(w.picked + i)) & kPicked) == 0) __builtin_amdgcn_s_sleep(1);
+        while (((x = ld_dev64(w.picked + i)) & kPicked) == 0 && !missing) { __builtin_amdgcn_s_sleep(1); missing = ++polls > kPostPolls; }
         sh.entry[i] = (static_cast<u64>(top_key - (static_cast<u32>(x >> 32) & 0x7FFFFFFFu)) << 32) | static_cast<u32>(x);
         sh.owned[i] = 0;
     }
+    u32 range = 0;                               // of workgroup tid
+    if (tid < walkers)
+        while (((range = ld_dev(w.range + tid)) & kRangeKnown) == 0 && !missing) { __builtin_amdgcn_s_sleep(1); missing = ++polls > kPostPolls; }
+    const bool any_missing = __any(missing);
+    if ((tid & 63u) == 0) sh.missing[tid >> 6] = any_missing ? 1u : 0u;
     if (tid < 256) sh.hist[tid] = 0;
     if (tid == 0) { sh.n = 0; sh.n_tie = 0; sh.kept = 0; }
     __syncthreads();
+    u32 is_missing = 0;
+#pragma unroll
+    for (int i = 0; i < THREADS / 64; ++i) is_missing |= sh.missing[i];
+    if (is_missing != 0) return false;           // uniform
     u64 prefix = 0;
     u32 top = 32 + shift, in = n, r = want;      // the r-th from the bottom among the `in` entries whose bits from `top` on are the prefix
     while (in > kShortPairs && top > 0) {        // uniform
@@ -1863,8 +1879,6 @@ __device__ inline void list_rank_short(const DataArgs& a, const ListArgs& w, Ran
     const u64 found = sh.found;
     const u32 T = top_key - static_cast<u32>(found >> 32), last = static_cast<u32>(found);
     if (tid < walkers) {
-        u32 range;
-        while (((range = ld_dev(w.range + tid)) & kRangeKnown) == 0) __builtin_amdgcn_s_sleep(1);        // on its way, as the entries were
         const u64 was = __hip_atomic_exchange(w.verdict + tid, kPicked | (static_cast<u64>(T) << 32) | last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const u32 first = range & 0xFFFFu, count = (range & ~kRangeKnown) >> 16;
         if (was != kWalkerLeft)
@@ -1891,6 +1905,82 @@ __device__ inline void list_rank_short(const DataArgs& a, const ListArgs& w, Ran
         }
         slot.prefix = T; slot.remaining = sh.kept; slot.n_tie = sh.n_tie; slot.need_tie = 0; slot.tie_end = tie_end; slot.state = kDone;
         *results = select_record(slot, true, T, sh.kept, sh.n_tie, tie_end, slot.path);
+    }
+    return true;
+}
+
+// One ranking by one workgroup from the weights alone, whatever else is in the workspace: radix levels of eight bits, the tie that is
+// kept last, outputs, record and count of codes.  Elements one at a time and a barrier for every few hundred: some ms for a million of
+// weights, but no registers that the callers' own work would have to make room for.
+template <bool LC, bool PQ, int THREADS>
+__device__ inline void list_search(const DataArgs& a, const ListArgs& w, ListShared& sh, condensa_select* results) {
+    const u32 tid = threadIdx.x;
+    Slot& slot = a.slots[0];
+    const u32 n_chunks = static_cast<u32>(a.n_chunks);
+    // f(there, index, value, its key) for all elements, in the order of their indices: THREADS at a time, until it returns true
+    auto for_all = [&](auto&& f) {
+#pragma unroll 1
+        for (u32 c = 0; c < n_chunks; ++c) {
+            const TensorDesc& td = a.td[a.chunk_map[c]];
+            const u64 base = (c - td.chunk_start) * kChunk;
+#pragma unroll 1
+            for (u32 i = tid; i < static_cast<u32>(kChunk); i += THREADS) {
+                const bool there = base + i < td.n;
+                float v = there ? td.w[base + i] : 0.0f;
+                if (LC && there) v = lc_shift(v, td.lam[base + i], a.mu);
+                if (f(there, c * kChunk + i, v, mag_key(v))) return;     // uniform
+            }
+        }
+    };
+    u32 T = 0, rem = static_cast<u32>(slot.k), n_tie = 0, b;
+#pragma unroll 1
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        __syncthreads();
+        if (tid < static_cast<u32>(kListBins)) sh.hist[tid] = 0;
+        __syncthreads();
+        for_all([&](bool there, u32, float, u32 key) {
+            if (there && (shift == 24 || (key >> (shift + 8)) == (T >> (shift + 8)))) atomicAdd(&sh.hist[(key >> shift) & 255u], 1u);
+            return false;
+        });
+        __syncthreads();
+        list_pick(sh, true, rem, &b, &rem, &n_tie);
+        T |= b << shift;
+    }
+    u32 last = 0xFFFFFFFFu;
+    u64 tie_end = slot.n;
+    if (rem < n_tie) {                           // uniform
+        u32 cum = 0;
+        for_all([&](bool there, u32 idx, float, u32 key) {
+            const u32 mine = there && key == T ? 1u : 0u;
+            u32 total;
+            const u32 upto = cum + wg_incl_scan_u32<THREADS>(mine, sh.wave, &total);
+            if (mine != 0 && upto == rem) sh.last = idx;
+            cum += total;
+            __syncthreads();
+            return cum >= rem;
+        });
+        last = sh.last;
+        const TensorDesc& td = a.td[a.chunk_map[last / kChunk]];
+        tie_end = static_cast<u64>(last) - td.chunk_start * kChunk + (a.per_tensor ? 0 : td.flat_start) + 1;
+    }
+    u32 codes = 0;
+    if (w.write)
+        for_all([&](bool there, u32 idx, float v, u32 key) {
+            const bool keep = key > T || (key == T && idx <= last);
+            int unused = 0;
+            if (there) list_fix_one<LC, PQ>(a, w, 0, idx, keep, &unused);
+            if (PQ && there && keep && (f32_to_f16_rne(v) & 0x7FFFu) != 0) ++codes;
+            return false;
+        });
+    if (PQ && w.nnz_out && w.write) {
+        u32 total;
+        __syncthreads();
+        wg_incl_scan_u32<THREADS>(codes, sh.wave, &total);
+        if (tid == 0) *w.nnz_out = total;
+    }
+    if (tid == 0) {
+        slot.prefix = T; slot.remaining = rem; slot.n_tie = n_tie; slot.need_tie = 0; slot.tie_end = tie_end; slot.state = kDone;
+        *results = select_record(slot, true, T, rem, n_tie, tie_end, 3);
     }
 }
 
@@ -3038,8 +3128,11 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
         bool on1[1] = {lane < n_found};
         FixLoads<LC, 1> loads;
         if (w.write && n_found != 0) list_fix_load<LC, 1>(a, w, 0, idx1, on1, loads);
-        if ((ticket >> 20) + 1 == walkers)                 // uniform: the last one
-            list_rank_short<LC, PQ, kSettleThreads>(a, w, s_mem.few, f.want, (ticket & 0xFFFFFu) + all, f.bin, win, walkers, results, &nz);
+        if ((ticket >> 20) + 1 == walkers &&               // uniform: the last one
+            !list_rank_short<LC, PQ, kSettleThreads>(a, w, s_mem.few, f.want, (ticket & 0xFFFFFu) + all, f.bin, win, walkers, results, &nz)) {
+            list_search<LC, PQ, kSettleThreads>(a, w, sh, results);
+            return;
+        }
         if (w.write && n_found != 0) {                     // uniform over the wavefront
             // The verdict comes from a workgroup that is running once all have posted; if some of them are not even running yet (another
             // launch holds the chip), this one does not keep them from it for long.

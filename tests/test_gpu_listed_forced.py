@@ -12,7 +12,7 @@ from gpu_util import assert_bits_equal, assert_select_equal, check_prune_against
 
 pytestmark = pytest.mark.gpu
 
-LATE, NO_SAMPLE, NO_VERDICT, ASK = 1, 2, 4, 8     # csrc/host.h
+LATE, NO_SAMPLE, NO_VERDICT, ASK, NO_POSTS = 1, 2, 4, 8, 16              # csrc/host.h
 
 
 @contextlib.contextmanager
@@ -83,12 +83,12 @@ def test_windows_whose_samples_do_not_come(sizes, kind):
         _check_all_calls(arrs[0], 0.1)
 
 
-@pytest.mark.parametrize("what", [NO_VERDICT, ASK], ids=["leave", "ask"])
+@pytest.mark.parametrize("what", [NO_VERDICT, ASK, NO_POSTS, NO_POSTS | NO_VERDICT], ids=["leave", "ask", "no_posts", "no_posts_leave"])
 @pytest.mark.parametrize("n", [140001, 300007, (1 << 21) + 3])
 @pytest.mark.parametrize("ties", [0, 60, 900, 2040])
 def test_entries_of_workgroups_that_do_not_stay(n, ties, what):
-    """The entries of the threshold's bin are settled by the workgroups that posted them and by the one that ranks them when those
-    have left: every decision, multiplier and code the same."""
+    """The entries of the threshold's bin are settled by the workgroups that posted them, by the one that ranks them when those have
+    left, and by a search of everything when it does not get them: every decision, multiplier and code the same."""
     w = np.random.default_rng(n + ties).standard_normal(n).astype(np.float32)
     order = np.argsort(-np.abs(w), kind="stable")
     k = n // 7
@@ -101,3 +101,4 @@ def test_entries_of_workgroups_that_do_not_stay(n, ties, what):
         res = P.condensa_prune([shifted], [k / n], theta_f16=True)
         torch.cuda.synchronize()
         check_prune_against_oracle(res, oracle.prune([w], [k / n], P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, 1, f"{n} {ties} {what}")
+        assert P.select_records(res["results"])[0]["path"] == (3 if what & NO_POSTS else 2)
