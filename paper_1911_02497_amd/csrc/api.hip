@@ -243,10 +243,11 @@ static u64 window_cand_capacity(u64 N, int J, const Config& cfg) {
 // Which selection a call takes when its configuration does not say.  Listed windows (k_listed.h): PER_TENSOR scope and
 // several densities while the lists' 32-bit indices last (four densities: 2^26 weights 209 us against 461 with the
 // windows of several densities and 417-500 with radix levels, 2^28 weights 726 against 1152 and 1954).  One density: up to
-// the size where its lists, in proportion to the population, cost more than the sampled window's deeper ranking does
-// (L-C step of 2^27 weights 509-531 us against 550-566, of 2^28 1004-1036 against 972-1003; pruning 295 against 315 and
-// 561 against 511).  Sampled window (k_window.h, k_fused.h): one density beyond that, several beyond 32-bit indices.
-// Radix levels: where neither applies.
+// 3 2^26 weights, where the lists cost as much as the sampled window's deeper ranking when each of their steps was a launch.
+// With one launch for all of them they are ahead beyond that line too (density 0.1, listed and sampled: pruning 2^27 weights 232 and
+// 316 us, 190 million 308 and 400, 2^28 418 and 507, 2^29 840 and 899, 2^30 1627 and 1680; L-C step 481 and 567, 674 and 767, 941 and
+// 997, 1917 and 2006, 3675 and 3670), so it could be moved.  Sampled window (k_window.h, k_fused.h): one density beyond that line,
+// several beyond 32-bit indices.  Radix levels: where neither applies.
 static bool list_fits(u64 N, int n_tensors, int n_slots) {
     return N > 0 && n_slots <= kListMaxRankings && N + static_cast<u64>(n_tensors) * kChunk < (static_cast<u64>(1) << 32);
 }
@@ -828,7 +829,8 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const L
     return w;
 }
 
-// Tag of a call's words in ListArgs::local: another one for each of 2^32 calls, and none that a workspace is likely to hold.
+// Tag of a call's words in ListArgs::local: another one for each of 2^32 calls, and none that a workspace is likely to hold.  The
+// mixing is the 32-bit finalizer of MurmurHash3 (A. Appleby, public domain), with its constants.
 static u32 call_tag(u32 call) {
     u32 x = call + 0x9E3779B9u;
     x = (x ^ (x >> 16)) * 0x85EBCA6Bu;

@@ -7,8 +7,9 @@
 //      the sample keys at the expected rank of the threshold and a little to either side of it.  Small populations get one
 //      workgroup, whose bounds lie as many standard deviations of the sample rank apart as the call asks for.  Large ones
 //      get up to kListMaxW, each with a sample spread over the whole population, and list_bounds (a workgroup at the end of
-//      the same launch, or k_list_bounds) takes mean and deviation of their keys: a confidence interval for the threshold that
-//      needs no assumption about how neighbours correlate.
+//      the same launch, or k_list_bounds) takes mean and deviation of their keys, or order statistics where these look
+//      nothing like a normal distribution's: a confidence interval for the threshold that needs no assumption about how
+//      neighbours correlate.
 //      Either way: a window [lo, hi] that holds the threshold unless the sample was unlucky, and an estimate `mid`.
 //   2. k_list_sweep / k_list_sweep_multi: ONE pass over the weights writes the outputs (final outside the windows,
 //      provisional -- kept from `mid` on -- inside), counts the keys above each window and lists the keys inside it
@@ -23,8 +24,8 @@
 // Weights with many equal magnitudes -- pruned before, widened from 8-bit codes -- are such rankings as a rule, so the
 // sample also says when a list could not hold its window (kListCrowded): the sweep then leaves that ranking out.
 // Microseconds at the threshold density 0.1 to 0.2, radix levels / one ranking after the other, by tickets / now: 20 M
-// weights of a VGG-19, nine tenths zeros 409 / 1052 / 151, E4M3 values 180 / 1000 / 136; layer by layer, zeros 365 / 7859 /
-// 226, E4M3 values 185 / 4453 / 241; ten densities, E4M3 values 269 / 6941 / 430; 2^18 weights, zeros 680 / 1227 / 71.
+// weights of a VGG-19, nine tenths zeros 409 / 1052 / 146, E4M3 values 180 / 1000 / 136; layer by layer, zeros 365 / 7859 /
+// 220, E4M3 values 185 / 4453 / 224; ten densities, E4M3 values 269 / 6941 / 416; 2^18 weights, zeros 680 / 1227 / 62.
 // One workgroup draws some 25 GB/s from memory it did not write, so the lists (10^5 entries) are walked by many.  When
 // no population exceeds list_lone elements, its list is short enough for one workgroup to do 3 and 4 alone
 // (k_list_finish): three launches, and a ranking that it leaves open stays with that workgroup (list_alone).
