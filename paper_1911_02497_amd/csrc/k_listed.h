@@ -666,25 +666,22 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
         const bool open = __any(none);
         const float n = static_cast<float>(n_drew), var = (wave_sum_f32(sq) - n * mean[2] * mean[2]) / (n - 1.0f);
         const float off = z * (1.0f + 8.0f / n) * sqrtf(var > 0.0f ? var / n : 0.0f);
-        u32 beyond = 0;                          // draws of the estimate beyond the interval's ends: above | below << 16
+        // draws of the estimate beyond the interval's ends, above | below << 10, and << 20 the equal ones among 49 pairs of every 16
+        u32 beyond = 0;
+        if (drew[0])
+            beyond = (dpp_or_zero<0x111, 0xF>(v[2][0]) == v[2][0] ? 1u << 20 : 0u) + (dpp_or_zero<0x112, 0xF>(v[2][0]) == v[2][0] ? 1u << 20 : 0u) +
+                     (dpp_or_zero<0x114, 0xF>(v[2][0]) == v[2][0] ? 1u << 20 : 0u) + (dpp_or_zero<0x118, 0xF>(v[2][0]) == v[2][0] ? 1u << 20 : 0u);
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
             if (64u * q >= W) break;             // uniform
             const float d = static_cast<float>(static_cast<int>((v[2][q] & ~kListCrowded) - ref)) - mean[2];
-            beyond += drew[q] ? (d > off ? 1u : 0u) + (d < -off ? 0x10000u : 0u) : 0u;
+            beyond += drew[q] ? (d > off ? 1u : 0u) + (d < -off ? 0x400u : 0u) : 0u;
         }
         beyond = wave_sum_u32(beyond);
-        const u32 above = beyond & 0xFFFFu, below = beyond >> 16;
+        const u32 above = beyond & 0x3FFu, below = (beyond >> 10) & 0x3FFu, equal = beyond >> 20;
         const u32 fewer = above < below ? above : below, more = above < below ? below : above;
         const bool even = static_cast<float>(fewer) >= n * least_beyond && static_cast<float>(more) <= n * most_beyond;
-        // or some draws of the first 64 are many: weights on a grid.  (A loop: what is executed once is bound by fetching its
-        // instructions; unrolled over all draws this took 1.2 us.)
-        bool alike = open || !even;
-#pragma unroll 1
-        for (int c = 0; c < 32 && w.uneven_copies != w.hist_copies && !alike; c += 8) {
-            const u32 x = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(v[2][0]), c));
-            alike = __popcll(__ballot(drew[0] && ((v[2][0] ^ x) & ~kListCrowded) == 0)) >= 6;
-        }
+        const bool alike = open || !even || equal >= (W < 64 ? 5u : 9u);         // the last: weights on a grid (3 are equal where they are not)
         if (alike) marks |= kListUneven;
         const bool all_equal = !(var > 0.0f);
         if (!open && (even || all_equal)) {
