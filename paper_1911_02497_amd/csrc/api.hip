@@ -14,6 +14,7 @@
 #include "k_window.h"
 #include "k_struct_fused.h"
 #include "k_struct_list.h"
+#include "k_struct_strip.h"
 
 namespace condensa {
 
@@ -310,6 +311,18 @@ static u32 list_groups(u64 n, int J, bool per_tensor, const Config& cfg) {      
     return w;
 }
 
+// Block pruning in strips: sampling workgroups, blocks that each draws, and bins over the window: a few blocks to each of a bin's places.
+constexpr u64 kStripMostBlocks = static_cast<u64>(1) << 24, kStripMostElems = static_cast<u64>(1) << 30;
+struct StripSample { u32 groups, log_bins; };
+static StripSample strip_sample_size(u64 F) {
+    StripSample s;
+    s.groups = F < (1u << 17) ? 32u : (F < (1u << 18) ? 64u : (F < (1u << 20) ? 128u : 256u));
+    const double listed = 8.0 * static_cast<double>(F) / std::sqrt(static_cast<double>(s.groups) * kStripSample);  // in the window of a threshold in the middle, at the most
+    s.log_bins = 8;
+    while (s.log_bins < 13 && listed / 24 > static_cast<double>(1u << s.log_bins)) ++s.log_bins;
+    return s;
+}
+
 Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const Config& cfg, bool no_window) {
     Layout L;
     const bool per_tensor = (scope == CONDENSA_SCOPE_PER_TENSOR);
@@ -410,6 +423,22 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
             L.sample = off;   off += align_up(L.sample_cap * sizeof(u32));
             L.cand_key = off; off += align_up(L.cand_cap * sizeof(u32));      // ids of the listed blocks
             L.cand_idx = off; off += align_up(L.cand_cap * sizeof(u64));      // their aggregate keys
+            if (op == CONDENSA_OP_BLOCK_PRUNE && cfg[CONDENSA_OPT_SELECT_PATH] == 0 && F > kSmallGroup && F <= kStripMostBlocks && N <= kStripMostElems) {
+                const StripSample ss = strip_sample_size(F);
+                const size_t bins = static_cast<size_t>(1) << ss.log_bins;
+                L.strips = true;
+                L.s_zero = off;
+                L.s_hist = off;   off += align_up(bins * kStripCopies * sizeof(u32));
+                L.s_above = off;  off += align_up(kStripAboves * kListLine * sizeof(u32));
+                L.s_meet = off;   off += align_up(kMeetWords * sizeof(u32));
+                L.s_pass = off;   off += align_up(3 * kStripPassWords * sizeof(u32));
+                L.s_coarse = off; off += align_up((F / kStripGroup + 2) * kListLine * sizeof(u32));
+                L.s_win = off;    off += align_up(sizeof(ListWin));
+                L.s_local = off;  off += align_up(3 * static_cast<size_t>(ss.groups) * sizeof(u64));
+                L.s_key = off;    off += align_up(bins * kStripSlots * sizeof(u64));
+                L.s_id = off;     off += align_up(bins * kStripSlots * sizeof(u32));
+                L.s_share = off;  off += align_up(2 * kStripResolveGrid * sizeof(u32) + sizeof(u64));
+            }
         }
     } else if (!per_tensor && !no_window && op != CONDENSA_OP_COUNT_NONZERO && op != CONDENSA_OP_LC_SGD_STEP) {
         L.sample_cap = window_sample_size(N, cfg);
@@ -838,6 +867,11 @@ static u32 call_tag(u32 call) {
     return x ^ (x >> 16);
 }
 
+static u32 next_tag() {
+    static std::atomic<u32> calls{0};
+    return call_tag(calls.fetch_add(1, std::memory_order_relaxed));
+}
+
 // Begins the call, takes the sample and bounds the windows in one launch; false when the call is not of that form.
 template <bool LC, bool VEC>
 static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n_tensors, const OutDesc* out, size_t n_out, const Slot* slots,
@@ -876,8 +910,7 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
     b.fillers = static_cast<u32>(begin_blocks(b.n_zero, tb.n_chunks));
     const u32 bounds = shape.bounds ? (per_tensor ? static_cast<u32>(n_tensors) : 1u) : 0u;
     ListArgs w = list_args(L, ws, tb.N, L.n_slots, shape, rq, cfg);
-    static std::atomic<u32> calls{0};
-    w.tag = call_tag(calls.fetch_add(1, std::memory_order_relaxed));
+    w.tag = next_tag();
     img->launching(st);
     hipLaunchKernelGGL((k_begin_sample<LC, VEC>), dim3(1 + groups + b.fillers + bounds), dim3(kListThreads), sample_lds(J), st, b, w);
     CONDENSA_LAUNCH_CHECK();
@@ -1482,6 +1515,131 @@ condensa_status condensa_count_nonzero(const condensa_tensor* tensors, int n_ten
 
 namespace condensa {
 
+// Lays the strips of every tensor when the call is one for them: GLOBAL scope (the layout has their regions), blocks of two dimensions and at most
+// kStripArea elements, theta apart from the weights, a threshold strictly inside the population.  b2, b3: the widest blocks there are.
+struct StripPlan { u32 n_tiles = 0, b2 = 1, b3 = 1; bool quad = true; };
+static bool strip_plan(Tables& tb, int n_tensors, const OutDesc* out, bool vec, const Slot& slot, const Layout& L, const Config& cfg, StripPlan* plan) {
+    if (!L.strips || cfg[CONDENSA_OPT_FUSED_SWEEP] != 0 || n_tensors > static_cast<int>(kStripTensors) || slot.k == 0 || slot.k >= slot.n) return false;
+    StripPlan p;
+    p.quad = vec;
+    bool any = false;
+    for (int t = 0; t < n_tensors; ++t) {
+        const TensorDesc& d = tb.td[t];
+        if (d.n == 0) continue;
+        if (d.d[0] != 1 || d.d[1] != 1 || d.b[0] != 1 || d.b[1] != 1 || d.d[3] > (1u << 26) || out[t].theta == d.w) return false;
+        p.b2 = d.b[2] > p.b2 ? d.b[2] : p.b2;
+        p.b3 = d.b[3] > p.b3 ? d.b[3] : p.b3;
+        if (d.d[3] % 4 != 0 || d.b[3] % 4 != 0) p.quad = false;
+        any = any || out[t].theta || out[t].mask;
+    }
+    if (!any || static_cast<u64>(p.b2) * p.b3 > kStripArea) return false;
+    u64 tiles = 0;
+    for (int t = 0; t < n_tensors; ++t) {
+        TensorDesc& d = tb.td[t];
+        if (d.n == 0) { d.reserved[0] = tiles; continue; }
+        tiles += strip_layout(&d, p.quad, tiles);
+    }
+    if (tiles >= L.cand_cap) return false;                  // (their counts go where the list of blocks would)
+    p.n_tiles = static_cast<u32>(tiles);
+    *plan = p;
+    return true;
+}
+
+static condensa_status run_strips(const Layout& L, const Tables& tb, int n_tensors, const std::vector<OutDesc>& out, const std::vector<Slot>& slots, const StripPlan& plan,
+                                  double* sumsq_dev, float* norms_dev, int32_t* keep_idx_dev, uint8_t* structure_mask_dev, condensa_select* results_dev,
+                                  void* ws, hipStream_t st, const Config& cfg) {
+    const StripSample ss = strip_sample_size(tb.F);
+    Layout Z = L;                                           // of the counters, only these are used
+    Z.zero_begin = L.s_zero;
+    Z.zero_bytes = L.s_coarse + align_up((plan.n_tiles / kStripGroup + 1) * kListLine * sizeof(u32)) - L.s_zero;
+    StructArgs a{};
+    a.td = at<TensorDesc>(ws, L.td);
+    a.slots = at<Slot>(ws, L.slots);
+    a.keys = at<u64>(ws, L.skeys);
+    a.F = tb.F;
+    a.n_tensors = n_tensors;
+    ListArgs w{};
+    w.local = at<u64>(ws, L.s_local);
+    w.n_local = ss.groups;
+    w.tag = next_tag();
+    w.win = at<ListWin>(ws, L.s_win);
+    w.margin16 = static_cast<int>(cfg[CONDENSA_OPT_WINDOW_MARGIN]);
+    w.force = t_force;
+    StripArgs s{};
+    s.win = w.win;
+    s.hist = at<u32>(ws, L.s_hist);
+    s.key = at<u64>(ws, L.s_key);
+    s.id = at<u32>(ws, L.s_id);
+    s.log_bins = ss.log_bins;
+    s.n_tiles = plan.n_tiles;
+    s.above = at<u32>(ws, L.s_above);
+    s.tiles = at<uint2>(ws, L.cand_idx);
+    s.coarse = at<u32>(ws, L.s_coarse);
+    s.pass = at<u32>(ws, L.s_pass);
+    s.meet = at<u32>(ws, L.s_meet);
+    s.share = at<u32>(ws, L.s_share);
+    s.tie_end = reinterpret_cast<u64*>(s.share + 2 * kStripResolveGrid);
+    s.out = at<OutDesc>(ws, L.out);
+    s.keep_idx = keep_idx_dev;
+    s.user_mask = structure_mask_dev;
+    s.results = results_dev;
+    s.quad = plan.quad ? 1 : 0;
+    StageImage img;
+    const size_t td_bytes = static_cast<size_t>(tb.n_td) * sizeof(TensorDesc), out_bytes = out.size() * sizeof(OutDesc), slot_bytes = sizeof(Slot);
+    const bool one = n_tensors <= kStripBeginTensors && td_bytes + out_bytes + slot_bytes <= kStageBytes;
+    if (one) {
+        const condensa_status rc = img.acquire(td_bytes + out_bytes + slot_bytes, st);
+        if (rc != CONDENSA_OK) return rc;
+    }
+    if (one && img.data() != nullptr) {
+        PhaseTimer timer(CONDENSA_PHASE_SAMPLE, st, cfg);
+        StripBeginArgs b{};
+        b.up = fill_image(img, Z, ws, tb, out.data(), out_bytes, slots.data(), slot_bytes, nullptr, 0);
+        b.zero = at<uint4>(ws, Z.zero_begin);
+        b.n_zero = Z.zero_bytes / 16;
+        b.F = tb.F;
+        b.k = slots[0].k;
+        b.n_tensors = n_tensors;
+        b.groups = ss.groups;
+        b.fillers = static_cast<u32>((b.n_zero + 2 * kStripBegin - 1) / (2 * kStripBegin));
+        b.b2 = plan.b2;
+        b.b3 = plan.b3;
+        b.quad = s.quad;
+        for (int t = 0; t < n_tensors; ++t) {
+            b.w[t] = tb.td[t].w;
+            b.d2[t] = tb.td[t].d[2];
+            b.d3[t] = tb.td[t].d[3];
+        }
+        for (int t = 0; t <= n_tensors; ++t) b.start[t] = static_cast<u32>(tb.td[t].struct_start);
+        img.launching(st);
+        hipLaunchKernelGGL(k_strip_begin, dim3(1 + b.groups + b.fillers + 1), dim3(kStripBegin), 0, st, b, w);
+        CONDENSA_LAUNCH_CHECK();
+        img.commit();
+    } else {
+        const condensa_status rc = begin_call(Z, tb, n_tensors, out.data(), out.size(), slots.data(), 1, ws, st, &img);
+        if (rc != CONDENSA_OK) return rc;
+        PhaseTimer timer(CONDENSA_PHASE_SAMPLE, st, cfg);
+        hipLaunchKernelGGL(k_strip_sample, dim3(ss.groups), dim3(kStripBegin), 0, st, a, w, plan.b2, plan.b3, s.quad);
+        CONDENSA_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_strip_bounds, dim3(1), dim3(64), 0, st, w, ss.groups);
+        CONDENSA_LAUNCH_CHECK();
+    }
+    {
+        PhaseTimer timer(CONDENSA_PHASE_AGGREGATE, st, cfg);
+        if (plan.quad) hipLaunchKernelGGL((k_struct_strips<true>), dim3(plan.n_tiles), dim3(kStripThreads), 0, st, a, s, sumsq_dev, norms_dev);
+        else           hipLaunchKernelGGL((k_struct_strips<false>), dim3(plan.n_tiles), dim3(kStripThreads), 0, st, a, s, sumsq_dev, norms_dev);
+        CONDENSA_LAUNCH_CHECK();
+    }
+    PhaseTimer timer(CONDENSA_PHASE_RESOLVE, st, cfg);
+    u64 grid = (tb.F + kMaskTile - 1) / kMaskTile;
+    if (grid > kStripResolveGrid) grid = kStripResolveGrid;
+    for (int late = 0; late <= ((t_force & kForceLate) ? 1 : 0); ++late) {
+        hipLaunchKernelGGL(k_strip_resolve, dim3(static_cast<unsigned>(grid)), dim3(kResolveThreads), 0, st, a, s);
+        CONDENSA_LAUNCH_CHECK();
+    }
+    return CONDENSA_OK;
+}
+
 static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, double density, int scope,
                                            float* const* theta, uint8_t* const* mask, double* sumsq_dev,
                                            float* norms_dev, int32_t* keep_idx_dev, uint8_t* structure_mask_dev,
@@ -1522,6 +1680,10 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
         const u64 n = per_tensor ? tb.td[g].n_struct : tb.F;
         init_slot(&slots[g], n, kept_count(density, n), 1u);
     }
+    StripPlan plan;
+    if (strip_plan(tb, n_tensors, out.data(), vec, slots[0], L, cfg, &plan))
+        return run_strips(L, tb, n_tensors, out, slots, plan, sumsq_dev, norms_dev, keep_idx_dev, structure_mask_dev, results_dev, workspace_dev,
+                          static_cast<hipStream_t>(stream), cfg);
     // One sweep for aggregation AND apply (k_struct_fused.h): 8x8 blocks, every matrix a whole number of 64-block
     // runs wide, 128-bit accesses everywhere, outputs apart from the weights, a threshold strictly inside the
     // population, and enough blocks for the sample to pay (or the form asked for): 2^20 blocks take 218 us this way and

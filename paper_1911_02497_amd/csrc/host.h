@@ -21,7 +21,7 @@ extern std::atomic<uint64_t> g_launches;        // kernels enqueued since the li
 // What a test has the calls of its own thread go through although the device is idle (condensa_test_force, not part of the
 // interface; 0: nothing).  All of it can happen by itself where other streams hold the chip, and no result depends on it.
 enum : u32 {
-    kForceLate = 1,        // the workgroups of k_list_resolve start once more when all of its work is done
+    kForceLate = 1,        // the workgroups of k_list_resolve and k_strip_resolve start once more when all of its work is done
     kForceNoSample = 2,    // the workgroups that bound windows give up on the samples without a look
     kForceNoVerdict = 4,   // the workgroups that posted entries in k_list_resolve do not wait for the verdict on them
     kForceAsk = 8,         // ... wait, but take no notice, so that they learn of it when they want to leave
@@ -165,6 +165,9 @@ struct Layout {
     size_t sample = 0, cand_key = 0, cand_idx = 0;          // window path
     size_t cand_w = 0, cand_lam = 0;                        // inputs of the candidates (fused sweep)
     size_t sorted_windows = 0;                              // several densities: the windows in sweep order
+    bool strips = false;                                    // block pruning in strips (k_struct_strip.h) has its regions
+    size_t s_zero = 0, s_hist = 0, s_above = 0, s_meet = 0, s_pass = 0, s_coarse = 0;      // cleared, the last as far as it is needed
+    size_t s_win = 0, s_local = 0, s_key = 0, s_id = 0, s_share = 0;
     u64 sample_cap = 0, cand_cap = 0;
     size_t total = 0;
     u64 max_chunks = 0, max_schunks = 0;

@@ -593,7 +593,8 @@ __device__ inline float wave_sum_f32(float v) {            // in every lane
     v = add(v, dpp_or_zero<0x143, 0xC>(__float_as_uint(v)));
     return __uint_as_float(static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(v)), 63)));
 }
-template <bool WAIT, typename NothingOf>
+// LOW: the lowest bits of the words, which say nothing (list_sample: twelve).
+template <bool WAIT, u32 LOW = 0xFFFu, typename NothingOf>
 __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0, u32 W, NothingOf&& nothing_of) {
     __shared__ ListWin s_win[kMaxJ];
     __shared__ u32 s_order[kMaxJ + 1];
@@ -689,7 +690,7 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
                 const float least = -static_cast<float>(ref), most = static_cast<float>(0x7FFFFFFFu - ref);
                 return d <= least ? 0u : (d >= most ? 0x7FFFFFFFu : ref + static_cast<u32>(static_cast<int>(d)));
             };
-            const u32 half = 0x800u;             // the words' low 12 bits say nothing
+            const u32 half = (LOW + 1u) / 2;
             const u32 hi = at(mean[0] + off), lo = at(mean[1] - off);
             word[0] = hi < 0x7FFFFFFFu - half ? hi + half : 0x7FFFFFFFu;
             word[1] = lo < half ? 0u : lo - half;
@@ -707,7 +708,7 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
                     if (!drew[q]) v[i][q] = 0xFFFFFFFFu;
                 }
             }
-            for (u32 bit = 0x40000000u; bit > 0xFFFu; bit >>= 1)         // the largest keys with at most that many of them below
+            for (u32 bit = 0x40000000u; bit > LOW; bit >>= 1)         // the largest keys with at most that many of them below
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     u32 n_below = 0;
@@ -715,8 +716,8 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
                     for (int q = 0; q < kPer; ++q) n_below += static_cast<u32>(__popcll(__ballot(v[i][q] < (word[i] | bit))));
                     if (n_below <= pick[i]) word[i] |= bit;
                 }
-            word[0] |= 0xFFFu;                   // the words' low bits (list_sample)
-            word[2] |= 0x800u;
+            word[0] |= LOW;
+            word[2] |= (LOW + 1u) / 2;
         }
         if (given_up || n_drew < 2) { word[0] = 0x7FFFFFFFu; word[1] = 0; marks = kListCrowded; }
         const ListWin x = list_window_of(word, nothing_of(j), marks);
