@@ -313,14 +313,18 @@ static u32 list_groups(u64 n, int J, bool per_tensor, const Config& cfg) {      
 
 // Block pruning in strips: sampling workgroups, blocks that each draws, and bins over the window: a few blocks to each of a bin's places.
 constexpr u64 kStripMostBlocks = static_cast<u64>(1) << 24, kStripMostElems = static_cast<u64>(1) << 30;
-struct StripSample { u32 groups, log_bins; };
-static StripSample strip_sample_size(u64 F) {
-    StripSample s;
-    s.groups = F < (1u << 17) ? 32u : (F < (1u << 18) ? 64u : (F < (1u << 20) ? 128u : 256u));
-    const double listed = 8.0 * static_cast<double>(F) / std::sqrt(static_cast<double>(s.groups) * kStripSample);  // in the window of a threshold in the middle, at the most
-    s.log_bins = 8;
-    while (s.log_bins < 13 && listed / 24 > static_cast<double>(1u << s.log_bins)) ++s.log_bins;
-    return s;
+struct StripBins { u32 log_bins, log_room; };
+static u32 strip_groups(u64 F) { return F < (1u << 17) ? 32u : (F < (1u << 18) ? 64u : (F < (1u << 20) ? 128u : 256u)); }
+// Rounds of draws: a second one, some 8 us, where there are so many blocks that a narrower window is worth it, and where the threshold is among the first
+// or last three of 128 draws, which would leave it unbounded (the fallback takes 15-20 us).
+static u32 strip_rounds(u64 F, u64 k) { return F >= (1u << 22) || (k < F - k ? k : F - k) < F / 50 ? 2u : 1u; }
+static StripBins strip_bins(u64 F) {
+    const double draws = static_cast<double>(strip_groups(F)) * strip_rounds(F, F / 2) * kStripSample;
+    const double listed = 8.0 * static_cast<double>(F) / std::sqrt(draws);             // in the window of a threshold in the middle, at the most
+    StripBins b{8, 5};
+    while ((1u << b.log_bins) < kStripMostBins && listed / 24 > static_cast<double>(1u << b.log_bins)) ++b.log_bins;
+    while ((kStripCopies << b.log_room) < kStripMostSlots && listed > 0.75 * static_cast<double>(1u << (b.log_bins + b.log_room))) ++b.log_room;
+    return b;
 }
 
 Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const Config& cfg, bool no_window) {
@@ -424,19 +428,19 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
             L.cand_key = off; off += align_up(L.cand_cap * sizeof(u32));      // ids of the listed blocks
             L.cand_idx = off; off += align_up(L.cand_cap * sizeof(u64));      // their aggregate keys
             if (op == CONDENSA_OP_BLOCK_PRUNE && cfg[CONDENSA_OPT_SELECT_PATH] == 0 && F > kSmallGroup && F <= kStripMostBlocks && N <= kStripMostElems) {
-                const StripSample ss = strip_sample_size(F);
-                const size_t bins = static_cast<size_t>(1) << ss.log_bins;
+                const StripBins sb = strip_bins(F);
+                const size_t bins = static_cast<size_t>(1) << sb.log_bins, slots = bins * kStripCopies << sb.log_room;
                 L.strips = true;
                 L.s_zero = off;
                 L.s_hist = off;   off += align_up(bins * kStripCopies * sizeof(u32));
                 L.s_above = off;  off += align_up(kStripAboves * kListLine * sizeof(u32));
                 L.s_meet = off;   off += align_up(kMeetWords * sizeof(u32));
                 L.s_pass = off;   off += align_up(3 * kStripPassWords * sizeof(u32));
-                L.s_coarse = off; off += align_up((F / kStripGroup + 2) * kListLine * sizeof(u32));
+                L.s_coarse = off; off += align_up((F / 64 + 2) * kListLine * sizeof(u32));
                 L.s_win = off;    off += align_up(sizeof(ListWin));
-                L.s_local = off;  off += align_up(3 * static_cast<size_t>(ss.groups) * sizeof(u64));
-                L.s_key = off;    off += align_up(bins * kStripSlots * sizeof(u64));
-                L.s_id = off;     off += align_up(bins * kStripSlots * sizeof(u32));
+                L.s_local = off;  off += align_up(3 * static_cast<size_t>(strip_groups(F)) * sizeof(u64));
+                L.s_key = off;    off += align_up(slots * sizeof(u64));
+                L.s_id = off;     off += align_up(slots * sizeof(u32));
                 L.s_share = off;  off += align_up(2 * kStripResolveGrid * sizeof(u32) + sizeof(u64));
             }
         }
@@ -1516,7 +1520,10 @@ condensa_status condensa_count_nonzero(const condensa_tensor* tensors, int n_ten
 namespace condensa {
 
 // Lays the strips of every tensor when the call is one for them: GLOBAL scope (the layout has their regions), blocks of two dimensions and at most
-// kStripArea elements, theta apart from the weights, a threshold strictly inside the population.  b2, b3: the widest blocks there are.
+// kStripArea elements, theta apart from the weights, a threshold strictly inside the population.  b2, b3: the widest blocks there are.  Larger blocks
+// leave a strip's additions to a few threads (43 thousand of 32x32: 196 us, 130 with the aggregates first).  Every such call takes the strips: they were ahead
+// or even from 4 thousand blocks (7 thousand of 5x5 33 -> 27 us; 45 thousand of 8x8, the threshold among the highest 2 %, 36 -> 38) to 2^24; beyond, and beyond
+// 2^30 weights, nothing was measured and k_struct_fused.h or the radix levels go on.
 struct StripPlan { u32 n_tiles = 0, b2 = 1, b3 = 1; bool quad = true; };
 static bool strip_plan(Tables& tb, int n_tensors, const OutDesc* out, bool vec, const Slot& slot, const Layout& L, const Config& cfg, StripPlan* plan) {
     if (!L.strips || cfg[CONDENSA_OPT_FUSED_SWEEP] != 0 || n_tensors > static_cast<int>(kStripTensors) || slot.k == 0 || slot.k >= slot.n) return false;
@@ -1548,10 +1555,12 @@ static bool strip_plan(Tables& tb, int n_tensors, const OutDesc* out, bool vec, 
 static condensa_status run_strips(const Layout& L, const Tables& tb, int n_tensors, const std::vector<OutDesc>& out, const std::vector<Slot>& slots, const StripPlan& plan,
                                   double* sumsq_dev, float* norms_dev, int32_t* keep_idx_dev, uint8_t* structure_mask_dev, condensa_select* results_dev,
                                   void* ws, hipStream_t st, const Config& cfg) {
-    const StripSample ss = strip_sample_size(tb.F);
+    const StripBins sb = strip_bins(tb.F);
+    const u32 groups = strip_groups(tb.F), rounds = strip_rounds(tb.F, slots[0].k);
+    const u32 log_group = plan.n_tiles < (1u << 14) ? 6u : 9u;           // a workgroup of k_strip_resolve adds up the counts of so many strips, and of all groups
     Layout Z = L;                                           // of the counters, only these are used
     Z.zero_begin = L.s_zero;
-    Z.zero_bytes = L.s_coarse + align_up((plan.n_tiles / kStripGroup + 1) * kListLine * sizeof(u32)) - L.s_zero;
+    Z.zero_bytes = L.s_coarse + align_up(((plan.n_tiles >> log_group) + 1) * kListLine * sizeof(u32)) - L.s_zero;
     StructArgs a{};
     a.td = at<TensorDesc>(ws, L.td);
     a.slots = at<Slot>(ws, L.slots);
@@ -1560,7 +1569,7 @@ static condensa_status run_strips(const Layout& L, const Tables& tb, int n_tenso
     a.n_tensors = n_tensors;
     ListArgs w{};
     w.local = at<u64>(ws, L.s_local);
-    w.n_local = ss.groups;
+    w.n_local = groups;
     w.tag = next_tag();
     w.win = at<ListWin>(ws, L.s_win);
     w.margin16 = static_cast<int>(cfg[CONDENSA_OPT_WINDOW_MARGIN]);
@@ -1570,7 +1579,9 @@ static condensa_status run_strips(const Layout& L, const Tables& tb, int n_tenso
     s.hist = at<u32>(ws, L.s_hist);
     s.key = at<u64>(ws, L.s_key);
     s.id = at<u32>(ws, L.s_id);
-    s.log_bins = ss.log_bins;
+    s.log_bins = sb.log_bins;
+    s.log_room = sb.log_room;
+    s.log_group = log_group;
     s.n_tiles = plan.n_tiles;
     s.above = at<u32>(ws, L.s_above);
     s.tiles = at<uint2>(ws, L.cand_idx);
@@ -1584,6 +1595,8 @@ static condensa_status run_strips(const Layout& L, const Tables& tb, int n_tenso
     s.user_mask = structure_mask_dev;
     s.results = results_dev;
     s.quad = plan.quad ? 1 : 0;
+    s.units = plan.b2 * plan.b3 / (plan.quad ? 4 : 1);
+    s.by_units = make_fastdiv(s.units);
     StageImage img;
     const size_t td_bytes = static_cast<size_t>(tb.n_td) * sizeof(TensorDesc), out_bytes = out.size() * sizeof(OutDesc), slot_bytes = sizeof(Slot);
     const bool one = n_tensors <= kStripBeginTensors && td_bytes + out_bytes + slot_bytes <= kStageBytes;
@@ -1600,7 +1613,8 @@ static condensa_status run_strips(const Layout& L, const Tables& tb, int n_tenso
         b.F = tb.F;
         b.k = slots[0].k;
         b.n_tensors = n_tensors;
-        b.groups = ss.groups;
+        b.groups = groups;
+        b.rounds = rounds;
         b.fillers = static_cast<u32>((b.n_zero + 2 * kStripBegin - 1) / (2 * kStripBegin));
         b.b2 = plan.b2;
         b.b3 = plan.b3;
@@ -1619,9 +1633,9 @@ static condensa_status run_strips(const Layout& L, const Tables& tb, int n_tenso
         const condensa_status rc = begin_call(Z, tb, n_tensors, out.data(), out.size(), slots.data(), 1, ws, st, &img);
         if (rc != CONDENSA_OK) return rc;
         PhaseTimer timer(CONDENSA_PHASE_SAMPLE, st, cfg);
-        hipLaunchKernelGGL(k_strip_sample, dim3(ss.groups), dim3(kStripBegin), 0, st, a, w, plan.b2, plan.b3, s.quad);
+        hipLaunchKernelGGL(k_strip_sample, dim3(groups), dim3(kStripBegin), 0, st, a, w, rounds, plan.b2, plan.b3, s.quad);
         CONDENSA_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_strip_bounds, dim3(1), dim3(64), 0, st, w, ss.groups);
+        hipLaunchKernelGGL(k_strip_bounds, dim3(1), dim3(64), 0, st, w, groups);
         CONDENSA_LAUNCH_CHECK();
     }
     {
@@ -1631,7 +1645,7 @@ static condensa_status run_strips(const Layout& L, const Tables& tb, int n_tenso
         CONDENSA_LAUNCH_CHECK();
     }
     PhaseTimer timer(CONDENSA_PHASE_RESOLVE, st, cfg);
-    u64 grid = (tb.F + kMaskTile - 1) / kMaskTile;
+    u64 grid = (tb.F + kStripSettle - 1) / kStripSettle;
     if (grid > kStripResolveGrid) grid = kStripResolveGrid;
     for (int late = 0; late <= ((t_force & kForceLate) ? 1 : 0); ++late) {
         hipLaunchKernelGGL(k_strip_resolve, dim3(static_cast<unsigned>(grid)), dim3(kResolveThreads), 0, st, a, s);

@@ -14,6 +14,10 @@
 //      between estimate and threshold, say how many come before) and the few blocks that were decided wrongly.
 //      Where the window missed, or a bin has more than its places (equal aggregates), the workgroups that are running find the threshold
 //      in a few passes over the stored keys, meeting in between (Meet), and settle in the same way.
+// Against aggregates, list and apply sweep, us a call: 688 128 blocks of 8x8 in 96 matrices 134 -> 98 (traced: 9, 77 and 16), 270 400 of 5x5 51.6 -> 39
+// (9, 18 and 13), 786 thousand of 4x4 69 -> 49, 172 thousand of 16x16 122 -> 101, 2.7 M of 5x5 304 -> 203, 16.8 M of 4x4 890 -> 669.
+// Weights pruned before (2^20 blocks of 4x4, nine tenths of them zero, the threshold among them) 116 -> 91, two scales with the threshold between them
+// 76 -> 84.
 // Section 3.1 (the schemes aggregate blocks), Table 1 (BlockPrune: blocks of any dimensionality and a given size).
 #pragma once
 #include "k_listed.h"
@@ -22,33 +26,38 @@
 namespace condensa {
 
 constexpr int kStripThreads = 128;               // of the sweep
-constexpr int kResolveThreads = 256;
+constexpr int kResolveThreads = 512;
+constexpr u32 kStripSettle = kResolveThreads * 4;          // blocks that a workgroup settles at a time
 constexpr int kStripBegin = 512;                 // threads of the launch that begins the call
 constexpr u32 kStripPer = 4;                     // loads of four elements that a thread makes for half a strip
 constexpr u32 kStripQuads = kStripPer * kStripThreads;
 constexpr u32 kStripLds = 2304;                  // elements of half a strip in LDS: sixteen workgroups to a compute unit
 constexpr u32 kStripBlocks = 2 * kStripThreads;  // blocks of a strip at most
 constexpr u32 kStripArea = 256;                  // elements of a block at most: the chain of additions of one thread
-constexpr u32 kStripCopies = 4, kStripRoom = 32; // of a bin: counters, chosen by strip, and places of each
-constexpr u32 kStripSlots = kStripCopies * kStripRoom;
+constexpr u32 kStripCopies = 4;                  // counters of a bin, chosen by strip
+constexpr u32 kStripMostSlots = 1024;            // places of a bin at most, the same number for each counter
+constexpr u32 kStripMostBins = 2048;             // every workgroup of k_strip_resolve reads all counters (with 8192 bins, 2.7 M blocks took it 86 us)
 constexpr u32 kStripAboves = 64;                 // counters of the blocks above the window, a line each
-constexpr u32 kStripGroup = 64;                  // strips whose counts are added up
 constexpr u32 kStripTensors = 1024;              // tensors of a call at most: a wavefront looks at all their starts
-constexpr u32 kStripSample = 128, kStripLanes = kStripBegin / kStripSample;         // sampled blocks of a workgroup, and lanes that share one
-constexpr u32 kStripPassBins = 512;
+constexpr u32 kStripLanes = 4, kStripSample = kStripBegin / kStripLanes;           // lanes that share a sampled block, and blocks of a workgroup at once
+constexpr u32 kStripRounds = 2;                  // at most
+constexpr int kStripPassBits = 10;
+constexpr u32 kStripPassBins = 1u << kStripPassBits;
 constexpr u32 kStripPassWords = kStripPassBins * 5 + kListLine;          // counts, greatest and (complemented) least keys, and the keys above
-constexpr int kStripResolveGrid = 1024;
+constexpr int kStripResolveGrid = 512;           // two to a compute unit
 
 struct StripArgs {
     const ListWin* win;
     u32* hist;             // [bins][kStripCopies] blocks offered
-    u64* key;              // [bins][kStripCopies][kStripRoom]
+    u64* key;              // [bins][kStripCopies][room]
     u32* id;
     u32 log_bins;          // at least 8
+    u32 log_room;          // at least 5
+    u32 log_group;         // strips whose counts are added up, a power of two
     u32 n_tiles;
     u32* above;            // [kStripAboves][kListLine]
     uint2* tiles;          // [n_tiles + 1] first id and provisionally kept blocks of a strip
-    u32* coarse;           // [n_tiles / kStripGroup + 1][kListLine] the latter added up, a line each: the updates of a line take turns, some 10 ns each
+    u32* coarse;           // [n_tiles / group + 1][kListLine] the latter added up, a line each: the updates of a line take turns, some 10 ns each
     u32* pass;             // [3][kStripPassWords] a pass of the fallback: this one, the next and the one being cleared
     u32* meet;             // [kMeetWords]
     u32* share;            // [2][kStripResolveGrid] keys above the threshold and ties in the share of each workgroup
@@ -58,6 +67,8 @@ struct StripArgs {
     u8* user_mask;
     condensa_select* results;
     int quad;              // every access to the tensors takes sixteen bytes, aligned, inside one block
+    u32 units;             // quads, or elements, of a block
+    FastDiv by_units;
 };
 
 // A tensor's strips, in the spare words of its descriptor: the first one's number, block columns and block rows of a strip (several rows of
@@ -80,13 +91,20 @@ inline u64 strip_layout(TensorDesc* d, bool quad, u64 first) {
     while (across > 1 && !fits(across, 1)) --across;
     const u64 pieces = (G3 + across - 1) / across;
     across = (G3 + pieces - 1) / pieces;
+    if (quad && pieces > 1) {                              // whole lines of 128 bytes, so that no two strips write to one
+        u64 lines = 1;
+        while (lines * b3 % 32 != 0) lines *= 2;
+        const u64 up = (across + lines - 1) / lines * lines;
+        if (fits(up, 1)) across = up;
+    }
+    const u64 pieces_now = (G3 + across - 1) / across;
     u64 down = 1;
-    while (pieces == 1 && down < G2 && fits(across, down + 1)) ++down;
+    while (pieces_now == 1 && down < G2 && fits(across, down + 1)) ++down;
     const u64 rows = (G2 + down - 1) / down;
     down = (G2 + rows - 1) / rows;
     d->reserved[0] = first | (across << 32);
-    d->reserved[1] = down | (pieces << 32);
-    return rows * pieces;
+    d->reserved[1] = down | (pieces_now << 32);
+    return rows * pieces_now;
 }
 
 // Bins over the window, and from where on a block is provisionally kept: of a crowded window's equals, none.
@@ -95,22 +113,27 @@ __device__ inline u32 strip_shift(const ListWin& w, u32 log_bins) {
     return span < (1u << log_bins) ? 0u : 32u - log_bins - static_cast<u32>(__clz(static_cast<int>(span)));
 }
 __device__ inline u32 strip_mid(const ListWin& w) { return win_crowded(w) ? w.hi + 1u : w.mid; }
+// Where the draws say that the keys crowd at a few places (equal ones, a gap), too many would meet in a bin: a few of its places are no use,
+// and its counters would be what the sweep waits for (2^20 blocks of 4x4 in two scales, the threshold between them: 127 us
+// listed, 84 now).
+__device__ inline bool strip_listed(const ListWin& w) { return !win_crowded(w) && !win_uneven(w); }
 
 // ---- sample ----------------------------------------------------------------------------------------------
 
 struct StripMatrix { const float* w; u32 start, d2, d3; };
 
-// One sampling workgroup, number `me` of W (a power of two): kStripSample blocks out of as many equal stretches of the population, in units of
+// One sampling workgroup, number `me` of W (a power of two): kStripSample ROUNDS blocks out of as many equal stretches of the population, in units of
 // four neighbours (which share lines), four lanes to a block (one lane alone made up to 32 loads of single elements, each from another line: the
-// launch took 19.7 us for 270 400 blocks of 5x5).  Bound by latency.  The sums are added in any order: the sample need not be exact.
+// launch took 19.7 us for 270 400 blocks of 5x5).  Bound by latency.  Their sums are added in any order and in binary32: a sample need not be exact (blocks
+// of 16x16: 10.5 us, in binary64 16.5).
 template <typename MatrixOf>
-__device__ inline void strip_sample(const ListArgs& w, u32 W, u32 me, u32 b2, u32 b3, int quad, u64 F, u64 k, MatrixOf&& matrix_of) {
-    __shared__ __align__(16) u32 s_key[kStripSample];
-    const u32 tid = threadIdx.x, i = tid / kStripLanes, mine = tid % kStripLanes;
-    {
+__device__ inline void strip_sample(const ListArgs& w, u32 W, u32 me, u32 rounds, u32 b2, u32 b3, int quad, u64 F, u64 k, MatrixOf&& matrix_of) {
+    __shared__ __align__(16) u32 s_key[kStripRounds * kStripSample];
+    const u32 tid = threadIdx.x, mine = tid % kStripLanes, count = rounds * kStripSample;
+    for (u32 i = tid / kStripLanes; i < count; i += kStripSample) {      // uniform
         const u32 units = static_cast<u32>(F / 4), turn = mix32(~(i >> 2)) & (W - 1);      // every W-th stretch can lie in one column of blocks, whose scale
         const u32 u = (i >> 2) * W + ((me + turn) & (W - 1));                            // is its own
-        const int log_stretches = 31 - __clz(static_cast<int>(kStripSample / 4 * W));
+        const int log_stretches = 31 - __clz(static_cast<int>(count / 4 * W));
         const u32 place = static_cast<u32>((static_cast<u64>(u) * units + __umulhi(mix32(u), units)) >> log_stretches);
         const u64 id = static_cast<u64>(place < units ? place : units - 1) * 4 + (i & 3u);
         const StripMatrix m = matrix_of(id);
@@ -118,7 +141,7 @@ __device__ inline void strip_sample(const ListArgs& w, u32 W, u32 me, u32 b2, u3
         const u32 h = m.d2 - g2 * b2 < b2 ? m.d2 - g2 * b2 : b2, wd = m.d3 - g3 * b3 < b3 ? m.d3 - g3 * b3 : b3;
         const float* p = m.w + static_cast<u64>(g2) * b2 * m.d3 + static_cast<u64>(g3) * b3;
         const u32 per = quad ? 4u : 1u, n = h * wd / per, in_row = wd / per, inv = ((1u << 20) + in_row - 1) / in_row;
-        double acc = 0.0;
+        float acc = 0.0f;
         for (u32 j0 = 0; j0 < b2 * b3 / per; j0 += 8 * kStripLanes) {     // uniform; every lane loads, without a branch
             float4 v[8];
 #pragma unroll
@@ -129,23 +152,24 @@ __device__ inline void strip_sample(const ListArgs& w, u32 W, u32 me, u32 b2, u3
                 else      v[j] = make_float4(*q, 0.0f, 0.0f, 0.0f);
             }
 #pragma unroll
-            for (u32 j = 0; j < 8; ++j) if (j0 + j * kStripLanes + mine < n) acc = add_squares(acc, v[j]);
+            for (u32 j = 0; j < 8; ++j) {
+                const float x = v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
+                acc += j0 + j * kStripLanes + mine < n ? x : 0.0f;
+            }
         }
 #pragma unroll
-        for (u32 d = 1; d < kStripLanes; d *= 2) {
-            const u64 bits = static_cast<u64>(__double_as_longlong(acc));
-            const u64 other = (static_cast<u64>(__shfl_xor(static_cast<u32>(bits >> 32), static_cast<int>(d), 64)) << 32) | __shfl_xor(static_cast<u32>(bits), static_cast<int>(d), 64);
-            acc += __longlong_as_double(static_cast<long long>(other));
-        }
-        if (mine == 0) s_key[i] = static_cast<u32>(static_cast<u64>(__double_as_longlong(acc)) >> 32) & 0x7FFFFFFFu;
+        for (u32 d = 1; d < kStripLanes; d *= 2) acc += __shfl_xor(acc, static_cast<int>(d), 64);
+        if (mine == 0) s_key[i] = static_cast<u32>(static_cast<u64>(__double_as_longlong(static_cast<double>(acc))) >> 32) & 0x7FFFFFFFu;
     }
     __syncthreads();
     // every key's rank by counting, four threads to a key; the three wanted ranks as in list_sample_units, one to either side
-    const float all = static_cast<float>(kStripSample), ks = static_cast<float>(k) / static_cast<float>(F) * all;
+    const float all = static_cast<float>(count), ks = static_cast<float>(k) / static_cast<float>(F) * all;
+    const u64 tag = static_cast<u64>(w.tag) << 32;
+    for (u32 i = tid / kStripLanes; i < count; i += kStripSample) {      // uniform
     const u32 key = s_key[i];
     u32 higher = 0, same = 0, lower = 0;                   // lower: equal ones before this
-#pragma unroll
-    for (u32 e0 = 0; e0 < kStripSample; e0 += 4 * kStripLanes) {
+#pragma unroll 8
+    for (u32 e0 = 0; e0 < count; e0 += 4 * kStripLanes) {
         const u32 e = e0 + 4 * mine;
         const uint4 x = *reinterpret_cast<const uint4*>(s_key + e);
         higher += (x.x > key ? 1u : 0u) + (x.y > key ? 1u : 0u) + (x.z > key ? 1u : 0u) + (x.w > key ? 1u : 0u);
@@ -158,7 +182,6 @@ __device__ inline void strip_sample(const ListArgs& w, u32 W, u32 me, u32 b2, u3
         same += __shfl_xor(same, static_cast<int>(d), 64);
         lower += __shfl_xor(lower, static_cast<int>(d), 64);
     }
-    const u64 tag = static_cast<u64>(w.tag) << 32;
 #pragma unroll
     for (u32 which = 0; which < 3; ++which) {
         float x = which == 0 ? floorf(ks - 1.0f) : (which == 1 ? ceilf(ks + 1.0f) + 1.0f : floorf(ks + 0.5f));
@@ -166,8 +189,9 @@ __device__ inline void strip_sample(const ListArgs& w, u32 W, u32 me, u32 b2, u3
         const u32 want = x >= 1.0f && x <= all ? static_cast<u32>(x) : 0u;
         u64* const to = &w.local[static_cast<u64>(which) * w.n_local + me];
         if (want == 0) { if (tid == 0) st_dev64(to, tag | kSampleNone); }
-        // three in a hundred equal: their bins would have no room for them, and their counters no time
-        else if (mine == 0 && lower == 0 && higher < want && want <= higher + same) st_dev64(to, tag | key | (same >= 4 ? kListCrowded : 0u));
+        // so many of a hundred equal: their bins would have no room for them, and their counters no time
+        else if (mine == 0 && lower == 0 && higher < want && want <= higher + same) st_dev64(to, tag | key | (same >= 4 && same * 64 >= count ? kListCrowded : 0u));
+    }
     }
 }
 
@@ -180,6 +204,7 @@ struct StripBeginArgs {
     int n_tensors;
     u32 groups;            // sampling workgroups: after the one that fetches the tables
     u32 fillers;           // workgroups that clear: after these.  Then one that bounds the window
+    u32 rounds;            // of samples in each
     u32 b2, b3;
     int quad;
     const float* w[kStripBeginTensors];
@@ -205,7 +230,7 @@ __global__ __launch_bounds__(kStripBegin) void k_strip_begin(StripBeginArgs b, L
         __shared__ StripMatrix s_m[kStripBeginTensors];
         if (tid < static_cast<u32>(b.n_tensors)) s_m[tid] = StripMatrix{b.w[tid], b.start[tid], b.d2[tid], b.d3[tid]};
         __syncthreads();
-        strip_sample(w, b.groups, block, b.b2, b.b3, b.quad, b.F, b.k, [&](u64 id) {
+        strip_sample(w, b.groups, block, b.rounds, b.b2, b.b3, b.quad, b.F, b.k, [&](u64 id) {
             int lo = 0, hi = b.n_tensors - 1;
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
@@ -220,8 +245,8 @@ __global__ __launch_bounds__(kStripBegin) void k_strip_begin(StripBeginArgs b, L
 }
 
 // The same as launches of their own (many tensors, captured calls).
-__global__ __launch_bounds__(kStripBegin) void k_strip_sample(StructArgs a, ListArgs w, u32 b2, u32 b3, int quad) {
-    strip_sample(w, gridDim.x, blockIdx.x, b2, b3, quad, a.F, a.slots[0].k, [&](u64 id) {
+__global__ __launch_bounds__(kStripBegin) void k_strip_sample(StructArgs a, ListArgs w, u32 rounds, u32 b2, u32 b3, int quad) {
+    strip_sample(w, gridDim.x, blockIdx.x, rounds, b2, b3, quad, a.F, a.slots[0].k, [&](u64 id) {
         const TensorDesc& td = a.td[tensor_of_struct(a.td, a.n_tensors, id)];
         return StripMatrix{td.w, static_cast<u32>(td.struct_start), td.d[2], td.d[3]};
     });
@@ -241,7 +266,7 @@ typedef u32 u32_loose __attribute__((aligned(1)));
 // a strip's loads are in flight at once, but only half of its rows stand in LDS at a time (the sums go on from the first half to the second): 256 KB of
 // weights to a compute unit.
 template <bool QUAD>
-__global__ __launch_bounds__(kStripThreads, 6) void k_struct_strips(StructArgs a, StripArgs s, double* sumsq, float* norms) {
+__global__ __launch_bounds__(kStripThreads, 5) void k_struct_strips(StructArgs a, StripArgs s, double* sumsq, float* norms) {
     __shared__ __align__(16) float s_tile[kStripLds];
     __shared__ u8 s_keep[kStripBlocks];
     __shared__ u32 s_count[2];
@@ -269,7 +294,7 @@ __global__ __launch_bounds__(kStripThreads, 6) void k_struct_strips(StructArgs a
     const u32 per_block = b3 / 4, log_per = 31u - static_cast<u32>(__clz(static_cast<int>(per_block | 1u)));
     const u32 swap_mask = (per_block & (per_block - 1)) ? 0u : per_block - 1, swap_shift = log_per < 4 ? 4 - log_per : 0u;      // (QUAD)
     const float* const w = td.w + origin;
-    const bool narrow = !QUAD && cols < 4;                 // uniform
+    const bool narrow = !QUAD && cols < 4, plain = !QUAD && !narrow && stride == b3;       // uniform
 
     float4 v[2 * kStripPer];
     u32 where[2 * kStripPer];                              // row << 16 | column
@@ -316,17 +341,21 @@ __global__ __launch_bounds__(kStripThreads, 6) void k_struct_strips(StructArgs a
             const u32 row = (where[i] >> 16) - p0, col = where[i] & 0xFFFFu;
             const u32 bc = fast_div(col, by_b3);
             u32 x = col - bc * b3;
-            if (QUAD) {
+            if constexpr (QUAD) {
                 const u32 at = row * (lds_row / 4) + bc * per_block + ((x / 4) ^ ((bc >> swap_shift) & swap_mask));
                 reinterpret_cast<float4*>(s_tile)[at] = v[i];
             } else {
-                const float e[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
                 u32 at = row * lds_row + bc * stride + x;
+                if (plain) {                               // uniform: what a column is away from another it is in LDS too
+                    s_tile[at] = v[i].x; s_tile[at + 1] = v[i].y; s_tile[at + 2] = v[i].z; s_tile[at + 3] = v[i].w;
+                } else {
+                    const float e[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
 #pragma unroll
-                for (u32 k = 0; k < 4; ++k) {
-                    if (k < cols) s_tile[at] = e[k];
-                    ++at;
-                    if (++x == b3) { x = 0; at += stride - b3; }
+                    for (u32 k = 0; k < 4; ++k) {
+                        if (k < cols) s_tile[at] = e[k];
+                        ++at;
+                        if (++x == b3) { x = 0; at += stride - b3; }
+                    }
                 }
             }
         }
@@ -338,7 +367,7 @@ __global__ __launch_bounds__(kStripThreads, 6) void k_struct_strips(StructArgs a
             const u32 h = to > from ? to - from : 0u, wd = cols - bc_of[g] * b3 < b3 ? cols - bc_of[g] * b3 : b3;
             if (h == 0) continue;
             double sum = acc[g];
-            if (QUAD) {
+            if constexpr (QUAD) {
                 const float4* const base = reinterpret_cast<const float4*>(s_tile) + (from - p0) * (lds_row / 4) + bc_of[g] * per_block;
                 const u32 turn = (bc_of[g] >> swap_shift) & swap_mask, wq = wd / 4, n = h * wq;
                 u32 x = 0, at = 0;
@@ -376,15 +405,15 @@ __global__ __launch_bounds__(kStripThreads, 6) void k_struct_strips(StructArgs a
     }
     u64 key[kMine];
     u32 list_at[kMine], place[kMine];
+    const u32 room = 1u << s.log_room;
 #pragma unroll
     for (u32 g = 0; g < kMine; ++g) {
         const u32 b = b0 + g * kStripThreads;
-        place[g] = kStripRoom;
+        place[g] = room;
         key[g] = 0;
         list_at[g] = 0;
         if ((b & ~63u) >= n_blocks) continue;              // uniform over the wavefront
         const bool mine = b < n_blocks;
-        const u64 u = u0 + b;
         key[g] = static_cast<u64>(__double_as_longlong(acc[g])) & 0x7FFFFFFFFFFFFFFFull;
         const u32 upper = static_cast<u32>(key[g] >> 32);
         const bool keep = mine && upper >= strip_mid(win);
@@ -395,19 +424,16 @@ __global__ __launch_bounds__(kStripThreads, 6) void k_struct_strips(StructArgs a
         }
         s_keep[b] = keep ? 1 : 0;
         if (mine) {
-            if (upper - win.lo <= win.hi - win.lo && !win_crowded(win)) {
+            if (strip_listed(win) && upper - win.lo <= win.hi - win.lo) {
                 list_at[g] = ((upper - win.lo) >> strip_shift(win, s.log_bins)) * kStripCopies + tile % kStripCopies;
                 place[g] = atomicAdd(&s.hist[list_at[g]], 1u);           // on its way while the strip is written
             }
-            a.keys[u] = key[g];
-            if (sumsq) sumsq[u] = acc[g];
-            if (norms) norms[u] = static_cast<float>(sqrt(acc[g]));
         }
     }
     __syncthreads();
     if (tid == 0) {
         s.tiles[tile] = make_uint2(static_cast<u32>(u0), s_count[0]);
-        if (s_count[0]) atomicAdd(&s.coarse[tile / kStripGroup * kListLine], s_count[0]);
+        if (s_count[0]) atomicAdd(&s.coarse[(tile >> s.log_group) * kListLine], s_count[0]);
         if (s_count[1]) atomicAdd(&s.above[tile % kStripAboves * kListLine], s_count[1]);
         if (tile + 1 == s.n_tiles) s.tiles[s.n_tiles] = make_uint2(static_cast<u32>(a.F), 0u);
     }
@@ -426,33 +452,47 @@ __global__ __launch_bounds__(kStripThreads, 6) void k_struct_strips(StructArgs a
             if (th) st4_stream(th + e, k ? v[i].x : 0.0f, k ? v[i].y : 0.0f, k ? v[i].z : 0.0f, k ? v[i].w : 0.0f);
             if (mk) st_mask4_stream(mk + e, k, k, k, k);
         } else {
-            u32 x = col - bc * b3;
-            const float y[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-            u8 k[4];
-            float z[4];
+            u32 x = col - bc * b3, m = 0;                  // mask bytes
+            if (b3 >= 3 && !narrow) {                      // uniform: four elements lie in two blocks at most
+                const u32 end = b3 - x, in_first = end >= 4 ? 0xFFFFFFFFu : (1u << (8 * end)) - 1u;
+                m = (s_keep[at] * 0x01010101u & in_first) | (s_keep[end >= 4 ? at : at + 1] * 0x01010101u & ~in_first);
+            } else {
 #pragma unroll
-            for (u32 j = 0; j < 4; ++j) {
-                k[j] = j < cols ? s_keep[at] : 0;
-                z[j] = k[j] ? y[j] : 0.0f;
-                if (++x == b3) { x = 0; ++at; }
+                for (u32 j = 0; j < 4; ++j) {
+                    m |= (j < cols ? static_cast<u32>(s_keep[at]) : 0u) << (8 * j);
+                    if (++x == b3) { x = 0; ++at; }
+                }
             }
+            auto kept = [&](float y, u32 j) { return (m >> (8 * j)) & 1u ? y : 0.0f; };
             if (!narrow) {
-                if (th) { f32x4_loose t; t.x = z[0]; t.y = z[1]; t.z = z[2]; t.w = z[3]; __builtin_nontemporal_store(t, reinterpret_cast<f32x4_loose*>(th + e)); }
-                if (mk) *reinterpret_cast<u32_loose*>(mk + e) = static_cast<u32>(k[0]) | (static_cast<u32>(k[1]) << 8) | (static_cast<u32>(k[2]) << 16) | (static_cast<u32>(k[3]) << 24);
+                if (th) {
+                    f32x4_loose t;
+                    t.x = kept(v[i].x, 0); t.y = kept(v[i].y, 1); t.z = kept(v[i].z, 2); t.w = kept(v[i].w, 3);
+                    __builtin_nontemporal_store(t, reinterpret_cast<f32x4_loose*>(th + e));
+                }
+                if (mk) *reinterpret_cast<u32_loose*>(mk + e) = m;
             } else {
                 for (u32 j = 0; j < cols; ++j) {
-                    if (th) th[e + j] = j == 0 ? z[0] : (j == 1 ? z[1] : z[2]);
-                    if (mk) mk[e + j] = j == 0 ? k[0] : (j == 1 ? k[1] : k[2]);
+                    if (th) th[e + j] = j == 0 ? kept(v[i].x, 0) : (j == 1 ? kept(v[i].y, 1) : kept(v[i].z, 2));
+                    if (mk) mk[e + j] = static_cast<u8>((m >> (8 * j)) & 1u);
                 }
             }
         }
     }
 #pragma unroll
-    for (u32 g = 0; g < kMine; ++g)
-        if (place[g] < kStripRoom) {
-            s.key[static_cast<u64>(list_at[g]) * kStripRoom + place[g]] = key[g];
-            s.id[static_cast<u64>(list_at[g]) * kStripRoom + place[g]] = static_cast<u32>(u0 + b0 + g * kStripThreads);
+    for (u32 g = 0; g < kMine; ++g) {
+        const u32 b = b0 + g * kStripThreads;
+        if (b >= n_blocks) continue;
+        const u64 u = u0 + b;
+        a.keys[u] = key[g];
+        if (sumsq) sumsq[u] = acc[g];
+        if (norms) norms[u] = static_cast<float>(sqrt(acc[g]));
+        if (place[g] < room) {
+            const u64 to = (static_cast<u64>(list_at[g]) << s.log_room) + place[g];
+            s.key[to] = key[g];
+            s.id[to] = static_cast<u32>(u);
         }
+    }
 }
 
 // ---- after the sweep ---------------------------------------------------------------------------------------
@@ -464,47 +504,54 @@ struct StripFound {        // the threshold
 };
 
 struct StripShared {
-    u64 key[kStripSlots];
-    u32 id[kStripSlots];
+    u64 key[kStripMostSlots];
+    u32 id[kStripMostSlots];
     u32 cnt[kStripPassBins];
     u64 most[kStripPassBins], leastc[kStripPassBins];
-    uint2 queue[kMaskTile];          // blocks decided wrongly: id, tensor << 1 | kept
+    uint2 queue[kStripSettle];          // blocks decided wrongly: id, tensor << 1 | kept
     u64 T, tie_end, a, b;
     u32 wave[kResolveThreads / 64];
-    u32 rem, n_tie, n, bin, rank, found, over, above, n_queue;
+    u32 rem, n_tie, n, bin, rank, found, over, n_queue[3];
 };
 
-// Writes the listed blocks again, each by a few lanes.
+// Writes the listed blocks again, a quad or an element (of s.units to a block) at a time: a workgroup has a few of them as a rule, but all of its
+// blocks may be equal and decided by their place.
 __device__ inline void strip_rewrite(const StructArgs& a, const StripArgs& s, const StripShared& sh, u32 n) {
-    const u32 tid = threadIdx.x;
-    for (u32 q0 = 0; q0 < n; q0 += kResolveThreads / 16) {   // sixteen lanes to a block
-        const u32 q = q0 + tid / 16;
-        if (q >= n) continue;
-        const uint2 x = sh.queue[q];
-        const bool keep = x.y & 1u;
-        const int t = static_cast<int>(x.y >> 1);
-        const TensorDesc& td = a.td[t];
-        const u32 d2 = td.d[2], d3 = td.d[3], b2 = td.b[2], b3 = td.b[3];
-        const u32 G3 = fast_div(d3 + b3 - 1, td.fd[kDivB3]), i = x.x - static_cast<u32>(td.struct_start), g2 = i / G3, g3 = i - g2 * G3;
-        const u32 h = d2 - g2 * b2 < b2 ? d2 - g2 * b2 : b2, wd = d3 - g3 * b3 < b3 ? d3 - g3 * b3 : b3;
-        const u64 e0 = static_cast<u64>(g2) * b2 * d3 + static_cast<u64>(g3) * b3;
-        const OutDesc o = s.out[t];
-        const u8 k = keep ? 1 : 0;
-        if (s.quad) {
-            const u32 wq = wd / 4, n_q = h * wq, inv = ((1u << 20) + wq - 1) / wq;
-            for (u32 c = tid & 15u; c < n_q; c += 16) {
-                const u32 row = (c * inv) >> 20;
-                const u64 e = e0 + static_cast<u64>(row) * d3 + (c - row * wq) * 4;
-                if (o.theta) *reinterpret_cast<float4*>(o.theta + e) = keep ? *reinterpret_cast<const float4*>(td.w + e) : make_float4(0.f, 0.f, 0.f, 0.f);
-                if (o.mask) *reinterpret_cast<u32*>(o.mask + e) = keep ? 0x01010101u : 0u;
-            }
-        } else {
-            const u32 n_e = h * wd, inv = ((1u << 20) + wd - 1) / wd;
-            for (u32 c = tid & 15u; c < n_e; c += 16) {
-                const u32 row = (c * inv) >> 20;
-                const u64 e = e0 + static_cast<u64>(row) * d3 + (c - row * wd);
-                if (o.theta) o.theta[e] = keep ? td.w[e] : 0.0f;
-                if (o.mask) o.mask[e] = k;
+    const u32 items = n * s.units;
+    constexpr u32 kAtOnce = 2;
+    for (u32 i0 = threadIdx.x; i0 < items; i0 += kAtOnce * kResolveThreads) {
+        u64 e[kAtOnce];
+        float* theta[kAtOnce];
+        u8* mask[kAtOnce];
+        float4 x[kAtOnce];
+        bool keep[kAtOnce], there[kAtOnce];
+#pragma unroll
+        for (u32 j = 0; j < kAtOnce; ++j) {
+            const u32 i = i0 + j * kResolveThreads, q = fast_div(i < items ? i : 0u, s.by_units), c = (i < items ? i : 0u) - q * s.units;
+            const uint2 entry = sh.queue[q];
+            const int t = static_cast<int>(entry.y >> 1);
+            const TensorDesc& td = a.td[t];
+            const u32 d2 = td.d[2], d3 = td.d[3], b2 = td.b[2], b3 = td.b[3];
+            const u32 G3 = fast_div(d3 + b3 - 1, td.fd[kDivB3]), b = entry.x - static_cast<u32>(td.struct_start), g2 = b / G3, g3 = b - g2 * G3;
+            const u32 h = d2 - g2 * b2 < b2 ? d2 - g2 * b2 : b2, wd = d3 - g3 * b3 < b3 ? d3 - g3 * b3 : b3;
+            const u32 per = s.quad ? 4u : 1u, in_row = wd / per, row = ((((1u << 20) + in_row - 1) / in_row) * c) >> 20;         // c < 256
+            keep[j] = (entry.y & 1u) != 0;
+            there[j] = i < items && row < h;
+            e[j] = (static_cast<u64>(g2) * b2 + (there[j] ? row : 0u)) * d3 + static_cast<u64>(g3) * b3 + (there[j] ? (c - row * in_row) * per : 0u);
+            theta[j] = s.out[t].theta;
+            mask[j] = s.out[t].mask;
+            x[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (keep[j] && there[j]) { if (s.quad) x[j] = *reinterpret_cast<const float4*>(td.w + e[j]); else x[j].x = td.w[e[j]]; }
+        }
+#pragma unroll
+        for (u32 j = 0; j < kAtOnce; ++j) {
+            if (!there[j]) continue;
+            if (s.quad) {
+                if (theta[j]) *reinterpret_cast<float4*>(theta[j] + e[j]) = x[j];
+                if (mask[j]) *reinterpret_cast<u32*>(mask[j] + e[j]) = keep[j] ? 0x01010101u : 0u;
+            } else {
+                if (theta[j]) theta[j][e[j]] = x[j].x;
+                if (mask[j]) mask[j][e[j]] = keep[j] ? 1 : 0;
             }
         }
     }
@@ -528,19 +575,23 @@ __device__ inline int strip_tensor_of(const StructArgs& a, u64 u) {
     return static_cast<int>(upto) - 1;
 }
 // `key`: strip_keys of this thread's first blocks, from id0 rounded down to a multiple of four; t0: id0's tensor.
+template <bool REWRITE>
 __device__ inline void strip_settle(const StructArgs& a, const StripArgs& s, StripShared& sh, const StripFound& f, u32 mid, u64 id0, u64 id1, u32 before, int t0,
                                     u64 (&key)[kMaskPer]) {
     const u32 tid = threadIdx.x;
     if (id0 >= id1) return;                                // uniform
     const u64 next_start = a.td[t0 + 1].struct_start;
     const bool wide = (reinterpret_cast<uintptr_t>(s.user_mask) & 3u) == 0;
-    const u64 base0 = id0 & ~static_cast<u64>(kMaskPer - 1);
-    for (u64 base = base0; base < id1; base += kMaskTile) {
+    if (REWRITE && tid < 3) sh.n_queue[tid] = 0;
+    __syncthreads();
+    u32 turn = 0;                                          // whose queue it is: the one after it is cleared when all have left the one before it
+    for (u64 base = id0 & ~static_cast<u64>(kMaskPer - 1); base < id1; base += kStripSettle) {
         const u64 i0 = base + tid * kMaskPer;
         const bool full = i0 >= id0 && i0 + kMaskPer <= id1;
-        if (base != base0) strip_keys(a, i0, key);
-        if (tid == 0) sh.n_queue = 0;
-        __syncthreads();
+        u64 next[kMaskPer] = {0, 0, 0, 0};
+        if (base + kStripSettle < id1) strip_keys(a, i0 + kStripSettle, next);         // on their way
+        const u32 after = turn == 2 ? 0u : turn + 1;
+        if (REWRITE && tid == 0 && base + kStripSettle < id1) sh.n_queue[after] = 0;
         u32 keep[kMaskPer], n = 0;
 #pragma unroll
         for (int k = 0; k < kMaskPer; ++k) {
@@ -549,10 +600,10 @@ __device__ inline void strip_settle(const StructArgs& a, const StripArgs& s, Str
             keep[k] = there && (key[k] > f.T || (key[k] == f.T && u < f.tie_end)) ? 1u : 0u;
             n += keep[k];
             const u32 was = static_cast<u32>(key[k] >> 32) >= mid ? 1u : 0u;
-            if (there && was != keep[k]) {
+            if (REWRITE && there && was != keep[k]) {
                 int t = t0;
                 if (u >= next_start) while (t + 1 < a.n_tensors && a.td[t + 1].struct_start <= u) ++t;
-                sh.queue[atomicAdd(&sh.n_queue, 1u)] = make_uint2(static_cast<u32>(u), static_cast<u32>(t) << 1 | keep[k]);
+                sh.queue[atomicAdd(&sh.n_queue[turn], 1u)] = make_uint2(static_cast<u32>(u), static_cast<u32>(t) << 1 | keep[k]);
             }
         }
         if (s.user_mask) {
@@ -570,8 +621,13 @@ __device__ inline void strip_settle(const StructArgs& a, const StripArgs& s, Str
 #pragma unroll
             for (int k = 0; k < kMaskPer; ++k) if (keep[k] && pos < a.F) s.keep_idx[pos++] = static_cast<int32_t>(i0 + k);
         }
-        const u32 n_queue = sh.n_queue;
-        if (n_queue) strip_rewrite(a, s, sh, n_queue);     // uniform
+#pragma unroll
+        for (int k = 0; k < kMaskPer; ++k) key[k] = next[k];
+        if (!REWRITE) continue;
+        const u32 n_queue = sh.n_queue[turn];
+        turn = after;
+        if (n_queue == 0) continue;                        // uniform
+        strip_rewrite(a, s, sh, n_queue);
         __syncthreads();                                   // the queue is used again
     }
 }
@@ -600,7 +656,7 @@ __device__ inline void strip_fallback(const StructArgs& a, const StripArgs& s, S
     u64 lo = static_cast<u64>(win.lo) << 32, hi = (static_cast<u64>(win.hi) << 32) | 0xFFFFFFFFull, rank = 0;          // rank 0: the interval is a guess
     u32 tie_here = 0, above_here = 0;
     StripFound f{0, 0, 0, 0};
-    for (u32 pass = 0;; ++pass) {                          // uniform over all workgroups; at most nine
+    for (u32 pass = 0;; ++pass) {                          // uniform over all workgroups; at most eight
         if (pass == 32) return;
         u32* const set = s.pass + pass % 3 * kStripPassWords;
         u32* const g_cnt = set;
@@ -608,8 +664,8 @@ __device__ inline void strip_fallback(const StructArgs& a, const StripArgs& s, S
         u64* const g_leastc = g_most + kStripPassBins;
         u32* const g_above = set + 5 * kStripPassBins;
         const u64 span = hi - lo;
-        const u32 shift = span < kStripPassBins ? 0u : static_cast<u32>(64 - 9 - __clzll(static_cast<long long>(span)));
-        static_assert(kStripPassBins == 1u << 9, "nine bits a pass");
+        const u32 shift = span < kStripPassBins ? 0u : static_cast<u32>(64 - kStripPassBits - __clzll(static_cast<long long>(span)));
+        static_assert(kStripPassBins == 2 * kResolveThreads, "two bins a thread");
         for (u32 i = tid; i < kStripPassBins; i += kResolveThreads) { sh.cnt[i] = 0; sh.most[i] = 0; sh.leastc[i] = 0; }
         __syncthreads();
         u32 above = 0;
@@ -697,10 +753,35 @@ __device__ inline void strip_fallback(const StructArgs& a, const StripArgs& s, S
         f.tie_end = ld_dev64(s.tie_end);
     }
     if (m.rank == 0 && tid == 0) strip_record(a, s, f);
+    // The blocks decided wrongly may be neighbours (equal ones up to the last tie kept), so everybody takes a few of everywhere.
+    const u32 mid = strip_mid(win);
+    const u64 stride = static_cast<u64>(m.size) * kResolveThreads;
+    for (u64 base = static_cast<u64>(m.rank) * kResolveThreads; base < a.F; base += kMaskPer * stride) {
+        u64 there[kMaskPer];
+#pragma unroll
+        for (int j = 0; j < kMaskPer; ++j) { const u64 u = base + j * stride + tid; there[j] = u < a.F ? a.keys[u] : 0; }
+        if (tid == 0) sh.n_queue[0] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kMaskPer; ++j) {
+            const u64 first = base + j * stride, u = first + tid;
+            if (first >= a.F) break;                       // uniform
+            const u32 keep = there[j] > f.T || (there[j] == f.T && u < f.tie_end) ? 1u : 0u, was = static_cast<u32>(there[j] >> 32) >= mid ? 1u : 0u;
+            int t = strip_tensor_of(a, first);
+            if (u < a.F && keep != was) {
+                while (t + 1 < a.n_tensors && a.td[t + 1].struct_start <= u) ++t;
+                sh.queue[atomicAdd(&sh.n_queue[0], 1u)] = make_uint2(static_cast<u32>(u), static_cast<u32>(t) << 1 | keep);
+            }
+        }
+        __syncthreads();
+        const u32 n = sh.n_queue[0];
+        if (n) strip_rewrite(a, s, sh, n);                 // uniform
+        __syncthreads();                                   // the queue is used again
+    }
     if (i0 >= i1) return;                                  // uniform
     u64 key[kMaskPer];
     strip_keys(a, (i0 & ~static_cast<u64>(kMaskPer - 1)) + tid * kMaskPer, key);
-    strip_settle(a, s, sh, f, strip_mid(win), i0, i1, above_before + (ties_before < f.rem ? ties_before : f.rem), strip_tensor_of(a, i0), key);
+    strip_settle<false>(a, s, sh, f, mid, i0, i1, above_before + (ties_before < f.rem ? ties_before : f.rem), strip_tensor_of(a, i0), key);
 }
 
 // Bound by latency: a launch and a chain of some six dependent loads -- the counters, the counters of one thread's bins, the places of the bins
@@ -715,20 +796,20 @@ __global__ __launch_bounds__(kResolveThreads) void k_strip_resolve(StructArgs a,
     // what comes before this workgroup's strips, and what lies above the window
     u32 above = tid < kStripAboves ? s.above[tid * kListLine] : 0u, before = 0;
     if (s.keep_idx) {
-        for (u32 i = tid; i < t0 / kStripGroup; i += kResolveThreads) before += s.coarse[i * kListLine];
-        const u32 i = t0 / kStripGroup * kStripGroup + tid;
-        if (i < t0) before += s.tiles[i].y;
+        for (u32 i = tid; i < t0 >> s.log_group; i += kResolveThreads) before += s.coarse[i * kListLine];
+        for (u32 i = (t0 >> s.log_group << s.log_group) + tid; i < t0; i += kResolveThreads) before += s.tiles[i].y;
     }
+    // (counting the blocks by runs of bins too, so that 32 KB need not be read, cost the sweep 3 us and gained 1)
     const uint4* const counts = reinterpret_cast<const uint4*>(s.hist);      // of a bin
     static_assert(kStripCopies == 4, "a bin's counters are loaded together");
-    const u32 per = bins / kResolveThreads;                // bins of a thread, from the top
+    const u32 per = bins > static_cast<u32>(kResolveThreads) ? bins / kResolveThreads : 1u;           // bins of a thread, from the top
     u32 sum = 0;
     for (u32 i = 0; i < per; i += 4) {
         uint4 c[4];
 #pragma unroll
-        for (u32 j = 0; j < 4; ++j) c[j] = i + j < per ? counts[bins - 1 - (tid * per + i + j)] : make_uint4(0, 0, 0, 0);
+        for (u32 j = 0; j < 4; ++j) c[j] = counts[bins - 1 - (tid * per + i + j < bins ? tid * per + (i + j < per ? i + j : i) : 0u)];
 #pragma unroll
-        for (u32 j = 0; j < 4; ++j) sum += c[j].x + c[j].y + c[j].z + c[j].w;
+        for (u32 j = 0; j < 4; ++j) sum += i + j < per && tid * per + i + j < bins ? c[j].x + c[j].y + c[j].z + c[j].w : 0u;
     }
     u64 mine[kMaskPer];                                    // the keys that this thread settles first
     strip_keys(a, (id0 & ~static_cast<u64>(kMaskPer - 1)) + tid * kMaskPer, mine);
@@ -738,11 +819,11 @@ __global__ __launch_bounds__(kResolveThreads) void k_strip_resolve(StructArgs a,
     wg_incl_scan_u32<kResolveThreads>(above, sh.wave, &above);
     const u32 upto = wg_incl_scan_u32<kResolveThreads>(sum, sh.wave, &inside);
     const u32 r = k - above;                               // wanted among the listed ones, if 1 <= r <= inside
-    if (!win_crowded(win) && above < k && upto - sum < r && r <= upto) { sh.a = tid; sh.rank = r - (upto - sum); sh.found = 1; }      // one thread at most
+    if (strip_listed(win) && above < k && upto - sum < r && r <= upto) { sh.a = tid; sh.rank = r - (upto - sum); sh.found = 1; }      // one thread at most
     __syncthreads();
     if (sh.found && tid < 64) {                            // its bins, a lane each
         const u32 bin = bins - 1 - (static_cast<u32>(sh.a) * per + lane), want = sh.rank;
-        static_assert((1u << 13) / kResolveThreads <= 64, "a lane a bin");
+        static_assert(kStripMostBins / kResolveThreads <= 64, "a lane a bin");
         const uint4 c = lane < per ? counts[bin] : make_uint4(0, 0, 0, 0);
         const u32 n = c.x + c.y + c.z + c.w, incl = wave_incl_scan_u32(n);
         if (incl - n < want && want <= incl) { sh.bin = bin; sh.rank = want - (incl - n); }
@@ -753,27 +834,46 @@ __global__ __launch_bounds__(kResolveThreads) void k_strip_resolve(StructArgs a,
     // The places of the bins between the estimate and the threshold, which lies in one of them; one that has no room for its blocks leaves it to the fallback.  Of the blocks
     // there that come before this workgroup's, those in other bins than the threshold's were decided wrongly.
     const u32 first = bin < mid_bin ? bin : mid_bin, last = bin < mid_bin ? mid_bin - 1 : bin;
-    const u32 n_slots = found ? (last - first + 1) * kStripSlots : 0u;
+    const u32 n_places = found ? (last - first + 1) * kStripCopies : 0u;
     u32 over = 0, wrong = 0;
-    for (u32 i0 = tid; i0 < n_slots; i0 += 4 * kResolveThreads) {
-        u32 n[4], id[4];
+    const u32 room = 1u << s.log_room, slots = kStripCopies << s.log_room;
+    for (u32 i = tid; found && i < slots; i += kResolveThreads) {        // the threshold's
+        const u32 at = bin * slots + i, have = s.hist[at >> s.log_room], id = s.id[at];                  // (garbage where there is no block)
+        const u64 key = s.key[at];
+        over |= have > room ? 1u : 0u;
+        if ((at & (room - 1)) < have) {
+            const u32 to = atomicAdd(&sh.n, 1u);
+            sh.key[to] = key;
+            sh.id[to] = id;
+        }
+    }
+    // A thread looks at the blocks of one copy of a bin, some ten: at eight at once without waiting for their number.
+    for (u32 i0 = tid; i0 < n_places; i0 += 2 * kResolveThreads) {
+        u32 have[2];
+        uint4 id[2][2];
 #pragma unroll
-        for (u32 j = 0; j < 4; ++j) {
-            const u32 i = i0 + j * kResolveThreads, at = first * kStripSlots + (i < n_slots ? i : tid);
-            n[j] = s.hist[at / kStripRoom];
-            id[j] = s.id[at];                              // (garbage where there is no block)
+        for (u32 j = 0; j < 2; ++j) {
+            const u32 i = i0 + j * kResolveThreads, at = first * kStripCopies + (i < n_places ? i : i0);
+            have[j] = s.hist[at];
+            id[j][0] = *reinterpret_cast<const uint4*>(s.id + (at << s.log_room));
+            id[j][1] = *reinterpret_cast<const uint4*>(s.id + (at << s.log_room) + 4);
         }
 #pragma unroll
-        for (u32 j = 0; j < 4; ++j) {
-            const u32 i = i0 + j * kResolveThreads, at = first * kStripSlots + i;
-            if (i >= n_slots) continue;
-            over |= n[j] > kStripRoom ? 1u : 0u;
-            const bool there = at % kStripRoom < n[j];
-            if (there && at / kStripSlots == bin) {
-                const u32 to = atomicAdd(&sh.n, 1u);
-                if (to < kStripSlots) { sh.key[to] = s.key[at]; sh.id[to] = id[j]; }
-            } else if (there && id[j] < id0) {
-                ++wrong;
+        for (u32 j = 0; j < 2; ++j) {
+            const u32 i = i0 + j * kResolveThreads, at = first * kStripCopies + i;
+            if (i >= n_places || at / kStripCopies == bin) continue;
+            over |= have[j] > room ? 1u : 0u;
+            auto count = [&](const uint4& x, u32 from) {
+                wrong += (from < have[j] && x.x < id0 ? 1u : 0u) + (from + 1 < have[j] && x.y < id0 ? 1u : 0u) +
+                         (from + 2 < have[j] && x.z < id0 ? 1u : 0u) + (from + 3 < have[j] && x.w < id0 ? 1u : 0u);
+            };
+            count(id[j][0], 0);
+            count(id[j][1], 4);
+            const uint4* const more = reinterpret_cast<const uint4*>(s.id + (at << s.log_room));
+            for (u32 from = 8; from < room && from < have[j]; from += 8) {
+                const uint4 x = more[from / 4], y = more[from / 4 + 1];
+                count(x, from);
+                count(y, from + 4);
             }
         }
     }
@@ -785,21 +885,24 @@ __global__ __launch_bounds__(kResolveThreads) void k_strip_resolve(StructArgs a,
         return;
     }
     const u32 n = sh.n;
-    {                                                      // two threads to an entry
-        const u32 i = tid >> 1;
+    for (u32 i0 = 0; i0 < n; i0 += kResolveThreads / 4) {  // four threads to an entry
+        const u32 i = i0 + tid / 4;
         const u64 key = sh.key[i < n ? i : 0];
         const u32 id = sh.id[i < n ? i : 0];
         u32 higher = 0, same = 0, lower = 0;
-        for (u32 e = tid & 1u; e < n; e += 2) {
+        for (u32 e = tid % 4; e < n; e += 4) {
             const u64 o = sh.key[e];
             higher += o > key ? 1u : 0u;
             same += o == key ? 1u : 0u;
             lower += o == key && sh.id[e] < id ? 1u : 0u;
         }
-        higher += __shfl_xor(higher, 1, 64);
-        same += __shfl_xor(same, 1, 64);
-        lower += __shfl_xor(lower, 1, 64);
-        if (i < n && (tid & 1u) == 0 && higher < want && want <= higher + same && lower == want - higher - 1) {       // the last one kept: one thread
+#pragma unroll
+        for (int d = 1; d < 4; d *= 2) {
+            higher += __shfl_xor(higher, d, 64);
+            same += __shfl_xor(same, d, 64);
+            lower += __shfl_xor(lower, d, 64);
+        }
+        if (i < n && tid % 4 == 0 && higher < want && want <= higher + same && lower == want - higher - 1) {       // the last one kept: one thread
             sh.T = key;
             sh.rem = want - higher;
             sh.n_tie = same;
@@ -811,8 +914,9 @@ __global__ __launch_bounds__(kResolveThreads) void k_strip_resolve(StructArgs a,
     if (s.keep_idx) {
         // bins below the estimate's that turn out to be kept, bins from it on that do not, and the threshold's own
         u32 add = bin < mid_bin ? wrong : 0u - wrong;
-        if (tid < n && sh.id[tid] < id0) {
-            const bool keep = sh.key[tid] > f.T || (sh.key[tid] == f.T && sh.id[tid] < f.tie_end), was = bin >= mid_bin;
+        for (u32 i = tid; i < n; i += kResolveThreads) {
+            if (sh.id[i] >= id0) continue;
+            const bool keep = sh.key[i] > f.T || (sh.key[i] == f.T && sh.id[i] < f.tie_end), was = bin >= mid_bin;
             add += static_cast<u32>(keep) - static_cast<u32>(was);
         }
         u32 total;
@@ -820,7 +924,7 @@ __global__ __launch_bounds__(kResolveThreads) void k_strip_resolve(StructArgs a,
         before = total;
     }
     if (blockIdx.x == 0 && tid == 0) strip_record(a, s, f);
-    strip_settle(a, s, sh, f, mid, id0, id1, before, tensor, mine);
+    strip_settle<true>(a, s, sh, f, mid, id0, id1, before, tensor, mine);
 }
 
 }  // namespace condensa

@@ -44,6 +44,7 @@ def _normal(shapes, seed):
     ((8, 8), [(515, 1028), (3, 4), (1200, 36)]),
     ((4, 4), [(300, 1604), (64, 4), (1000, 40)]),
     ((16, 16), [(1024, 1040), (720, 1000), (4096, 16)]),
+    ((64, 4), [(700, 4096), (1111, 100)]),
     ((2, 64), [(301, 4096), (9001, 60)]),
     ((5, 5), [(650, 650), (1, 1), (2, 3), (333, 331), (700, 3)]),
     ((3, 7), [(200, 4099), (41, 6), (2000, 21)]),
