@@ -40,7 +40,7 @@ N_STRESS = 64 * 4096 * 4608
 # kernel it was taken from (reported as null once they differ).
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "lc_step_large_model_hbm_counters.md")
 PRUNE_TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "prune_large_model_hbm_counters.md")
-KERNEL_SOURCES = ("paper_1911_02497_amd/csrc/common.h", "paper_1911_02497_amd/csrc/k_fused.h")
+KERNEL_SOURCES = ("paper_1911_02497_amd/csrc/common.h", "paper_1911_02497_amd/csrc/k_listed.h")
 SMALL_WORKLOADS = ("single_prune_fp16", "vgg_thresholds", "vgg_masks", "resnet_filter_global",
                    "resnet_filter_per_tensor", "transformer_block8", "transformer_block32")
 
@@ -259,10 +259,10 @@ def time_workload(name, args, P, workloads, torch, dev, steps, warmup, resident=
         k_ms = phases["sweep"]["ms"] / phases["sweep"]["intervals"]
         k_bpe = 9 if bpe == 9 else 4
         k_gbps = k_bpe * N / (k_ms * 1e-3) / 1e9
-        rec["roofline"] = {"bound": "hbm", "kernel": "k_window_fused<prune>" if bpe == 9 else "selection sweep(s)",
+        rec["roofline"] = {"bound": "hbm", "kernel": "k_list_sweep<prune>" if bpe == 9 else "selection sweep(s)",
                            "achieved": round(k_gbps, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                            "frac": round(k_gbps / HBM_PEAK_GBPS, 4),
-                           "traffic": measured_traffic("k_window_fused", info["tensors"], False, PRUNE_TRAFFIC_PROFILE) if bpe == 9 else None,
+                           "traffic": measured_traffic("k_list_sweep", info["tensors"], False, PRUNE_TRAFFIC_PROFILE) if bpe == 9 else None,
                            "avg_launch_ms": round(k_ms, 4),
                            "launches_averaged": phases["sweep"]["intervals"], "algorithmic_bytes_per_launch": k_bpe * N}
     if with_oracle:
@@ -637,13 +637,13 @@ def main():
     assert rec["k"] == int(np.floor(density * N + 0.5)) and rec["n"] == N, rec
 
     # ---- roofline of the dominant kernel --------------------------------------------------------------
-    # One-sweep window path (default): k_window_fused reads w, lambda (8 B) and writes theta, lambda', g
+    # One sweep (default: k_list_sweep; k_window_fused where the sampled window is asked for) reads w, lambda (8 B) and writes theta, lambda', g
     # (12 B) [+1 mask, +2 binary16 codes] per weight, and that is also all the step needs.  Two sweeps (radix
     # path, or --two-sweeps): k_lc_apply moves the same bytes and the selection reads w, lambda once more.
     one_sweep = rec["path"] == 2 and not args.two_sweeps
     kernel_bytes_per_elem = 20 + (1 if args.mask else 0) + (2 if pq else 0)
     step_bytes_per_elem = kernel_bytes_per_elem + (0 if one_sweep else 8)
-    kernel_name, phase = ("k_window_fused<LC>", "sweep") if one_sweep else ("k_lc_apply", "apply")
+    kernel_name, phase = ("k_list_sweep<LC>" if args.select_path == 0 else "k_window_fused<LC>", "sweep") if one_sweep else ("k_lc_apply", "apply")
     kp = phases[phase]
     kernel_ms = kp["ms"] / max(kp["intervals"], 1)
     achieved = kernel_bytes_per_elem * N / (kernel_ms * 1e-3) / 1e9 if kernel_ms > 0 else 0.0

@@ -244,17 +244,15 @@ static u64 window_cand_capacity(u64 N, int J, const Config& cfg) {
 // Which selection a call takes when its configuration does not say.  Listed windows (k_listed.h): PER_TENSOR scope and
 // several densities while the lists' 32-bit indices last (four densities: 2^26 weights 209 us against 461 with the
 // windows of several densities and 417-500 with radix levels, 2^28 weights 726 against 1152 and 1954).  One density: up to
-// 3 2^26 weights, where the lists cost as much as the sampled window's deeper ranking when each of their steps was a launch.
-// With one launch for all of them they are ahead beyond that line too (density 0.1, listed and sampled: pruning 2^27 weights 232 and
-// 316 us, 190 million 308 and 400, 2^28 418 and 507, 2^29 840 and 899, 2^30 1627 and 1680; L-C step 481 and 567, 674 and 767, 941 and
-// 997, 1917 and 2006, 3675 and 3670), so it could be moved.  Sampled window (k_window.h, k_fused.h): one density beyond that line,
-// several beyond 32-bit indices.  Radix levels: where neither applies.
+// 2^31 weights (density 0.1, listed and sampled: pruning 2^27 weights 232 and 316 us, 2^28 418 and 507, 2^29 840 and 899, 1.2 G 1746 and 1878; L-C step
+// 481 and 567, 941 and 997, 1917 and 2006, 3797 and 3921).  Sampled window (k_window.h, k_fused.h): one density beyond that line, where the list would
+// hold more than its workgroups settle quickly, several beyond 32-bit indices.  Radix levels: where neither applies.
 static bool list_fits(u64 N, int n_tensors, int n_slots) {
     return N > 0 && n_slots <= kListMaxRankings && N + static_cast<u64>(n_tensors) * kChunk < (static_cast<u64>(1) << 32);
 }
 static bool want_list(u64 N, int n_tensors, int n_slots, bool per_tensor, int J, const Config& cfg) {
     if (cfg[CONDENSA_OPT_SELECT_PATH] != 0 || !list_fits(N, n_tensors, n_slots)) return false;
-    return per_tensor || J > 1 || N < (static_cast<u64>(3) << 26);
+    return per_tensor || J > 1 || N < (static_cast<u64>(1) << 31);
 }
 static bool want_window(u64 N, int n_tensors, bool per_tensor, int J, const Config& cfg) {
     if (per_tensor) return false;
@@ -301,6 +299,8 @@ static u32 list_hist_copies(int n_slots) {
     while (c > 1 && c * static_cast<u32>(n_slots) > 256) c /= 2;
     return c;
 }
+static u32 list_posted(u64 N) { return N > kListLong ? kListPosted : kListFound; }
+static u32 list_walkers(u64 N) { return N > kListLong ? kMaxWalkers * kListParts : kMaxWalkers; }
 static u32 list_uneven_copies(int n_slots) { return n_slots == 1 ? 64u : list_hist_copies(n_slots); }
 static u32 list_groups(u64 n, int J, bool per_tensor, const Config& cfg) {         // sampling workgroups of a population
     const int64_t opt = cfg[CONDENSA_OPT_SAMPLE_LOG2];
@@ -355,7 +355,7 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
         L.l_nnz = off;     off += align_up(kListSegs * sizeof(u32));
         L.seg = off;       off += op == CONDENSA_OP_LC_STEP ? align_up(kNnzSegs * sizeof(u64)) : 0;
         L.l_hist = off;    off += align_up(static_cast<size_t>(L.n_slots) * list_uneven_copies(L.n_slots) * kListBins * sizeof(u32));
-        L.l_post = off;    off += L.n_slots == 1 ? align_up(256 + (kListFound + kMaxWalkers) * sizeof(u64) + kMaxWalkers * sizeof(u32)) : 0;
+        L.l_post = off;    off += L.n_slots == 1 ? align_up(256 + (list_posted(N) + list_walkers(N)) * sizeof(u64) + list_walkers(N) * sizeof(u32)) : 0;
         L.l_gathered = off; off += align_up(static_cast<size_t>(L.n_slots) * kListLine * sizeof(u32));
         L.l_fb = off;      off += align_up(sizeof(FallbackCtl));
         L.l_gmax = off;    off += align_up(2 * static_cast<size_t>(L.n_slots) * sizeof(u32));
@@ -824,8 +824,8 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const L
     w.arrived = at<u32>(ws, L.l_post);
     w.ended = w.arrived + kListLine;
     w.picked = at<u64>(ws, L.l_post + 256);
-    w.verdict = w.picked + kListFound;
-    w.range = reinterpret_cast<u32*>(w.verdict + kMaxWalkers);
+    w.verdict = w.picked + list_posted(N);
+    w.range = reinterpret_cast<u32*>(w.verdict + list_walkers(N));
     w.gathered = at<u32>(ws, L.l_gathered);
     w.bin_want = at<u32>(ws, L.l_want);
     w.gkey = at<u32>(ws, L.l_gkey);
@@ -973,8 +973,11 @@ static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* w
     }
     if (n_slots == 1) {
         for (int late = 0; late <= ((t_force & kForceLate) ? 1 : 0); ++late) {
-            if (LC && rq.pq) hipLaunchKernelGGL((k_list_resolve<LC, VEC, LC>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
-            else             hipLaunchKernelGGL((k_list_resolve<LC, VEC, false>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
+            const bool is_long = a.N > kListLong;
+            if (is_long && LC && rq.pq) hipLaunchKernelGGL((k_list_resolve<LC, VEC, LC, true>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
+            else if (is_long)           hipLaunchKernelGGL((k_list_resolve<LC, VEC, false, true>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
+            else if (LC && rq.pq)       hipLaunchKernelGGL((k_list_resolve<LC, VEC, LC, false>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
+            else                        hipLaunchKernelGGL((k_list_resolve<LC, VEC, false, false>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
             CONDENSA_LAUNCH_CHECK();
         }
         return CONDENSA_OK;

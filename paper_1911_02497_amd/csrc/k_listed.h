@@ -49,7 +49,11 @@ static_assert(kListBins == 1 << 8, "list_window: 32 - 8 bits");
 constexpr u32 kListRanked = 2048;                // gathered entries that are held in LDS
 constexpr u32 kListGather = 1u << 18;            // gathered entries of a ranking at most; with more (ties) it is left open
 constexpr u32 kListLine = 32;                    // words of a 128-byte line
+// Lists of more elements than this are long: with 256 sampling workgroups of four units their bins outgrow kListFound, and a wavefront's share of corrections
+// its queue.
+constexpr u64 kListLong = static_cast<u64>(1) << 27;
 constexpr u32 kListFound = 4096;                 // entries of the threshold's bin that k_list_resolve ranks from LDS
+constexpr u32 kListPosted = 16384;               // ... and of long lists
 constexpr u32 kListRow = 64;                     // segments are multiples of this many entries
 
 // Populations up to here are sampled and finished by one workgroup.  Several densities: the windows of one sampling workgroup
@@ -172,6 +176,7 @@ constexpr u64 kPicked = static_cast<u64>(1) << 63;         // the entry is there
 constexpr u32 kRangeKnown = 0x80000000u;
 constexpr u64 kWalkerLeft = 1;
 constexpr u32 kMaxWalkers = kListSegs / 8;                 // a segment for each of a workgroup's eight wavefronts
+constexpr u32 kListParts = 4;                              // wavefronts that share a segment where lists are long
 constexpr u32 kStateUnsure = 1;      // the interval is the sample's alone; `rank` counts from the top of the population
 constexpr u32 kStateMaybe = 2;       // the gathered entries are many: if all are equal they are the ties, else list_rank takes them
 constexpr u32 kStateTied = 4;        // the ties are the gathered entries, and the outputs are right but for theirs
@@ -193,7 +198,7 @@ struct ListArgs {
                            // k_list_finish for itself
     u32* arrived;          // one ranking: workgroups that have walked their part of the list << 20 | entries they gathered
     u32* ended;            // one ranking, prune + binary16 step: workgroups that are done
-    u64* picked;           // one ranking: [kListFound] gathered entries, index | key << 32 | kPicked
+    u64* picked;           // one ranking: [kListFound or kListPosted] gathered entries, index | key << 32 | kPicked
     u32* range;            // one ranking: [kMaxWalkers] where a workgroup's entries stand among these, first | number << 16 | kRangeKnown
     u64* verdict;          // one ranking: [kMaxWalkers] for each workgroup: the last entry kept (as in `picked`), or kWalkerLeft
     u32* gathered;         // [rankings][kListLine] entries in the threshold's bin (a counter in a line of its own)
@@ -1908,6 +1913,153 @@ __device__ inline bool list_rank_short(const DataArgs& a, const ListArgs& w, Ran
     return true;
 }
 
+// The same for long lists (k_list_resolve<..., LONG>), whose bins hold thousands of entries (7000 and up at 10^9 weights): up to kListPosted of them, of
+// which LDS holds those that share the threshold's first digits.  1.2 G weights pruned: the launch 57 us, 130 where such bins were left to the whole grid, 155
+// where every digit was a pass over the posted entries.  A kernel of its own: with this in the one for short lists the L-C step of 20 M weights took 3.6 us more.
+struct RankLong {
+    u64 entry[kListFound];                       // as in RankShort
+    u64 pair[kShortPairs];
+    u64 found;
+    __align__(16) u32 hist[256];
+    u32 bin, rem, in, n, n_tie, kept, n_owned, missing[16];
+    u32 owned[kListPosted / 32];                 // a bit each: its workgroup settles it
+};
+template <bool LC, bool PQ, int THREADS>
+__device__ inline bool list_rank_long(const DataArgs& a, const ListArgs& w, RankLong& sh, u32 want, u32 n, u32 bin, const ListWin& win, u32 walkers,
+                                       condensa_select* results, int* nz) {
+    static_assert(THREADS >= 256 && THREADS >= static_cast<int>(kMaxWalkers * kListParts), "a thread a bin, a thread a workgroup");
+    const u32 tid = threadIdx.x, shift = win_shift(win), top_key = win.lo + (bin << shift) + ((1u << shift) - 1u);
+    static_assert(THREADS / 64 <= 16, "a word a wavefront");
+    const bool in_lds = n <= kListFound;         // uniform
+    auto entry = [&](u64 x) { return (static_cast<u64>(top_key - (static_cast<u32>(x >> 32) & 0x7FFFFFFFu)) << 32) | static_cast<u32>(x); };
+    // f(place, entry) for all that were posted, eight loads at a time (they pass the caches)
+    auto posted = [&](auto&& f) {
+        for (u32 i0 = tid; i0 < n; i0 += 8 * THREADS) {
+            u64 x[8];
+#pragma unroll
+            for (u32 j = 0; j < 8; ++j) x[j] = ld_dev64(w.picked + (i0 + j * THREADS < n ? i0 + j * THREADS : i0));
+#pragma unroll
+            for (u32 j = 0; j < 8; ++j) if (i0 + j * THREADS < n) f(i0 + j * THREADS, x[j]);
+        }
+    };
+    bool missing = (w.force & kForceNoPosts) != 0;
+    u32 polls = 0;
+    if (tid < 256) sh.hist[tid] = 0;
+    for (u32 i = tid; i < kListPosted / 32; i += THREADS) sh.owned[i] = 0;
+    if (tid == 0) { sh.n = 0; sh.n_tie = 0; sh.kept = 0; sh.n_owned = 0; }
+    __syncthreads();
+    u64 prefix = 0;
+    u32 top = 32 + shift, in = n, r = want;      // the r-th from the bottom among the `in` entries whose bits from `top` on are the prefix
+    u32 width = top < 8 ? top : 8;
+    auto count = [&](u64 e) { if ((e >> top) == prefix) atomicAdd(&sh.hist[static_cast<u32>(e >> (top - width)) & ((1u << width) - 1u)], 1u); };
+    auto there = [&](u32 i, u64 x) {             // (at the first look, as a rule)
+        while ((x & kPicked) == 0 && !missing) { __builtin_amdgcn_s_sleep(1); missing = ++polls > kPostPolls; x = ld_dev64(w.picked + i); }
+        return entry(x);
+    };
+    if (in_lds) for (u32 i = tid; i < n && !missing; i += THREADS) sh.entry[i] = there(i, ld_dev64(w.picked + i));       // (one or two rounds, as a rule)
+    else if (!missing) posted([&](u32 i, u64 x) { count(there(i, x)); });
+    u32 range = 0;                               // of workgroup tid
+    if (tid < walkers)
+        while (((range = ld_dev(w.range + tid)) & kRangeKnown) == 0 && !missing) { __builtin_amdgcn_s_sleep(1); missing = ++polls > kPostPolls; }
+    const bool any_missing = __any(missing);
+    if ((tid & 63u) == 0) sh.missing[tid >> 6] = any_missing ? 1u : 0u;
+    __syncthreads();
+    u32 is_missing = 0;
+#pragma unroll
+    for (int i = 0; i < THREADS / 64; ++i) is_missing |= sh.missing[i];
+    if (is_missing != 0) return false;           // uniform
+    auto pick = [&]() {                          // the digit that the counts say
+        if (tid < 64) {                          // four bins a lane, from the bottom
+            const uint4 c4 = *reinterpret_cast<const uint4*>(sh.hist + 4 * tid);
+            const u32 c[4] = {c4.x, c4.y, c4.z, c4.w}, sum = c[0] + c[1] + c[2] + c[3];
+            u32 before = wave_incl_scan_u32(sum) - sum;
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) {
+                if (before < r && r <= before + c[i]) { sh.bin = 4 * tid + i; sh.rem = r - before; sh.in = c[i]; }
+                before += c[i];
+            }
+        }
+        __syncthreads();
+        prefix = (prefix << width) | sh.bin;
+        r = sh.rem;
+        in = sh.in;
+        top -= width;
+        width = top < 8 ? top : 8;
+        if (tid < 256) sh.hist[tid] = 0;
+        __syncthreads();
+    };
+    u32 held = n;                                // entries in LDS
+    bool all_ties = true;                        // ... those that the threshold's equals are among
+    if (!in_lds) {                               // only those that share its first digits are brought there
+        pick();
+        while (in > kListFound && top > 0) {     // uniform; (thousands of equal keys)
+            posted([&](u32, u64 x) { count(entry(x)); });
+            __syncthreads();
+            pick();
+        }
+        all_ties = top >= 32;
+        posted([&](u32, u64 x) { const u64 e = entry(x); if ((e >> top) == prefix) sh.entry[atomicAdd(&sh.n, 1u)] = e; });       // `in` of them
+        __syncthreads();
+        held = in;
+        if (tid == 0) sh.n = 0;
+        __syncthreads();
+    }
+    while (in > kShortPairs && top > 0) {        // uniform
+        for (u32 i = tid; i < held; i += THREADS) count(sh.entry[i]);
+        __syncthreads();
+        pick();
+    }
+    for (u32 i = tid; i < held; i += THREADS)
+        if ((sh.entry[i] >> top) == prefix) sh.pair[atomicAdd(&sh.n, 1u)] = sh.entry[i];       // `in` of them
+    __syncthreads();
+    if (tid < in) {
+        const u64 mine = sh.pair[tid];
+        u32 less = 0;
+#pragma unroll 4
+        for (u32 e = 0; e < in; ++e) less += sh.pair[e] < mine ? 1u : 0u;
+        if (less + 1 == r) sh.found = mine;      // entries differ: one thread
+    }
+    __syncthreads();
+    const u64 found = sh.found;
+    const u32 T = top_key - static_cast<u32>(found >> 32), last = static_cast<u32>(found);
+    if (tid < walkers) {
+        const u64 was = __hip_atomic_exchange(w.verdict + tid, kPicked | (static_cast<u64>(T) << 32) | last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const u32 first = range & 0xFFFFu, number = (range & ~kRangeKnown) >> 16;
+        if (was != kWalkerLeft && number != 0) {
+            atomicAdd(&sh.n_owned, number);
+            for (u32 i = first; i < first + number && i < kListPosted; ++i) atomicOr(&sh.owned[i / 32], 1u << (i % 32));
+        }
+    }
+    auto tie = [&](u64 e) {
+        if ((e >> 32) == (found >> 32)) {
+            atomicAdd(&sh.n_tie, 1u);
+            if (e <= found) atomicAdd(&sh.kept, 1u);
+        }
+    };
+    if (all_ties) for (u32 i = tid; i < held; i += THREADS) tie(sh.entry[i]);
+    else          posted([&](u32, u64 x) { tie(entry(x)); });
+    __syncthreads();
+    if (w.write && sh.n_owned != n) {            // uniform: some have left
+        auto fix = [&](u32 i, u64 e) {
+            if ((sh.owned[i / 32] >> (i % 32)) & 1u) return;
+            const bool kept = e <= found;
+            if (kept != (top_key - static_cast<u32>(e >> 32) >= win.mid)) list_fix_one<LC, PQ>(a, w, 0, static_cast<u32>(e), kept, nz);
+        };
+        for (u32 i = tid; i < n; i += THREADS) fix(i, in_lds ? sh.entry[i] : entry(ld_dev64(w.picked + i)));
+    }
+    if (tid == 0) {
+        Slot& slot = a.slots[0];
+        u64 tie_end = slot.n;
+        if (sh.kept < sh.n_tie) {
+            const TensorDesc& td = a.td[a.chunk_map[last / kChunk]];
+            tie_end = static_cast<u64>(last) - td.chunk_start * kChunk + (a.per_tensor ? 0 : td.flat_start) + 1;
+        }
+        slot.prefix = T; slot.remaining = sh.kept; slot.n_tie = sh.n_tie; slot.need_tie = 0; slot.tie_end = tie_end; slot.state = kDone;
+        *results = select_record(slot, true, T, sh.kept, sh.n_tie, tie_end, slot.path);
+    }
+    return true;
+}
+
 // One ranking by one workgroup from the weights alone, whatever else is in the workspace: radix levels of eight bits, the tie that is
 // kept last, outputs, record and count of codes.  Elements one at a time and a barrier for every few hundred: some ms for a million of
 // weights, but no registers that the callers' own work would have to make room for.
@@ -2103,7 +2255,7 @@ __global__ __launch_bounds__(kBlock) void k_list_gather(DataArgs a, ListArgs w) 
 // LDS), kListDeep rows of two segments at a time with their loads in flight together; called by all lanes, `there` says which hold
 // an entry.
 template <typename F>
-__device__ inline void list_walk_own(const ListArgs& w, const ListRank& rk, const u32* cnt_of, u32 first_seg, u32 stride, F&& f) {
+__device__ inline void list_walk_own(const ListArgs& w, const ListRank& rk, const u32* cnt_of, u32 first_seg, u32 stride, F&& f, u32 part = 0, u32 parts = 1) {
     const u32 lane = threadIdx.x & 63u;
     for (u32 seg0 = first_seg; seg0 < rk.n_segs; seg0 += 2 * stride) {
         u32 cnt[2], most = 0;
@@ -2115,7 +2267,7 @@ __device__ inline void list_walk_own(const ListArgs& w, const ListRank& rk, cons
             first[b] = rk.base + static_cast<u64>(seg) * rk.seg_cap;
             most = cnt[b] > most ? cnt[b] : most;
         }
-        for (u32 i0 = 0; i0 < most; i0 += 64 * kListDeep) {              // uniform
+        for (u32 i0 = 64 * kListDeep * part; i0 < most; i0 += 64 * kListDeep * parts) {              // uniform
             u32 x[kListDeep][2], e[kListDeep][2];
 #pragma unroll
             for (u32 d = 0; d < kListDeep; ++d)
@@ -3043,13 +3195,15 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_settle(DataArgs a, L
 // Posting is one update that counts workgroups and entries both; the entries follow it, each with a bit that says it is there, and the
 // last workgroup waits for those still on their way (their workgroups wait for nobody).
 // Bound by latency: a launch and some ten dependent accesses.
-template <bool LC, bool VEC, bool PQ>
+// LONG: lists of millions of entries (list_long).  Four wavefronts share a segment, and bins of thousands are ranked in the same way.
+template <bool LC, bool VEC, bool PQ, bool LONG>
 __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, ListArgs w, condensa_select* results, int vec_out) {
     constexpr u32 kWaves = kSettleThreads / 64, kRoom = 256, kFound = 64;              // for each wavefront
-    static_assert(kMaxWalkers == kListSegs / kWaves, "a segment a wavefront");
+    static_assert(kMaxWalkers == kListSegs / kWaves && kMaxWalkers * kListParts <= static_cast<u32>(kSettleGrid), "a segment a wavefront");
+    constexpr u32 kPosted = LONG ? kListPosted : kListFound, kParts = LONG ? kListParts : 1u;
     __shared__ union {                                     // one after the other
         ListShared rank;
-        RankShort few;
+        typename std::conditional<LONG, RankLong, RankShort>::type few;
         u32 words[kFallbackWords];
     } s_mem;
     __shared__ ListFindShared<kSettleThreads> find;
@@ -3087,16 +3241,17 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
     const bool crowded = win_crowded(win);
     int nz = 0;
     WaveQueue<kRoom> queue{s_queue + wave * kRoom, 0, win_mid_bin(win) > f.bin, win.lo, win_shift(win), f.bin, win_mid_bin(win)};
-    if (!crowded && f.want != 0 && f.n_in <= kListFound) {               // the same in every workgroup
-        const u32 walkers = (rk.n_segs + kWaves - 1) / kWaves;           // at most kMaxWalkers, fewer than the grid
+    if (!crowded && f.want != 0 && f.n_in <= kPosted) {               // the same in every workgroup
+        const u32 part = blockIdx.x % kParts;              // (2.7 M entries, 1.2 G weights pruned: a wavefront a segment 30 us walked and 14 corrected, now 5 and 10)
+        const u32 walkers = (rk.n_segs + kWaves - 1) / kWaves * kParts;  // at most the grid
         if (blockIdx.x >= walkers) return;
         u32* const fkey = s_fkey + wave * kFound;
         u32* const fidx = s_fidx + wave * kFound;
         auto post = [&](u32 at, u32 key, u32 idx) {
-            if (at < kListFound) st_dev64(w.picked + at, kPicked | (static_cast<u64>(key) << 32) | idx);
+            if (at < kPosted) st_dev64(w.picked + at, kPicked | (static_cast<u64>(key) << 32) | idx);
         };
         u32 n_found = 0;                                   // uniform
-        list_walk_own(w, rk, find.cnt, blockIdx.x * kWaves + wave, gridDim.x * kWaves, [&](bool there, u32 key, u32 idx) {
+        list_walk_own(w, rk, find.cnt, blockIdx.x / kParts * kWaves + wave, gridDim.x * kWaves, [&](bool there, u32 key, u32 idx) {
             const bool found = queue.template offer<LC, PQ>(a, w, 0, there, key, idx, &nz);
             const u64 m = __ballot(found);
             if (m == 0) return;                            // uniform
@@ -3110,7 +3265,7 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
             if (lane == 0) base = add_dev(w.arrived, count) & 0xFFFFFu;
             base = __shfl(base, 0, 64);                    // by all lanes: one that lane 0 does not take part in returns 0
             if (found) post(base + lanes_below(m), key, idx);
-        });
+        }, part, kParts);
         if (lane == 0) s_found[wave] = n_found;
         __syncthreads();
         u32 before = 0, all = 0;
@@ -3120,24 +3275,28 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
         __syncthreads();
         const u32 ticket = s_found[kWaves], base = (ticket & 0xFFFFFu) + before;
         if (lane < n_found) post(base + lane, fkey[lane], fidx[lane]);
-        if (tid == 0) st_dev(w.range + blockIdx.x, kRangeKnown | (all << 16) | ((ticket & 0xFFFFu) < kListFound ? ticket & 0xFFFFu : kListFound));
+        if (tid == 0) st_dev(w.range + blockIdx.x, kRangeKnown | (all << 16) | ((ticket & 0xFFFFu) < kPosted ? ticket & 0xFFFFu : kPosted));
         queue.template fix<LC, PQ>(a, w, 0, &nz);
         // what settling its own entries will read is on its way meanwhile
         const u32 idx1[1] = {lane < n_found ? fidx[lane] : 0u};
         bool on1[1] = {lane < n_found};
         FixLoads<LC, 1> loads;
         if (w.write && n_found != 0) list_fix_load<LC, 1>(a, w, 0, idx1, on1, loads);
-        if ((ticket >> 20) + 1 == walkers &&               // uniform: the last one
-            !list_rank_short<LC, PQ, kSettleThreads>(a, w, s_mem.few, f.want, (ticket & 0xFFFFFu) + all, f.bin, win, walkers, results, &nz)) {
-            list_search<LC, PQ, kSettleThreads>(a, w, sh, results);
-            return;
+        if ((ticket >> 20) + 1 == walkers) {               // uniform: the last one
+            bool ranked;
+            if constexpr (LONG) ranked = list_rank_long<LC, PQ, kSettleThreads>(a, w, s_mem.few, f.want, (ticket & 0xFFFFFu) + all, f.bin, win, walkers, results, &nz);
+            else                ranked = list_rank_short<LC, PQ, kSettleThreads>(a, w, s_mem.few, f.want, (ticket & 0xFFFFFu) + all, f.bin, win, walkers, results, &nz);
+            if (!ranked) {
+                list_search<LC, PQ, kSettleThreads>(a, w, sh, results);
+                return;
+            }
         }
         if (w.write && n_found != 0) {                     // uniform over the wavefront
             // The verdict comes from a workgroup that is running once all have posted; if some of them are not even running yet (another
             // launch holds the chip), this one does not keep them from it for long.
             u64 v = 0;
             if (lane == 0) {
-                for (int polls = 0; polls < ((w.force & kForceNoVerdict) ? 0 : 64) && ((v = ld_dev64(w.verdict + blockIdx.x)) & kPicked) == 0; ++polls) __builtin_amdgcn_s_sleep(4);
+                for (int polls = 0; polls < ((w.force & kForceNoVerdict) ? 0 : (LONG ? 192 : 64)) && ((v = ld_dev64(w.verdict + blockIdx.x)) & kPicked) == 0; ++polls) __builtin_amdgcn_s_sleep(4);
                 if (w.force & kForceAsk) v = 0;
             }
             v = (static_cast<u64>(__shfl(static_cast<u32>(v >> 32), 0, 64)) << 32) | __shfl(static_cast<u32>(v), 0, 64);

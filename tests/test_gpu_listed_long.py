@@ -1,0 +1,63 @@
+"""GPU parity of listed windows on lists of millions of entries (more than 2^27 weights, one density): bins of thousands of entries, ties in them,
+workgroups that leave.  Against the radix levels, which the oracle anchors at sizes that it can sort; bit for bit."""
+import contextlib
+
+import pytest
+import torch
+
+import paper_1911_02497_amd as P
+from gpu_util import DEV
+
+pytestmark = pytest.mark.gpu
+
+LATE, NO_VERDICT, ASK, NO_POSTS = 1, 4, 8, 16                            # csrc/host.h
+FIELDS = ("n", "k", "n_gt", "n_tie_kept", "n_tie", "threshold_key", "tie_end")
+
+
+@contextlib.contextmanager
+def forced(what):
+    lib = P.library()
+    lib.condensa_test_force(what)
+    try:
+        yield
+    finally:
+        lib.condensa_test_force(0)
+
+
+def _weights(kind, n):
+    g = torch.Generator(device=DEV).manual_seed(n % 1000)
+    w = torch.empty(n, dtype=torch.float32, device=DEV).normal_(0.0, 0.02, generator=g)
+    if kind == "ties":                                     # the upper half of a bin's width around the threshold of 0.1: thousands of equal keys
+        w[(w.abs() - 0.0329).abs() < 1e-6] = 0.0329
+    return [w[:n // 3].view(-1, 1), w[n // 3:]]
+
+
+def _same(a, b):
+    return torch.equal(a.view(torch.int32) if a.dtype == torch.float32 else a, b.view(torch.int32) if b.dtype == torch.float32 else b)
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("kind", ["normal", "ties"])
+@pytest.mark.parametrize("n", [(1 << 27) + 1, 400_000_003])
+def test_prune_and_steps(kind, n):
+    ws = _weights(kind, n)
+    lam = [t * 0.0 for t in ws]
+    for d in (0.1, 0.6):
+        ref = P.condensa_prune(ws, [d], config={"select_path": 1})
+        want = P.select_records(ref["results"])[0]
+        step = P.condensa_lc_step(ws, lam, 1e-3, d, config={"select_path": 1})
+        for what in (0, LATE, NO_VERDICT, ASK) if d == 0.1 else (0, NO_POSTS) if n < 1 << 28 else (0,):
+            with forced(what):
+                res = P.condensa_prune(ws, [d])
+                got = P.select_records(res["results"])[0]
+            assert all(got[f] == want[f] for f in FIELDS), (what, got, want)
+            for name in ("theta", "mask"):
+                assert all(_same(a, b) for a, b in zip(res[name][0], ref[name][0])), (what, name)
+            with forced(what):
+                res = P.condensa_lc_step(ws, lam, 1e-3, d)
+            for name in ("theta", "lambda", "grad", "mask"):
+                assert all(_same(a, b) for a, b in zip(res[name], step[name])), (what, name)
+        pq = P.condensa_lc_step_pq(ws, lam, 1e-3, d, nnz=True)
+        assert int(pq["nnz"].item()) == sum(int(((c & 0x7FFF) != 0).sum()) for c in pq["theta_f16"])
+        assert all(_same(a, b) for a, b in zip(pq["mask"], step["mask"]))
+        del ref, step, pq, res
