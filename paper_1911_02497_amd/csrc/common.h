@@ -187,6 +187,14 @@ __device__ inline void st_words4_stream(void* p, u32x4 t) {          // sixteen 
     __builtin_amdgcn_raw_buffer_store_b128(t, r, off, 0, kStreamPolicy);
 #endif
 }
+// The same at `off` bytes from a place that is the same in all lanes (and known to be: in scalar registers).
+__device__ inline void st_words4_stream(void* base, u32 off, u32x4 t) {
+#if defined(CONDENSA_PLAIN_STREAM_STORES)
+    __builtin_nontemporal_store(t, reinterpret_cast<u32x4*>(static_cast<char*>(base) + off));
+#else
+    __builtin_amdgcn_raw_buffer_store_b128(t, __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7FFFFFFF, 0x00020000), off, 0, kStreamPolicy);
+#endif
+}
 __device__ inline void st4_stream(float* p, float a, float b, float c, float d) {
     u32x4 t;
     t.x = __float_as_uint(a); t.y = __float_as_uint(b); t.z = __float_as_uint(c); t.w = __float_as_uint(d);

@@ -1012,22 +1012,24 @@ constexpr int kListMultiQuads = 4;
 // and 53.7; two of 295 thousand 37.4 and 36.9, of 2.3 M 42.3 and 47.5).
 constexpr u64 kListMultiFew = static_cast<u64>(1) << 19;
 __host__ __device__ inline int list_multi_quads(u64 N) { return N <= kListMultiFew ? 1 : kListMultiQuads; }
-constexpr u32 kListMultiBuf = 512;               // buffered entries of a wavefront: an equal share for each ranking; with more, they come from the tile
+constexpr u32 kListMultiBuf = 256;               // buffered entries of a wavefront, of all rankings; with more, they come from the tile
 struct ListMultiShared {
-    u32 key[kListMultiBuf];
     u32 tile[256 * kListMultiQuads];             // the tile's keys, then its regions
+    u32 key[kListMultiBuf];
+    u32 what[kListMultiBuf];                     // element of the tile | ranking << 12 | place among the ranking's entries << 16
     u32 count[kMaxJ];                            // entries | those from the estimate on << 16
     u32 gap[2 * (kMaxJ + 1)];
     u32 ranking[kMaxJ];
-    u16 off[kListMultiBuf];
 };
+static_assert(256 * kListMultiQuads <= 1 << 12 && kMaxJ <= 16, "ListMultiShared::what");
 
 __device__ inline u32 list_reserve(const ListArgs& w, u64 r, const ListRank& rk, u32 count, u32 above) {
     return static_cast<u32>(atomicAdd(reinterpret_cast<unsigned long long*>(&w.cnt[r * w.max_segs + blockIdx.x % rk.n_segs]),
                                       (static_cast<unsigned long long>(above) << 32) | count));
 }
-// `mine`: in lane j, ranking j's buffered entries and (upper half) its keys above the window.
-__device__ inline void list_multi_flush(const DataArgs& a, const ListArgs& w, const ListMultiShared& sh, u64 r0, u64 mine, u32 i0) {
+// `mine`: in lane j, ranking j's buffered entries and (upper half) its keys above the window; `total`: the entries of all.  A lane takes an
+// entry, whatever its ranking (one ranking after the other, the ten of a search cost a wavefront 250 instructions).
+__device__ inline void list_multi_flush(const DataArgs& a, const ListArgs& w, const ListMultiShared& sh, u64 r0, u64 mine, u32 total, u32 i0) {
     const int lane = threadIdx.x;
     ListRank rk{};
     u32 at = 0;
@@ -1035,18 +1037,18 @@ __device__ inline void list_multi_flush(const DataArgs& a, const ListArgs& w, co
         rk = w.rank[r0 + lane];
         at = list_reserve(w, r0 + lane, rk, static_cast<u32>(mine), static_cast<u32>(mine >> 32));
     }
-    const u64 first = rk.base + (rk.n_segs ? static_cast<u64>(blockIdx.x % rk.n_segs) * rk.seg_cap : 0);
-    const u32 share = kListMultiBuf / static_cast<u32>(a.J);
+    const u64 first = rk.base + (rk.n_segs ? static_cast<u64>(blockIdx.x % rk.n_segs) * rk.seg_cap : 0) + at;
+    const u32 room = at < rk.seg_cap ? rk.seg_cap - at : 0u;
     __syncthreads();                                                    // one wavefront: orders the LDS buffer
-    for (int j = 0; j < a.J; ++j) {
-        const u32 count = __shfl(static_cast<u32>(mine), j, 64);
-        const u32 pos = __shfl(at, j, 64), cap = __shfl(rk.seg_cap, j, 64);
-        const u64 to = ((static_cast<u64>(__shfl(static_cast<u32>(first >> 32), j, 64)) << 32) | __shfl(static_cast<u32>(first), j, 64)) + pos;
-        for (u32 i = lane; i < count; i += 64)
-            if (pos + i < cap) {
-                w.key[to + i] = sh.key[j * share + i];
-                w.idx[to + i] = i0 + sh.off[j * share + i];
-            }
+    for (u32 e0 = 0; e0 < total; e0 += 64) {                            // uniform
+        const u32 e = e0 + lane, what = e < total ? sh.what[e] : 0u, i = what >> 16;
+        const int j = static_cast<int>((what >> 12) & 15u);
+        const u64 to = ((static_cast<u64>(__shfl(static_cast<u32>(first >> 32), j, 64)) << 32) | __shfl(static_cast<u32>(first), j, 64)) + i;
+        const bool fits = i < __shfl(room, j, 64);
+        if (e < total && fits) {
+            w.key[to] = sh.key[e];
+            w.idx[to] = i0 + (what & 0xFFFu);
+        }
     }
 }
 
@@ -1080,8 +1082,8 @@ __device__ inline void list_multi_general(const DataArgs& a, const ListArgs& w, 
         }
     }
     const u32 i0 = static_cast<u32>(c) * kChunk + sub * kWaveElems;
-    const u32 share = kListMultiBuf / static_cast<u32>(a.J);
     u64 mine = 0;                                                       // lane j: ranking j's buffered entries and keys above
+    u32 total = 0;
     for (int j = 0; j < a.J; ++j) {
         const ListWin win = w.win[r0 + j];
         if (win_crowded(win)) continue;                                 // uniform
@@ -1106,12 +1108,13 @@ __device__ inline void list_multi_general(const DataArgs& a, const ListArgs& w, 
                 if (hit != 0) {                                         // uniform
                     const u32 n_hit = static_cast<u32>(__popcll(hit));
                     const bool me = (hit >> lane) & 1u;
-                    if (count + n_hit <= share) {
+                    if (total + n_hit <= kListMultiBuf) {
                         if (me) {
-                            sh.key[j * share + count + lanes_below(hit)] = x;
-                            sh.off[j * share + count + lanes_below(hit)] = static_cast<u16>(q * 256 + lane * 4 + k);
+                            sh.key[total + lanes_below(hit)] = x;
+                            sh.what[total + lanes_below(hit)] = static_cast<u32>(q * 256 + lane * 4 + k) | static_cast<u32>(j) << 12 | (count + lanes_below(hit)) << 16;
                         }
                         count += n_hit;
+                        total += n_hit;
                     } else {                                            // full buffer: straight to the list
                         const ListRank rk = w.rank[r0 + j];
                         u32 at = 0;
@@ -1143,12 +1146,15 @@ __device__ inline void list_multi_general(const DataArgs& a, const ListArgs& w, 
         }
         if (lane == j) mine = (static_cast<u64>(above) << 32) | count;
     }
-    list_multi_flush(a, w, sh, r0, mine, i0);
+    list_multi_flush(a, w, sh, r0, mine, total, i0);
 }
 
 // WIDE: masks only, each 16-byte aligned.
+// Bound by instructions (ten densities: 980 for a wavefront's 1024 elements, 1214 before) and the latency of what a wavefront waits for, with six of them
+// on a SIMD: outputs, estimates and biases of all rankings are loaded at once, a lane each, and counts cross the lanes two to a sum in registers.
+// Ten masks of 20 M weights 76 -> 53 us, the call 123 -> 104; of 113 M weights, the call 501 -> 354, two densities of them 235 -> 193.
 template <bool VEC, bool WIDE, int Q>
-__global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w) {
+__global__ __launch_bounds__(64, WIDE || Q == 1 ? 6 : 5) void k_list_sweep_multi(DataArgs a, ListArgs w) {
     constexpr int kWaveElems = 256 * Q;
     constexpr u32 kSub = kChunk / kWaveElems;
     __shared__ __align__(16) ListMultiShared sh;
@@ -1175,6 +1181,10 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
         v[q][0] = x.x; v[q][1] = x.y; v[q][2] = x.z; v[q][3] = x.w;
     }
     const u32 n = srt.n;
+    // What the loops over rankings need is loaded by a lane each, now, and read across lanes there.
+    const u32 mid_of = lane < kMaxJ ? srt.mid[lane < kMaxJ ? lane : 0] : 0u, bias_of = lane < kMaxJ ? srt.bias[lane < kMaxJ ? lane : 0] : 0u;
+    OutDesc out_of{};
+    if (w.write && lane < a.J) out_of = w.out[static_cast<u64>(lane) * a.n_tensors + t];
     if (lane < kMaxJ) { sh.count[lane] = 0; sh.ranking[lane] = srt.ranking[lane]; }
     if (lane <= kMaxJ) { sh.gap[2 * lane] = srt.gap_lo[lane]; sh.gap[2 * lane + 1] = srt.gap_len[lane]; }
     u32 region[Q][4];
@@ -1183,7 +1193,7 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
 #pragma unroll
         for (int k = 0; k < 4; ++k) region[q][k] = 0;
     for (u32 p = 0; p < n; ++p) {
-        const u32 mid = srt.mid[p];                                     // uniform
+        const u32 mid = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(mid_of), static_cast<int>(p)));       // uniform
 #pragma unroll
         for (int q = 0; q < Q; ++q)
 #pragma unroll
@@ -1204,30 +1214,32 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
     u32 packed[Q];                                                      // regions of a float4's elements, a byte each
 #pragma unroll
     for (int q = 0; q < Q; ++q) packed[q] = region[q][0] | (region[q][1] << 8) | (region[q][2] << 16) | (region[q][3] << 24);
-    const u32 i0 = static_cast<u32>(c) * kChunk + sub * kWaveElems, share = kListMultiBuf / static_cast<u32>(a.J);
-    bool full_buffer = false;
-    while (inside) {
-        const u32 i = static_cast<u32>(__ffs(inside)) - 1u, off = (i >> 2) * 256 + lane * 4 + (i & 3u);
-        inside &= inside - 1u;
-        u32 word = packed[0];
+    const u32 i0 = static_cast<u32>(c) * kChunk + sub * kWaveElems;
+    u32 total = 0;                                                      // uniform
+    for (u64 left; (left = __ballot(inside != 0)) != 0;) {              // uniform
+        if (inside) {
+            const u32 i = static_cast<u32>(__ffs(inside)) - 1u, off = (i >> 2) * 256 + lane * 4 + (i & 3u);
+            inside &= inside - 1u;
+            u32 word = packed[0];
 #pragma unroll
-        for (int q = 1; q < Q; ++q) word = (i >> 2) == static_cast<u32>(q) ? packed[q] : word;
-        const u32 r = (word >> (8 * (i & 3u))) & 0xFFu, x = sh.tile[off];
-        // below the gap of its region: the window of the highest estimate it reaches; else the next one up
-        const bool reaches = x < sh.gap[2 * r];
-        const u32 j = sh.ranking[reaches ? n - r : n - r - 1u];
-        const u32 at = atomicAdd(&sh.count[j], reaches ? 0x10001u : 1u) & 0xFFFFu;
-        if (at < share) {
-            sh.key[j * share + at] = x;
-            sh.off[j * share + at] = static_cast<u16>(off);
+            for (int q = 1; q < Q; ++q) word = (i >> 2) == static_cast<u32>(q) ? packed[q] : word;
+            const u32 r = (word >> (8 * (i & 3u))) & 0xFFu, x = sh.tile[off];
+            // below the gap of its region: the window of the highest estimate it reaches; else the next one up
+            const bool reaches = x < sh.gap[2 * r];
+            const u32 j = sh.ranking[reaches ? n - r : n - r - 1u];
+            const u32 at = atomicAdd(&sh.count[j], reaches ? 0x10001u : 1u) & 0xFFFFu, e = total + lanes_below(left);
+            if (e < kListMultiBuf) {
+                sh.key[e] = x;
+                sh.what[e] = off | j << 12 | at << 16;
+            }
         }
-        full_buffer = full_buffer || at >= share;
+        total += static_cast<u32>(__popcll(left));
     }
-    u64 full_buffers = __ballot(full_buffer);
-    if (full_buffers != 0) full_buffers = __ballot(lane < a.J && (sh.count[lane < a.J ? lane : 0] & 0xFFFFu) > share);
-    while (full_buffers != 0) {                                         // uniform.  All of that ranking's entries from the tile
-        const u32 j = static_cast<u32>(__ffsll(static_cast<long long>(full_buffers))) - 1u;
-        full_buffers &= full_buffers - 1u;
+    const bool buffered = total <= kListMultiBuf;                       // uniform
+    u64 from_tile = buffered ? 0 : __ballot(lane < a.J && (sh.count[lane < a.J ? lane : 0] & 0xFFFFu) != 0);
+    while (from_tile != 0) {                                            // uniform.  All of that ranking's entries from the tile
+        const u32 j = static_cast<u32>(__ffsll(static_cast<long long>(from_tile))) - 1u;
+        from_tile &= from_tile - 1u;
         const ListWin win = w.win[r0 + j];
         const ListRank rk = w.rank[r0 + j];
         u32 pos = 0;
@@ -1251,11 +1263,15 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
         const uint4 x = *reinterpret_cast<const uint4*>(&sh.tile[4 * lane]);
         packed[0] = x.x; packed[1] = x.y; packed[2] = x.z; packed[3] = x.w;
     }
-    u32 kept_of_lane = 0;                                               // lane j: ranking j's keys from its estimate on
+    auto pointer_of = [](const void* p, int j) {                        // lane j's, in all lanes
+        const u64 x = reinterpret_cast<u64>(p);
+        return reinterpret_cast<void*>((static_cast<u64>(static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(x >> 32), j))) << 32) |
+                                       static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(x), j)));
+    };
+    u32 kept_of_lane = 0, kept_pair = 0;                                // lane j: ranking j's keys from its estimate on
     for (int j = 0; j < a.J; ++j) {
-        const u32 bias = srt.bias[j] * 0x01010101u;                     // uniform
-        OutDesc o{};
-        if (w.write) o = w.out[static_cast<u64>(j) * a.n_tensors + t];
+        const u32 bias = static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(bias_of), j)) * 0x01010101u;
+        u8* const mask = static_cast<u8*>(pointer_of(out_of.mask, j));
         u32 m[Q], kept = 0;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -1263,33 +1279,39 @@ __global__ __launch_bounds__(64) void k_list_sweep_multi(DataArgs a, ListArgs w)
             kept = __builtin_amdgcn_udot4(m[q], 0x01010101u, kept, false);
         }
         if constexpr (WIDE) {
-            if (o.mask) {
+            if (mask) {
                 u32x4 t4;
                 t4.x = m[0]; t4.y = m[1]; t4.z = m[2]; t4.w = m[3];
-                st_words4_stream(o.mask + base + lane * 16, t4);
+                st_words4_stream(mask + base, static_cast<u32>(lane) * 16u, t4);
             }
         } else {
+            float* const theta = static_cast<float*>(pointer_of(out_of.theta, j));
+            u16* const theta16 = static_cast<u16*>(pointer_of(out_of.theta16, j));
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
                 const u64 e0 = base + q * 256 + lane * 4;
-                if (o.mask) st_mask4_stream(o.mask + e0, static_cast<u8>(m[q] & 1u), static_cast<u8>((m[q] >> 8) & 1u),
-                                            static_cast<u8>((m[q] >> 16) & 1u), static_cast<u8>(m[q] >> 24));
-                if (!o.theta && !o.theta16) continue;
+                if (mask) st_mask4_stream(mask + e0, static_cast<u8>(m[q] & 1u), static_cast<u8>((m[q] >> 8) & 1u),
+                                          static_cast<u8>((m[q] >> 16) & 1u), static_cast<u8>(m[q] >> 24));
+                if (!theta && !theta16) continue;
                 float th[4];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) th[k] = ((m[q] >> (8 * k)) & 1u) ? v[q][k] : 0.0f;
-                if (o.theta) st4_stream(o.theta + e0, th[0], th[1], th[2], th[3]);
-                if (o.theta16)
-                    st_code4_stream(o.theta16 + e0, f32_to_f16_rne(th[0]), f32_to_f16_rne(th[1]), f32_to_f16_rne(th[2]), f32_to_f16_rne(th[3]));
+                if (theta) st4_stream(theta + e0, th[0], th[1], th[2], th[3]);
+                if (theta16)
+                    st_code4_stream(theta16 + e0, f32_to_f16_rne(th[0]), f32_to_f16_rne(th[1]), f32_to_f16_rne(th[2]), f32_to_f16_rne(th[3]));
             }
         }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) kept += __shfl_xor(kept, d, 64);
-        if (lane == j) kept_of_lane = kept;
+        // two rankings' counts are added up over the wavefront together (at most 1024 each)
+        kept_pair |= kept << (16 * (j & 1));
+        if ((j & 1) == 0 && j + 1 < a.J) continue;
+        const u32 sums = wave_sum_u32(kept_pair);
+        kept_pair = 0;
+        if (lane == (j & ~1)) kept_of_lane = sums & 0xFFFFu;
+        if (lane == (j | 1)) kept_of_lane = sums >> 16;
     }
     __syncthreads();
     const u32 offered = lane < a.J ? sh.count[lane] & 0xFFFFu : 0u, reached = lane < a.J ? sh.count[lane] >> 16 : 0u;
-    list_multi_flush(a, w, sh, r0, (static_cast<u64>(kept_of_lane - reached) << 32) | (offered <= share ? offered : 0u), i0);
+    list_multi_flush(a, w, sh, r0, (static_cast<u64>(kept_of_lane - reached) << 32) | (buffered ? offered : 0u), buffered ? total : 0u, i0);
 }
 
 // ---- the threshold among the listed keys ---------------------------------------------------------------
