@@ -609,6 +609,17 @@ static u64 begin_blocks(u64 n_zero, u64 n_chunks) {
     return blocks > 512 ? 512 : (blocks ? blocks : 1);
 }
 
+static BeginTables begin_tables_args(const UploadArgs& up, const Layout& L, const Tables& tb, int n_tensors, void* ws) {
+    BeginTables b{};
+    b.up = up;
+    b.zero = at<uint4>(ws, L.zero_begin);
+    b.n_zero = L.zero_bytes / 16;
+    b.chunk_map = at<u32>(ws, L.chunk_map);
+    b.n_chunks = static_cast<u32>(tb.n_chunks);
+    b.n_tensors = n_tensors;
+    return b;
+}
+
 // What every call starts with: the tables [tensors | outputs | rankings] reach the front of the workspace, the
 // counter and histogram region is cleared and the chunk -> tensor map is written.  One launch while the tables are
 // small (kBeginTensors tensors, one staging slot), two beyond that.  Without a slot (`img`: a captured call, or none free) and for
@@ -642,14 +653,9 @@ static condensa_status begin_call(const Layout& L, const Tables& tb, int n_tenso
     const UploadArgs up = fill_image(*img, L, ws, tb, out, out_bytes, slots, slot_bytes, lists, list_bytes);
     if (n_tensors <= kBeginTensors && td_bytes + out_bytes + slot_bytes + list_bytes <= kStageBytes) {
         BeginArgs b{};
-        b.up = up;
-        b.zero = at<uint4>(ws, L.zero_begin);
-        b.n_zero = L.zero_bytes / 16;
-        b.chunk_map = at<u32>(ws, L.chunk_map);
-        b.n_chunks = static_cast<u32>(tb.n_chunks);
-        b.n_tensors = n_tensors;
+        b.t = begin_tables_args(up, L, tb, n_tensors, ws);
         for (int t = 0; t <= n_tensors; ++t) b.chunk_start[t] = static_cast<u32>(tb.td[t].chunk_start);
-        const u64 blocks = begin_blocks(b.n_zero, tb.n_chunks) + 1;
+        const u64 blocks = begin_blocks(b.t.n_zero, tb.n_chunks) + 1;
         img->launching(st);
         hipLaunchKernelGGL(k_begin, dim3(static_cast<unsigned>(blocks)), dim3(kBeginThreads), 0, st, b);
         CONDENSA_LAUNCH_CHECK();
@@ -1720,10 +1726,6 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
         slots[0].path = 2;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    StageImage img;
-    rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slots.data(), static_cast<size_t>(L.n_slots) + (fused ? 3 : 0), workspace_dev, st, &img);
-    if (rc != CONDENSA_OK) return rc;
-
     StructArgs a{};
     a.td = at<TensorDesc>(workspace_dev, L.td);
     a.slots = at<Slot>(workspace_dev, L.slots);
@@ -1743,6 +1745,56 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
     a.hist_base = at<u64>(workspace_dev, L.hist0);
     a.coarse = at<u64>(workspace_dev, L.histc);
 
+    // every structure one contiguous row (filters, neurons) of some length: staged, coalesced reads
+    constexpr u64 kFewRowsMax = 32768;           // up to 1024 workgroups of kFewRows rows
+    bool rows = tb.F > 0 && !fused && tb.N / tb.F >= 16;
+    u64 loose = 0;                               // elements of tensors whose rows are not all 16-byte aligned
+    u32 longest = 0;
+    for (int t = 0; t < n_tensors && rows; ++t) {
+        const TensorDesc& d = tb.td[t];
+        if (d.n > 0 && d.d[3] > longest) longest = d.d[3];
+        if (d.n > 0 && !(d.d[1] == 1 && d.d[2] == 1 && d.b[0] == 1 && d.b[3] == d.d[3])) rows = false;
+        if (d.n > 0 && (d.d[3] % 4 != 0 || !aligned16(d.w))) loose += d.n;
+    }
+    StageImage img;
+    const size_t n_slots_up = static_cast<size_t>(L.n_slots) + (fused ? 3 : 0);
+    // Few tensors, few rows, none long: the aggregates are taken in the launch that begins the call, which saves some 3 us of 25 to 40.  More rows,
+    // and every workgroup's look at the arguments, which lie in host memory, costs that again: 32 000 of 16 elements in 80 tensors take 50.0 us so
+    // and 45.5 in two launches.  A row of 8 000 elements takes its workgroup 75 us alone, and the launch saved is hardly seen (64 of them: 102.5 us and
+    // 102.8); 64 of 200 000 take 2 238 us so and 2 188 in two launches.
+    bool begun = false;
+    if (rows && tb.F <= kBeginRows && longest <= kBeginRowsLength && n_tensors <= kBeginRowsTensors) {
+        const size_t td_bytes = static_cast<size_t>(tb.n_td) * sizeof(TensorDesc), out_bytes = out.size() * sizeof(OutDesc), slot_bytes = n_slots_up * sizeof(Slot);
+        if (td_bytes + out_bytes + slot_bytes <= kStageBytes) {
+            rc = img.acquire(td_bytes + out_bytes + slot_bytes, st);
+            if (rc != CONDENSA_OK) return rc;
+            begun = img.data() != nullptr;
+        }
+        if (begun) {
+            PhaseTimer timer(CONDENSA_PHASE_AGGREGATE, st, cfg);
+            BeginRowsArgs b{};
+            b.begin = begin_tables_args(fill_image(img, L, workspace_dev, tb, out.data(), out_bytes, slots.data(), slot_bytes, nullptr, 0), L, tb, n_tensors, workspace_dev);
+            const u64 fill = (b.begin.n_zero > tb.n_chunks ? b.begin.n_zero : tb.n_chunks) / (8 * kBlock) + 1;
+            b.fillers = static_cast<u32>(fill < 256 ? fill : 256);
+            for (int t = 0; t < n_tensors; ++t) {
+                b.w[t] = tb.td[t].w;
+                b.n[t] = tb.td[t].n;
+                b.len[t] = tb.td[t].d[3];
+                b.start[t] = static_cast<u32>(tb.td[t].struct_start);
+                b.chunk_start[t] = static_cast<u32>(tb.td[t].chunk_start);
+            }
+            b.chunk_start[n_tensors] = static_cast<u32>(tb.n_chunks);
+            const dim3 grid(static_cast<unsigned>(1 + b.fillers + (tb.F + kFewRows - 1) / kFewRows));
+            img.launching(st);
+            hipLaunchKernelGGL(k_begin_rows, grid, dim3(kBlock), 0, st, b, a, sumsq_dev, norms_dev);
+            CONDENSA_LAUNCH_CHECK();
+            img.commit();
+        }
+    }
+    if (!begun) {
+        rc = begin_call(L, tb, n_tensors, out.data(), out.size(), slots.data(), n_slots_up, workspace_dev, st, &img);
+        if (rc != CONDENSA_OK) return rc;
+    }
     const unsigned sblocks = static_cast<unsigned>((tb.F + kBlock - 1) / kBlock);
     const unsigned mtiles = static_cast<unsigned>((tb.F + kMaskTile - 1) / kMaskTile);
     // groups of at most kSmallGroup structures: one workgroup per group ranks, masks and lists them
@@ -1780,17 +1832,8 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
         CONDENSA_LAUNCH_CHECK();
     }
     if (tb.F > 0) {
-        {
+        if (!begun) {
             PhaseTimer timer(CONDENSA_PHASE_AGGREGATE, st, cfg);
-            // every structure one contiguous row (filters, neurons) of some length: staged, coalesced reads
-            constexpr u64 kFewRowsMax = 32768;           // up to 1024 workgroups of kFewRows rows
-            bool rows = tb.N / tb.F >= 16;
-            u64 loose = 0;                               // elements of tensors whose rows are not all 16-byte aligned
-            for (int t = 0; t < n_tensors && rows; ++t) {
-                const TensorDesc& d = tb.td[t];
-                if (d.n > 0 && !(d.d[1] == 1 && d.d[2] == 1 && d.b[0] == 1 && d.b[3] == d.d[3])) rows = false;
-                if (d.n > 0 && (d.d[3] % 4 != 0 || !aligned16(d.w))) loose += d.n;
-            }
             // Not all of them aligned, 256 rows to a workgroup or 64.  256: rows of one piece (a million of 17 elements 132 us the call, 149
             // with 64; of 33, 140 and 175; 40 thousand 39 and 37), and few loose ones among short ones of which there are very many (a
             // million of 256 and 40 of 33: 604 and 618) or among short and long ones where no compute unit gets a workgroup more than the

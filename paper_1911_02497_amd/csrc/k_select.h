@@ -281,29 +281,33 @@ __device__ inline void store_ticket(u64* done, u64 ticket) {
 // and 5.8 us before, 5.4 now (10.9 with 256 threads: the link wants every load of the image in flight at once).
 constexpr int kBeginThreads = 1024;
 constexpr int kBeginTensors = 256;
-struct BeginArgs {
+struct BeginTables {
     UploadArgs up;
     uint4* zero;
     u64 n_zero;            // 16-byte words
     u32* chunk_map;
     u32 n_chunks;
     int n_tensors;
+};
+struct BeginArgs {
+    BeginTables t;
     u32 chunk_start[kBeginTensors + 1];
 };
 static_assert(sizeof(BeginArgs) <= 3584, "kernel arguments");
-__global__ __launch_bounds__(kBeginThreads) void k_begin(BeginArgs b) {
-    __shared__ u32 s_start[kBeginTensors + 1];
+// The first `fillers` + 1 workgroups of a launch, of THREADS threads.
+template <int THREADS>
+__device__ inline void begin_tables(const BeginTables& b, u32 fillers, const u32* chunk_start, u32* s_start) {
     const int tid = threadIdx.x;
     if (blockIdx.x == 0) {
-        upload_words(b.up, tid, kBeginThreads);
+        upload_words(b.up, tid, THREADS);
         __syncthreads();                   // every load has returned: its value went into a store
         if (tid == 0) store_ticket(b.up.done, b.up.ticket);
         return;
     }
-    for (int t = tid; t <= b.n_tensors; t += kBeginThreads) s_start[t] = b.chunk_start[t];
+    for (int t = tid; t <= b.n_tensors; t += THREADS) s_start[t] = chunk_start[t];
     __syncthreads();
-    const u64 stride = static_cast<u64>(gridDim.x - 1) * kBeginThreads;
-    const u64 i0 = static_cast<u64>(blockIdx.x - 1) * kBeginThreads + tid;
+    const u64 stride = static_cast<u64>(fillers) * THREADS;
+    const u64 i0 = static_cast<u64>(blockIdx.x - 1) * THREADS + tid;
     const uint4 z = make_uint4(0, 0, 0, 0);
     for (u64 i = i0; i < b.n_zero; i += stride) b.zero[i] = z;
     for (u64 c = i0; c < b.n_chunks; c += stride) {
@@ -314,6 +318,10 @@ __global__ __launch_bounds__(kBeginThreads) void k_begin(BeginArgs b) {
         }
         b.chunk_map[c] = static_cast<u32>(lo);
     }
+}
+__global__ __launch_bounds__(kBeginThreads) void k_begin(BeginArgs b) {
+    __shared__ u32 s_start[kBeginTensors + 1];
+    begin_tables<kBeginThreads>(b.t, gridDim.x - 1, b.chunk_start, s_start);
 }
 
 // Many tensors (or tables beyond one staging slot): the upload, then the clearing and the map as a second launch,
