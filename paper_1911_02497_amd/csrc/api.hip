@@ -837,9 +837,9 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const L
     w.gkey = at<u32>(ws, L.l_gkey);
     w.gidx = at<u32>(ws, L.l_gidx);
     w.gather_cap = L.l_gather_cap;
-    // workgroups that walk each list: about a thousand in all, up to 256 for one ranking (20 M weights: 64 take 4.8 us to count
-    // 80 thousand keys, 256 take 7.5; 134 M weights want them all)
-    const u64 by_size = (N >> 19) < 32 ? 32 : ((N >> 19) > 256 ? 256 : N >> 19);
+    // workgroups that walk each list (several rankings): about a thousand in all, 64 for one ranking or more (four densities of 20 M weights 76.3 us
+    // with 38, 73.6 with 64, 73.8 with 100; ten 107.5, 105.0 and 104.9, the same as 64 from 0.4 to 6 M weights), up to 256 (134 M weights want them all)
+    const u64 by_size = (N >> 19) < 64 ? 64 : ((N >> 19) > 256 ? 256 : N >> 19);
     const u64 share = n_slots >= 1024 ? 1 : 1024 / static_cast<u64>(n_slots);
     w.parts = static_cast<u32>(by_size < share ? by_size : share);
     w.cnt = at<u64>(ws, L.l_cnt);
@@ -1710,7 +1710,8 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
     // One sweep for aggregation AND apply (k_struct_fused.h): 8x8 blocks, every matrix a whole number of 64-block
     // runs wide, 128-bit accesses everywhere, outputs apart from the weights, a threshold strictly inside the
     // population, and enough blocks for the sample to pay (or the form asked for): 2^20 blocks take 218 us this way and
-    // 181 with the aggregates first and a list (k_struct_list.h), 1.5 M blocks 262 and 258, 3.7 M blocks 487 and 606.
+    // 181 with the aggregates first and a list (k_struct_list.h), 1.5 M blocks 262 and 258, 3.7 M blocks 487 and 606.  Strips
+    // (above) come first: this is left with more than 2^24 blocks, 2^30 weights or 1024 tensors.
     bool fused = !per_tensor && (theta || mask) && vec && tb.F > kSmallGroup && slots[0].k > 0 && slots[0].k < tb.F &&
                  (cfg[CONDENSA_OPT_SELECT_PATH] == 2 || (cfg[CONDENSA_OPT_SELECT_PATH] == 0 && tb.F >= (static_cast<u64>(3) << 19))) &&
                  cfg[CONDENSA_OPT_FUSED_SWEEP] == 0;

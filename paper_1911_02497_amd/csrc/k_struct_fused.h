@@ -1,4 +1,5 @@
-// BlockPrune (Table 1) with the weights read once: aggregation and apply in one sweep for 8x8 blocks.
+// BlockPrune (Table 1) with the weights read once: aggregation and apply in one sweep for 8x8 blocks, where there are more of them than
+// k_struct_strip.h takes.
 //
 // Structure pruning needs every aggregate before the first block can be decided, so the plain form reads
 // the weights twice (aggregate, then apply: 13 bytes per weight with theta and mask).  As for element

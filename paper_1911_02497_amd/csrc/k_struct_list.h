@@ -1,5 +1,6 @@
 // Structure rankings of moderate size (more than k_struct_small's 4096 structures, at most kSmallCallElems, GLOBAL
-// scope): one histogram over a window of the aggregates, then a list.
+// scope): one histogram over a window of the aggregates, then a list.  Filters, neurons, blocks in place, of more than 256 elements or of
+// more than two dimensions; other blocks go in strips (k_struct_strip.h).
 //
 // The six levels of a 63-bit ranking are six dependent launches plus the tie search, and the first of them separate little:
 // aggregates of one model share their sign and most exponent bits.  So every workgroup of k_struct_list_hist first takes the
