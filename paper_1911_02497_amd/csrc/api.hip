@@ -1231,7 +1231,14 @@ size_t condensa_workspace_bytes(int op, uint64_t total_elems, uint64_t n_structu
     if (total_elems > kMaxElems || n_structures > total_elems) return 0;
     Config cfg;
     if (resolve_config(config, &cfg) != CONDENSA_OK) return 0;
-    return make_layout(op, total_elems, n_structures, n_tensors, n_densities, scope, cfg).total;
+    const size_t total = make_layout(op, total_elems, n_structures, n_tensors, n_densities, scope, cfg).total;
+    // Large calls that choose their path answer for the sampled window too, which needs more (1.2 G weights: 766 MB, listed 205): who has asked without
+    // a configuration can ask for that path with the same workspace.  Smaller ones never could.
+    if (cfg[CONDENSA_OPT_SELECT_PATH] != 0 || n_densities != 1 || scope != CONDENSA_SCOPE_GLOBAL || (op != CONDENSA_OP_PRUNE && op != CONDENSA_OP_LC_STEP) ||
+        total_elems < (static_cast<u64>(3) << 26)) return total;
+    cfg.v[CONDENSA_OPT_SELECT_PATH] = 2;
+    const size_t window = make_layout(op, total_elems, n_structures, n_tensors, n_densities, scope, cfg).total;
+    return window > total ? window : total;
 }
 
 condensa_status condensa_prune(const condensa_tensor* tensors, int n_tensors, const double* densities,
