@@ -1677,7 +1677,12 @@ static condensa_status run_structure_prune(int op, Tables& tb, int n_tensors, do
                                            size_t workspace_bytes, void* stream, const Config& cfg) {
     const bool per_tensor = (scope == CONDENSA_SCOPE_PER_TENSOR);
     if (per_tensor && n_tensors == 0) return CONDENSA_OK;
-    const Layout L = make_layout(op, tb.N, tb.F, n_tensors, 1, scope, cfg);
+    Layout L = make_layout(op, tb.N, tb.F, n_tensors, 1, scope, cfg);
+    // A workspace sized for another selection path, or for a population too large for strips, may lack their regions, which come last: the call goes without them.
+    if (L.strips && workspace_bytes < L.total) {
+        L.strips = false;
+        L.total = L.s_zero;
+    }
 
     std::vector<OutDesc> out(static_cast<size_t>(n_tensors > 0 ? n_tensors : 1), OutDesc{});
     std::vector<ByteRange> ranges;

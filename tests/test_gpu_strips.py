@@ -9,6 +9,7 @@ import torch
 import oracle
 import paper_1911_02497_amd as P
 from gpu_util import DEV, up
+from paper_1911_02497_amd.binding import OP_BLOCK_PRUNE
 from test_gpu_structure import _compare
 
 pytestmark = pytest.mark.gpu
@@ -125,3 +126,14 @@ def test_more_tensors_than_one_launch_begins_and_capture():
         graph.replay()
         torch.cuda.synchronize()
         _compare(res, oracle.block_prune_nd(new, (4, 4), 0.35, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, new, f"replay {seed}")
+
+
+def test_workspace_without_room_for_strips():
+    arrs = _normal([(512, 1024), (264, 520)], 6)
+    n, f = sum(a.size for a in arrs), 64 * 128 + 33 * 65
+    short, full = [P.condensa_workspace_bytes(OP_BLOCK_PRUNE, n, f, 2, 1, P.SCOPE_GLOBAL, config=c) for c in ({"select_path": 1}, None)]
+    assert short < full
+    for size in (short, full - 256, full):
+        _check(arrs, (8, 8), 0.3, f"{size} bytes", workspace=torch.empty(size, dtype=torch.uint8, device=DEV))
+    with pytest.raises(P.CondensaError):
+        P.condensa_block_prune_nd(up(arrs), (8, 8), 0.3, P.SCOPE_GLOBAL, workspace=torch.empty(short - 256, dtype=torch.uint8, device=DEV))
