@@ -263,6 +263,22 @@ static bool want_window(u64 N, int n_tensors, bool per_tensor, int J, const Conf
     return N > 0 && !want_list(N, n_tensors, J, per_tensor, J, cfg);
 }
 
+// One density whose selection is a sweep of its own (an output in place of an input, two sweeps asked for, no outputs): the listed windows' sweep then
+// writes nothing but its list, and the sampled window's own sweep does that faster where there are many weights, its launches being paid for.  L-C steps in
+// place, density 0.1, listed and sampled: 2.4 10^8 weights 1193 and 1159 us, 3.2 10^8 1524 and 1454, 1.2 G 5810 and 5341; from 3 2^26 on (where lists
+// of one sweep begin to be worth more than windows).  Pruning in place and selection alone: 3.2 10^8 weights 727 and 755, 305 and 332; 8 10^8 1770 and 1739,
+// 682 and 670 (density 0.6: 1800 and 1836, 698 and 744); 1.66 G 3790 and 3639, 1442 and 1315; from 2^29 on.  A workspace without room for it: listed windows.
+static void prefer_window_for_two_sweeps(int op, u64 N, int n_tensors, size_t workspace_bytes, Config* cfg, Layout* L) {
+    const u64 from = op == CONDENSA_OP_LC_STEP ? static_cast<u64>(3) << 26 : static_cast<u64>(1) << 29;
+    if (!L->listed || (*cfg)[CONDENSA_OPT_SELECT_PATH] != 0 || N < from) return;
+    Config sampled = *cfg;
+    sampled.v[CONDENSA_OPT_SELECT_PATH] = 2;
+    const Layout W = make_layout(op, N, 0, n_tensors, 1, CONDENSA_SCOPE_GLOBAL, sampled);
+    if (workspace_bytes < W.total) return;
+    *cfg = sampled;
+    *L = W;
+}
+
 // Segments of the rankings' lists: what their sweep's wavefronts call for (elements per wavefront).
 static u64 list_wave_elems(u64 N, int J, bool lc) { return 256u * static_cast<u64>(J > 1 ? list_multi_quads(N) : (lc ? kFusedQuadsLC : kFusedQuadsPrune)); }
 static u32 list_max_segs(u64 n, int n_slots, int J, bool lc) {
@@ -1055,7 +1071,7 @@ static condensa_status poke_upload(void* dst_dev, const char* src_host, size_t b
 static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors, const double* densities,
                                   int n_densities, int scope, float* const* theta, uint16_t* const* theta_f16,
                                   uint8_t* const* mask, condensa_select* results_dev, void* workspace_dev,
-                                  size_t workspace_bytes, void* stream, const Config& cfg, HostArena& arena,
+                                  size_t workspace_bytes, void* stream, const Config& given, HostArena& arena,
                                   bool no_alloc) {
     if (n_densities < 1 || n_densities > CONDENSA_MAX_DENSITIES) return CONDENSA_ERR_SIZE;
     if (densities == nullptr || results_dev == nullptr) return CONDENSA_ERR_NULL;
@@ -1069,7 +1085,8 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
     const bool per_tensor = (scope == CONDENSA_SCOPE_PER_TENSOR);
     if (per_tensor && n_tensors == 0) return CONDENSA_OK;
     // the allocation-free form keeps to the radix levels, whose workspace is small whatever the input
-    const Layout L = make_layout(CONDENSA_OP_PRUNE, tb.N, 0, n_tensors, J, scope, cfg, no_alloc);
+    Config cfg = given;
+    Layout L = make_layout(CONDENSA_OP_PRUNE, tb.N, 0, n_tensors, J, scope, cfg, no_alloc);
 
     // output table, overlap and alignment checks
     const bool any_out = theta || theta_f16 || mask;
@@ -1106,6 +1123,8 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
         ranges[n_ranges++] = byte_range(tb.td[t].w, n * 4, in_place);
         in_place_any = in_place_any || in_place;
     }
+    if (J == 1 && !per_tensor && (!any_out || in_place_any || cfg[CONDENSA_OPT_FUSED_SWEEP] != 0))
+        prefer_window_for_two_sweeps(CONDENSA_OP_PRUNE, tb.N, n_tensors, workspace_bytes, &cfg, &L);
     ranges[n_ranges++] = byte_range(workspace_dev, workspace_bytes < L.total ? workspace_bytes : L.total, true);
     ranges[n_ranges++] = byte_range(results_dev, static_cast<u64>(L.n_slots) * sizeof(condensa_select), true);
     if (ranges_conflict(ranges, n_ranges)) return CONDENSA_ERR_ARG;
@@ -1232,8 +1251,8 @@ size_t condensa_workspace_bytes(int op, uint64_t total_elems, uint64_t n_structu
     Config cfg;
     if (resolve_config(config, &cfg) != CONDENSA_OK) return 0;
     const size_t total = make_layout(op, total_elems, n_structures, n_tensors, n_densities, scope, cfg).total;
-    // Large calls that choose their path answer for the sampled window too, which needs more (1.2 G weights: 766 MB, listed 205): who has asked without
-    // a configuration can ask for that path with the same workspace.  Smaller ones never could.
+    // Large calls that choose their path answer for the sampled window too, which needs more (1.2 G weights: 766 MB, listed 205): two sweeps take
+    // it by themselves, and who has asked without a configuration can ask for that path with the same workspace.  Smaller ones never could.
     if (cfg[CONDENSA_OPT_SELECT_PATH] != 0 || n_densities != 1 || scope != CONDENSA_SCOPE_GLOBAL || (op != CONDENSA_OP_PRUNE && op != CONDENSA_OP_LC_STEP) ||
         total_elems < (static_cast<u64>(3) << 26)) return total;
     cfg.v[CONDENSA_OPT_SELECT_PATH] = 2;
@@ -1306,7 +1325,7 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
     Tables tb;
     rc = build_tensor_table(tensors, n_tensors, &tb, arena);
     if (rc != CONDENSA_OK) return rc;
-    const Layout L = make_layout(CONDENSA_OP_LC_STEP, tb.N, 0, n_tensors, 1, CONDENSA_SCOPE_GLOBAL, cfg);
+    Layout L = make_layout(CONDENSA_OP_LC_STEP, tb.N, 0, n_tensors, 1, CONDENSA_SCOPE_GLOBAL, cfg);
 
     std::vector<OutDesc> out(static_cast<size_t>(n_tensors > 0 ? n_tensors : 1), OutDesc{});
     std::vector<ByteRange> ranges;
@@ -1342,6 +1361,7 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
         if (o.mask && (reinterpret_cast<uintptr_t>(o.mask) & 3u)) vec = false;
         if (o.theta16 && (reinterpret_cast<uintptr_t>(o.theta16) & 7u)) vec = false;
     }
+    if (in_place_any || cfg[CONDENSA_OPT_FUSED_SWEEP] != 0) prefer_window_for_two_sweeps(CONDENSA_OP_LC_STEP, tb.N, n_tensors, workspace_bytes, &cfg, &L);
     ranges.push_back(byte_range(workspace_dev, workspace_bytes < L.total ? workspace_bytes : L.total, true));
     ranges.push_back(byte_range(result_dev, sizeof(condensa_select), true));
     ranges.push_back(byte_range(nnz_dev, sizeof(uint64_t), true));

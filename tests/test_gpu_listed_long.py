@@ -7,6 +7,7 @@ import torch
 
 import paper_1911_02497_amd as P
 from gpu_util import DEV
+from paper_1911_02497_amd.binding import OP_PRUNE, OP_LC_STEP
 
 pytestmark = pytest.mark.gpu
 
@@ -61,3 +62,37 @@ def test_prune_and_steps(kind, n):
         assert int(pq["nnz"].item()) == sum(int(((c & 0x7FFF) != 0).sum()) for c in pq["theta_f16"])
         assert all(_same(a, b) for a, b in zip(pq["mask"], step["mask"]))
         del ref, step, pq, res
+
+
+# a selection that is a sweep of its own: either side of the lines between the two windows, and a workspace that has room for the lists alone
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("op,n", [("lc", (3 << 26) - 1), ("lc", 3 << 26), ("prune", (1 << 29) - 1), ("prune", (1 << 29) + 3)])
+def test_two_sweeps(op, n):
+    w = _weights("normal", n)
+    d = 0.1
+    lists = n // 4                                         # bytes: more than the lists take, less than the sampled window
+    if op == "lc":
+        lam = [t * 1e-4 for t in w]
+        ref = P.condensa_lc_step(w, lam, 1e-3, d, config={"select_path": 1})
+        names = ("theta", "lambda", "grad", "mask")
+    else:
+        ref = P.condensa_prune(w, [d], config={"select_path": 1})
+        names = ("theta", "mask")
+    want = P.select_records(ref["results"])[0]
+    for ws in (None, torch.empty(lists, dtype=torch.uint8, device=DEV)):
+        if ws is not None:
+            assert n < 3 << 26 or lists < P.condensa_workspace_bytes(OP_LC_STEP if op == "lc" else OP_PRUNE, n, 0, 2, 1, P.SCOPE_GLOBAL)
+        if op == "lc":
+            mine = [t.clone() for t in lam]
+            res = P.condensa_lc_step(w, mine, 1e-3, d, in_place=True, workspace=ws)
+            res = dict(res, **{"lambda": mine})
+            pairs = [(res[name], ref[name]) for name in names]
+        else:
+            res = P.condensa_prune(w, [d], workspace=ws, config={"fused_sweep": 1})
+            pairs = [(res[name][0], ref[name][0]) for name in names]
+            alone = P.select_records(P.condensa_prune(w, [d], theta=False, mask=False, workspace=ws)["results"])[0]
+            assert all(alone[f] == want[f] for f in FIELDS), (alone, want)
+        got = P.select_records(res["results"])[0]
+        assert all(got[f] == want[f] for f in FIELDS), (got, want)
+        assert all(_same(a, b) for x, y in pairs for a, b in zip(x, y))
+        del res, pairs
