@@ -853,9 +853,11 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const L
     w.gkey = at<u32>(ws, L.l_gkey);
     w.gidx = at<u32>(ws, L.l_gidx);
     w.gather_cap = L.l_gather_cap;
-    // workgroups that walk each list (several rankings): about a thousand in all, 64 for one ranking or more (four densities of 20 M weights 76.3 us
-    // with 38, 73.6 with 64, 73.8 with 100; ten 107.5, 105.0 and 104.9, the same as 64 from 0.4 to 6 M weights), up to 256 (134 M weights want them all)
-    const u64 by_size = (N >> 19) < 64 ? 64 : ((N >> 19) > 256 ? 256 : N >> 19);
+    // workgroups that walk each list (several rankings): about a thousand in all, up to 256 for one ranking (134 M weights want them all).  At least 64 where
+    // the rankings share a population (four densities of 20 M weights 76.3 us with 38, 73.6 with 64, 73.8 with 100; ten 107.5, 105.0 and 104.9, the same as 64
+    // from 0.4 to 6 M weights); 32 where each has its own (16 of 2^20 weights 64.0 us with 32, 64.8 with 64; 17 layers of VGG-19 72.6 with 38 and with 60)
+    const u64 least = L.n_groups > 1 ? 32 : 64;
+    const u64 by_size = (N >> 19) < least ? least : ((N >> 19) > 256 ? 256 : N >> 19);
     const u64 share = n_slots >= 1024 ? 1 : 1024 / static_cast<u64>(n_slots);
     w.parts = static_cast<u32>(by_size < share ? by_size : share);
     w.cnt = at<u64>(ws, L.l_cnt);
