@@ -315,8 +315,12 @@ static u32 list_hist_copies(int n_slots) {
     while (c > 1 && c * static_cast<u32>(n_slots) > 256) c /= 2;
     return c;
 }
-static u32 list_posted(u64 N) { return N > kListLong ? kListPosted : kListFound; }
-static u32 list_walkers(u64 N) { return N > kListLong ? kMaxWalkers * kListParts : kMaxWalkers; }
+// One ranking: posted entries, verdicts and ranges (ListArgs::picked and what follows it).  Those of long lists lie where gathered entries otherwise
+// do (posted they are not gathered), cleared that far, so that such calls ask for no more workspace than when their bins were short.
+static u32 list_posted(u64 N) { return list_long(N) ? kListPosted : kListFound; }
+static u32 list_walkers(u64 N) { return list_long(N) ? kMaxWalkers * kListParts : kMaxWalkers; }
+static size_t list_post_bytes(u64 N) { return (list_posted(N) + list_walkers(N)) * sizeof(u64) + list_walkers(N) * sizeof(u32); }
+static_assert((kListPosted + kMaxWalkers * kListParts) * sizeof(u64) + kMaxWalkers * kListParts * sizeof(u32) <= kListGather * sizeof(u32), "gathered keys make room");
 static u32 list_uneven_copies(int n_slots) { return n_slots == 1 ? 64u : list_hist_copies(n_slots); }
 static u32 list_groups(u64 n, int J, bool per_tensor, const Config& cfg) {         // sampling workgroups of a population
     const int64_t opt = cfg[CONDENSA_OPT_SAMPLE_LOG2];
@@ -371,13 +375,18 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
         L.l_nnz = off;     off += align_up(kListSegs * sizeof(u32));
         L.seg = off;       off += op == CONDENSA_OP_LC_STEP ? align_up(kNnzSegs * sizeof(u64)) : 0;
         L.l_hist = off;    off += align_up(static_cast<size_t>(L.n_slots) * list_uneven_copies(L.n_slots) * kListBins * sizeof(u32));
-        L.l_post = off;    off += L.n_slots == 1 ? align_up(256 + (list_posted(N) + list_walkers(N)) * sizeof(u64) + list_walkers(N) * sizeof(u32)) : 0;
+        const bool long_list = L.n_slots == 1 && list_long(N);
+        L.l_post = off;    off += L.n_slots == 1 ? align_up(256 + (long_list ? 0 : list_post_bytes(N))) : 0;
         L.l_gathered = off; off += align_up(static_cast<size_t>(L.n_slots) * kListLine * sizeof(u32));
         L.l_fb = off;      off += align_up(sizeof(FallbackCtl));
         L.l_gmax = off;    off += align_up(2 * static_cast<size_t>(L.n_slots) * sizeof(u32));
         L.l_masks = off;   off += align_up(3 * static_cast<size_t>(L.n_groups) * sizeof(u32));
         L.l_meet = off;    off += align_up(kMeetWords * sizeof(u32));
-        L.zero_bytes = off - L.zero_begin;
+        L.l_gather_cap = (1u << 20) / L.n_slots > kListGather ? kListGather : ((1u << 20) / L.n_slots < kListRanked ? kListRanked : (1u << 20) / L.n_slots);
+        L.l_gkey = off;
+        L.l_posted = long_list ? L.l_gkey : L.l_post + 256;
+        L.zero_bytes = off - L.zero_begin + (long_list ? align_up(list_post_bytes(N)) : 0);
+        off += align_up(static_cast<size_t>(L.n_slots) * L.l_gather_cap * sizeof(u32));
         L.chunk_map = off; off += align_up(static_cast<size_t>(L.max_chunks + 1) * sizeof(u32));
         L.tiecnt = off;    off += align_up(static_cast<size_t>(J) * L.max_chunks * sizeof(u32));
         L.l_special = off; off += align_up(2 * static_cast<size_t>(L.n_slots) * sizeof(u32));
@@ -385,8 +394,6 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
         L.l_fb_bins = list_fallback_bins(L.n_slots, J);
         L.l_fb_hist = off; off += align_up(3 * static_cast<size_t>(L.n_slots) * L.l_fb_bins * sizeof(u32));
         L.l_want = off;    off += align_up(static_cast<size_t>(L.n_slots) * sizeof(u32));
-        L.l_gather_cap = (1u << 20) / L.n_slots > kListGather ? kListGather : ((1u << 20) / L.n_slots < kListRanked ? kListRanked : (1u << 20) / L.n_slots);
-        L.l_gkey = off;    off += align_up(static_cast<size_t>(L.n_slots) * L.l_gather_cap * sizeof(u32));
         L.l_gidx = off;    off += align_up(static_cast<size_t>(L.n_slots) * L.l_gather_cap * sizeof(u32));
         L.l_win = off;     off += align_up(static_cast<size_t>(L.n_slots) * sizeof(ListWin));
         L.l_sorted = off;  off += J > 1 ? align_up(static_cast<size_t>(L.n_groups) * sizeof(ListSorted)) : 0;
@@ -845,7 +852,7 @@ static ListArgs list_args(const Layout& L, void* ws, u64 N, int n_slots, const L
     w.count_in_sweep = !shape.lone && n_slots == 1 ? 1 : 0;
     w.arrived = at<u32>(ws, L.l_post);
     w.ended = w.arrived + kListLine;
-    w.picked = at<u64>(ws, L.l_post + 256);
+    w.picked = at<u64>(ws, L.l_posted);
     w.verdict = w.picked + list_posted(N);
     w.range = reinterpret_cast<u32*>(w.verdict + list_walkers(N));
     w.gathered = at<u32>(ws, L.l_gathered);
@@ -997,7 +1004,7 @@ static condensa_status launch_listed(const DataArgs& a, const Layout& L, void* w
     }
     if (n_slots == 1) {
         for (int late = 0; late <= ((t_force & kForceLate) ? 1 : 0); ++late) {
-            const bool is_long = a.N > kListLong;
+            const bool is_long = list_long(a.N);
             if (is_long && LC && rq.pq) hipLaunchKernelGGL((k_list_resolve<LC, VEC, LC, true>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
             else if (is_long)           hipLaunchKernelGGL((k_list_resolve<LC, VEC, false, true>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);
             else if (LC && rq.pq)       hipLaunchKernelGGL((k_list_resolve<LC, VEC, LC, false>), fb, dim3(kSettleThreads), 0, st, a, w, results, vo);

@@ -159,7 +159,7 @@ struct Layout {
     size_t tl_cnt = 0, tl_key = 0, tl_idx = 0;              // short lists of the keys that reach the last radix level's bins
     bool listed = false;                                    // the call takes the listed windows (k_listed.h): its regions are
     size_t l_rank = 0, l_cnt = 0, l_nnz = 0, l_fb = 0, l_fb_hist = 0, l_special = 0, l_state = 0, l_masks = 0, l_meet = 0;
-    size_t l_local = 0, l_win = 0, l_key = 0, l_idx = 0, l_sorted = 0, l_hist = 0, l_post = 0, l_gathered = 0, l_gmax = 0, l_want = 0, l_gkey = 0, l_gidx = 0;
+    size_t l_local = 0, l_win = 0, l_key = 0, l_idx = 0, l_sorted = 0, l_hist = 0, l_post = 0, l_posted = 0, l_gathered = 0, l_gmax = 0, l_want = 0, l_gkey = 0, l_gidx = 0;
     u32 l_max_segs = 0, l_gather_cap = 0, l_fb_bins = 0;
     size_t skeys = 0, sblock = 0, smask = 0;                // structure keys, per-block kept counts, keep flags
     size_t sample = 0, cand_key = 0, cand_idx = 0;          // window path

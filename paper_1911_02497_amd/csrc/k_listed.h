@@ -52,6 +52,7 @@ constexpr u32 kListLine = 32;                    // words of a 128-byte line
 // Lists of more elements than this are long: with 256 sampling workgroups of four units their bins outgrow kListFound, and a wavefront's share of corrections
 // its queue.
 constexpr u64 kListLong = static_cast<u64>(1) << 27;
+inline bool list_long(u64 N) { return N > kListLong; }
 constexpr u32 kListFound = 4096;                 // entries of the threshold's bin that k_list_resolve ranks from LDS
 constexpr u32 kListPosted = 16384;               // ... and of long lists
 constexpr u32 kListRow = 64;                     // segments are multiples of this many entries

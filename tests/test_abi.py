@@ -3,7 +3,10 @@ import ctypes
 import os
 import re
 
+import pytest
+
 import paper_1911_02497_amd as P
+from paper_1911_02497_amd import binding as B
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -258,3 +261,11 @@ def test_argument_errors_are_found_on_the_host_before_any_launch():
     assert lib.condensa_block_prune(t, 1, 0, 4, 0.5, 0, null, null, null, null, null, null, res, ws, 1 << 30, null, null) == -4
     for code in (0, -1, -2, -3, -4, -5, -6, -7):
         assert len(lib.condensa_status_string(code)) > 0
+
+
+@pytest.mark.parametrize("op,n,tensors,scope,kept", [
+    (B.OP_PRUNE, (1 << 27) + 1, 1, B.SCOPE_GLOBAL, 24897024), (B.OP_PRUNE, (3 << 26) - 1, 97, B.SCOPE_GLOBAL, 36507648),
+    (B.OP_PRUNE, 1207959552, 1, B.SCOPE_PER_TENSOR, 211500800), (B.OP_LC_STEP, 190_000_000, 17, B.SCOPE_GLOBAL, 34391040)])
+def test_kept_workspaces_of_long_lists_still_do(op, n, tensors, scope, kept):
+    """Sizes that these calls asked for while every bin of a list was ranked from 4096 posted entries: a program may have kept such a workspace."""
+    assert P.condensa_workspace_bytes(op, n, 0, tensors, 1, scope) <= kept
