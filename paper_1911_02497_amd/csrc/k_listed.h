@@ -54,7 +54,7 @@ constexpr u32 kListLine = 32;                    // words of a 128-byte line
 constexpr u64 kListLong = static_cast<u64>(1) << 27;
 inline bool list_long(u64 N) { return N > kListLong; }
 constexpr u32 kListFound = 4096;                 // entries of the threshold's bin that k_list_resolve ranks from LDS
-constexpr u32 kListPosted = 16384;               // ... and of long lists
+constexpr u32 kListPosted = 65536;               // ... and of long lists: 1.2 G weights 12 to 25 thousand as their threshold lies in its binade, more where rows differ in size
 constexpr u32 kListRow = 64;                     // segments are multiples of this many entries
 
 // Populations up to here are sampled and finished by one workgroup.  Several densities: the windows of one sampling workgroup
@@ -174,7 +174,8 @@ struct ListState {         // a ranking that the list did not resolve
     u32 unused[2];
 };
 constexpr u64 kPicked = static_cast<u64>(1) << 63;         // the entry is there
-constexpr u32 kRangeKnown = 0x80000000u;
+constexpr u32 kRangeKnown = 0x80000000u, kRangeBits = 17;
+static_assert(kListPosted < 1u << kRangeBits, "ListArgs::range");
 constexpr u64 kWalkerLeft = 1;
 constexpr u32 kMaxWalkers = kListSegs / 8;                 // a segment for each of a workgroup's eight wavefronts
 constexpr u32 kListParts = 4;                              // wavefronts that share a segment where lists are long
@@ -200,7 +201,7 @@ struct ListArgs {
     u32* arrived;          // one ranking: workgroups that have walked their part of the list << 20 | entries they gathered
     u32* ended;            // one ranking, prune + binary16 step: workgroups that are done
     u64* picked;           // one ranking: [kListFound or kListPosted] gathered entries, index | key << 32 | kPicked
-    u32* range;            // one ranking: [kMaxWalkers] where a workgroup's entries stand among these, first | number << 16 | kRangeKnown
+    u32* range;            // one ranking: [kMaxWalkers] where a workgroup's entries stand among these, first | number << kRangeBits | kRangeKnown
     u64* verdict;          // one ranking: [kMaxWalkers] for each workgroup: the last entry kept (as in `picked`), or kWalkerLeft
     u32* gathered;         // [rankings][kListLine] entries in the threshold's bin (a counter in a line of its own)
     u32* bin_want;         // [rankings] rank to find among them
@@ -1907,7 +1908,7 @@ __device__ inline bool list_rank_short(const DataArgs& a, const ListArgs& w, Ran
     const u32 T = top_key - static_cast<u32>(found >> 32), last = static_cast<u32>(found);
     if (tid < walkers) {
         const u64 was = __hip_atomic_exchange(w.verdict + tid, kPicked | (static_cast<u64>(T) << 32) | last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const u32 first = range & 0xFFFFu, count = (range & ~kRangeKnown) >> 16;
+        const u32 first = range & ((1u << kRangeBits) - 1u), count = (range & ~kRangeKnown) >> kRangeBits;
         if (was != kWalkerLeft)
             for (u32 i = 0; i < count && first + i < kListFound; ++i) sh.owned[first + i] = 1;
     }
@@ -1936,9 +1937,10 @@ __device__ inline bool list_rank_short(const DataArgs& a, const ListArgs& w, Ran
     return true;
 }
 
-// The same for long lists (k_list_resolve<..., LONG>), whose bins hold thousands of entries (7000 and up at 10^9 weights): up to kListPosted of them, of
-// which LDS holds those that share the threshold's first digits.  1.2 G weights pruned: the launch 57 us, 130 where such bins were left to the whole grid, 155
-// where every digit was a pass over the posted entries.  A kernel of its own: with this in the one for short lists the L-C step of 20 M weights took 3.6 us more.
+// The same for long lists (k_list_resolve<..., LONG>), whose bins hold thousands of entries: up to kListPosted of them, of which LDS holds those that share
+// the threshold's first digits.  1.2 G weights pruned, 12 thousand in the bin: the launch 57 us, 130 where such bins were left to the whole grid, 155
+// where every digit was a pass over the posted entries.  Up to 65 536 and not 16 384: the same call with 20 thousand 1834 -> 1770 us; 604 M weights in rows of
+// very different sizes, L-C step 2145 -> 2033.  A kernel of its own: with this in the one for short lists the L-C step of 20 M weights took 3.6 us more.
 struct RankLong {
     u64 entry[kListFound];                       // as in RankShort
     u64 pair[kShortPairs];
@@ -2047,7 +2049,7 @@ __device__ inline bool list_rank_long(const DataArgs& a, const ListArgs& w, Rank
     const u32 T = top_key - static_cast<u32>(found >> 32), last = static_cast<u32>(found);
     if (tid < walkers) {
         const u64 was = __hip_atomic_exchange(w.verdict + tid, kPicked | (static_cast<u64>(T) << 32) | last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const u32 first = range & 0xFFFFu, number = (range & ~kRangeKnown) >> 16;
+        const u32 first = range & ((1u << kRangeBits) - 1u), number = (range & ~kRangeKnown) >> kRangeBits;
         if (was != kWalkerLeft && number != 0) {
             atomicAdd(&sh.n_owned, number);
             for (u32 i = first; i < first + number && i < kListPosted; ++i) atomicOr(&sh.owned[i / 32], 1u << (i % 32));
@@ -3218,7 +3220,7 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_settle(DataArgs a, L
 // Posting is one update that counts workgroups and entries both; the entries follow it, each with a bit that says it is there, and the
 // last workgroup waits for those still on their way (their workgroups wait for nobody).
 // Bound by latency: a launch and some ten dependent accesses.
-// LONG: lists of millions of entries (list_long).  Four wavefronts share a segment, and bins of thousands are ranked in the same way.
+// LONG: lists of millions of entries (list_long says which).  Four wavefronts share a segment, and bins of thousands are ranked in the same way.
 template <bool LC, bool VEC, bool PQ, bool LONG>
 __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, ListArgs w, condensa_select* results, int vec_out) {
     constexpr u32 kWaves = kSettleThreads / 64, kRoom = 256, kFound = 64;              // for each wavefront
@@ -3298,7 +3300,7 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
         __syncthreads();
         const u32 ticket = s_found[kWaves], base = (ticket & 0xFFFFFu) + before;
         if (lane < n_found) post(base + lane, fkey[lane], fidx[lane]);
-        if (tid == 0) st_dev(w.range + blockIdx.x, kRangeKnown | (all << 16) | ((ticket & 0xFFFFu) < kPosted ? ticket & 0xFFFFu : kPosted));
+        if (tid == 0) st_dev(w.range + blockIdx.x, kRangeKnown | (all << kRangeBits) | ((ticket & 0xFFFFFu) < kPosted ? ticket & 0xFFFFFu : kPosted));
         queue.template fix<LC, PQ>(a, w, 0, &nz);
         // what settling its own entries will read is on its way meanwhile
         const u32 idx1[1] = {lane < n_found ? fidx[lane] : 0u};

@@ -64,6 +64,30 @@ def test_prune_and_steps(kind, n):
         del ref, step, pq, res
 
 
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("scale,d", [(1.0, 0.1), (1.5, 0.4)])
+def test_bins_of_tens_of_thousands(scale, d):
+    """Rows whose sizes differ widen the window: some 30 thousand entries in the threshold's bin."""
+    g = torch.Generator(device=DEV).manual_seed(5)
+    w = torch.empty((131072, 4608), dtype=torch.float32, device=DEV).normal_(0.0, 0.02, generator=g)
+    w *= torch.exp(scale * torch.empty((131072, 1), dtype=torch.float32, device=DEV).normal_(0.0, 1.0, generator=g))
+    ws = [w[:100_000], w[100_000:]]
+    lam = [t * 0.0 for t in ws]
+    ref = P.condensa_prune(ws, [d], config={"select_path": 1})
+    want = P.select_records(ref["results"])[0]
+    for what in (0, LATE, NO_VERDICT, ASK):
+        with forced(what):
+            res = P.condensa_prune(ws, [d])
+        got = P.select_records(res["results"])[0]
+        assert all(got[f] == want[f] for f in FIELDS) and got["path"] == 2, (what, got, want)
+        for name in ("theta", "mask"):
+            assert all(_same(a, b) for a, b in zip(res[name][0], ref[name][0])), (what, name)
+        with forced(what):
+            pq = P.condensa_lc_step_pq(ws, lam, 1e-3, d, nnz=True)
+        assert all(_same(a, b) for a, b in zip(pq["mask"], ref["mask"][0])), what
+        assert int(pq["nnz"].item()) == sum(int(((c & 0x7FFF) != 0).sum()) for c in pq["theta_f16"])
+
+
 # a selection that is a sweep of its own: either side of the lines between the two windows, and a workspace that has room for the lists alone
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("op,n", [("lc", (3 << 26) - 1), ("lc", 3 << 26), ("prune", (1 << 29) - 1), ("prune", (1 << 29) + 3)])
