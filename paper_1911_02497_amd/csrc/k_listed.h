@@ -49,10 +49,10 @@ static_assert(kListBins == 1 << 8, "list_window: 32 - 8 bits");
 constexpr u32 kListRanked = 2048;                // gathered entries that are held in LDS
 constexpr u32 kListGather = 1u << 18;            // gathered entries of a ranking at most; with more (ties) it is left open
 constexpr u32 kListLine = 32;                    // words of a 128-byte line
-// Lists of more elements than this are long: with 256 sampling workgroups of four units their bins outgrow kListFound, and a wavefront's share of corrections
-// its queue.
-constexpr u64 kListLong = static_cast<u64>(1) << 27;
-inline bool list_long(u64 N) { return N > kListLong; }
+// Lists of at least so many elements are long: from there on their bins outgrow kListFound (201 M weights: 4.1 thousand entries at the most), and posting to the
+// larger arrays costs up to 8 us: pruning 151 M weights 250 us short and 258 long, 189 M 302 and 309, L-C step 517 and 524, 624 and 630; 208 M 338 either way.
+constexpr u64 kListLong = static_cast<u64>(3) << 26;
+inline bool list_long(u64 N) { return N >= kListLong; }
 constexpr u32 kListFound = 4096;                 // entries of the threshold's bin that k_list_resolve ranks from LDS
 constexpr u32 kListPosted = 65536;               // ... and of long lists: 1.2 G weights 12 to 25 thousand as their threshold lies in its binade, more where rows differ in size
 constexpr u32 kListRow = 64;                     // segments are multiples of this many entries

@@ -1,4 +1,4 @@
-"""GPU parity of listed windows on lists of millions of entries (more than 2^27 weights, one density): bins of thousands of entries, ties in them,
+"""GPU parity of listed windows on lists of millions of entries (2^27 weights and more, one density; 3 2^26 and more are ranked by kernels of their own): bins of thousands of entries, ties in them,
 workgroups that leave.  Against the radix levels, which the oracle anchors at sizes that it can sort; bit for bit."""
 import contextlib
 
@@ -39,7 +39,7 @@ def _same(a, b):
 
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("kind", ["normal", "ties"])
-@pytest.mark.parametrize("n", [(1 << 27) + 1, 400_000_003])
+@pytest.mark.parametrize("n", [(1 << 27) + 1, (3 << 26) - 1, 3 << 26, 400_000_003])
 def test_prune_and_steps(kind, n):
     ws = _weights(kind, n)
     lam = [t * 0.0 for t in ws]
