@@ -1360,6 +1360,41 @@ __device__ inline void list_walk(const ListArgs& w, u32 s, const ListRank& rk, u
     }
 }
 
+// f(there, key, index) for the entries of the ranking that this wavefront takes: every `stride`-th segment, `cnt` entries each (in
+// LDS), kListDeep rows of two segments at a time with their loads in flight together; called by all lanes, `there` says which hold
+// an entry.
+template <typename F>
+__device__ inline void list_walk_own(const ListArgs& w, const ListRank& rk, const u32* cnt_of, u32 first_seg, u32 stride, F&& f, u32 part = 0, u32 parts = 1) {
+    const u32 lane = threadIdx.x & 63u;
+    for (u32 seg0 = first_seg; seg0 < rk.n_segs; seg0 += 2 * stride) {
+        u32 cnt[2], most = 0;
+        u64 first[2];
+#pragma unroll
+        for (u32 b = 0; b < 2; ++b) {
+            const u32 seg = seg0 + b * stride;
+            cnt[b] = seg < rk.n_segs ? cnt_of[seg] : 0u;
+            first[b] = rk.base + static_cast<u64>(seg) * rk.seg_cap;
+            most = cnt[b] > most ? cnt[b] : most;
+        }
+        for (u32 i0 = 64 * kListDeep * part; i0 < most; i0 += 64 * kListDeep * parts) {              // uniform
+            u32 x[kListDeep][2], e[kListDeep][2];
+#pragma unroll
+            for (u32 d = 0; d < kListDeep; ++d)
+#pragma unroll
+                for (u32 b = 0; b < 2; ++b) {
+                    const u32 i = i0 + 64 * d + lane, last = cnt[b] ? cnt[b] - 1u : 0u;
+                    const u64 at = first[b] + (i < cnt[b] ? i : last);
+                    if (i0 + 64 * d < cnt[b]) { x[d][b] = w.key[at]; e[d][b] = w.idx[at]; }        // uniform
+                }
+#pragma unroll
+            for (u32 d = 0; d < kListDeep; ++d)
+#pragma unroll
+                for (u32 b = 0; b < 2; ++b)
+                    if (i0 + 64 * d < cnt[b]) f(i0 + 64 * d + lane < cnt[b], x[d][b], e[d][b]);    // uniform
+        }
+    }
+}
+
 // hist[bin] += 1 for the lanes that are `there`; all lanes call it.  Lanes that meet on a counter take turns, and listed keys
 // often are equal (weights on a grid), so the two commonest-looking bins are added up across the wavefront first.
 __device__ inline void wave_count(u32* hist, bool there, u32 bin) {
@@ -1839,12 +1874,13 @@ struct RankShort {
     u8 owned[kListFound];                        // its workgroup settles it
 };
 // Posts are on their way when they are waited for (their workgroups are running), so this bound, some 0.1 s, is not met.  If it were, the
-// workgroup would search the whole population itself (list_search) instead of waiting for ever.
+// workgroup would fetch the entries itself from the lists, which are whole, and settle them all: it tells nobody, so the others leave.  (1.2 G weights
+// have some 2.7 M listed: a few ms.)
 constexpr u32 kPostPolls = 1u << 16;
-// False: entries are missing.
+// `cnt`: entries of the list's segments, in LDS.
 template <bool LC, bool PQ, int THREADS>
-__device__ inline bool list_rank_short(const DataArgs& a, const ListArgs& w, RankShort& sh, u32 want, u32 n, u32 bin, const ListWin& win, u32 walkers,
-                                       condensa_select* results, int* nz) {
+__device__ inline void list_rank_short(const DataArgs& a, const ListArgs& w, const ListRank& rk, const u32* cnt, RankShort& sh, u32 want, u32 n, u32 bin,
+                                       const ListWin& win, u32 walkers, condensa_select* results, int* nz) {
     static_assert(THREADS >= 256 && THREADS >= static_cast<int>(kMaxWalkers), "a thread a bin, a thread a workgroup");
     const u32 tid = threadIdx.x, shift = win_shift(win), top_key = win.lo + (bin << shift) + ((1u << shift) - 1u);
     static_assert(THREADS / 64 <= static_cast<int>(kMaxWalkers / 8), "a word a wavefront");
@@ -1867,7 +1903,16 @@ __device__ inline bool list_rank_short(const DataArgs& a, const ListArgs& w, Ran
     u32 is_missing = 0;
 #pragma unroll
     for (int i = 0; i < THREADS / 64; ++i) is_missing |= sh.missing[i];
-    if (is_missing != 0) return false;           // uniform
+    if (is_missing != 0) {                       // uniform
+        for (u32 i = tid; i < n; i += THREADS) sh.owned[i] = 0;
+        list_walk_own(w, rk, cnt, tid >> 6, THREADS / 64, [&](bool there, u32 key, u32 idx) {
+            const u32 at = there && (key - win.lo) >> shift == bin ? atomicAdd(&sh.n, 1u) : n;             // n of them
+            if (at < n) sh.entry[at] = (static_cast<u64>(top_key - key) << 32) | idx;
+        });
+        __syncthreads();
+        if (tid == 0) sh.n = 0;
+        __syncthreads();
+    }
     u64 prefix = 0;
     u32 top = 32 + shift, in = n, r = want;      // the r-th from the bottom among the `in` entries whose bits from `top` on are the prefix
     while (in > kShortPairs && top > 0) {        // uniform
@@ -1906,7 +1951,7 @@ __device__ inline bool list_rank_short(const DataArgs& a, const ListArgs& w, Ran
     __syncthreads();
     const u64 found = sh.found;
     const u32 T = top_key - static_cast<u32>(found >> 32), last = static_cast<u32>(found);
-    if (tid < walkers) {
+    if (tid < walkers && is_missing == 0) {
         const u64 was = __hip_atomic_exchange(w.verdict + tid, kPicked | (static_cast<u64>(T) << 32) | last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const u32 first = range & ((1u << kRangeBits) - 1u), count = (range & ~kRangeKnown) >> kRangeBits;
         if (was != kWalkerLeft)
@@ -1932,9 +1977,8 @@ __device__ inline bool list_rank_short(const DataArgs& a, const ListArgs& w, Ran
             tie_end = static_cast<u64>(last) - td.chunk_start * kChunk + (a.per_tensor ? 0 : td.flat_start) + 1;
         }
         slot.prefix = T; slot.remaining = sh.kept; slot.n_tie = sh.n_tie; slot.need_tie = 0; slot.tie_end = tie_end; slot.state = kDone;
-        *results = select_record(slot, true, T, sh.kept, sh.n_tie, tie_end, slot.path);
+        *results = select_record(slot, true, T, sh.kept, sh.n_tie, tie_end, is_missing == 0 ? slot.path : 3);
     }
-    return true;
 }
 
 // The same for long lists (k_list_resolve<..., LONG>), whose bins hold thousands of entries: up to kListPosted of them, of which LDS holds those that share
@@ -1950,19 +1994,20 @@ struct RankLong {
     u32 owned[kListPosted / 32];                 // a bit each: its workgroup settles it
 };
 template <bool LC, bool PQ, int THREADS>
-__device__ inline bool list_rank_long(const DataArgs& a, const ListArgs& w, RankLong& sh, u32 want, u32 n, u32 bin, const ListWin& win, u32 walkers,
-                                       condensa_select* results, int* nz) {
+__device__ inline void list_rank_long(const DataArgs& a, const ListArgs& w, const ListRank& rk, const u32* cnt, RankLong& sh, u32 want, u32 n, u32 bin,
+                                      const ListWin& win, u32 walkers, condensa_select* results, int* nz) {
     static_assert(THREADS >= 256 && THREADS >= static_cast<int>(kMaxWalkers * kListParts), "a thread a bin, a thread a workgroup");
     const u32 tid = threadIdx.x, shift = win_shift(win), top_key = win.lo + (bin << shift) + ((1u << shift) - 1u);
     static_assert(THREADS / 64 <= 16, "a word a wavefront");
     const bool in_lds = n <= kListFound;         // uniform
     auto entry = [&](u64 x) { return (static_cast<u64>(top_key - (static_cast<u32>(x >> 32) & 0x7FFFFFFFu)) << 32) | static_cast<u32>(x); };
+    const u64* from = w.picked;
     // f(place, entry) for all that were posted, eight loads at a time (they pass the caches)
     auto posted = [&](auto&& f) {
         for (u32 i0 = tid; i0 < n; i0 += 8 * THREADS) {
             u64 x[8];
 #pragma unroll
-            for (u32 j = 0; j < 8; ++j) x[j] = ld_dev64(w.picked + (i0 + j * THREADS < n ? i0 + j * THREADS : i0));
+            for (u32 j = 0; j < 8; ++j) x[j] = ld_dev64(from + (i0 + j * THREADS < n ? i0 + j * THREADS : i0));
 #pragma unroll
             for (u32 j = 0; j < 8; ++j) if (i0 + j * THREADS < n) f(i0 + j * THREADS, x[j]);
         }
@@ -1992,7 +2037,22 @@ __device__ inline bool list_rank_long(const DataArgs& a, const ListArgs& w, Rank
     u32 is_missing = 0;
 #pragma unroll
     for (int i = 0; i < THREADS / 64; ++i) is_missing |= sh.missing[i];
-    if (is_missing != 0) return false;           // uniform
+    if (is_missing != 0) {                       // uniform
+        u64* const own = reinterpret_cast<u64*>(w.gidx);                 // where the indices of gathered entries otherwise are
+        static_assert(2 * kListPosted <= kListGather, "room for them");
+        if (tid < 256) sh.hist[tid] = 0;
+        list_walk_own(w, rk, cnt, tid >> 6, THREADS / 64, [&](bool there, u32 key, u32 idx) {
+            const u32 at = there && (key - win.lo) >> shift == bin ? atomicAdd(&sh.n, 1u) : n;             // n of them
+            if (at < n) st_dev64(own + at, kPicked | (static_cast<u64>(key) << 32) | idx);
+        });
+        wait_dev();
+        __syncthreads();
+        if (tid == 0) sh.n = 0;
+        from = own;
+        if (in_lds) posted([&](u32 i, u64 x) { sh.entry[i] = entry(x); });
+        else        posted([&](u32, u64 x) { count(entry(x)); });
+        __syncthreads();
+    }
     auto pick = [&]() {                          // the digit that the counts say
         if (tid < 64) {                          // four bins a lane, from the bottom
             const uint4 c4 = *reinterpret_cast<const uint4*>(sh.hist + 4 * tid);
@@ -2047,7 +2107,7 @@ __device__ inline bool list_rank_long(const DataArgs& a, const ListArgs& w, Rank
     __syncthreads();
     const u64 found = sh.found;
     const u32 T = top_key - static_cast<u32>(found >> 32), last = static_cast<u32>(found);
-    if (tid < walkers) {
+    if (tid < walkers && is_missing == 0) {
         const u64 was = __hip_atomic_exchange(w.verdict + tid, kPicked | (static_cast<u64>(T) << 32) | last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const u32 first = range & ((1u << kRangeBits) - 1u), number = (range & ~kRangeKnown) >> kRangeBits;
         if (was != kWalkerLeft && number != 0) {
@@ -2070,7 +2130,7 @@ __device__ inline bool list_rank_long(const DataArgs& a, const ListArgs& w, Rank
             const bool kept = e <= found;
             if (kept != (top_key - static_cast<u32>(e >> 32) >= win.mid)) list_fix_one<LC, PQ>(a, w, 0, static_cast<u32>(e), kept, nz);
         };
-        for (u32 i = tid; i < n; i += THREADS) fix(i, in_lds ? sh.entry[i] : entry(ld_dev64(w.picked + i)));
+        for (u32 i = tid; i < n; i += THREADS) fix(i, in_lds ? sh.entry[i] : entry(ld_dev64(from + i)));
     }
     if (tid == 0) {
         Slot& slot = a.slots[0];
@@ -2080,83 +2140,7 @@ __device__ inline bool list_rank_long(const DataArgs& a, const ListArgs& w, Rank
             tie_end = static_cast<u64>(last) - td.chunk_start * kChunk + (a.per_tensor ? 0 : td.flat_start) + 1;
         }
         slot.prefix = T; slot.remaining = sh.kept; slot.n_tie = sh.n_tie; slot.need_tie = 0; slot.tie_end = tie_end; slot.state = kDone;
-        *results = select_record(slot, true, T, sh.kept, sh.n_tie, tie_end, slot.path);
-    }
-    return true;
-}
-
-// One ranking by one workgroup from the weights alone, whatever else is in the workspace: radix levels of eight bits, the tie that is
-// kept last, outputs, record and count of codes.  Elements one at a time and a barrier for every few hundred: some ms for a million of
-// weights, but no registers that the callers' own work would have to make room for.
-template <bool LC, bool PQ, int THREADS>
-__device__ inline void list_search(const DataArgs& a, const ListArgs& w, ListShared& sh, condensa_select* results) {
-    const u32 tid = threadIdx.x;
-    Slot& slot = a.slots[0];
-    const u32 n_chunks = static_cast<u32>(a.n_chunks);
-    // f(there, index, value, its key) for all elements, in the order of their indices: THREADS at a time, until it returns true
-    auto for_all = [&](auto&& f) {
-#pragma unroll 1
-        for (u32 c = 0; c < n_chunks; ++c) {
-            const TensorDesc& td = a.td[a.chunk_map[c]];
-            const u64 base = (c - td.chunk_start) * kChunk;
-#pragma unroll 1
-            for (u32 i = tid; i < static_cast<u32>(kChunk); i += THREADS) {
-                const bool there = base + i < td.n;
-                float v = there ? td.w[base + i] : 0.0f;
-                if (LC && there) v = lc_shift(v, td.lam[base + i], a.mu);
-                if (f(there, c * kChunk + i, v, mag_key(v))) return;     // uniform
-            }
-        }
-    };
-    u32 T = 0, rem = static_cast<u32>(slot.k), n_tie = 0, b;
-#pragma unroll 1
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        __syncthreads();
-        if (tid < static_cast<u32>(kListBins)) sh.hist[tid] = 0;
-        __syncthreads();
-        for_all([&](bool there, u32, float, u32 key) {
-            if (there && (shift == 24 || (key >> (shift + 8)) == (T >> (shift + 8)))) atomicAdd(&sh.hist[(key >> shift) & 255u], 1u);
-            return false;
-        });
-        __syncthreads();
-        list_pick(sh, true, rem, &b, &rem, &n_tie);
-        T |= b << shift;
-    }
-    u32 last = 0xFFFFFFFFu;
-    u64 tie_end = slot.n;
-    if (rem < n_tie) {                           // uniform
-        u32 cum = 0;
-        for_all([&](bool there, u32 idx, float, u32 key) {
-            const u32 mine = there && key == T ? 1u : 0u;
-            u32 total;
-            const u32 upto = cum + wg_incl_scan_u32<THREADS>(mine, sh.wave, &total);
-            if (mine != 0 && upto == rem) sh.last = idx;
-            cum += total;
-            __syncthreads();
-            return cum >= rem;
-        });
-        last = sh.last;
-        const TensorDesc& td = a.td[a.chunk_map[last / kChunk]];
-        tie_end = static_cast<u64>(last) - td.chunk_start * kChunk + (a.per_tensor ? 0 : td.flat_start) + 1;
-    }
-    u32 codes = 0;
-    if (w.write)
-        for_all([&](bool there, u32 idx, float v, u32 key) {
-            const bool keep = key > T || (key == T && idx <= last);
-            int unused = 0;
-            if (there) list_fix_one<LC, PQ>(a, w, 0, idx, keep, &unused);
-            if (PQ && there && keep && (f32_to_f16_rne(v) & 0x7FFFu) != 0) ++codes;
-            return false;
-        });
-    if (PQ && w.nnz_out && w.write) {
-        u32 total;
-        __syncthreads();
-        wg_incl_scan_u32<THREADS>(codes, sh.wave, &total);
-        if (tid == 0) *w.nnz_out = total;
-    }
-    if (tid == 0) {
-        slot.prefix = T; slot.remaining = rem; slot.n_tie = n_tie; slot.need_tie = 0; slot.tie_end = tie_end; slot.state = kDone;
-        *results = select_record(slot, true, T, rem, n_tie, tie_end, 3);
+        *results = select_record(slot, true, T, sh.kept, sh.n_tie, tie_end, is_missing == 0 ? slot.path : 3);
     }
 }
 
@@ -2273,41 +2257,6 @@ __global__ __launch_bounds__(kBlock) void k_list_gather(DataArgs a, ListArgs w) 
     for (u32 f = tid; f < n_f; f += kBlock) {
         const u32 to = s_base + f;
         if (to < w.gather_cap) { gkey[to] = s_fkey[f]; gidx[to] = w.idx[rk.base + s_fidx[f]]; }
-    }
-}
-
-// f(there, key, index) for the entries of the ranking that this wavefront takes: every `stride`-th segment, `cnt` entries each (in
-// LDS), kListDeep rows of two segments at a time with their loads in flight together; called by all lanes, `there` says which hold
-// an entry.
-template <typename F>
-__device__ inline void list_walk_own(const ListArgs& w, const ListRank& rk, const u32* cnt_of, u32 first_seg, u32 stride, F&& f, u32 part = 0, u32 parts = 1) {
-    const u32 lane = threadIdx.x & 63u;
-    for (u32 seg0 = first_seg; seg0 < rk.n_segs; seg0 += 2 * stride) {
-        u32 cnt[2], most = 0;
-        u64 first[2];
-#pragma unroll
-        for (u32 b = 0; b < 2; ++b) {
-            const u32 seg = seg0 + b * stride;
-            cnt[b] = seg < rk.n_segs ? cnt_of[seg] : 0u;
-            first[b] = rk.base + static_cast<u64>(seg) * rk.seg_cap;
-            most = cnt[b] > most ? cnt[b] : most;
-        }
-        for (u32 i0 = 64 * kListDeep * part; i0 < most; i0 += 64 * kListDeep * parts) {              // uniform
-            u32 x[kListDeep][2], e[kListDeep][2];
-#pragma unroll
-            for (u32 d = 0; d < kListDeep; ++d)
-#pragma unroll
-                for (u32 b = 0; b < 2; ++b) {
-                    const u32 i = i0 + 64 * d + lane, last = cnt[b] ? cnt[b] - 1u : 0u;
-                    const u64 at = first[b] + (i < cnt[b] ? i : last);
-                    if (i0 + 64 * d < cnt[b]) { x[d][b] = w.key[at]; e[d][b] = w.idx[at]; }        // uniform
-                }
-#pragma unroll
-            for (u32 d = 0; d < kListDeep; ++d)
-#pragma unroll
-                for (u32 b = 0; b < 2; ++b)
-                    if (i0 + 64 * d < cnt[b]) f(i0 + 64 * d + lane < cnt[b], x[d][b], e[d][b]);    // uniform
-        }
     }
 }
 
@@ -3308,13 +3257,9 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
         FixLoads<LC, 1> loads;
         if (w.write && n_found != 0) list_fix_load<LC, 1>(a, w, 0, idx1, on1, loads);
         if ((ticket >> 20) + 1 == walkers) {               // uniform: the last one
-            bool ranked;
-            if constexpr (LONG) ranked = list_rank_long<LC, PQ, kSettleThreads>(a, w, s_mem.few, f.want, (ticket & 0xFFFFFu) + all, f.bin, win, walkers, results, &nz);
-            else                ranked = list_rank_short<LC, PQ, kSettleThreads>(a, w, s_mem.few, f.want, (ticket & 0xFFFFFu) + all, f.bin, win, walkers, results, &nz);
-            if (!ranked) {
-                list_search<LC, PQ, kSettleThreads>(a, w, sh, results);
-                return;
-            }
+            const u32 n_in = (ticket & 0xFFFFFu) + all;
+            if constexpr (LONG) list_rank_long<LC, PQ, kSettleThreads>(a, w, rk, find.cnt, s_mem.few, f.want, n_in, f.bin, win, walkers, results, &nz);
+            else                list_rank_short<LC, PQ, kSettleThreads>(a, w, rk, find.cnt, s_mem.few, f.want, n_in, f.bin, win, walkers, results, &nz);
         }
         if (w.write && n_found != 0) {                     // uniform over the wavefront
             // The verdict comes from a workgroup that is running once all have posted; if some of them are not even running yet (another

@@ -1,6 +1,7 @@
 """GPU parity of listed windows on lists of millions of entries (2^27 weights and more, one density; 3 2^26 and more are ranked by kernels of their own): bins of thousands of entries, ties in them,
 workgroups that leave.  Against the radix levels, which the oracle anchors at sizes that it can sort; bit for bit."""
 import contextlib
+import time
 
 import pytest
 import torch
@@ -75,11 +76,16 @@ def test_bins_of_tens_of_thousands(scale, d):
     lam = [t * 0.0 for t in ws]
     ref = P.condensa_prune(ws, [d], config={"select_path": 1})
     want = P.select_records(ref["results"])[0]
-    for what in (0, LATE, NO_VERDICT, ASK):
+    for what in (0, LATE, NO_VERDICT, ASK, NO_POSTS, NO_POSTS | NO_VERDICT):
         with forced(what):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
             res = P.condensa_prune(ws, [d])
+            torch.cuda.synchronize()
+            seconds = time.perf_counter() - t0
         got = P.select_records(res["results"])[0]
-        assert all(got[f] == want[f] for f in FIELDS) and got["path"] == 2, (what, got, want)
+        assert all(got[f] == want[f] for f in FIELDS) and got["path"] == (3 if what & NO_POSTS else 2), (what, got, want)
+        assert seconds < 0.5, (what, seconds)              # one workgroup goes over the list, not over the weights (seconds)
         for name in ("theta", "mask"):
             assert all(_same(a, b) for a, b in zip(res[name][0], ref[name][0])), (what, name)
         with forced(what):
