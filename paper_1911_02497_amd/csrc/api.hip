@@ -382,7 +382,8 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
         L.l_gmax = off;    off += align_up(2 * static_cast<size_t>(L.n_slots) * sizeof(u32));
         L.l_masks = off;   off += align_up(3 * static_cast<size_t>(L.n_groups) * sizeof(u32));
         L.l_meet = off;    off += align_up(kMeetWords * sizeof(u32));
-        L.l_gather_cap = (1u << 20) / L.n_slots > kListGather ? kListGather : ((1u << 20) / L.n_slots < kListRanked ? kListRanked : (1u << 20) / L.n_slots);
+        const u32 gather = long_list && !per_tensor ? kListGatherLong : kListGather;
+        L.l_gather_cap = (1u << 20) / L.n_slots > gather ? gather : ((1u << 20) / L.n_slots < kListRanked ? kListRanked : (1u << 20) / L.n_slots);
         L.l_gkey = off;
         L.l_posted = long_list ? L.l_gkey : L.l_post + 256;
         L.zero_bytes = off - L.zero_begin + (long_list ? align_up(list_post_bytes(N)) : 0);

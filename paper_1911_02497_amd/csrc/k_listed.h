@@ -48,6 +48,10 @@ constexpr int kListBins = 256;                   // bins over a window
 static_assert(kListBins == 1 << 8, "list_window: 32 - 8 bits");
 constexpr u32 kListRanked = 2048;                // gathered entries that are held in LDS
 constexpr u32 kListGather = 1u << 18;            // gathered entries of a ranking at most; with more (ties) it is left open
+// ... of one GLOBAL ranking whose list is long: as many as values of binary16 have equals there (N / 2100 at the most); left open, they cost two more sweeps (1.2 G
+// such weights, 380 thousand ties: L-C step 12 970 -> 3 990 us, pruned 6 550 -> 1 895; such calls' workspaces
+// have room for the sampled window, which is more).
+constexpr u32 kListGatherLong = 1u << 20;
 constexpr u32 kListLine = 32;                    // words of a 128-byte line
 // Lists of at least so many elements are long: from there on their bins outgrow kListFound (201 M weights: 4.1 thousand entries at the most), and posting to the
 // larger arrays costs up to 8 us: pruning 151 M weights 250 us short and 258 long, 189 M 302 and 309, L-C step 517 and 524, 624 and 630; 208 M 338 either way.
@@ -2875,8 +2879,12 @@ __device__ inline bool list_state(const ListArgs& w, u32 s, ListState* st) {
     return true;
 }
 
+// Long lists: gathered ties are counted by chunk from where they lie, not by another sweep over the weights (604 M weights in binary16, 190 thousand ties, L-C step 2 855 ->
+// 2 010 us; 302 M 1 490 -> 1 055), unless so many meet in a chunk that their updates take turns (4.7 M weights in E4M3, hundreds in a chunk: 212 us swept, 295 so).
+__device__ inline bool list_ties_counted(const DataArgs& a, const ListState& st) { return (st.flags & kStateTied) && st.n <= 16 * a.n_chunks; }
+
 // `words`: kFallbackWords of LDS.  `tied`: some suspected ties are ties; `search`: some of those have to be searched.
-template <bool LC, bool VEC, bool PQ, int THREADS>
+template <bool LC, bool VEC, bool PQ, bool LONG, int THREADS>
 __device__ inline void list_fallback(const DataArgs& a, const ListArgs& w, Meet& m, FallbackShared& sh, u32* words, condensa_select* results, int n_groups,
                                      int vec_out, bool tied, bool search) {
     const u32 tid = threadIdx.x, lane = tid & 63u;
@@ -2977,7 +2985,18 @@ __device__ inline void list_fallback(const DataArgs& a, const ListArgs& w, Meet&
         meet(m);
     }
 
-    if (search || ld_dev(&w.fb->ties) != 0) {              // ---- ties per chunk
+    bool counted = false;
+    if constexpr (LONG) {                                  // ---- ties per chunk, where they lie gathered (one ranking)
+        ListState st;
+        counted = search && list_state(w, 0, &st) && list_ties_counted(a, st);         // uniform over all workgroups
+        if (counted) {
+            for (u64 c = c0 + tid; c < c1; c += THREADS) st_dev(&a.tiecnt[c], 0u);
+            meet(m);
+            for (u32 i = m.rank * THREADS + tid; i < st.n; i += m.size * THREADS) add_dev(&a.tiecnt[ld_dev(w.gidx + i) / kChunk], 1u);
+            meet(m);
+        }
+    }
+    if (!counted && (search || ld_dev(&w.fb->ties) != 0)) {              // ---- ties per chunk
         u32 cur = 0xFFFFFFFFu, mask = 0;
         for_chunks<LC, VEC, THREADS>(a, c0, c1, wanted(w.tie_of), [&](u64 c, const auto& ck) {
             const u32 g = group_of(c);
@@ -3019,13 +3038,31 @@ __device__ inline void list_fallback(const DataArgs& a, const ListArgs& w, Meet&
             u32 cum = 0;
             if (tid == 0) { sh.pick[0] = static_cast<u32>(cb); sh.pick[1] = 0; sh.pick[2] = 0; }           // (found below; never out of range)
             __syncthreads();
-            for (u64 b = cb; b < ce && cum < st.rank; b += THREADS) {    // uniform
-                const u64 c = b + tid;
-                const u32 x = c < ce ? ld_dev(&cnt[c]) : 0u;
-                u32 total;
-                const u32 upto = cum + wg_incl_scan_u32<THREADS>(x, sh.wave, &total);
-                if (upto - x < st.rank && st.rank <= upto) { sh.pick[0] = static_cast<u32>(c); sh.pick[1] = st.rank - (upto - x); }
-                cum += total;
+            if constexpr (LONG) {
+                constexpr u32 kAtOnce = 8;                 // chunks of a thread
+                for (u64 b = cb; b < ce && cum < st.rank; b += kAtOnce * THREADS) {    // uniform
+                    u32 x[kAtOnce], sum = 0, total;
+#pragma unroll
+                    for (u32 i = 0; i < kAtOnce; ++i) { const u64 c = b + kAtOnce * tid + i; x[i] = ld_dev(&cnt[c < ce ? c : ce - 1]); }
+#pragma unroll
+                    for (u32 i = 0; i < kAtOnce; ++i) { if (b + kAtOnce * tid + i >= ce) x[i] = 0; sum += x[i]; }
+                    u32 before = cum + wg_incl_scan_u32<THREADS>(sum, sh.wave, &total) - sum;
+#pragma unroll
+                    for (u32 i = 0; i < kAtOnce; ++i) {
+                        if (before < st.rank && st.rank <= before + x[i]) { sh.pick[0] = static_cast<u32>(b + kAtOnce * tid + i); sh.pick[1] = st.rank - before; }
+                        before += x[i];
+                    }
+                    cum += total;
+                }
+            } else {
+                for (u64 b = cb; b < ce && cum < st.rank; b += THREADS) {              // uniform
+                    const u64 c = b + tid;
+                    const u32 x = c < ce ? ld_dev(&cnt[c]) : 0u;
+                    u32 total;
+                    const u32 upto = cum + wg_incl_scan_u32<THREADS>(x, sh.wave, &total);
+                    if (upto - x < st.rank && st.rank <= upto) { sh.pick[0] = static_cast<u32>(c); sh.pick[1] = st.rank - (upto - x); }
+                    cum += total;
+                }
             }
             __syncthreads();
             const u64 c = sh.pick[0];
@@ -3157,7 +3194,7 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_settle(DataArgs a, L
     if (!tied && w.fb->apply == 0) return;                 // the same in every workgroup
     Meet m;
     if (!meet_join(m, w.meet, fs.pick)) return;
-    list_fallback<false, VEC, false, kSettleThreads>(a, w, m, fs, s_words, results, n_groups, vec_out, tied, search);
+    list_fallback<false, VEC, false, false, kSettleThreads>(a, w, m, fs, s_words, results, n_groups, vec_out, tied, search);
 }
 
 // One ranking: everything after the sweep in one launch (k_list_hist, k_list_gather and k_list_settle took 22 us for the L-C step of
@@ -3342,7 +3379,7 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
     }
     if (first && nnz && gather && tid == 0) __hip_atomic_fetch_add(w.nnz_out, ld_dev64(&a.ctl->nnz_delta), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const bool tied = gather;
-    list_fallback<LC, VEC, PQ, kSettleThreads>(a, w, m, fs, s_mem.words, results, 1, vec_out, tied, tied && f.want < f.n_in);
+    list_fallback<LC, VEC, PQ, LONG, kSettleThreads>(a, w, m, fs, s_mem.words, results, 1, vec_out, tied, tied && f.want < f.n_in);
 }
 
 }  // namespace condensa
