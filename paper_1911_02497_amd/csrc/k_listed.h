@@ -3287,7 +3287,7 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
         const u32 ticket = s_found[kWaves], base = (ticket & 0xFFFFFu) + before;
         if (lane < n_found) post(base + lane, fkey[lane], fidx[lane]);
         if (tid == 0) st_dev(w.range + blockIdx.x, kRangeKnown | (all << kRangeBits) | ((ticket & 0xFFFFFu) < kPosted ? ticket & 0xFFFFFu : kPosted));
-        queue.template fix<LC, PQ>(a, w, 0, &nz);
+        if constexpr (!LONG) queue.template fix<LC, PQ>(a, w, 0, &nz);
         // what settling its own entries will read is on its way meanwhile
         const u32 idx1[1] = {lane < n_found ? fidx[lane] : 0u};
         bool on1[1] = {lane < n_found};
@@ -3298,6 +3298,9 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
             if constexpr (LONG) list_rank_long<LC, PQ, kSettleThreads>(a, w, rk, find.cnt, s_mem.few, f.want, n_in, f.bin, win, walkers, results, &nz);
             else                list_rank_short<LC, PQ, kSettleThreads>(a, w, rk, find.cnt, s_mem.few, f.want, n_in, f.bin, win, walkers, results, &nz);
         }
+        // Long lists have hundreds of corrections for a wavefront, 40 to 80 us where its estimate is poor: the workgroup that ranks does its own last, or the
+        // others, done with theirs, hear nothing for so long that they leave (604 M weights in rows of very different sizes, L-C step 2 205 -> 2 033 us).
+        if constexpr (LONG) queue.template fix<LC, PQ>(a, w, 0, &nz);
         if (w.write && n_found != 0) {                     // uniform over the wavefront
             // The verdict comes from a workgroup that is running once all have posted; if some of them are not even running yet (another
             // launch holds the chip), this one does not keep them from it for long.

@@ -155,6 +155,24 @@ def test_ties_do_not_set_the_time():
     assert this < 1.2 * other, (this, other)
 
 
+def _rows_differ(n, scale):
+    """n matrices of rows whose sizes are spread by e^scale to either side, and multipliers."""
+    g, by_row = [torch.Generator(device=DEV).manual_seed(s) for s in (3, 7)]
+    ws = [torch.empty((4096, 4608), dtype=torch.float32, device=DEV).normal_(0.0, 0.02, generator=g) for _ in range(n)]
+    lam = [torch.empty((4096, 4608), dtype=torch.float32, device=DEV).normal_(0.0, 6e-6, generator=g) for _ in range(n)]
+    for w in ws:
+        w *= torch.exp(scale * torch.randn((4096, 1), device=DEV, generator=by_row))
+    return ws, lam
+
+
+@pytest.mark.timeout(300)
+def test_workgroups_wait_for_the_one_that_ranks():
+    """Hundreds of thousands of corrections: the workgroup that ranks did its own first, the others left meanwhile, and it settled their entries one after the
+    other: 1.15 times the step of rows alike, 1.06 where it ranks at once."""
+    alike, this = [_step_time(*_rows_differ(32, scale)) for scale in (0.0, 1.0)]
+    assert this < 1.1 * alike, (this, alike)
+
+
 # a selection that is a sweep of its own: either side of the lines between the two windows, and a workspace that has room for the lists alone
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("op,n", [("lc", (3 << 26) - 1), ("lc", 3 << 26), ("prune", (1 << 29) - 1), ("prune", (1 << 29) + 3)])
