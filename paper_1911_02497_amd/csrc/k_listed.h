@@ -582,7 +582,9 @@ static_assert(sizeof(BeginSampleArgs) + sizeof(ListArgs) <= 3584, "kernel argume
 // draws).  That holds for draws from something like a normal distribution.  Where they are not -- a model close to its compressed
 // form, whose threshold lies at a gap; weights on a grid; workgroups without such a rank in their sample -- the mean can lie where
 // no keys are, the interval can end before them, or a few draws far off stretch it.  So the share of the draws beyond either end
-// has to be what it is in a normal distribution, give or take three of its deviations (and not nothing).  Else order
+// has to be what it is in a normal distribution, give or take three of its deviations (and not nothing).  Long lists (elsewhere a wrong decision more costs less than the test): so has the share above the mean.
+// Where rows differ in size, a workgroup with many large ones has more keys around the threshold too, and the mean lies 2 to 3 of its deviations too low; the median
+// does not (1.2 G such weights, a million wrong decisions less: L-C step 4 104 -> 3 850 us, pruned 1 827 -> 1 775; 604 M 2 033 -> 1 950).  Else order
 // statistics W/2 -+ z sqrt(W)/2, which assume nothing, take its place.  Elsewhere they would leave windows 1.3 times as wide for 256
 // workgroups and twice for 32, estimates off by 1.25 times as much, and take 1.8 us to find.
 // L-C step of VGG-19 whose kept weights stand apart from the others, at their share: 262 us by the mean alone, 103 so.
@@ -693,10 +695,17 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
         const u32 above = beyond & 0x3FFu, below = (beyond >> 10) & 0x3FFu, equal = beyond >> 20;
         const u32 fewer = above < below ? above : below, more = above < below ? below : above;
         const bool even = static_cast<float>(fewer) >= n * least_beyond && static_cast<float>(more) <= n * most_beyond;
+        bool skewed = false;
+        if (LOW != 0 && w.gather_cap > kListGather) {    // uniform: one GLOBAL ranking, a long list
+            u32 over = 0;                        // above their mean
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) over += static_cast<u32>(__popcll(__ballot(drew[q] && static_cast<float>(static_cast<int>((v[2][q] & ~kListCrowded) - ref)) > mean[2])));
+            skewed = fabsf(static_cast<float>(over) - 0.5f * n) > 0.75f * sqrtf(n);                  // 2.5 deviations of what it is in a normal distribution
+        }
         const bool alike = open || !even || equal >= (W < 64 ? 5u : 9u);         // the last: weights on a grid (3 are equal where they are not)
         if (alike) marks |= kListUneven;
         const bool all_equal = !(var > 0.0f);
-        if (!open && (even || all_equal)) {
+        if (!open && ((even && !skewed) || all_equal)) {
             auto at = [&](float d) {             // a key; ref + d may lie outside
                 const float least = -static_cast<float>(ref), most = static_cast<float>(0x7FFFFFFFu - ref);
                 return d <= least ? 0u : (d >= most ? 0x7FFFFFFFu : ref + static_cast<u32>(static_cast<int>(d)));
