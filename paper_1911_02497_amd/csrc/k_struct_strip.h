@@ -16,8 +16,8 @@
 //      in a few passes over the stored keys, meeting in between (Meet), and settle in the same way.
 // Against aggregates, list and apply sweep, us a call: 688 128 blocks of 8x8 in 96 matrices 134 -> 98 (traced: 9, 77 and 16), 270 400 of 5x5 51.6 -> 39
 // (9, 18 and 13), 786 thousand of 4x4 69 -> 49, 172 thousand of 16x16 122 -> 101, 2.7 M of 5x5 304 -> 203, 16.8 M of 4x4 890 -> 669.
-// Weights pruned before (2^20 blocks of 4x4, nine tenths of them zero, the threshold among them) 116 -> 91, two scales with the threshold between them
-// 76 -> 84.
+// Weights pruned before (2^20 blocks of 4x4, nine tenths of them zero, the threshold among them) 114 -> 87.  Slower where windows hold a gap: two scales in any order with the
+// threshold between them 74.4 -> 82.4, halves 74.6 -> 79.7, a quarter of blocks of which half are larger 78.6 -> 87.2, half of the blocks that are not zero 80.8 -> 82.7.
 // Section 3.1 (the schemes aggregate blocks), Table 1 (BlockPrune: blocks of any dimensionality and a given size).
 #pragma once
 #include "k_listed.h"
@@ -37,6 +37,8 @@ constexpr u32 kStripArea = 256;                  // elements of a block at most:
 constexpr u32 kStripCopies = 4;                  // counters of a bin, chosen by strip
 constexpr u32 kStripMostSlots = 1024;            // places of a bin at most, the same number for each counter
 constexpr u32 kStripMostBins = 2048;             // every workgroup of k_strip_resolve reads all counters (with 8192 bins, 2.7 M blocks took it 86 us)
+constexpr u32 kStripGather = 256;                // blocks that the fallback ranks by all pairs at most (836 took 110 us, a pass over 16.8 M keys 37)
+static_assert(kStripGather <= kStripMostSlots);
 constexpr u32 kStripAboves = 64;                 // counters of the blocks above the window, a line each
 constexpr u32 kStripTensors = 1024;              // tensors of a call at most: a wavefront looks at all their starts
 constexpr u32 kStripLanes = 4, kStripSample = kStripBegin / kStripLanes;           // lanes that share a sampled block, and blocks of a workgroup at once
@@ -115,7 +117,7 @@ __device__ inline u32 strip_shift(const ListWin& w, u32 log_bins) {
 __device__ inline u32 strip_mid(const ListWin& w) { return win_crowded(w) ? w.hi + 1u : w.mid; }
 // Where the draws say that the keys crowd at a few places (equal ones, a gap), too many would meet in a bin: a few of its places are no use,
 // and its counters would be what the sweep waits for (2^20 blocks of 4x4 in two scales, the threshold between them: 127 us
-// listed, 84 now).
+// listed, 82 now).
 __device__ inline bool strip_listed(const ListWin& w) { return !win_crowded(w) && !win_uneven(w); }
 
 // ---- sample ----------------------------------------------------------------------------------------------
@@ -166,32 +168,32 @@ __device__ inline void strip_sample(const ListArgs& w, u32 W, u32 me, u32 rounds
     const float all = static_cast<float>(count), ks = static_cast<float>(k) / static_cast<float>(F) * all;
     const u64 tag = static_cast<u64>(w.tag) << 32;
     for (u32 i = tid / kStripLanes; i < count; i += kStripSample) {      // uniform
-    const u32 key = s_key[i];
-    u32 higher = 0, same = 0, lower = 0;                   // lower: equal ones before this
+        const u32 key = s_key[i];
+        u32 higher = 0, same = 0, lower = 0;                   // lower: equal ones before this
 #pragma unroll 8
-    for (u32 e0 = 0; e0 < count; e0 += 4 * kStripLanes) {
-        const u32 e = e0 + 4 * mine;
-        const uint4 x = *reinterpret_cast<const uint4*>(s_key + e);
-        higher += (x.x > key ? 1u : 0u) + (x.y > key ? 1u : 0u) + (x.z > key ? 1u : 0u) + (x.w > key ? 1u : 0u);
-        same += (x.x == key ? 1u : 0u) + (x.y == key ? 1u : 0u) + (x.z == key ? 1u : 0u) + (x.w == key ? 1u : 0u);
-        lower += (x.x == key && e < i ? 1u : 0u) + (x.y == key && e + 1 < i ? 1u : 0u) + (x.z == key && e + 2 < i ? 1u : 0u) + (x.w == key && e + 3 < i ? 1u : 0u);
-    }
+        for (u32 e0 = 0; e0 < count; e0 += 4 * kStripLanes) {
+            const u32 e = e0 + 4 * mine;
+            const uint4 x = *reinterpret_cast<const uint4*>(s_key + e);
+            higher += (x.x > key ? 1u : 0u) + (x.y > key ? 1u : 0u) + (x.z > key ? 1u : 0u) + (x.w > key ? 1u : 0u);
+            same += (x.x == key ? 1u : 0u) + (x.y == key ? 1u : 0u) + (x.z == key ? 1u : 0u) + (x.w == key ? 1u : 0u);
+            lower += (x.x == key && e < i ? 1u : 0u) + (x.y == key && e + 1 < i ? 1u : 0u) + (x.z == key && e + 2 < i ? 1u : 0u) + (x.w == key && e + 3 < i ? 1u : 0u);
+        }
 #pragma unroll
-    for (u32 d = 1; d < kStripLanes; d *= 2) {
-        higher += __shfl_xor(higher, static_cast<int>(d), 64);
-        same += __shfl_xor(same, static_cast<int>(d), 64);
-        lower += __shfl_xor(lower, static_cast<int>(d), 64);
-    }
+        for (u32 d = 1; d < kStripLanes; d *= 2) {
+            higher += __shfl_xor(higher, static_cast<int>(d), 64);
+            same += __shfl_xor(same, static_cast<int>(d), 64);
+            lower += __shfl_xor(lower, static_cast<int>(d), 64);
+        }
 #pragma unroll
-    for (u32 which = 0; which < 3; ++which) {
-        float x = which == 0 ? floorf(ks - 1.0f) : (which == 1 ? ceilf(ks + 1.0f) + 1.0f : floorf(ks + 0.5f));
-        if (which == 2) x = x < 1.0f ? 1.0f : (x > all ? all : x);
-        const u32 want = x >= 1.0f && x <= all ? static_cast<u32>(x) : 0u;
-        u64* const to = &w.local[static_cast<u64>(which) * w.n_local + me];
-        if (want == 0) { if (tid == 0) st_dev64(to, tag | kSampleNone); }
-        // so many of a hundred equal: their bins would have no room for them, and their counters no time
-        else if (mine == 0 && lower == 0 && higher < want && want <= higher + same) st_dev64(to, tag | key | (same >= 4 && same * 64 >= count ? kListCrowded : 0u));
-    }
+        for (u32 which = 0; which < 3; ++which) {
+            float x = which == 0 ? floorf(ks - 1.0f) : (which == 1 ? ceilf(ks + 1.0f) + 1.0f : floorf(ks + 0.5f));
+            if (which == 2) x = x < 1.0f ? 1.0f : (x > all ? all : x);
+            const u32 want = x >= 1.0f && x <= all ? static_cast<u32>(x) : 0u;
+            u64* const to = &w.local[static_cast<u64>(which) * w.n_local + me];
+            if (want == 0) { if (tid == 0) st_dev64(to, tag | kSampleNone); }
+            // so many of a hundred equal: their bins would have no room for them, and their counters no time
+            else if (mine == 0 && lower == 0 && higher < want && want <= higher + same) st_dev64(to, tag | key | (same >= 4 && same * 64 >= count ? kListCrowded : 0u));
+        }
     }
 }
 
@@ -557,7 +559,6 @@ __device__ inline void strip_rewrite(const StructArgs& a, const StripArgs& s, co
     }
 }
 
-// Structure mask, kept ids and corrections of blocks id0 .. id1 - 1, of whose predecessors `before` are kept.
 __device__ inline void strip_keys(const StructArgs& a, u64 i0, u64 (&key)[kMaskPer]) {       // of four neighbours; those that there are not read 0
     if (i0 + kMaskPer <= a.F) {
         const ulonglong2 x = *reinterpret_cast<const ulonglong2*>(a.keys + i0), y = *reinterpret_cast<const ulonglong2*>(a.keys + i0 + 2);
@@ -574,7 +575,7 @@ __device__ inline int strip_tensor_of(const StructArgs& a, u64 u) {
     for (u32 t0 = 0; t0 < n; t0 += 64) upto += static_cast<u32>(__popcll(__ballot(t0 + lane < n && a.td[t0 + lane < n ? t0 + lane : 0].struct_start <= u)));
     return static_cast<int>(upto) - 1;
 }
-// `key`: strip_keys of this thread's first blocks, from id0 rounded down to a multiple of four; t0: id0's tensor.
+// Structure mask, kept ids and corrections of blocks id0 .. id1 - 1, of whose predecessors `before` are kept.  `key`: strip_keys of this thread's first blocks, from id0 rounded down to a multiple of four; t0: id0's tensor.
 template <bool REWRITE>
 __device__ inline void strip_settle(const StructArgs& a, const StripArgs& s, StripShared& sh, const StripFound& f, u32 mid, u64 id0, u64 id1, u32 before, int t0,
                                     u64 (&key)[kMaskPer]) {
@@ -646,16 +647,60 @@ __device__ inline void strip_record(const StructArgs& a, const StripArgs& s, con
     *s.results = out;
 }
 
+// The last block kept of n in LDS, the want-th from the top.
+__device__ inline StripFound strip_rank(StripShared& sh, u32 n, u32 want, u64 n_all) {
+    const u32 tid = threadIdx.x;
+    for (u32 i0 = 0; i0 < n; i0 += kResolveThreads / 4) {  // four threads to an entry
+        const u32 i = i0 + tid / 4;
+        const u64 key = sh.key[i < n ? i : 0];
+        const u32 id = sh.id[i < n ? i : 0];
+        u32 higher = 0, same = 0, lower = 0;
+        for (u32 e = tid % 4; e < n; e += 4) {
+            const u64 o = sh.key[e];
+            higher += o > key ? 1u : 0u;
+            same += o == key ? 1u : 0u;
+            lower += o == key && sh.id[e] < id ? 1u : 0u;
+        }
+#pragma unroll
+        for (int d = 1; d < 4; d *= 2) {
+            higher += __shfl_xor(higher, d, 64);
+            same += __shfl_xor(same, d, 64);
+            lower += __shfl_xor(lower, d, 64);
+        }
+        if (i < n && tid % 4 == 0 && higher < want && want <= higher + same && lower == want - higher - 1) {       // the last one kept: one thread
+            sh.T = key;
+            sh.rem = want - higher;
+            sh.n_tie = same;
+            sh.tie_end = want - higher == same ? n_all : static_cast<u64>(id) + 1;
+        }
+    }
+    __syncthreads();
+    return StripFound{sh.T, sh.rem, sh.n_tie, sh.tie_end};
+}
+
 // What the places of the bins do not tell: all workgroups that are running, over all keys.  A pass counts the keys of an interval in
-// kStripPassBins bins and keeps every bin's greatest and least key, so a bin of equal keys ends the search.
+// kStripPassBins bins and keeps every bin's greatest and least key, so a bin of equal keys ends the search.  One of few keys too: they are gathered, and everybody
+// ranks them (2^20 blocks of 4x4 in two scales, the threshold at the gap between them: two
+// passes and two meetings less, and the counters of the bins are not looked at where none were filled: the call 92.3 -> 82.4 us).
 __device__ inline void strip_fallback(const StructArgs& a, const StripArgs& s, StripShared& sh, const ListWin& win) {
     const u32 tid = threadIdx.x;
     Meet m;
     if (!meet_join(m, s.meet, sh.wave)) return;
     const u64 i0 = a.F * m.rank / m.size, i1 = a.F * (m.rank + 1) / m.size, k = a.slots[0].k;
     u64 lo = static_cast<u64>(win.lo) << 32, hi = (static_cast<u64>(win.hi) << 32) | 0xFFFFFFFFull, rank = 0;          // rank 0: the interval is a guess
-    u32 tie_here = 0, above_here = 0;
+    u32 tie_here = 0, above_here = 0, kept_before = 0;     // kept_before: of the blocks before this workgroup's share
+    bool gathered = false;
     StripFound f{0, 0, 0, 0};
+    auto share = [&](auto&& g) {                           // g(block, key) for this workgroup's, several loads at a time
+        constexpr int kAtOnce = 8;
+        for (u64 base = i0; base < i1; base += kAtOnce * kResolveThreads) {
+            u64 there[kAtOnce];
+#pragma unroll
+            for (int j = 0; j < kAtOnce; ++j) { const u64 i = base + j * kResolveThreads + tid; there[j] = a.keys[i < i1 ? i : base]; }
+#pragma unroll
+            for (int j = 0; j < kAtOnce; ++j) { const u64 i = base + j * kResolveThreads + tid; if (i < i1) g(i, there[j]); }
+        }
+    };
     for (u32 pass = 0;; ++pass) {                          // uniform over all workgroups; at most eight
         if (pass == 32) return;
         u32* const set = s.pass + pass % 3 * kStripPassWords;
@@ -669,8 +714,7 @@ __device__ inline void strip_fallback(const StructArgs& a, const StripArgs& s, S
         for (u32 i = tid; i < kStripPassBins; i += kResolveThreads) { sh.cnt[i] = 0; sh.most[i] = 0; sh.leastc[i] = 0; }
         __syncthreads();
         u32 above = 0;
-        for (u64 i = i0 + tid; i < i1; i += kResolveThreads) {
-            const u64 key = a.keys[i];
+        share([&](u64, u64 key) {
             if (key > hi) ++above;
             else if (key >= lo) {
                 const u32 bin = static_cast<u32>((key - lo) >> shift);
@@ -678,7 +722,7 @@ __device__ inline void strip_fallback(const StructArgs& a, const StripArgs& s, S
                 atomicMax(reinterpret_cast<unsigned long long*>(&sh.most[bin]), static_cast<unsigned long long>(key));
                 atomicMax(reinterpret_cast<unsigned long long*>(&sh.leastc[bin]), static_cast<unsigned long long>(~key));
             }
-        }
+        });
         u32 above_all;
         wg_incl_scan_u32<kResolveThreads>(above, sh.wave, &above_all);
         for (u32 i = tid; i < kStripPassBins; i += kResolveThreads) {
@@ -715,7 +759,8 @@ __device__ inline void strip_fallback(const StructArgs& a, const StripArgs& s, S
         __syncthreads();
         lo = sh.a; hi = sh.b; rank = sh.rank;
         const bool done = lo == hi;
-        if (done) {
+        gathered = !done && sh.n <= kStripGather;
+        if (done || gathered) {
             f.T = lo; f.rem = static_cast<u32>(rank); f.n_tie = sh.n;
             u32 higher = 0;                                // this share's, in the bins above
             for (u32 i = tid; i < kStripPassBins; i += kResolveThreads) if (i > sh.bin) higher += sh.cnt[i];
@@ -724,33 +769,60 @@ __device__ inline void strip_fallback(const StructArgs& a, const StripArgs& s, S
             tie_here = sh.cnt[sh.bin];
         }
         __syncthreads();
+        if (gathered) {                                    // the next pass's set is cleared; one of its spare words counts
+            u32* const n_there = s.pass + (pass + 1) % 3 * kStripPassWords + 5 * kStripPassBins + 1;
+            if (tid == 0) {
+                st_dev(s.share + m.rank, above_here);
+                sh.n_queue[0] = tie_here ? add_dev(n_there, tie_here) : 0u;
+            }
+            __syncthreads();
+            if (tie_here) share([&](u64 i, u64 key) {
+                if (key < lo || key > hi) return;
+                const u32 to = atomicAdd(&sh.n_queue[0], 1u);            // f.n_tie of them
+                st_dev64(s.key + to, key);
+                st_dev(s.id + to, static_cast<u32>(i));
+            });
+            meet(m);
+            for (u32 i = tid; i < f.n_tie; i += kResolveThreads) { sh.key[i] = ld_dev64(s.key + i); sh.id[i] = ld_dev(s.id + i); }
+            u32 before = 0;
+            for (u32 i = tid; i < m.rank; i += kResolveThreads) before += ld_dev(s.share + i);
+            __syncthreads();
+            const u32 n = f.n_tie;
+            f = strip_rank(sh, n, f.rem, a.slots[0].n);
+            for (u32 i = tid; i < n; i += kResolveThreads) before += sh.id[i] < i0 && (sh.key[i] > f.T || (sh.key[i] == f.T && sh.id[i] < f.tie_end)) ? 1u : 0u;
+            wg_incl_scan_u32<kResolveThreads>(before, sh.wave, &kept_before);
+            break;
+        }
         if (done) break;
     }
-    if (tid == 0) {
-        st_dev(s.share + m.rank, above_here);
-        st_dev(s.share + kStripResolveGrid + m.rank, tie_here);
-    }
-    meet(m);
-    u32 above = 0, ties = 0, above_before, ties_before;
-    for (u32 i = tid; i < m.rank; i += kResolveThreads) { above += ld_dev(s.share + i); ties += ld_dev(s.share + kStripResolveGrid + i); }
-    wg_incl_scan_u32<kResolveThreads>(above, sh.wave, &above_before);
-    wg_incl_scan_u32<kResolveThreads>(ties, sh.wave, &ties_before);
-    f.tie_end = a.slots[0].n;
-    if (f.rem < f.n_tie) {                                 // the last tie kept is in one of the shares
-        if (ties_before < f.rem && f.rem <= ties_before + tie_here) {
-            u32 seen = ties_before;
-            for (u64 base = i0; base < i1; base += kResolveThreads) {
-                const u64 i = base + tid;
-                const u32 eq = i < i1 && a.keys[i] == f.T ? 1u : 0u;
-                u32 total;
-                const u32 upto = seen + wg_incl_scan_u32<kResolveThreads>(eq, sh.wave, &total);
-                if (eq && upto == f.rem) st_dev64(s.tie_end, i + 1);
-                seen += total;
-                if (seen >= f.rem) break;                  // uniform
-            }
+    if (!gathered) {
+        if (tid == 0) {
+            st_dev(s.share + m.rank, above_here);
+            st_dev(s.share + kStripResolveGrid + m.rank, tie_here);
         }
         meet(m);
-        f.tie_end = ld_dev64(s.tie_end);
+        u32 above = 0, ties = 0, above_before, ties_before;
+        for (u32 i = tid; i < m.rank; i += kResolveThreads) { above += ld_dev(s.share + i); ties += ld_dev(s.share + kStripResolveGrid + i); }
+        wg_incl_scan_u32<kResolveThreads>(above, sh.wave, &above_before);
+        wg_incl_scan_u32<kResolveThreads>(ties, sh.wave, &ties_before);
+        f.tie_end = a.slots[0].n;
+        if (f.rem < f.n_tie) {                                 // the last tie kept is in one of the shares
+            if (ties_before < f.rem && f.rem <= ties_before + tie_here) {
+                u32 seen = ties_before;
+                for (u64 base = i0; base < i1; base += kResolveThreads) {
+                    const u64 i = base + tid;
+                    const u32 eq = i < i1 && a.keys[i] == f.T ? 1u : 0u;
+                    u32 total;
+                    const u32 upto = seen + wg_incl_scan_u32<kResolveThreads>(eq, sh.wave, &total);
+                    if (eq && upto == f.rem) st_dev64(s.tie_end, i + 1);
+                    seen += total;
+                    if (seen >= f.rem) break;                  // uniform
+                }
+            }
+            meet(m);
+            f.tie_end = ld_dev64(s.tie_end);
+        }
+        kept_before = above_before + (ties_before < f.rem ? ties_before : f.rem);
     }
     if (m.rank == 0 && tid == 0) strip_record(a, s, f);
     // The blocks decided wrongly may be neighbours (equal ones up to the last tie kept), so everybody takes a few of everywhere.
@@ -781,7 +853,7 @@ __device__ inline void strip_fallback(const StructArgs& a, const StripArgs& s, S
     if (i0 >= i1) return;                                  // uniform
     u64 key[kMaskPer];
     strip_keys(a, (i0 & ~static_cast<u64>(kMaskPer - 1)) + tid * kMaskPer, key);
-    strip_settle<false>(a, s, sh, f, mid, i0, i1, above_before + (ties_before < f.rem ? ties_before : f.rem), strip_tensor_of(a, i0), key);
+    strip_settle<false>(a, s, sh, f, mid, i0, i1, kept_before, strip_tensor_of(a, i0), key);
 }
 
 // Bound by latency: a launch and a chain of some six dependent loads -- the counters, the counters of one thread's bins, the places of the bins
@@ -792,6 +864,10 @@ __global__ __launch_bounds__(kResolveThreads) void k_strip_resolve(StructArgs a,
     const u32 t0 = static_cast<u32>(static_cast<u64>(s.n_tiles) * blockIdx.x / gridDim.x), t1 = static_cast<u32>(static_cast<u64>(s.n_tiles) * (blockIdx.x + 1) / gridDim.x);
     const u64 id0 = s.tiles[t0].x, id1 = s.tiles[t1].x;
     const ListWin win = *s.win;
+    if (!strip_listed(win)) {                              // uniform, the same in every workgroup
+        strip_fallback(a, s, sh, win);
+        return;
+    }
     const u32 bins = 1u << s.log_bins, shift = strip_shift(win, s.log_bins), k = static_cast<u32>(a.slots[0].k), mid = strip_mid(win);
     // what comes before this workgroup's strips, and what lies above the window
     u32 above = tid < kStripAboves ? s.above[tid * kListLine] : 0u, before = 0;
@@ -819,7 +895,7 @@ __global__ __launch_bounds__(kResolveThreads) void k_strip_resolve(StructArgs a,
     wg_incl_scan_u32<kResolveThreads>(above, sh.wave, &above);
     const u32 upto = wg_incl_scan_u32<kResolveThreads>(sum, sh.wave, &inside);
     const u32 r = k - above;                               // wanted among the listed ones, if 1 <= r <= inside
-    if (strip_listed(win) && above < k && upto - sum < r && r <= upto) { sh.a = tid; sh.rank = r - (upto - sum); sh.found = 1; }      // one thread at most
+    if (above < k && upto - sum < r && r <= upto) { sh.a = tid; sh.rank = r - (upto - sum); sh.found = 1; }      // one thread at most
     __syncthreads();
     if (sh.found && tid < 64) {                            // its bins, a lane each
         const u32 bin = bins - 1 - (static_cast<u32>(sh.a) * per + lane), want = sh.rank;
@@ -885,32 +961,7 @@ __global__ __launch_bounds__(kResolveThreads) void k_strip_resolve(StructArgs a,
         return;
     }
     const u32 n = sh.n;
-    for (u32 i0 = 0; i0 < n; i0 += kResolveThreads / 4) {  // four threads to an entry
-        const u32 i = i0 + tid / 4;
-        const u64 key = sh.key[i < n ? i : 0];
-        const u32 id = sh.id[i < n ? i : 0];
-        u32 higher = 0, same = 0, lower = 0;
-        for (u32 e = tid % 4; e < n; e += 4) {
-            const u64 o = sh.key[e];
-            higher += o > key ? 1u : 0u;
-            same += o == key ? 1u : 0u;
-            lower += o == key && sh.id[e] < id ? 1u : 0u;
-        }
-#pragma unroll
-        for (int d = 1; d < 4; d *= 2) {
-            higher += __shfl_xor(higher, d, 64);
-            same += __shfl_xor(same, d, 64);
-            lower += __shfl_xor(lower, d, 64);
-        }
-        if (i < n && tid % 4 == 0 && higher < want && want <= higher + same && lower == want - higher - 1) {       // the last one kept: one thread
-            sh.T = key;
-            sh.rem = want - higher;
-            sh.n_tie = same;
-            sh.tie_end = want - higher == same ? a.slots[0].n : static_cast<u64>(id) + 1;
-        }
-    }
-    __syncthreads();
-    const StripFound f{sh.T, sh.rem, sh.n_tie, sh.tie_end};
+    const StripFound f = strip_rank(sh, n, want, a.slots[0].n);
     if (s.keep_idx) {
         // bins below the estimate's that turn out to be kept, bins from it on that do not, and the threshold's own
         u32 add = bin < mid_bin ? wrong : 0u - wrong;

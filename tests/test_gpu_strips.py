@@ -98,6 +98,25 @@ def test_many_equal_aggregates_and_gaps(kind, block):
         _check([w], block, d, f"{kind} {d}")
 
 
+# the fallback: a threshold at a gap, in a bin that it gathers or beyond; ties there that end inside one of the workgroups' shares
+@pytest.mark.parametrize("copies", [0, 60, 255, 700])
+@pytest.mark.parametrize("block,n", [((4, 4), 200), ((5, 5), 180), ((2, 2), 400)])
+def test_ties_at_a_gap(block, n, copies):
+    rng = np.random.default_rng(copies)
+    big = rng.random(n * n) < 0.5
+    w = rng.standard_normal((n * block[0], n * block[1])).astype(np.float32) * np.where(np.kron(big.reshape(n, n), np.ones(block, bool)), np.float32(1), np.float32(1e-2))
+    k = int(big.sum())
+    blocks = w.reshape(n, block[0], n, block[1]).transpose(0, 2, 1, 3).reshape(n * n, -1)
+    order = np.argsort(-(blocks.astype(np.float64) ** 2).sum(1))
+    same = rng.choice(order[k - 900:k], copies, replace=False)
+    blocks[same] = blocks[order[k - 1]]
+    w = np.ascontiguousarray(blocks.reshape(n, n, *block).transpose(0, 2, 1, 3).reshape(w.shape))
+    for at in (k - copies - 1, k - copies // 2, k - 1, k, k + 1):
+        _check([w], block, (at + 0.25) / (n * n), f"{copies} {at}")
+        with forced(LATE):
+            _check([w], block, (at + 0.25) / (n * n), f"{copies} {at}, late")
+
+
 @pytest.mark.parametrize("block,shapes", [((8, 8), [(512, 1024), (264, 520)]), ((5, 5), [(650, 651), (333, 331)])])
 def test_windows_that_miss(block, shapes):
     arrs = _normal(shapes, 3)

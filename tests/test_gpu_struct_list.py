@@ -61,26 +61,26 @@ def test_long_lists_of_ties(rows, cols, common, share):
         _compare(block_prune(up([w]), 1, 3, d, P.SCOPE_GLOBAL), oracle.block_prune([w], 1, 3, d, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], f"{common} {share} {d}")
 
 
-def _seconds(call):
+def _seconds(call, calls=4):
     call()
     torch.cuda.synchronize()
     best = 1e9
     for _ in range(5):
         t0 = time.perf_counter()
-        for _ in range(4):
+        for _ in range(calls):
             call()
         torch.cuda.synchronize()
-        best = min(best, (time.perf_counter() - t0) / 4)
+        best = min(best, (time.perf_counter() - t0) / calls)
     return best
 
 
-def _time_of(scales, block, density=0.25):
+def _time_of(scales, block, density=0.25, calls=4):
     g = torch.Generator(device=DEV).manual_seed(3)
     s = torch.from_numpy(scales).to(DEV).repeat_interleave(block, 0).repeat_interleave(block, 1)
     w = (torch.empty(s.shape, dtype=torch.float32, device=DEV).normal_(generator=g) * s).contiguous()
     table = P.TensorTable([w])
     res = P.condensa_block_prune(table, block, block, density)
-    return _seconds(lambda: P.condensa_block_prune(table, block, block, density, outputs=res, workspace=res["workspace"]))
+    return _seconds(lambda: P.condensa_block_prune(table, block, block, density, outputs=res, workspace=res["workspace"]), calls)
 
 
 @pytest.mark.parametrize("kind", KINDS[1:] + ["pruned"])
@@ -91,3 +91,12 @@ def test_the_layout_does_not_set_the_time(kind, density):
     for noise and wider windows."""
     alike, this = _time_of(_scales("alike", 1024, 1024), 4, density), _time_of(_scales(kind, 1024, 1024), 4, density)
     assert this < 2.5 * alike, (alike, this)
+
+
+def test_a_gap_costs_little():
+    """Blocks of two sizes in any order, the threshold at the gap between them, which the strips' bins do not resolve: 1.54 times the time of blocks alike where
+    the keys at the gap were found by four passes, 1.36 where they are gathered after the first."""
+    alike = _time_of(_scales("alike", 1024, 1024), 4, 0.5, 40)
+    two = np.where(np.random.default_rng(2).random((1024, 1024)) < 0.5, np.float32(100), np.float32(1))
+    this = _time_of(two, 4, 0.5, 40)
+    assert this < 1.45 * alike, (this, alike)
