@@ -274,3 +274,30 @@ def test_populations_with_fewer_sampling_workgroups_than_they_ask_for(ds):
     paths = [r["path"] for r in P.select_records(res["results"])]
     for j in range(len(ds)):
         assert paths[j * len(arrs):j * len(arrs) + 4] == [2] * 4, paths
+
+
+# A wavefront of the sweep over several densities buffers 256 listed entries of its 1024 elements: runs of them with fewer, as many, one more and
+# all listed, for disjoint windows (masks alone, all outputs, an unaligned tensor) and overlapping ones
+@pytest.mark.parametrize("listed", [255, 256, 257, 1024])
+@pytest.mark.parametrize("ds", [[0.1, 0.4], [0.5, 0.02, 0.1, 0.3], [0.1, 0.1002, 0.4]], ids=str)
+def test_wavefronts_with_many_listed_entries(listed, ds):
+    n, per = 3 << 20, 1024
+    rng = np.random.default_rng(listed)
+    w = rng.standard_normal(n).astype(np.float32)
+    marks = np.sort(np.abs(w))[::-1]
+    T = np.array([marks[int(d * n)] for d in ds], np.float32)
+    for run in range(0, n // per, 97):
+        at = np.zeros(per, np.float32)
+        near = T[np.arange(listed) % T.size].view(np.int32) + rng.permutation(listed).astype(np.int32) * 3 - listed         # distinct, a few hundred steps off
+        at[rng.permutation(per)[:listed]] = near.view(np.float32) * rng.choice(np.array([-1, 1], np.float32), listed)
+        w[run * per:(run + 1) * per] = at
+    ora = oracle.prune([w], ds, P.SCOPE_GLOBAL)
+    for all_outputs in (False, True):
+        res = P.condensa_prune(up([w]), ds, theta=all_outputs, theta_f16=all_outputs)
+        torch.cuda.synchronize()
+        check_prune_against_oracle(res, ora, P.SCOPE_GLOBAL, 1, f"{listed} {all_outputs}")
+    buf = torch.zeros(n + 1, dtype=torch.float32, device=DEV)
+    buf[1:].copy_(torch.from_numpy(w))
+    res = P.condensa_prune([buf[1:]], ds)
+    torch.cuda.synchronize()
+    check_prune_against_oracle(res, ora, P.SCOPE_GLOBAL, 1, f"{listed} not aligned")

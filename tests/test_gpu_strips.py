@@ -58,7 +58,56 @@ def _normal(shapes, seed):
 def test_strips(block, shapes, density):
     arrs = _normal(shapes, sum(block))
     arrs[0][:16, :16] = arrs[0][16:32, 16:32]              # equal blocks
-    _check(arrs, block, density, f"{block} {density}")
+    dev = up(arrs)
+    before = P.condensa_launch_count()
+    _check(arrs, block, density, f"{block} {density}", dev=dev)
+    assert P.condensa_launch_count() - before == 3         # strips it was
+
+
+def _same_as_radix(dev, block, density, launches):
+    ref = P.condensa_block_prune_nd(dev, block, density, P.SCOPE_GLOBAL, fill_keep_idx=True, config={"select_path": 1})
+    before = P.condensa_launch_count()
+    res = P.condensa_block_prune_nd(dev, block, density, P.SCOPE_GLOBAL, fill_keep_idx=True)
+    took = P.condensa_launch_count() - before
+    assert took == 3 if launches == 3 else took > 3, took
+    want, got = [P.select_records(r["results"])[0] for r in (ref, res)]
+    assert all(got[f] == want[f] for f in ("n", "k", "n_gt", "n_tie_kept", "n_tie", "threshold_key", "tie_end")), (got, want)
+    as_bits = {torch.float32: torch.int32, torch.float64: torch.int64}
+    for name in ("theta", "mask", "sumsq", "norms", "keep_idx", "structure_mask"):
+        for a, b in zip(*[(r[name] if isinstance(r[name], list) else [r[name]]) for r in (res, ref)]):
+            assert torch.equal(a.view(as_bits.get(a.dtype, a.dtype)), b.view(as_bits.get(b.dtype, b.dtype))), name
+
+
+# a whole number of strips short of 2^14 (the counts are added up by 64 below, by 512 from there on) and 2^22 blocks (a second round of draws), both, more; then
+# bins with all their places, up to the 2^24 blocks that strips take at most, and one row of them more
+@pytest.mark.parametrize("block,shape,launches", [
+    ((4, 4), (4 * 2047, 4 * 2048), 3), ((4, 4), (4 * 2048, 4 * 2048), 3), ((4, 4), (4 * 2050 - 1, 4 * 2052), 3), ((3, 5), (3 * 2500, 5 * 2111 - 2), 3),
+    ((2, 2), (8192, 8192), 3), ((2, 2), (8194, 8192), 4), ((1, 3), (5000, 3 * 3355 - 1), 3)])
+def test_sizes_where_the_plan_changes(block, shape, launches):
+    g = torch.Generator(device=DEV).manual_seed(shape[0])
+    w = torch.empty(shape, dtype=torch.float32, device=DEV).normal_(0.0, 0.02, generator=g)
+    for density in (0.3, 0.004):
+        _same_as_radix([w], block, density, launches)
+    w.mul_(2048).round_()                                  # many equal aggregates: bins overflow
+    _same_as_radix([w], block, 0.3, launches)
+
+
+@pytest.mark.parametrize("block", [(4, 4), (5, 5)])
+def test_values_that_are_not_numbers(block):
+    g = torch.Generator(device=DEV).manual_seed(9)
+    w = torch.empty((1000, 1200), dtype=torch.float32, device=DEV).normal_(0.0, 0.02, generator=g)
+    w[::23, ::7] = float("nan")
+    w[5::31, ::5] = float("-inf")
+    for density in (0.01, 0.2, 0.5, 0.95):
+        _same_as_radix([w], block, density, 3)
+
+
+@pytest.mark.parametrize("scale", [1e-24, 1e-20, 1e17, 1e21])          # squares that leave binary32, in which samples are summed
+@pytest.mark.parametrize("block,shape", [((8, 8), (1024, 1032)), ((5, 5), (651, 650))])
+def test_scales_beyond_the_sample(block, shape, scale):
+    (a,) = _normal([shape], 8)
+    for density in (0.05, 0.5):
+        _check([a * np.float32(scale)], block, density, f"{scale} {density}")
 
 
 def test_any_alignment_and_missing_outputs():

@@ -1,6 +1,7 @@
 """GPU parity and time of rankings of 4097 to 2^21 structures where the aggregates follow the layout of the matrix: scales that
 go with the column or the row of blocks, two halves far apart, blocks pruned before; against the oracle (bit exact) and against a matrix whose
-blocks are alike."""
+blocks are alike.  Through strips, which such calls take, and through the aggregates' list (k_struct_list.h), which is left with rows, blocks in place, of more than
+256 elements or more than two dimensions, and calls that ask for two sweeps: the last stand for them here."""
 import time
 
 import numpy as np
@@ -15,6 +16,17 @@ from test_gpu_structure import _compare
 pytestmark = pytest.mark.gpu
 
 block_prune = with_form(P.condensa_block_prune, fill_keep_idx=True)
+HOW = {"strips": None, "list": {"fused_sweep": 1}}
+
+
+def _pruned(how, w, b2, b3, d, what, **kw):
+    before = P.condensa_launch_count()
+    res = block_prune(up([w]) if not kw else kw.pop("dev"), b2, b3, d, P.SCOPE_GLOBAL, config=HOW[how], **kw)
+    launches = P.condensa_launch_count() - before
+    k = P.select_records(res["results"])[0]["k"]
+    if 0 < k < res["sumsq"].numel():                       # else nobody has to rank
+        assert launches == 3 if how == "strips" else launches > 4, (what, launches)
+    _compare(res, oracle.block_prune([w], b2, b3, d, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], what)
 
 
 def _scales(kind, rows, cols, seed=1):
@@ -39,18 +51,32 @@ def _scales(kind, rows, cols, seed=1):
 KINDS = ["alike", "first_column_small", "first_column_large", "columns", "rows", "halves"]
 
 
+@pytest.mark.parametrize("how", HOW)
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("density", [0.05, 0.25, 0.5])
-def test_scales_that_follow_the_layout(kind, density):
+def test_scales_that_follow_the_layout(kind, density, how):
     rng = np.random.default_rng(7)
     w = rng.standard_normal((512, 1024)).astype(np.float32) * np.kron(_scales(kind, 128, 256), np.ones((4, 4), np.float32))
-    _compare(block_prune(up([w]), 4, 4, density, P.SCOPE_GLOBAL), oracle.block_prune([w], 4, 4, density, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], kind)
+    _pruned(how, w, 4, 4, density, kind)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_in_place(kind):
+    rng = np.random.default_rng(8)
+    w = rng.standard_normal((300, 700)).astype(np.float32) * np.kron(_scales(kind, 75, 175), np.ones((4, 4), np.float32))
+    for density in (0.05, 0.5):
+        dev = up([w])
+        _pruned("list", w, 4, 4, density, kind, dev=dev, outputs={"_buffers": {"theta": dev}})
+        dev = up([w])                                      # ... as every caller asks for it
+        res = block_prune(dev, 4, 4, density, P.SCOPE_GLOBAL, outputs={"_buffers": {"theta": dev}})
+        _compare(res, oracle.block_prune([w], 4, 4, density, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], kind)
 
 
 @pytest.mark.parametrize("rows,cols", [(128, 256), (300, 301), (1024, 515)])
 @pytest.mark.parametrize("common", [0.0, 0.5, 3.0])          # many equal aggregates at one end of the list, or in its middle
 @pytest.mark.parametrize("share", [0.4, 0.97])
-def test_long_lists_of_ties(rows, cols, common, share):
+@pytest.mark.parametrize("how", HOW)
+def test_long_lists_of_ties(rows, cols, common, share, how):
     rng = np.random.default_rng(rows)
     w = rng.uniform(0.4, 2.0, (rows, cols * 3)).astype(np.float32)
     same = np.repeat(rng.random((rows, cols)) < share, 3, axis=1)
@@ -58,7 +84,7 @@ def test_long_lists_of_ties(rows, cols, common, share):
     tied = float(same.mean())
     for d in (0.3 * (1 - tied), 1 - tied - 1.5 / (rows * cols), 1 - tied, 1 - 0.7 * tied, 0.6 * tied, tied, 1.0 - 0.5 / (rows * cols)):
         d = min(max(d, 0.0), 1.0)
-        _compare(block_prune(up([w]), 1, 3, d, P.SCOPE_GLOBAL), oracle.block_prune([w], 1, 3, d, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], f"{common} {share} {d}")
+        _pruned(how, w, 1, 3, d, f"{common} {share} {d}")
 
 
 def _seconds(call, calls=4):
@@ -74,22 +100,23 @@ def _seconds(call, calls=4):
     return best
 
 
-def _time_of(scales, block, density=0.25, calls=4):
+def _time_of(scales, block, density=0.25, calls=4, how="strips"):
     g = torch.Generator(device=DEV).manual_seed(3)
     s = torch.from_numpy(scales).to(DEV).repeat_interleave(block, 0).repeat_interleave(block, 1)
     w = (torch.empty(s.shape, dtype=torch.float32, device=DEV).normal_(generator=g) * s).contiguous()
     table = P.TensorTable([w])
-    res = P.condensa_block_prune(table, block, block, density)
-    return _seconds(lambda: P.condensa_block_prune(table, block, block, density, outputs=res, workspace=res["workspace"]), calls)
+    res = P.condensa_block_prune(table, block, block, density, config=HOW[how])
+    return _seconds(lambda: P.condensa_block_prune(table, block, block, density, outputs=res, workspace=res["workspace"], config=HOW[how]), calls)
 
 
 @pytest.mark.parametrize("kind", KINDS[1:] + ["pruned"])
 @pytest.mark.parametrize("density", [0.25, 0.5])
-def test_the_layout_does_not_set_the_time(kind, density):
+@pytest.mark.parametrize("how", HOW)
+def test_the_layout_does_not_set_the_time(kind, density, how):
     """2^20 blocks of 4x4: a sample that sees one column of blocks puts the threshold outside its window and hundreds of thousands
     of blocks on the list of one workgroup, 5 to 25 times the time, and so do blocks pruned before; the bound leaves room
     for noise and wider windows."""
-    alike, this = _time_of(_scales("alike", 1024, 1024), 4, density), _time_of(_scales(kind, 1024, 1024), 4, density)
+    alike, this = [_time_of(_scales(k, 1024, 1024), 4, density, how=how) for k in ("alike", kind)]
     assert this < 2.5 * alike, (alike, this)
 
 

@@ -62,11 +62,13 @@ def test_rows_of_more_tensors_than_the_search_holds():
     _compare(neuron_prune(up(ts), 0.3, P.SCOPE_GLOBAL), oracle.neuron_prune(ts, 0.3, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, ts, "600 tensors")
 
 
-@pytest.mark.parametrize("rows", [1023, 1025, 2048, 2051])       # 1024 blocks a row of blocks: 2048 tiles of kept ids and more
-def test_kept_ids_of_many_tiles(rows):
+# 1024 blocks a row of blocks: 2048 tiles of kept ids and more; without strips, which have no tiles, and with them
+@pytest.mark.parametrize("config", [{"fused_sweep": 1}, None])
+@pytest.mark.parametrize("rows", [1023, 1025, 2048, 2051])
+def test_kept_ids_of_many_tiles(rows, config):
     rng = np.random.default_rng(rows)
     w = rng.choice(np.array([0.25, 0.5, 1.0], np.float32), (rows, 2048)) * rng.standard_normal((rows, 2048)).astype(np.float32)
-    _compare(block_prune(up([w]), 1, 2, 0.31, P.SCOPE_GLOBAL), oracle.block_prune([w], 1, 2, 0.31, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], f"rows={rows}")
+    _compare(block_prune(up([w]), 1, 2, 0.31, P.SCOPE_GLOBAL, config=config), oracle.block_prune([w], 1, 2, 0.31, P.SCOPE_GLOBAL), P.SCOPE_GLOBAL, [w], f"rows={rows}")
 
 
 @pytest.mark.parametrize("zeros", [0.5, 0.9, 0.999, 1.0])
