@@ -244,7 +244,7 @@ def time_workload(name, args, P, workloads, torch, dev, steps, warmup, resident=
     phases = P.condensa_profile_read()
     N, bpe = info["N"], info["bytes_per_elem"]
     if name == "prune_stress":
-        # one sweep (window path, default) reads the weights once: 4 + 4 theta + 1 mask; two sweeps read them twice
+        # one sweep (either window, default) reads the weights once: 4 + 4 theta + 1 mask; two sweeps read them twice
         path = P.select_records(info["result"][0]["results"])[0]["path"]
         one_sweep = path == 2 and not args.two_sweeps
         bpe = 9 if one_sweep else (13 if path == 2 else 21)
@@ -730,7 +730,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": f"L-C compression step{' with prune + binary16 (P+Q)' if pq else ''}, {T} fp32 tensors of {rows}x{cols} ({N} weights) + multipliers, "
                                f"mu={mu}, density={density}, outputs theta/lambda'/grad" + ("/theta_f16" if pq else "") + ("/mask" if args.mask else ""),
-                   "select_path": {1: "radix", 2: "window"}.get(rec["path"], str(rec["path"])),
+                   "select_path": {1: "radix", 2: "sampled window" if args.two_sweeps or args.select_path == 2 else "listed window"}.get(rec["path"], str(rec["path"])),
                    "sweeps_over_the_weights": 1 if one_sweep else (2 if rec["path"] == 2 else 4),
                    "kernel_launches_per_step": launches,
                    "threshold_key": rec["threshold_key"], "n_tie": rec["n_tie"]},

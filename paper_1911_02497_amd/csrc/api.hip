@@ -1567,9 +1567,10 @@ namespace condensa {
 
 // Lays the strips of every tensor when the call is one for them: GLOBAL scope (the layout has their regions), blocks of two dimensions and at most
 // kStripArea elements, theta apart from the weights, a threshold strictly inside the population.  b2, b3: the widest blocks there are.  Larger blocks
-// leave a strip's additions to a few threads (43 thousand of 32x32: 196 us, 130 with the aggregates first).  Every such call takes the strips: they were ahead
-// or even from 4 thousand blocks (7 thousand of 5x5 33 -> 27 us; 45 thousand of 8x8, the threshold among the highest 2 %, 36 -> 38) to 2^24; beyond, and beyond
-// 2^30 weights, nothing was measured and k_struct_fused.h or the radix levels go on.
+// leave a strip's additions to a few threads (43 thousand of 32x32: 196 us, 130 with the aggregates first).  Every such call takes the strips: they are ahead
+// from 4 thousand blocks (7 thousand of 5x5 31-36 -> 24 us; 45 thousand of 8x8, the threshold among the highest 2 %, 34-38 -> 32) to 2^24, but for thresholds at a gap
+// (k_struct_strip.h: 2^20 blocks in two scales 74 -> 82 us), which no rule on sizes tells; beyond, and beyond 2^30 weights, nothing was measured and
+// k_struct_fused.h or the radix levels go on.
 struct StripPlan { u32 n_tiles = 0, b2 = 1, b3 = 1; bool quad = true; };
 static bool strip_plan(Tables& tb, int n_tensors, const OutDesc* out, bool vec, const Slot& slot, const Layout& L, const Config& cfg, StripPlan* plan) {
     if (!L.strips || cfg[CONDENSA_OPT_FUSED_SWEEP] != 0 || n_tensors > static_cast<int>(kStripTensors) || slot.k == 0 || slot.k >= slot.n) return false;

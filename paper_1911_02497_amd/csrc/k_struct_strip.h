@@ -31,7 +31,7 @@ constexpr u32 kStripSettle = kResolveThreads * 4;          // blocks that a work
 constexpr int kStripBegin = 512;                 // threads of the launch that begins the call
 constexpr u32 kStripPer = 4;                     // loads of four elements that a thread makes for half a strip
 constexpr u32 kStripQuads = kStripPer * kStripThreads;
-constexpr u32 kStripLds = 2304;                  // elements of half a strip in LDS: sixteen workgroups to a compute unit
+constexpr u32 kStripLds = 2304;                  // elements of half a strip in LDS (sixteen workgroups would fit into a compute unit's)
 constexpr u32 kStripBlocks = 2 * kStripThreads;  // blocks of a strip at most
 constexpr u32 kStripArea = 256;                  // elements of a block at most: the chain of additions of one thread
 constexpr u32 kStripCopies = 4;                  // counters of a bin, chosen by strip
@@ -127,7 +127,8 @@ struct StripMatrix { const float* w; u32 start, d2, d3; };
 // One sampling workgroup, number `me` of W (a power of two): kStripSample ROUNDS blocks out of as many equal stretches of the population, in units of
 // four neighbours (which share lines), four lanes to a block (one lane alone made up to 32 loads of single elements, each from another line: the
 // launch took 19.7 us for 270 400 blocks of 5x5).  Bound by latency.  Their sums are added in any order and in binary32: a sample need not be exact (blocks
-// of 16x16: 10.5 us, in binary64 16.5).
+// of 16x16: 10.5 us, in binary64 16.5).  Blocks whose squares leave binary32 (weights below 1e-22 or beyond 1e19) lie outside every window, then, and the fallback
+// takes them.
 template <typename MatrixOf>
 __device__ inline void strip_sample(const ListArgs& w, u32 W, u32 me, u32 rounds, u32 b2, u32 b3, int quad, u64 F, u64 k, MatrixOf&& matrix_of) {
     __shared__ __align__(16) u32 s_key[kStripRounds * kStripSample];
@@ -265,8 +266,8 @@ typedef u32 u32_loose __attribute__((aligned(1)));
 // at any alignment, the last four of a piece of a row ending with it (some elements twice, the same values); neighbouring blocks stand an odd number of
 // words apart in LDS.
 // Bound by memory, once enough is under way: a strip takes some 15 us from its first load to its last store, so what a compute unit holds decides.  All of
-// a strip's loads are in flight at once, but only half of its rows stand in LDS at a time (the sums go on from the first half to the second): 256 KB of
-// weights to a compute unit.
+// a strip's loads are in flight at once, but only half of its rows stand in LDS at a time (the sums go on from the first half to the second).  The
+// registers (90 and 91) let ten workgroups onto a compute unit, 160 KB of weights.
 template <bool QUAD>
 __global__ __launch_bounds__(kStripThreads, 5) void k_struct_strips(StructArgs a, StripArgs s, double* sumsq, float* norms) {
     __shared__ __align__(16) float s_tile[kStripLds];
