@@ -948,7 +948,9 @@ static condensa_status begin_and_sample(const Layout& L, const Tables& tb, int n
     ListArgs w = list_args(L, ws, tb.N, L.n_slots, shape, rq, cfg);
     w.tag = next_tag();
     img->launching(st);
-    hipLaunchKernelGGL((k_begin_sample<LC, VEC>), dim3(1 + groups + b.fillers + bounds), dim3(kListThreads), sample_lds(J), st, b, w);
+    const dim3 grid(1 + groups + b.fillers + bounds);
+    if (L.l_gather_cap > kListGather) hipLaunchKernelGGL((k_begin_sample<LC, VEC, true>), grid, dim3(kListThreads), sample_lds(J), st, b, w);
+    else                              hipLaunchKernelGGL((k_begin_sample<LC, VEC, false>), grid, dim3(kListThreads), sample_lds(J), st, b, w);
     CONDENSA_LAUNCH_CHECK();
     img->commit();
     *begun = true;

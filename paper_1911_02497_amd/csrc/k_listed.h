@@ -582,7 +582,7 @@ static_assert(sizeof(BeginSampleArgs) + sizeof(ListArgs) <= 3584, "kernel argume
 // draws).  That holds for draws from something like a normal distribution.  Where they are not -- a model close to its compressed
 // form, whose threshold lies at a gap; weights on a grid; workgroups without such a rank in their sample -- the mean can lie where
 // no keys are, the interval can end before them, or a few draws far off stretch it.  So the share of the draws beyond either end
-// has to be what it is in a normal distribution, give or take three of its deviations (and not nothing).  Long lists (elsewhere a wrong decision more costs less than the test): so has the share above the mean.
+// has to be what it is in a normal distribution, give or take three of its deviations (and not nothing).  Long lists (LONG; elsewhere a wrong decision more costs less than the test): so has the share above the mean.
 // Where rows differ in size, a workgroup with many large ones has more keys around the threshold too, and the mean lies 2 to 3 of its deviations too low; the median
 // does not (1.2 G such weights, a million wrong decisions less: L-C step 4 104 -> 3 850 us, pruned 1 827 -> 1 775; 604 M 2 033 -> 1 950).  Else order
 // statistics W/2 -+ z sqrt(W)/2, which assume nothing, take its place.  Elsewhere they would leave windows 1.3 times as wide for 256
@@ -607,7 +607,7 @@ __device__ inline float wave_sum_f32(float v) {            // in every lane
     return __uint_as_float(static_cast<u32>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(v)), 63)));
 }
 // LOW: the lowest bits of the words, which say nothing (list_sample: twelve).
-template <bool WAIT, u32 LOW = 0xFFFu, typename NothingOf>
+template <bool WAIT, bool LONG, u32 LOW = 0xFFFu, typename NothingOf>
 __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0, u32 W, NothingOf&& nothing_of) {
     __shared__ ListWin s_win[kMaxJ];
     __shared__ u32 s_order[kMaxJ + 1];
@@ -696,7 +696,7 @@ __device__ inline void list_bounds(const ListArgs& w, int J, u64 r0, u32 group0,
         const u32 fewer = above < below ? above : below, more = above < below ? below : above;
         const bool even = static_cast<float>(fewer) >= n * least_beyond && static_cast<float>(more) <= n * most_beyond;
         bool skewed = false;
-        if (LOW != 0 && w.gather_cap > kListGather) {    // uniform: one GLOBAL ranking, a long list
+        if constexpr (LONG) {
             u32 over = 0;                        // above their mean
 #pragma unroll
             for (int q = 0; q < kPer; ++q) over += static_cast<u32>(__popcll(__ballot(drew[q] && static_cast<float>(static_cast<int>((v[2][q] & ~kListCrowded) - ref)) > mean[2])));
@@ -758,10 +758,13 @@ __global__ __launch_bounds__(kBoundsThreads) void k_list_bounds(DataArgs a, List
     const u64 r0 = static_cast<u64>(blockIdx.x) * a.J;
     const ListRank rk = w.rank[r0];
     if (rk.n_groups == 1) return;                // its windows are written
-    list_bounds<false>(w, a.J, r0, rk.group0, rk.n_groups, [&](u32 j) { return a.slots[r0 + j].k == 0; });
+    auto nothing_of = [&](u32 j) { return a.slots[r0 + j].k == 0; };
+    if (w.gather_cap > kListGather) list_bounds<false, true>(w, a.J, r0, rk.group0, rk.n_groups, nothing_of);       // uniform
+    else                            list_bounds<false, false>(w, a.J, r0, rk.group0, rk.n_groups, nothing_of);
 }
 
-template <bool LC, bool VEC>
+// LONG: one GLOBAL ranking, a long list.
+template <bool LC, bool VEC, bool LONG>
 __global__ __launch_bounds__(kListThreads, 8) void k_begin_sample(BeginSampleArgs b, ListArgs w) {
     __shared__ u32 s_start[kBeginSampleTensors + 1];
     const int tid = threadIdx.x;
@@ -788,7 +791,7 @@ __global__ __launch_bounds__(kListThreads, 8) void k_begin_sample(BeginSampleArg
         const u32 g = block - b.groups - b.fillers;
         const u32 group0 = b.per_tensor ? b.group0[g] : 0u, W = b.per_tensor ? b.group0[g + 1] - group0 : b.groups;
         const u64 n_pop = b.per_tensor ? b.n[g] : b.N;
-        if (W != 1) list_bounds<true>(w, b.J, static_cast<u64>(g) * b.J, group0, W, [&](u32 j) { return kept_of(static_cast<int>(j), n_pop) == 0; });
+        if (W != 1) list_bounds<true, LONG>(w, b.J, static_cast<u64>(g) * b.J, group0, W, [&](u32 j) { return kept_of(static_cast<int>(j), n_pop) == 0; });
         return;
     }
     if (tid <= b.n_tensors) s_start[tid] = b.chunk_start[tid];
@@ -3396,7 +3399,7 @@ __global__ __launch_bounds__(kSettleThreads, 4) void k_list_resolve(DataArgs a, 
 
 // The kernels that PER_TENSOR calls launch one after the other, so that they lie together in the code object: with others between them (that of long lists,
 // strips) VGG-19 per layer took 72.6 us instead of 72.1 with every instruction the same, now 72.0.
-template __global__ void k_begin_sample<false, true>(BeginSampleArgs, ListArgs);
+template __global__ void k_begin_sample<false, true, false>(BeginSampleArgs, ListArgs);
 template __global__ void k_list_sweep<false, true, 4, false>(DataArgs, ListArgs);
 template __global__ void k_list_settle<true>(DataArgs, ListArgs, condensa_select*, int, int);
 

@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kStripBegin) void k_strip_begin(StripBeginArgs b, L
     }
     const u32 block = blockIdx.x - 1;
     if (block >= b.groups + b.fillers) {                   // from what the workgroups before it leave
-        list_bounds<true, 0u>(w, 1, 0, 0, b.groups, [](u32) { return false; });
+        list_bounds<true, false, 0u>(w, 1, 0, 0, b.groups, [](u32) { return false; });
         return;
     }
     if (block < b.groups) {
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(kStripBegin) void k_strip_sample(StructArgs a, List
         return StripMatrix{td.w, static_cast<u32>(td.struct_start), td.d[2], td.d[3]};
     });
 }
-__global__ __launch_bounds__(64) void k_strip_bounds(ListArgs w, u32 groups) { list_bounds<false, 0u>(w, 1, 0, 0, groups, [](u32) { return false; }); }
+__global__ __launch_bounds__(64) void k_strip_bounds(ListArgs w, u32 groups) { list_bounds<false, false, 0u>(w, 1, 0, 0, groups, [](u32) { return false; }); }
 
 // ---- the sweep ---------------------------------------------------------------------------------------------
 
