@@ -279,6 +279,11 @@ static void prefer_window_for_two_sweeps(int op, u64 N, int n_tensors, size_t wo
     *L = W;
 }
 
+// A workspace may have room for the lists with fewer gathered entries alone (sized for several densities, which an L-C step does not have, or by hand).
+static void fewer_gathered_where_short(int op, u64 N, int n_tensors, int J, int scope, size_t workspace_bytes, const Config& cfg, Layout* L) {
+    if (L->l_gather_cap > kListGather && workspace_bytes < L->total) *L = make_layout(op, N, 0, n_tensors, J, scope, cfg, false, true);
+}
+
 // Segments of the rankings' lists: what their sweep's wavefronts call for (elements per wavefront).
 static u64 list_wave_elems(u64 N, int J, bool lc) { return 256u * static_cast<u64>(J > 1 ? list_multi_quads(N) : (lc ? kFusedQuadsLC : kFusedQuadsPrune)); }
 static u32 list_max_segs(u64 n, int n_slots, int J, bool lc) {
@@ -347,7 +352,7 @@ static StripBins strip_bins(u64 F) {
     return b;
 }
 
-Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const Config& cfg, bool no_window) {
+Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const Config& cfg, bool no_window, bool few_gathered) {
     Layout L;
     const bool per_tensor = (scope == CONDENSA_SCOPE_PER_TENSOR);
     const bool structure = (op == CONDENSA_OP_FILTER_PRUNE || op == CONDENSA_OP_BLOCK_PRUNE);
@@ -382,7 +387,7 @@ Layout make_layout(int op, u64 N, u64 F, int n_tensors, int J, int scope, const 
         L.l_gmax = off;    off += align_up(2 * static_cast<size_t>(L.n_slots) * sizeof(u32));
         L.l_masks = off;   off += align_up(3 * static_cast<size_t>(L.n_groups) * sizeof(u32));
         L.l_meet = off;    off += align_up(kMeetWords * sizeof(u32));
-        const u32 gather = long_list && !per_tensor ? kListGatherLong : kListGather;
+        const u32 gather = long_list && !per_tensor && !few_gathered ? kListGatherLong : kListGather;
         L.l_gather_cap = (1u << 20) / L.n_slots > gather ? gather : ((1u << 20) / L.n_slots < kListRanked ? kListRanked : (1u << 20) / L.n_slots);
         L.l_gkey = off;
         L.l_posted = long_list ? L.l_gkey : L.l_post + 256;
@@ -1137,6 +1142,7 @@ static condensa_status prune_impl(const condensa_tensor* tensors, int n_tensors,
     }
     if (J == 1 && !per_tensor && (!any_out || in_place_any || cfg[CONDENSA_OPT_FUSED_SWEEP] != 0))
         prefer_window_for_two_sweeps(CONDENSA_OP_PRUNE, tb.N, n_tensors, workspace_bytes, &cfg, &L);
+    fewer_gathered_where_short(CONDENSA_OP_PRUNE, tb.N, n_tensors, J, scope, workspace_bytes, cfg, &L);
     ranges[n_ranges++] = byte_range(workspace_dev, workspace_bytes < L.total ? workspace_bytes : L.total, true);
     ranges[n_ranges++] = byte_range(results_dev, static_cast<u64>(L.n_slots) * sizeof(condensa_select), true);
     if (ranges_conflict(ranges, n_ranges)) return CONDENSA_ERR_ARG;
@@ -1374,6 +1380,7 @@ static condensa_status lc_step_impl(bool pq, const condensa_tensor* tensors, int
         if (o.theta16 && (reinterpret_cast<uintptr_t>(o.theta16) & 7u)) vec = false;
     }
     if (in_place_any || cfg[CONDENSA_OPT_FUSED_SWEEP] != 0) prefer_window_for_two_sweeps(CONDENSA_OP_LC_STEP, tb.N, n_tensors, workspace_bytes, &cfg, &L);
+    fewer_gathered_where_short(CONDENSA_OP_LC_STEP, tb.N, n_tensors, 1, CONDENSA_SCOPE_GLOBAL, workspace_bytes, cfg, &L);
     ranges.push_back(byte_range(workspace_dev, workspace_bytes < L.total ? workspace_bytes : L.total, true));
     ranges.push_back(byte_range(result_dev, sizeof(condensa_select), true));
     ranges.push_back(byte_range(nnz_dev, sizeof(uint64_t), true));

@@ -175,6 +175,6 @@ struct Layout {
 };
 
 Layout make_layout(int op, u64 total_elems, u64 n_structures, int n_tensors, int n_densities, int scope,
-                   const Config& cfg, bool no_window = false);
+                   const Config& cfg, bool no_window = false, bool few_gathered = false);
 
 }  // namespace condensa

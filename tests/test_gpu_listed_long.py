@@ -144,6 +144,27 @@ def test_values_on_a_floating_point_grid(n, digits):
 
 
 @pytest.mark.timeout(300)
+def test_workspaces_with_room_for_fewer_gathered_entries():
+    n = (3 << 26) + 7
+    ws = _weights("normal", n)
+    for t in ws:
+        t.view(torch.int32).add_(1 << 14).bitwise_and_(-1 << 15)         # 260 thousand ties
+    lam = [t * 0.0 for t in ws]
+    ref = P.condensa_lc_step(ws, lam, 1e-3, 0.1, config={"select_path": 1})
+    want = P.select_records(ref["results"])[0]
+    assert want["n_tie"] > 1 << 17
+    full = P.condensa_workspace_bytes(OP_LC_STEP, n, 0, 2, 4, P.SCOPE_GLOBAL)            # (four densities: the lists alone)
+    for size in (full, full - 256, full - 6 * (1 << 20)):
+        res = P.condensa_lc_step(ws, lam, 1e-3, 0.1, workspace=torch.empty(size, dtype=torch.uint8, device=DEV))
+        got = P.select_records(res["results"])[0]
+        assert all(got[f] == want[f] for f in FIELDS), (size, got, want)
+        for name in ("theta", "lambda", "grad", "mask"):
+            assert all(_same(a, b) for a, b in zip(res[name], ref[name])), (size, name)
+    with pytest.raises(P.CondensaError):
+        P.condensa_lc_step(ws, lam, 1e-3, 0.1, workspace=torch.empty(full - 7 * (1 << 20), dtype=torch.uint8, device=DEV))
+
+
+@pytest.mark.timeout(300)
 def test_ties_do_not_set_the_time():
     """Counted by another sweep over weights and multipliers they took 1.5 times the step of other weights (1.04 times counted where they lie gathered)."""
     g = torch.Generator(device=DEV).manual_seed(5)
